@@ -147,6 +147,17 @@ def _weights(shape, gen):
             yield name, normal(dims, 0.02)
 
 
+def _normal(dims, dt, gen, std=1.0):
+    return torch.empty(dims, dtype=dt, device="cuda").normal_(0.0, std, generator=gen)
+
+
+def _loss_inputs(case, dt, gen):
+    rows, d = case["rows"], case["d"]
+    ft = _normal((rows, d), dt, gen)
+    fd = ft + _normal((rows, d), dt, gen, 0.5)                 # a draft's estimate of the feature
+    return ft, fd, _normal((case["vocab"], d), dt, gen, 3.0 / math.sqrt(d))
+
+
 def prepare(case, seed):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     if case["kind"] == "request":
@@ -163,7 +174,7 @@ def prepare(case, seed):
                 "seed": seed & 0xFFFF}
 
     def normal(dims, dt, std=1.0):
-        return torch.empty(dims, dtype=dt, device="cuda").normal_(0.0, std, generator=gen)
+        return _normal(dims, dt, gen, std)
     if case["kind"] == "hca":
         q = normal((case["batch"], case["seq"], case["hq"], case["hd"]), torch.bfloat16)
         kv = (case["batch"], case["seq"], case["hkv"], case["hd"])
@@ -173,11 +184,9 @@ def prepare(case, seed):
         vs = [v0] + [v0 + normal(kv, torch.bfloat16, 0.3 * m) for m in range(1, case["streams"])]
         return {"kind": "hca", "q": q, "ks": ks, "vs": vs}
     dt = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
-    rows, d, vocab = case["rows"], case["d"], case["vocab"]
-    ft = normal((rows, d), dt)
-    fd = ft + normal((rows, d), dt, 0.5)                       # a draft's estimate of the feature
-    head = P.spec_pack_weight(normal((vocab, d), dt, 3.0 / math.sqrt(d)))
-    scratch = torch.empty(P.spec_topk_loss_scratch_bytes(rows, vocab, case["k"]), dtype=torch.uint8, device="cuda")
+    ft, fd, head = _loss_inputs(case, dt, gen)
+    head = P.spec_pack_weight(head)
+    scratch = torch.empty(P.spec_topk_loss_scratch_bytes(case["rows"], case["vocab"], case["k"]), dtype=torch.uint8, device="cuda")
     return {"kind": "loss", "ft": ft, "fd": fd, "head": head, "k": case["k"], "scratch": scratch}
 
 
@@ -254,3 +263,110 @@ def tolerance(case):
     if wl.BY_NAME[case["model"]].dtype == "bf16":
         return {"rel": 0.015, "max": 0.07}                     # measured 0.003 .. 0.004, 0.012 .. 0.018
     return {"rel": 2e-5, "max": 2e-4}
+
+
+def _exact_request(case, seed):
+    """The greedy target model over prompt and answer in 64 bits, one causal forward.  The answer is found by guess and
+    correction: the guess walks the cycle that the weights were made around, a wrong token is replaced from the forward's
+    logits.  As in work(), every cycle is taken to emit the tree's longest path (otherwise the outputs have other sizes)."""
+    shape = _shape(case)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    w = dict(_weights(shape, gen))
+    prompt = torch.randint(0, shape.vocab, (case["prompt"],), generator=gen, device="cuda")
+    gen.manual_seed(seed)                                      # the draws of _weights up to the cycle
+    torch.empty_like(w["embed"]).normal_(0.0, 1.0, generator=gen)
+    cycle = torch.randperm(shape.vocab, device="cuda", generator=gen)
+    after = torch.empty_like(cycle)
+    after[cycle.roll(1)] = cycle
+    step = 1 if case["total"] == 1 else 1 + (int(case["static"][5:]) if case["static"].startswith("chain") else case["depth"])
+    count = 1 + -(-(case["gen"] - 1) // step) * step
+    answer = [after[prompt[-1]]]
+    while len(answer) < count:
+        answer.append(after[answer[-1]])
+    answer = torch.stack(answer)
+    n, hq, hkv, hd = case["prompt"], shape.n_q_heads, shape.n_kv_heads, shape.head_dim
+
+    def norm(h, weight):
+        return h / torch.sqrt((h * h).mean(-1, keepdim=True) + shape.rms_eps) * weight.double()
+
+    def linear(x, name):
+        return x @ w[name].double().t()
+
+    def turn(x, angle):
+        a, b = x[..., :hd // 2], x[..., hd // 2:]
+        c, s = torch.cos(angle)[:, None], torch.sin(angle)[:, None]
+        return torch.cat([a * c - b * s, b * c + a * s], -1)
+
+    def forward(tokens):
+        t = tokens.numel()
+        angle = torch.arange(t, device="cuda").double()[:, None] * shape.rope_theta ** (
+            -2.0 * torch.arange(hd // 2, device="cuda").double() / hd)
+        hidden = torch.ones(t, t, dtype=torch.bool, device="cuda").triu(1)
+        h = w["embed"][tokens].double()
+        for l in range(shape.n_layers):
+            p = "layers.%d." % l
+            a = norm(h, w[p + "attn_norm"])
+            q = turn(linear(a, p + "wq").view(t, hq, hd), angle)
+            k = turn(linear(a, p + "wk").view(t, hkv, hd), angle)
+            v = linear(a, p + "wv").view(t, hkv, hd)
+            o = torch.empty(t, hq, hd, dtype=torch.float64, device="cuda")
+            for i in range(hq):
+                kv = i * hkv // hq
+                score = (q[:, i] @ k[:, kv].t()).mul_(hd ** -0.5).masked_fill_(hidden, -math.inf)
+                o[:, i] = torch.softmax(score, -1) @ v[:, kv]
+            h = h + linear(o.view(t, hq * hd), p + "wo")
+            b = norm(h, w[p + "ffn_norm"])
+            h = h + linear(torch.nn.functional.silu(linear(b, p + "w_gate")) * linear(b, p + "w_up"), p + "w_down")
+        return linear(norm(h[n - 1:], w["final_norm"]), "lm_head")
+    for _ in range(4):
+        logits = forward(torch.cat([prompt, answer[:-1]]))
+        found = logits.argmax(-1)
+        if bool((found == answer).all()):
+            return {"tokens": answer.cpu().numpy().astype(np.int32), "logits": logits[count - step:].cpu().numpy()}
+        answer = found
+    return None
+
+
+def _exact_hca(s):
+    q, j = s["q"].double(), len(s["ks"])
+    batch, t, hq, hd = q.shape
+    ks, vs = [k.double() for k in s["ks"]], [v.double() for v in s["vs"]]
+    off = torch.arange(t, device="cuda")[:, None] - torch.arange(t, device="cuda")[None]
+    out = torch.empty_like(q)
+    for b in range(batch):
+        for i in range(hq):
+            kv = i * ks[0].shape[2] // hq
+            # the key of position t - o is stream j-1-o's for o <= j-2, stream 0's beyond
+            score = q[b, :, i] @ ks[0][b, :, kv].t()
+            for o in range(j - 1):
+                score = torch.where(off == o, q[b, :, i] @ ks[j - 1 - o][b, :, kv].t(), score)
+            p = torch.softmax((score * hd ** -0.5).masked_fill_(off < 0, -math.inf), -1)
+            got = p.masked_fill(off < j - 1, 0.0) @ vs[0][b, :, kv]
+            for o in range(j - 1):
+                got += torch.where(off == o, p, 0.0) @ vs[j - 1 - o][b, :, kv]
+            out[b, :, i] = got
+    return out
+
+
+def _exact_loss(case, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    dt = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
+    ft, fd, head = _loss_inputs(case, dt, gen)
+    topk, ce = [], []
+    for r in range(0, case["rows"], 256):
+        zq, zp = ft[r:r + 256].double() @ head.double().t(), fd[r:r + 256].double() @ head.double().t()
+        q, logp = torch.softmax(zq, -1), torch.log_softmax(zp, -1)
+        best = zq.topk(case["k"], -1).indices
+        topk.append(-(q.gather(1, best) * logp.gather(1, best)).sum(-1))
+        ce.append(-(q * logp).sum(-1))
+    topk, ce = torch.cat(topk), torch.cat(ce)
+    return topk, ce, torch.stack([topk.sum(), ce.sum()])
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits by plain torch; sampled requests have no such value."""
+    if case["kind"] == "hca":
+        return _exact_hca(prepare(case, seed))
+    if case["kind"] == "loss":
+        return _exact_loss(case, seed)
+    return _exact_request(case, seed) if case["temperature"] == 0 else None
