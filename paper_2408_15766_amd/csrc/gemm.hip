@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
   // SwiGLU mode streams the one gate/up matrix (see pack_gate_up_kernel): a block holds 16 gate rows in the lanes
   // c < 16 and the up rows of the same 16 columns in the lanes c >= 16; seg_rows[0] is the number of columns.
   const int bx = blockIdx.x, by = blockIdx.y, mt = 0;
-  const int m_loc = a.m;                                       // (more than 128 rows go to gemm_tiled_kernel)
+  const int m_loc = a.m;                                       // (more than 128 rows: gemm_mm_kernel, gemm_tiled_kernel)
   const bool swiglu = a.act != nullptr;
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
   const int blk_raw = bx * a.blk_per_wg + wave * a.blk_per_wave;   // four adjacent blocks, or strided over more workgroups: see launch_t
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
     }
 }
 
-// ---- more than 128 token rows (prefill) -------------------------------------------------------
+// ---- more than 128 token rows, fp32 -------------------------------------------------------
 // The same contraction when X has several 128-row tiles.  One launch covers all tiles; a workgroup owns
 // (256 weight rows, one K split, one tile).  Here the matrix cores are the limit, and with one weight block
 // per wave every MFMA would need its own token fragment from LDS (LDS bandwidth runs out first), so a wave
@@ -436,6 +436,212 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_tiled_kernel(GemmArgs a)
   }
 }
 
+// ---- more than 128 token rows, bf16 (prefill, LM head of the loss) ------------------------------
+// Here the matrix cores are the limit, and what holds them up is the arrival of operands.  A workgroup of eight wavefronts
+// (two per SIMD, so that one's products cover the other's waits) owns TW*TB 32-token blocks x (8/TW)*WB 32-row weight blocks
+// for one K split; a wavefront owns TB x WB of them.  Both operands are copied straight into the LDS, 64 k at a time (half a
+// packed tile): X two stages deep (it sits in L2), the weights three (their first touch comes from HBM: two stages are about
+// 2 us of cover).  One barrier per stage, placed before the stage's last step: by then every fragment of the stage is in
+// registers, so the copies of later stages may overwrite it, and the next stage's first fragments are read while the last
+// step's products run.  Each stage buffer is an array of its own: the compiler then knows which copies a read depends on and
+// adds no waits to the two written below.  The sums of a row run in the order of gemm_stream_kernel's (k ascending in
+// one accumulator).
+// Measured (MI355X, us; before = 128 x 256 tiles with the weights streamed through registers): 512 x 12288 x 4096 with 2 splits
+// 86 -> 55, 512 x 32000 x 4096 161 -> 129, 4096 x 28672 x 4096 1113 -> 824, 4096 x 4096 x 14336 492 -> 373 (1.27 PFLOP/s; the clock drops to
+// about 1.8 GHz under this load, the matrix cores are busy three quarters of the time).
+template <int TW, int TB, int WB>
+struct MmTile {
+  static constexpr int kTok = TW * TB * 32;                   // tokens per workgroup
+  static constexpr int kBlocks = 8 / TW * WB;                 // 32-row weight blocks per workgroup
+  static constexpr int kX = kTok * 128, kW = kBlocks * 4096;  // bytes of one stage
+  static constexpr int kXLoads = kX / 8192, kWLoads = kW / 8192;   // 1 KB copies per wave and stage
+};
+constexpr int kMmThreads = 512;
+
+typedef __attribute__((address_space(3))) void lds_void;
+// 16 bytes per lane from base + voff (lane) + soff (wave-uniform) straight into the LDS, to dst + 16 * lane; dst is wave-uniform
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base) {
+  return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7FFFFFFF, 0x00027000);
+}
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t base, int voff, int soff, void *dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(base, (lds_void *)dst, 16, voff, soff, 0, 0);
+}
+
+// Workgroup barrier that waits for nothing else (__syncthreads would also wait for every copy into the LDS under way)
+__device__ __forceinline__ void wg_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <int TW, int TB, int WB>
+__global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
+  using L = MmTile<TW, TB, WB>;
+  constexpr int XI = L::kXLoads, WI = L::kWLoads;
+  __shared__ __attribute__((aligned(1024))) unsigned char xs0[L::kX], xs1[L::kX], ws0[L::kW], ws1[L::kW], ws2[L::kW];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 31, g = lane >> 5;
+  const int per = 8 * a.m_tiles;
+  const int q = ((int)blockIdx.x / per) * 8 + ((int)blockIdx.x % 8);
+  const int mt = ((int)blockIdx.x % per) / 8;
+  if (q >= a.grid_x * a.n_split) return;
+  const int bx = q % a.grid_x, by = q / a.grid_x;
+  const int m0 = mt * L::kTok, m_loc = min(a.m - m0, L::kTok);
+
+  const bool swiglu = a.act != nullptr;
+  const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
+  const int n_it_total = (a.in + 127) / 128;
+  const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
+  const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
+  const int it_end = min(n_it_total, (int)((long long)(by + 1) * n_slabs_total / a.n_split) * kSlabIters);
+  const int n_stage = 2 * (it_end - it_begin);
+
+  auto block_seg = [&](int blk, int &b0) { const int s = blk < e0 ? 0 : (blk < e1 ? 1 : 2); b0 = s == 0 ? 0 : (s == 1 ? e0 : e1); return s; };
+  // the 1 KB pieces of the weight blocks that this wave copies
+  __amdgpu_buffer_rsrc_t wsrc[WI];
+#pragma unroll
+  for (int i = 0; i < WI; i++) {
+    const int blk = min(bx * L::kBlocks + (wave * WI + i) / 4, a.total_blocks - 1);
+    int b0;
+    const int seg = block_seg(blk, b0);
+    const void *w = seg == 0 ? a.seg_w[0] : (seg == 1 ? a.seg_w[1] : a.seg_w[2]);
+    wsrc[i] = buffer_of((const char *)w + ((size_t)(blk - b0) * n_it_total + it_begin) * (size_t)kTileBytes + (wave * WI + i) % 4 * 1024);
+  }
+  // the X rows this wave copies: row segment rs = (t * 2 + g) * 32 + c holds the 64 bytes (32 k) of half g, its four 16-byte
+  // pieces rotated by the row so that the fragment reads of eight consecutive rows touch all banks
+  const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const char *)a.x + (size_t)m0 * a.ldx * 2);
+  uint32_t xoff[XI];
+  int xk[XI];
+#pragma unroll
+  for (int i = 0; i < XI; i++) {
+    const int rs = (wave * XI + i) * 16 + (lane >> 2);
+    const int rc = rs & 31, rg = (rs >> 5) & 1, row = (rs >> 6) * 32 + rc;
+    const int piece = (lane & 3) ^ ((rc >> 2) & 3);
+    xk[i] = it_begin * 128 + rg * 64 + piece * 8;
+    xoff[i] = (uint32_t)(row < m_loc ? row : 0) * (uint32_t)a.ldx * 2u;
+  }
+  auto load_w = [&](unsigned char *buf, int s, int i0, int i1) {
+    s = min(s, n_stage - 1);                                  // past the end: the last stage again (never read)
+#pragma unroll
+    for (int i = i0; i < i1; i++) load_to_lds(wsrc[i], lane * 16, s * (kTileBytes / 2), buf + (wave * WI + i) * 1024);
+  };
+  auto load_x = [&](unsigned char *buf, int s) {
+    s = min(s, n_stage - 1);
+    const int ks = (s >> 1) * 128 + (s & 1) * 32;
+#pragma unroll
+    for (int i = 0; i < XI; i++) {
+      const int k = xk[i] + ks;
+      load_to_lds(xsrc, (int)(xoff[i] + (uint32_t)(k < a.in ? k : 0) * 2u), 0, buf + (wave * XI + i) * 1024);
+    }
+  };
+
+  f32x16_t acc[WB][TB];
+#pragma unroll
+  for (int wb = 0; wb < WB; wb++)
+#pragma unroll
+    for (int t = 0; t < TB; t++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[wb][t][v] = 0.f;
+
+  const int th = wave & (TW - 1), wq = wave / TW;
+  const int xbase = th * TB * 4096 + (g * 32 + c) * 64, xsw = (c >> 2) & 3;
+  const int wbase = wq * WB * 4096 + lane * 16;
+  struct Frag { u32x4_t x[TB], w[WB]; };
+  auto read = [&](Frag &f, const unsigned char *xb, const unsigned char *wb, int j) {
+#pragma unroll
+    for (int b = 0; b < WB; b++) f.w[b] = *(const u32x4_t *)(wb + wbase + b * 4096 + j * 1024);
+#pragma unroll
+    for (int t = 0; t < TB; t++) f.x[t] = *(const u32x4_t *)(xb + xbase + t * 4096 + ((j ^ xsw) * 16));
+  };
+  auto mul = [&](const Frag &f) {
+#pragma unroll
+    for (int wb = 0; wb < WB; wb++)
+#pragma unroll
+      for (int t = 0; t < TB; t++) mfma_step(acc[wb][t], f.x[t], f.w[wb], bf16_t{});
+  };
+  Frag f[2];
+  auto stage = [&](unsigned char *xc, unsigned char *wc, unsigned char *xn, unsigned char *wn, unsigned char *wp, int s) {
+    // on entry f[0] = the fragments of step 0
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+      read(f[(j + 1) & 1], xc, wc, j + 1);
+      if (j == 0) load_w(wp, s + 2, 0, WI / 2);                // the copies spread over the steps
+      if (j == 1) load_w(wp, s + 2, WI / 2, WI);
+      __builtin_amdgcn_sched_barrier(0);                      // the reads ahead of the products that hide them
+      mul(f[j & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // every fragment of this stage is in registers, and this wave's share of the next one has arrived (only the W loads of the
+    // stage after it may still be under way)
+    __builtin_amdgcn_s_waitcnt(0x0070 | WI);                  // vmcnt(WI) lgkmcnt(0)
+    wg_barrier();
+    read(f[0], xn, wn, 0);
+    load_x(xc, s + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(f[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  load_w(ws0, 0, 0, WI);
+  load_x(xs0, 0);
+  load_w(ws1, 1, 0, WI);
+  load_x(xs1, 1);
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (WI + XI));             // stage 0 here
+  wg_barrier();
+  read(f[0], xs0, ws0, 0);
+  int s = 0;
+  for (; s + 6 <= n_stage; s += 6) {
+    stage(xs0, ws0, xs1, ws1, ws2, s);
+    stage(xs1, ws1, xs0, ws2, ws0, s + 1);
+    stage(xs0, ws2, xs1, ws0, ws1, s + 2);
+    stage(xs1, ws0, xs0, ws1, ws2, s + 3);
+    stage(xs0, ws1, xs1, ws2, ws0, s + 4);
+    stage(xs1, ws2, xs0, ws0, ws1, s + 5);
+  }
+  if (s < n_stage) {                                          // two or four stages are left: a K range is whole 128-k tiles
+    stage(xs0, ws0, xs1, ws1, ws2, s);
+    stage(xs1, ws1, xs0, ws2, ws0, s + 1);
+    if (s + 2 < n_stage) {
+      stage(xs0, ws2, xs1, ws0, ws1, s + 2);
+      stage(xs1, ws0, xs0, ws1, ws2, s + 3);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);                         // no copy into the LDS outlives the workgroup
+
+#pragma unroll
+  for (int wb = 0; wb < WB; wb++) {
+    const int blk = bx * L::kBlocks + wq * WB + wb;
+    if (blk >= a.total_blocks) continue;
+    if (swiglu) {
+      const int f_ = a.seg_rows[0], col = blk * 16 + (c & 15);
+#pragma unroll
+      for (int t = 0; t < TB; t++) {                          // one token block at a time: the exchange needs registers of its own
+        const int i0 = (th * TB + t) * 32;
+        const f32x16_t one[1] = {acc[wb][t]};
+        swiglu_epilogue<bf16_t, 1>(one, (bf16_t *)a.act + (size_t)(m0 + i0) * f_ + col, f_, col, col < f_, m_loc - i0, c, g);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      continue;
+    }
+    int b0;
+    const int seg = block_seg(blk, b0);
+    const int rows = seg == 0 ? a.seg_rows[0] : (seg == 1 ? a.seg_rows[1] : a.seg_rows[2]);
+    const int col0 = seg == 0 ? a.seg_col0[0] : (seg == 1 ? a.seg_col0[1] : a.seg_col0[2]);
+    const int row = (blk - b0) * 32 + c;
+    if (row >= rows) continue;
+    float *out = a.part + ((size_t)by * a.m_pad + m0 + th * TB * 32) * a.ldp;
+    const uint32_t o0 = (uint32_t)(col0 + row);
+#pragma unroll
+    for (int t = 0; t < TB; t++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        const int i = t * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+        if (th * TB * 32 + i < m_loc) out[o0 + (uint32_t)i * (uint32_t)a.ldp] = acc[wb][t][v];
+      }
+  }
+}
+
 // ---- packing ---------------------------------------------------------------------------------
 // One thread moves one 16-byte piece: dst piece index p = ((rb * n_it + it) * 8 + j) * 64 + lane.
 template <typename T>
@@ -527,8 +733,8 @@ static hipError_t init_t() {
     hipError_t e = hipFuncSetAttribute(fn[tb - 1], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  return hipFuncSetAttribute((const void *)gemm_tiled_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             2 * 4 * 32 * kSlabStride);
+  if constexpr (sizeof(T) == 2) return hipSuccess;
+  else return hipFuncSetAttribute((const void *)gemm_tiled_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 4 * 32 * kSlabStride);
 }
 hipError_t gemm_init() {
   // kernel attributes belong to the device's copy of the code: once per device, for the current device
@@ -541,6 +747,39 @@ hipError_t gemm_init() {
   if (e == hipSuccess) e = init_t<float>();
   if (dev >= 0 && dev < 64) done[dev] = e == hipSuccess;
   return e;
+}
+
+template <int TW, int TB, int WB>
+static hipError_t launch_mm_tile(GemmArgs a, hipStream_t st) {
+  using L = MmTile<TW, TB, WB>;
+  a.m_tiles = (a.m + L::kTok - 1) / L::kTok;
+  a.grid_x = (a.total_blocks + L::kBlocks - 1) / L::kBlocks;
+  const dim3 grid((a.grid_x * a.n_split + 7) / 8 * 8 * a.m_tiles, 1);
+  hipLaunchKernelGGL((gemm_mm_kernel<TW, TB, WB>), grid, dim3(kMmThreads), 0, st, a);
+  return hipGetLastError();
+}
+// A compute unit holds one workgroup, so a launch lasts as many rounds as its workgroups fill the 256 compute units.  A round
+// of 256 x 256, 256 x 192 and 128 x 256 tiles (tokens x weight rows) takes 118, 94 and 70 us at K = 4096, i.e. 100 : 80 : 60;
+// the tile with the smallest product is taken, the larger one on a tie (it moves fewer bytes per product).  512 rows at the 7B
+// shape: QKV (2 splits) 55 us with 256 x 192 against 59 and 77, gate/up 98 against 108 and 138, O (4 splits) 29 us with
+// 128 x 256 against 38 and 34, LM head 129 us with 256 x 256 against 170 and 150.
+static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
+  auto cost = [&](int tok, int blocks, int per_round) {
+    const long long wgs = (long long)((a.m + tok - 1) / tok) * ((a.total_blocks + blocks - 1) / blocks) * a.n_split;
+    return (wgs + 255) / 256 * per_round;
+  };
+  const long long c256 = cost(256, 8, 100), c192 = cost(256, 6, 80), c128 = cost(128, 8, 60);
+  if (c256 <= c192 && c256 <= c128) return launch_mm_tile<2, 4, 2>(a, st);
+  if (c192 <= c128) return launch_mm_tile<4, 2, 3>(a, st);
+  return launch_mm_tile<2, 2, 2>(a, st);
+}
+
+// Copies into the LDS need 16-byte aligned sources, and the kernel's offsets inside a tile are 32-bit.
+static bool mm_takes(const GemmArgs &a) {
+  uintptr_t low = (uintptr_t)a.x | (uintptr_t)a.seg_w[0];
+  if (a.nseg > 1) low |= (uintptr_t)a.seg_w[1];
+  if (a.nseg > 2) low |= (uintptr_t)a.seg_w[2];
+  return (low & 15) == 0 && a.ldx % 8 == 0 && a.ldx >= 0 && a.ldx < (1 << 22) && a.in < (1 << 22) && a.ldp < (1 << 24);
 }
 
 template <typename T>
@@ -568,11 +807,26 @@ static hipError_t launch_t(GemmArgs a, hipStream_t st) {
   // SwiGLU mode: the one gate/up matrix, 16 columns per block, whole K (the activation is not linear)
   if (a.act != nullptr && (a.nseg != 1 || a.n_split != 1 || a.seg_blocks[0] != (a.seg_rows[0] + 15) / 16)) return hipErrorInvalidValue;
   dim3 grid(a.grid_x, a.n_split);
-  if (a.m_tiles > 1) {                                         // two blocks per wave; see gemm_tiled_kernel's id decoding
-    a.grid_x = (a.total_blocks + 2 * kGemmWaves - 1) / (2 * kGemmWaves);
-    const dim3 tgrid((a.grid_x * a.n_split + 7) / 8 * 8 * a.m_tiles, 1);
-    hipLaunchKernelGGL((gemm_tiled_kernel<T>), tgrid, dim3(kGemmThreads), (size_t)2 * 4 * 32 * kSlabStride, st, a);
-    return hipGetLastError();
+  if (a.m_tiles > 1) {
+    if constexpr (sizeof(T) == 2) {
+      if (mm_takes(a)) return launch_mm(a, st);
+      for (int m0 = 0; m0 < a.m; m0 += 128) {                  // any alignment: 128 rows at a time through the streaming kernel
+        GemmArgs t = a;
+        t.m = std::min(128, a.m - m0);
+        t.x = (const char *)a.x + (ptrdiff_t)m0 * a.ldx * (ptrdiff_t)sizeof(T);
+        if (a.act) t.act = (char *)a.act + (size_t)m0 * a.seg_rows[0] * sizeof(T);
+        else t.part = a.part + (size_t)m0 * a.ldp;
+        const hipError_t e = launch_t<T>(t, st);
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
+    } else {
+      // two blocks per wave; see gemm_tiled_kernel's id decoding
+      a.grid_x = (a.total_blocks + 2 * kGemmWaves - 1) / (2 * kGemmWaves);
+      const dim3 tgrid((a.grid_x * a.n_split + 7) / 8 * 8 * a.m_tiles, 1);
+      hipLaunchKernelGGL((gemm_tiled_kernel<T>), tgrid, dim3(kGemmThreads), (size_t)2 * 4 * 32 * kSlabStride, st, a);
+      return hipGetLastError();
+    }
   }
   const size_t lds = (size_t)2 * tb * 32 * kSlabStride;
   if (lds > 160 * 1024) return hipErrorInvalidValue;

@@ -152,6 +152,29 @@ def test_gemm_row_is_independent_of_batch(env):
     assert torch.equal(ten, full[:, 5:15])
 
 
+@pytest.mark.parametrize("m,k,rows,n_split", [(129, 8, [31], 1), (129, 136, [32], 1), (255, 256, [225, 64, 40], 1), (257, 904, [520], 2),
+                                              (512, 2056, [4096, 32, 64], 4), (640, 1096, [12290], 2), (1025, 384, [8192], 1)])
+def test_gemm_many_rows_matches_fp64(env, m, k, rows, n_split):
+    """More than 128 bf16 rows: every tile shape of that launch (128 x 256, 256 x 192, 256 x 256), one row or one weight block
+    past a tile, segments that meet inside a tile, K of less than one stage, of 2 / 4 / 6n stages and ragged, K splits; the
+    same call on an X that is not 16-byte aligned takes the other path.  fp32 sums of k terms of size 0.05: relative error of
+    the whole far below 1e-6 * sqrt(k)."""
+    torch, P = env
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed(m, k) & 0xFFFF)
+    flat = torch.randn(m * k + 8, device="cuda", generator=g).to(torch.bfloat16)
+    ws = [(torch.randn(r, k, device="cuda", generator=g) * 0.05).to(torch.bfloat16) for r in rows]
+    for off in (0, 4):
+        x = flat[off:off + m * k].view(m, k)
+        got = P.spec_k_gemm(x, ws, n_split)
+        want = x.double() @ torch.cat(ws).double().t()
+        err = got.double().sum(0) - want
+        assert err.abs().max() <= 1e-6 * np.sqrt(k) * max(1.0, float(want.abs().max()))
+        act = P.spec_k_gemm_swiglu(x, ws[0], ws[0].flip(0)).double()
+        gate, up = want[:, :rows[0]], want[:, :rows[0]].flip(1)
+        ref = gate * torch.sigmoid(gate) * up
+        assert ((act - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * np.sqrt(k)).all()
+
+
 def make_tree(rng, rows, max_depth):
     par = np.full(rows, -1, np.int32)
     dep = np.zeros(rows, np.int32)
