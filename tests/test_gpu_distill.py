@@ -120,6 +120,22 @@ def test_all_equal_target_logits(env):
         check(got_topk, got_ce, want, want if k < 9000 else alt, want_ce)
 
 
+@pytest.mark.parametrize("vocab,k", [(4096, 1), (4100, 64), (9000, 65), (9000, 100), (33000, 124), (131072, 128)])
+def test_large_logits_next_to_each_other(env, vocab, k):
+    # target logits that fall with the token id: the largest sit in neighbouring registers of few threads, so that far more
+    # than k of them pass a bound made from one value per thread; a row of scattered logits and a rising one beside it
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(27, 3, 128, vocab, "fp32")
+    w[:, 0] = np.linspace(4.0, -4.0, vocab, dtype=np.float32)
+    ft[0] = 0.0
+    ft[0, 0] = 1.0
+    ft[2] = 0.0
+    ft[2, 0] = -1.0
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, k, "fp32")
+    want, alt, want_ce = oracle_losses(ft, fd, w, k)
+    check(got_topk, got_ce, want, alt, want_ce)
+
+
 def test_topk_loss_full_size_sampled_rows(env):
     # the benchmark's launch: 4096 positions (batch 2 x 2048), LLaMA2-7B widths; the oracle takes 24 sampled rows
     torch, P = env
