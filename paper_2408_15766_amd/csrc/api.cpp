@@ -1190,15 +1190,13 @@ int spec_topk_loss(int32_t dtype, const void *feat_target, const void *feat_draf
     const int m = rows - r0 < l.chunk ? rows - r0 : l.chunk;
     const void *xs[2] = {(const char *)feat_target + (size_t)r0 * d * esz, (const char *)feat_draft + (size_t)r0 * d * esz};
     float *zs[2] = {sf + l.zq, sf + l.zp};
-    for (int side = 0; side < 2; side++) {                    // the LM head over the chunk's rows: fp32 logits
-      GemmArgs a{};
-      a.x = xs[side]; a.ldx = d; a.m = m; a.in = d;
-      for (int s = 0; s < 3; s++) { a.seg_w[s] = lm_head; a.seg_rows[s] = 0; a.seg_blocks[s] = 0; a.seg_col0[s] = 0; }
-      a.seg_rows[0] = vocab; a.seg_blocks[0] = (vocab + 31) / 32;
-      a.nseg = 1; a.total_blocks = a.seg_blocks[0];
-      a.part = zs[side]; a.ldp = l.ldz; a.m_pad = l.chunk; a.n_split = 1;
-      if (launch_gemm(dtype, a, st) != hipSuccess) return SPEC_EHIP;
-    }
+    GemmArgs a{};                                             // the LM head over both sides' rows: fp32 logits
+    a.x = xs[0]; a.x2 = xs[1]; a.ldx = d; a.m = m; a.in = d;
+    for (int s = 0; s < 3; s++) { a.seg_w[s] = lm_head; a.seg_rows[s] = 0; a.seg_blocks[s] = 0; a.seg_col0[s] = 0; }
+    a.seg_rows[0] = vocab; a.seg_blocks[0] = (vocab + 31) / 32;
+    a.nseg = 1; a.total_blocks = a.seg_blocks[0];
+    a.part = zs[0]; a.part2 = zs[1]; a.ldp = l.ldz; a.m_pad = l.chunk; a.n_split = 1;
+    if (launch_gemm(dtype, a, st) != hipSuccess) return SPEC_EHIP;
     if (launch_topk_loss_rows(zs[0], zs[1], l.ldz, m, vocab, k, sf + l.cand, out_topk + r0, out_ce + r0, st) != hipSuccess)
       return SPEC_EHIP;
   }

@@ -8,7 +8,7 @@
 // never touch a weight twice; the matrix cores are used only because M ~ 60
 // is too much for the vector ALUs at that rate.
 //
-// Layout of one MFMA step (v_mfma_f32_32x32x16_bf16 / 32x32x2_f32):
+// Layout of one MFMA step (v_mfma_f32_32x32x16_bf16; fp32 storage has a kernel of its own, gemm_f32_kernel):
 //   A operand = 32 token rows   x k-slice   (from the X slab staged in LDS)
 //   B operand = 32 weight rows  x k-slice   (straight from global memory)
 //   D         = lane (c = lane%32, g = lane/32) holds weight row c of the
@@ -28,7 +28,7 @@
 // Each wave owns one 32-row block of W for the workgroup's K range and all
 // token blocks; the four waves of a workgroup share the X slab.  Which blocks a
 // workgroup takes is the launch's choice (four adjacent ones, or fewer, spread so
-// that every compute unit has a workgroup: launch_t).  Weight loads
+// that every compute unit has a workgroup: launch_stream).  Weight loads
 // run kStages - 1 iterations ahead through a register ring; the X slab is
 // double-buffered in LDS and prefetched one slab ahead through registers.
 //
@@ -72,12 +72,6 @@ template <> struct GemmTraits<float>  { static constexpr int kEpl = 4; };
 
 __device__ __forceinline__ void mfma_step(f32x16_t &acc, const u32x4_t &x, const u32x4_t &w, bf16_t) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, w), acc, 0, 0, 0);
-}
-__device__ __forceinline__ void mfma_step(f32x16_t &acc, const u32x4_t &x, const u32x4_t &w, float) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x.x), __uint_as_float(w.x), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x.y), __uint_as_float(w.y), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x.z), __uint_as_float(w.z), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x.w), __uint_as_float(w.w), acc, 0, 0, 0);
 }
 
 constexpr int gcd_ce(int a, int b) { return b == 0 ? a : gcd_ce(b, a % b); }
@@ -124,7 +118,8 @@ __device__ __forceinline__ void swiglu_epilogue(const f32x16_t (&acc)[TB], T *ac
     }
 }
 
-template <typename T, int TB>
+// PAIR: a second set of m rows (x2 -> part2) follows the first as rows m .. 2m-1 of the token tile.
+template <typename T, int TB, bool PAIR>
 __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) void gemm_stream_kernel(GemmArgs a) {
   constexpr int EPL = GemmTraits<T>::kEpl;
   constexpr int KI = 2 * kLaneBytes / (int)sizeof(T);         // k elements per iteration
@@ -141,11 +136,11 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
   // runs the same branch-free loop and the same barriers.
   // SwiGLU mode streams the one gate/up matrix (see pack_gate_up_kernel): a block holds 16 gate rows in the lanes
   // c < 16 and the up rows of the same 16 columns in the lanes c >= 16; seg_rows[0] is the number of columns.
-  const int bx = blockIdx.x, by = blockIdx.y, mt = 0;
-  const int m_loc = a.m;                                       // (more than 128 rows: gemm_mm_kernel, gemm_tiled_kernel)
+  const int bx = blockIdx.x, by = blockIdx.y;
+  const int m_loc = PAIR ? 2 * a.m : a.m;                      // (more than 128 rows: gemm_mm_kernel)
   const bool swiglu = a.act != nullptr;
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
-  const int blk_raw = bx * a.blk_per_wg + wave * a.blk_per_wave;   // four adjacent blocks, or strided over more workgroups: see launch_t
+  const int blk_raw = bx * a.blk_per_wg + wave * a.blk_per_wave;   // four adjacent blocks, or strided over more workgroups: see launch_stream
   const bool active = blk_raw < a.total_blocks;
   const int blk = active ? blk_raw : a.total_blocks - 1;
   const int seg = blk < e0 ? 0 : (blk < e1 ? 1 : 2);
@@ -186,7 +181,6 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
 #pragma unroll
     for (int j = 0; j < 8; j++) dst[j] = __builtin_nontemporal_load((const u32x4_t *)(p + j * 1024));   // read once: do not keep in cache
   };
-  const char *xbase = (const char *)a.x + (size_t)mt * 128 * a.ldx * sizeof(T);
   auto load_x = [&](int slab) {
     const int k0 = k_begin + slab * kSlabIters * KI;
 #pragma unroll
@@ -194,7 +188,9 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
       const int q = tid + i * kGemmThreads;
       const int r = q / (kSlabRowBytes / 16), cc = q % (kSlabRowBytes / 16);
       const int kk = k0 + cc * EPL;
-      xr[i] = *(const u32x4_t *)(xbase + ((size_t)(r < m_loc ? r : 0) * a.ldx + (kk < a.in ? kk : 0)) * sizeof(T));
+      const bool second = PAIR && r >= a.m && r < m_loc;
+      const char *xbase = (const char *)(second ? a.x2 : a.x);
+      xr[i] = *(const u32x4_t *)(xbase + ((size_t)(r < m_loc ? (second ? r - a.m : r) : 0) * a.ldx + (kk < a.in ? kk : 0)) * sizeof(T));
     }
   };
   auto store_x = [&](int buf) {
@@ -262,178 +258,19 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
 
   if (swiglu) {
     const int col = blk * 16 + (c & 15);
-    swiglu_epilogue<T, TB>(acc, (T *)a.act + (size_t)mt * 128 * seg_rows + col, seg_rows, col, active && col < seg_rows, m_loc, c, g);
+    swiglu_epilogue<T, TB>(acc, (T *)a.act + col, seg_rows, col, active && col < seg_rows, m_loc, c, g);
     return;
   }
   if (!active || row >= seg_rows) return;
-  float *out = a.part + ((size_t)by * a.m_pad + (size_t)mt * 128) * a.ldp + seg_col0 + row;
+  const size_t o0 = (size_t)by * a.m_pad * a.ldp + seg_col0 + row;
 #pragma unroll
   for (int t = 0; t < TB; t++)
 #pragma unroll
     for (int v = 0; v < 16; v++) {
       const int i = t * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-      if (i < m_loc) store_through(&out[(size_t)i * a.ldp], acc[t][v]);
+      const bool second = PAIR && i >= a.m;
+      if (i < m_loc) store_through(&(second ? a.part2 : a.part)[o0 + (size_t)(second ? i - a.m : i) * a.ldp], acc[t][v]);
     }
-}
-
-// ---- more than 128 token rows, fp32 -------------------------------------------------------
-// The same contraction when X has several 128-row tiles.  One launch covers all tiles; a workgroup owns
-// (256 weight rows, one K split, one tile).  Here the matrix cores are the limit, and with one weight block
-// per wave every MFMA would need its own token fragment from LDS (LDS bandwidth runs out first), so a wave
-// streams TWO weight blocks and uses each fragment twice.  In SwiGLU mode the blocks are those of the gate/up
-// matrix (gate rows in the lanes c < 16, up rows of the same columns in the lanes c >= 16) and the activation is
-// formed in registers after one exchange between the two lane halves.  Tiles of the same weight rows
-// take workgroup ids 8 apart inside a window of 8 * m_tiles ids: they run together on one XCD and share the
-// weights through its L2 (default cache policy instead of the read-once hint).
-template <typename T>
-__global__ __launch_bounds__(kGemmThreads, 1) void gemm_tiled_kernel(GemmArgs a) {
-  constexpr int TB = 4, WB = 2;
-  constexpr int EPL = GemmTraits<T>::kEpl;
-  constexpr int KI = 2 * kLaneBytes / (int)sizeof(T);
-  constexpr int XCH = TB * 32 * (kSlabRowBytes / 16) / kGemmThreads;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  constexpr int kSlabBytes = TB * 32 * kSlabStride;
-  static_assert(kSlabIters == 2, "the two ring stages alternate with the two iterations of a slab");
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = lane & 31, g = lane >> 5;
-  const int per = 8 * a.m_tiles;
-  const int q = ((int)blockIdx.x / per) * 8 + ((int)blockIdx.x % 8);
-  const int mt = ((int)blockIdx.x % per) / 8;
-  if (q >= a.grid_x * a.n_split) return;                       // padding of the id space; whole workgroup
-  const int bx = q % a.grid_x, by = q / a.grid_x;
-  const int m_loc = min(a.m - mt * 128, 128);
-
-  const bool swiglu = a.act != nullptr;
-  const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
-  const int unit = bx * kGemmWaves + wave;                     // pair of consecutive blocks
-  bool active[WB]; int seg_rows[WB], seg_col0[WB], row[WB], blk_of[WB];
-  const char *wstream[WB];
-  const int n_it_total = (a.in + KI - 1) / KI;
-  const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
-  const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
-  const int it_end = min(n_it_total, (int)((long long)(by + 1) * n_slabs_total / a.n_split) * kSlabIters);
-  const int k_begin = it_begin * KI;
-  const int n_iter = it_end - it_begin;
-  const int n_slab = (n_iter + kSlabIters - 1) / kSlabIters;
-#pragma unroll
-  for (int wb = 0; wb < WB; wb++) {
-    const int blk_raw = unit * WB + wb;
-    active[wb] = blk_raw < a.total_blocks;
-    const int blk = active[wb] ? blk_raw : a.total_blocks - 1;
-    blk_of[wb] = blk;
-    const int seg = blk < e0 ? 0 : (blk < e1 ? 1 : 2);
-    const int b0 = seg == 0 ? 0 : (seg == 1 ? e0 : e1);
-    seg_rows[wb] = seg == 0 ? a.seg_rows[0] : (seg == 1 ? a.seg_rows[1] : a.seg_rows[2]);
-    seg_col0[wb] = seg == 0 ? a.seg_col0[0] : (seg == 1 ? a.seg_col0[1] : a.seg_col0[2]);
-    const void *seg_w = seg == 0 ? a.seg_w[0] : (seg == 1 ? a.seg_w[1] : a.seg_w[2]);
-    row[wb] = (blk - b0) * 32 + c;
-    wstream[wb] = (const char *)seg_w + ((size_t)(blk - b0) * n_it_total + it_begin) * (size_t)kTileBytes + lane * 16;
-  }
-
-  f32x16_t acc[WB][TB];
-#pragma unroll
-  for (int wb = 0; wb < WB; wb++)
-#pragma unroll
-    for (int t = 0; t < TB; t++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) acc[wb][t][v] = 0.f;
-  u32x4_t ring[2][WB][8];
-  u32x4_t xr[XCH];
-
-  auto load_w = [&](u32x4_t (&dst)[WB][8], int it) {
-#pragma unroll
-    for (int wb = 0; wb < WB; wb++) {
-      const char *p = wstream[wb] + (size_t)it * kTileBytes;
-#pragma unroll
-      for (int j = 0; j < 8; j++) dst[wb][j] = *(const u32x4_t *)(p + j * 1024);
-    }
-  };
-  const char *xbase = (const char *)a.x + (size_t)mt * 128 * a.ldx * sizeof(T);
-  auto load_x = [&](int slab) {
-    const int k0 = k_begin + slab * kSlabIters * KI;
-#pragma unroll
-    for (int i = 0; i < XCH; i++) {
-      const int qq = tid + i * kGemmThreads;
-      const int r = qq / (kSlabRowBytes / 16), cc = qq % (kSlabRowBytes / 16);
-      const int kk = k0 + cc * EPL;
-      xr[i] = *(const u32x4_t *)(xbase + ((size_t)(r < m_loc ? r : 0) * a.ldx + (kk < a.in ? kk : 0)) * sizeof(T));
-    }
-  };
-  auto store_x = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < XCH; i++) {
-      const int qq = tid + i * kGemmThreads;
-      const int r = qq / (kSlabRowBytes / 16), cc = qq % (kSlabRowBytes / 16);
-      *(u32x4_t *)(lds + buf * kSlabBytes + r * kSlabStride + cc * 16) = xr[i];
-    }
-  };
-  auto compute = [&](const u32x4_t (&w)[WB][8], int buf, int ii) {
-    const unsigned char *base = lds + buf * kSlabBytes + c * kSlabStride + ii * (2 * kLaneBytes) + g * kLaneBytes;
-#pragma unroll
-    for (int j = 0; j < 8; j++) {
-      u32x4_t xf[TB];
-#pragma unroll
-      for (int t = 0; t < TB; t++) xf[t] = *(const u32x4_t *)(base + t * 32 * kSlabStride + j * 16);
-#pragma unroll
-      for (int wb = 0; wb < WB; wb++)
-#pragma unroll
-        for (int t = 0; t < TB; t++) mfma_step(acc[wb][t], xf[t], w[wb][j], T{});
-    }
-  };
-
-  load_x(0);
-  if (0 < n_iter) load_w(ring[0], 0);
-  store_x(0);
-  __syncthreads();
-  // Steady state: a next slab exists, so every load below is unconditional and the compiler can count the
-  // outstanding loads exactly (a guarded load would make it wait for everything before each compute).
-  // The ring stage of iteration it = 2 S + ii is ii.
-  int S = 0;
-  for (; S + 1 < n_slab; S++) {
-    const int buf = S & 1;
-    load_x(S + 1);
-#pragma unroll
-    for (int ii = 0; ii < kSlabIters; ii++) {
-      load_w(ring[(ii + 1) & 1], S * kSlabIters + ii + 1);
-      __builtin_amdgcn_sched_barrier(0);                       // keep the prefetch ahead of the MFMAs
-      compute(ring[ii & 1], buf, ii);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    store_x(buf ^ 1);
-    __syncthreads();
-  }
-  for (; S < n_slab; S++) {                                    // last slab: one or two iterations, nothing follows
-    const int buf = S & 1;
-#pragma unroll
-    for (int ii = 0; ii < kSlabIters; ii++) {
-      const int it = S * kSlabIters + ii;
-      if (it + 1 < n_iter) load_w(ring[(ii + 1) & 1], it + 1);
-      if (it < n_iter) compute(ring[ii & 1], buf, ii);
-    }
-  }
-
-  if (swiglu) {
-    const int f = a.seg_rows[0];
-#pragma unroll
-    for (int wb = 0; wb < WB; wb++) {
-      const int col = blk_of[wb] * 16 + (c & 15);
-      swiglu_epilogue<T, TB>(acc[wb], (T *)a.act + (size_t)mt * 128 * f + col, f, col, active[wb] && col < f, m_loc, c, g);
-    }
-    return;
-  }
-#pragma unroll
-  for (int wb = 0; wb < WB; wb++) {
-    if (!active[wb] || row[wb] >= seg_rows[wb]) continue;
-    float *out = a.part + ((size_t)by * a.m_pad + (size_t)mt * 128) * a.ldp + seg_col0[wb] + row[wb];
-#pragma unroll
-    for (int t = 0; t < TB; t++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        const int i = t * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-        if (i < m_loc) out[(size_t)i * a.ldp] = acc[wb][t][v];
-      }
-  }
 }
 
 // ---- more than 128 token rows, bf16 (prefill, LM head of the loss) ------------------------------
@@ -487,7 +324,9 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
   const int mt = ((int)blockIdx.x % per) / 8;
   if (q >= a.grid_x * a.n_split) return;
   const int bx = q % a.grid_x, by = q / a.grid_x;
-  const int m0 = mt * L::kTok, m_loc = min(a.m - m0, L::kTok);
+  const int set_tiles = (a.m + L::kTok - 1) / L::kTok;        // tiles of the second set of rows follow the first set's
+  const bool second = mt >= set_tiles;
+  const int m0 = (second ? mt - set_tiles : mt) * L::kTok, m_loc = min(a.m - m0, L::kTok);
 
   const bool swiglu = a.act != nullptr;
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
@@ -510,7 +349,7 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
   }
   // the X rows this wave copies: row segment rs = (t * 2 + g) * 32 + c holds the 64 bytes (32 k) of half g, its four 16-byte
   // pieces rotated by the row so that the fragment reads of eight consecutive rows touch all banks
-  const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const char *)a.x + (size_t)m0 * a.ldx * 2);
+  const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const char *)(second ? a.x2 : a.x) + (size_t)m0 * a.ldx * 2);
   uint32_t xoff[XI];
   int xk[XI];
 #pragma unroll
@@ -630,7 +469,7 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
     const int col0 = seg == 0 ? a.seg_col0[0] : (seg == 1 ? a.seg_col0[1] : a.seg_col0[2]);
     const int row = (blk - b0) * 32 + c;
     if (row >= rows) continue;
-    float *out = a.part + ((size_t)by * a.m_pad + m0 + th * TB * 32) * a.ldp;
+    float *out = (second ? a.part2 : a.part) + ((size_t)by * a.m_pad + m0 + th * TB * 32) * a.ldp;
     const uint32_t o0 = (uint32_t)(col0 + row);
 #pragma unroll
     for (int t = 0; t < TB; t++)
@@ -639,6 +478,156 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
         const int i = t * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
         if (th * TB * 32 + i < m_loc) out[o0 + (uint32_t)i * (uint32_t)a.ldp] = acc[wb][t][v];
       }
+  }
+}
+
+// ---- fp32 storage ---------------------------------------------------------------------------------
+// The fp32 configurations are small: a projection is a few hundred rows by a few hundred k, and a wavefront that walks all of
+// K for a 32 x 32 tile (one v_mfma_f32_32x32x2 per two k, 64 cycles each) is what the launch waits for.  So the tile is
+// 16 weight rows wide per MFMA (v_mfma_f32_16x16x4: no products for absent rows with up to 16 tokens), the four wavefronts of a
+// workgroup split its K range by whole 64-k tiles (wavefront w takes tiles w, w + 4, ...), and their sums meet in the LDS once,
+// in wavefront order.  Nothing is staged: a wavefront reads its own operands, the 16-byte pieces of TB token blocks and RB
+// half weight blocks, one step ahead.  The order of a row's sums depends on K and the split alone.
+// Measured (MI355X), against 32 x 32 tiles with all of K in one wavefront: the projections of a 256-wide layer, up to 16 rows,
+// 9.4 -> 3.4 us per launch; 2 x 129 rows x 9000 x 512 2 x 72 -> 48 us (25 TFLOP/s of 157: two tiles of k per wavefront).
+// Lane (r = lane % 16, kg = lane / 16) supplies row r and, in step jj of a tile, the four k of piece (g = kg % 2, j = 2 jj + kg / 2).
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+template <int TB, int RB>
+__global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
+  constexpr int JU = TB * RB >= 8 ? 2 : 4;                    // steps loaded at a time
+  constexpr int E = TB * RB * 4;                              // sums per lane
+  __shared__ float sums[kGemmWaves][E][kWave];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, kg = lane >> 4;
+  const int tiles = (a.m + TB * 16 - 1) / (TB * 16);          // per set of rows
+  const bool second = (int)blockIdx.z >= tiles;
+  const int m0 = ((int)blockIdx.z - (second ? tiles : 0)) * TB * 16, m_loc = min(a.m - m0, TB * 16);
+  const int by = blockIdx.y, blk = RB == 2 ? (int)blockIdx.x : (int)blockIdx.x >> 1, h0 = RB == 2 ? 0 : (int)blockIdx.x & 1;
+  const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
+  const int seg = blk < e0 ? 0 : (blk < e1 ? 1 : 2);
+  const int b0 = seg == 0 ? 0 : (seg == 1 ? e0 : e1);
+  const int seg_rows = seg == 0 ? a.seg_rows[0] : (seg == 1 ? a.seg_rows[1] : a.seg_rows[2]);
+  const int seg_col0 = seg == 0 ? a.seg_col0[0] : (seg == 1 ? a.seg_col0[1] : a.seg_col0[2]);
+  const void *seg_w = seg == 0 ? a.seg_w[0] : (seg == 1 ? a.seg_w[1] : a.seg_w[2]);
+  constexpr int KI = 64;
+  const int n_it_total = (a.in + KI - 1) / KI;
+  const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
+  const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
+  const int it_end = min(n_it_total, (int)((long long)(by + 1) * n_slabs_total / a.n_split) * kSlabIters);
+
+  const char *w0 = (const char *)seg_w + (size_t)(blk - b0) * n_it_total * kTileBytes + (((kg & 1) * 32 + r) * 16 + (kg >> 1) * 1024);
+  const float *xbase = (const float *)(second ? a.x2 : a.x) + (size_t)m0 * a.ldx;
+  const float *xrow[TB];
+#pragma unroll
+  for (int t = 0; t < TB; t++) xrow[t] = xbase + (size_t)(t * 16 + r < m_loc ? t * 16 + r : 0) * a.ldx;
+  f32x4_t acc[RB][TB];
+#pragma unroll
+  for (int b = 0; b < RB; b++)
+#pragma unroll
+    for (int t = 0; t < TB; t++) acc[b][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  constexpr int HALVES = 4 / JU;
+  struct Step { f32x4_t x[JU][TB], w[JU][RB]; };
+  // step s of this wavefront: half s % HALVES of tile it_begin + wave + 4 * (s / HALVES)
+  const int n_tiles = max(0, (it_end - it_begin - wave + 3) / 4), n_step = n_tiles * HALVES;
+  auto load = [&](Step &d, int s) {
+    const int it = it_begin + wave + 4 * (s / HALVES);
+    const char *wp = w0 + (size_t)it * kTileBytes;
+#pragma unroll
+    for (int u = 0; u < JU; u++) {
+      const int jj = (s % HALVES) * JU + u;
+#pragma unroll
+      for (int b = 0; b < RB; b++) d.w[u][b] = *(const f32x4_t *)(wp + (h0 + b) * 256 + jj * 2048);
+      const int kk = it * KI + (kg & 1) * 32 + (2 * jj + (kg >> 1)) * 4;
+#pragma unroll
+      for (int t = 0; t < TB; t++) d.x[u][t] = *(const f32x4_t *)(xrow[t] + (kk < a.in ? kk : 0));   // past K: meets a zero weight
+    }
+  };
+  auto mul = [&](const Step &d) {
+#pragma unroll
+    for (int u = 0; u < JU; u++)
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int b = 0; b < RB; b++)
+#pragma unroll
+          for (int t = 0; t < TB; t++) acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x[u][t][e], d.w[u][b][e], acc[b][t], 0, 0, 0);
+  };
+  Step cur, nxt;
+  if (n_step > 0) load(cur, 0);
+  int s = 0;
+  for (; s + 2 < n_step; s += 2) {
+    load(nxt, s + 1);
+    mul(cur);
+    load(cur, s + 2);
+    mul(nxt);
+  }
+  if (s + 1 < n_step) {
+    load(nxt, s + 1);
+    mul(cur);
+    mul(nxt);
+  } else if (s < n_step) {
+    mul(cur);
+  }
+
+  // lane (r, kg) holds, for weight row r of half h0 + b, tokens t * 16 + 4 * kg + v
+#pragma unroll
+  for (int t = 0; t < TB; t++)
+#pragma unroll
+    for (int b = 0; b < RB; b++)
+#pragma unroll
+      for (int v = 0; v < 4; v++) sums[wave][(t * RB + b) * 4 + v][lane] = acc[b][t][v];
+  __syncthreads();
+  auto total = [&](int e) { return ((sums[0][e][lane] + sums[1][e][lane]) + sums[2][e][lane]) + sums[3][e][lane]; };
+  if (a.act != nullptr) {                                     // SwiGLU (RB == 2): half 0 = gate rows, half 1 = the up rows of the same columns
+    if constexpr (RB == 2) {
+      const int col = blk * 16 + r;
+#pragma unroll
+      for (int t = 0; t < TB; t++) {                          // wavefront w finishes v = w
+        const float g = total(t * 8 + wave), u = total(t * 8 + 4 + wave);
+        const int i = t * 16 + 4 * kg + wave;
+        if (i < m_loc && col < seg_rows) ((float *)a.act)[(size_t)(m0 + i) * seg_rows + col] = silu_mul(g, u);
+      }
+    }
+    return;
+  }
+  float *out = (second ? a.part2 : a.part) + ((size_t)by * a.m_pad + m0) * a.ldp + seg_col0;
+#pragma unroll
+  for (int t = 0; t < TB; t++)
+#pragma unroll
+    for (int b = 0; b < RB; b++) {
+      const int row = (blk - b0) * 32 + (h0 + b) * 16 + r, i = t * 16 + 4 * kg + wave;
+      const float y = total((t * RB + b) * 4 + wave);
+      if (i < m_loc && row < seg_rows) out[(size_t)i * a.ldp + row] = y;
+    }
+}
+
+template <int TB>
+static hipError_t launch_f32_tile(const GemmArgs &a, bool halves, hipStream_t st) {
+  const int tiles = (a.m + TB * 16 - 1) / (TB * 16) * (a.x2 ? 2 : 1);
+  if (tiles > 65535) return hipErrorInvalidValue;
+  if (halves) hipLaunchKernelGGL((gemm_f32_kernel<TB, 1>), dim3(a.total_blocks * 2, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
+  else hipLaunchKernelGGL((gemm_f32_kernel<TB, 2>), dim3(a.total_blocks, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
+  return hipGetLastError();
+}
+// Token blocks per workgroup: the count out of 1, 2, 3, 4, 6 with the fewest padded blocks in all, the larger one on a tie (fewer
+// passes over the weights).  Half weight blocks where whole ones would leave compute units without a workgroup.
+static hipError_t launch_f32(const GemmArgs &a, hipStream_t st) {
+  const int blocks = (a.m + 15) / 16;
+  int tb = 1;
+  long long best = blocks;
+  for (int c : {2, 3, 4, 6}) {
+    const long long padded = (long long)(blocks + c - 1) / c * c;
+    if (padded <= best) { best = padded; tb = c; }
+  }
+  const long long wgs = (long long)a.total_blocks * a.n_split * ((blocks + tb - 1) / tb) * (a.x2 ? 2 : 1);
+  const bool halves = a.act == nullptr && wgs <= 128;
+  switch (tb) {
+    case 1: return launch_f32_tile<1>(a, halves, st);
+    case 2: return launch_f32_tile<2>(a, halves, st);
+    case 3: return launch_f32_tile<3>(a, halves, st);
+    case 4: return launch_f32_tile<4>(a, halves, st);
+    default: return launch_f32_tile<6>(a, halves, st);
   }
 }
 
@@ -723,18 +712,12 @@ hipError_t launch_pack_weight(int dtype, const void *src, int rows, int in, void
 
 // The double-buffered slab exceeds the 64 KiB default for dynamic LDS from two token blocks on: raise the
 // limit once per kernel, at context creation (never during a stream capture).
-template <typename T>
-static hipError_t init_t() {
-  const void *fn[4] = {(const void *)gemm_stream_kernel<T, 1>, (const void *)gemm_stream_kernel<T, 2>,
-                       (const void *)gemm_stream_kernel<T, 3>, (const void *)gemm_stream_kernel<T, 4>};
-  for (int tb = 1; tb <= 4; tb++) {
-    const size_t lds = (size_t)2 * tb * 32 * kSlabStride;
-    if (lds > 160 * 1024) continue;
-    hipError_t e = hipFuncSetAttribute(fn[tb - 1], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  if constexpr (sizeof(T) == 2) return hipSuccess;
-  else return hipFuncSetAttribute((const void *)gemm_tiled_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 4 * 32 * kSlabStride);
+template <int TB>
+static hipError_t init_tb() {
+  const int lds = 2 * TB * 32 * kSlabStride;
+  hipError_t e = hipFuncSetAttribute((const void *)gemm_stream_kernel<bf16_t, TB, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_stream_kernel<bf16_t, TB, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  return e;
 }
 hipError_t gemm_init() {
   // kernel attributes belong to the device's copy of the code: once per device, for the current device
@@ -743,8 +726,10 @@ hipError_t gemm_init() {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev >= 0 && dev < 64 && done[dev]) return hipSuccess;
-  e = init_t<bf16_t>();
-  if (e == hipSuccess) e = init_t<float>();
+  e = init_tb<1>();
+  if (e == hipSuccess) e = init_tb<2>();
+  if (e == hipSuccess) e = init_tb<3>();
+  if (e == hipSuccess) e = init_tb<4>();
   if (dev >= 0 && dev < 64) done[dev] = e == hipSuccess;
   return e;
 }
@@ -752,7 +737,7 @@ hipError_t gemm_init() {
 template <int TW, int TB, int WB>
 static hipError_t launch_mm_tile(GemmArgs a, hipStream_t st) {
   using L = MmTile<TW, TB, WB>;
-  a.m_tiles = (a.m + L::kTok - 1) / L::kTok;
+  a.m_tiles = (a.m + L::kTok - 1) / L::kTok * (a.x2 ? 2 : 1);
   a.grid_x = (a.total_blocks + L::kBlocks - 1) / L::kBlocks;
   const dim3 grid((a.grid_x * a.n_split + 7) / 8 * 8 * a.m_tiles, 1);
   hipLaunchKernelGGL((gemm_mm_kernel<TW, TB, WB>), grid, dim3(kMmThreads), 0, st, a);
@@ -765,7 +750,7 @@ static hipError_t launch_mm_tile(GemmArgs a, hipStream_t st) {
 // 128 x 256 against 38 and 34, LM head 129 us with 256 x 256 against 170 and 150.
 static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
   auto cost = [&](int tok, int blocks, int per_round) {
-    const long long wgs = (long long)((a.m + tok - 1) / tok) * ((a.total_blocks + blocks - 1) / blocks) * a.n_split;
+    const long long wgs = (long long)((a.m + tok - 1) / tok) * (a.x2 ? 2 : 1) * ((a.total_blocks + blocks - 1) / blocks) * a.n_split;
     return (wgs + 255) / 256 * per_round;
   };
   const long long c256 = cost(256, 8, 100), c192 = cost(256, 6, 80), c128 = cost(128, 8, 60);
@@ -776,16 +761,15 @@ static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
 
 // Copies into the LDS need 16-byte aligned sources, and the kernel's offsets inside a tile are 32-bit.
 static bool mm_takes(const GemmArgs &a) {
-  uintptr_t low = (uintptr_t)a.x | (uintptr_t)a.seg_w[0];
+  uintptr_t low = (uintptr_t)a.x | (uintptr_t)a.x2 | (uintptr_t)a.seg_w[0];
   if (a.nseg > 1) low |= (uintptr_t)a.seg_w[1];
   if (a.nseg > 2) low |= (uintptr_t)a.seg_w[2];
   return (low & 15) == 0 && a.ldx % 8 == 0 && a.ldx >= 0 && a.ldx < (1 << 22) && a.in < (1 << 22) && a.ldp < (1 << 24);
 }
 
-template <typename T>
-static hipError_t launch_t(GemmArgs a, hipStream_t st) {
-  a.m_tiles = (a.m + 127) / 128;
-  const int tb = a.m_tiles > 1 ? 4 : (a.m + 31) / 32;
+template <bool PAIR>
+static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
+  const int tb = ((PAIR ? 2 * a.m : a.m) + 31) / 32;
   // Workgroups along the rows.  A compute unit sustains about 30 GB/s whatever the number of its waves, so what counts is
   // the largest number of blocks any workgroup streams.  With four blocks per workgroup the launch may leave compute
   // units idle (7B gate/up: 688 blocks = 172 workgroups); if the blocks fit in three, two or one per workgroup on at
@@ -804,40 +788,36 @@ static hipError_t launch_t(GemmArgs a, hipStream_t st) {
       a.blk_per_wg = kGemmWaves; a.blk_per_wave = 1;
     }
   }
-  // SwiGLU mode: the one gate/up matrix, 16 columns per block, whole K (the activation is not linear)
-  if (a.act != nullptr && (a.nseg != 1 || a.n_split != 1 || a.seg_blocks[0] != (a.seg_rows[0] + 15) / 16)) return hipErrorInvalidValue;
-  dim3 grid(a.grid_x, a.n_split);
-  if (a.m_tiles > 1) {
-    if constexpr (sizeof(T) == 2) {
-      if (mm_takes(a)) return launch_mm(a, st);
-      for (int m0 = 0; m0 < a.m; m0 += 128) {                  // any alignment: 128 rows at a time through the streaming kernel
-        GemmArgs t = a;
-        t.m = std::min(128, a.m - m0);
-        t.x = (const char *)a.x + (ptrdiff_t)m0 * a.ldx * (ptrdiff_t)sizeof(T);
-        if (a.act) t.act = (char *)a.act + (size_t)m0 * a.seg_rows[0] * sizeof(T);
-        else t.part = a.part + (size_t)m0 * a.ldp;
-        const hipError_t e = launch_t<T>(t, st);
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
-    } else {
-      // two blocks per wave; see gemm_tiled_kernel's id decoding
-      a.grid_x = (a.total_blocks + 2 * kGemmWaves - 1) / (2 * kGemmWaves);
-      const dim3 tgrid((a.grid_x * a.n_split + 7) / 8 * 8 * a.m_tiles, 1);
-      hipLaunchKernelGGL((gemm_tiled_kernel<T>), tgrid, dim3(kGemmThreads), (size_t)2 * 4 * 32 * kSlabStride, st, a);
-      return hipGetLastError();
-    }
-  }
+  const dim3 grid(a.grid_x, a.n_split);
   const size_t lds = (size_t)2 * tb * 32 * kSlabStride;
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  static_assert((size_t)2 * 4 * 32 * kSlabStride <= 160 * 1024, "four token blocks fit the LDS");
   switch (tb) {
-    case 1: hipLaunchKernelGGL((gemm_stream_kernel<T, 1>), grid, dim3(kGemmThreads), lds, st, a); break;
-    case 2: hipLaunchKernelGGL((gemm_stream_kernel<T, 2>), grid, dim3(kGemmThreads), lds, st, a); break;
-    case 3: hipLaunchKernelGGL((gemm_stream_kernel<T, 3>), grid, dim3(kGemmThreads), lds, st, a); break;
-    case 4: hipLaunchKernelGGL((gemm_stream_kernel<T, 4>), grid, dim3(kGemmThreads), lds, st, a); break;
+    case 1: hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, 1, PAIR>), grid, dim3(kGemmThreads), lds, st, a); break;
+    case 2: hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, 2, PAIR>), grid, dim3(kGemmThreads), lds, st, a); break;
+    case 3: hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, 3, PAIR>), grid, dim3(kGemmThreads), lds, st, a); break;
+    case 4: hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, 4, PAIR>), grid, dim3(kGemmThreads), lds, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// Up to 128 rows in all the launch is bound by the weights, read once; a pair of row sets shares that one pass.
+static hipError_t launch_bf16(const GemmArgs &a, hipStream_t st) {
+  const long long rows = (long long)a.m * (a.x2 ? 2 : 1);
+  if (rows <= 128) return a.x2 ? launch_stream<true>(a, st) : launch_stream<false>(a, st);
+  if (mm_takes(a)) return launch_mm(a, st);
+  for (int set = 0; set < (a.x2 ? 2 : 1); set++)               // any alignment: 128 rows at a time through the streaming kernel
+    for (int m0 = 0; m0 < a.m; m0 += 128) {
+      GemmArgs t = a;
+      t.m = std::min(128, a.m - m0);
+      t.x = (const char *)(set ? a.x2 : a.x) + (ptrdiff_t)m0 * a.ldx * (ptrdiff_t)sizeof(bf16_t);
+      t.x2 = nullptr;
+      if (a.act) t.act = (char *)a.act + (size_t)m0 * a.seg_rows[0] * sizeof(bf16_t);
+      else t.part = (set ? a.part2 : a.part) + (size_t)m0 * a.ldp;
+      const hipError_t e = launch_stream<false>(t, st);
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
 }
 
 int gemm_k_per_iter(int dtype) { return dtype == 1 ? 128 : 64; }
@@ -847,7 +827,10 @@ hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st) {
   { hipError_t e = gemm_init(); if (e != hipSuccess) return e; }
   if (a.m < 1 || a.m_pad < a.m || a.nseg < 1 || a.nseg > 3 || a.n_split < 1 || a.in < 1) return hipErrorInvalidValue;
   if (a.n_split > (a.in + gemm_k_per_slab(dtype) - 1) / gemm_k_per_slab(dtype)) return hipErrorInvalidValue;   // no empty split
-  return dtype == 1 ? launch_t<bf16_t>(a, st) : launch_t<float>(a, st);
+  // SwiGLU mode: the one gate/up matrix, 16 columns per block, whole K (the activation is not linear)
+  if (a.act != nullptr && (a.nseg != 1 || a.n_split != 1 || a.x2 != nullptr || a.seg_blocks[0] != (a.seg_rows[0] + 15) / 16))
+    return hipErrorInvalidValue;
+  return dtype == 1 ? launch_bf16(a, st) : launch_f32(a, st);
 }
 
 }  // namespace spec

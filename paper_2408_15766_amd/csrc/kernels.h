@@ -35,7 +35,8 @@ constexpr int kTopkSlice = 4096;       // vocabulary entries per first-stage top
 
 // ---- gemm.hip --------------------------------------------------------------------------------
 struct GemmArgs {
-  const void *x;  int ldx;  int m;      // X [m, in], row stride ldx elements; m > 128 runs as tiles of 128 rows (prefill)
+  const void *x;  int ldx;  int m;      // X [m, in], row stride ldx elements; any m (up to 128 rows stream the weights, more are tiled)
+  const void *x2; float *part2;         // if not null: a second set of m rows through the same weights, results in part2 (not in SwiGLU mode)
   int in;                               // K, a multiple of 16 bytes / element size
   const void *seg_w[3];                 // up to three PACKED weight matrices ([rows, in] before packing) sharing X (e.g. q, k, v)
   int seg_rows[3];
@@ -48,7 +49,7 @@ struct GemmArgs {
   // seg_blocks[0] = ceil(columns / 16), n_split = 1.  The wave that streams a block writes
   // act[i][c] = silu(gate) * up in the storage type instead of partial sums.
   void *act;
-  int m_tiles, grid_x;                  // set by launch_gemm: 128-row tiles of X, workgroups per tile and split
+  int m_tiles, grid_x;                  // set by launch_gemm: token tiles, workgroups per tile and split
   int blk_per_wg, blk_per_wave;         // set by launch_gemm: wave w of workgroup x streams block x * blk_per_wg + w * blk_per_wave
 };
 hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st);

@@ -72,6 +72,9 @@ CASES = [
     ("bf16", 600, 256, 5000, 5),        # two row chunks (512 + 88)
     ("bf16", 40, 256, 128256, 10),      # LLaMA3 vocabulary: 32 slices
     ("bf16", 12, 256, 128256, 128),     # 4096 candidates in the merge
+    ("bf16", 17, 264, 1000, 3),         # both sides' rows in one token tile of the LM head, the boundary inside a 32-row block
+    ("bf16", 64, 256, 1000, 3),         # ... the largest such pair
+    ("bf16", 65, 256, 1000, 3),         # ... and one row more per side: tiled, each side its own tiles
     ("bf16", 1, 256, 100, 100),         # K = V: Eq. (1) becomes the cross-entropy (vocabulary smaller than one slice)
 ]
 

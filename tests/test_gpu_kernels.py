@@ -68,6 +68,22 @@ def test_gemm_matches_matmul(env, dtype, m, k, rows, n_split):
     assert np.abs(got - want).max() < tol
 
 
+@pytest.mark.parametrize("m,k,rows,n_split", [(1, 4, [1], 1), (16, 256, [257, 33, 31], 1), (17, 688, [48], 1), (33, 324, [4100], 1),
+                                              (49, 1100, [96], 2), (81, 4096, [320], 4), (129, 512, [9000], 1), (700, 100, [64], 1)])
+def test_gemm_fp32_matches_fp64(env, m, k, rows, n_split):
+    """fp32 storage: every number of token blocks per workgroup (1, 2, 3, 4, 6), half and whole weight blocks, fewer than four
+    64-k tiles (wavefronts without work), ragged K and rows, K splits; a row alone gives the bits it has among the others."""
+    torch, P = env
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed("f32", m, k) & 0xFFFF)
+    x = torch.randn(m, k, device="cuda", generator=g)
+    ws = [torch.randn(r, k, device="cuda", generator=g) * 0.05 for r in rows]
+    got = P.spec_k_gemm(x, ws, n_split)
+    want = x.double() @ torch.cat(ws).double().t()
+    assert (got.double().sum(0) - want).abs().max() <= 1e-6 * np.sqrt(k) * max(1.0, float(want.abs().max()))
+    for i in sorted({0, m // 2, m - 1}):
+        assert torch.equal(P.spec_k_gemm(x[i:i + 1].contiguous(), ws, n_split)[:, 0], got[:, i])
+
+
 @pytest.mark.parametrize("dtype,m,k,rows", [("fp32", 16, 256, 688), ("bf16", 60, 4096, 1100), ("bf16", 1, 1280, 64), ("bf16", 200, 768, 300),
                                             ("bf16", 40, 256, 77), ("fp32", 33, 128, 77), ("bf16", 60, 512, 15), ("bf16", 130, 256, 45)])
 def test_gemm_swiglu_epilogue_matches_oracle(env, dtype, m, k, rows):
