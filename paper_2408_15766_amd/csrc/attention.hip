@@ -366,12 +366,15 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 
 // x = hi + lo with hi, lo bf16: the pair keeps ~16 mantissa bits of an fp32 value.
-__device__ __forceinline__ void split8(const float (&x)[8], u32x4_t &hi, u32x4_t &lo) {
+// rest (if wanted): what the pair leaves over, as a third bf16 (24 mantissa bits in all: an fp32 value exactly).
+__device__ __forceinline__ void split8(const float (&x)[8], u32x4_t &hi, u32x4_t &lo, u32x4_t *rest = nullptr) {
   uint32_t h[4], l[4];
 #pragma unroll
   for (int e = 0; e < 4; e++) {
     h[e] = pack_bf16x2(x[2 * e], x[2 * e + 1]);
-    l[e] = pack_bf16x2(x[2 * e] - __uint_as_float(h[e] << 16), x[2 * e + 1] - __uint_as_float(h[e] & 0xFFFF0000u));
+    const float r0 = x[2 * e] - __uint_as_float(h[e] << 16), r1 = x[2 * e + 1] - __uint_as_float(h[e] & 0xFFFF0000u);
+    l[e] = pack_bf16x2(r0, r1);
+    if (rest) (*rest)[e] = pack_bf16x2(r0 - __uint_as_float(l[e] << 16), r1 - __uint_as_float(l[e] & 0xFFFF0000u));
   }
   hi = u32x4_t{h[0], h[1], h[2], h[3]};
   lo = u32x4_t{l[0], l[1], l[2], l[3]};
@@ -594,10 +597,230 @@ static hipError_t launch_hybrid(AttnArgs a, int q_groups, hipStream_t st) {
   return hipGetLastError();
 }
 
+// ---- many rows of a causal chain (prefill), bf16 storage ---------------------------------------
+// With hundreds of rows a row's keys need no split over workgroups: one workgroup of WAVES wavefronts takes WAVES * 32
+// consecutive rows of one query head and walks all of their keys, 64 at a time, so there are no partial outputs to
+// write and merge (512 rows at 4096 keys, 32 heads: 170 MB of them per layer).  S^T = K Q^T and O^T = V^T P^T as in the
+// bulk above, a lane owns one query, probabilities enter as bf16 hi + lo and queries as three bf16 (exactly: the bulk's rows have sixteen
+// keys each in full fp32, here the third term makes up for them; 0.22 % of the outputs round differently from fp64, 0.26 %
+// with the bulk and tail).  K and V^T blocks are double-buffered in the LDS, the loads of a block run two blocks ahead; the
+// block is 32 keys at head dim 128 because 64 spill beside three query terms (2048 rows 110 us against 154).  The running maximum moves only when a score exceeds it by 2^8 (the
+// terms stay far inside fp32's range and the division by the sum cancels the choice), which spares the 64 output
+// registers a rescaling per block.  Rows may stand at any positions (depth); a block past a wavefront's last position is skipped.
+// Measured (MI355X, us; with parts and merge before): 512 rows, 32 heads 80 -> 28; 1024 rows, 64 heads on 8 kv heads 316 -> 59; 2048
+// rows, 32 on 8 387 -> 110, at 2048 keys before them 666 -> 251.
+template <int HD> struct CausalLds {
+  static constexpr int kKeys = HD == 128 ? 32 : 64;   // keys per staged block: what the registers beside the queries leave
+  static constexpr int kstr = HD * 2 + 16;            // bytes per staged key row (+16: conflict-free b128 reads)
+  static constexpr int vstr = kKeys * 2 + 8;          // bytes per dim row of V^T (+8: conflict-free b64 reads)
+  static constexpr int buf = kKeys * kstr + HD * vstr;
+};
+template <int HD, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_causal_kernel(AttnArgs a) {
+  using L = CausalLds<HD>;
+  constexpr int NT = WAVES * 64, KEYS = L::kKeys, KT = KEYS / 32;
+  constexpr int DB = HD / 32, KK = HD / 16, PPR = HD * 2 / 16;
+  constexpr int KP = KEYS * PPR / NT, VP = KEYS / 2 * PPR / NT;
+  static_assert(KEYS * PPR % NT == 0 && KEYS / 2 * PPR % NT == 0, "staging split");
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  __shared__ int wave_hi[WAVES];
+
+  // Workgroup -> (head, row tile): last tile (the longest) first; with a multiple of eight kv heads all workgroups of a kv head
+  // run on one XCD (ids 8 apart) and share its keys and values through that L2.
+  const int G = a.hq / a.hkv, n_qt = (a.rows + WAVES * 32 - 1) / (WAVES * 32);
+  const bool affine = (a.hkv & 7) == 0;
+  const int lists = affine ? 8 : 1, heads = a.hq / lists;     // heads per list
+  const int id = (int)blockIdx.x / lists, list = (int)blockIdx.x % lists;
+  const int qt = n_qt - 1 - id / heads, hl = id % heads;
+  const int hk = (hl / G) * lists + list, h = hk * G + hl % G;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 31, g = lane >> 5;
+  const int i = (qt * WAVES + wave) * 32 + c;                 // row of this lane
+  const bool valid = i < a.rows;
+  const int base = a.base_ptr ? *a.base_ptr : a.base;
+  const int lim = valid ? base + a.depth[i] : -1;             // last key position of the row
+  int lo = valid ? lim : 0x7FFFFFFF, hi = lim;                // over the wavefront's rows
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) { lo = min(lo, __shfl_xor(lo, o, 64)); hi = max(hi, __shfl_xor(hi, o, 64)); }
+  lo = __builtin_amdgcn_readfirstlane(lo); hi = __builtin_amdgcn_readfirstlane(hi);
+  if (lane == 0) wave_hi[wave] = hi;
+  __syncthreads();
+  int last = wave_hi[0];                                      // last key position of the workgroup (at least 0: its first row is valid)
+#pragma unroll
+  for (int w = 1; w < WAVES; w++) last = max(last, wave_hi[w]);
+  last = __builtin_amdgcn_readfirstlane(last);
+  const int nb = last / KEYS + 1;
+
+  const size_t kv_stride = (size_t)a.hkv * HD;
+  const bf16_t *kg = (const bf16_t *)a.kcache + (size_t)hk * HD, *vg = (const bf16_t *)a.vcache + (size_t)hk * HD;
+  u32x4_t kreg[KP], vreg[VP][2];
+  auto prefetch = [&](int blk) {                              // keys past the workgroup's last are read from it and masked
+#pragma unroll
+    for (int e = 0; e < KP; e++) {
+      const int q = tid + e * NT;
+      kreg[e] = *(const u32x4_t *)(kg + (size_t)min(blk * KEYS + q / PPR, last) * kv_stride + (q % PPR) * 8);
+    }
+#pragma unroll
+    for (int e = 0; e < VP; e++) {
+      const int q = tid + e * NT;
+      const int pair = q % (KEYS / 2), piece = q / (KEYS / 2);
+      vreg[e][0] = *(const u32x4_t *)(vg + (size_t)min(blk * KEYS + 2 * pair, last) * kv_stride + piece * 8);
+      vreg[e][1] = *(const u32x4_t *)(vg + (size_t)min(blk * KEYS + 2 * pair + 1, last) * kv_stride + piece * 8);
+    }
+  };
+  auto stage = [&](int b) {
+    unsigned char *k_lds = lds + b * L::buf, *vt_lds = k_lds + KEYS * L::kstr;
+#pragma unroll
+    for (int e = 0; e < KP; e++) {
+      const int q = tid + e * NT;
+      *(u32x4_t *)(k_lds + (q / PPR) * L::kstr + (q % PPR) * 16) = kreg[e];
+    }
+#pragma unroll
+    for (int e = 0; e < VP; e++) {                            // V^T[dim][key], two keys per 32-bit store
+      const int q = tid + e * NT;
+      const int pair = q % (KEYS / 2), piece = q / (KEYS / 2);
+#pragma unroll
+      for (int d2 = 0; d2 < 8; d2++) {
+        const uint32_t x0 = vreg[e][0][d2 >> 1], x1 = vreg[e][1][d2 >> 1];
+        *(uint32_t *)(vt_lds + (piece * 8 + d2) * L::vstr + pair * 4) = (d2 & 1) ? ((x0 >> 16) | (x1 & 0xFFFF0000u)) : ((x0 & 0xFFFFu) | (x1 << 16));
+      }
+    }
+  };
+
+  u32x4_t qhi[KK], qlo[KK], qrest[KK];                        // step kk covers dims kk*16 + g*8 .. +8 of the lane's query
+  {
+    const float *qrow = (const float *)a.q + ((size_t)(valid ? i : a.rows - 1) * a.hq + h) * HD;
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++) {
+      float x[8];
+      const float4 x0 = *(const float4 *)(qrow + kk * 16 + g * 8), x1 = *(const float4 *)(qrow + kk * 16 + g * 8 + 4);
+      x[0] = x0.x; x[1] = x0.y; x[2] = x0.z; x[3] = x0.w; x[4] = x1.x; x[5] = x1.y; x[6] = x1.z; x[7] = x1.w;
+      split8(x, qhi[kk], qlo[kk], &qrest[kk]);
+    }
+  }
+  f32x16_t o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; db++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) o[db][v] = 0.f;
+  const float c2 = a.scale * 1.4426950408889634f;             // scores in units of log2
+  float m_run = -INFINITY, l_run = 0.f;
+
+  prefetch(0);
+  stage(0);
+  __syncthreads();
+  if (nb > 1) prefetch(1);
+  for (int blk = 0; blk < nb; blk++) {
+    const int cur = blk & 1;
+    const unsigned char *k_lds = lds + cur * L::buf, *vt_lds = k_lds + KEYS * L::kstr;
+    if (blk + 1 < nb) {                                       // the other buffer was left by everyone at the last barrier
+      stage(cur ^ 1);
+      if (blk + 2 < nb) prefetch(blk + 2);
+    }
+    if (blk * KEYS <= hi) {                                   // some row of the wavefront sees this block
+      f32x16_t s[KT];
+#pragma unroll
+      for (int kt = 0; kt < KT; kt++) {
+#pragma unroll
+        for (int v = 0; v < 16; v++) s[kt][v] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; kk++) {
+          const u32x4_t kf = *(const u32x4_t *)(k_lds + (kt * 32 + c) * L::kstr + kk * 32 + g * 16);
+          s[kt] = mfma_bf16(kf, qhi[kk], s[kt]);
+          s[kt] = mfma_bf16(kf, qlo[kk], s[kt]);
+          s[kt] = mfma_bf16(kf, qrest[kk], s[kt]);
+        }
+      }
+      // s[kt][v] = q . k for key blk*KEYS + kt*32 + 8*(v/4) + 4*g + v%4
+      if (blk * KEYS + KEYS - 1 > lo) {                       // the block reaches past some row's position
+        const int key0 = blk * KEYS + 4 * g;
+#pragma unroll
+        for (int kt = 0; kt < KT; kt++)
+#pragma unroll
+          for (int v = 0; v < 16; v++)
+            if (key0 + kt * 32 + 8 * (v >> 2) + (v & 3) > lim) s[kt][v] = -INFINITY;
+      }
+      float mb = -INFINITY;
+#pragma unroll
+      for (int kt = 0; kt < KT; kt++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) mb = fmaxf(mb, s[kt][v]);
+      mb = fmaxf(mb, __shfl_xor(mb, 32, 64)) * c2;
+      const bool move = mb > m_run + 8.f;                     // also the first finite maximum after -inf
+      if (__any(move)) {
+        const float m_new = move ? mb : m_run;
+        const float corr = move ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
+        l_run *= corr;
+        m_run = m_new;
+#pragma unroll
+        for (int db = 0; db < DB; db++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) o[db][v] *= corr;
+      }
+      const float m_use = m_run == -INFINITY ? 0.f : m_run;   // nothing seen yet: every term below is 0
+      float ls = 0.f;
+#pragma unroll
+      for (int kt = 0; kt < KT; kt++)
+#pragma unroll
+        for (int u = 0; u < 2; u++) {                         // 16 keys: the lane's own values v = 8u .. 8u+7
+          float x[8];
+#pragma unroll
+          for (int e = 0; e < 8; e++) { x[e] = __builtin_amdgcn_exp2f(fmaf(s[kt][8 * u + e], c2, -m_use)); ls += x[e]; }
+          u32x4_t phi, plo;
+          split8(x, phi, plo);
+#pragma unroll
+          for (int db = 0; db < DB; db++) {
+            const unsigned char *vp = vt_lds + (db * 32 + c) * L::vstr + (32 * kt + 16 * u + 4 * g) * 2;
+            const u32x2_t v0 = *(const u32x2_t *)vp, v1 = *(const u32x2_t *)(vp + 16);
+            const u32x4_t vf = {v0.x, v0.y, v1.x, v1.y};
+            o[db] = mfma_bf16(vf, phi, o[db]);
+            o[db] = mfma_bf16(vf, plo, o[db]);
+          }
+        }
+      ls += __shfl_xor(ls, 32, 64);
+      l_run += ls;
+    }
+    __syncthreads();                                          // block blk+1 staged; everyone is done with block blk
+  }
+  if (!valid) return;
+  const float inv = 1.f / l_run;
+  bf16_t *orow = (bf16_t *)a.out + ((size_t)i * a.hq + h) * HD;
+#pragma unroll
+  for (int db = 0; db < DB; db++)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; q4++) {
+      u32x2_t w;
+      w.x = pack_bf16x2(o[db][4 * q4 + 0] * inv, o[db][4 * q4 + 1] * inv);
+      w.y = pack_bf16x2(o[db][4 * q4 + 2] * inv, o[db][4 * q4 + 3] * inv);
+      *(u32x2_t *)(orow + db * 32 + 8 * q4 + 4 * g) = w;
+    }
+}
+
+template <int HD, int WAVES>
+static hipError_t launch_causal(const AttnArgs &a, hipStream_t st) {
+  constexpr int kLds = 2 * CausalLds<HD>::buf;
+  static bool attr_done[64] = {};                             // per device: the attribute belongs to the device's copy of the code
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64 || !attr_done[dev]) {
+    e = hipFuncSetAttribute((const void *)attn_causal_kernel<HD, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < 64) attr_done[dev] = true;
+  }
+  const long long grid = (long long)a.hq * ((a.rows + WAVES * 32 - 1) / (WAVES * 32));
+  if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((attn_causal_kernel<HD, WAVES>), dim3((unsigned)grid), dim3(WAVES * 64), kLds, st, a);
+  return hipGetLastError();
+}
+
 template <typename T, int HD, int G>
 static hipError_t launch_thg(AttnArgs a, int max_pos, hipStream_t st) {
   hipError_t e;
-  if (sizeof(T) == 2) {
+  if constexpr (sizeof(T) == 2) {
+    // a long chain: no parts, no tail.  Shorter ones leave most of the chip idle with 128-row tiles: 200 rows over 300 keys 26.7
+    // us against 25.8 with parts, 256 over 256 (32 kv heads) 27.7 against 39.1
+    if (a.anc == nullptr && a.rows >= kChainRows) return launch_causal<HD, 4>(a, st);
     // hybrid: matrix-core bulk over [0, A(max_pos)) and the vector tail of every row in one launch
     a.tail_only = 1;
     a.bulk_keys = bulk_end(max_pos);

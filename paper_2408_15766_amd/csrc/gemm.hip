@@ -744,19 +744,46 @@ static hipError_t launch_mm_tile(GemmArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 // A compute unit holds one workgroup, so a launch lasts as many rounds as its workgroups fill the 256 compute units.  A round
-// of 256 x 256, 256 x 192 and 128 x 256 tiles (tokens x weight rows) takes 118, 94 and 70 us at K = 4096, i.e. 100 : 80 : 60;
-// the tile with the smallest product is taken, the larger one on a tie (it moves fewer bytes per product).  512 rows at the 7B
-// shape: QKV (2 splits) 55 us with 256 x 192 against 59 and 77, gate/up 98 against 108 and 138, O (4 splits) 29 us with
-// 128 x 256 against 38 and 34, LM head 129 us with 256 x 256 against 170 and 150.
+// of 256 x 256, 256 x 192 and 128 x 256 tiles (tokens x weight rows) takes 118, 94 and 70 us at K = 4096, of which about 6 are
+// filling and draining; the tile with the smallest product is taken, the larger one when they are close (it moves fewer bytes
+// per product).  512 rows at the 7B shape: QKV (2 splits) 55 us with 256 x 192 against 59 and 77, gate/up 98 against 108 and 138,
+// O (4 splits) 29 us with 128 x 256 against 38 and 34, LM head 129 us with 256 x 256 against 170 and 150.
+static float mm_us(int tile, int m, int sets, int blocks, int in, int n_split) {
+  const int tok = tile == 2 ? 128 : 256, wb = tile == 1 ? 6 : 8;
+  const float at4096 = tile == 0 ? 112.f : (tile == 1 ? 88.f : 64.f);
+  const long long wgs = (long long)((m + tok - 1) / tok) * sets * ((blocks + wb - 1) / wb) * n_split;
+  return (float)((wgs + 255) / 256) * (at4096 * (float)in / (4096.f * (float)n_split) + 6.f);
+}
+static int mm_tile(int m, int sets, int blocks, int in, int n_split, float *us) {
+  int best = 0;
+  float t = mm_us(0, m, sets, blocks, in, n_split);
+  for (int tile = 1; tile < 3; tile++) {
+    const float u = mm_us(tile, m, sets, blocks, in, n_split);
+    if (u < 0.97f * t) { t = u; best = tile; }                // (launches of several rounds do not end exactly round by round)
+  }
+  if (us) *us = t;
+  return best;
+}
 static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
-  auto cost = [&](int tok, int blocks, int per_round) {
-    const long long wgs = (long long)((a.m + tok - 1) / tok) * (a.x2 ? 2 : 1) * ((a.total_blocks + blocks - 1) / blocks) * a.n_split;
-    return (wgs + 255) / 256 * per_round;
-  };
-  const long long c256 = cost(256, 8, 100), c192 = cost(256, 6, 80), c128 = cost(128, 8, 60);
-  if (c256 <= c192 && c256 <= c128) return launch_mm_tile<2, 4, 2>(a, st);
-  if (c192 <= c128) return launch_mm_tile<4, 2, 3>(a, st);
-  return launch_mm_tile<2, 2, 2>(a, st);
+  switch (mm_tile(a.m, a.x2 ? 2 : 1, a.total_blocks, a.in, a.n_split, nullptr)) {
+    case 0: return launch_mm_tile<2, 4, 2>(a, st);
+    case 1: return launch_mm_tile<4, 2, 3>(a, st);
+    default: return launch_mm_tile<2, 2, 2>(a, st);
+  }
+}
+// K splits for m > 128 rows: more of them fill the chip when the tiles do not, and each writes and reads m * rows partial sums
+// (at about 4 TB/s).  7B O projection: 512 rows 29 us + 17 of sums with four splits, 2048 rows 70 + 17 with one (66 + 33 with two).
+int gemm_rows_split(int m, int rows, int in, int max_split) {
+  const int blocks = (rows + 31) / 32, slabs = (in + 255) / 256;
+  int best = 1;
+  float t = 0.f;
+  for (int s = 1; s <= max_split && (s == 1 || slabs / s >= 4); s++) {
+    float u;
+    mm_tile(m, 1, blocks, in, s, &u);
+    u += (float)s * (float)m * (float)rows * (8.f / 4e6f);
+    if (s == 1 || u < t) { t = u; best = s; }
+  }
+  return best;
 }
 
 // Copies into the LDS need 16-byte aligned sources, and the kernel's offsets inside a tile are 32-bit.

@@ -55,6 +55,8 @@ struct GemmArgs {
 hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st);
 hipError_t gemm_init();                 // one-time kernel attributes; call outside any stream capture
 int gemm_k_per_slab(int dtype);
+// K splits (at most max_split) of a bf16 projection over m > 128 rows: a function of the shape and m
+int gemm_rows_split(int m, int rows, int in, int max_split);
 int gemm_k_per_iter(int dtype);
 // Packed layout of a row-major [rows, in] matrix (see gemm.hip): size in bytes, and the out-of-place repack.
 size_t packed_weight_bytes(int dtype, int rows, int in);
@@ -107,6 +109,8 @@ struct AttnArgs {
   void *out;
   int tail_only, bulk_keys, bulk_blocks, bulk_parts, q_groups;   // set by launch_attention (hybrid matrix-core / vector split)
 };
+// bf16 chains (anc == nullptr) of at least this many rows run without partial outputs and leave `part` alone.
+constexpr int kChainRows = 256;
 hipError_t launch_attention(int dtype, const AttnArgs &a, int max_pos, hipStream_t st);
 
 // ---- hca.hip ---------------------------------------------------------------------------------

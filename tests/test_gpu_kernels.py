@@ -348,3 +348,30 @@ def test_attention_long_context_matches_oracle(env, q_scale):
             want.append(attention_row(q3[i, h], k3[vis, h // 4], v3[vis, h // 4]))
             got.append(got_all[i, h])
     assert attention_error_ok(np.array(got), np.array(want), "bf16", np.abs(vc).max())
+
+
+@pytest.mark.parametrize("rows,hq,hkv,hd,base,order", [(257, 4, 4, 128, 0, "chain"), (256, 8, 8, 64, 63, "chain"), (300, 8, 1, 128, 64, "chain"),
+                                                       (289, 16, 8, 128, 1000, "chain"), (260, 4, 2, 64, 5, "reversed"), (270, 2, 1, 128, 130, "scattered")])
+def test_attention_of_a_long_chain_matches_fp64(env, rows, hq, hkv, hd, base, order):
+    """256 rows and more without a tree (prefill): ragged row tiles and key blocks, grouped heads, head counts with and without
+    the placement over eight L2s, empty and long caches, rows that do not stand in order of position (the caller may pass any
+    depths); peaked scores so that the running maximum moves."""
+    torch, P = env
+    rng = np.random.default_rng(case_seed("chain", rows, hq, hd))
+    depth = {"chain": np.arange(rows), "reversed": np.arange(rows)[::-1], "scattered": rng.integers(0, rows, rows)}[order].astype(np.int32)
+    q = rand_storage(rng, (rows, hq * hd), "bf16", 4.0) * 1.01            # queries are fp32: not exact in bf16
+    kc = rand_storage(rng, (base + rows, hkv * hd), "bf16")
+    vc = rand_storage(rng, (base + rows, hkv * hd), "bf16")
+    out = P.spec_k_attention(to_dev(torch, q, "fp32"), to_dev(torch, kc, "bf16"), to_dev(torch, vc, "bf16"), base,
+                             torch.from_numpy(depth.copy()).cuda(), None, hq, hkv, hd)
+    got = out.float().cpu().numpy().reshape(rows, hq, hd).astype(np.float64)
+    q3 = q.astype(np.float32).reshape(rows, hq, hd).astype(np.float64)
+    k3, v3 = kc.reshape(-1, hkv, hd).astype(np.float64), vc.reshape(-1, hkv, hd).astype(np.float64)
+    want = np.empty_like(got)
+    hidden = np.arange(base + rows)[None] > (base + depth)[:, None]
+    for h in range(hq):
+        sc = q3[:, h] @ k3[:, h * hkv // hq].T / np.sqrt(hd)
+        sc[hidden] = -np.inf
+        p = np.exp(sc - sc.max(1, keepdims=True))
+        want[:, h] = p @ v3[:, h * hkv // hq] / p.sum(1, keepdims=True)
+    assert attention_error_ok(got, want, "bf16", np.abs(vc).max())
