@@ -844,7 +844,12 @@ int spec_accept(spec_ctx *c, const spec_tree *tree, int32_t *out_tokens, int32_t
   phase_begin(c, 2);
   if (g.temperature > 0.f && c->st.n_nodes > 0 && c->st.sampled) {
     // sampled children: the ratio rule against the draft rows kept while drafting (c->part serves as its scratch)
-    HIPCHK(c, launch_accept_qratio(c->logits, c->st_qrows, c->st_qrow_of, g.vocab, g.temperature, c->t_tok, c->t_par, N, g.seed, c->cycle,
+    const int q_rows = c->st.n_expanded + (c->st.rows[0] ? 1 : 0);
+    float2 *q_stat = (float2 *)c->sc_val;                      // the drafting top-k's scratch: kMaxTopK^2 floats a slice, two per row wanted
+    static_assert(kMaxTopK * kMaxTopK >= 2 * kMaxNodes, "one pair per draft row and slice fits");
+    HIPCHK(c, launch_rows_softmax_stats(c->logits, N, g.vocab, g.temperature, c->stats, c->stream));
+    if (q_rows > 0) HIPCHK(c, launch_rows_softmax_stats(c->st_qrows, q_rows, g.vocab, g.temperature, q_stat, c->stream));
+    HIPCHK(c, launch_accept_qratio(c->logits, c->st_qrows, c->st_qrow_of, c->stats, q_stat, g.vocab, g.temperature, c->t_tok, c->t_par, N, g.seed, c->cycle,
                                    c->part, c->acc, c->stream));
   } else if (g.temperature > 0.f) {
     HIPCHK(c, launch_rows_softmax_stats(c->logits, N, g.vocab, g.temperature, c->stats, c->stream));
@@ -1132,7 +1137,7 @@ int spec_k_accept_qratio(const float *p_logits, const float *q_logits, int32_t n
   if (!p_logits || !q_logits || !tree_tok || !tree_par || !work || !result || n_nodes < 1 || n_nodes > kMaxNodes || vocab < 1 ||
       !(temperature > 0.f))
     return SPEC_EINVAL;
-  return launch_accept_qratio(p_logits, q_logits, nullptr, vocab, temperature, tree_tok, tree_par, n_nodes, seed, cycle, work,
+  return launch_accept_qratio(p_logits, q_logits, nullptr, nullptr, nullptr, vocab, temperature, tree_tok, tree_par, n_nodes, seed, cycle, work,
                               (AcceptResult *)result, (hipStream_t)stream) == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 

@@ -192,7 +192,9 @@ hipError_t launch_accept_sample(const float *logits, int vocab, const float2 *st
 // The ratio rule for sampled children: p_logits[i], q_logits[i] are the target / draft logit rows AT node i (fp32,
 // row stride vocab); children are tried in node order; work: vocab floats of scratch.
 // qrow_of (nullable): node -> row of q_logits holding the draft's logits at that node (-1: the node has no children).
-hipError_t launch_accept_qratio(const float *p_logits, const float *q_logits, const int *qrow_of, int vocab, float temp,
+// p_stat / q_stat (both or neither nullptr): launch_rows_softmax_stats of the target rows / of the rows of q_logits at this temperature.
+hipError_t launch_accept_qratio(const float *p_logits, const float *q_logits, const int *qrow_of, const float2 *p_stat,
+                                const float2 *q_stat, int vocab, float temp,
                                 const int *tree_tok, const int *tree_par, int n_nodes, uint64_t seed, uint32_t cycle, float *work,
                                 AcceptResult *res, hipStream_t st);
 
