@@ -8,10 +8,16 @@
 // flash-attention loop over blocks of kBlockKeys keys staged in LDS.  The band is J-1 single keys per
 // query, different for every query, and is folded in afterwards by the lanes that own the query.
 //
-// Work decomposition: a workgroup = 4 wavefronts = 128 consecutive queries of one (batch, head); a wavefront
+// Work decomposition: a workgroup = 8 wavefronts = 256 (or 4 = 128) consecutive queries of one (batch, head); a wavefront
 // owns 32 queries (one MFMA column block).  S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16, so a
 // lane holds, for ITS query (lane % 32), 16 keys of every 32-key tile and 64 of the 128 output dims, and
-// the softmax needs one exchange with lane ^ 32 only.
+// the softmax needs one exchange with lane ^ 32 only (by a permute of the vector unit; a query's two lanes add up their
+// own sums and meet once, at the end).
+// Bound: the serial chain of a block inside a wavefront (LDS reads, matrix instructions, maximum, exponentials), with two
+// wavefronts per SIMD to cover each other; a wavefront's share of the staging is part of it and halves with 8 wavefronts.
+// Measured (MI355X, us, launches back to back): batch 2 x 2048, 32 heads of 128, three streams 115.7 -> 100 with 8
+// wavefronts; with 4: batch 2 x 1024 45.3 -> 42.6 (value rows read whole 1.5 of it, the maximum without a shuffle 0.3),
+// 333 x 16 heads of 64 10.5 -> 10.0.
 #include "common.h"
 #include "kernels.h"
 
@@ -24,9 +30,6 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
-constexpr int kHcaWaves = 4;
-constexpr int kHcaThreads = kHcaWaves * 64;
-constexpr int kHcaRows = kHcaWaves * 32;      // queries per workgroup
 constexpr int kKeyTiles = 2;                  // 32-key MFMA tiles per staged block
 constexpr int kBlockKeys = 32 * kKeyTiles;
 
@@ -36,13 +39,22 @@ __device__ __forceinline__ f32x16_t mfma16(const u32x4_t &a, const u32x4_t &b, f
 __device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-template <int HD> struct HcaLds {
+// Maximum over the lanes l and l ^ 32, in both, without the LDS round trip of a shuffle.
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <int HD, int WAVES> struct HcaLds {
   static constexpr int kstr = HD * 2 + 16;              // bytes per staged key row (+16: conflict-free b128 reads)
   static constexpr int vstr = kBlockKeys * 2 + 8;       // bytes per dim row of V^T (+8: conflict-free b64 reads)
-  static constexpr int buf = kBlockKeys * kstr + HD * vstr;
+  // A wavefront stages whole value rows (HD / 8 lanes a row, 512 / HD key pairs), eight dims a lane: the lanes of dims 32
+  // apart would store to the same banks, so every 32 dims start 512 / HD words further on.
+  static constexpr int vpad = 512 / HD * 4;
+  static constexpr int buf = kBlockKeys * kstr + HD * vstr + HD / 32 * vpad;
   static constexpr int brow = HD * 2 + 16;              // band scratch: bytes per key (or value) row
   static constexpr int bwave = 2 * 32 * brow;           // ... per wavefront: 32 key rows + 32 value rows
-  static constexpr int total = 2 * buf > kHcaWaves * bwave ? 2 * buf : kHcaWaves * bwave;   // main loop double-buffered
+  static constexpr int total = 2 * buf > WAVES * bwave ? 2 * buf : WAVES * bwave;   // main loop double-buffered
 };
 
 // Orders this wavefront's LDS writes before its later LDS reads of other lanes' data.  The LDS executes
@@ -53,15 +65,16 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int HD>
-__global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void hca_attention_kernel(HcaArgs a) {
-  using L = HcaLds<HD>;
+template <int HD, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void hca_attention_kernel(HcaArgs a) {
+  using L = HcaLds<HD, WAVES>;
+  constexpr int NT = WAVES * 64, ROWS = WAVES * 32;   // threads, queries per workgroup
   constexpr int DB = HD / 32;                 // 32-dim blocks of the output
   constexpr int KK = HD / 16;                 // MFMA steps of q.k
   constexpr int PPR = HD * 2 / 16;            // 16-byte pieces per key row
-  constexpr int KP = kBlockKeys * PPR / kHcaThreads;          // K pieces per thread per block
-  constexpr int VP = kBlockKeys / 2 * PPR / kHcaThreads;      // V (key pair, piece) items per thread per block
-  static_assert(kBlockKeys * PPR % kHcaThreads == 0 && (kBlockKeys / 2 * PPR) % kHcaThreads == 0, "staging split");
+  constexpr int KP = kBlockKeys * PPR / NT;          // K pieces per thread per block
+  constexpr int VP = kBlockKeys / 2 * PPR / NT;      // V (key pair, piece) items per thread per block
+  static_assert(kBlockKeys * PPR % NT == 0 && (kBlockKeys / 2 * PPR) % NT == 0, "staging split");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
   // Workgroup id -> (batch, kv head, head of the group, query tile).  Ids 8 apart run on one XCD: all tiles and heads that
@@ -74,7 +87,7 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
   // of 8 the XCD placement would leave XCDs idle or uneven; the ids then run chunk by chunk over all groups.)
   constexpr int kHcaChunk = 8;
   const int G = a.hq / a.hkv;
-  const int n_qt = (a.seq + kHcaRows - 1) / kHcaRows;
+  const int n_qt = (a.seq + ROWS - 1) / ROWS;
   const int n_grp = a.batch * a.hkv;
   const bool affine = (n_grp & 7) == 0;
   const int grp_per_list = affine ? n_grp >> 3 : n_grp;      // groups whose workgroups form one ordered list
@@ -89,7 +102,7 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const int grp = affine ? grp_local * 8 + ((int)blockIdx.x & 7) : grp_local;
   const int bi = grp / a.hkv, hk = grp % a.hkv;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 31, g = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 31, g = lane >> 5;
   const int T = a.seq, J = a.n_streams;
   const float c2 = a.scale_log2e;
   const size_t kv_stride = (size_t)a.hkv * HD;                // elements between consecutive positions
@@ -97,11 +110,11 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const bf16_t *kg = (const bf16_t *)a.k[0] + kv_off;
   const bf16_t *vg = (const bf16_t *)a.v[0] + kv_off;
 
-  const int r0 = qt * kHcaRows + wave * 32;   // first query of the wavefront
+  const int r0 = qt * ROWS + wave * 32;   // first query of the wavefront
   const int t = r0 + c;
   const int tq = min(t, T - 1);               // queries past the end compute on the last one and are not stored
   const int lim = tq - (J - 1);               // last old-region key of this query (may be negative: none)
-  const int wg_lim = min(qt * kHcaRows + kHcaRows - 1, T - 1) - (J - 1);
+  const int wg_lim = min(qt * ROWS + ROWS - 1, T - 1) - (J - 1);
   const int nb = wg_lim >= 0 ? wg_lim / kBlockKeys + 1 : 0;
   const int wave_lim = min(r0 + 31, T - 1) - (J - 1);
 
@@ -112,13 +125,13 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
   uint32_t koff[KP], voff[VP];
 #pragma unroll
   for (int e = 0; e < KP; e++) {
-    const int q = tid + e * kHcaThreads;
+    const int q = tid + e * NT;
     koff[e] = (uint32_t)((q / PPR) * kv_stride + (q % PPR) * 8) * kEsz;
   }
 #pragma unroll
   for (int e = 0; e < VP; e++) {
-    const int q = tid + e * kHcaThreads;
-    voff[e] = (uint32_t)((2 * (q % (kBlockKeys / 2))) * kv_stride + (q / (kBlockKeys / 2)) * 8) * kEsz;
+    const int q = tid + e * NT;
+    voff[e] = (uint32_t)((2 * (q / PPR)) * kv_stride + (q % PPR) * 8) * kEsz;
   }
   const uint32_t row_bytes = (uint32_t)kv_stride * kEsz;
   u32x4_t kreg[KP], vreg[VP][2];
@@ -136,14 +149,14 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
     } else {
 #pragma unroll
       for (int e = 0; e < KP; e++) {
-        const int q = tid + e * kHcaThreads;
+        const int q = tid + e * NT;
         const int key = min(blk * kBlockKeys + q / PPR, T - 1);
         kreg[e] = *(const u32x4_t *)(kg + (size_t)key * kv_stride + (q % PPR) * 8);
       }
 #pragma unroll
       for (int e = 0; e < VP; e++) {
-        const int q = tid + e * kHcaThreads;
-        const int pair = q % (kBlockKeys / 2), piece = q / (kBlockKeys / 2);
+        const int q = tid + e * NT;
+        const int pair = q / PPR, piece = q % PPR;
         const int key0 = min(blk * kBlockKeys + 2 * pair, T - 1), key1 = min(blk * kBlockKeys + 2 * pair + 1, T - 1);
         vreg[e][0] = *(const u32x4_t *)(vg + (size_t)key0 * kv_stride + piece * 8);
         vreg[e][1] = *(const u32x4_t *)(vg + (size_t)key1 * kv_stride + piece * 8);
@@ -154,27 +167,27 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
     unsigned char *k_lds = lds + buf * L::buf, *vt_lds = k_lds + kBlockKeys * L::kstr;
 #pragma unroll
     for (int e = 0; e < KP; e++) {
-      const int q = tid + e * kHcaThreads;
+      const int q = tid + e * NT;
       *(u32x4_t *)(k_lds + (q / PPR) * L::kstr + (q % PPR) * 16) = kreg[e];
     }
 #pragma unroll
     for (int e = 0; e < VP; e++) {                            // V^T[dim][key], two keys per 32-bit store
-      const int q = tid + e * kHcaThreads;
-      const int pair = q % (kBlockKeys / 2), piece = q / (kBlockKeys / 2);
+      const int q = tid + e * NT;
+      const int pair = q / PPR, piece = q % PPR;
       const uint32_t w0[4] = {vreg[e][0].x, vreg[e][0].y, vreg[e][0].z, vreg[e][0].w};
       const uint32_t w1[4] = {vreg[e][1].x, vreg[e][1].y, vreg[e][1].z, vreg[e][1].w};
 #pragma unroll
       for (int d2 = 0; d2 < 8; d2++) {
         const uint32_t x = (d2 & 1) ? ((w0[d2 >> 1] >> 16) | (w1[d2 >> 1] & 0xFFFF0000u))
                                     : ((w0[d2 >> 1] & 0xFFFFu) | (w1[d2 >> 1] << 16));
-        *(uint32_t *)(vt_lds + (piece * 8 + d2) * L::vstr + pair * 4) = x;
+        *(uint32_t *)(vt_lds + (piece * 8 + d2) * L::vstr + (piece >> 2) * L::vpad + pair * 4) = x;
       }
     }
   };
 
   // V^T fragment (A operand) of 16-key step st = 2*tile + half and dim block db: keys step*16 + 4g + {0..3, 8..11}
   auto vread = [&](const unsigned char *vt_lds, int st, int db) {
-    const unsigned char *vp = vt_lds + (db * 32 + c) * L::vstr + (16 * st + 4 * g) * 2;
+    const unsigned char *vp = vt_lds + (db * 32 + c) * L::vstr + db * L::vpad + (16 * st + 4 * g) * 2;
     const u32x2_t v0 = *(const u32x2_t *)vp, v1 = *(const u32x2_t *)(vp + 16);
     return u32x4_t{v0.x, v0.y, v1.x, v1.y};
   };
@@ -241,7 +254,7 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
       const float m_use = m_new == -INFINITY ? 0.f : m_new;
       const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
       const float p = have ? __builtin_amdgcn_exp2f(sc - m_use) : 0.f;
-      l_run = l_run * corr + p;
+      l_run = l_run * corr + (g == 0 ? p : 0.f);               // the two lanes of a query add up their sums at the end
       m_run = m_new;
 #pragma unroll
       for (int db = 0; db < DB; db++)
@@ -300,7 +313,7 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
       for (int kt = 0; kt < kKeyTiles; kt++)
 #pragma unroll
         for (int v = 0; v < 16; v++) mb = fmaxf(mb, s[kt][v]);
-      mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
+      mb = max_halves(mb);
       // The reference maximum moves only when the block's maximum exceeds it by more than 2^8: until then
       // the probabilities are taken against the old reference (at most 2^8, harmless in fp32 and bf16, and
       // the final division by the sum cancels the choice), and the 64 output registers are left alone.
@@ -337,14 +350,13 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
           for (int db = 0; db < DB; db++) o[db] = mfma16(vread(vt_lds, 2 * kt + h, db), pf, o[db]);
         }
       }
-      ls += __shfl_xor(ls, 32, 64);
       l_run += ls;
     }
     __syncthreads();                                          // block blk+1 staged; everyone is done with block blk
   }
 
+  const float inv = 1.f / (l_run + __shfl_xor(l_run, 32, 64));
   if (t >= T) return;
-  const float inv = 1.f / l_run;
   bf16_t *orow = (bf16_t *)a.out + (((size_t)bi * T + t) * a.hq + (size_t)hk * G + gh) * HD;
 #pragma unroll
   for (int db = 0; db < DB; db++)
@@ -357,23 +369,41 @@ __global__ __launch_bounds__(kHcaThreads) __attribute__((amdgpu_waves_per_eu(2, 
     }
 }
 
-template <int HD>
-hipError_t launch_hd(const HcaArgs &a, hipStream_t st) {
+// Workgroups of 8 wavefronts pay from long walks on (a tile's start, its band and the unequal lengths of its wavefronts at the
+// diagonal weigh more than in a tile of 128) and need two for each of the 256 compute units, or longest-first order has
+// nothing left to even out.  Measured (us, 4 -> 8 wavefronts): 512 workgroups of 2048 positions (batch 2, 32 heads) 131 -> 123, of
+// 4096 (32 heads) 184 -> 167; 256 of 2048 (32 heads) 74 -> 80, 512 and more of 256 .. 700 5 .. 30 % slower, 1500 (batch 3)
+// 114 -> 118, 1800 equal.  Head dim 64 has too few pieces per block for 512 threads to stage.
+constexpr long long kWideWorkgroups = 512;
+constexpr int kWideSeq = 2048;
+
+template <int HD, int WAVES>
+hipError_t launch_waves(const HcaArgs &a, hipStream_t st) {
+  constexpr int kLds = HcaLds<HD, WAVES>::total;
   static bool attr_done[64] = {};                             // per device: the attribute belongs to the device's copy of the code
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64 || !attr_done[dev]) {
-    e = hipFuncSetAttribute((const void *)hca_attention_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, HcaLds<HD>::total);
+    e = hipFuncSetAttribute((const void *)hca_attention_kernel<HD, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64) attr_done[dev] = true;
   }
   const int G = a.hq / a.hkv;
-  const int n_qt = (a.seq + kHcaRows - 1) / kHcaRows;
+  const int n_qt = (a.seq + WAVES * 32 - 1) / (WAVES * 32);
   const long long grid = (long long)a.batch * a.hkv * G * n_qt;
   if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((hca_attention_kernel<HD>), dim3((unsigned)grid), dim3(kHcaThreads), HcaLds<HD>::total, st, a);
+  hipLaunchKernelGGL((hca_attention_kernel<HD, WAVES>), dim3((unsigned)grid), dim3(WAVES * 64), kLds, st, a);
   return hipGetLastError();
+}
+
+template <int HD>
+hipError_t launch_hd(const HcaArgs &a, hipStream_t st) {
+  if constexpr (HD == 128) {
+    const long long wgs = (long long)a.batch * a.hq * ((a.seq + 255) / 256);
+    if (a.seq >= kWideSeq && wgs >= kWideWorkgroups) return launch_waves<HD, 8>(a, st);
+  }
+  return launch_waves<HD, 4>(a, st);
 }
 
 }  // namespace

@@ -69,6 +69,25 @@ def test_hca_attention_matches_oracle(env, n_streams, batch, seq, hq, hkv, hd):
         check(got[b], want, vs)
 
 
+@pytest.mark.parametrize("n_streams,batch,seq,hq,hkv", [
+    (8, 1, 2049, 64, 8),     # one query in the last 256-query tile, the band across the tiles' edge
+    (3, 2, 2048, 32, 2),     # whole tiles; kv groups not a multiple of 8
+    (2, 1, 2207, 64, 64),    # wavefronts of the last tile without a query, ragged key block
+    (2, 1, 2047, 64, 8),     # just too short for wide workgroups
+    (2, 1, 2048, 32, 8),     # too few of them
+])
+def test_hca_attention_wide_workgroups(env, n_streams, batch, seq, hq, hkv):
+    # launches of 256-query workgroups (head dim 128, long sequences that fill the chip), and two that just miss the rule
+    torch, P = env
+    q, ks, vs = wl.make_hca_streams(16, n_streams, batch, seq, hq, hkv, 128)
+    got = run_gpu(torch, P, q, ks, vs)
+    heads = [0, hq - 1]
+    for b in range(batch):
+        want = hca.hca_attention(q[b].astype(np.float64), [k[b].astype(np.float64) for k in ks],
+                                 [v[b].astype(np.float64) for v in vs], heads=heads)
+        check(got[b], want, vs, heads=heads)
+
+
 def test_hca_attention_peaked_scores(env):
     # wide score range: the running maximum moves from block to block and the rescaling path runs
     torch, P = env
