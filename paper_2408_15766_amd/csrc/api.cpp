@@ -218,7 +218,6 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   const bool bf16 = c.dtype == SPEC_DTYPE_BF16;
   const int m_small = std::max({c.tree_total, kMaxDepth + 1, c.tree_topk});    // rows of any forward but a prompt's
   const int m_max = std::max(m_small, std::min(prefill_chunk(c), c.max_seq));
-  const int attn_rows = bf16 ? std::min(m_max, kChainRows) : m_max;   // more bf16 rows (a prompt's) write no partial outputs
   const int k = std::max(1, c.tree_topk), D = std::max(1, c.tree_depth);
   const int seq_draft = c.max_seq + D * k;
   const int max_parts = (c.max_seq + D * k) / kAttnPart + 2;   // parts of the longest row + the tail slot
@@ -248,7 +247,9 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   TAKE(gfeat, void *, (size_t)m_max * d * esz)
   TAKE(pend_feat, void *, (size_t)(kMaxDepth + 1) * d * esz)
   TAKE(part, float *, part_floats * 4)
-  TAKE(attn_part, float *, (size_t)attn_rows * c.n_q_heads * max_parts * (c.head_dim + 2) * 4)
+  // rows that write a partial per part (fp32: all; bf16: a block of a chain's), or one per row (a long chain's tails)
+  const size_t partials = bf16 ? std::max((size_t)std::min(m_max, kPartialRows) * max_parts, (size_t)m_max) : (size_t)m_max * max_parts;
+  TAKE(attn_part, float *, partials * c.n_q_heads * (c.head_dim + 2) * 4)
   TAKE(logits, float *, (size_t)std::max(c.tree_total, 1) * v * 4)
   TAKE(dlogits, float *, (size_t)kMaxTopK * v * 4)
   TAKE(rope, float2 *, (size_t)m_max * (c.head_dim / 2) * 8)

@@ -27,12 +27,14 @@
 //    that they keep fp32-class accuracy.  The remaining positions [A(p), p] (16..47 keys: the end
 //    of the cache plus the row's own path) take the vector path.  A(p) depends on the position
 //    only, so a row is computed by the same instructions over the same key groups whether it is
-//    alone or part of a tree.
+//    alone or part of a tree.  A prompt of hundreds of rows takes a kernel of its own (attn_chain_kernel) that repeats
+//    this arithmetic step by step, merge included: its rows have the bits they would have alone.
 //
 // Parts (fixed absolute boundaries: attn_part_begin; larger parts for far keys, where a long context would otherwise
 // mean many partials to merge and many short workgroups) are merged per row in ascending order, the tail
 // last, by attn_combine_kernel.  In the hybrid path the bulk and the tail are independent and run in ONE
 // launch (different workgroups), so the chain per layer is two dependent kernels.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -366,15 +368,12 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 
 // x = hi + lo with hi, lo bf16: the pair keeps ~16 mantissa bits of an fp32 value.
-// rest (if wanted): what the pair leaves over, as a third bf16 (24 mantissa bits in all: an fp32 value exactly).
-__device__ __forceinline__ void split8(const float (&x)[8], u32x4_t &hi, u32x4_t &lo, u32x4_t *rest = nullptr) {
+__device__ __forceinline__ void split8(const float (&x)[8], u32x4_t &hi, u32x4_t &lo) {
   uint32_t h[4], l[4];
 #pragma unroll
   for (int e = 0; e < 4; e++) {
     h[e] = pack_bf16x2(x[2 * e], x[2 * e + 1]);
-    const float r0 = x[2 * e] - __uint_as_float(h[e] << 16), r1 = x[2 * e + 1] - __uint_as_float(h[e] & 0xFFFF0000u);
-    l[e] = pack_bf16x2(r0, r1);
-    if (rest) (*rest)[e] = pack_bf16x2(r0 - __uint_as_float(l[e] << 16), r1 - __uint_as_float(l[e] & 0xFFFF0000u));
+    l[e] = pack_bf16x2(x[2 * e] - __uint_as_float(h[e] << 16), x[2 * e + 1] - __uint_as_float(h[e] & 0xFFFF0000u));
   }
   hi = u32x4_t{h[0], h[1], h[2], h[3]};
   lo = u32x4_t{l[0], l[1], l[2], l[3]};
@@ -598,30 +597,42 @@ static hipError_t launch_hybrid(AttnArgs a, int q_groups, hipStream_t st) {
 }
 
 // ---- many rows of a causal chain (prefill), bf16 storage ---------------------------------------
-// With hundreds of rows a row's keys need no split over workgroups: one workgroup of WAVES wavefronts takes WAVES * 32
-// consecutive rows of one query head and walks all of their keys, 64 at a time, so there are no partial outputs to
-// write and merge (512 rows at 4096 keys, 32 heads: 170 MB of them per layer).  S^T = K Q^T and O^T = V^T P^T as in the
-// bulk above, a lane owns one query, probabilities enter as bf16 hi + lo and queries as three bf16 (exactly: the bulk's rows have sixteen
-// keys each in full fp32, here the third term makes up for them; 0.22 % of the outputs round differently from fp64, 0.26 %
-// with the bulk and tail).  K and V^T blocks are double-buffered in the LDS, the loads of a block run two blocks ahead; the
-// block is 32 keys at head dim 128 because 64 spill beside three query terms (2048 rows 110 us against 154).  The running maximum moves only when a score exceeds it by 2^8 (the
-// terms stay far inside fp32's range and the division by the sum cancels the choice), which spares the 64 output
-// registers a rescaling per block.  Rows may stand at any positions (depth); a block past a wavefront's last position is skipped.
-// Measured (MI355X, us; with parts and merge before): 512 rows, 32 heads 80 -> 28; 1024 rows, 64 heads on 8 kv heads 316 -> 59; 2048
-// rows, 32 on 8 387 -> 110, at 2048 keys before them 666 -> 251.
-template <int HD> struct CausalLds {
-  static constexpr int kKeys = HD == 128 ? 32 : 64;   // keys per staged block: what the registers beside the queries leave
+// The same arithmetic as the hybrid path and its merge, bit for bit, without partial outputs of the bulk in memory: with hundreds of
+// rows a row's keys need no split over workgroups (512 rows at 4096 keys, 32 heads: 170 MB of partials per layer).  The tails run
+// first (attn_tail_kernel: one wavefront per row and kv head, fp32) and leave their partial; then one workgroup of WAVES
+// wavefronts takes WAVES * 32 consecutive rows of one query head and walks their bulk keys twice.  The merge weights a part by
+// exp(its maximum - the row's maximum), so the row's maximum has to be known before the first part is folded in: pass 1 forms
+// the scores for their maximum only (two products, K only), pass 2 runs the online softmax of every part as the hybrid
+// path does (32 keys at a time, from a fresh maximum per part) and folds a finished part into the row's sums.
+// Two sets of output registers (part and row) leave no room for both query terms at head dim 128: the low one is read from the LDS.
+// K and V^T blocks are double-buffered there, the loads of a block run two blocks ahead.  Rows may stand at any positions
+// (depth); a block past a wavefront's last bulk key is skipped (it would add exact zeros).
+// Bound: from one full chip of workgroups on the matrix cores (pass 1 1.7, pass 2 1.0 PFLOP/s), below that the serial chain of a block.
+// Measured (MI355X, us per call, the hybrid path before): 512 rows, 32 heads 99 -> 81 (tails 19, the walk 51); 1024 rows, 64 heads on 8 kv
+// heads 335 -> 157; 2048 rows, 32 on 8 415 -> 200, at 2048 keys before them 696 -> 375; 4096 rows 1309 -> 513.
+template <int HD, int WAVES> struct ChainLds {
+  static constexpr int kScan = 64;                    // keys per staged block in pass 1 ...
+  static constexpr int kKeys = HD == 128 ? 32 : 64;   // ... and in pass 2: what the registers beside queries and outputs leave
   static constexpr int kstr = HD * 2 + 16;            // bytes per staged key row (+16: conflict-free b128 reads)
   static constexpr int vstr = kKeys * 2 + 8;          // bytes per dim row of V^T (+8: conflict-free b64 reads)
-  static constexpr int buf = kKeys * kstr + HD * vstr;
+  static constexpr int scan = kScan * kstr, walk = kKeys * kstr + HD * vstr;
+  static constexpr int buf = scan > walk ? scan : walk;
+  static constexpr bool kQueryLds = HD == 128;
+  static constexpr int total = 2 * buf + (kQueryLds ? WAVES * (HD / 16) * 1024 : 0);
 };
+// a * b rounded to fp32, whatever it is added to afterwards
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
 template <int HD, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_causal_kernel(AttnArgs a) {
-  using L = CausalLds<HD>;
-  constexpr int NT = WAVES * 64, KEYS = L::kKeys, KT = KEYS / 32;
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_chain_kernel(AttnArgs a) {
+  using L = ChainLds<HD, WAVES>;
+  constexpr int NT = WAVES * 64, SCAN = L::kScan, KEYS = L::kKeys, KT = KEYS / 32;
   constexpr int DB = HD / 32, KK = HD / 16, PPR = HD * 2 / 16;
-  constexpr int KP = KEYS * PPR / NT, VP = KEYS / 2 * PPR / NT;
-  static_assert(KEYS * PPR % NT == 0 && KEYS / 2 * PPR % NT == 0, "staging split");
+  constexpr int SP = SCAN * PPR / NT, KP = KEYS * PPR / NT, VP = KEYS / 2 * PPR / NT;
+  static_assert(SCAN * PPR % NT == 0 && KEYS * PPR % NT == 0 && KEYS / 2 * PPR % NT == 0, "staging split");
+  static_assert(kAttnPart % KEYS == 0 && kAttnNear % KEYS == 0 && kAttnFarPart % KEYS == 0, "a part ends with a staged block");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   __shared__ int wave_hi[WAVES];
 
@@ -638,56 +649,24 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
   const int i = (qt * WAVES + wave) * 32 + c;                 // row of this lane
   const bool valid = i < a.rows;
   const int base = a.base_ptr ? *a.base_ptr : a.base;
-  const int lim = valid ? base + a.depth[i] : -1;             // last key position of the row
-  int lo = valid ? lim : 0x7FFFFFFF, hi = lim;                // over the wavefront's rows
+  const int k_end = valid ? bulk_end(base + a.depth[i]) : 0;  // keys [0, k_end) belong to this row's bulk
+  int lo = valid ? k_end : 0x7FFFFFFF, hi = k_end;            // over the wavefront's rows
 #pragma unroll
   for (int o = 1; o < 32; o <<= 1) { lo = min(lo, __shfl_xor(lo, o, 64)); hi = max(hi, __shfl_xor(hi, o, 64)); }
   lo = __builtin_amdgcn_readfirstlane(lo); hi = __builtin_amdgcn_readfirstlane(hi);
   if (lane == 0) wave_hi[wave] = hi;
   __syncthreads();
-  int last = wave_hi[0];                                      // last key position of the workgroup (at least 0: its first row is valid)
+  int k_wg = wave_hi[0];                                      // the workgroup's bulk keys are [0, k_wg)
 #pragma unroll
-  for (int w = 1; w < WAVES; w++) last = max(last, wave_hi[w]);
-  last = __builtin_amdgcn_readfirstlane(last);
-  const int nb = last / KEYS + 1;
+  for (int w = 1; w < WAVES; w++) k_wg = max(k_wg, wave_hi[w]);
+  k_wg = __builtin_amdgcn_readfirstlane(k_wg);
 
   const size_t kv_stride = (size_t)a.hkv * HD;
   const bf16_t *kg = (const bf16_t *)a.kcache + (size_t)hk * HD, *vg = (const bf16_t *)a.vcache + (size_t)hk * HD;
-  u32x4_t kreg[KP], vreg[VP][2];
-  auto prefetch = [&](int blk) {                              // keys past the workgroup's last are read from it and masked
-#pragma unroll
-    for (int e = 0; e < KP; e++) {
-      const int q = tid + e * NT;
-      kreg[e] = *(const u32x4_t *)(kg + (size_t)min(blk * KEYS + q / PPR, last) * kv_stride + (q % PPR) * 8);
-    }
-#pragma unroll
-    for (int e = 0; e < VP; e++) {
-      const int q = tid + e * NT;
-      const int pair = q % (KEYS / 2), piece = q / (KEYS / 2);
-      vreg[e][0] = *(const u32x4_t *)(vg + (size_t)min(blk * KEYS + 2 * pair, last) * kv_stride + piece * 8);
-      vreg[e][1] = *(const u32x4_t *)(vg + (size_t)min(blk * KEYS + 2 * pair + 1, last) * kv_stride + piece * 8);
-    }
-  };
-  auto stage = [&](int b) {
-    unsigned char *k_lds = lds + b * L::buf, *vt_lds = k_lds + KEYS * L::kstr;
-#pragma unroll
-    for (int e = 0; e < KP; e++) {
-      const int q = tid + e * NT;
-      *(u32x4_t *)(k_lds + (q / PPR) * L::kstr + (q % PPR) * 16) = kreg[e];
-    }
-#pragma unroll
-    for (int e = 0; e < VP; e++) {                            // V^T[dim][key], two keys per 32-bit store
-      const int q = tid + e * NT;
-      const int pair = q % (KEYS / 2), piece = q / (KEYS / 2);
-#pragma unroll
-      for (int d2 = 0; d2 < 8; d2++) {
-        const uint32_t x0 = vreg[e][0][d2 >> 1], x1 = vreg[e][1][d2 >> 1];
-        *(uint32_t *)(vt_lds + (piece * 8 + d2) * L::vstr + pair * 4) = (d2 & 1) ? ((x0 >> 16) | (x1 & 0xFFFF0000u)) : ((x0 & 0xFFFFu) | (x1 << 16));
-      }
-    }
-  };
+  // keys past the workgroup's last are read from it and masked
+  auto piece_of = [&](const bf16_t *p, int key, int piece) { return *(const u32x4_t *)(p + (size_t)min(key, k_wg - 1) * kv_stride + piece * 8); };
 
-  u32x4_t qhi[KK], qlo[KK], qrest[KK];                        // step kk covers dims kk*16 + g*8 .. +8 of the lane's query
+  u32x4_t qhi[KK], qlo[KK];                                   // step kk covers dims kk*16 + g*8 .. +8 of the lane's query
   {
     const float *qrow = (const float *)a.q + ((size_t)(valid ? i : a.rows - 1) * a.hq + h) * HD;
 #pragma unroll
@@ -695,143 +674,303 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
       float x[8];
       const float4 x0 = *(const float4 *)(qrow + kk * 16 + g * 8), x1 = *(const float4 *)(qrow + kk * 16 + g * 8 + 4);
       x[0] = x0.x; x[1] = x0.y; x[2] = x0.z; x[3] = x0.w; x[4] = x1.x; x[5] = x1.y; x[6] = x1.z; x[7] = x1.w;
-      split8(x, qhi[kk], qlo[kk], &qrest[kk]);
+      split8(x, qhi[kk], qlo[kk]);
     }
   }
-  f32x16_t o[DB];
+  unsigned char *q_lds = lds + 2 * L::buf + wave * (KK * 1024) + lane * 16;
+  if constexpr (L::kQueryLds) {
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++) *(u32x4_t *)(q_lds + kk * 1024) = qlo[kk];
+  }
+  const float *tail = a.part + (((size_t)(valid ? i : a.rows - 1) * a.hq + h) * a.max_parts + a.max_parts - 1) * (HD + 2);
+  const float m_tail = tail[0];
+
+  // pass 1: the row's largest score
+  float smax = -INFINITY;
+  if (k_wg > 0) {
+    u32x4_t sreg[SP];
+    const int nb = (k_wg + SCAN - 1) / SCAN;
+    auto prefetch = [&](int blk) {
+#pragma unroll
+      for (int e = 0; e < SP; e++) { const int q = tid + e * NT; sreg[e] = piece_of(kg, blk * SCAN + q / PPR, q % PPR); }
+    };
+    auto stage = [&](int b) {
+#pragma unroll
+      for (int e = 0; e < SP; e++) { const int q = tid + e * NT; *(u32x4_t *)(lds + b * L::buf + (q / PPR) * L::kstr + (q % PPR) * 16) = sreg[e]; }
+    };
+    prefetch(0);
+    stage(0);
+    __syncthreads();
+    if (nb > 1) prefetch(1);
+    for (int blk = 0; blk < nb; blk++) {
+      const unsigned char *k_lds = lds + (blk & 1) * L::buf;
+      if (blk + 1 < nb) {                                     // the other buffer was left by everyone at the last barrier
+        stage((blk + 1) & 1);
+        if (blk + 2 < nb) prefetch(blk + 2);
+      }
+      if (blk * SCAN < hi) {                                  // some row of the wavefront has keys here
+        f32x16_t s[2];
+#pragma unroll
+        for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) s[kt][v] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; kk++)
+#pragma unroll
+          for (int kt = 0; kt < 2; kt++) {
+            const u32x4_t kf = *(const u32x4_t *)(k_lds + (kt * 32 + c) * L::kstr + kk * 32 + g * 16);
+            s[kt] = mfma_bf16(kf, qhi[kk], s[kt]);
+            s[kt] = mfma_bf16(kf, qlo[kk], s[kt]);
+          }
+        // s[kt][v] = q . k for key blk*64 + kt*32 + 8*(v/4) + 4*g + v%4
+        if (blk * SCAN + SCAN > lo) {                         // some row ends inside the block
+          const int key0 = blk * SCAN + 4 * g;
+#pragma unroll
+          for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+            for (int v = 0; v < 16; v++)
+              if (key0 + kt * 32 + 8 * (v >> 2) + (v & 3) >= k_end) s[kt][v] = -INFINITY;
+        }
+#pragma unroll
+        for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) smax = fmaxf(smax, s[kt][v]);
+      }
+      __syncthreads();                                        // block blk+1 staged; everyone is done with block blk
+    }
+    smax = fmaxf(smax, __shfl_xor(smax, 32, 64));
+  }
+  const float m_row = fmaxf(smax * a.scale, m_tail);          // (the scale is positive and rounding keeps order)
+  const int n_front = attn_parts_covering(k_end);
+  const bool few = n_front + 1 <= kCombineFew;                // the merge rounds a part's weighted sum only when there are many
+
+  f32x16_t o[DB], row[DB];                                    // output of the part under way, and of the row
 #pragma unroll
   for (int db = 0; db < DB; db++)
 #pragma unroll
-    for (int v = 0; v < 16; v++) o[db][v] = 0.f;
-  const float c2 = a.scale * 1.4426950408889634f;             // scores in units of log2
-  float m_run = -INFINITY, l_run = 0.f;
+    for (int v = 0; v < 16; v++) o[db][v] = row[db][v] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f, l_row = 0.f;
+  auto weigh = [&](float l, float m, float &w) {
+    w = __expf(m - m_row);
+    const float lw = mul_rounded(l, w);
+    l_row = few ? fmaf(l, w, l_row) : l_row + lw;
+  };
 
-  prefetch(0);
-  stage(0);
-  __syncthreads();
-  if (nb > 1) prefetch(1);
-  for (int blk = 0; blk < nb; blk++) {
-    const int cur = blk & 1;
-    const unsigned char *k_lds = lds + cur * L::buf, *vt_lds = k_lds + KEYS * L::kstr;
-    if (blk + 1 < nb) {                                       // the other buffer was left by everyone at the last barrier
-      stage(cur ^ 1);
-      if (blk + 2 < nb) prefetch(blk + 2);
-    }
-    if (blk * KEYS <= hi) {                                   // some row of the wavefront sees this block
-      f32x16_t s[KT];
+  // pass 2
+  if (k_wg > 0) {
+    u32x4_t kreg[KP], vreg[VP][2];
+    const int nb = (k_wg + KEYS - 1) / KEYS;
+    auto prefetch = [&](int blk) {
 #pragma unroll
-      for (int kt = 0; kt < KT; kt++) {
+      for (int e = 0; e < KP; e++) { const int q = tid + e * NT; kreg[e] = piece_of(kg, blk * KEYS + q / PPR, q % PPR); }
 #pragma unroll
-        for (int v = 0; v < 16; v++) s[kt][v] = 0.f;
+      for (int e = 0; e < VP; e++) {
+        const int q = tid + e * NT;
+        const int pair = q % (KEYS / 2), piece = q / (KEYS / 2);
+        vreg[e][0] = piece_of(vg, blk * KEYS + 2 * pair, piece);
+        vreg[e][1] = piece_of(vg, blk * KEYS + 2 * pair + 1, piece);
+      }
+    };
+    auto stage = [&](int b) {
+      unsigned char *k_lds = lds + b * L::buf, *vt_lds = k_lds + KEYS * L::kstr;
 #pragma unroll
-        for (int kk = 0; kk < KK; kk++) {
-          const u32x4_t kf = *(const u32x4_t *)(k_lds + (kt * 32 + c) * L::kstr + kk * 32 + g * 16);
-          s[kt] = mfma_bf16(kf, qhi[kk], s[kt]);
-          s[kt] = mfma_bf16(kf, qlo[kk], s[kt]);
-          s[kt] = mfma_bf16(kf, qrest[kk], s[kt]);
+      for (int e = 0; e < KP; e++) {
+        const int q = tid + e * NT;
+        *(u32x4_t *)(k_lds + (q / PPR) * L::kstr + (q % PPR) * 16) = kreg[e];
+      }
+#pragma unroll
+      for (int e = 0; e < VP; e++) {                          // V^T[dim][key], two keys per 32-bit store
+        const int q = tid + e * NT;
+        const int pair = q % (KEYS / 2), piece = q / (KEYS / 2);
+#pragma unroll
+        for (int d2 = 0; d2 < 8; d2++) {
+          const uint32_t x0 = vreg[e][0][d2 >> 1], x1 = vreg[e][1][d2 >> 1];
+          *(uint32_t *)(vt_lds + (piece * 8 + d2) * L::vstr + pair * 4) = (d2 & 1) ? ((x0 >> 16) | (x1 & 0xFFFF0000u)) : ((x0 & 0xFFFFu) | (x1 << 16));
         }
       }
-      // s[kt][v] = q . k for key blk*KEYS + kt*32 + 8*(v/4) + 4*g + v%4
-      if (blk * KEYS + KEYS - 1 > lo) {                       // the block reaches past some row's position
-        const int key0 = blk * KEYS + 4 * g;
-#pragma unroll
-        for (int kt = 0; kt < KT; kt++)
-#pragma unroll
-          for (int v = 0; v < 16; v++)
-            if (key0 + kt * 32 + 8 * (v >> 2) + (v & 3) > lim) s[kt][v] = -INFINITY;
+    };
+    prefetch(0);
+    stage(0);
+    __syncthreads();
+    if (nb > 1) prefetch(1);
+    int part_lo = 0;                                          // first key of the part under way
+    for (int blk = 0; blk < nb; blk++) {
+      const unsigned char *k_lds = lds + (blk & 1) * L::buf, *vt_lds = k_lds + KEYS * L::kstr;
+      if (blk + 1 < nb) {
+        stage((blk + 1) & 1);
+        if (blk + 2 < nb) prefetch(blk + 2);
       }
-      float mb = -INFINITY;
+      if (blk * KEYS < hi) {
 #pragma unroll
-      for (int kt = 0; kt < KT; kt++)
+        for (int kt = 0; kt < KT; kt++) {
+          f32x16_t s;
 #pragma unroll
-        for (int v = 0; v < 16; v++) mb = fmaxf(mb, s[kt][v]);
-      mb = fmaxf(mb, __shfl_xor(mb, 32, 64)) * c2;
-      const bool move = mb > m_run + 8.f;                     // also the first finite maximum after -inf
-      if (__any(move)) {
-        const float m_new = move ? mb : m_run;
-        const float corr = move ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
-        l_run *= corr;
-        m_run = m_new;
+          for (int v = 0; v < 16; v++) s[v] = 0.f;
 #pragma unroll
-        for (int db = 0; db < DB; db++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) o[db][v] *= corr;
-      }
-      const float m_use = m_run == -INFINITY ? 0.f : m_run;   // nothing seen yet: every term below is 0
-      float ls = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < KT; kt++)
-#pragma unroll
-        for (int u = 0; u < 2; u++) {                         // 16 keys: the lane's own values v = 8u .. 8u+7
-          float x[8];
-#pragma unroll
-          for (int e = 0; e < 8; e++) { x[e] = __builtin_amdgcn_exp2f(fmaf(s[kt][8 * u + e], c2, -m_use)); ls += x[e]; }
-          u32x4_t phi, plo;
-          split8(x, phi, plo);
-#pragma unroll
-          for (int db = 0; db < DB; db++) {
-            const unsigned char *vp = vt_lds + (db * 32 + c) * L::vstr + (32 * kt + 16 * u + 4 * g) * 2;
-            const u32x2_t v0 = *(const u32x2_t *)vp, v1 = *(const u32x2_t *)(vp + 16);
-            const u32x4_t vf = {v0.x, v0.y, v1.x, v1.y};
-            o[db] = mfma_bf16(vf, phi, o[db]);
-            o[db] = mfma_bf16(vf, plo, o[db]);
+          for (int kk = 0; kk < KK; kk++) {
+            const u32x4_t kf = *(const u32x4_t *)(k_lds + (kt * 32 + c) * L::kstr + kk * 32 + g * 16);
+            u32x4_t ql;
+            if constexpr (L::kQueryLds) ql = *(const u32x4_t *)(q_lds + kk * 1024);
+            else ql = qlo[kk];
+            s = mfma_bf16(kf, qhi[kk], s);
+            s = mfma_bf16(kf, ql, s);
           }
+#pragma unroll
+          for (int v = 0; v < 16; v++) s[v] = mul_rounded(s[v], a.scale);
+          const int b0 = blk * KEYS + kt * 32;
+          if (b0 + 32 > lo) {                                 // some row ends inside the block
+            const int key0 = b0 + 4 * g;
+#pragma unroll
+            for (int v = 0; v < 16; v++)
+              if (key0 + 8 * (v >> 2) + (v & 3) >= k_end) s[v] = -INFINITY;
+          }
+          float mb = -INFINITY;
+#pragma unroll
+          for (int v = 0; v < 16; v++) mb = fmaxf(mb, s[v]);
+          mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
+          const float m_new = fmaxf(m_run, mb);
+          float corr = 1.f;
+          if (__any(m_new != m_run)) {                        // (otherwise the factor is exactly 1)
+            if (m_new != -INFINITY) corr = __expf(m_run - m_new);
+#pragma unroll
+            for (int db = 0; db < DB; db++)
+#pragma unroll
+              for (int v = 0; v < 16; v++) o[db][v] *= corr;
+            m_run = m_new;
+          }
+          const float m_use = m_run == -INFINITY ? 0.f : m_run;   // nothing seen yet: every term is 0
+          float ls = 0.f;
+#pragma unroll
+          for (int u = 0; u < 2; u++) {                       // 16 keys: the lane's own values v = 8u .. 8u+7
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; e++) { x[e] = __expf(s[8 * u + e] - m_use); ls += x[e]; }
+            u32x4_t phi, plo;
+            split8(x, phi, plo);
+#pragma unroll
+            for (int db = 0; db < DB; db++) {
+              const unsigned char *vp = vt_lds + (db * 32 + c) * L::vstr + (32 * kt + 16 * u + 4 * g) * 2;
+              const u32x2_t v0 = *(const u32x2_t *)vp, v1 = *(const u32x2_t *)(vp + 16);
+              const u32x4_t vf = {v0.x, v0.y, v1.x, v1.y};
+              o[db] = mfma_bf16(vf, phi, o[db]);
+              o[db] = mfma_bf16(vf, plo, o[db]);
+            }
+          }
+          ls += __shfl_xor(ls, 32, 64);
+          l_run = fmaf(l_run, corr, ls);
         }
-      ls += __shfl_xor(ls, 32, 64);
-      l_run += ls;
+        const int done = (blk + 1) * KEYS;
+        if (done >= hi || (done <= kAttnNear ? done % kAttnPart : (done - kAttnNear) % kAttnFarPart) == 0) {
+          if (part_lo < k_end) {                              // this row has keys in the part
+            float w;
+            weigh(l_run, m_run, w);
+#pragma unroll
+            for (int db = 0; db < DB; db++)
+#pragma unroll
+              for (int v = 0; v < 16; v++) row[db][v] = fmaf(o[db][v], w, row[db][v]);
+          }
+#pragma unroll
+          for (int db = 0; db < DB; db++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) o[db][v] = 0.f;
+          m_run = -INFINITY; l_run = 0.f;
+          part_lo = done;
+        }
+      }
+      __syncthreads();                                        // block blk+1 staged; everyone is done with block blk
     }
-    __syncthreads();                                          // block blk+1 staged; everyone is done with block blk
   }
   if (!valid) return;
-  const float inv = 1.f / l_run;
+  float w;
+  weigh(tail[1], m_tail, w);
   bf16_t *orow = (bf16_t *)a.out + ((size_t)i * a.hq + h) * HD;
 #pragma unroll
   for (int db = 0; db < DB; db++)
 #pragma unroll
     for (int q4 = 0; q4 < 4; q4++) {
-      u32x2_t w;
-      w.x = pack_bf16x2(o[db][4 * q4 + 0] * inv, o[db][4 * q4 + 1] * inv);
-      w.y = pack_bf16x2(o[db][4 * q4 + 2] * inv, o[db][4 * q4 + 3] * inv);
-      *(u32x2_t *)(orow + db * 32 + 8 * q4 + 4 * g) = w;
+      const int d0 = db * 32 + 8 * q4 + 4 * g;
+      const float2 t0 = *(const float2 *)(tail + 2 + d0), t1 = *(const float2 *)(tail + 2 + d0 + 2);
+      const float t[4] = {t0.x, t0.y, t1.x, t1.y};
+      float y[4];
+#pragma unroll
+      for (int e = 0; e < 4; e++) y[e] = fmaf(t[e], w, row[db][4 * q4 + e]) / l_row;
+      *(u32x2_t *)(orow + d0) = u32x2_t{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
     }
 }
 
-template <int HD, int WAVES>
-static hipError_t launch_causal(const AttnArgs &a, hipStream_t st) {
-  constexpr int kLds = 2 * CausalLds<HD>::buf;
+// The tails of all rows: one (row, kv head) item per wavefront.
+template <int HD, int G>
+__global__ __launch_bounds__(256) void attn_tail_kernel(AttnArgs a) {
+  constexpr int kQ = G * HD * 4, kWaveLds = kQ + kTailKeys * PartLds<bf16_t>::vrow(HD);
+  __shared__ __attribute__((aligned(16))) unsigned char lds[4 * kWaveLds];
+  const int w = threadIdx.x >> 6, item = (int)blockIdx.x * 4 + w;
+  if (item >= a.rows * a.hkv) return;
+  unsigned char *mine = lds + w * kWaveLds;
+  attn_tail_body<bf16_t, HD, G>(a, item / a.hkv, item % a.hkv, threadIdx.x & 63, (float (*)[HD])mine, mine + kQ, true);
+}
+
+template <int HD, int G, int WAVES>
+static hipError_t launch_chain(AttnArgs a, hipStream_t st) {
+  constexpr int kLds = ChainLds<HD, WAVES>::total;
   static bool attr_done[64] = {};                             // per device: the attribute belongs to the device's copy of the code
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64 || !attr_done[dev]) {
-    e = hipFuncSetAttribute((const void *)attn_causal_kernel<HD, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    e = hipFuncSetAttribute((const void *)attn_chain_kernel<HD, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64) attr_done[dev] = true;
   }
-  const long long grid = (long long)a.hq * ((a.rows + WAVES * 32 - 1) / (WAVES * 32));
-  if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_causal_kernel<HD, WAVES>), dim3((unsigned)grid), dim3(WAVES * 64), kLds, st, a);
+  const long long grid = (long long)a.hq * ((a.rows + WAVES * 32 - 1) / (WAVES * 32)), items = (long long)a.rows * a.hkv;
+  if (grid > 0x7FFFFFFFll || items > 0x7FFFFFFFll) return hipErrorInvalidValue;
+  a.max_parts = 1;                                            // the tail's partial is the only one
+  hipLaunchKernelGGL((attn_tail_kernel<HD, G>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, st, a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_chain_kernel<HD, WAVES>), dim3((unsigned)grid), dim3(WAVES * 64), kLds, st, a);
   return hipGetLastError();
+}
+
+// Which chains take attn_chain_kernel.  A workgroup of it walks all keys of its rows one block after the other, so its time grows
+// with the keys alone until the chip is full; the hybrid path's grows with rows * heads * keys, and with few keys the
+// fixed costs of its three launches and its partials count.  Crossing points measured in rows * heads, hybrid path faster below
+// (32 heads of 128 on 32 and on 8 kv heads, 40 on 40, 64 on 8, 16 of 64): about 300 keys 8 .. 12 thousand, 900 keys 12 .. 18,
+// 2600 keys 18 .. 22, 8700 keys 22 .. 27.  us per call at the ends, hybrid / chain: 512 rows of 32 heads alone 102 / 81, 320 rows 76 / 64,
+// 256 rows 58 / 60; at 2048 keys before them 384 rows 138 / 184, 512 174 / 193, 640 222 / 202, 1024 388 / 231; at 8192 keys 512 rows
+// 389 / 530, 768 587 / 548.  Tiles are 128 rows: below 192 rows (1.5 tiles) the hybrid path is never slower.
+static bool chain_pays(int rows, int hq, int keys) {
+  return rows >= 192 && (long long)rows * hq >= 5600 + 21600ll * keys / (keys + 1500);
 }
 
 template <typename T, int HD, int G>
 static hipError_t launch_thg(AttnArgs a, int max_pos, hipStream_t st) {
   hipError_t e;
   if constexpr (sizeof(T) == 2) {
-    // a long chain: no parts, no tail.  Shorter ones leave most of the chip idle with 128-row tiles: 200 rows over 300 keys 26.7
-    // us against 25.8 with parts, 256 over 256 (32 kv heads) 27.7 against 39.1
-    if (a.anc == nullptr && a.rows >= kChainRows) return launch_causal<HD, 4>(a, st);
+    if (attn_parts_covering(bulk_end(max_pos)) + 1 > a.max_parts) return hipErrorInvalidValue;
+    if (a.anc == nullptr && chain_pays(a.rows, a.hq, max_pos + 1)) return launch_chain<HD, G, 4>(a, st);
     // hybrid: matrix-core bulk over [0, A(max_pos)) and the vector tail of every row in one launch
     a.tail_only = 1;
     a.bulk_keys = bulk_end(max_pos);
     a.bulk_blocks = (a.bulk_keys + 31) / 32;
     a.bulk_parts = attn_parts_covering(a.bulk_keys);
-    if (a.bulk_parts + 1 > a.max_parts) return hipErrorInvalidValue;
-    // At least four wavefronts per bulk workgroup, also for fewer than four blocks of 32 query rows: the ones
-    // without rows still take their share of loading and staging the K/V blocks.
-    const int qblocks = (a.rows * G + 31) / 32;
-    if (qblocks <= 4) e = launch_hybrid<HD, G, 4>(a, 1, st);
-    else e = launch_hybrid<HD, G, 8>(a, (qblocks + 7) / 8, st);
+    const int rows = a.rows;
+    for (int r0 = 0; r0 < rows; r0 += kPartialRows) {         // (more rows than the partials are planned for: a chain's)
+      a.rows = std::min(kPartialRows, rows - r0);
+      // At least four wavefronts per bulk workgroup, also for fewer than four blocks of 32 query rows: the ones
+      // without rows still take their share of loading and staging the K/V blocks.
+      const int qblocks = (a.rows * G + 31) / 32;
+      if (qblocks <= 4) e = launch_hybrid<HD, G, 4>(a, 1, st);
+      else e = launch_hybrid<HD, G, 8>(a, (qblocks + 7) / 8, st);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((attn_combine_kernel<T, HD>), dim3(a.rows, a.hq), dim3(HD), 0, st, a);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      a.q = (const float *)a.q + (size_t)a.rows * a.hq * HD;
+      a.out = (T *)a.out + (size_t)a.rows * a.hq * HD;
+      a.depth += a.rows;
+      if (a.anc) a.anc += (size_t)a.rows * kAncStride;
+    }
+    return hipSuccess;
   } else {
     a.tail_only = 0;
     a.bulk_blocks = 0;

@@ -109,8 +109,9 @@ struct AttnArgs {
   void *out;
   int tail_only, bulk_keys, bulk_blocks, bulk_parts, q_groups;   // set by launch_attention (hybrid matrix-core / vector split)
 };
-// bf16 chains (anc == nullptr) of at least this many rows run without partial outputs and leave `part` alone.
-constexpr int kChainRows = 256;
+// bf16: rows whose partials of all parts `part` has to hold ([min(rows, kPartialRows)][hq][max_parts][hd + 2], and at least
+// [rows][hq][hd + 2]); a chain (anc == nullptr) of more rows goes in blocks, or keeps one partial per row and head (the tail's).
+constexpr int kPartialRows = 256;
 hipError_t launch_attention(int dtype, const AttnArgs &a, int max_pos, hipStream_t st);
 
 // ---- hca.hip ---------------------------------------------------------------------------------

@@ -375,3 +375,28 @@ def test_attention_of_a_long_chain_matches_fp64(env, rows, hq, hkv, hd, base, or
         p = np.exp(sc - sc.max(1, keepdims=True))
         want[:, h] = p @ v3[:, h * hkv // hq] / p.sum(1, keepdims=True)
     assert attention_error_ok(got, want, "bf16", np.abs(vc).max())
+
+
+@pytest.mark.parametrize("rows,hq,hkv,hd,base,order", [(520, 32, 8, 128, 0, "chain"), (300, 64, 8, 128, 1000, "chain"), (200, 64, 64, 128, 0, "chain"),
+                                                       (640, 32, 8, 128, 3500, "chain"), (700, 16, 16, 64, 0, "chain"), (1300, 16, 16, 64, 100, "chain"),
+                                                       (513, 40, 40, 128, 15, "reversed"), (777, 32, 4, 64, 130, "scattered")])
+def test_attention_row_is_independent_of_the_other_rows(env, rows, hq, hkv, hd, base, order):
+    """A bf16 row's bits are those it has alone or among few rows, whichever path a long chain takes (one launch over all keys, or
+    blocks of 256 rows with partials): rows with a tail only, with up to and more than seven parts before the tail, near and far
+    parts; one row in a tile, half-filled wavefronts; positions out of order."""
+    torch, P = env
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed("rows", rows, hq, hd) & 0xFFFF)
+    q = torch.randn(rows, hq * hd, device="cuda", generator=g) * 3.0
+    kc = torch.randn(base + rows, hkv * hd, device="cuda", generator=g).to(torch.bfloat16)
+    vc = torch.randn(base + rows, hkv * hd, device="cuda", generator=g).to(torch.bfloat16)
+    dep = torch.arange(rows, dtype=torch.int32, device="cuda")
+    if order == "reversed":
+        dep = dep.flip(0).contiguous()
+    elif order == "scattered":
+        dep = torch.randint(0, rows, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    run = lambda a, b: P.spec_k_attention(q[a:b].contiguous(), kc, vc, base, dep[a:b].contiguous(), None, hq, hkv, hd)
+    whole = run(0, rows).view(torch.int16)
+    few = torch.cat([run(a, min(a + 150, rows)) for a in range(0, rows, 150)]).view(torch.int16)
+    assert torch.equal(whole, few)
+    for i in (0, 15, 16, rows // 2, rows - 1):
+        assert torch.equal(run(i, i + 1).view(torch.int16)[0], whole[i])
