@@ -20,11 +20,12 @@ namespace {
 
 enum State { CREATED = 0, READY = 1, DRAFTED = 2, VERIFIED = 3 };
 
-// Prompt rows per target forward during prefill.  bf16: as many as the workspace is planned for (the weights are read once per
-// forward and the launches of a projection fill the chip better: 8B widths, 16 layers, 4096-token prompt: GEMMs 33 -> 27.5 ms, the whole request 81 -> 61 ms with the attention that this allows); a longer prompt is cut into
-// equal chunks.  fp32 (small models): the attention writes partial outputs per row, which bounds the chunk.
-constexpr int kPrefillChunk = 4096, kPrefillChunkFp32 = 512;
-constexpr int kPartRows = 4096;        // bf16: splits * rows of partial sums that a projection over many rows may use
+// Prompt rows per target forward during prefill; a longer prompt is cut into equal chunks.  More rows fill the launches better
+// and read the weights less often, and each costs workspace (8B widths, 16 layers, 4096-token prompt, whole request: 1024 rows 77 ms,
+// 2048 70, 4096 70 .. 73; 7B at max_seq 4200, without caches and logits: 292, 394 and 598 MiB).  The results do not depend on it.
+// fp32 (small models): the attention writes partial outputs per row, which bounds the chunk.
+constexpr int kPrefillChunk = 2048, kPrefillChunkFp32 = 512;
+constexpr int kPartRows = 512;         // rows of a forward that the partial sums are planned for: more go in blocks (project)
 // A captured forward sizes its attention launches for a bound on the key positions, not for the positions of
 // the cycle it was captured in.  The bound is the context rounded up to the next multiple of kGraphBucket, and
 // the graph is captured again when the context outgrows it: sizing for max_seq instead costs 2-9 % of the verify
@@ -33,7 +34,7 @@ constexpr int kGraphBucket = 256;
 constexpr int kDraftNodeStream = 1 << 16;  // random stream of node i's child sampling: (cycle, kDraftNodeStream + i)
 constexpr int kMaxGemmEvents = 2048;  // event pairs kept per cycle at profile level 2
 
-struct GemmPlan { int n_split; };
+struct GemmPlan { int n_split; bool fold = false; };   // fold: one set of partial sums (the splits added up inside the launch)
 
 struct RowTables {                    // device index tables describing the rows of one forward
   const int *token, *pos, *slot, *depth, *anc;
@@ -142,11 +143,11 @@ int fail(spec_ctx *c, int code, const char *fmt, ...) {
 
 size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
-// The split count depends on the matrix shape only (never on the number of rows), so a token
-// sees the same summation order in plain decoding and inside a tree.
 // rows of the packed gate/up matrix: per 16 columns, 16 gate rows and 16 up rows
 int gate_up_rows(int f) { return 32 * ((f + 15) / 16); }
 
+// The split count depends on the matrix shape only (never on the number of rows), so a token
+// sees the same summation order in plain decoding, inside a tree and in a prompt of any length.
 GemmPlan plan_gemm(int total_rows, int in, int dtype) {
   const int blocks = (total_rows + 31) / 32;
   const int kslab = gemm_k_per_slab(dtype);
@@ -174,13 +175,6 @@ GemmPlan plan_gemm(int total_rows, int in, int dtype) {
   return p;
 }
 
-// The same for a forward over m rows.  More than 512 bf16 rows need fewer splits to fill the chip and pay more for each (a
-// prompt's rows are only ever computed there); up to 512 the counts above serve the tiles as well.
-GemmPlan plan_rows(int total_rows, int in, int dtype, int m) {
-  GemmPlan p = plan_gemm(total_rows, in, dtype);
-  if (dtype == SPEC_DTYPE_BF16 && m > 512) p.n_split = gemm_rows_split(m, total_rows, in, std::min(8, std::max(1, kPartRows / m)));
-  return p;
-}
 int prefill_chunk(const spec_config &c) { return c.dtype == SPEC_DTYPE_BF16 ? kPrefillChunk : kPrefillChunkFp32; }
 
 struct Layout {                       // workspace carve-out; all offsets 256-byte aligned
@@ -215,7 +209,6 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   Layout L;
   const size_t esz = c.dtype == SPEC_DTYPE_BF16 ? 2 : 4;
   const int d = c.d_model, dq = c.n_q_heads * c.head_dim, dkv = c.n_kv_heads * c.head_dim, f = c.d_ffn, v = c.vocab;
-  const bool bf16 = c.dtype == SPEC_DTYPE_BF16;
   const int m_small = std::max({c.tree_total, kMaxDepth + 1, c.tree_topk});    // rows of any forward but a prompt's
   const int m_max = std::max(m_small, std::min(prefill_chunk(c), c.max_seq));
   const int k = std::max(1, c.tree_topk), D = std::max(1, c.tree_depth);
@@ -226,11 +219,7 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
     struct { int rows, in; } g[5] = {{dq + 2 * dkv, d}, {d, dq}, {gate_up_rows(f), d}, {d, f}, {d, 2 * d}};
     for (auto &e : g) {
       GemmPlan p = plan_gemm(e.rows, e.in, c.dtype);
-      // (gate/up over many rows applies SwiGLU itself)
-      size_t rows = (size_t)p.n_split * (bf16 ? std::min(m_max, 128) : m_max);
-      if (bf16 && m_max > 128) rows = std::max(rows, (size_t)p.n_split * std::min(m_max, 512));
-      if (bf16 && m_max > 512 && &e != &g[2]) rows = std::max(rows, (size_t)kPartRows);
-      part_floats = std::max(part_floats, rows * e.rows);
+      part_floats = std::max(part_floats, (size_t)p.n_split * std::min(m_max, kPartRows) * e.rows);
       part_floats = std::max(part_floats, std::min((size_t)v, (size_t)p.n_split * 512 * e.rows));   // the ratio rule's scratch, small models
     }
   }
@@ -247,8 +236,8 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   TAKE(gfeat, void *, (size_t)m_max * d * esz)
   TAKE(pend_feat, void *, (size_t)(kMaxDepth + 1) * d * esz)
   TAKE(part, float *, part_floats * 4)
-  // rows that write a partial per part (fp32: all; bf16: a block of a chain's), or one per row (a long chain's tails)
-  const size_t partials = bf16 ? std::max((size_t)std::min(m_max, kPartialRows) * max_parts, (size_t)m_max) : (size_t)m_max * max_parts;
+  // rows that write a partial per part (fp32: all; bf16: up to a long chain's), or one per row
+  const size_t partials = c.dtype == SPEC_DTYPE_BF16 ? std::max((size_t)std::min(m_max, kPartialRows) * max_parts, (size_t)m_max) : (size_t)m_max * max_parts;
   TAKE(attn_part, float *, partials * c.n_q_heads * (c.head_dim + 2) * 4)
   TAKE(logits, float *, (size_t)std::max(c.tree_total, 1) * v * 4)
   TAKE(dlogits, float *, (size_t)kMaxTopK * v * 4)
@@ -352,8 +341,8 @@ int run_gemm(spec_ctx *c, const void *x, int ldx, int m, int in, const Seg *segs
   }
   a.total_blocks = blocks;
   a.part = out; a.ldp = ldp; a.m_pad = m_pad;
-  a.n_split = p.n_split;
-  if (out == c->part && !swiglu_act && (size_t)p.n_split * m_pad * ldp > c->part_floats)
+  a.n_split = p.n_split; a.fold = p.fold;
+  if (out == c->part && !swiglu_act && (size_t)(p.fold ? 1 : p.n_split) * m_pad * ldp > c->part_floats)
     return fail(c, SPEC_ECAP, "%d splits of %d x %d partial sums exceed the workspace", p.n_split, m_pad, ldp);
   const bool ev = c->prof_level >= 2 && c->gemm_bucket && c->n_gemm_ev < kMaxGemmEvents;
   if (ev) (void)hipEventRecord(c->ev_gemm[2 * c->n_gemm_ev], c->stream);
@@ -366,6 +355,33 @@ int run_gemm(spec_ctx *c, const void *x, int ldx, int m, int in, const Seg *segs
   return SPEC_OK;
 }
 
+// Rows of a projection whose partial sums fit the workspace at a time, whole token tiles of the many-row GEMM.
+int row_block(const spec_ctx *c, int m, int ldp, int sets) {
+  const size_t fit = c->part_floats / ((size_t)sets * ldp);
+  return fit >= (size_t)m ? m : std::max(1, (int)(fit >= 256 ? fit / 256 * 256 : fit));
+}
+
+// Projection of m rows: partial sums of a block of rows, then reduce(first row, rows, splits, partial sums' row count).
+template <typename Reduce>
+int project(spec_ctx *c, const void *x, int m, int in, const Seg *segs, int nseg, int rows, Reduce reduce) {
+  GemmPlan p = plan_gemm(rows, in, c->cfg.dtype);
+  int step = row_block(c, m, rows, p.n_split);
+  if (c->cfg.dtype == SPEC_DTYPE_BF16 && p.n_split > 1 && m > 128) {
+    uintptr_t low = (uintptr_t)x;
+    for (int s = 0; s < nseg; s++) low |= (uintptr_t)segs[s].w;
+    p.fold = (low & 15) == 0 && gemm_fold_pays(m, rows, in, p.n_split, step);   // (a caller's weights may lie at any address)
+    if (p.fold) step = row_block(c, m, rows, 1);
+  }
+  const int sets = p.fold ? 1 : p.n_split;
+  for (int r0 = 0; r0 < m; r0 += step) {
+    const int n = std::min(step, m - r0);
+    int rc = run_gemm(c, (const char *)x + (size_t)r0 * in * c->esz, in, n, in, segs, nseg, c->part, rows, n, p);
+    if (rc) return rc;
+    HIPCHK(c, reduce(r0, n, sets));
+  }
+  return SPEC_OK;
+}
+
 // One decoder layer over m rows.  In: c->h (fp32 residual stream) and c->x (rows normed by the
 // layer's attn_norm).  Out: c->h updated; x_out = rmsnorm(h) * next_norm (or h itself, cast).
 int layer_forward(spec_ctx *c, const spec_layer_weights &lw, char *kcache, char *vcache, int m, int base,
@@ -373,13 +389,19 @@ int layer_forward(spec_ctx *c, const spec_layer_weights &lw, char *kcache, char 
   const spec_config &g = c->cfg;
   const int d = g.d_model, dq = g.n_q_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim, f = g.d_ffn;
   const int dt = g.dtype;
+  auto at = [](const void *p, size_t r, size_t row_bytes) { return (void *)((char *)p + r * row_bytes); };
+  auto add_norm = [&](const void *norm, void *out) {          // h += the sums; out = the normed rows
+    return [&, norm, out](int r0, int n, int split) {
+      return launch_reduce_add_norm(dt, c->part, split, n, d, n, d, 1, norm, g.rms_eps, c->h + (size_t)r0 * d, at(out, r0, d * c->esz), c->stream);
+    };
+  };
   {
     const Seg segs[3] = {{lw.wq, dq}, {lw.wk, dkv}, {lw.wv, dkv}};
-    const GemmPlan p = plan_rows(dq + 2 * dkv, d, dt, m);
-    int rc = run_gemm(c, c->x, d, m, d, segs, 3, c->part, dq + 2 * dkv, m, p);
+    int rc = project(c, c->x, m, d, segs, 3, dq + 2 * dkv, [&](int r0, int n, int split) {
+      return launch_reduce_rope_kv(dt, c->part, split, n, dq + 2 * dkv, n, g.n_q_heads, g.n_kv_heads, g.head_dim, c->rope + (size_t)r0 * (g.head_dim / 2),
+                                   rt.slot + r0, at(c->qbuf, r0, (size_t)dq * 4), kcache, vcache, c->stream);
+    });
     if (rc) return rc;
-    HIPCHK(c, launch_reduce_rope_kv(dt, c->part, p.n_split, m, dq + 2 * dkv, m, g.n_q_heads, g.n_kv_heads, g.head_dim,
-                                    c->rope, rt.slot, c->qbuf, kcache, vcache, c->stream));
   }
   {
     if (rt.anc != nullptr && m > kMaxNodes) return fail(c, SPEC_EINVAL, "attention: %d rows of a tree", m);   // partial outputs are planned for fewer
@@ -393,36 +415,30 @@ int layer_forward(spec_ctx *c, const spec_layer_weights &lw, char *kcache, char 
   }
   {
     const Seg segs[1] = {{lw.wo, d}};
-    const GemmPlan p = plan_rows(d, dq, dt, m);
-    int rc = run_gemm(c, c->attn_out, dq, m, dq, segs, 1, c->part, d, m, p);
+    int rc = project(c, c->attn_out, m, dq, segs, 1, d, add_norm(lw.ffn_norm, c->x));
     if (rc) return rc;
-    HIPCHK(c, launch_reduce_add_norm(dt, c->part, p.n_split, m, d, m, d, 1, lw.ffn_norm, g.rms_eps, c->h, c->x, c->stream));
   }
   {
     // gate and up projections, one packed matrix.  Without a K split a wavefront owns both sums of a column and
     // applies SwiGLU itself (no partial sums, no extra pass); with a K split the row kernel does it.
     const int gu = gate_up_rows(f);
-    GemmPlan p = plan_gemm(gu, d, dt);
-    if (dt == SPEC_DTYPE_BF16 && m > 128) p.n_split = 1;
+    const GemmPlan p = plan_gemm(gu, d, dt);
+    int rc;
     if (p.n_split == 1) {
       const Seg segs[1] = {{lw.w_gate_up, f}};
-      int rc = run_gemm(c, c->x, d, m, d, segs, 1, c->part, gu, m, p, c->act);
-      if (rc) return rc;
+      rc = run_gemm(c, c->x, d, m, d, segs, 1, c->part, gu, m, p, c->act);
     } else {
       const Seg segs[1] = {{lw.w_gate_up, gu}};
-      int rc = run_gemm(c, c->x, d, m, d, segs, 1, c->part, gu, m, p);
-      if (rc) return rc;
-      HIPCHK(c, launch_reduce_swiglu(dt, c->part, p.n_split, m, gu, m, f, c->act, c->stream));
+      rc = project(c, c->x, m, d, segs, 1, gu, [&](int r0, int n, int split) {
+        return launch_reduce_swiglu(dt, c->part, split, n, gu, n, f, at(c->act, r0, (size_t)f * c->esz), c->stream);
+      });
     }
+    if (rc) return rc;
   }
   {
     const Seg segs[1] = {{lw.w_down, d}};
-    const GemmPlan p = plan_rows(d, f, dt, m);
-    int rc = run_gemm(c, c->act, f, m, f, segs, 1, c->part, d, m, p);
-    if (rc) return rc;
-    HIPCHK(c, launch_reduce_add_norm(dt, c->part, p.n_split, m, d, m, d, 1, next_norm, g.rms_eps, c->h, x_out, c->stream));
+    return project(c, c->act, m, f, segs, 1, d, add_norm(next_norm, x_out));
   }
-  return SPEC_OK;
 }
 
 // LM head over `rows` feature rows starting at `x` -> logits [rows, vocab] fp32.
@@ -461,11 +477,11 @@ int draft_forward(spec_ctx *c, int m, int base, const void *feat, const int *src
   HIPCHK(c, launch_concat_feat_embed(g.dtype, feat, src_row, c->w.embed, rt.token, m, d, c->xcat, c->stream, rt.pos, g.head_dim,
                                      g.rope_theta, c->rope));
   const Seg segs[1] = {{c->w.draft_fc, d}};
-  const GemmPlan p = plan_rows(d, 2 * d, g.dtype, m);
-  int rc = run_gemm(c, c->xcat, 2 * d, m, 2 * d, segs, 1, c->part, d, m, p);
+  int rc = project(c, c->xcat, m, 2 * d, segs, 1, d, [&](int r0, int n, int split) {
+    return launch_reduce_add_norm(g.dtype, c->part, split, n, d, n, d, 0, c->w.draft_layer.attn_norm, g.rms_eps, c->h + (size_t)r0 * d,
+                                  (char *)c->x + (size_t)r0 * d * c->esz, c->stream);
+  });
   if (rc) return rc;
-  HIPCHK(c, launch_reduce_add_norm(g.dtype, c->part, p.n_split, m, d, m, d, 0, c->w.draft_layer.attn_norm, g.rms_eps, c->h,
-                                   c->x, c->stream));
   char *kc = c->kv_d;
   char *vc = kc + c->d_kv_stride * c->esz;
   return layer_forward(c, c->w.draft_layer, kc, vc, m, base, rt, max_pos, nullptr, c->gfeat, base_ptr);

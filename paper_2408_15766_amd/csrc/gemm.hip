@@ -311,7 +311,10 @@ __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
 }
 
-template <int TW, int TB, int WB>
+// FOLD: the workgroup walks all K ranges of its tile one after the other (the copies run on across the borders) and adds up
+// the ranges' sums in registers, ((range 0 + range 1) + range 2) + .., the order in which the row kernels add partial sums: the
+// bits of n_split sets of partial sums with one set in memory.  Only the smallest tile leaves registers for a second set of sums.
+template <int TW, int TB, int WB, bool FOLD>
 __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
   using L = MmTile<TW, TB, WB>;
   constexpr int XI = L::kXLoads, WI = L::kWLoads;
@@ -322,8 +325,8 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
   const int per = 8 * a.m_tiles;
   const int q = ((int)blockIdx.x / per) * 8 + ((int)blockIdx.x % 8);
   const int mt = ((int)blockIdx.x % per) / 8;
-  if (q >= a.grid_x * a.n_split) return;
-  const int bx = q % a.grid_x, by = q / a.grid_x;
+  if (q >= a.grid_x * (FOLD ? 1 : a.n_split)) return;
+  const int bx = q % a.grid_x, by = FOLD ? 0 : q / a.grid_x;
   const int set_tiles = (a.m + L::kTok - 1) / L::kTok;        // tiles of the second set of rows follow the first set's
   const bool second = mt >= set_tiles;
   const int m0 = (second ? mt - set_tiles : mt) * L::kTok, m_loc = min(a.m - m0, L::kTok);
@@ -332,8 +335,8 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
   const int n_it_total = (a.in + 127) / 128;
   const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
-  const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
-  const int it_end = min(n_it_total, (int)((long long)(by + 1) * n_slabs_total / a.n_split) * kSlabIters);
+  auto range_begin = [&](int r) { return min(n_it_total, (int)((long long)r * n_slabs_total / a.n_split) * kSlabIters); };
+  const int it_begin = range_begin(by), it_end = FOLD ? n_it_total : range_begin(by + 1);
   const int n_stage = 2 * (it_end - it_begin);
 
   auto block_seg = [&](int blk, int &b0) { const int s = blk < e0 ? 0 : (blk < e1 ? 1 : 2); b0 = s == 0 ? 0 : (s == 1 ? e0 : e1); return s; };
@@ -422,6 +425,33 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   };
 
+  f32x16_t sum[FOLD ? WB : 1][FOLD ? TB : 1];                 // FOLD: the finished ranges
+  int range = 0, border = FOLD ? 2 * range_begin(1) : -1;     // stages before the next range begins
+  auto fold = [&]() __attribute__((always_inline)) {
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int wb = 0; wb < WB; wb++)
+#pragma unroll
+        for (int t = 0; t < TB; t++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) sum[wb][t][v] = range == 0 ? acc[wb][t][v] : sum[wb][t][v] + acc[wb][t][v];
+    }
+  };
+  auto turn = [&](int done) __attribute__((always_inline)) {   // (a range is whole slabs, a multiple of four stages; the last one ends with the loop)
+    if constexpr (FOLD) {
+      if (done != border || done >= n_stage) return;
+      fold();
+#pragma unroll
+      for (int wb = 0; wb < WB; wb++)
+#pragma unroll
+        for (int t = 0; t < TB; t++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) acc[wb][t][v] = 0.f;
+      range++;
+      border = 2 * range_begin(range + 1);
+    }
+  };
+
   load_w(ws0, 0, 0, WI);
   load_x(xs0, 0);
   load_w(ws1, 1, 0, WI);
@@ -433,20 +463,25 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
   for (; s + 6 <= n_stage; s += 6) {
     stage(xs0, ws0, xs1, ws1, ws2, s);
     stage(xs1, ws1, xs0, ws2, ws0, s + 1);
+    turn(s + 2);
     stage(xs0, ws2, xs1, ws0, ws1, s + 2);
     stage(xs1, ws0, xs0, ws1, ws2, s + 3);
+    turn(s + 4);
     stage(xs0, ws1, xs1, ws2, ws0, s + 4);
     stage(xs1, ws2, xs0, ws0, ws1, s + 5);
+    turn(s + 6);
   }
   if (s < n_stage) {                                          // two or four stages are left: a K range is whole 128-k tiles
     stage(xs0, ws0, xs1, ws1, ws2, s);
     stage(xs1, ws1, xs0, ws2, ws0, s + 1);
     if (s + 2 < n_stage) {
+      turn(s + 2);
       stage(xs0, ws2, xs1, ws0, ws1, s + 2);
       stage(xs1, ws0, xs0, ws1, ws2, s + 3);
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);                         // no copy into the LDS outlives the workgroup
+  fold();
 
 #pragma unroll
   for (int wb = 0; wb < WB; wb++) {
@@ -476,7 +511,7 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
 #pragma unroll
       for (int v = 0; v < 16; v++) {
         const int i = t * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-        if (th * TB * 32 + i < m_loc) out[o0 + (uint32_t)i * (uint32_t)a.ldp] = acc[wb][t][v];
+        if (th * TB * 32 + i < m_loc) out[o0 + (uint32_t)i * (uint32_t)a.ldp] = FOLD ? sum[FOLD ? wb : 0][FOLD ? t : 0][v] : acc[wb][t][v];
       }
   }
 }
@@ -734,13 +769,13 @@ hipError_t gemm_init() {
   return e;
 }
 
-template <int TW, int TB, int WB>
+template <int TW, int TB, int WB, bool FOLD = false>
 static hipError_t launch_mm_tile(GemmArgs a, hipStream_t st) {
   using L = MmTile<TW, TB, WB>;
   a.m_tiles = (a.m + L::kTok - 1) / L::kTok * (a.x2 ? 2 : 1);
   a.grid_x = (a.total_blocks + L::kBlocks - 1) / L::kBlocks;
-  const dim3 grid((a.grid_x * a.n_split + 7) / 8 * 8 * a.m_tiles, 1);
-  hipLaunchKernelGGL((gemm_mm_kernel<TW, TB, WB>), grid, dim3(kMmThreads), 0, st, a);
+  const dim3 grid((a.grid_x * (FOLD ? 1 : a.n_split) + 7) / 8 * 8 * a.m_tiles, 1);
+  hipLaunchKernelGGL((gemm_mm_kernel<TW, TB, WB, FOLD>), grid, dim3(kMmThreads), 0, st, a);
   return hipGetLastError();
 }
 // A compute unit holds one workgroup, so a launch lasts as many rounds as its workgroups fill the 256 compute units.  A round
@@ -754,38 +789,44 @@ static float mm_us(int tile, int m, int sets, int blocks, int in, int n_split) {
   const long long wgs = (long long)((m + tok - 1) / tok) * sets * ((blocks + wb - 1) / wb) * n_split;
   return (float)((wgs + 255) / 256) * (at4096 * (float)in / (4096.f * (float)n_split) + 6.f);
 }
-static int mm_tile(int m, int sets, int blocks, int in, int n_split, float *us) {
+static int mm_tile(int m, int sets, int blocks, int in, int n_split) {
   int best = 0;
   float t = mm_us(0, m, sets, blocks, in, n_split);
   for (int tile = 1; tile < 3; tile++) {
     const float u = mm_us(tile, m, sets, blocks, in, n_split);
     if (u < 0.97f * t) { t = u; best = tile; }                // (launches of several rounds do not end exactly round by round)
   }
-  if (us) *us = t;
   return best;
 }
 static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
-  switch (mm_tile(a.m, a.x2 ? 2 : 1, a.total_blocks, a.in, a.n_split, nullptr)) {
+  if (a.fold) return launch_mm_tile<2, 2, 2, true>(a, st);
+  switch (mm_tile(a.m, a.x2 ? 2 : 1, a.total_blocks, a.in, a.n_split)) {
     case 0: return launch_mm_tile<2, 4, 2>(a, st);
     case 1: return launch_mm_tile<4, 2, 3>(a, st);
     default: return launch_mm_tile<2, 2, 2>(a, st);
   }
 }
-// K splits for m > 128 rows: more of them fill the chip when the tiles do not, and each writes and reads m * rows partial sums
-// (at about 4 TB/s).  7B O projection: 512 rows 29 us + 17 of sums with four splits, 2048 rows 70 + 17 with one (66 + 33 with two).
-int gemm_rows_split(int m, int rows, int in, int max_split) {
-  const int blocks = (rows + 31) / 32, slabs = (in + 255) / 256;
-  int best = 1;
-  float t = 0.f;
-  for (int s = 1; s <= max_split && (s == 1 || slabs / s >= 4); s++) {
-    float u;
-    mm_tile(m, 1, blocks, in, s, &u);
-    u += (float)s * (float)m * (float)rows * (8.f / 4e6f);
-    if (s == 1 || u < t) { t = u; best = s; }
-  }
-  return best;
+// Whether m rows pay for folding the ranges instead of writing n_split sets of partial sums for `block` rows at a time.
+// A set is written and read at about 8 TB/s (it stays in the memory-side cache).  us per layer of prefill, blocks -> fold: 7B shape, 1800 rows
+// 1152 -> 1087, 4096 2594 -> 2493; 8B 2048 1290 -> 1213; 70B 1024 2072 -> 1997.  The 13B shape keeps the blocks: folded tiles of its 5120
+// rows (20 per token tile) fall unevenly on the XCDs (1536 rows 1308 -> 1476 when folded), hence rounds by XCD.
+static float mm_xcd_us(int tile, int m, int blocks, int in, int ranges) {   // mm_us, with the rounds of the busiest XCD
+  const int tok = tile == 2 ? 128 : 256, wb = tile == 1 ? 6 : 8;
+  const float at4096 = tile == 0 ? 112.f : (tile == 1 ? 88.f : 64.f);
+  const int per_xcd = ((blocks + wb - 1) / wb * ranges + 7) / 8 * ((m + tok - 1) / tok);
+  return (float)((per_xcd + 31) / 32) * (at4096 * (float)in / (4096.f * (float)ranges) + 6.f);
 }
-
+bool gemm_fold_pays(int m, int rows, int in, int n_split, int block) {
+  if (in >= (1 << 22) || rows >= (1 << 24)) return false;     // as mm_takes
+  const int blocks = (rows + 31) / 32;
+  const float set_us = (float)m * (float)rows * (8.f / 8e6f);
+  float split_us = (float)n_split * set_us;
+  for (int r0 = 0; r0 < m; r0 += block) {
+    const int n = std::min(block, m - r0);
+    split_us += mm_xcd_us(mm_tile(n, 1, blocks, in, n_split), n, blocks, in, n_split);
+  }
+  return mm_xcd_us(2, m, blocks, in, 1) + set_us < split_us;
+}
 // Copies into the LDS need 16-byte aligned sources, and the kernel's offsets inside a tile are 32-bit.
 static bool mm_takes(const GemmArgs &a) {
   uintptr_t low = (uintptr_t)a.x | (uintptr_t)a.x2 | (uintptr_t)a.seg_w[0];
@@ -793,6 +834,8 @@ static bool mm_takes(const GemmArgs &a) {
   if (a.nseg > 2) low |= (uintptr_t)a.seg_w[2];
   return (low & 15) == 0 && a.ldx % 8 == 0 && a.ldx >= 0 && a.ldx < (1 << 22) && a.in < (1 << 22) && a.ldp < (1 << 24);
 }
+
+bool gemm_can_fold(const GemmArgs &a) { return a.act == nullptr && a.x2 == nullptr && mm_takes(a); }
 
 template <bool PAIR>
 static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
@@ -831,7 +874,8 @@ static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
 // Up to 128 rows in all the launch is bound by the weights, read once; a pair of row sets shares that one pass.
 static hipError_t launch_bf16(const GemmArgs &a, hipStream_t st) {
   const long long rows = (long long)a.m * (a.x2 ? 2 : 1);
-  if (rows <= 128) return a.x2 ? launch_stream<true>(a, st) : launch_stream<false>(a, st);
+  if (a.fold && !gemm_can_fold(a)) return hipErrorInvalidValue;
+  if (rows <= 128 && !a.fold) return a.x2 ? launch_stream<true>(a, st) : launch_stream<false>(a, st);
   if (mm_takes(a)) return launch_mm(a, st);
   for (int set = 0; set < (a.x2 ? 2 : 1); set++)               // any alignment: 128 rows at a time through the streaming kernel
     for (int m0 = 0; m0 < a.m; m0 += 128) {

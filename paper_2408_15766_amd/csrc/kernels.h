@@ -45,6 +45,7 @@ struct GemmArgs {
   int nseg, total_blocks;
   float *part;  int ldp;  int m_pad;    // partial sums [n_split][m_pad][ldp], fp32
   int n_split;                          // K is cut into n_split ranges of whole slabs, balanced to one slab
+  int fold;                             // bf16: the ranges' sums are added up in ascending order and part is [1][m_pad][ldp] (gemm_can_fold)
   // SwiGLU mode (act != nullptr): one segment, the packed gate/up matrix; seg_rows[0] = columns of act,
   // seg_blocks[0] = ceil(columns / 16), n_split = 1.  The wave that streams a block writes
   // act[i][c] = silu(gate) * up in the storage type instead of partial sums.
@@ -53,10 +54,10 @@ struct GemmArgs {
   int blk_per_wg, blk_per_wave;         // set by launch_gemm: wave w of workgroup x streams block x * blk_per_wg + w * blk_per_wave
 };
 hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st);
+bool gemm_can_fold(const GemmArgs &a);
+bool gemm_fold_pays(int m, int rows, int in, int n_split, int block);
 hipError_t gemm_init();                 // one-time kernel attributes; call outside any stream capture
 int gemm_k_per_slab(int dtype);
-// K splits (at most max_split) of a bf16 projection over m > 128 rows: a function of the shape and m
-int gemm_rows_split(int m, int rows, int in, int max_split);
 int gemm_k_per_iter(int dtype);
 // Packed layout of a row-major [rows, in] matrix (see gemm.hip): size in bytes, and the out-of-place repack.
 size_t packed_weight_bytes(int dtype, int rows, int in);

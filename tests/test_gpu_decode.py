@@ -394,7 +394,7 @@ LONG_PROMPT = [wl.LLAMA2_7B.with_(name="llama2-7b-2layer-p1400", n_layers=2, pro
 @pytest.mark.parametrize("sh", LONG_PROMPT, ids=lambda s: s.name)
 def test_bf16_logits_long_prompt_within_tolerance_of_oracle(env, sh):
     """A 1400-token prompt: every verified row's attention runs eight 128-key parts and the 256-key parts beyond
-    position 1024 on the matrix cores (and the prefill three 512-row chunks), MHA 32 x 128 and GQA 32 / 8; the logits
+    position 1024 on the matrix cores (and the prefill one chunk), MHA 32 x 128 and GQA 32 / 8; the logits
     of the verified tree against the bf16-storage oracle, every logit inside the tolerance."""
     torch, P = env
     hw = wl.make_weights(sh)
@@ -407,6 +407,51 @@ def test_bf16_logits_long_prompt_within_tolerance_of_oracle(env, sh):
     g_max, g_rms, ok = logit_stats(sh.name, eng.logits(t.n_nodes), oracle_logits_for(hw, sh, prompt, t, first, np.float64, wl.round_to_bf16),
                                    "GPU vs oracle with bf16 storage")
     assert ok.all() and g_max <= STORE_MAX and g_rms <= STORE_RMS
+
+
+PROMPT_ROWS = [(wl.LLAMA3_8B.with_(name="llama3-8b-width-2layer", n_layers=2, vocab=4096), (3, 130, 300, 700, 2100, 4700)),
+               # gate/up with a K split, too
+               (wl.LLAMA2_7B.with_(name="bf16-d2048-ffn1536-2layer", n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=16, d_ffn=1536, vocab=4096),
+                (17, 200, 513, 2049)),
+               (wl.TINY, (5, 130, 513, 1100))]
+
+
+@pytest.mark.parametrize("sh,lengths", PROMPT_ROWS, ids=lambda v: getattr(v, "name", None))
+def test_prompt_rows_do_not_depend_on_the_prompts_length(env, sh, lengths):
+    """The cache rows (target, every layer, and draft) of a prompt's prefix have the same bits whatever follows it: prompts of a few
+    rows, of several tiles, of one chunk and of several with a ragged last one (2048 rows a chunk in bf16, 512 in fp32).  And
+    prefilling a prompt with its answer gives the rows that decoding the answer gave."""
+    torch, P = env
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    dt = torch.bfloat16 if sh.dtype == "bf16" else torch.float32
+    weights = P.pack_weights((name, torch.ones(dims, dtype=dt, device="cuda") if kind == "ones" else
+                              torch.empty(dims, dtype=dt, device="cuda").normal_(0.0, 0.02, generator=gen))
+                             for name, dims, kind in wl.tensor_specs(sh))
+    text = np.random.default_rng(3).integers(0, sh.vocab, max(lengths)).astype(np.int32)
+
+    def rows(eng, n):
+        out = [eng.kv(0, l, n) for l in range(sh.n_layers)] + [eng.kv(1, 0, n - 1)]
+        return [a for kv in out for a in kv]
+
+    def prefill(prompt):
+        eng = P.Engine(sh.with_(prompt_len=len(prompt)), weights)
+        eng.prefill(prompt)
+        got = rows(eng, len(prompt))
+        eng.close()
+        return got
+    longest = prefill(text)
+    for n in lengths[:-1]:
+        for a, b in zip(prefill(text[:n]), longest):
+            assert a.tobytes() == b[:a.shape[0]].tobytes()
+    n = lengths[-2] - 9
+    eng = P.Engine(sh.with_(prompt_len=n), weights)
+    tokens, _ = eng.generate(text[:n], 12)
+    done = eng.committed
+    decoded = rows(eng, done - 1)                              # (the draft's last pairs are still pending)
+    eng.close()
+    whole = prefill(np.concatenate([text[:n], np.array(tokens, np.int32)])[:done - 1])
+    for a, b in zip(decoded, whole):
+        assert a.tobytes() == b.tobytes()
 
 
 def test_bf16_spec_equals_greedy_bit_exact(env, bf16_model):
