@@ -100,6 +100,15 @@ int spec_k_accept_qratio(const float *p_logits, const float *q_logits, int32_t n
                          const int32_t *tree_tok, const int32_t *tree_par, uint64_t seed, uint32_t cycle, float *work,
                          int32_t *result, void *stream);
 
+/* The same walk as the engine runs it: q_logits holds q_rows draft rows, those
+ * of the nodes with children, and qrow_of[i] (device) is the row of node i
+ * (-1: none); the softmax statistics of all rows are computed first, by slices
+ * of 4096 tokens.  stats: 2 * (n_nodes + q_rows) * ceil(vocab / 4096) floats of
+ * device scratch, 8-byte aligned. */
+int spec_k_accept_qratio_rows(const float *p_logits, const float *q_logits, const int32_t *qrow_of, int32_t n_nodes, int32_t q_rows, int32_t vocab,
+                              float temperature, const int32_t *tree_tok, const int32_t *tree_par, uint64_t seed, uint32_t cycle, float *work,
+                              float *stats, int32_t *result, void *stream);
+
 /* The drafting side of the same rule: m (<= 16) distinct tokens drawn from
  * softmax(logits / temperature) without replacement, in draw order, as the m
  * largest of logits / temperature + Gumbel noise of stream (seed, cycle,

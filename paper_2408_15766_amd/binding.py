@@ -95,6 +95,8 @@ lib.spec_k_topk_logprob.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32,
 lib.spec_k_topk_logprob_static.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
 lib.spec_k_accept_qratio.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_float, C.c_void_p, C.c_void_p, C.c_uint64,
                                      C.c_uint32, C.c_void_p, C.c_void_p, C.c_void_p]
+lib.spec_k_accept_qratio_rows.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_float, C.c_void_p, C.c_void_p,
+                                          C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
 lib.spec_k_sample_children.argtypes = [C.c_void_p, C.c_int32, C.c_float, C.c_int32, C.c_uint64, C.c_uint32, C.c_uint32, C.c_void_p,
                                        C.c_void_p, C.c_void_p, C.c_void_p]
 lib.spec_hca_attention.argtypes = [C.c_int32, C.c_void_p, C.POINTER(C.c_void_p), C.POINTER(C.c_void_p), C.c_int32, C.c_int32,
@@ -356,6 +358,27 @@ def spec_k_accept_qratio(p_logits, q_logits, tree_tok, tree_par, temperature: fl
                                   tree_par.data_ptr(), seed, cycle, work.data_ptr(), res.data_ptr(), _stream_ptr())
     if rc:
         raise SpecError(rc, "spec_k_accept_qratio")
+    r = res.cpu().numpy()
+    m = int(r[0])
+    return [int(x) for x in r[2:2 + m]], [int(x) for x in r[17:18 + m]]
+
+
+def spec_k_accept_qratio_rows(p_logits, q_logits, qrow_of, tree_tok, tree_par, temperature: float, seed: int, cycle: int):
+    """As spec_k_accept_qratio, with draft rows only for nodes that have children: q_logits fp32 torch [rows, vocab],
+    qrow_of int32 torch [n_nodes] (-1: no row); the path of the engine's acceptance."""
+    import torch
+    n, vocab = p_logits.shape
+    assert q_logits.shape[1] == vocab and p_logits.dtype == torch.float32 and q_logits.dtype == torch.float32
+    assert p_logits.is_contiguous() and q_logits.is_contiguous() and qrow_of.dtype == torch.int32 and qrow_of.shape == (n,)
+    assert int(qrow_of.max()) < q_logits.shape[0]
+    work = torch.empty(vocab, dtype=torch.float32, device=p_logits.device)
+    stats = torch.full((2 * (n + q_logits.shape[0]) * ((vocab + 4095) // 4096),), float("nan"), dtype=torch.float32, device=p_logits.device)
+    res = torch.zeros(33, dtype=torch.int32, device=p_logits.device)
+    rc = lib.spec_k_accept_qratio_rows(p_logits.data_ptr(), q_logits.data_ptr(), qrow_of.data_ptr(), n, q_logits.shape[0], vocab, temperature,
+                                       tree_tok.data_ptr(), tree_par.data_ptr(), seed, cycle, work.data_ptr(), stats.data_ptr(), res.data_ptr(),
+                                       _stream_ptr())
+    if rc:
+        raise SpecError(rc, "spec_k_accept_qratio_rows")
     r = res.cpu().numpy()
     m = int(r[0])
     return [int(x) for x in r[2:2 + m]], [int(x) for x in r[17:18 + m]]

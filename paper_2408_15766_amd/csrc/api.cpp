@@ -850,6 +850,17 @@ int spec_verify(spec_ctx *c, const spec_tree *tree) {
   return SPEC_OK;
 }
 
+// The ratio rule with the softmax statistics of all rows from wide launches.  q_rows rows of draft logits; p_stat, q_stat: one pair per row
+// and slice.
+static hipError_t accept_qratio_rows(const float *p_logits, int n_nodes, const float *q_logits, int q_rows, const int *qrow_of, int vocab, float temp,
+                                     float2 *p_stat, float2 *q_stat, const int *tok, const int *par, uint64_t seed, uint32_t cycle, float *work,
+                                     AcceptResult *acc, hipStream_t st) {
+  hipError_t e = launch_rows_softmax_stats(p_logits, n_nodes, vocab, temp, p_stat, st);
+  if (e == hipSuccess && q_rows > 0) e = launch_rows_softmax_stats(q_logits, q_rows, vocab, temp, q_stat, st);
+  if (e != hipSuccess) return e;
+  return launch_accept_qratio(p_logits, q_logits, qrow_of, p_stat, q_stat, vocab, temp, tok, par, n_nodes, seed, cycle, work, acc, st);
+}
+
 int spec_accept(spec_ctx *c, const spec_tree *tree, int32_t *out_tokens, int32_t *n_out) {
   if (!c) return SPEC_EINVAL;
   if (!tree || !out_tokens || !n_out) return fail(c, SPEC_EINVAL, "accept: NULL argument");
@@ -864,10 +875,8 @@ int spec_accept(spec_ctx *c, const spec_tree *tree, int32_t *out_tokens, int32_t
     const int q_rows = c->st.n_expanded + (c->st.rows[0] ? 1 : 0);
     float2 *q_stat = (float2 *)c->sc_val;                      // the drafting top-k's scratch: kMaxTopK^2 floats a slice, two per row wanted
     static_assert(kMaxTopK * kMaxTopK >= 2 * kMaxNodes, "one pair per draft row and slice fits");
-    HIPCHK(c, launch_rows_softmax_stats(c->logits, N, g.vocab, g.temperature, c->stats, c->stream));
-    if (q_rows > 0) HIPCHK(c, launch_rows_softmax_stats(c->st_qrows, q_rows, g.vocab, g.temperature, q_stat, c->stream));
-    HIPCHK(c, launch_accept_qratio(c->logits, c->st_qrows, c->st_qrow_of, c->stats, q_stat, g.vocab, g.temperature, c->t_tok, c->t_par, N, g.seed, c->cycle,
-                                   c->part, c->acc, c->stream));
+    HIPCHK(c, accept_qratio_rows(c->logits, N, c->st_qrows, q_rows, c->st_qrow_of, g.vocab, g.temperature, c->stats, q_stat, c->t_tok, c->t_par,
+                                 g.seed, c->cycle, c->part, c->acc, c->stream));
   } else if (g.temperature > 0.f) {
     HIPCHK(c, launch_rows_softmax_stats(c->logits, N, g.vocab, g.temperature, c->stats, c->stream));
     HIPCHK(c, launch_accept_sample(c->logits, g.vocab, c->stats, g.temperature, c->t_tok, c->t_par, N, g.seed, c->cycle, c->acc, c->stream));
@@ -1156,6 +1165,17 @@ int spec_k_accept_qratio(const float *p_logits, const float *q_logits, int32_t n
     return SPEC_EINVAL;
   return launch_accept_qratio(p_logits, q_logits, nullptr, nullptr, nullptr, vocab, temperature, tree_tok, tree_par, n_nodes, seed, cycle, work,
                               (AcceptResult *)result, (hipStream_t)stream) == hipSuccess ? SPEC_OK : SPEC_EHIP;
+}
+
+int spec_k_accept_qratio_rows(const float *p_logits, const float *q_logits, const int32_t *qrow_of, int32_t n_nodes, int32_t q_rows, int32_t vocab,
+                              float temperature, const int32_t *tree_tok, const int32_t *tree_par, uint64_t seed, uint32_t cycle, float *work,
+                              float *stats, int32_t *result, void *stream) {
+  if (!p_logits || (!q_logits && q_rows > 0) || !qrow_of || !tree_tok || !tree_par || !work || !stats || !result || n_nodes < 1 || n_nodes > kMaxNodes ||
+      q_rows < 0 || q_rows > kMaxNodes || vocab < 1 || !(temperature > 0.f))
+    return SPEC_EINVAL;
+  float2 *p_stat = (float2 *)stats, *q_stat = p_stat + (size_t)n_nodes * argmax_slices(vocab);
+  return accept_qratio_rows(p_logits, n_nodes, q_logits, q_rows, qrow_of, vocab, temperature, p_stat, q_stat, tree_tok, tree_par, seed, cycle, work,
+                            (AcceptResult *)result, (hipStream_t)stream) == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
 int spec_k_sample_children(const float *logits, int32_t vocab, float temperature, int32_t m, uint64_t seed, uint32_t cycle,

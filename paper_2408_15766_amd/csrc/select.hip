@@ -122,7 +122,8 @@ __device__ __forceinline__ float2 merge_softmax_stats(const float2 *part, int n_
   float tot = 0.f;
   for (int s0 = 0; s0 < n_slices; s0 += 64) {              // slices in ascending groups of 64, fixed butterfly inside
     const int sl = s0 + lane;
-    tot += wave_sum(sl < n_slices ? stat[sl].y * expf(stat[sl].x - m) : 0.f);
+    // (a slice without any probability has the maximum -inf and no sum of its own)
+    tot += wave_sum(sl < n_slices && stat[sl].x != -INFINITY ? stat[sl].y * expf(stat[sl].x - m) : 0.f);
   }
   return make_float2(m, tot);
 }

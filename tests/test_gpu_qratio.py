@@ -55,6 +55,43 @@ def test_accept_qratio_matches_oracle_decisions(env, vocab, branching, temperatu
     assert compared >= trials * 0.9 and 0 < accepted_some < compared
 
 
+@pytest.mark.parametrize("vocab,branching,temperature,trials,masked", [(4096, (3, 2), 1.0, 24, False), (9001, (4, 2), 0.8, 24, False), (32000, (2, 2), 1.0, 16, False),
+                                                                       (270001, (2, 1), 1.0, 4, False), (16500, (3, 2), 1.0, 24, True)])
+def test_accept_qratio_from_row_statistics_matches_oracle_decisions(env, vocab, branching, temperature, trials, masked):
+    """The engine's form: draft rows only for nodes with children, in another order than the nodes, and every row's statistics from
+    slices of 4096 tokens (one, several, more than 64, a ragged last one).  The level of every (row, slice) is its own, so that
+    statistics of another row or slice change probabilities by factors; masked: whole slices without probability."""
+    torch, P = env
+    g = np.random.default_rng(vocab + 1)
+    n_nodes = 1 + branching[0] + branching[0] * branching[1]
+    n_exp = 1 + branching[0]
+    n_slices = (vocab + 4095) // 4096
+    compared = accepted_some = rejected_some = 0
+    for cycle in range(trials):
+        level = np.repeat(g.standard_normal((n_nodes, n_slices)) * 2, 4096, axis=1)[:, :vocab]
+        if masked:
+            for row in level:
+                row.reshape(-1)[4096 * int(g.integers(1, n_slices)):][:4096] = -np.inf
+        p_logits = (g.standard_normal((n_nodes, vocab)) * 2 + level).astype(np.float32)
+        q_logits = (p_logits + g.standard_normal((n_nodes, vocab)) * 1.0).astype(np.float32)
+        token, parent = make_tree(g, q_logits, temperature, branching, 78, cycle)
+        want_acc, want_next, margin = qratio.accept_qratio(token, parent, p_logits, q_logits, temperature, 78, cycle)
+        place = g.permutation(n_exp).astype(np.int32)          # node -> row
+        q_rows = np.empty((n_exp, vocab), np.float32)
+        q_rows[place] = q_logits[:n_exp]
+        qrow_of = np.concatenate([place, np.full(n_nodes - n_exp, -1, np.int32)])
+        cu = lambda a: torch.from_numpy(a).cuda()
+        got_acc, got_tok = P.spec_k_accept_qratio_rows(cu(p_logits), cu(q_rows), cu(qrow_of), cu(token), cu(parent), temperature, 78, cycle)
+        if margin < 1e-4:
+            continue
+        compared += 1
+        accepted_some += bool(want_acc)
+        rejected_some += want_acc[:1] != [1]
+        assert got_acc == want_acc, (cycle, got_acc, want_acc)
+        assert got_tok == [int(token[c]) for c in want_acc] + [want_next], (cycle, got_tok, want_next)
+    assert compared >= trials * 0.9 and accepted_some and rejected_some
+
+
 @pytest.mark.parametrize("vocab,m", [(50, 3), (1000, 16), (32000, 10), (128256, 4)])
 def test_sample_children_matches_oracle(env, vocab, m):
     torch, P = env

@@ -110,6 +110,28 @@ def test_static_tree_sampled_children_match_oracle(env, tiny_gpu, name, seed):
         assert got == want and taus == wt
 
 
+def test_static_tree_sampled_children_with_many_draft_rows_and_slices(env):
+    """113 draft rows (eight chains of fifteen) over a vocabulary of four 4096-token slices, the last one ragged: the rows' statistics
+    come from the sampled-children scratch, every decision and every drafted token agrees with the oracle.  LM head times four:
+    rows whose distributions differ."""
+    torch, P = env
+    sh = wl.TINY.with_(name="tiny-v12305", vocab=12305)
+    hw = dict(wl.make_weights(sh))
+    hw["lm_head"] = hw["lm_head"] * np.float32(4)
+    prompt, ss = wl.make_prompt(sh), StaticShape([-1] + [0] * 8 + list(range(1, 113)), [0] + list(range(8)) + [0] * 112)
+    assert ss.n_nodes == 121 and len(ss.expanded) == 113
+    orec, grec = [], []
+    want, wt = spec_decode_static(as_dtype(hw, np.float64), sh, prompt, 24, ss, temperature=1.0, seed=1, sampled=True, record=orec)
+    eng = P.Engine(sh, P.upload_weights(hw, sh.dtype), tree=(15, 8, 121), temperature=1.0, seed=1)
+    eng.set_static_tree(ss.parent, ss.rank, True)
+    got, taus = eng.generate(prompt, 24, record=grec)
+    assert min(r["margin"] for r in orec) > 1e-4 and 1 in wt and max(wt) > 2
+    assert got == want and taus == wt
+    for a, b in zip(grec, orec):
+        assert list(a["tree"].token) == list(b["tree"].token)
+        assert a["emitted"] == [int(b["tree"].token[j]) for j in b["accepted"]] + [b["bonus"]]
+
+
 def test_static_tree_errors_and_return_to_dynamic(env, tiny_gpu):
     torch, P = env
     sh, hw, w64, prompt, dw = tiny_gpu
