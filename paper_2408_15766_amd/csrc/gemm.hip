@@ -524,7 +524,7 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
 // in wavefront order.  Nothing is staged: a wavefront reads its own operands, the 16-byte pieces of TB token blocks and RB
 // half weight blocks, one step ahead.  The order of a row's sums depends on K and the split alone.
 // Measured (MI355X), against 32 x 32 tiles with all of K in one wavefront: the projections of a 256-wide layer, up to 16 rows,
-// 9.4 -> 3.4 us per launch; 2 x 129 rows x 9000 x 512 2 x 72 -> 48 us (25 TFLOP/s of 157: two tiles of k per wavefront).
+// 9.4 -> 3.4 us per launch.  Launches that fill the chip take gemm_f32_tiled_kernel below (same bits).
 // Lane (r = lane % 16, kg = lane / 16) supplies row r and, in step jj of a tile, the four k of piece (g = kg % 2, j = 2 jj + kg / 2).
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 template <int TB, int RB>
@@ -637,6 +637,167 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
     }
 }
 
+// ---- fp32 storage, launches that fill the chip ----------------------------------------------------------
+// gemm_f32_kernel fetches (tokens + weight rows) * 4 bytes for 2 * tokens * weight rows operations, in half used lines: about ten operations per
+// byte, and once the launch fills the chip the L2 limits it at about 60 TFLOP/s.  Here four wavefronts share a tile of 32 tokens x 64 weight
+// rows (two by two, 16 x 32 each) whose operands are copied straight into the LDS, 64 k at a time, one tile ahead; both keep the
+// packed layout there, in which a fragment read touches every bank evenly.  Three workgroups fit a compute unit, so one's waits are
+// covered by the others (tiles of 64 x 64, 64 x 128 and 128 x 128 were slower: fewer wavefronts).  Bound: the fp32 matrix rate (150 TFLOP/s
+// in a loop of nothing but these instructions).
+// The bits are gemm_f32_kernel's: an fp32 MFMA is a chain of fused multiply-adds in the order of its k (both shapes, checked against
+// fmaf), the 64-k tiles w, w + 4, ... of the K range have one accumulator, w = 0, 1, 2, 3 one after the other here, and the four sums are
+// added up in that order.
+// Measured (MI355X, us; gemm_f32_kernel before): 512 x 32000 x 4096 1966 -> 1110 (121 TFLOP/s), 1400 x 32000 x 1024 1083 -> 799, 512 x 12288 x
+// 4096 588 -> 411, 300 x 5504 x 1024 53 -> 44.
+constexpr int kF32Blocks = 2;                                 // 32-row weight blocks per workgroup
+__global__ __launch_bounds__(kGemmThreads, 3) void gemm_f32_tiled_kernel(GemmArgs a) {
+  constexpr int KI = 64, XI = kTileBytes / 4096, WI = kF32Blocks * XI;   // 1 KB copies per wave and tile
+  __shared__ __attribute__((aligned(1024))) unsigned char xs0[kTileBytes], xs1[kTileBytes], ws0[kF32Blocks * kTileBytes], ws1[kF32Blocks * kTileBytes];   // (arrays of their own: see gemm_mm_kernel)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, kg = lane >> 4, th = wave & 1, wh = wave >> 1;   // the wavefront's 16 tokens and its weight block
+  // ids 8 apart run on one XCD: the token tiles of a weight tile follow each other there
+  const int per = 8 * a.m_tiles;
+  const int q = ((int)blockIdx.x / per) * 8 + ((int)blockIdx.x % 8);
+  const int mt = ((int)blockIdx.x % per) / 8;
+  if (q >= a.grid_x * a.n_split) return;
+  const int bx = q % a.grid_x, by = q / a.grid_x;
+  const int set_tiles = (a.m + 31) / 32;
+  const bool second = mt >= set_tiles;
+  const int m0 = (second ? mt - set_tiles : mt) * 32, m_loc = min(a.m - m0, 32);
+  const int n_it_total = (a.in + KI - 1) / KI;
+  const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
+  const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
+  const int it_end = min(n_it_total, (int)((long long)(by + 1) * n_slabs_total / a.n_split) * kSlabIters);
+
+  const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
+  auto seg_of = [&](int blk, int &b0) { const int s = blk < e0 ? 0 : (blk < e1 ? 1 : 2); b0 = s == 0 ? 0 : (s == 1 ? e0 : e1); return s; };
+  // the 1 KB pieces this wave copies: of a weight tile as it is, of the X rows (piece j of row c, half g at j * 1024 + (g * 32 + c) * 16)
+  __amdgpu_buffer_rsrc_t wsrc[WI];
+#pragma unroll
+  for (int i = 0; i < WI; i++) {
+    const int p = wave * WI + i, blk = min(bx * kF32Blocks + p / 8, a.total_blocks - 1);
+    int b0;
+    const int seg = seg_of(blk, b0);
+    const void *w = seg == 0 ? a.seg_w[0] : (seg == 1 ? a.seg_w[1] : a.seg_w[2]);
+    wsrc[i] = buffer_of((const char *)w + (size_t)(blk - b0) * n_it_total * kTileBytes + p % 8 * 1024);
+  }
+  const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const float *)(second ? a.x2 : a.x) + (size_t)m0 * a.ldx);
+  const uint32_t xrow = (uint32_t)((lane & 31) < m_loc ? lane & 31 : 0) * (uint32_t)a.ldx * 4u;
+  auto copy = [&](unsigned char *xb, unsigned char *wb, int it) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < WI; i++) load_to_lds(wsrc[i], lane * 16, it * kTileBytes, wb + (wave * WI + i) * 1024);
+#pragma unroll
+    for (int i = 0; i < XI; i++) {
+      const int k = it * KI + (lane >> 5) * 32 + (wave * XI + i) * 4;   // past K: meets a zero weight
+      load_to_lds(xsrc, (int)(xrow + (uint32_t)(k < a.in ? k : 0) * 4u), 0, xb + (wave * XI + i) * 1024);
+    }
+  };
+
+  f32x4_t acc[2], sum[2];                                     // by half of the weight block
+  acc[0] = acc[1] = sum[0] = sum[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  struct Frag { f32x4_t x, w[2]; };                           // of step jj, as in gemm_f32_kernel
+  const int xfrag = ((kg & 1) * 32 + th * 16 + r) * 16 + (kg >> 1) * 1024, wfrag = wh * kTileBytes + ((kg & 1) * 32 + r) * 16 + (kg >> 1) * 1024;
+  auto read = [&](Frag &f, const unsigned char *xb, const unsigned char *wb, int jj) __attribute__((always_inline)) {
+    f.w[0] = *(const f32x4_t *)(wb + wfrag + jj * 2048);
+    f.w[1] = *(const f32x4_t *)(wb + wfrag + 256 + jj * 2048);
+    f.x = *(const f32x4_t *)(xb + xfrag + jj * 2048);
+  };
+  auto mul = [&](const Frag &f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+#pragma unroll
+      for (int b = 0; b < 2; b++) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.x[e], f.w[b][e], acc[b], 0, 0, 0);
+  };
+  Frag f[2];
+  int w = 0, it = it_begin, left = it_end - it_begin;         // tile `it` of those of group w: it_begin + w, + 4, ...
+  copy(xs0, ws0, it);
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  wg_barrier();
+  read(f[0], xs0, ws0, 0);
+  auto stage = [&](unsigned char *xc, unsigned char *wc, unsigned char *xn, unsigned char *wn) __attribute__((always_inline)) {
+    // on entry f[0] = the fragments of step 0; nobody reads the other buffers any more
+    const bool more = left > 1, turn = it + 4 >= it_end;      // turn: the group's last tile
+    const int next_w = turn ? w + 1 : w, next_it = turn ? it_begin + w + 1 : it + 4;
+#pragma unroll
+    for (int jj = 0; jj < 3; jj++) {
+      read(f[(jj + 1) & 1], xc, wc, jj + 1);
+      if (jj == 0 && more) copy(xn, wn, next_it);
+      __builtin_amdgcn_sched_barrier(0);                      // the reads ahead of the products that hide them
+      mul(f[jj & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (more) {
+      __builtin_amdgcn_s_waitcnt(0x0070);                     // vmcnt(0) lgkmcnt(0): every fragment of this tile is in registers, the next tile has arrived
+      wg_barrier();
+      read(f[0], xn, wn, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    mul(f[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (turn) {
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        // (a group without tiles adds its zero in gemm_f32_kernel)
+#pragma unroll
+        for (int v = 0; v < 4; v++) sum[b][v] = (w == 0 ? acc[b][v] : sum[b][v] + acc[b][v]) + (more ? -0.f : 0.f);
+        acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+    w = next_w; it = next_it; left--;
+  };
+  while (left >= 2) {
+    stage(xs0, ws0, xs1, ws1);
+    stage(xs1, ws1, xs0, ws0);
+  }
+  if (left) stage(xs0, ws0, xs1, ws1);
+
+  // lane (r, kg) holds, for weight row r of a half, tokens th * 16 + 4 * kg + v
+  const int blk = bx * kF32Blocks + wh, i0 = th * 16 + 4 * kg;
+  if (blk >= a.total_blocks) return;
+  if (a.act != nullptr) {                                     // SwiGLU: half 0 = gate rows, half 1 = the up rows of the same columns
+    const int f_ = a.seg_rows[0], col = blk * 16 + r;
+#pragma unroll
+    for (int v = 0; v < 4; v++)
+      if (i0 + v < m_loc && col < f_) ((float *)a.act)[(size_t)(m0 + i0 + v) * f_ + col] = silu_mul(sum[0][v], sum[1][v]);
+    return;
+  }
+  int b0;
+  const int seg = seg_of(blk, b0);
+  const int rows = seg == 0 ? a.seg_rows[0] : (seg == 1 ? a.seg_rows[1] : a.seg_rows[2]);
+  const int col0 = seg == 0 ? a.seg_col0[0] : (seg == 1 ? a.seg_col0[1] : a.seg_col0[2]);
+  float *out = (second ? a.part2 : a.part) + ((size_t)by * a.m_pad + m0) * a.ldp + col0;
+#pragma unroll
+  for (int b = 0; b < 2; b++) {
+    const int row = (blk - b0) * 32 + b * 16 + r;
+#pragma unroll
+    for (int v = 0; v < 4; v++)
+      if (i0 + v < m_loc && row < rows) out[(size_t)(i0 + v) * a.ldp + row] = sum[b][v];
+  }
+}
+
+static hipError_t launch_f32_tiled(GemmArgs a, hipStream_t st) {
+  a.m_tiles = (a.m + 31) / 32 * (a.x2 ? 2 : 1);
+  a.grid_x = (a.total_blocks + kF32Blocks - 1) / kF32Blocks;
+  const long long grid = ((long long)a.grid_x * a.n_split + 7) / 8 * 8 * a.m_tiles;
+  if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gemm_f32_tiled_kernel, dim3((unsigned)grid), dim3(kGemmThreads), 0, st, a);
+  return hipGetLastError();
+}
+// Which launches take it: more than 16 rows (one token block of gemm_f32_kernel, which then only streams the weights) and 16500 (row, weight
+// block, split) products, about one wavefront of gemm_f32_kernel's widest tile per SIMD.  us, gemm_f32_kernel / this one, by thousands of them: 12.3 (64 rows, 2048 x
+// 6144) 29.5 / 32.3; 12.8 (100, 2752 x 1024, 4 splits) 13.1 / 11.8; 16.4 (32, 4096 x 4096, 4 splits) 18.6 / 19.9; 16.9 (33, the same) 23.7 / 22.9;
+// 17 (17, 1024 x 32000) 28.3 / 24.1; 18 (64, 1024 x 9000) 28.9 / 22.8; 19.2 (200, 1024 x 3072) 19.4 / 22.5; 19.2 (100, 2048 x 6144) 42.9 / 39.6;
+// 24.6 (64, 4096 x 12288) 97 / 76; 100 (100, 1024 x 32000) 125 / 76; beyond that 1.2 to 2.4 times as fast.  16 rows: 1024 x 32000 21.4 / 23.9.
+// The copies into the LDS need 16-byte aligned sources, and the kernel's offsets inside a tile are 32-bit.
+static bool f32_tiled_pays(const GemmArgs &a) {
+  uintptr_t low = (uintptr_t)a.x | (uintptr_t)a.x2 | (uintptr_t)a.seg_w[0];
+  if (a.nseg > 1) low |= (uintptr_t)a.seg_w[1];
+  if (a.nseg > 2) low |= (uintptr_t)a.seg_w[2];
+  if ((low & 15) || a.ldx % 4 || a.ldx < 0 || a.ldx >= (1 << 22) || a.in >= (1 << 22)) return false;
+  const long long rows = (long long)a.m * (a.x2 ? 2 : 1);
+  return rows > 16 && rows * a.total_blocks * a.n_split > 16500;
+}
+
 template <int TB>
 static hipError_t launch_f32_tile(const GemmArgs &a, bool halves, hipStream_t st) {
   const int tiles = (a.m + TB * 16 - 1) / (TB * 16) * (a.x2 ? 2 : 1);
@@ -645,9 +806,10 @@ static hipError_t launch_f32_tile(const GemmArgs &a, bool halves, hipStream_t st
   else hipLaunchKernelGGL((gemm_f32_kernel<TB, 2>), dim3(a.total_blocks, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
   return hipGetLastError();
 }
-// Token blocks per workgroup: the count out of 1, 2, 3, 4, 6 with the fewest padded blocks in all, the larger one on a tie (fewer
+// Otherwise, token blocks per workgroup: the count out of 1, 2, 3, 4, 6 with the fewest padded blocks in all, the larger one on a tie (fewer
 // passes over the weights).  Half weight blocks where whole ones would leave compute units without a workgroup.
 static hipError_t launch_f32(const GemmArgs &a, hipStream_t st) {
+  if (f32_tiled_pays(a)) return launch_f32_tiled(a, st);
   const int blocks = (a.m + 15) / 16;
   int tb = 1;
   long long best = blocks;

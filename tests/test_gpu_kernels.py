@@ -84,6 +84,35 @@ def test_gemm_fp32_matches_fp64(env, m, k, rows, n_split):
         assert torch.equal(P.spec_k_gemm(x[i:i + 1].contiguous(), ws, n_split)[:, 0], got[:, i])
 
 
+@pytest.mark.parametrize("m,k,rows,n_split", [(17, 100, [33000], 1), (31, 64, [20000, 33, 31], 1), (130, 260, [3000, 1111, 65], 1), (33, 516, [16400], 2),
+                                              (258, 1100, [1001, 1030], 3), (300, 2752, [1000], 4), (520, 1024, [1100], 1)])
+def test_gemm_fp32_tiled_matches_fp64_and_small_launches_bits(env, m, k, rows, n_split):
+    """fp32 launches that fill the chip (more than 16500 row-block products): 32 x 64 tiles, one row or one block past a tile, segments that
+    meet inside one, one to many 64-k tiles, groups of K without a tile, ragged K, K splits.  Rows alone take the other kernel and have
+    the same bits, and so has the whole through an X that is not 16-byte aligned; SwiGLU in the epilogue likewise."""
+    torch, P = env
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed("f32t", m, k) & 0xFFFF)
+    flat = torch.randn(m * k + 4, device="cuda", generator=g)
+    ws = [torch.randn(r, k, device="cuda", generator=g) * 0.05 for r in rows]
+    assert m * sum((r + 31) // 32 for r in rows) * n_split > 16500
+    x, off = flat[:m * k].view(m, k), torch.empty(m * k + 1, device="cuda")[1:].view(m, k)
+    off.copy_(x)
+    got = P.spec_k_gemm(x, ws, n_split)
+    want = x.double() @ torch.cat(ws).double().t()
+    assert (got.double().sum(0) - want).abs().max() <= 1e-6 * np.sqrt(k) * max(1.0, float(want.abs().max()))
+    assert torch.equal(P.spec_k_gemm(off, ws, n_split), got)
+    for i in sorted({0, 15, 16, m // 2, m - 1}):
+        assert torch.equal(P.spec_k_gemm(x[i:i + 1].contiguous(), ws, n_split)[:, 0], got[:, i])
+    gate, up = torch.cat(ws), torch.cat(ws).flip(0)
+    act = P.spec_k_gemm_swiglu(x, gate, up)
+    gd = want
+    ud = want.flip(1)
+    ref = gd * torch.sigmoid(gd) * ud
+    assert ((act.double() - ref).abs() <= 1e-5 * np.sqrt(k) * (1 + ref.abs())).all()
+    assert torch.equal(P.spec_k_gemm_swiglu(off, gate, up), act)
+    assert torch.equal(P.spec_k_gemm_swiglu(x[m - 1:].contiguous(), gate, up)[0], act[m - 1])
+
+
 @pytest.mark.parametrize("dtype,m,k,rows", [("fp32", 16, 256, 688), ("bf16", 60, 4096, 1100), ("bf16", 1, 1280, 64), ("bf16", 200, 768, 300),
                                             ("bf16", 40, 256, 77), ("fp32", 33, 128, 77), ("bf16", 60, 512, 15), ("bf16", 130, 256, 45)])
 def test_gemm_swiglu_epilogue_matches_oracle(env, dtype, m, k, rows):
