@@ -16,8 +16,8 @@
 // Bound: the serial chain of a block inside a wavefront (LDS reads, matrix instructions, maximum, exponentials), with two
 // wavefronts per SIMD to cover each other; a wavefront's share of the staging is part of it and halves with 8 wavefronts.
 // Measured (MI355X, us, launches back to back): batch 2 x 2048, 32 heads of 128, three streams 115.7 -> 100 with 8
-// wavefronts; with 4: batch 2 x 1024 45.3 -> 42.6 (value rows read whole 1.5 of it, the maximum without a shuffle 0.3),
-// 333 x 16 heads of 64 10.5 -> 10.0.
+// wavefronts; with 4: batch 2 x 1024 45.3 -> 42.6 (value rows read whole 1.5 of it, the maximum without a shuffle 0.3).  Short launches
+// (333 positions, 16 heads of 64: 11.6) are bound by launch and latency and did not change.
 #include "common.h"
 #include "kernels.h"
 
@@ -369,13 +369,20 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
-// Workgroups of 8 wavefronts pay from long walks on (a tile's start, its band and the unequal lengths of its wavefronts at the
-// diagonal weigh more than in a tile of 128) and need two for each of the 256 compute units, or longest-first order has
-// nothing left to even out.  Measured (us, 4 -> 8 wavefronts): 512 workgroups of 2048 positions (batch 2, 32 heads) 131 -> 123, of
-// 4096 (32 heads) 184 -> 167; 256 of 2048 (32 heads) 74 -> 80, 512 and more of 256 .. 700 5 .. 30 % slower, 1500 (batch 3)
-// 114 -> 118, 1800 equal.  Head dim 64 has too few pieces per block for 512 threads to stage.
-constexpr long long kWideWorkgroups = 512;
-constexpr int kWideSeq = 2048;
+// Workgroups of 8 wavefronts save staging, but a tile of 256 has more rows past the end of the sequence, and a compute unit holds one
+// where it holds two of 4 wavefronts, so that the order longest first evens out less.  They pay
+//  * without a half-empty tile (an even number of 128-query tiles): 512 workgroups of 2000 positions 109 -> 98 us, of 1920 100 -> 99; 448 of
+//    2000 96 -> 94, of 1920 88 -> 93; 432 of 2304 102 -> 97, of 2100 92 -> 94;
+//  * from 1700 positions on (14 tiles): 448 of 1700 88 -> 82, of 1792 91 -> 85; 480 of 1536 103 -> 106, of 1280 83 -> 86, 400 of 1280 82 -> 85;
+//  * with 400 to 512 workgroups, a long and a short one for most of the 256 compute units: 400 of 2560 102 -> 97, 480 of 3072 138 -> 129, 512 of
+//    2048 110 -> 99, of 4096 179 -> 160; 320 of 2048 71 -> 75, 360 of 2304 85 -> 83, 384 of 4096 136 -> 135, 392 of 1792 80 -> 81; 560 of
+//    2560 140 -> 144, 576 of 2304 135 -> 139, 640 of 2048 169 -> 172;
+//  * and again from three each on, a little: 768 of 2000 179 -> 175, of 4096 266 -> 264, 864 of 2304 211 -> 205, 896 of 1792 181 -> 182, 1024 of
+//    4096 360 -> 336; 672 of 3072 194 -> 192, of 1792 143 -> 143, 720 of 2304 198 -> 198.
+// (4 -> 8 wavefronts, head dim 128, three streams, launches back to back.)  Head dim 64 has too few pieces per block for 512 threads to stage.
+bool wide_pays(long long tiles128, long long workgroups) {
+  return tiles128 % 2 == 0 && tiles128 >= 14 && ((workgroups >= 400 && workgroups <= 512) || workgroups >= 768);
+}
 
 template <int HD, int WAVES>
 hipError_t launch_waves(const HcaArgs &a, hipStream_t st) {
@@ -400,8 +407,8 @@ hipError_t launch_waves(const HcaArgs &a, hipStream_t st) {
 template <int HD>
 hipError_t launch_hd(const HcaArgs &a, hipStream_t st) {
   if constexpr (HD == 128) {
-    const long long wgs = (long long)a.batch * a.hq * ((a.seq + 255) / 256);
-    if (a.seq >= kWideSeq && wgs >= kWideWorkgroups) return launch_waves<HD, 8>(a, st);
+    const long long tiles = (a.seq + 127) / 128;
+    if (wide_pays(tiles, (long long)a.batch * a.hq * ((tiles + 1) / 2))) return launch_waves<HD, 8>(a, st);
   }
   return launch_waves<HD, 4>(a, st);
 }

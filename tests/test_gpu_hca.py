@@ -70,14 +70,19 @@ def test_hca_attention_matches_oracle(env, n_streams, batch, seq, hq, hkv, hd):
 
 
 @pytest.mark.parametrize("n_streams,batch,seq,hq,hkv", [
-    (8, 1, 2049, 64, 8),     # one query in the last 256-query tile, the band across the tiles' edge
     (3, 2, 2048, 32, 2),     # whole tiles; kv groups not a multiple of 8
-    (2, 1, 2207, 64, 64),    # wavefronts of the last tile without a query, ragged key block
-    (2, 1, 2047, 64, 8),     # just too short for wide workgroups
+    (8, 1, 1665, 64, 8),     # one query in the last 128: wavefronts of the last tile without a query, the band across the tiles' edge
+    (2, 1, 2207, 56, 56),    # ragged key block
+    (2, 1, 2047, 64, 8),     # one query short of a whole tile
+    (2, 3, 1793, 32, 4),     # (odd number of 128-query tiles: narrow)
+    (1, 3, 2000, 32, 4),     # three workgroups per compute unit
+    (8, 1, 2049, 64, 8),     # narrow: half of the last tile would be empty
+    (2, 1, 2207, 64, 64),    # narrow: 576 workgroups
+    (2, 1, 1650, 64, 8),     # just too short for wide workgroups
     (2, 1, 2048, 32, 8),     # too few of them
 ])
 def test_hca_attention_wide_workgroups(env, n_streams, batch, seq, hq, hkv):
-    # launches of 256-query workgroups (head dim 128, long sequences that fill the chip), and two that just miss the rule
+    # launches of 256-query workgroups (head dim 128, long sequences that fill the chip), and some that just miss the rule
     torch, P = env
     q, ks, vs = wl.make_hca_streams(16, n_streams, batch, seq, hq, hkv, 128)
     got = run_gpu(torch, P, q, ks, vs)
@@ -86,6 +91,17 @@ def test_hca_attention_wide_workgroups(env, n_streams, batch, seq, hq, hkv):
         want = hca.hca_attention(q[b].astype(np.float64), [k[b].astype(np.float64) for k in ks],
                                  [v[b].astype(np.float64) for v in vs], heads=heads)
         check(got[b], want, vs, heads=heads)
+
+
+def test_hca_attention_wide_workgroups_have_the_narrow_ones_bits(env):
+    # 2 x 2048 positions of 32 heads take 256-query workgroups, one batch element alone 128-query ones: a wavefront's 32 queries and the
+    # order of their keys are the same
+    torch, P = env
+    q, ks, vs = [[torch.from_numpy(x).cuda().to(torch.bfloat16) for x in xs] for xs in (lambda a, b, c: ([a], b, c))(*wl.make_hca_streams(18, 3, 2, 2048, 32, 8, 128))]
+    both = P.spec_hca_attention(q[0], ks, vs)
+    for b in range(2):
+        one = P.spec_hca_attention(q[0][b:b + 1], [k[b:b + 1] for k in ks], [v[b:b + 1] for v in vs])
+        assert torch.equal(one[0], both[b])
 
 
 def test_hca_attention_peaked_scores(env):
