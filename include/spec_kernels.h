@@ -31,6 +31,10 @@ int spec_k_gemm(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in
                 const void *w0, int32_t rows0, const void *w1, int32_t rows1, const void *w2, int32_t rows2,
                 float *part, int32_t ldp, int32_t m_pad, int32_t n_split, void *stream);
 
+/* The tile (tokens x weight rows) that spec_k_gemm takes for m > 128 bf16 rows
+ * and `blocks` 32-row weight blocks in all (host only; for tests). */
+int spec_k_gemm_tile(int32_t m, int32_t blocks, int32_t in, int32_t n_split, int32_t *tokens, int32_t *rows);
+
 /* The gate and up projections of the SwiGLU feed-forward block (the target LLMs of
  * Sec. 4.1 are LLaMA models) in one launch, with the activation applied in the
  * launch's epilogue: act[i][c] = silu(x[i] . w_gate[c]) * (x[i] . w_up[c]), silu(g)

@@ -284,6 +284,15 @@ def spec_k_gemm(x, ws: Sequence, n_split: int, m: Optional[int] = None):
     return part
 
 
+def spec_k_gemm_tile(m: int, blocks: int, k: int, n_split: int = 1):
+    """(tokens, weight rows) of the tile that a launch over m > 128 bf16 rows takes."""
+    t, r = C.c_int32(), C.c_int32()
+    rc = lib.spec_k_gemm_tile(m, blocks, k, n_split, C.byref(t), C.byref(r))
+    if rc:
+        raise SpecError(rc, "spec_k_gemm_tile")
+    return t.value, r.value
+
+
 def spec_k_gemm_swiglu(x, w_gate, w_up, packed=None):
     """x: torch [m, in]; w_gate, w_up: row-major torch [rows, in] (packed here, per call: test use) -> act [m, rows].
     packed: optional packed gate/up matrix from spec_pack_gate_up, to keep packing out of a timed loop."""

@@ -1116,6 +1116,12 @@ int spec_k_gemm(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in
   return launch_gemm(dtype, a, (hipStream_t)stream) == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
+int spec_k_gemm_tile(int32_t m, int32_t blocks, int32_t in, int32_t n_split, int32_t *tokens, int32_t *rows) {
+  if (!tokens || !rows || m <= 128 || blocks < 1 || in < 1 || n_split < 1) return SPEC_EINVAL;
+  gemm_mm_tile(m, 1, blocks, in, n_split, tokens, rows);
+  return SPEC_OK;
+}
+
 int spec_k_gemm_swiglu(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in, const void *w_gate_up, int32_t rows, void *act,
                        void *stream) {
   if (!x || !w_gate_up || !act || ((uintptr_t)act & 3) || rows < 1 || (dtype != 0 && dtype != 1)) return SPEC_EINVAL;

@@ -73,7 +73,7 @@ __device__ __forceinline__ void put_candidate(float *out, int pos, uint64_t key,
   out[8 + 3 * pos + 2] = key ? zp : 0.f;
 }
 
-// Bound: the logits' way from the last-level cache (16 16-byte loads per thread in flight); the selection works on registers.
+// Bound: the logits' way from the last-level cache (eight 16-byte loads per thread in flight); the selection works on registers.
 __global__ __launch_bounds__(kLossThreads) void loss_slice_kernel(const float *zq, const float *zp, int ldz, int vocab, int k,
                                                                    int n_slices, float *scratch) {
   constexpr int PER = kTopkSlice / kLossThreads;   // 16

@@ -960,6 +960,10 @@ static int mm_tile(int m, int sets, int blocks, int in, int n_split) {
   }
   return best;
 }
+void gemm_mm_tile(int m, int sets, int blocks, int in, int n_split, int *tokens, int *rows) {
+  const int tile = mm_tile(m, sets, blocks, in, n_split);
+  *tokens = tile == 2 ? 128 : 256; *rows = tile == 1 ? 192 : 256;
+}
 static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
   if (a.fold) return launch_mm_tile<2, 2, 2, true>(a, st);
   switch (mm_tile(a.m, a.x2 ? 2 : 1, a.total_blocks, a.in, a.n_split)) {

@@ -56,6 +56,7 @@ struct GemmArgs {
 hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st);
 bool gemm_can_fold(const GemmArgs &a);
 bool gemm_fold_pays(int m, int rows, int in, int n_split, int block);
+void gemm_mm_tile(int m, int sets, int blocks, int in, int n_split, int *tokens, int *rows);   // tile of a launch over more than 128 bf16 rows
 hipError_t gemm_init();                 // one-time kernel attributes; call outside any stream capture
 int gemm_k_per_slab(int dtype);
 int gemm_k_per_iter(int dtype);

@@ -403,6 +403,10 @@ hipError_t launch_accept_greedy(const float *amax_val, const int *amax_idx, int 
 template <int U = 8, typename Load, typename F>
 __device__ __forceinline__ void for_share(int n, Load load, F f) {
   const int T = blockDim.x;
+  if (n <= 2 * T) {                                           // too short a share to fill the loads: 1000 entries 37.4 us with them (five nodes), 35.6 without
+    for (int v = threadIdx.x; v < n; v += T) f(v, load(v));
+    return;
+  }
   for (int v0 = threadIdx.x; v0 < n; v0 += U * T) {
     decltype(load(0)) x[U];
 #pragma unroll

@@ -75,6 +75,7 @@ CASES = [
     ("bf16", 17, 264, 1000, 3),         # both sides' rows in one token tile of the LM head, the boundary inside a 32-row block
     ("bf16", 64, 256, 1000, 3),         # ... the largest such pair
     ("bf16", 65, 256, 1000, 3),         # ... and one row more per side: tiled, each side its own tiles
+    ("fp32", 45, 200, 7000, 5),         # fp32 rows enough for the tiled LM head: each side its own 32-row tiles, ragged ones
     ("bf16", 1, 256, 100, 100),         # K = V: Eq. (1) becomes the cross-entropy (vocabulary smaller than one slice)
 ]
 

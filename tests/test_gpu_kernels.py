@@ -197,14 +197,23 @@ def test_gemm_row_is_independent_of_batch(env):
     assert torch.equal(ten, full[:, 5:15])
 
 
-@pytest.mark.parametrize("m,k,rows,n_split", [(129, 8, [31], 1), (129, 136, [32], 1), (255, 256, [225, 64, 40], 1), (257, 904, [520], 2),
-                                              (512, 2056, [4096, 32, 64], 4), (640, 1096, [12290], 2), (1025, 384, [8192], 1)])
-def test_gemm_many_rows_matches_fp64(env, m, k, rows, n_split):
+# the tile a case takes in each of its two calls (partial sums; SwiGLU over the first matrix)
+MANY_ROWS = [(129, 8, [31], 1, 256, 256), (129, 136, [32], 1, 128, 128), (255, 256, [225, 64, 40], 1, 128, 128), (257, 904, [520], 2, 128, 128),
+             (512, 2056, [4096, 32, 64], 4, 192, 128), (640, 1096, [12290], 2, 128, 128), (1025, 384, [8192], 1, 192, 192),
+             (510, 2056, [15990], 2, 256, 256), (509, 1160, [9010, 22000, 990], 1, 256, 192), (2045, 264, [7990], 1, 256, 256),
+             (2045, 520, [3970, 20, 40], 2, 256, 256)]
+
+
+@pytest.mark.parametrize("m,k,rows,n_split,tile,tile_swiglu", MANY_ROWS)
+def test_gemm_many_rows_matches_fp64(env, m, k, rows, n_split, tile, tile_swiglu):
     """More than 128 bf16 rows: every tile shape of that launch (128 x 256, 256 x 192, 256 x 256), one row or one weight block
     past a tile, segments that meet inside a tile, K of less than one stage, of 2 / 4 / 6n stages and ragged, K splits; the
     same call on an X that is not 16-byte aligned takes the other path.  fp32 sums of k terms of size 0.05: relative error of
     the whole far below 1e-6 * sqrt(k)."""
     torch, P = env
+    sizes = {256: (256, 256), 192: (256, 192), 128: (128, 256)}
+    assert P.spec_k_gemm_tile(m, sum((r + 31) // 32 for r in rows), k, n_split) == sizes[tile]
+    assert P.spec_k_gemm_tile(m, (rows[0] + 15) // 16, k) == sizes[tile_swiglu]
     g = torch.Generator(device="cuda"); g.manual_seed(case_seed(m, k) & 0xFFFF)
     flat = torch.randn(m * k + 8, device="cuda", generator=g).to(torch.bfloat16)
     ws = [(torch.randn(r, k, device="cuda", generator=g) * 0.05).to(torch.bfloat16) for r in rows]
