@@ -521,22 +521,21 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
 // K for a 32 x 32 tile (one v_mfma_f32_32x32x2 per two k, 64 cycles each) is what the launch waits for.  So the tile is
 // 16 weight rows wide per MFMA (v_mfma_f32_16x16x4: no products for absent rows with up to 16 tokens), the four wavefronts of a
 // workgroup split its K range by whole 64-k tiles (wavefront w takes tiles w, w + 4, ...), and their sums meet in the LDS once,
-// in wavefront order.  Nothing is staged: a wavefront reads its own operands, the 16-byte pieces of TB token blocks and RB
-// half weight blocks, one step ahead.  The order of a row's sums depends on K and the split alone.
+// in wavefront order.  Nothing is staged: a wavefront reads its own operands, the 16-byte pieces of a 16-token block and RB
+// half weight blocks, one 64-k tile ahead.  The order of a row's sums depends on K and the split alone.
 // Measured (MI355X), against 32 x 32 tiles with all of K in one wavefront: the projections of a 256-wide layer, up to 16 rows,
 // 9.4 -> 3.4 us per launch.  Launches that fill the chip take gemm_f32_tiled_kernel below (same bits).
 // Lane (r = lane % 16, kg = lane / 16) supplies row r and, in step jj of a tile, the four k of piece (g = kg % 2, j = 2 jj + kg / 2).
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-template <int TB, int RB>
+template <int RB>
 __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
-  constexpr int JU = TB * RB >= 8 ? 2 : 4;                    // steps loaded at a time
-  constexpr int E = TB * RB * 4;                              // sums per lane
+  constexpr int E = RB * 4;                                   // sums per lane
   __shared__ float sums[kGemmWaves][E][kWave];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kg = lane >> 4;
-  const int tiles = (a.m + TB * 16 - 1) / (TB * 16);          // per set of rows
+  const int tiles = (a.m + 15) / 16;                          // per set of rows
   const bool second = (int)blockIdx.z >= tiles;
-  const int m0 = ((int)blockIdx.z - (second ? tiles : 0)) * TB * 16, m_loc = min(a.m - m0, TB * 16);
+  const int m0 = ((int)blockIdx.z - (second ? tiles : 0)) * 16, m_loc = min(a.m - m0, 16);
   const int by = blockIdx.y, blk = RB == 2 ? (int)blockIdx.x : (int)blockIdx.x >> 1, h0 = RB == 2 ? 0 : (int)blockIdx.x & 1;
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
   const int seg = blk < e0 ? 0 : (blk < e1 ? 1 : 2);
@@ -552,89 +551,72 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
 
   const char *w0 = (const char *)seg_w + (size_t)(blk - b0) * n_it_total * kTileBytes + (((kg & 1) * 32 + r) * 16 + (kg >> 1) * 1024);
   const float *xbase = (const float *)(second ? a.x2 : a.x) + (size_t)m0 * a.ldx;
-  const float *xrow[TB];
+  const float *xrow = xbase + (size_t)(r < m_loc ? r : 0) * a.ldx;
+  f32x4_t acc[RB];
 #pragma unroll
-  for (int t = 0; t < TB; t++) xrow[t] = xbase + (size_t)(t * 16 + r < m_loc ? t * 16 + r : 0) * a.ldx;
-  f32x4_t acc[RB][TB];
-#pragma unroll
-  for (int b = 0; b < RB; b++)
-#pragma unroll
-    for (int t = 0; t < TB; t++) acc[b][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int b = 0; b < RB; b++) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  constexpr int HALVES = 4 / JU;
-  struct Step { f32x4_t x[JU][TB], w[JU][RB]; };
-  // step s of this wavefront: half s % HALVES of tile it_begin + wave + 4 * (s / HALVES)
-  const int n_tiles = max(0, (it_end - it_begin - wave + 3) / 4), n_step = n_tiles * HALVES;
-  auto load = [&](Step &d, int s) {
-    const int it = it_begin + wave + 4 * (s / HALVES);
+  struct Tile { f32x4_t x[4], w[4][RB]; };
+  const int n_tiles = max(0, (it_end - it_begin - wave + 3) / 4);   // of this wavefront
+  auto load = [&](Tile &d, int s) {
+    const int it = it_begin + wave + 4 * s;
     const char *wp = w0 + (size_t)it * kTileBytes;
 #pragma unroll
-    for (int u = 0; u < JU; u++) {
-      const int jj = (s % HALVES) * JU + u;
+    for (int jj = 0; jj < 4; jj++) {
 #pragma unroll
-      for (int b = 0; b < RB; b++) d.w[u][b] = *(const f32x4_t *)(wp + (h0 + b) * 256 + jj * 2048);
+      for (int b = 0; b < RB; b++) d.w[jj][b] = *(const f32x4_t *)(wp + (h0 + b) * 256 + jj * 2048);
       const int kk = it * KI + (kg & 1) * 32 + (2 * jj + (kg >> 1)) * 4;
-#pragma unroll
-      for (int t = 0; t < TB; t++) d.x[u][t] = *(const f32x4_t *)(xrow[t] + (kk < a.in ? kk : 0));   // past K: meets a zero weight
+      d.x[jj] = *(const f32x4_t *)(xrow + (kk < a.in ? kk : 0));   // past K: meets a zero weight
     }
   };
-  auto mul = [&](const Step &d) {
+  auto mul = [&](const Tile &d) {
 #pragma unroll
-    for (int u = 0; u < JU; u++)
+    for (int jj = 0; jj < 4; jj++)
 #pragma unroll
       for (int e = 0; e < 4; e++)
 #pragma unroll
-        for (int b = 0; b < RB; b++)
-#pragma unroll
-          for (int t = 0; t < TB; t++) acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x[u][t][e], d.w[u][b][e], acc[b][t], 0, 0, 0);
+        for (int b = 0; b < RB; b++) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x[jj][e], d.w[jj][b][e], acc[b], 0, 0, 0);
   };
-  Step cur, nxt;
-  if (n_step > 0) load(cur, 0);
+  Tile cur, nxt;
+  if (n_tiles > 0) load(cur, 0);
   int s = 0;
-  for (; s + 2 < n_step; s += 2) {
+  for (; s + 2 < n_tiles; s += 2) {
     load(nxt, s + 1);
     mul(cur);
     load(cur, s + 2);
     mul(nxt);
   }
-  if (s + 1 < n_step) {
+  if (s + 1 < n_tiles) {
     load(nxt, s + 1);
     mul(cur);
     mul(nxt);
-  } else if (s < n_step) {
+  } else if (s < n_tiles) {
     mul(cur);
   }
 
-  // lane (r, kg) holds, for weight row r of half h0 + b, tokens t * 16 + 4 * kg + v
+  // lane (r, kg) holds, for weight row r of half h0 + b, tokens 4 * kg + v
 #pragma unroll
-  for (int t = 0; t < TB; t++)
+  for (int b = 0; b < RB; b++)
 #pragma unroll
-    for (int b = 0; b < RB; b++)
-#pragma unroll
-      for (int v = 0; v < 4; v++) sums[wave][(t * RB + b) * 4 + v][lane] = acc[b][t][v];
+    for (int v = 0; v < 4; v++) sums[wave][b * 4 + v][lane] = acc[b][v];
   __syncthreads();
   auto total = [&](int e) { return ((sums[0][e][lane] + sums[1][e][lane]) + sums[2][e][lane]) + sums[3][e][lane]; };
+  const int i = 4 * kg + wave;                                // wavefront w finishes v = w
   if (a.act != nullptr) {                                     // SwiGLU (RB == 2): half 0 = gate rows, half 1 = the up rows of the same columns
     if constexpr (RB == 2) {
       const int col = blk * 16 + r;
-#pragma unroll
-      for (int t = 0; t < TB; t++) {                          // wavefront w finishes v = w
-        const float g = total(t * 8 + wave), u = total(t * 8 + 4 + wave);
-        const int i = t * 16 + 4 * kg + wave;
-        if (i < m_loc && col < seg_rows) ((float *)a.act)[(size_t)(m0 + i) * seg_rows + col] = silu_mul(g, u);
-      }
+      const float g = total(wave), u = total(4 + wave);
+      if (i < m_loc && col < seg_rows) ((float *)a.act)[(size_t)(m0 + i) * seg_rows + col] = silu_mul(g, u);
     }
     return;
   }
   float *out = (second ? a.part2 : a.part) + ((size_t)by * a.m_pad + m0) * a.ldp + seg_col0;
 #pragma unroll
-  for (int t = 0; t < TB; t++)
-#pragma unroll
-    for (int b = 0; b < RB; b++) {
-      const int row = (blk - b0) * 32 + (h0 + b) * 16 + r, i = t * 16 + 4 * kg + wave;
-      const float y = total((t * RB + b) * 4 + wave);
-      if (i < m_loc && row < seg_rows) out[(size_t)i * a.ldp + row] = y;
-    }
+  for (int b = 0; b < RB; b++) {
+    const int row = (blk - b0) * 32 + (h0 + b) * 16 + r;
+    const float y = total(b * 4 + wave);
+    if (i < m_loc && row < seg_rows) out[(size_t)i * a.ldp + row] = y;
+  }
 }
 
 // ---- fp32 storage, launches that fill the chip ----------------------------------------------------------
@@ -783,11 +765,11 @@ static hipError_t launch_f32_tiled(GemmArgs a, hipStream_t st) {
   hipLaunchKernelGGL(gemm_f32_tiled_kernel, dim3((unsigned)grid), dim3(kGemmThreads), 0, st, a);
   return hipGetLastError();
 }
-// Which launches take it: more than 16 rows (one token block of gemm_f32_kernel, which then only streams the weights) and 16500 (row, weight
-// block, split) products, about one wavefront of gemm_f32_kernel's widest tile per SIMD.  us, gemm_f32_kernel / this one, by thousands of them: 12.3 (64 rows, 2048 x
-// 6144) 29.5 / 32.3; 12.8 (100, 2752 x 1024, 4 splits) 13.1 / 11.8; 16.4 (32, 4096 x 4096, 4 splits) 18.6 / 19.9; 16.9 (33, the same) 23.7 / 22.9;
-// 17 (17, 1024 x 32000) 28.3 / 24.1; 18 (64, 1024 x 9000) 28.9 / 22.8; 19.2 (200, 1024 x 3072) 19.4 / 22.5; 19.2 (100, 2048 x 6144) 42.9 / 39.6;
-// 24.6 (64, 4096 x 12288) 97 / 76; 100 (100, 1024 x 32000) 125 / 76; beyond that 1.2 to 2.4 times as fast.  16 rows: 1024 x 32000 21.4 / 23.9.
+// Which launches take it: more than 16 rows (up to 16 one pass over the weights does in gemm_f32_kernel) and 1024 workgroups of that kernel, four
+// per compute unit.  us, gemm_f32_kernel / this one: 846 (48 rows, 512 x 9000) 12.5 / 12.9; 960 (80, 2048 x 6144) 30 / 39, (160, 1024 x 3072) 15.2 /
+// 14.4; 1024 (17, 4096 x 4096, 4 splits) 20.7 / 18.3, (128, 2752 x 1024, 4 splits) 12.7 / 11.8; 1128 (64, 1024 x 9000) 25.3 / 22.5; 1204 (100, 1024 x 5504)
+// 20.4 / 21.9; 1248 (200, 1024 x 3072) 18.2 / 21.9; 1344 (100, 2048 x 6144) 41.4 / 39.3; 1376 (128, 1024 x 5504) 23.7 / 22.2, (17, 4096 x 22016) 120 / 83;
+// 2000 (17, 1024 x 32000) 39 / 24; beyond that up to 2.4 times as fast.  16 rows of 1024 x 32000 21.4 / 23.7.
 // The copies into the LDS need 16-byte aligned sources, and the kernel's offsets inside a tile are 32-bit.
 static bool f32_tiled_pays(const GemmArgs &a) {
   uintptr_t low = (uintptr_t)a.x | (uintptr_t)a.x2 | (uintptr_t)a.seg_w[0];
@@ -795,37 +777,23 @@ static bool f32_tiled_pays(const GemmArgs &a) {
   if (a.nseg > 2) low |= (uintptr_t)a.seg_w[2];
   if ((low & 15) || a.ldx % 4 || a.ldx < 0 || a.ldx >= (1 << 22) || a.in >= (1 << 22)) return false;
   const long long rows = (long long)a.m * (a.x2 ? 2 : 1);
-  return rows > 16 && rows * a.total_blocks * a.n_split > 16500;
+  return rows > 16 && (long long)((a.m + 15) / 16) * (a.x2 ? 2 : 1) * a.total_blocks * a.n_split >= 1024;
 }
 
-template <int TB>
-static hipError_t launch_f32_tile(const GemmArgs &a, bool halves, hipStream_t st) {
-  const int tiles = (a.m + TB * 16 - 1) / (TB * 16) * (a.x2 ? 2 : 1);
-  if (tiles > 65535) return hipErrorInvalidValue;
-  if (halves) hipLaunchKernelGGL((gemm_f32_kernel<TB, 1>), dim3(a.total_blocks * 2, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
-  else hipLaunchKernelGGL((gemm_f32_kernel<TB, 2>), dim3(a.total_blocks, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
-  return hipGetLastError();
-}
-// Otherwise, token blocks per workgroup: the count out of 1, 2, 3, 4, 6 with the fewest padded blocks in all, the larger one on a tie (fewer
-// passes over the weights).  Half weight blocks where whole ones would leave compute units without a workgroup.
+// gemm_f32_kernel: half weight blocks while whole ones are few, or with up to 16 rows some more (then the weights' way counts and
+// not the products).  us, whole / half: 96 workgroups (16 rows, 1024 x 3072) 5.6 / 4.6, 128 (16 rows, 2752 x 1024, 4 splits) 4.7 / 4.1, (32 rows, 1024 x
+// 1024, 2 splits) 4.1 / 4.1; 192 (32 rows, 1024 x 3072) 5.7 / 6.8, 256 (32 rows, 2752 x 1024) 4.9 / 5.8; up to 16 rows 172 (one row, 1024 x 5504) 5.4 / 5.0, 282
+// (one row, 1024 x 9000) 8.8 / 7.1, 384 (16 rows, 4096 x 12288) 34.3 / 35.3, 512 (16 rows, 4096 x 4096, 4 splits) 13.3 / 14.7.  More 16-token blocks per
+// workgroup (2, 3, 4, 6) only lengthen it: 48 rows of 688 x 256 4.0 / 5.1 with two, 6.3 with three.
 static hipError_t launch_f32(const GemmArgs &a, hipStream_t st) {
   if (f32_tiled_pays(a)) return launch_f32_tiled(a, st);
-  const int blocks = (a.m + 15) / 16;
-  int tb = 1;
-  long long best = blocks;
-  for (int c : {2, 3, 4, 6}) {
-    const long long padded = (long long)(blocks + c - 1) / c * c;
-    if (padded <= best) { best = padded; tb = c; }
-  }
-  const long long wgs = (long long)a.total_blocks * a.n_split * ((blocks + tb - 1) / tb) * (a.x2 ? 2 : 1);
-  const bool halves = a.act == nullptr && wgs <= 128;
-  switch (tb) {
-    case 1: return launch_f32_tile<1>(a, halves, st);
-    case 2: return launch_f32_tile<2>(a, halves, st);
-    case 3: return launch_f32_tile<3>(a, halves, st);
-    case 4: return launch_f32_tile<4>(a, halves, st);
-    default: return launch_f32_tile<6>(a, halves, st);
-  }
+  const int tiles = (a.m + 15) / 16 * (a.x2 ? 2 : 1);
+  if (tiles > 65535) return hipErrorInvalidValue;
+  const long long wgs = (long long)a.total_blocks * a.n_split * tiles;
+  const bool halves = a.act == nullptr && wgs <= (a.m <= 16 ? 300 : 128);
+  if (halves) hipLaunchKernelGGL(gemm_f32_kernel<1>, dim3(a.total_blocks * 2, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
+  else hipLaunchKernelGGL(gemm_f32_kernel<2>, dim3(a.total_blocks, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
+  return hipGetLastError();
 }
 
 // ---- packing ---------------------------------------------------------------------------------

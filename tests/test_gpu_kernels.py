@@ -71,8 +71,8 @@ def test_gemm_matches_matmul(env, dtype, m, k, rows, n_split):
 @pytest.mark.parametrize("m,k,rows,n_split", [(1, 4, [1], 1), (16, 256, [257, 33, 31], 1), (17, 688, [48], 1), (33, 324, [4100], 1),
                                               (49, 1100, [96], 2), (81, 4096, [320], 4), (129, 512, [9000], 1), (700, 100, [64], 1)])
 def test_gemm_fp32_matches_fp64(env, m, k, rows, n_split):
-    """fp32 storage: every number of token blocks per workgroup (1, 2, 3, 4, 6), half and whole weight blocks, fewer than four
-    64-k tiles (wavefronts without work), ragged K and rows, K splits; a row alone gives the bits it has among the others."""
+    """fp32 storage: one to many 16-token blocks, half and whole weight blocks, fewer than four 64-k tiles (wavefronts without
+    work), ragged K and rows, K splits; a row alone gives the bits it has among the others."""
     torch, P = env
     g = torch.Generator(device="cuda"); g.manual_seed(case_seed("f32", m, k) & 0xFFFF)
     x = torch.randn(m, k, device="cuda", generator=g)
@@ -87,14 +87,14 @@ def test_gemm_fp32_matches_fp64(env, m, k, rows, n_split):
 @pytest.mark.parametrize("m,k,rows,n_split", [(17, 100, [33000], 1), (31, 64, [20000, 33, 31], 1), (130, 260, [3000, 1111, 65], 1), (33, 516, [16400], 2),
                                               (258, 1100, [1001, 1030], 3), (300, 2752, [1000], 4), (520, 1024, [1100], 1)])
 def test_gemm_fp32_tiled_matches_fp64_and_small_launches_bits(env, m, k, rows, n_split):
-    """fp32 launches that fill the chip (more than 16500 row-block products): 32 x 64 tiles, one row or one block past a tile, segments that
+    """fp32 launches that fill the chip (more than 16 rows, 1024 workgroups of the small kernel): 32 x 64 tiles, one row or one block past a tile, segments that
     meet inside one, one to many 64-k tiles, groups of K without a tile, ragged K, K splits.  Rows alone take the other kernel and have
     the same bits, and so has the whole through an X that is not 16-byte aligned; SwiGLU in the epilogue likewise."""
     torch, P = env
     g = torch.Generator(device="cuda"); g.manual_seed(case_seed("f32t", m, k) & 0xFFFF)
     flat = torch.randn(m * k + 4, device="cuda", generator=g)
     ws = [torch.randn(r, k, device="cuda", generator=g) * 0.05 for r in rows]
-    assert m * sum((r + 31) // 32 for r in rows) * n_split > 16500
+    assert (m + 15) // 16 * sum((r + 31) // 32 for r in rows) * n_split >= 1024
     x, off = flat[:m * k].view(m, k), torch.empty(m * k + 1, device="cuda")[1:].view(m, k)
     off.copy_(x)
     got = P.spec_k_gemm(x, ws, n_split)
