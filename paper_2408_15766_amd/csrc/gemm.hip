@@ -284,8 +284,9 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
 // adds no waits to the two written below.  The sums of a row run in the order of gemm_stream_kernel's (k ascending in
 // one accumulator).
 // Measured (MI355X, us; before = 128 x 256 tiles with the weights streamed through registers): 512 x 12288 x 4096 with 2 splits
-// 86 -> 55, 512 x 32000 x 4096 161 -> 129, 4096 x 28672 x 4096 1113 -> 824, 4096 x 4096 x 14336 492 -> 373 (1.27 PFLOP/s; the clock drops to
-// about 1.8 GHz under this load, the matrix cores are busy three quarters of the time).
+// 86 -> 55, 512 x 32000 x 4096 161 -> 129, 4096 x 28672 x 4096 1113 -> 824, 4096 x 4096 x 14336 492 -> 373 (1.27
+// PFLOP/s).  What limits it, by counters: the clock falls to about 1.9 GHz in the large launches, and there the matrix cores are busy 52 .. 56 % of the
+// cycles (LM head of 2 x 512 rows, 2048 x 28672 x 4096) while a wavefront waits for half of its time.
 template <int TW, int TB, int WB>
 struct MmTile {
   static constexpr int kTok = TW * TB * 32;                   // tokens per workgroup
