@@ -370,7 +370,7 @@ def test_bf16_logits_within_tolerance_of_oracle(env, bf16_model):
 
 
 def test_bf16_prefill_in_several_tiles_matches_oracle(env):
-    """A 300-token prompt at 7B width runs the prefill projections as three 128-row tiles (the last one ragged), with
+    """A 300-token prompt at 7B width runs the prefill projections as two 256-row or three 128-row tiles (the last one ragged), with
     SwiGLU formed inside the tiled gate/up launch; the logits of the following verify depend on every cached key and
     value, and are compared with the bf16-storage oracle like in the test above."""
     torch, P = env

@@ -389,11 +389,14 @@ def test_attention_long_context_matches_oracle(env, q_scale):
 
 
 @pytest.mark.parametrize("rows,hq,hkv,hd,base,order", [(257, 4, 4, 128, 0, "chain"), (256, 8, 8, 64, 63, "chain"), (300, 8, 1, 128, 64, "chain"),
-                                                       (289, 16, 8, 128, 1000, "chain"), (260, 4, 2, 64, 5, "reversed"), (270, 2, 1, 128, 130, "scattered")])
+                                                       (289, 16, 8, 128, 1000, "chain"), (260, 4, 2, 64, 5, "reversed"), (270, 2, 1, 128, 130, "scattered"),
+                                                       # launches large enough for one walk over all keys
+                                                       (300, 32, 4, 128, 0, "chain"), (257, 64, 8, 64, 1000, "reversed"), (270, 64, 64, 128, 130, "scattered")])
 def test_attention_of_a_long_chain_matches_fp64(env, rows, hq, hkv, hd, base, order):
-    """256 rows and more without a tree (prefill): ragged row tiles and key blocks, grouped heads, head counts with and without
-    the placement over eight L2s, empty and long caches, rows that do not stand in order of position (the caller may pass any
-    depths); peaked scores so that the running maximum moves."""
+    """Hundreds of rows without a tree (prefill), few heads (blocks of 256 rows with partials) and many (one walk over all keys, no
+    partials): ragged row tiles and key blocks, grouped heads, head counts with and without the placement over
+    eight L2s, empty and long caches, rows that do not stand in order of position (the caller may pass any depths); peaked
+    scores so that the running maximum moves."""
     torch, P = env
     rng = np.random.default_rng(case_seed("chain", rows, hq, hd))
     depth = {"chain": np.arange(rows), "reversed": np.arange(rows)[::-1], "scattered": rng.integers(0, rows, rows)}[order].astype(np.int32)
