@@ -284,9 +284,12 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
 // adds no waits to the two written below.  The sums of a row run in the order of gemm_stream_kernel's (k ascending in
 // one accumulator).
 // Measured (MI355X, us; before = 128 x 256 tiles with the weights streamed through registers): 512 x 12288 x 4096 with 2 splits
-// 86 -> 55, 512 x 32000 x 4096 161 -> 129, 4096 x 28672 x 4096 1113 -> 824, 4096 x 4096 x 14336 492 -> 373 (1.27
-// PFLOP/s).  What limits it, by counters: the clock falls to about 1.9 GHz in the large launches, and there the matrix cores are busy 52 .. 56 % of the
-// cycles (LM head of 2 x 512 rows, 2048 x 28672 x 4096) while a wavefront waits for half of its time.
+// 86 -> 50, 512 x 32000 x 4096 161 -> 129, 4096 x 28672 x 4096 1113 -> 790, 4096 x 4096 x 14336 492 -> 373.
+// What limits it (LM head of 2 x 512 rows, 240 us when this was taken; with parts of the loop left out): without the copies into the LDS 194,
+// without the fragment reads as well 158, without the barrier no change.  So it is the traffic through the LDS, and the power: the clock falls
+// to 1.8 GHz in the large launches, the matrix cores are busy 59 % of the cycles, and products from registers alone run at 1.59 PFLOP/s on
+// normally distributed data (2.39 on zeros).  Four wavefronts of 128 x 128 read a third less from the LDS, but one wavefront per SIMD
+// pays more at the ends of a tile: the same time at K = 8192, 3 % slower at 4096.
 template <int TW, int TB, int WB>
 struct MmTile {
   static constexpr int kTok = TW * TB * 32;                   // tokens per workgroup
@@ -295,6 +298,14 @@ struct MmTile {
   static constexpr int kXLoads = kX / 8192, kWLoads = kW / 8192;   // 1 KB copies per wave and stage
 };
 constexpr int kMmThreads = 512;
+
+// The token tiles of gemm_mm_mixed_kernel, per weight tile and K range: full ones of 256 rows (the last may have fewer, but more than 128), and
+// one ragged end of up to 128 rows per set.
+struct MmLists { int weight_tiles, set_full, full, ragged; };
+__host__ __device__ inline MmLists mm_lists(int m, int sets, int weight_tiles) {
+  const int f = m / 256 + (m % 256 > 128 ? 1 : 0);
+  return MmLists{weight_tiles, f, sets * f, m % 256 != 0 && m % 256 <= 128 ? sets : 0};
+}
 
 typedef __attribute__((address_space(3))) void lds_void;
 // 16 bytes per lane from base + voff (lane) + soff (wave-uniform) straight into the LDS, to dst + 16 * lane; dst is wave-uniform
@@ -312,25 +323,30 @@ __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// A field of the launch's arguments as a value of its own: a choice between two fields must not become a choice between their addresses (that
+// would put the arguments into private memory).
+template <typename V> __device__ __forceinline__ V pinned(V v) { asm("" : "+s"(v)); return v; }
+
 // FOLD: the workgroup walks all K ranges of its tile one after the other (the copies run on across the borders) and adds up
 // the ranges' sums in registers, ((range 0 + range 1) + range 2) + .., the order in which the row kernels add partial sums: the
 // bits of n_split sets of partial sums with one set in memory.  Only the smallest tile leaves registers for a second set of sums.
+//
+// One tile: token rows from m0 on of the first or second set of rows, weight blocks from bx * kBlocks on, K range by.  xs, ws: the stage buffers.
 template <int TW, int TB, int WB, bool FOLD>
-__global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
+__device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, bool second, int m0, unsigned char *xs0, unsigned char *xs1, unsigned char *ws0,
+                                             unsigned char *ws1, unsigned char *ws2) {
   using L = MmTile<TW, TB, WB>;
   constexpr int XI = L::kXLoads, WI = L::kWLoads;
-  __shared__ __attribute__((aligned(1024))) unsigned char xs0[L::kX], xs1[L::kX], ws0[L::kW], ws1[L::kW], ws2[L::kW];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, g = lane >> 5;
-  const int per = 8 * a.m_tiles;
-  const int q = ((int)blockIdx.x / per) * 8 + ((int)blockIdx.x % 8);
-  const int mt = ((int)blockIdx.x % per) / 8;
-  if (q >= a.grid_x * (FOLD ? 1 : a.n_split)) return;
-  const int bx = q % a.grid_x, by = FOLD ? 0 : q / a.grid_x;
-  const int set_tiles = (a.m + L::kTok - 1) / L::kTok;        // tiles of the second set of rows follow the first set's
-  const bool second = mt >= set_tiles;
-  const int m0 = (second ? mt - set_tiles : mt) * L::kTok, m_loc = min(a.m - m0, L::kTok);
+  bx = __builtin_amdgcn_readfirstlane(bx); by = __builtin_amdgcn_readfirstlane(by); m0 = __builtin_amdgcn_readfirstlane(m0);   // scalars, whatever divisions they come from
+  const int m_loc = min(a.m - m0, L::kTok);
+  const void *const w_0 = pinned(a.seg_w[0]), *const w_1 = pinned(a.seg_w[1]), *const w_2 = pinned(a.seg_w[2]);
+  const int rows_0 = pinned(a.seg_rows[0]), rows_1 = pinned(a.seg_rows[1]), rows_2 = pinned(a.seg_rows[2]);
+  const int col_0 = pinned(a.seg_col0[0]), col_1 = pinned(a.seg_col0[1]), col_2 = pinned(a.seg_col0[2]);
+  const void *const x_0 = pinned(a.x), *const x_1 = pinned(a.x2);
+  float *const out_0 = pinned(a.part), *const out_1 = pinned(a.part2);
 
   const bool swiglu = a.act != nullptr;
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
@@ -348,12 +364,12 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
     const int blk = min(bx * L::kBlocks + (wave * WI + i) / 4, a.total_blocks - 1);
     int b0;
     const int seg = block_seg(blk, b0);
-    const void *w = seg == 0 ? a.seg_w[0] : (seg == 1 ? a.seg_w[1] : a.seg_w[2]);
+    const void *w = seg == 0 ? w_0 : (seg == 1 ? w_1 : w_2);
     wsrc[i] = buffer_of((const char *)w + ((size_t)(blk - b0) * n_it_total + it_begin) * (size_t)kTileBytes + (wave * WI + i) % 4 * 1024);
   }
   // the X rows this wave copies: row segment rs = (t * 2 + g) * 32 + c holds the 64 bytes (32 k) of half g, its four 16-byte
   // pieces rotated by the row so that the fragment reads of eight consecutive rows touch all banks
-  const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const char *)(second ? a.x2 : a.x) + (size_t)m0 * a.ldx * 2);
+  const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const char *)(second ? x_1 : x_0) + (size_t)m0 * a.ldx * 2);
   uint32_t xoff[XI];
   int xk[XI];
 #pragma unroll
@@ -404,6 +420,18 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
       for (int t = 0; t < TB; t++) mfma_step(acc[wb][t], f.x[t], f.w[wb], bf16_t{});
   };
   Frag f[2];
+  // The order of a step: a fragment read of the next step behind each product, the copies behind the first ones.  In one bunch ahead
+  // of the products they kept the LDS from both wavefronts of a SIMD at the same time (2048 x 28672 x 4096 467 -> 450 us, 1024 x 128256 x 4096
+  // 951 -> 911).
+  auto spread = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    if (TB * WB >= 8) for (int i = 0; i < TB * WB; i++) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // a matrix instruction
+      if (i < TB + WB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
+      if (i >= 2) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);        // a copy
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
   auto stage = [&](unsigned char *xc, unsigned char *wc, unsigned char *xn, unsigned char *wn, unsigned char *wp, int s) {
     // on entry f[0] = the fragments of step 0
 #pragma unroll
@@ -411,9 +439,9 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
       read(f[(j + 1) & 1], xc, wc, j + 1);
       if (j == 0) load_w(wp, s + 2, 0, WI / 2);                // the copies spread over the steps
       if (j == 1) load_w(wp, s + 2, WI / 2, WI);
-      __builtin_amdgcn_sched_barrier(0);                      // the reads ahead of the products that hide them
+      if (TB * WB < 8) __builtin_amdgcn_sched_barrier(0);
       mul(f[j & 1]);
-      __builtin_amdgcn_sched_barrier(0);
+      spread();
     }
     // every fragment of this stage is in registers, and this wave's share of the next one has arrived (only the W loads of the
     // stage after it may still be under way)
@@ -421,9 +449,9 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
     wg_barrier();
     read(f[0], xn, wn, 0);
     load_x(xc, s + 2);
-    __builtin_amdgcn_sched_barrier(0);
+    if (TB * WB < 8) __builtin_amdgcn_sched_barrier(0);
     mul(f[1]);
-    __builtin_amdgcn_sched_barrier(0);
+    spread();
   };
 
   f32x16_t sum[FOLD ? WB : 1][FOLD ? TB : 1];                 // FOLD: the finished ranges
@@ -489,7 +517,7 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
     const int blk = bx * L::kBlocks + wq * WB + wb;
     if (blk >= a.total_blocks) continue;
     if (swiglu) {
-      const int f_ = a.seg_rows[0], col = blk * 16 + (c & 15);
+      const int f_ = rows_0, col = blk * 16 + (c & 15);
 #pragma unroll
       for (int t = 0; t < TB; t++) {                          // one token block at a time: the exchange needs registers of its own
         const int i0 = (th * TB + t) * 32;
@@ -501,11 +529,11 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
     }
     int b0;
     const int seg = block_seg(blk, b0);
-    const int rows = seg == 0 ? a.seg_rows[0] : (seg == 1 ? a.seg_rows[1] : a.seg_rows[2]);
-    const int col0 = seg == 0 ? a.seg_col0[0] : (seg == 1 ? a.seg_col0[1] : a.seg_col0[2]);
+    const int rows = seg == 0 ? rows_0 : (seg == 1 ? rows_1 : rows_2);
+    const int col0 = seg == 0 ? col_0 : (seg == 1 ? col_1 : col_2);
     const int row = (blk - b0) * 32 + c;
     if (row >= rows) continue;
-    float *out = (second ? a.part2 : a.part) + ((size_t)by * a.m_pad + m0 + th * TB * 32) * a.ldp;
+    float *out = (second ? out_1 : out_0) + ((size_t)by * a.m_pad + m0 + th * TB * 32) * a.ldp;
     const uint32_t o0 = (uint32_t)(col0 + row);
 #pragma unroll
     for (int t = 0; t < TB; t++)
@@ -515,6 +543,54 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
         if (th * TB * 32 + i < m_loc) out[o0 + (uint32_t)i * (uint32_t)a.ldp] = FOLD ? sum[FOLD ? wb : 0][FOLD ? t : 0][v] : acc[wb][t][v];
       }
   }
+}
+
+// Tiles of one shape.  Ids 8 apart run on one XCD: the token tiles of a weight tile follow each other there.
+template <int TW, int TB, int WB, bool FOLD>
+__global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_kernel(GemmArgs a) {
+  using L = MmTile<TW, TB, WB>;
+  __shared__ __attribute__((aligned(1024))) unsigned char xs0[L::kX], xs1[L::kX], ws0[L::kW], ws1[L::kW], ws2[L::kW];
+  const int per = 8 * a.m_tiles;
+  const int q = ((int)blockIdx.x / per) * 8 + ((int)blockIdx.x % 8);
+  const int mt = ((int)blockIdx.x % per) / 8;
+  if (q >= a.grid_x * (FOLD ? 1 : a.n_split)) return;
+  const int set_tiles = (a.m + L::kTok - 1) / L::kTok;        // tiles of the second set of rows follow the first set's
+  const bool second = mt >= set_tiles;
+  mm_tile_body<TW, TB, WB, FOLD>(a, q % a.grid_x, FOLD ? 0 : q / a.grid_x, second, (second ? mt - set_tiles : mt) * L::kTok, xs0, xs1, ws0, ws1, ws2);
+}
+
+// Measured against whole tiles only (us, launches of one shape): 2048 x 28672 x 4096 (3.5 rounds) 455 -> 432, 1024 x 57344 x 8192 841 -> 803, 1333 x
+// 28672 x 4096 320 -> 300.  In a prompt of thousands of rows, where every launch runs into the power limit, less of it is left: whole requests 0.7 to 1 %.
+// Tiles of 256 x 256 and, for what they would leave the chip half empty with, halves of 128 x 256: the tiles behind the last whole round
+// of an XCD's 32 compute units, and a last token tile of up to 128 rows.  XCD x = id % 8 has the weight tiles (and K ranges) x, x + 8, ..; its
+// list is every full token tile of each, in that order: n_big of them whole, the rest as pairs of halves, then the ragged ends.
+__global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_mixed_kernel(GemmArgs a) {
+  using L = MmTile<2, 4, 2>;
+  using H = MmTile<2, 2, 2>;
+  static_assert(H::kW == L::kW && 2 * H::kTok == L::kTok, "a half is half the tokens of a tile");
+  __shared__ __attribute__((aligned(1024))) unsigned char xs0[L::kX], xs1[L::kX], ws0[L::kW], ws1[L::kW], ws2[L::kW];
+  const MmLists l = mm_lists(a.m, a.x2 ? 2 : 1, a.grid_x * a.n_split);
+  const int x = (int)blockIdx.x % 8, j = (int)blockIdx.x / 8;
+  const int n_q = (l.weight_tiles - x + 7) / 8, n_full = n_q * l.full;
+  int ql, set, m0;
+  const bool big = j < a.n_big;
+  if (big || j - a.n_big < 2 * (n_full - a.n_big)) {
+    const int h = big ? 0 : j - a.n_big, t = big ? j : a.n_big + h / 2;
+    if (t >= n_full) return;
+    ql = t / l.full;
+    const int tok = t % l.full;
+    set = tok / l.set_full;
+    m0 = (tok % l.set_full) * L::kTok + (h & 1) * H::kTok;
+  } else {
+    const int r = j - a.n_big - 2 * max(n_full - a.n_big, 0);
+    if (r >= n_q * l.ragged) return;
+    ql = r / l.ragged; set = r % l.ragged;
+    m0 = l.set_full * L::kTok;
+  }
+  const int q = ql * 8 + x, bx = q % a.grid_x, by = q / a.grid_x;
+  const bool second = __builtin_amdgcn_readfirstlane(set) != 0;
+  if (big) mm_tile_body<2, 4, 2, false>(a, bx, by, second, m0, xs0, xs1, ws0, ws1, ws2);
+  else mm_tile_body<2, 2, 2, false>(a, bx, by, second, m0, xs0, xs1, ws0, ws1, ws2);
 }
 
 // ---- fp32 storage ---------------------------------------------------------------------------------
@@ -933,10 +1009,36 @@ void gemm_mm_tile(int m, int sets, int blocks, int in, int n_split, int *tokens,
   const int tile = mm_tile(m, sets, blocks, in, n_split);
   *tokens = tile == 2 ? 128 : 256; *rows = tile == 1 ? 192 : 256;
 }
+// The 256 x 256 tiles of an XCD that stay whole: all of them, or the whole rounds of its 32 compute units.  A whole tile takes tb, a half th
+// (the times of mm_us); halves start wherever a compute unit is free.
+static int mm_big_tiles(int m, int sets, int weight_tiles, int in, int n_split) {
+  const MmLists l = mm_lists(m, sets, weight_tiles);
+  const int n_q = (weight_tiles + 7) / 8, n_full = n_q * l.full, n_ragged = n_q * l.ragged;
+  const float k = (float)in / (4096.f * (float)n_split), tb = 112.f * k + 6.f, th = 64.f * k + 6.f;
+  auto us = [&](int big) {
+    const int rounds = big / 32, rest = big % 32, free_cu = 32 - rest;
+    int halves = n_ragged + 2 * (n_full - big);
+    if (rest == 0) return rounds * tb + (float)((halves + 31) / 32) * th;
+    halves -= free_cu;                                        // beside the last whole tiles
+    return (rounds + 1) * tb + (float)(halves > 0 ? (halves + 31) / 32 : 0) * th;
+  };
+  const int whole = n_full / 32 * 32;
+  return us(whole) < 0.97f * us(n_full) ? whole : n_full;
+}
+static hipError_t launch_mm_mixed(GemmArgs a, hipStream_t st) {
+  const int sets = a.x2 ? 2 : 1;
+  a.grid_x = (a.total_blocks + 7) / 8;
+  const MmLists l = mm_lists(a.m, sets, a.grid_x * a.n_split);
+  a.n_big = mm_big_tiles(a.m, sets, l.weight_tiles, a.in, a.n_split);
+  const int n_q = (l.weight_tiles + 7) / 8;                   // (of XCD 0, the longest list)
+  const int list = a.n_big + 2 * (n_q * l.full - a.n_big) + n_q * l.ragged;
+  hipLaunchKernelGGL(gemm_mm_mixed_kernel, dim3(8 * list), dim3(kMmThreads), 0, st, a);
+  return hipGetLastError();
+}
 static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
   if (a.fold) return launch_mm_tile<2, 2, 2, true>(a, st);
   switch (mm_tile(a.m, a.x2 ? 2 : 1, a.total_blocks, a.in, a.n_split)) {
-    case 0: return launch_mm_tile<2, 4, 2>(a, st);
+    case 0: return launch_mm_mixed(a, st);
     case 1: return launch_mm_tile<4, 2, 3>(a, st);
     default: return launch_mm_tile<2, 2, 2>(a, st);
   }

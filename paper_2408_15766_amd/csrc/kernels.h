@@ -51,6 +51,7 @@ struct GemmArgs {
   // act[i][c] = silu(gate) * up in the storage type instead of partial sums.
   void *act;
   int m_tiles, grid_x;                  // set by launch_gemm: token tiles, workgroups per tile and split
+  int n_big;                            // set by launch_gemm: whole 256 x 256 tiles per XCD (gemm_mm_mixed_kernel)
   int blk_per_wg, blk_per_wave;         // set by launch_gemm: wave w of workgroup x streams block x * blk_per_wg + w * blk_per_wave
 };
 hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st);

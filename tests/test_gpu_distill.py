@@ -90,6 +90,16 @@ def test_topk_loss_matches_oracle(env, dtype, rows, d, vocab, k):
     np.testing.assert_allclose(tot, [got_topk.sum(), got_ce.sum()], rtol=1e-5)
 
 
+@pytest.mark.parametrize("rows", [330, 260])
+def test_lm_head_in_whole_and_half_tiles(env, rows):
+    # both sides' rows through one launch whose token tiles end raggedly (74 and 4 rows) and whose last round runs in half tiles
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(28, rows, 264, 37000, "bf16")
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 5, "bf16")
+    want, alt, want_ce = oracle_losses(ft, fd, w, 5)
+    check(got_topk, got_ce, want, alt, want_ce)
+
+
 def test_whole_small_vocabulary_equals_cross_entropy(env):
     torch, P = env
     ft, fd, w = wl.make_distill_inputs(22, 7, 128, 100, "fp32")

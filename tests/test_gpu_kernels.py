@@ -229,6 +229,33 @@ def test_gemm_many_rows_matches_fp64(env, m, k, rows, n_split, tile, tile_swiglu
         assert ((act - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * np.sqrt(k)).all()
 
 
+# m, k, weight rows, whole 256 x 256 tiles per XCD as the launch plans them: none, one round, two; with and without a ragged end of up to 128 rows,
+# lists of XCDs that differ by one weight tile, a last full tile of 129 .. 255 rows
+SPLIT_TILES = [(600, 264, 20500), (700, 520, 20510), (1333, 264, 20600), (2049, 264, 16500), (2300, 136, 7000), (2047, 264, 18499)]
+
+
+@pytest.mark.parametrize("m,k,rows", SPLIT_TILES)
+def test_gemm_whole_and_half_tiles_match_fp64_and_single_rows(env, m, k, rows):
+    """Launches whose last round runs in tiles of half the tokens: against fp64 (fp32 sums of k terms of size 0.05), and rows at the edges of
+    tiles and halves have the bits they have alone; SwiGLU over a matrix of the same block count likewise."""
+    torch, P = env
+    assert P.spec_k_gemm_tile(m, (rows + 31) // 32, k) == (256, 256)
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed("split", m, rows) & 0xFFFF)
+    x = torch.randn(m, k, device="cuda", generator=g).to(torch.bfloat16)
+    w = (torch.randn(rows, k, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    got = P.spec_k_gemm(x, [w], 1)[0]
+    want = x.double() @ w.double().t()
+    assert (got.double() - want).abs().max() <= 1e-6 * np.sqrt(k) * max(1.0, float(want.abs().max()))
+    gate, up = w[:rows // 2], w[rows // 2:rows // 2 * 2]
+    act = P.spec_k_gemm_swiglu(x, gate, up)
+    gd, ud = want[:, :rows // 2], want[:, rows // 2:rows // 2 * 2]
+    ref = gd * torch.sigmoid(gd) * ud
+    assert ((act.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * np.sqrt(k)).all()
+    for i in sorted({0, 127, 128, 255, 256, m // 2, m // 256 * 256 - 1, m // 256 * 256, m - 1} & set(range(m))):
+        assert torch.equal(P.spec_k_gemm(x[i:i + 1].contiguous(), [w], 1)[0, 0], got[i])
+        assert torch.equal(P.spec_k_gemm_swiglu(x[i:i + 1].contiguous(), gate, up)[0], act[i])
+
+
 def make_tree(rng, rows, max_depth):
     par = np.full(rows, -1, np.int32)
     dep = np.zeros(rows, np.int32)
