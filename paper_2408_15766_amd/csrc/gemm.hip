@@ -425,7 +425,7 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
   // 951 -> 911).
   auto spread = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    if (TB * WB >= 8) for (int i = 0; i < TB * WB; i++) {
+    for (int i = 0; i < TB * WB; i++) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // a matrix instruction
       if (i < TB + WB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
       if (i >= 2) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);        // a copy
@@ -439,7 +439,6 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
       read(f[(j + 1) & 1], xc, wc, j + 1);
       if (j == 0) load_w(wp, s + 2, 0, WI / 2);                // the copies spread over the steps
       if (j == 1) load_w(wp, s + 2, WI / 2, WI);
-      if (TB * WB < 8) __builtin_amdgcn_sched_barrier(0);
       mul(f[j & 1]);
       spread();
     }
@@ -449,7 +448,6 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
     wg_barrier();
     read(f[0], xn, wn, 0);
     load_x(xc, s + 2);
-    if (TB * WB < 8) __builtin_amdgcn_sched_barrier(0);
     mul(f[1]);
     spread();
   };
