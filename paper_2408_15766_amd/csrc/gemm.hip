@@ -422,13 +422,17 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
   Frag f[2];
   // The order of a step: a fragment read of the next step behind each product, the copies behind the first ones.  In one bunch ahead
   // of the products they kept the LDS from both wavefronts of a SIMD at the same time (2048 x 28672 x 4096 467 -> 450 us, 1024 x 128256 x 4096
-  // 951 -> 911).
+  // 951 -> 911).  The four products of the smallest tile's step are too few for that: its reads stay ahead (32 workgroups, K 2464 36 us against 39).
+  constexpr bool kSpread = TB * WB > 4;
+  auto ahead = [&]() __attribute__((always_inline)) { if constexpr (!kSpread) __builtin_amdgcn_sched_barrier(0); };
   auto spread = [&]() __attribute__((always_inline)) {
+    if constexpr (kSpread) {
 #pragma unroll
-    for (int i = 0; i < TB * WB; i++) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // a matrix instruction
-      if (i < TB + WB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
-      if (i >= 2) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);        // a copy
+      for (int i = 0; i < TB * WB; i++) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // a matrix instruction
+        if (i < TB + WB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
+        if (i >= 2) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);        // a copy
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -439,6 +443,7 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
       read(f[(j + 1) & 1], xc, wc, j + 1);
       if (j == 0) load_w(wp, s + 2, 0, WI / 2);                // the copies spread over the steps
       if (j == 1) load_w(wp, s + 2, WI / 2, WI);
+      ahead();
       mul(f[j & 1]);
       spread();
     }
@@ -448,6 +453,7 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
     wg_barrier();
     read(f[0], xn, wn, 0);
     load_x(xc, s + 2);
+    ahead();
     mul(f[1]);
     spread();
   };
