@@ -15,9 +15,11 @@
 // own sums and meet once, at the end).
 // Bound: the serial chain of a block inside a wavefront (LDS reads, matrix instructions, maximum, exponentials), with two
 // wavefronts per SIMD to cover each other; a wavefront's share of the staging is part of it and halves with 8 wavefronts.
-// Measured (MI355X, us, launches back to back): batch 2 x 2048, 32 heads of 128, three streams 115.7 -> 100 with 8
-// wavefronts; with 4: batch 2 x 1024 45.3 -> 42.6 (value rows read whole 1.5 of it, the maximum without a shuffle 0.3).  Short launches
-// (333 positions, 16 heads of 64: 11.6) are bound by launch and latency and did not change.
+// Measured (MI355X, us, launches back to back): batch 2 x 2048, 32 heads of 128, three streams 115.7 -> 102 with 8
+// wavefronts -> 98 with the band behind the loop; with 4: batch 2 x 1024 45.3 -> 43.3 (value rows read whole 1.5 of it, the maximum without a shuffle
+// 0.3) -> 38.0.  Short launches (333 positions, 16 heads of 64: 9.8) are bound by launch and latency and did not change.
+// Tried: scores of the next block under the exponentials of this one, with keys and values copied straight into the LDS and transposed by the
+// read (ds_read_b64_tr_b16): 84 -> 90 with one stream; without the exponentials that form would take 67, so the matrix cores' power limit is near.
 #include "common.h"
 #include "kernels.h"
 
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
   };
 
   // query fragments (B operand): step kk covers dims kk*16 + g*8 .. +8 of query c.  They are requested before
-  // the band rows and the first key block: loads complete in order, so once that block has arrived nothing in
+  // the first key block: loads complete in order, so once that block has arrived nothing in
   // the main loop waits on the memory counter for the queries' sake (such a wait would also stall on the
   // block in flight).
   const bf16_t *qrow = (const bf16_t *)a.q + (((size_t)bi * T + tq) * a.hq + (size_t)hk * G + gh) * HD;
@@ -208,68 +210,6 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     for (int v = 0; v < 16; v++) o[db][v] = 0.f;
   // running maximum (of score * scale * log2 e) and sum of 2^(score' - maximum)
   float m_run = -INFINITY, l_run = 0.f;
-
-  // The band first (its loads travel together with the first key block's): key t-off of stream J-1-off,
-  // off = J-2 .. 0.  The 32 queries of the wavefront need 32 consecutive rows of that stream: they are read
-  // with coalesced 16-byte accesses (a row = PPR lanes) into the wavefront's own LDS area, and then every
-  // lane pair (c, c+32) picks up the row of ITS query, splitting the dot product by the dims of its query
-  // fragments and the value row by the dims of its output registers.  No other wavefront is involved; the
-  // workgroup barrier below separates this use of the LDS from the key blocks'.
-  {
-    unsigned char *bk = lds + wave * L::bwave, *bv = bk + 32 * L::brow;
-    constexpr int BP = 32 * PPR / 64;                         // 16-byte pieces per lane per tensor
-    for (int off = J - 2; off >= 0; off--) {
-      const bf16_t *kb = (const bf16_t *)a.k[J - 1 - off] + kv_off;
-      const bf16_t *vb = (const bf16_t *)a.v[J - 1 - off] + kv_off;
-      u32x4_t kw_[BP], vw_[BP];
-#pragma unroll
-      for (int e = 0; e < BP; e++) {
-        const int idx = lane + 64 * e;
-        const int row = min(max(r0 + idx / PPR - off, 0), T - 1);
-        kw_[e] = *(const u32x4_t *)(kb + (size_t)row * kv_stride + (idx % PPR) * 8);
-        vw_[e] = *(const u32x4_t *)(vb + (size_t)row * kv_stride + (idx % PPR) * 8);
-      }
-#pragma unroll
-      for (int e = 0; e < BP; e++) {
-        const int idx = lane + 64 * e;
-        *(u32x4_t *)(bk + (idx / PPR) * L::brow + (idx % PPR) * 16) = kw_[e];
-        *(u32x4_t *)(bv + (idx / PPR) * L::brow + (idx % PPR) * 16) = vw_[e];
-      }
-      wave_lds_order();
-      const bool have = tq - off >= 0;
-      float dot = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < KK; kk++) {
-        const u32x4_t kw = *(const u32x4_t *)(bk + c * L::brow + kk * 32 + g * 16);
-        const uint32_t kx[4] = {kw.x, kw.y, kw.z, kw.w}, qx[4] = {qf[kk].x, qf[kk].y, qf[kk].z, qf[kk].w};
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          dot = fmaf(lo_f32(qx[e]), lo_f32(kx[e]), dot);
-          dot = fmaf(hi_f32(qx[e]), hi_f32(kx[e]), dot);
-        }
-      }
-      dot += __shfl_xor(dot, 32, 64);
-      const float sc = have ? dot * c2 : -INFINITY;
-      const float m_new = fmaxf(m_run, sc);
-      const float m_use = m_new == -INFINITY ? 0.f : m_new;
-      const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
-      const float p = have ? __builtin_amdgcn_exp2f(sc - m_use) : 0.f;
-      l_run = l_run * corr + (g == 0 ? p : 0.f);               // the two lanes of a query add up their sums at the end
-      m_run = m_new;
-#pragma unroll
-      for (int db = 0; db < DB; db++)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; q4++) {
-          const u32x2_t vw = *(const u32x2_t *)(bv + c * L::brow + (db * 32 + 8 * q4 + 4 * g) * 2);
-          o[db][4 * q4 + 0] = fmaf(p, lo_f32(vw.x), o[db][4 * q4 + 0] * corr);
-          o[db][4 * q4 + 1] = fmaf(p, hi_f32(vw.x), o[db][4 * q4 + 1] * corr);
-          o[db][4 * q4 + 2] = fmaf(p, lo_f32(vw.y), o[db][4 * q4 + 2] * corr);
-          o[db][4 * q4 + 3] = fmaf(p, hi_f32(vw.y), o[db][4 * q4 + 3] * corr);
-        }
-      wave_lds_order();                                       // the next stream's rows overwrite the area
-    }
-  }
-  __syncthreads();
 
   if (nb > 0) {
     prefetch(0);
@@ -353,6 +293,72 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
       l_run += ls;
     }
     __syncthreads();                                          // block blk+1 staged; everyone is done with block blk
+  }
+
+  // The band last: key t-off of stream J-1-off, off = J-2 .. 0.  These rows are read once, from HBM (67 MB a stream at batch 2 x 2048, 32
+  // heads); ahead of the loop all workgroups of the launch asked for them at the same time and the matrix cores waited, behind it they ask as
+  // they finish, under the others' blocks (three of 1000 positions, 8 heads, eight streams 41.7 -> 38.4 us, one of 852, 32 heads, five 34.0 ->
+  // 31.6; a single short workgroup per compute unit gains nothing, 608 positions of 4 heads 21.9 -> 22.1).  The 32 queries of the wavefront need 32 consecutive rows of a stream: they are read with coalesced
+  // 16-byte accesses (a row = PPR lanes) into the wavefront's own LDS area, and then every lane pair (c, c+32) picks up the row of ITS query,
+  // splitting the dot product by the dims of its query fragments and the value row by the dims of its output registers.  No other wavefront is
+  // involved (every one has left the key blocks' LDS at the last barrier); the next stream's rows travel while one's are used.
+  {
+    unsigned char *bk = lds + wave * L::bwave, *bv = bk + 32 * L::brow;
+    constexpr int BP = 32 * PPR / 64;                         // 16-byte pieces per lane per tensor
+    u32x4_t kw_[BP], vw_[BP];
+    auto fetch = [&](int off) __attribute__((always_inline)) {
+      const bf16_t *kb = (const bf16_t *)a.k[J - 1 - off] + kv_off;
+      const bf16_t *vb = (const bf16_t *)a.v[J - 1 - off] + kv_off;
+#pragma unroll
+      for (int e = 0; e < BP; e++) {
+        const int idx = lane + 64 * e;
+        const int row = min(max(r0 + idx / PPR - off, 0), T - 1);
+        kw_[e] = *(const u32x4_t *)(kb + (size_t)row * kv_stride + (idx % PPR) * 8);
+        vw_[e] = *(const u32x4_t *)(vb + (size_t)row * kv_stride + (idx % PPR) * 8);
+      }
+    };
+    if (J > 1) fetch(J - 2);
+    for (int off = J - 2; off >= 0; off--) {
+#pragma unroll
+      for (int e = 0; e < BP; e++) {
+        const int idx = lane + 64 * e;
+        *(u32x4_t *)(bk + (idx / PPR) * L::brow + (idx % PPR) * 16) = kw_[e];
+        *(u32x4_t *)(bv + (idx / PPR) * L::brow + (idx % PPR) * 16) = vw_[e];
+      }
+      if (off > 0) fetch(off - 1);                            // on their way while this stream's rows are used
+      wave_lds_order();
+      const bool have = tq - off >= 0;
+      float dot = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KK; kk++) {
+        const u32x4_t kw = *(const u32x4_t *)(bk + c * L::brow + kk * 32 + g * 16);
+        const uint32_t kx[4] = {kw.x, kw.y, kw.z, kw.w}, qx[4] = {qf[kk].x, qf[kk].y, qf[kk].z, qf[kk].w};
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          dot = fmaf(lo_f32(qx[e]), lo_f32(kx[e]), dot);
+          dot = fmaf(hi_f32(qx[e]), hi_f32(kx[e]), dot);
+        }
+      }
+      dot += __shfl_xor(dot, 32, 64);
+      const float sc = have ? dot * c2 : -INFINITY;
+      const float m_new = fmaxf(m_run, sc);
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
+      const float p = have ? __builtin_amdgcn_exp2f(sc - m_use) : 0.f;
+      l_run = l_run * corr + (g == 0 ? p : 0.f);               // the two lanes of a query add up their sums at the end
+      m_run = m_new;
+#pragma unroll
+      for (int db = 0; db < DB; db++)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++) {
+          const u32x2_t vw = *(const u32x2_t *)(bv + c * L::brow + (db * 32 + 8 * q4 + 4 * g) * 2);
+          o[db][4 * q4 + 0] = fmaf(p, lo_f32(vw.x), o[db][4 * q4 + 0] * corr);
+          o[db][4 * q4 + 1] = fmaf(p, hi_f32(vw.x), o[db][4 * q4 + 1] * corr);
+          o[db][4 * q4 + 2] = fmaf(p, lo_f32(vw.y), o[db][4 * q4 + 2] * corr);
+          o[db][4 * q4 + 3] = fmaf(p, hi_f32(vw.y), o[db][4 * q4 + 3] * corr);
+        }
+      wave_lds_order();                                       // the next stream's rows overwrite the area
+    }
   }
 
   const float inv = 1.f / (l_run + __shfl_xor(l_run, 32, 64));
