@@ -382,6 +382,30 @@ __device__ __forceinline__ f32x16_t mfma_bf16(const u32x4_t &a, const u32x4_t &b
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
+// Value rows in the LDS: HD * 2 bytes a row, its 64-byte chunks permuted by the row so that the four rows a column read takes at a time
+// lie in different banks.
+template <int HD> __device__ __forceinline__ int value_chunk(int row, int chunk) { return chunk ^ (HD == 128 ? row & 3 : (row >> 1) & 1); }
+template <int HD> __device__ __forceinline__ int value_piece(int row, int piece) { return row * HD * 2 + value_chunk<HD>(row, piece >> 2) * 64 + (piece & 3) * 16; }
+// V^T fragments (A operand) out of them, by the LDS's transposing read (of the 4 x 16 matrix of 16-bit values whose row r the lanes 4 r .. 4 r + 3 of
+// sixteen point at, lane i gets column i): lane (c, g) has dim db * 32 + c at keys first + 4 g + {0 .. 3, 8 .. 11}.
+template <int HD> __device__ __forceinline__ int value_lane(int lane) {   // for db = 0, first = 0; db: ^ 64 db, first: a multiple of 16 rows further on
+  const int row = 4 * (lane >> 5) + ((lane & 15) >> 2);
+  return row * HD * 2 + value_chunk<HD>(row, 0) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+}
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+__device__ __forceinline__ u32x2_t read_columns(const unsigned char *p) {
+  return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)p));
+}
+template <int HD> __device__ __forceinline__ u32x4_t value_fragment(const unsigned char *v_lds, int at, int db, int first) {
+  const unsigned char *p = v_lds + (at ^ 64 * db) + first * HD * 2;
+  const u32x2_t v0 = read_columns(p), v1 = read_columns(p + 8 * HD * 2);
+  return u32x4_t{v0.x, v0.y, v1.x, v1.y};
+}
+// four floats at a 4-byte aligned address in one store
+__device__ __forceinline__ void store4_any(float *p, float a, float b, float c, float d) {
+  typedef __attribute__((ext_vector_type(4), aligned(4))) float f4_t;
+  *(f4_t *)p = f4_t{a, b, c, d};
+}
 
 // One launch covers both regions of the hybrid path.  Workgroups [0, n_bulk) (n_bulk = bulk_parts * kv heads
 // * q_groups, part fastest) run the matrix-core bulk: NW waves, wave w owns 32 "query rows" (row i, head gh
@@ -398,13 +422,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int DB = HD / 32;                 // 32-dim blocks of the output
   constexpr int KK = HD / 16;                 // MFMA steps of q.k
   constexpr int KSTR = HD * 2 + 16;           // LDS bytes per key row (+16: conflict-free b128 reads)
-  constexpr int VSTR = 32 * 2 + 8;            // LDS bytes per dim row of V^T (+8: conflict-free b64 reads)
   constexpr int NT = NW * 64;
   constexpr int PIECES = (32 * HD * 2 / 16 + NT - 1) / NT;   // 16-byte pieces of one K (or V) block per thread
   constexpr int kTailWaves = TailWaves<NW>::value;
   constexpr int kTailQ = G * HD * 4;                                         // a tail wavefront's query area
   constexpr int kTailWave = kTailQ + kTailKeys * PartLds<bf16_t>::vrow(HD);  // ... plus its staged value rows
-  constexpr int kBulkBuf = 32 * KSTR + HD * VSTR;                            // one staged K block + V^T block
+  constexpr int kBulkBuf = 32 * KSTR + 32 * HD * 2;                          // one staged K block + V block
   constexpr int kBulkLds = 2 * kBulkBuf;                                     // double-buffered
   constexpr int kLds = kBulkLds > kTailWaves * kTailWave ? kBulkLds : kTailWaves * kTailWave;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
@@ -469,20 +492,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int v = 0; v < 16; v++) o[db][v] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
+  const int vat = value_lane<HD>(lane);
 
   auto stage = [&](auto set_tag, int buf) {
     constexpr int SET = decltype(set_tag)::value;
-    unsigned char *k_lds = lds + buf * kBulkBuf, *vt_lds = k_lds + 32 * KSTR;
+    unsigned char *k_lds = lds + buf * kBulkBuf, *v_lds = k_lds + 32 * KSTR;
 #pragma unroll
     for (int e = 0; e < PIECES; e++) {
       const int q = tid + e * NT;
       if (q < 32 * PPR) {
         const int key = q / PPR, piece = q % PPR;
         *(u32x4_t *)(k_lds + key * KSTR + piece * 16) = kreg[SET][e];
-        const uint32_t w[4] = {vreg[SET][e].x, vreg[SET][e].y, vreg[SET][e].z, vreg[SET][e].w};
-#pragma unroll
-        for (int d2 = 0; d2 < 8; d2++)                       // V^T[dim][key]
-          *(uint16_t *)(vt_lds + (piece * 8 + d2) * VSTR + key * 2) = (uint16_t)(w[d2 >> 1] >> ((d2 & 1) * 16));
+        *(u32x4_t *)(v_lds + value_piece<HD>(key, piece)) = vreg[SET][e];
       }
     }
   };
@@ -514,7 +535,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       constexpr int j = decltype(j_tag)::value, cur = j & 1;
       const int b = b_lo + j;
       const bool live = computes && b < b_hi;                // same for all lanes of a wavefront
-      const unsigned char *k_lds = lds + cur * kBulkBuf, *vt_lds = k_lds + 32 * KSTR;
+      const unsigned char *k_lds = lds + cur * kBulkBuf, *v_lds = k_lds + 32 * KSTR;
       float pv[16];
       if (live) {
         f32x16_t s;
@@ -566,9 +587,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
           split8(x, phi, plo);
 #pragma unroll
           for (int db = 0; db < DB; db++) {
-            const unsigned char *vp = vt_lds + (db * 32 + c) * VSTR + (16 * u + 4 * g) * 2;
-            const u32x2_t v0 = *(const u32x2_t *)vp, v1 = *(const u32x2_t *)(vp + 16);
-            const u32x4_t vf = {v0.x, v0.y, v1.x, v1.y};
+            const u32x4_t vf = value_fragment<HD>(v_lds, vat, db, 16 * u);
             o[db] = mfma_bf16(vf, phi, o[db]);
             o[db] = mfma_bf16(vf, plo, o[db]);
           }
@@ -585,7 +604,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
   for (int db = 0; db < DB; db++)
 #pragma unroll
-    for (int v = 0; v < 16; v++) dst[2 + db * 32 + 8 * (v >> 2) + 4 * g + (v & 3)] = o[db][v];
+    for (int v = 0; v < 16; v += 4) store4_any(dst + 2 + db * 32 + 2 * v + 4 * g, o[db][v], o[db][v + 1], o[db][v + 2], o[db][v + 3]);
 }
 
 template <int HD, int G, int NW>
@@ -614,8 +633,7 @@ template <int HD, int WAVES> struct ChainLds {
   static constexpr int kScan = 64;                    // keys per staged block in pass 1 ...
   static constexpr int kKeys = HD == 128 ? 32 : 64;   // ... and in pass 2: what the registers beside queries and outputs leave
   static constexpr int kstr = HD * 2 + 16;            // bytes per staged key row (+16: conflict-free b128 reads)
-  static constexpr int vstr = kKeys * 2 + 8;          // bytes per dim row of V^T (+8: conflict-free b64 reads)
-  static constexpr int scan = kScan * kstr, walk = kKeys * kstr + HD * vstr;
+  static constexpr int scan = kScan * kstr, walk = kKeys * kstr + kKeys * HD * 2;
   static constexpr int buf = scan > walk ? scan : walk;
   static constexpr bool kQueryLds = HD == 128;
   static constexpr int total = 2 * buf + (kQueryLds ? WAVES * (HD / 16) * 1024 : 0);
@@ -630,8 +648,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
   using L = ChainLds<HD, WAVES>;
   constexpr int NT = WAVES * 64, SCAN = L::kScan, KEYS = L::kKeys, KT = KEYS / 32;
   constexpr int DB = HD / 32, KK = HD / 16, PPR = HD * 2 / 16;
-  constexpr int SP = SCAN * PPR / NT, KP = KEYS * PPR / NT, VP = KEYS / 2 * PPR / NT;
-  static_assert(SCAN * PPR % NT == 0 && KEYS * PPR % NT == 0 && KEYS / 2 * PPR % NT == 0, "staging split");
+  constexpr int SP = SCAN * PPR / NT, KP = KEYS * PPR / NT;
+  static_assert(SCAN * PPR % NT == 0 && KEYS * PPR % NT == 0, "staging split");
   static_assert(kAttnPart % KEYS == 0 && kAttnNear % KEYS == 0 && kAttnFarPart % KEYS == 0, "a part ends with a staged block");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   __shared__ int wave_hi[WAVES];
@@ -758,44 +776,33 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 
   // pass 2
   if (k_wg > 0) {
-    u32x4_t kreg[KP], vreg[VP][2];
+    u32x4_t kreg[KP], vreg[KP];
     const int nb = (k_wg + KEYS - 1) / KEYS;
     auto prefetch = [&](int blk) {
 #pragma unroll
-      for (int e = 0; e < KP; e++) { const int q = tid + e * NT; kreg[e] = piece_of(kg, blk * KEYS + q / PPR, q % PPR); }
-#pragma unroll
-      for (int e = 0; e < VP; e++) {
+      for (int e = 0; e < KP; e++) {
         const int q = tid + e * NT;
-        const int pair = q % (KEYS / 2), piece = q / (KEYS / 2);
-        vreg[e][0] = piece_of(vg, blk * KEYS + 2 * pair, piece);
-        vreg[e][1] = piece_of(vg, blk * KEYS + 2 * pair + 1, piece);
+        kreg[e] = piece_of(kg, blk * KEYS + q / PPR, q % PPR);
+        vreg[e] = piece_of(vg, blk * KEYS + q / PPR, q % PPR);
       }
     };
     auto stage = [&](int b) {
-      unsigned char *k_lds = lds + b * L::buf, *vt_lds = k_lds + KEYS * L::kstr;
+      unsigned char *k_lds = lds + b * L::buf, *v_lds = k_lds + KEYS * L::kstr;
 #pragma unroll
       for (int e = 0; e < KP; e++) {
         const int q = tid + e * NT;
         *(u32x4_t *)(k_lds + (q / PPR) * L::kstr + (q % PPR) * 16) = kreg[e];
-      }
-#pragma unroll
-      for (int e = 0; e < VP; e++) {                          // V^T[dim][key], two keys per 32-bit store
-        const int q = tid + e * NT;
-        const int pair = q % (KEYS / 2), piece = q / (KEYS / 2);
-#pragma unroll
-        for (int d2 = 0; d2 < 8; d2++) {
-          const uint32_t x0 = vreg[e][0][d2 >> 1], x1 = vreg[e][1][d2 >> 1];
-          *(uint32_t *)(vt_lds + (piece * 8 + d2) * L::vstr + pair * 4) = (d2 & 1) ? ((x0 >> 16) | (x1 & 0xFFFF0000u)) : ((x0 & 0xFFFFu) | (x1 << 16));
-        }
+        *(u32x4_t *)(v_lds + value_piece<HD>(q / PPR, q % PPR)) = vreg[e];
       }
     };
+    const int vat = value_lane<HD>(lane);
     prefetch(0);
     stage(0);
     __syncthreads();
     if (nb > 1) prefetch(1);
     int part_lo = 0;                                          // first key of the part under way
     for (int blk = 0; blk < nb; blk++) {
-      const unsigned char *k_lds = lds + (blk & 1) * L::buf, *vt_lds = k_lds + KEYS * L::kstr;
+      const unsigned char *k_lds = lds + (blk & 1) * L::buf, *v_lds = k_lds + KEYS * L::kstr;
       if (blk + 1 < nb) {
         stage((blk + 1) & 1);
         if (blk + 2 < nb) prefetch(blk + 2);
@@ -849,9 +856,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
             split8(x, phi, plo);
 #pragma unroll
             for (int db = 0; db < DB; db++) {
-              const unsigned char *vp = vt_lds + (db * 32 + c) * L::vstr + (32 * kt + 16 * u + 4 * g) * 2;
-              const u32x2_t v0 = *(const u32x2_t *)vp, v1 = *(const u32x2_t *)(vp + 16);
-              const u32x4_t vf = {v0.x, v0.y, v1.x, v1.y};
+              const u32x4_t vf = value_fragment<HD>(v_lds, vat, db, 32 * kt + 16 * u);
               o[db] = mfma_bf16(vf, phi, o[db]);
               o[db] = mfma_bf16(vf, plo, o[db]);
             }
