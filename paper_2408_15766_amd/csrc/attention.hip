@@ -23,7 +23,7 @@
 //    for every row of a tree (depth <= kMaxDepth), is the same key set for spec and plain decoding,
 //    and is shared by all rows, so it runs as dense 32-key blocks on the MFMA units: S^T = K Q^T
 //    and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16, K/V blocks staged once in LDS for all rows
-//    (V transposed on the way in), queries and probabilities split into bf16 hi + lo parts so
+//    (V transposed on the way out), queries and probabilities split into bf16 hi + lo parts so
 //    that they keep fp32-class accuracy.  The remaining positions [A(p), p] (16..47 keys: the end
 //    of the cache plus the row's own path) take the vector path.  A(p) depends on the position
 //    only, so a row is computed by the same instructions over the same key groups whether it is
@@ -32,7 +32,7 @@
 //
 // Parts (fixed absolute boundaries: attn_part_begin; larger parts for far keys, where a long context would otherwise
 // mean many partials to merge and many short workgroups) are merged per row in ascending order, the tail
-// last, by attn_combine_kernel.  In the hybrid path the bulk and the tail are independent and run in ONE
+// last, by attn_combine_kernel (RowMerge).  In the hybrid path the bulk and the tail are independent and run in ONE
 // launch (different workgroups), so the chain per layer is two dependent kernels.
 #include <algorithm>
 #include <type_traits>
@@ -79,6 +79,27 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// Scores are kept in units of log2: the launch's scale holds 1/sqrt(hd) * log2(e), and every weight is a power of two taken by the hardware.
+__device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// The merge of a row's parts, in ascending order and the tail last: (reference m, sum l, outputs o) of part after part go into the row's.  The row's
+// reference moves only when a part's exceeds it by more than kRefSlack: until then weights are up to 2^kRefSlack, harmless in fp32, and the
+// sums are left alone.  The final division cancels the choice.  step() returns what the row's sums are to be multiplied by before the part
+// is added with weight w.
+constexpr float kRefSlack = 8.f;
+struct RowMerge {
+  float m = -INFINITY, l = 0.f;
+  __device__ __forceinline__ float step(float m_part, float l_part, float &w) {
+    const bool move = m_part > m + kRefSlack;                  // also the first part
+    const float m_new = move ? m_part : m;
+    const float turn = move ? exp2_(m - m_new) : 1.f;
+    m = m_new;
+    w = exp2_(m_part - (m_new == -INFINITY ? 0.f : m_new));     // (a part whose scores are all -inf weighs nothing)
+    l = fmaf(l_part, w, l * turn);
+    return turn;
+  }
+};
 
 // One wavefront: row i, kv head hk, part `part` (full mode) or the tail range (tail mode).  `qs` and `vs`
 // are this wavefront's own LDS areas ([G][HD] floats and 64 staged value rows); no workgroup barrier is
@@ -148,8 +169,8 @@ __device__ __forceinline__ void attn_part_body(const AttnArgs &a, int i, int hk,
     for (int gh = 0; gh < G; gh++) {
       const float sc = valid ? s[gh] * a.scale : -INFINITY;
       const float m_new = fmaxf(m_run[gh], wave_max(sc));
-      const float corr = __expf(m_run[gh] - m_new);      // first block: exp(-inf) = 0
-      pk[gh] = valid ? __expf(sc - m_new) : 0.f;
+      const float corr = exp2_(m_run[gh] - m_new);       // first block: 2^-inf = 0
+      pk[gh] = valid ? exp2_(sc - m_new) : 0.f;
       l_run[gh] = l_run[gh] * corr + wave_sum(pk[gh]);
 #pragma unroll
       for (int dd = 0; dd < DPL; dd++) o[gh][dd] *= corr;
@@ -245,7 +266,7 @@ __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk,
     t += __shfl_xor(t, 2, 64);
     const float sc = valid ? t * a.scale : -INFINITY;
     m_run[gh] = wave_max(sc);                        // at least key p itself is valid
-    pk[gh] = valid ? __expf(sc - m_run[gh]) : 0.f;
+    pk[gh] = valid ? exp2_(sc - m_run[gh]) : 0.f;
     l_run[gh] = wave_sum(qt == 0 ? pk[gh] : 0.f);
   }
   wave_lds_sync();                                   // value rows staged
@@ -290,16 +311,14 @@ __global__ __launch_bounds__(64) void attn_part_kernel(AttnArgs a) {
   attn_part_body<T, HD, G>(a, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x, qs, vs, true);
 }
 
-// grid (rows, hq); block HD threads.  Merges the row's parts in ascending order; in hybrid mode these are
-// the bulk parts followed by the tail (kept in the last slot).  The (max, sum) pairs of up to kCombineChunk
-// parts are fetched by one thread each and turned into weights in LDS, so that the per-dim pass issues
-// independent, coalesced loads; the sums themselves run in ascending part order.
+// grid (rows, hq); block HD threads.  Merges the row's parts in ascending order (RowMerge); in hybrid mode these are
+// the bulk parts followed by the tail (kept in the last slot).  The (reference, sum) pairs of up to kCombineChunk
+// parts are fetched by one thread each, so that the per-dim pass issues independent, coalesced loads.
 constexpr int kCombineChunk = 64;
 constexpr int kCombineFew = 8;         // up to this many parts a thread keeps everything in registers
 template <typename T, int HD>
 __global__ __launch_bounds__(HD) void attn_combine_kernel(AttnArgs a) {
   __shared__ float pm[kCombineChunk], pl[kCombineChunk];
-  __shared__ float red[2];
   const int i = blockIdx.x, h = blockIdx.y, d = threadIdx.x;
   const int p = (a.base_ptr ? *a.base_ptr : a.base) + a.depth[i];
   const int n_front = attn_parts_covering(a.tail_only ? bulk_end(p) : p + 1);
@@ -315,51 +334,40 @@ __global__ __launch_bounds__(HD) void attn_combine_kernel(AttnArgs a) {
       const float *sp = src + slot(t < n_parts ? t : 0);
       pm_[t] = sp[0]; pl_[t] = sp[1]; pv_[t] = sp[2 + d];
     }
-    float m = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < kCombineFew; t++) if (t < n_parts) m = fmaxf(m, pm_[t]);
-    float l = 0.f, o = 0.f;
+    RowMerge row;
+    float o = 0.f;
 #pragma unroll
     for (int t = 0; t < kCombineFew; t++)
       if (t < n_parts) {
-        const float w = __expf(pm_[t] - m);
-        l += pl_[t] * w; o += pv_[t] * w;
+        float w;
+        const float turn = row.step(pm_[t], pl_[t], w);
+        o = fmaf(pv_[t], w, o * turn);
       }
-    ((T *)a.out)[((size_t)i * a.hq + h) * HD + d] = from_f32<T>(o / l);
+    ((T *)a.out)[((size_t)i * a.hq + h) * HD + d] = from_f32<T>(o / row.l);
     return;
   }
-  // pass 1: the row's maximum
-  float m = -INFINITY;
-  for (int t = d; t < n_parts; t += HD) m = fmaxf(m, src[slot(t)]);
-  m = wave_max(m);
-  if (HD > 64) {
-    if ((d & 63) == 0) red[d >> 6] = m;
-    __syncthreads();
-    m = fmaxf(red[0], red[1]);
-  }
-  // pass 2: chunks of parts; weights once per part, then every thread adds its dim in ascending order
-  float l = 0.f, o = 0.f;
+  // chunks of parts: the (reference, sum) pairs through the LDS, the outputs of four parts in flight; every thread steps through all of them
+  RowMerge row;
+  float o = 0.f;
   for (int t0 = 0; t0 < n_parts; t0 += kCombineChunk) {
     const int nt = min(kCombineChunk, n_parts - t0);
+    if (t0 > 0) __syncthreads();
+    if (d < nt) { const float *sp = src + slot(t0 + d); pm[d] = sp[0]; pl[d] = sp[1]; }
     __syncthreads();
-    if (d < nt) {
-      const float *sp = src + slot(t0 + d);
-      const float w = __expf(sp[0] - m);
-      pm[d] = w; pl[d] = sp[1] * w;
-    }
-    __syncthreads();
+    auto add = [&](int t, float v) __attribute__((always_inline)) {
+      float w;
+      const float turn = row.step(pm[t], pl[t], w);
+      o = fmaf(v, w, o * turn);
+    };
     int t = 0;
     for (; t + 4 <= nt; t += 4) {
       const float v0 = src[slot(t0 + t) + 2 + d], v1 = src[slot(t0 + t + 1) + 2 + d];
       const float v2 = src[slot(t0 + t + 2) + 2 + d], v3 = src[slot(t0 + t + 3) + 2 + d];
-      l += pl[t]; o += v0 * pm[t];
-      l += pl[t + 1]; o += v1 * pm[t + 1];
-      l += pl[t + 2]; o += v2 * pm[t + 2];
-      l += pl[t + 3]; o += v3 * pm[t + 3];
+      add(t, v0); add(t + 1, v1); add(t + 2, v2); add(t + 3, v3);
     }
-    for (; t < nt; t++) { l += pl[t]; o += src[slot(t0 + t) + 2 + d] * pm[t]; }
+    for (; t < nt; t++) add(t, src[slot(t0 + t) + 2 + d]);
   }
-  ((T *)a.out)[((size_t)i * a.hq + h) * HD + d] = from_f32<T>(o / l);
+  ((T *)a.out)[((size_t)i * a.hq + h) * HD + d] = from_f32<T>(o / row.l);
 }
 
 // ---- matrix-core path for the bulk region (bf16 storage) -----------------------------------
@@ -406,6 +414,42 @@ __device__ __forceinline__ void store4_any(float *p, float a, float b, float c, 
   typedef __attribute__((ext_vector_type(4), aligned(4))) float f4_t;
   *(f4_t *)p = f4_t{a, b, c, d};
 }
+
+// Maximum and sum over the lanes l and l ^ 32, in both, without the LDS round trip of a shuffle
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// The running softmax of a part over a block of 32 keys: s[v] = q . k (masked keys -inf), a lane and lane ^ 32 share a query.  The reference m moves
+// only when the block's maximum exceeds it by more than kRefSlack, as in RowMerge: the output registers (times `turn`) are seldom touched.
+struct PartSoftmax {
+  float m = -INFINITY, l = 0.f;
+  // turn: what the part's outputs are to be multiplied by (1 unless some query of the wavefront moves); p[v]: the keys' weights
+  __device__ __forceinline__ bool block(const f32x16_t &s, float scale, float &turn, float (&p)[16]) {
+    float mb = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; v++) mb = fmaxf(mb, s[v]);
+    mb = max_halves(mb) * scale;                              // (the scale is positive and rounding keeps order)
+    const bool move = mb > m + kRefSlack;                      // also the first key
+    const bool any = __any(move);
+    turn = 1.f;
+    if (any) {
+      const float m_new = move ? mb : m;
+      turn = move ? exp2_(m - m_new) : 1.f;
+      m = m_new;
+    }
+    const float m_use = m == -INFINITY ? 0.f : m;              // nothing seen yet: every term is 0
+    float ls = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; v++) { p[v] = exp2_(fmaf(s[v], scale, -m_use)); ls += p[v]; }
+    l = fmaf(l, turn, sum_halves(ls));
+    return any;
+  }
+};
 
 // One launch covers both regions of the hybrid path.  Workgroups [0, n_bulk) (n_bulk = bulk_parts * kv heads
 // * q_groups, part fastest) run the matrix-core bulk: NW waves, wave w owns 32 "query rows" (row i, head gh
@@ -491,8 +535,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   for (int db = 0; db < DB; db++)
 #pragma unroll
     for (int v = 0; v < 16; v++) o[db][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  PartSoftmax run_;
   const int vat = value_lane<HD>(lane);
+  int k_low = k_end;                                         // the least over the wavefront's rows
+#pragma unroll
+  for (int x = 1; x < 32; x <<= 1) k_low = min(k_low, __shfl_xor(k_low, x, 64));
+  k_low = __builtin_amdgcn_readfirstlane(k_low);
 
   auto stage = [&](auto set_tag, int buf) {
     constexpr int SET = decltype(set_tag)::value;
@@ -550,25 +598,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         // s[v] = q . k for key 8*(v/4) + 4*g + v%4 of the block and query row c
         // keys at or past k_end are masked: they add exact zeros, so a row's result does not depend on them
         const int key0 = b * 32 + 4 * g;
-        float mb = -INFINITY;
+        if (b * 32 + 32 > k_low) {                            // some row of the wavefront ends inside the block
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-          s[v] = key0 + 8 * (v >> 2) + (v & 3) < k_end ? s[v] * a.scale : -INFINITY;
-          mb = fmaxf(mb, s[v]);
+          for (int v = 0; v < 16; v++)
+            if (key0 + 8 * (v >> 2) + (v & 3) >= k_end) s[v] = -INFINITY;
         }
-        mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
-        const float m_new = fmaxf(m_run, mb);
-        const float corr = m_new == -INFINITY ? 1.f : __expf(m_run - m_new);
-        float ls = 0.f;
+        float turn;
+        if (run_.block(s, a.scale, turn, pv)) {
 #pragma unroll
-        for (int v = 0; v < 16; v++) { pv[v] = s[v] == -INFINITY ? 0.f : __expf(s[v] - m_new); ls += pv[v]; }
-        ls += __shfl_xor(ls, 32, 64);
-        l_run = l_run * corr + ls;
-        m_run = m_new;
+          for (int db = 0; db < DB; db++)
 #pragma unroll
-        for (int db = 0; db < DB; db++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) o[db][v] *= corr;
+            for (int v = 0; v < 16; v++) o[db][v] *= turn;
+        }
       }
       if constexpr (j + 1 < NB) {
         constexpr int NEXT = (j + 1) % R;
@@ -600,7 +641,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   else run(std::integral_constant<int, kAttnFarPart / 32>{});
   if (!valid_q) return;
   float *dst = a.part + (((size_t)i * a.hq + hk * G + gh) * a.max_parts + part) * (HD + 2);
-  if (g == 0) { dst[0] = m_run; dst[1] = l_run; }
+  if (g == 0) { dst[0] = run_.m; dst[1] = run_.l; }
 #pragma unroll
   for (int db = 0; db < DB; db++)
 #pragma unroll
@@ -619,37 +660,29 @@ static hipError_t launch_hybrid(AttnArgs a, int q_groups, hipStream_t st) {
 // The same arithmetic as the hybrid path and its merge, bit for bit, without partial outputs of the bulk in memory: with hundreds of
 // rows a row's keys need no split over workgroups (512 rows at 4096 keys, 32 heads: 170 MB of partials per layer).  The tails run
 // first (attn_tail_kernel: one wavefront per row and kv head, fp32) and leave their partial; then one workgroup of WAVES
-// wavefronts takes WAVES * 32 consecutive rows of one query head and walks their bulk keys twice.  The merge weights a part by
-// exp(its maximum - the row's maximum), so the row's maximum has to be known before the first part is folded in: pass 1 forms
-// the scores for their maximum only (two products, K only), pass 2 runs the online softmax of every part as the hybrid
-// path does (32 keys at a time, from a fresh maximum per part) and folds a finished part into the row's sums.
+// wavefronts takes WAVES * 32 consecutive rows of one query head and walks their bulk keys: the running softmax of every part as the hybrid
+// path does it (32 keys at a time, from nothing per part), and each finished part goes into the row's sums as the merge does it (RowMerge
+// needs no maximum ahead of time, so that one walk is enough; a merge weighted by the row's maximum took a walk over all keys for that alone).
 // Two sets of output registers (part and row) leave no room for both query terms at head dim 128: the low one is read from the LDS.
-// K and V^T blocks are double-buffered there, the loads of a block run two blocks ahead.  Rows may stand at any positions
+// K and V blocks are double-buffered there, the loads of a block run two blocks ahead.  Rows may stand at any positions
 // (depth); a block past a wavefront's last bulk key is skipped (it would add exact zeros).
-// Bound: from one full chip of workgroups on the matrix cores (pass 1 1.7, pass 2 1.0 PFLOP/s), below that the serial chain of a block.
-// Measured (MI355X, us per call, the hybrid path before): 512 rows, 32 heads 99 -> 81 (tails 19, the walk 51); 1024 rows, 64 heads on 8 kv
-// heads 335 -> 157; 2048 rows, 32 on 8 415 -> 200, at 2048 keys before them 696 -> 375; 4096 rows 1309 -> 513.
+// Bound: from one full chip of workgroups on the matrix cores, below that the serial chain of a block.
+// Measured (MI355X, us per call with the tails; in two walks, references moving at every new maximum, before): 512 rows, 32 heads 58 -> 48; 1024 rows,
+// 64 heads on 8 kv heads 134 -> 110; 1333 rows, 32 on 8 115 -> 87; 2048 rows 177 -> 130, at 2048 keys before them 355 -> 251.
 template <int HD, int WAVES> struct ChainLds {
-  static constexpr int kScan = 64;                    // keys per staged block in pass 1 ...
-  static constexpr int kKeys = HD == 128 ? 32 : 64;   // ... and in pass 2: what the registers beside queries and outputs leave
+  static constexpr int kKeys = HD == 128 ? 32 : 64;   // keys per staged block: what the registers beside queries and outputs leave
   static constexpr int kstr = HD * 2 + 16;            // bytes per staged key row (+16: conflict-free b128 reads)
-  static constexpr int scan = kScan * kstr, walk = kKeys * kstr + kKeys * HD * 2;
-  static constexpr int buf = scan > walk ? scan : walk;
+  static constexpr int buf = kKeys * kstr + kKeys * HD * 2;
   static constexpr bool kQueryLds = HD == 128;
   static constexpr int total = 2 * buf + (kQueryLds ? WAVES * (HD / 16) * 1024 : 0);
 };
-// a * b rounded to fp32, whatever it is added to afterwards
-__device__ __forceinline__ float mul_rounded(float a, float b) {
-#pragma clang fp contract(off)
-  return a * b;
-}
 template <int HD, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_chain_kernel(AttnArgs a) {
   using L = ChainLds<HD, WAVES>;
-  constexpr int NT = WAVES * 64, SCAN = L::kScan, KEYS = L::kKeys, KT = KEYS / 32;
+  constexpr int NT = WAVES * 64, KEYS = L::kKeys, KT = KEYS / 32;
   constexpr int DB = HD / 32, KK = HD / 16, PPR = HD * 2 / 16;
-  constexpr int SP = SCAN * PPR / NT, KP = KEYS * PPR / NT;
-  static_assert(SCAN * PPR % NT == 0 && KEYS * PPR % NT == 0, "staging split");
+  constexpr int KP = KEYS * PPR / NT;
+  static_assert(KEYS * PPR % NT == 0, "staging split");
   static_assert(kAttnPart % KEYS == 0 && kAttnNear % KEYS == 0 && kAttnFarPart % KEYS == 0, "a part ends with a staged block");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   __shared__ int wave_hi[WAVES];
@@ -701,80 +734,23 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     for (int kk = 0; kk < KK; kk++) *(u32x4_t *)(q_lds + kk * 1024) = qlo[kk];
   }
   const float *tail = a.part + (((size_t)(valid ? i : a.rows - 1) * a.hq + h) * a.max_parts + a.max_parts - 1) * (HD + 2);
-  const float m_tail = tail[0];
-
-  // pass 1: the row's largest score
-  float smax = -INFINITY;
-  if (k_wg > 0) {
-    u32x4_t sreg[SP];
-    const int nb = (k_wg + SCAN - 1) / SCAN;
-    auto prefetch = [&](int blk) {
-#pragma unroll
-      for (int e = 0; e < SP; e++) { const int q = tid + e * NT; sreg[e] = piece_of(kg, blk * SCAN + q / PPR, q % PPR); }
-    };
-    auto stage = [&](int b) {
-#pragma unroll
-      for (int e = 0; e < SP; e++) { const int q = tid + e * NT; *(u32x4_t *)(lds + b * L::buf + (q / PPR) * L::kstr + (q % PPR) * 16) = sreg[e]; }
-    };
-    prefetch(0);
-    stage(0);
-    __syncthreads();
-    if (nb > 1) prefetch(1);
-    for (int blk = 0; blk < nb; blk++) {
-      const unsigned char *k_lds = lds + (blk & 1) * L::buf;
-      if (blk + 1 < nb) {                                     // the other buffer was left by everyone at the last barrier
-        stage((blk + 1) & 1);
-        if (blk + 2 < nb) prefetch(blk + 2);
-      }
-      if (blk * SCAN < hi) {                                  // some row of the wavefront has keys here
-        f32x16_t s[2];
-#pragma unroll
-        for (int kt = 0; kt < 2; kt++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) s[kt][v] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < KK; kk++)
-#pragma unroll
-          for (int kt = 0; kt < 2; kt++) {
-            const u32x4_t kf = *(const u32x4_t *)(k_lds + (kt * 32 + c) * L::kstr + kk * 32 + g * 16);
-            s[kt] = mfma_bf16(kf, qhi[kk], s[kt]);
-            s[kt] = mfma_bf16(kf, qlo[kk], s[kt]);
-          }
-        // s[kt][v] = q . k for key blk*64 + kt*32 + 8*(v/4) + 4*g + v%4
-        if (blk * SCAN + SCAN > lo) {                         // some row ends inside the block
-          const int key0 = blk * SCAN + 4 * g;
-#pragma unroll
-          for (int kt = 0; kt < 2; kt++)
-#pragma unroll
-            for (int v = 0; v < 16; v++)
-              if (key0 + kt * 32 + 8 * (v >> 2) + (v & 3) >= k_end) s[kt][v] = -INFINITY;
-        }
-#pragma unroll
-        for (int kt = 0; kt < 2; kt++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) smax = fmaxf(smax, s[kt][v]);
-      }
-      __syncthreads();                                        // block blk+1 staged; everyone is done with block blk
-    }
-    smax = fmaxf(smax, __shfl_xor(smax, 32, 64));
-  }
-  const float m_row = fmaxf(smax * a.scale, m_tail);          // (the scale is positive and rounding keeps order)
-  const int n_front = attn_parts_covering(k_end);
-  const bool few = n_front + 1 <= kCombineFew;                // the merge rounds a part's weighted sum only when there are many
 
   f32x16_t o[DB], row[DB];                                    // output of the part under way, and of the row
 #pragma unroll
   for (int db = 0; db < DB; db++)
 #pragma unroll
     for (int v = 0; v < 16; v++) o[db][v] = row[db][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f, l_row = 0.f;
-  auto weigh = [&](float l, float m, float &w) {
-    w = __expf(m - m_row);
-    const float lw = mul_rounded(l, w);
-    l_row = few ? fmaf(l, w, l_row) : l_row + lw;
+  PartSoftmax part;
+  RowMerge merge;
+  auto turn_row = [&](float turn) __attribute__((always_inline)) {
+    if (__any(turn != 1.f)) {
+#pragma unroll
+      for (int db = 0; db < DB; db++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) row[db][v] *= turn;
+    }
   };
 
-  // pass 2
   if (k_wg > 0) {
     u32x4_t kreg[KP], vreg[KP];
     const int nb = (k_wg + KEYS - 1) / KEYS;
@@ -822,8 +798,6 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
             s = mfma_bf16(kf, qhi[kk], s);
             s = mfma_bf16(kf, ql, s);
           }
-#pragma unroll
-          for (int v = 0; v < 16; v++) s[v] = mul_rounded(s[v], a.scale);
           const int b0 = blk * KEYS + kt * 32;
           if (b0 + 32 > lo) {                                 // some row ends inside the block
             const int key0 = b0 + 4 * g;
@@ -831,27 +805,18 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
             for (int v = 0; v < 16; v++)
               if (key0 + 8 * (v >> 2) + (v & 3) >= k_end) s[v] = -INFINITY;
           }
-          float mb = -INFINITY;
-#pragma unroll
-          for (int v = 0; v < 16; v++) mb = fmaxf(mb, s[v]);
-          mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
-          const float m_new = fmaxf(m_run, mb);
-          float corr = 1.f;
-          if (__any(m_new != m_run)) {                        // (otherwise the factor is exactly 1)
-            if (m_new != -INFINITY) corr = __expf(m_run - m_new);
+          float turn, pv[16];
+          if (part.block(s, a.scale, turn, pv)) {
 #pragma unroll
             for (int db = 0; db < DB; db++)
 #pragma unroll
-              for (int v = 0; v < 16; v++) o[db][v] *= corr;
-            m_run = m_new;
+              for (int v = 0; v < 16; v++) o[db][v] *= turn;
           }
-          const float m_use = m_run == -INFINITY ? 0.f : m_run;   // nothing seen yet: every term is 0
-          float ls = 0.f;
 #pragma unroll
           for (int u = 0; u < 2; u++) {                       // 16 keys: the lane's own values v = 8u .. 8u+7
             float x[8];
 #pragma unroll
-            for (int e = 0; e < 8; e++) { x[e] = __expf(s[8 * u + e] - m_use); ls += x[e]; }
+            for (int e = 0; e < 8; e++) x[e] = pv[8 * u + e];
             u32x4_t phi, plo;
             split8(x, phi, plo);
 #pragma unroll
@@ -861,14 +826,12 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
               o[db] = mfma_bf16(vf, plo, o[db]);
             }
           }
-          ls += __shfl_xor(ls, 32, 64);
-          l_run = fmaf(l_run, corr, ls);
         }
         const int done = (blk + 1) * KEYS;
         if (done >= hi || (done <= kAttnNear ? done % kAttnPart : (done - kAttnNear) % kAttnFarPart) == 0) {
           if (part_lo < k_end) {                              // this row has keys in the part
             float w;
-            weigh(l_run, m_run, w);
+            turn_row(merge.step(part.m, part.l, w));
 #pragma unroll
             for (int db = 0; db < DB; db++)
 #pragma unroll
@@ -878,16 +841,16 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
           for (int db = 0; db < DB; db++)
 #pragma unroll
             for (int v = 0; v < 16; v++) o[db][v] = 0.f;
-          m_run = -INFINITY; l_run = 0.f;
+          part = PartSoftmax{};
           part_lo = done;
         }
       }
       __syncthreads();                                        // block blk+1 staged; everyone is done with block blk
     }
   }
-  if (!valid) return;
   float w;
-  weigh(tail[1], m_tail, w);
+  turn_row(merge.step(tail[0], tail[1], w));
+  if (!valid) return;
   bf16_t *orow = (bf16_t *)a.out + ((size_t)i * a.hq + h) * HD;
 #pragma unroll
   for (int db = 0; db < DB; db++)
@@ -898,7 +861,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
       const float t[4] = {t0.x, t0.y, t1.x, t1.y};
       float y[4];
 #pragma unroll
-      for (int e = 0; e < 4; e++) y[e] = fmaf(t[e], w, row[db][4 * q4 + e]) / l_row;
+      for (int e = 0; e < 4; e++) y[e] = fmaf(t[e], w, row[db][4 * q4 + e]) / merge.l;
       *(u32x2_t *)(orow + d0) = u32x2_t{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
     }
 }
@@ -938,13 +901,13 @@ static hipError_t launch_chain(AttnArgs a, hipStream_t st) {
 
 // Which chains take attn_chain_kernel.  A workgroup of it walks all keys of its rows one block after the other, so its time grows
 // with the keys alone until the chip is full; the hybrid path's grows with rows * heads * keys, and with few keys the
-// fixed costs of its three launches and its partials count.  Crossing points measured in rows * heads, hybrid path faster below
-// (32 heads of 128 on 32 and on 8 kv heads, 40 on 40, 64 on 8, 16 of 64): about 300 keys 8 .. 12 thousand, 900 keys 12 .. 18,
-// 2600 keys 18 .. 22, 8700 keys 22 .. 27.  us per call at the ends, hybrid / chain: 512 rows of 32 heads alone 102 / 81, 320 rows 76 / 64,
-// 256 rows 58 / 60; at 2048 keys before them 384 rows 138 / 184, 512 174 / 193, 640 222 / 202, 1024 388 / 231; at 8192 keys 512 rows
-// 389 / 530, 768 587 / 548.  Tiles are 128 rows: below 192 rows (1.5 tiles) the hybrid path is never slower.
+// fixed costs of its three launches and its partials count.  Crossing points measured in thousands of rows * heads, hybrid path faster below
+// (32 heads of 128 on 32 and on 8 kv heads, 64 on 8, 40 on 40, 16 of 64): about 250 keys 5.5, 8, 8, 6, 4.5; 1050 keys 9, 10, 13, 10, 7.5; 2500 keys
+// 13, 16, 17, 12, 10; 8700 keys 16, 18, 17.5, 16, 16.  us per call beside them, hybrid / chain: 192 rows of 32 heads alone 28.5 / 26.5, 320 rows 50 / 35, 512
+// 78 / 48; at 768 keys before them 256 rows 52 / 60, 320 71 / 62; at 2048 384 rows 109 / 114, 512 148 / 121; at 8192 384 rows 261 / 330, 512 352 / 337,
+// 768 533 / 352.  Tiles are 128 rows: below 192 rows (1.5 tiles) the hybrid path is never slower.
 static bool chain_pays(int rows, int hq, int keys) {
-  return rows >= 192 && (long long)rows * hq >= 5600 + 21600ll * keys / (keys + 1500);
+  return rows >= 192 && (long long)rows * hq >= 4200 + 14400ll * keys / (keys + 1500);
 }
 
 template <typename T, int HD, int G>
@@ -1000,7 +963,9 @@ static hipError_t launch_th(const AttnArgs &a, int max_pos, hipStream_t st) {
 }
 
 // max_pos: largest key position any row attends to (host-known bound: base + max depth).
-hipError_t launch_attention(int dtype, const AttnArgs &a, int max_pos, hipStream_t st) {
+hipError_t launch_attention(int dtype, const AttnArgs &args, int max_pos, hipStream_t st) {
+  AttnArgs a = args;
+  a.scale = (float)((double)a.scale * 1.4426950408889634);    // scores in units of log2
   if (a.rows < 1 || a.hkv < 1 || a.hq % a.hkv != 0) return hipErrorInvalidValue;
   if (a.hd == 128) return dtype == 1 ? launch_th<bf16_t, 128>(a, max_pos, st) : launch_th<float, 128>(a, max_pos, st);
   if (a.hd == 64) return dtype == 1 ? launch_th<bf16_t, 64>(a, max_pos, st) : launch_th<float, 64>(a, max_pos, st);

@@ -468,3 +468,30 @@ def test_attention_row_is_independent_of_the_other_rows(env, rows, hq, hkv, hd, 
     assert torch.equal(whole, few)
     for i in (0, 15, 16, rows // 2, rows - 1):
         assert torch.equal(run(i, i + 1).view(torch.int16)[0], whole[i])
+
+
+@pytest.mark.parametrize("shape", ["rising", "falling", "one far peak", "steps"])
+@pytest.mark.parametrize("rows,hq,hkv,hd,base", [(3, 4, 1, 128, 1500), (260, 32, 8, 128, 300), (260, 32, 32, 64, 300)])
+def test_attention_where_references_move(env, shape, rows, hq, hkv, hd, base):
+    """Scores that climb, fall or jump by far more than 2^8 along the keys, so that the reference of a part moves again and again, or never from
+    its first block, and that of the row between parts: against fp64, and a row of many has the bits it has alone."""
+    torch, P = env
+    n = base + rows
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed("move", shape, rows, hd) & 0xFFFF)
+    pos = torch.arange(n, device="cuda", dtype=torch.float64) / n
+    level = {"rising": 60 * pos, "falling": -60 * pos, "one far peak": 50.0 * (torch.arange(n, device="cuda") == 33), "steps": 9.0 * (torch.arange(n, device="cuda") // 48 % 5)}[shape]
+    direction = torch.randn(hkv * hd, device="cuda", generator=g).sign()
+    kc = (torch.randn(n, hkv * hd, device="cuda", generator=g) * 0.3 + (level / hd ** 0.5)[:, None].float() * direction).to(torch.bfloat16)
+    vc = torch.randn(n, hkv * hd, device="cuda", generator=g).to(torch.bfloat16)
+    q = direction.view(hkv, 1, hd).expand(hkv, hq // hkv, hd).reshape(1, hq * hd).repeat(rows, 1) * (1 + 0.1 * torch.randn(rows, 1, device="cuda", generator=g))
+    dep = torch.arange(rows, dtype=torch.int32, device="cuda")
+    run = lambda a, b: P.spec_k_attention(q[a:b].contiguous(), kc, vc, base, dep[a:b].contiguous(), None, hq, hkv, hd)
+    got = run(0, rows)
+    for i in (0, rows // 2, rows - 1):
+        assert torch.equal(run(i, i + 1)[0], got[i])
+    k3, v3 = kc.double().view(n, hkv, hd).repeat_interleave(hq // hkv, 1), vc.double().view(n, hkv, hd).repeat_interleave(hq // hkv, 1)
+    sc = torch.bmm(q.double().view(rows, hq, hd).transpose(0, 1).contiguous(), k3.permute(1, 2, 0).contiguous()) / hd ** 0.5
+    sc.masked_fill_(torch.arange(n, device="cuda")[None, None] > (base + dep)[None, :, None], -np.inf)
+    want = torch.bmm(torch.softmax(sc, -1), v3.transpose(0, 1).contiguous()).transpose(0, 1).contiguous().view(rows, hq, hd)
+    # queries and probabilities enter as hi + lo pairs, a score's relative error of 2^-16 is an absolute one of 60 * 2^-16 in the exponent
+    assert ((got.double().view_as(want) - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -9 * float(vc.double().abs().max())).all()
