@@ -192,7 +192,7 @@ __device__ __forceinline__ void attn_part_body(const AttnArgs &a, int i, int hk,
       for (int kk = 0; kk < 8; kk++)
 #pragma unroll
         for (int gh = 0; gh < G; gh++) {
-          const float w = __shfl(pk[gh], k0 + kk, 64);
+          const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pk[gh]), k0 + kk));
 #pragma unroll
           for (int dd = 0; dd < DPL; dd++) o[gh][dd] = fmaf(w, vv[kk][dd], o[gh][dd]);
         }
@@ -262,8 +262,8 @@ __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk,
 #pragma unroll
   for (int gh = 0; gh < G; gh++) {
     float t = s[gh];
-    t += __shfl_xor(t, 1, 64);                       // quad sum, fixed order
-    t += __shfl_xor(t, 2, 64);
+    t += dpp_f32<0xB1>(t);                           // quad sum, fixed order: quad_perm [1,0,3,2], [2,3,0,1]
+    t += dpp_f32<0x4E>(t);
     const float sc = valid ? t * a.scale : -INFINITY;
     m_run[gh] = wave_max(sc);                        // at least key p itself is valid
     pk[gh] = valid ? exp2_(sc - m_run[gh]) : 0.f;
@@ -288,7 +288,7 @@ __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk,
     for (int u = 0; u < 8; u++)
 #pragma unroll
       for (int gh = 0; gh < G; gh++) {
-        const float w = __shfl(pk[gh], (k0 + u) * 4, 64);
+        const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pk[gh]), (k0 + u) * 4));
 #pragma unroll
         for (int dd = 0; dd < DPL; dd++) o[gh][dd] = fmaf(w, vv[u][dd], o[gh][dd]);
       }

@@ -76,36 +76,44 @@ __device__ __forceinline__ void store_act(bf16_t *p, float r, float nx, bool ok,
   }
 }
 
-// Butterfly reductions over the 64 lanes of a wavefront; every lane gets the result.
-// The exchange pattern is fixed, so the result does not depend on the data.
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
-__device__ __forceinline__ int wave_min_i(int x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = min(x, __shfl_xor(x, o, 64));
-  return x;
-}
-__device__ __forceinline__ int wave_sum_i(int x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-
-// Order-independent reductions (max, min) without LDS traffic: four DPP exchanges inside each row of 16
-// lanes (xor 1, xor 2, mirror within 8, mirror within 16), then the four row results are read lane by lane.
-// Needs all 64 lanes active.  Every lane gets the result.
+// What the lane `lane ^ O` holds, for a butterfly that goes through O = 32, 16, 8, 4, 2, 1 in this order, on the vector unit alone (a
+// shuffle is a round trip through the LDS, about 100 cycles each: six of them were a third of a small row kernel's arithmetic).  O = 4 takes the
+// lane 4 before in the row of 16, which after the steps before holds the same as lane ^ 4.  Needs all 64 lanes active.
 template <int CTRL> __device__ __forceinline__ int dpp_i32(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true); }
 template <int CTRL> __device__ __forceinline__ float dpp_f32(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
 }
+template <int O> __device__ __forceinline__ int butterfly(int x) {
+  if constexpr (O >= 16) {                                    // the two halves (rows) swap: one result holds the lower one's, the other the upper one's
+    const bool upper = (threadIdx.x & O) != 0;
+    if constexpr (O == 32) { const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false); return upper ? r[0] : r[1]; }
+    else { const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false); return upper ? r[0] : r[1]; }
+  } else {
+    return dpp_i32<(O == 8 ? 0x128 : O == 4 ? 0x124 : O == 2 ? 0x4E : 0xB1)>(x);   // row_ror 8, row_ror 4, quad_perm [2,3,0,1], [1,0,3,2]
+  }
+}
+// Butterfly reductions over the 64 lanes of a wavefront; every lane gets the result.
+// The exchange pattern is fixed, so the result does not depend on the data.  (f is commutative: of a swap's two results either order will do.)
+template <typename F> __device__ __forceinline__ int wave_reduce(int x, F f) {
+  { const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false); x = f(r[0], r[1]); }
+  { const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false); x = f(r[0], r[1]); }
+  x = f(x, butterfly<8>(x));
+  x = f(x, butterfly<4>(x));
+  x = f(x, butterfly<2>(x));
+  return f(x, butterfly<1>(x));
+}
+__device__ __forceinline__ float wave_sum(float x) {
+  return __int_as_float(wave_reduce(__float_as_int(x), [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); }));
+}
+__device__ __forceinline__ float wave_max(float x) {
+  return __int_as_float(wave_reduce(__float_as_int(x), [](int a, int b) { return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b))); }));
+}
+__device__ __forceinline__ int wave_min_i(int x) { return wave_reduce(x, [](int a, int b) { return min(a, b); }); }
+__device__ __forceinline__ int wave_sum_i(int x) { return wave_reduce(x, [](int a, int b) { return a + b; }); }
+
+// Order-independent reductions (max, min) without LDS traffic: four DPP exchanges inside each row of 16
+// lanes (xor 1, xor 2, mirror within 8, mirror within 16), then the four row results are read lane by lane.
+// Needs all 64 lanes active.  Every lane gets the result.
 __device__ __forceinline__ float wave_max_dpp(float x) {
   x = fmaxf(x, dpp_f32<0xB1>(x));     // quad_perm [1,0,3,2]
   x = fmaxf(x, dpp_f32<0x4E>(x));     // quad_perm [2,3,0,1]
@@ -127,13 +135,13 @@ __device__ __forceinline__ int wave_min_dpp(int x) {
 // (value, index) pair ordered by larger value first, then lower index.
 struct ValIdx { float v; int i; };
 __device__ __forceinline__ bool better(float v, int i, float v2, int i2) { return v > v2 || (v == v2 && i < i2); }
+template <int O> __device__ __forceinline__ void best_step(ValIdx &a) {
+  const float ov = __int_as_float(butterfly<O>(__float_as_int(a.v)));
+  const int oi = butterfly<O>(a.i);
+  if (better(ov, oi, a.v, a.i)) { a.v = ov; a.i = oi; }
+}
 __device__ __forceinline__ ValIdx wave_best(ValIdx a) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    float ov = __shfl_xor(a.v, o, 64);
-    int oi = __shfl_xor(a.i, o, 64);
-    if (better(ov, oi, a.v, a.i)) { a.v = ov; a.i = oi; }
-  }
+  best_step<32>(a); best_step<16>(a); best_step<8>(a); best_step<4>(a); best_step<2>(a); best_step<1>(a);
   return a;
 }
 

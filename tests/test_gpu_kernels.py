@@ -390,6 +390,30 @@ def test_gemm_large_shapes_sampled_against_oracle(env, name, rows, k, n_split):
         assert np.abs(got[:, c] - want).max() < 2e-3
 
 
+@pytest.mark.parametrize("vocab,k", [(40, 16), (262144, 16), (262145, 16), (300000, 11)])
+def test_topk_logprob_merge_of_slices(env, vocab, k):
+    """One slice, 64 (a list per lane) and more (several): rows whose best entries sit in one slice, are spread one per slice, tie across
+    slices, and a row of three finite entries (the rest follow by index)."""
+    torch, P = env
+    rng = np.random.default_rng(vocab)
+    logits = rng.standard_normal((4, vocab)).astype(np.float32)
+    logits[0, vocab - 20:] += 10.0
+    logits[1, ::4096] += 12.0
+    logits[2] = np.round(logits[2])
+    logits[3] = -np.inf
+    logits[3, [vocab - 1, vocab // 2, 5]] = [1.0, 2.0, 1.0]
+    tok, lp = P.spec_k_topk_logprob(torch.from_numpy(logits).cuda(), k)
+    torch.cuda.synchronize()
+    tok, lp = tok.cpu().numpy(), lp.cpu().numpy()
+    for r in range(4):
+        want = np.lexsort((np.arange(vocab), -logits[r].astype(np.float64)))[:k]
+        assert list(tok[r]) == list(want)
+        x = logits[r].astype(np.float64)
+        want_lp = x - x.max() - np.log(np.exp(x - x.max()).sum())
+        fin = np.isfinite(want_lp[want])
+        assert np.abs(lp[r][fin] - want_lp[want][fin]).max() < 5e-6 and np.isneginf(lp[r][~fin]).all()
+
+
 @pytest.mark.parametrize("q_scale", [1.0, 6.0], ids=["flat", "peaked"])
 def test_attention_long_context_matches_oracle(env, q_scale):
     """Long-KV verify of the LLaMA3-8B configuration: 4100 cached keys (eight 128-key parts and thirteen 256-key parts
