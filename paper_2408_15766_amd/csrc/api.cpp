@@ -509,6 +509,23 @@ int sync(spec_ctx *c) {
   return SPEC_OK;
 }
 
+// Captures what `launch` enqueues into a graph, in place of *exec.  The stream may have work under way: capturing runs nothing, so a caller that has just
+// enqueued the same launches for this cycle hides the capture behind them.
+template <typename Launch>
+int capture(spec_ctx *c, hipGraphExec_t *exec, const char *what, Launch launch) {
+  if (*exec) { (void)hipGraphExecDestroy(*exec); *exec = nullptr; }
+  hipGraph_t graph = nullptr;
+  HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+  const int rc = launch();
+  hipError_t e = hipStreamEndCapture(c->stream, &graph);
+  if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
+  if (e != hipSuccess) return fail(c, SPEC_EHIP, "graph capture (%s): %s", what, hipGetErrorString(e));
+  e = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
+  (void)hipGraphDestroy(graph);
+  if (e != hipSuccess) { *exec = nullptr; return fail(c, SPEC_EHIP, "graph instantiate (%s): %s", what, hipGetErrorString(e)); }
+  return SPEC_OK;
+}
+
 // End of a drafting call: the device tree goes to the host arrays of the caller.
 int finish_draft(spec_ctx *c, spec_tree *out) {
   c->gemm_bucket = 0;
@@ -770,20 +787,17 @@ int spec_draft_tree(spec_ctx *c, spec_tree *out) {
   if (c->graphs && c->stream != nullptr && c->prof_level < 2) {
     const int need = c->n + D;                                  // largest key position of a draft row of this cycle
     if (c->expand_exec == nullptr || need > c->expand_exec_bound) {
-      if (c->expand_exec) { (void)hipGraphExecDestroy(c->expand_exec); c->expand_exec = nullptr; }
+      // no graph for this context yet: this cycle's launches go out one by one and the graph is captured while they run
+      rc = expand_all(nullptr, c->n, 0);
+      if (rc) return rc;
       const int bound = std::min(c->seq_draft - 1, (need / kGraphBucket + 1) * kGraphBucket - 1);
-      hipGraph_t graph = nullptr;
-      HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-      rc = expand_all(c->t_base, 0, bound);
-      hipError_t e = hipStreamEndCapture(c->stream, &graph);
-      if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
-      if (e != hipSuccess) return fail(c, SPEC_EHIP, "graph capture (draft): %s", hipGetErrorString(e));
-      e = hipGraphInstantiate(&c->expand_exec, graph, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(graph);
-      if (e != hipSuccess) { c->expand_exec = nullptr; return fail(c, SPEC_EHIP, "graph instantiate (draft): %s", hipGetErrorString(e)); }
+      c->expand_exec_bound = 0;
+      rc = capture(c, &c->expand_exec, "draft", [&] { return expand_all(c->t_base, 0, bound); });
+      if (rc) return rc;
       c->expand_exec_bound = bound;
+    } else {
+      HIPCHK(c, hipGraphLaunch(c->expand_exec, c->stream));
     }
-    HIPCHK(c, hipGraphLaunch(c->expand_exec, c->stream));
   } else {
     rc = expand_all(nullptr, c->n, 0);
     if (rc) return rc;
@@ -824,33 +838,27 @@ int spec_verify(spec_ctx *c, const spec_tree *tree) {
   HIPCHK(c, hipMemcpyAsync(c->t_n, &s.tree_n, offsetof(HostStage, acc), hipMemcpyHostToDevice, c->stream));
   RowTables rt{c->t_tok, c->t_pos, c->t_slot, c->t_dep, c->t_anc};
   int rc;
+  auto forward = [&](int base, int pos_bound, const int *base_ptr) -> int {
+    const int r = target_forward(c, N, base, rt, pos_bound, base_ptr);
+    return r ? r : lm_head(c, c->feats, N, c->logits);
+  };
   const bool use_graph = c->graphs && c->stream != nullptr && c->prof_level < 2 && N == g.tree_total;
-  if (use_graph) {
-    // Every launch argument of the forward is either fixed or read from device memory (the tree
-    // tables and the base), so the sequence is captured once and replayed each cycle.
-    const int need = c->n + kMaxDepth;                          // largest key position a row of this cycle can have
-    if (c->verify_exec == nullptr || c->verify_exec_rows != N || need > c->verify_exec_bound) {
-      if (c->verify_exec) { (void)hipGraphExecDestroy(c->verify_exec); c->verify_exec = nullptr; }
+  const int need = c->n + kMaxDepth;                            // largest key position a row of this cycle can have
+  if (use_graph && c->verify_exec != nullptr && c->verify_exec_rows == N && need <= c->verify_exec_bound) {
+    HIPCHK(c, hipGraphLaunch(c->verify_exec, c->stream));
+  } else {
+    rc = forward(c->n, c->n + max_depth, nullptr);
+    if (rc) return rc;
+    if (use_graph) {
+      // Every launch argument of the forward is either fixed or read from device memory (the tree tables and the base), so the
+      // sequence is captured once, while this cycle's launches run, and replayed from the next cycle on.
       const int bound = std::min(g.max_seq - 1, (need / kGraphBucket + 1) * kGraphBucket - 1);
-      hipGraph_t graph = nullptr;
-      HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-      rc = target_forward(c, N, 0, rt, bound, c->t_base);
-      if (!rc) rc = lm_head(c, c->feats, N, c->logits);
-      hipError_t e = hipStreamEndCapture(c->stream, &graph);
-      if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
-      if (e != hipSuccess) return fail(c, SPEC_EHIP, "graph capture: %s", hipGetErrorString(e));
-      e = hipGraphInstantiate(&c->verify_exec, graph, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(graph);
-      if (e != hipSuccess) { c->verify_exec = nullptr; return fail(c, SPEC_EHIP, "graph instantiate: %s", hipGetErrorString(e)); }
+      c->verify_exec_rows = c->verify_exec_bound = 0;
+      rc = capture(c, &c->verify_exec, "verify", [&] { return forward(0, bound, c->t_base); });
+      if (rc) return rc;
       c->verify_exec_rows = N;
       c->verify_exec_bound = bound;
     }
-    HIPCHK(c, hipGraphLaunch(c->verify_exec, c->stream));
-  } else {
-    rc = target_forward(c, N, c->n, rt, c->n + max_depth);
-    if (rc) return rc;
-    rc = lm_head(c, c->feats, N, c->logits);
-    if (rc) return rc;
     if (c->prof_level >= 2 && c->n_gemm_ev < kMaxGemmEvents) {
       // calibration: an event pair with nothing between its records, taken in the flow of the forward (the
       // stream still has queued work, so the interval is the event mechanism's own cost, not host pacing)
