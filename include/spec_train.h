@@ -60,8 +60,9 @@ int spec_hca_attention(int32_t n_streams, const void *q, const void *const *k, c
  * bytes of device memory, 256-byte aligned, owned by the caller; it holds the
  * fp32 logits of at most 512 positions at a time (sized to stay in the
  * last-level cache between the GEMM and the loss kernels) and per-slice
- * candidates.  The logits themselves are
- * not returned.  Errors: SPEC_EINVAL for bad arguments or a scratch that is too
+ * candidates (up to 16 MiB, or one set of 512 positions if that is more; with
+ * room for one set only, these are merged set by set).  The logits themselves
+ * are not returned.  Errors: SPEC_EINVAL for bad arguments or a scratch that is too
  * small (nothing is launched), SPEC_EHIP if a launch fails. */
 uint64_t spec_topk_loss_scratch_bytes(int32_t rows, int32_t vocab, int32_t k);
 int spec_topk_loss(int32_t dtype, const void *feat_target, const void *feat_draft, int32_t rows, int32_t d,

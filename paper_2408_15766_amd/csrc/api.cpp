@@ -1246,7 +1246,10 @@ int spec_hca_attention(int32_t n_streams, const void *q, const void *const *k, c
 
 namespace {
 constexpr int kLossChunk = 512;                               // positions whose logits are live at a time
-struct LossLayout { int chunk, ldz; size_t zq, zp, cand, rows_topk, rows_ce, total; };   // offsets in floats
+// The slices' results of as many chunks as this holds are merged by one launch: a merge of 512 positions is one wavefront for
+// each and takes 7 us, most of it the launch and two dependent reads; one of 4096 takes 10 instead of eight times 7.
+constexpr size_t kLossMergeFloats = (16u << 20) / sizeof(float);
+struct LossLayout { int chunk, merged, ldz; size_t zq, zp, rows_topk, rows_ce, cand, least, total; };   // offsets in floats
 LossLayout loss_layout(int rows, int vocab, int k) {
   LossLayout l{};
   l.chunk = rows < kLossChunk ? rows : kLossChunk;
@@ -1255,10 +1258,13 @@ LossLayout loss_layout(int rows, int vocab, int k) {
   size_t o = 0;
   l.zq = o; o += up((size_t)l.chunk * l.ldz);
   l.zp = o; o += up((size_t)l.chunk * l.ldz);
-  l.cand = o; o += up(topk_loss_scratch_floats(l.chunk, vocab, k));
   l.rows_topk = o; o += up((size_t)rows);                     // used when the caller does not want the per-row losses
   l.rows_ce = o; o += up((size_t)rows);
-  l.total = o;
+  l.cand = o;
+  l.least = o + up(topk_loss_scratch_floats(l.chunk, vocab, k));   // merged chunk by chunk
+  const size_t fit = kLossMergeFloats / topk_loss_scratch_floats(l.chunk, vocab, k);
+  l.merged = (int)std::min<int64_t>(rows, (int64_t)std::max<size_t>(fit, 1) * l.chunk);   // positions merged by one launch
+  l.total = o + up(topk_loss_scratch_floats(l.merged, vocab, k));
   return l;
 }
 bool loss_args_ok(int rows, int vocab, int k) {
@@ -1280,7 +1286,8 @@ int spec_topk_loss(int32_t dtype, const void *feat_target, const void *feat_draf
   const int epl = dtype == 1 ? 8 : 4;
   if (d < 1 || d % epl || ((uintptr_t)scratch & 255)) return SPEC_EINVAL;
   const LossLayout l = loss_layout(rows, vocab, k);
-  if (scratch_bytes < (uint64_t)l.total * sizeof(float)) return SPEC_EINVAL;
+  if (scratch_bytes < (uint64_t)l.least * sizeof(float)) return SPEC_EINVAL;
+  const int merged = scratch_bytes < (uint64_t)l.total * sizeof(float) ? l.chunk : l.merged;
   float *sf = (float *)scratch;
   float *out_topk = loss_topk ? loss_topk : sf + l.rows_topk, *out_ce = loss_ce ? loss_ce : sf + l.rows_ce;
   const size_t esz = dtype == 1 ? 2 : 4;
@@ -1296,7 +1303,12 @@ int spec_topk_loss(int32_t dtype, const void *feat_target, const void *feat_draf
     a.nseg = 1; a.total_blocks = a.seg_blocks[0];
     a.part = zs[0]; a.part2 = zs[1]; a.ldp = l.ldz; a.m_pad = l.chunk; a.n_split = 1;
     if (launch_gemm(dtype, a, st) != hipSuccess) return SPEC_EHIP;
-    if (launch_topk_loss_rows(zs[0], zs[1], l.ldz, m, vocab, k, sf + l.cand, out_topk + r0, out_ce + r0, st) != hipSuccess)
+    const int g0 = r0 / merged * merged;                      // the group's first position
+    if (launch_topk_loss_slices(zs[0], zs[1], l.ldz, m, vocab, k, sf + l.cand + topk_loss_scratch_floats(r0 - g0, vocab, k), st) != hipSuccess)
+      return SPEC_EHIP;
+    const int done = r0 + m - g0;
+    if ((done == merged || r0 + m == rows) &&
+        launch_topk_loss_merge(done, vocab, k, sf + l.cand, out_topk + g0, out_ce + g0, st) != hipSuccess)
       return SPEC_EHIP;
   }
   if (loss_sum && launch_loss_total(out_topk, out_ce, rows, loss_sum, st) != hipSuccess) return SPEC_EHIP;

@@ -18,6 +18,8 @@
 // and 59 -> 69 us.
 #include <limits.h>
 
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -32,15 +34,16 @@ constexpr int kLossWaves = kLossThreads / 64;
 __host__ __device__ inline size_t slice_floats(int k) { return 8 + 3 * (size_t)k; }
 
 // The largest t (from the top bit down) with count(t) >= k, where count(t) = number of keys >= t; stops early at a t with
-// exactly k.  Keys differ, so exactly k of them are >= the result if there are k keys at all; otherwise the result is 0.
+// exactly k (up to `more` above k).  Keys differ, so exactly k of them are >= the result if there are k keys at all; otherwise
+// the result is 0.
 template <int LAST = 0, typename Count>                      // LAST: lowest bit looked at
-__device__ __forceinline__ uint64_t kth_key(int k, Count count) {
+__device__ __forceinline__ uint64_t kth_key(int k, Count count, int more = 0) {
   uint64_t t = 0;
   for (int bit = 63; bit >= LAST; bit--) {
     const uint64_t trial = t | (1ull << bit);
     const int n = count(trial);
     if (n >= k) t = trial;
-    if (n == k) break;
+    if (n >= k && n <= k + more) break;
   }
   return t;
 }
@@ -73,43 +76,68 @@ __device__ __forceinline__ void put_candidate(float *out, int pos, uint64_t key,
   out[8 + 3 * pos + 2] = key ? zp : 0.f;
 }
 
-// Bound: the logits' way from the last-level cache (eight 16-byte loads per thread in flight); the selection works on registers.
-__global__ __launch_bounds__(kLossThreads) void loss_slice_kernel(const float *zq, const float *zp, int ldz, int vocab, int k,
-                                                                   int n_slices, float *scratch) {
+// exp(x) for x <= 0 (and -inf -> 0, NaN -> NaN): 2^p for the rounded product p = x * log2(e), times 1 + the remainder x - p * ln 2.
+// Relative error: that of the exponential unit and |p| * 2e-9; results below 2^-126 are 0.  expf() scales for those and
+// checks both ends of its range: 14 instructions against 6, two thirds of the slices' vector instructions.
+__device__ __forceinline__ float exp_nonpos(float x) {
+  const float p = x * 1.44269504f, r = __builtin_amdgcn_exp2f(p);
+  return fmaf(r, fmaxf(fmaf(p, -0.693147182f, x), -1.f), r);  // the maximum takes the remainder of -inf, a NaN, to -1: r = 0
+}
+
+constexpr int kWaveCand = 128;                               // places for a wavefront's tokens at or above the bound
+struct SliceShared {
+  float red_max[kLossWaves][2], red_sum[kLossWaves][4];
+  __attribute__((aligned(16))) uint32_t tmax[kLossThreads];
+  uint64_t ckey[kLossWaves][kWaveCand];
+  float czp[kLossWaves][kWaveCand];
+  float tau;
+  int cnt[2][kLossWaves];
+};
+
+// One slice of one position.  EDGE: the slice reaches past the vocabulary (the last one); only there token numbers are tested.
+//
+// Bound: vector instructions, then the logits' way from the last-level cache (eight 16-byte loads per thread in flight).
+// The candidates are found by comparing logits with a bound (one instruction a token; keys are built for those that pass), and
+// their places by the masks of these comparisons, most of which are empty; each wavefront lists its own, so one barrier
+// stands between finding and choosing.  512 positions, vocabulary 32000, K = 10, between two LM-head products: with
+// expf(), a key for every token and the places counted over the workgroup first 37.9 us, now 30.5 (the reads and maxima
+// alone 20.6); 188 positions, vocabulary 128256, K = 100: 69 -> 50.
+template <bool EDGE>
+__device__ __forceinline__ void loss_slice(const float *rq, const float *rp, int ldz, int vocab, int k, int c0, float *out, SliceShared &sh) {
   constexpr int PER = kTopkSlice / kLossThreads;   // 16
   constexpr int C4 = PER / 4;
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   static_assert(kLossWaves == 4, "the reductions below combine four wavefronts");
-  __shared__ float red_max[kLossWaves][2], red_sum[kLossWaves][4];
-  __shared__ __attribute__((aligned(16))) uint32_t tmax[kLossThreads];
-  __shared__ uint64_t ckey[kLossThreads];
-  __shared__ float czp[kLossThreads];
-  __shared__ uint32_t tau_s;
-  __shared__ int cnt[2][kLossWaves];
-  const int slice = blockIdx.x, rowi = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int c0 = slice * kTopkSlice;
-  const float *rq = zq + (size_t)rowi * ldz, *rp = zp + (size_t)rowi * ldz;
+  auto &red_max = sh.red_max;
+  auto &red_sum = sh.red_sum;
+  auto &tmax = sh.tmax;
+  auto &ckey = sh.ckey;
+  auto &czp = sh.czp;
+  auto &tau_s = sh.tau;
+  auto &cnt = sh.cnt;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int t = threadIdx.x;
   // element 4 * i + j of a thread is token c0 + i * 1024 + 4 * t + j; rows are 256-byte aligned and ldz is a multiple of 64
   auto token = [&](int e) { return c0 + (e >> 2) * (4 * kLossThreads) + 4 * t + (e & 3); };
+  auto inside = [&](int e) { return !EDGE || token(e) < vocab; };
   float vq[PER], vp[PER];
 #pragma unroll
   for (int i = 0; i < C4; i++) {
-    const int c = min(token(4 * i), ldz - 4);                 // past the row: any of its values, masked below
+    const int c = EDGE ? min(token(4 * i), ldz - 4) : token(4 * i);   // past the row: any of its values, masked below
     const f32x4_t q4 = *(const f32x4_t *)(rq + c), p4 = *(const f32x4_t *)(rp + c);
 #pragma unroll
     for (int j = 0; j < 4; j++) { vq[4 * i + j] = q4[j]; vp[4 * i + j] = p4[j]; }
   }
 #pragma unroll
   for (int e = 0; e < PER; e++)
-    if (token(e) >= vocab) vq[e] = vp[e] = -INFINITY;
+    if (!inside(e)) vq[e] = vp[e] = -INFINITY;
   // two workgroup-wide reductions, each over several quantities at once (wavefront results in LDS, then every
   // thread combines the four wavefronts in the same fixed order)
   float mq = vq[0], mp = vp[0];
 #pragma unroll
   for (int e = 1; e < PER; e++) { mq = fmaxf(mq, vq[e]); mp = fmaxf(mp, vp[e]); }
   // the best key (value word) of each thread: the K-th largest of these 256 bounds the K-th largest logit from below
-  const uint32_t best = token(0) < vocab ? (uint32_t)(order_key(mq, 0) >> 32) : 0u;
-  tmax[t] = best;
+  tmax[t] = inside(0) ? (uint32_t)(order_key(mq, 0) >> 32) : 0u;
   mq = wave_max(mq);
   mp = wave_max(mp);
   if (lane == 0) { red_max[wave][0] = mq; red_max[wave][1] = mp; }
@@ -120,74 +148,120 @@ __global__ __launch_bounds__(kLossThreads) void loss_slice_kernel(const float *z
     typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
     const u32x4_t m4 = *(const u32x4_t *)(tmax + 4 * lane);
     const uint32_t m[4] = {m4.x, m4.y, m4.z, m4.w};
-    const uint32_t tau = (uint32_t)(kth_key<32>(k, [&](uint64_t x) { return wave_count(m, (uint32_t)(x >> 32)); }) >> 32);
-    if (lane == 0) tau_s = tau ? tau : 1u;                    // fewer than k threads with tokens: every token passes
+    const uint64_t tau = kth_key<32>(k, [&](uint64_t x) { return wave_count(m, (uint32_t)(x >> 32)); }, 8);
+    if (lane == 0) tau_s = tau ? key_value(tau) : -INFINITY;  // fewer than k threads with tokens: every token passes
   }
   float sq = 0.f, sp = 0.f, cross = 0.f;
 #pragma unroll
   for (int e = 0; e < PER; e++) {
-    const bool in = token(e) < vocab;
-    const float wq = expf(vq[e] - mq);                       // exp(-inf) = 0 for padding
+    const float wq = exp_nonpos(vq[e] - mq);                 // 0 for padding
     sq += wq;
-    sp += expf(vp[e] - mp);
-    cross += in ? wq * vp[e] : 0.f;
+    sp += exp_nonpos(vp[e] - mp);
+    cross = inside(e) ? fmaf(wq, vp[e], cross) : cross;
   }
   sq = wave_sum(sq);
   sp = wave_sum(sp);
   cross = wave_sum(cross);
   if (lane == 0) { red_sum[wave][0] = sq; red_sum[wave][1] = sp; red_sum[wave][2] = cross; }
-  ckey[t] = 0ull;
   __syncthreads();
-  sq = ((red_sum[0][0] + red_sum[1][0]) + red_sum[2][0]) + red_sum[3][0];
-  sp = ((red_sum[0][1] + red_sum[1][1]) + red_sum[2][1]) + red_sum[3][1];
-  cross = ((red_sum[0][2] + red_sum[1][2]) + red_sum[2][2]) + red_sum[3][2];
-  float *out = scratch + ((size_t)rowi * n_slices + slice) * slice_floats(k);
-  if (t == 0) { out[0] = mq; out[1] = sq; out[2] = mp; out[3] = sp; out[4] = cross; }
+  if (t == 0) {
+    out[0] = mq; out[2] = mp;
+    out[1] = ((red_sum[0][0] + red_sum[1][0]) + red_sum[2][0]) + red_sum[3][0];
+    out[3] = ((red_sum[0][1] + red_sum[1][1]) + red_sum[2][1]) + red_sum[3][1];
+    out[4] = ((red_sum[0][2] + red_sum[1][2]) + red_sum[2][2]) + red_sum[3][2];
+  }
 
-  // The tokens at or above the bound: about K, unless large logits sit together in few threads or tie.
-  uint64_t key[PER];
+  // hides from the compiler that these are the values of before: masks and token numbers of all sixteen tokens are
+  // then formed where they are used instead of being held in registers
+  auto seen = [&] {
 #pragma unroll
-  for (int e = 0; e < PER; e++) key[e] = token(e) < vocab ? order_key(vq[e], token(e)) : 0ull;
-  auto compact = [&](uint64_t thr, auto put) {                // put(position, e) for every key >= thr, in a fixed order
-    const int mine = wave_count(key, thr);
-    if (lane == 0) cnt[0][wave] = mine;
-    __syncthreads();
-    int pos = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < kLossWaves; w++) { pos += w < wave ? cnt[0][w] : 0; total += cnt[0][w]; }
+    for (int e = 0; e < PER; e++) asm volatile("" : "+v"(vq[e]));
+    asm volatile("" : "+v"(t), "+s"(vocab));
+  };
+  // put(position, e) for the wavefront's tokens with pass(e), in a fixed order from `pos` on; the position behind the last
+  auto compact = [&](int pos, auto pass, auto put) {
 #pragma unroll
     for (int e = 0; e < PER; e++) {
-      const uint64_t mask = __ballot(key[e] >= thr);
-      if (key[e] >= thr) put(pos + __popcll(mask & ((1ull << lane) - 1ull)), e);
-      pos += __popcll(mask);
+      const uint64_t mask = __ballot(pass(e));
+      if (mask) {
+        if (pass(e)) put(pos + __popcll(mask & ((1ull << lane) - 1ull)), e);
+        pos += __popcll(mask);
+      }
     }
-    return total;
+    return pos;
   };
-  const int n_pass = __builtin_amdgcn_readfirstlane(compact((uint64_t)tau_s << 32, [&](int pos, int e) {
-    if (pos < kLossThreads) { ckey[pos] = key[e]; czp[pos] = vp[e]; }
-  }));
+  // The tokens at or above the bound: about K, unless large logits sit together in few threads or tie.  NaNs pass.
+  const float tau = tau_s;
+  seen();
+  const int mine = compact(0, [&](int e) { return inside(e) && !(vq[e] < tau); }, [&](int pos, int e) {
+    if (pos < kWaveCand) { ckey[wave][pos] = order_key(vq[e], token(e)); czp[wave][pos] = vp[e]; }
+  });
+  if (lane == 0) cnt[0][wave] = mine;
   __syncthreads();
-  if (n_pass <= kLossThreads) {
+  const int n0 = cnt[0][0], n1 = cnt[0][1], n2 = cnt[0][2], n3 = cnt[0][3];
+  const int n_pass = __builtin_amdgcn_readfirstlane(n0 + n1 + n2 + n3);
+  const int n_most = __builtin_amdgcn_readfirstlane(max(max(n0, n1), max(n2, n3)));
+  if (n_pass <= 256 && n_most <= kWaveCand) {
     if (wave != 0) return;
-    uint64_t ck[4];
+    auto finish = [&](auto per) {                             // the K best of up to 64 * per candidates
+      constexpr int N = decltype(per)::value;
+      uint64_t ck[N];
+      float cz[N];
 #pragma unroll
-    for (int i = 0; i < 4; i++) ck[i] = ckey[lane + 64 * i];
-    uint64_t thr = 1;
-    if (n_pass > k) thr = kth_key(k, [&](uint64_t x) { return wave_count(ck, x); });
-    int pos = 0;
+      for (int i = 0; i < N; i++) {
+        const int c = lane + 64 * i;                          // the wavefronts' tokens one behind the other
+        const int w = (c >= n0) + (c >= n0 + n1) + (c >= n0 + n1 + n2);
+        const int at = c - (w > 0 ? n0 : 0) - (w > 1 ? n1 : 0) - (w > 2 ? n2 : 0);
+        ck[i] = 0ull;
+        if (c < n_pass) { ck[i] = ckey[w][at]; cz[i] = czp[w][at]; }
+      }
+      uint64_t thr = 1;
+      if (n_pass > k) thr = kth_key(k, [&](uint64_t x) { return wave_count(ck, x); });
+      int pos = 0;
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const uint64_t mask = __ballot(ck[i] >= thr);
-      if (ck[i] >= thr) put_candidate(out, pos + __popcll(mask & ((1ull << lane) - 1ull)), ck[i], czp[lane + 64 * i]);
-      pos += __popcll(mask);
-    }
-    for (int i = pos + lane; i < k; i += 64) put_candidate(out, i, 0ull, 0.f);   // the slice has fewer than k tokens
+      for (int i = 0; i < N; i++) {
+        const uint64_t mask = __ballot(ck[i] >= thr);
+        if (ck[i] >= thr) put_candidate(out, pos + __popcll(mask & ((1ull << lane) - 1ull)), ck[i], cz[i]);
+        pos += __popcll(mask);
+      }
+      for (int i = pos + lane; i < k; i += 64) put_candidate(out, i, 0ull, 0.f);   // the slice has fewer than k tokens
+    };
+    if (n_pass <= 64) finish(std::integral_constant<int, 1>{});
+    else finish(std::integral_constant<int, 4>{});
     return;
   }
-  int turn = 0;                                               // n_pass > 256 >= k: the slice has k tokens
-  const uint64_t thr = kth_key(k, [&](uint64_t x) { return block_total<kLossWaves>(wave_count(key, x), cnt, turn); });
+  seen();                                                     // more tokens than k pass: the slice has k tokens
+#pragma unroll
+  for (int e = 0; e < PER; e++)                               // value words; 0 (below every logit's) past the vocabulary
+    vq[e] = __uint_as_float(inside(e) ? (uint32_t)(order_key(vq[e], 0) >> 32) : 0u);
+  auto key = [&](int e) { return (uint64_t)__float_as_uint(vq[e]) << 32 | (uint32_t)(0x7FFFFFFF - token(e)); };
+  int turn = 0;
+  const uint64_t thr = kth_key(k, [&](uint64_t x) {
+    int n = 0;
+    seen();                                                   // keeps the token numbers of all sixteen out of registers
+#pragma unroll
+    for (int e = 0; e < PER; e++) n += __popcll(__ballot(key(e) >= x));
+    return block_total<kLossWaves>(n, cnt, turn);
+  });
+  int n = 0, pos = 0;
+#pragma unroll
+  for (int e = 0; e < PER; e++) n += __popcll(__ballot(key(e) >= thr));
   __syncthreads();
-  compact(thr, [&](int pos, int e) { put_candidate(out, pos, key[e], vp[e]); });
+  if (lane == 0) cnt[0][wave] = n;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kLossWaves; w++) pos += w < wave ? cnt[0][w] : 0;
+  seen();
+  compact(pos, [&](int e) { return key(e) >= thr; }, [&](int at, int e) { put_candidate(out, at, key(e), vp[e]); });
+}
+__global__ __launch_bounds__(kLossThreads, 7) void loss_slice_kernel(const float *zq, const float *zp, int ldz, int vocab, int k,
+                                                                   int n_slices, float *scratch) {
+  __shared__ SliceShared sh;
+  const int slice = blockIdx.x, rowi = blockIdx.y, c0 = slice * kTopkSlice;
+  const float *rq = zq + (size_t)rowi * ldz, *rp = zp + (size_t)rowi * ldz;
+  float *out = scratch + ((size_t)rowi * n_slices + slice) * slice_floats(k);
+  if (c0 + kTopkSlice <= vocab) loss_slice<false>(rq, rp, ldz, vocab, k, c0, out, sh);
+  else loss_slice<true>(rq, rp, ldz, vocab, k, c0, out, sh);
 }
 
 constexpr int kLossMaxCand = 4096;
@@ -258,15 +332,18 @@ size_t topk_loss_scratch_floats(int rows, int vocab, int k) {
   return (size_t)rows * n_slices * slice_floats(k);
 }
 
-hipError_t launch_topk_loss_rows(const float *zq, const float *zp, int ldz, int rows, int vocab, int k, float *scratch,
-                                 float *loss_topk, float *loss_ce, hipStream_t st) {
+hipError_t launch_topk_loss_slices(const float *zq, const float *zp, int ldz, int rows, int vocab, int k, float *scratch, hipStream_t st) {
   const int n_slices = (vocab + kTopkSlice - 1) / kTopkSlice;
   if (rows < 1 || rows > 65535 || vocab < 1 || ldz < vocab || ldz % 64 || ((uintptr_t)zq & 15) || ((uintptr_t)zp & 15) || k < 1 || k > kLossMaxK || k > vocab || n_slices * k > kLossMaxCand)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(loss_slice_kernel, dim3(n_slices, rows), dim3(kLossThreads), 0, st, zq, zp, ldz, vocab, k, n_slices, scratch);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int n_cand = n_slices * k;                           // one wavefront needs no barriers: up to four candidates per lane
+  return hipGetLastError();
+}
+
+hipError_t launch_topk_loss_merge(int rows, int vocab, int k, const float *scratch, float *loss_topk, float *loss_ce, hipStream_t st) {
+  const int n_slices = (vocab + kTopkSlice - 1) / kTopkSlice, n_cand = n_slices * k;
+  if (rows < 1 || vocab < 1 || k < 1 || k > kLossMaxK || k > vocab || n_cand > kLossMaxCand) return hipErrorInvalidValue;
+  // one wavefront needs no barriers: up to four candidates per lane
   if (n_cand <= 256) hipLaunchKernelGGL((loss_merge_kernel<1, 4>), dim3(rows), dim3(64), 0, st, k, n_slices, scratch, loss_topk, loss_ce);
   else if (n_cand <= 1024) hipLaunchKernelGGL((loss_merge_kernel<4, 4>), dim3(rows), dim3(256), 0, st, k, n_slices, scratch, loss_topk, loss_ce);
   else hipLaunchKernelGGL((loss_merge_kernel<16, 4>), dim3(rows), dim3(1024), 0, st, k, n_slices, scratch, loss_topk, loss_ce);

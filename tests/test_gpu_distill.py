@@ -150,6 +150,70 @@ def test_large_logits_next_to_each_other(env, vocab, k):
     check(got_topk, got_ce, want, alt, want_ce)
 
 
+@pytest.mark.parametrize("vocab,k", [(4096, 40), (9000, 30), (12288, 100), (4097, 55)])
+def test_candidates_of_one_wavefront_and_of_all(env, vocab, k):
+    # tokens above the bound: all in the first wavefront's quarter of a slice (more than it has places for, or fewer), and
+    # spread over the four so that their lists are read one behind the other
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(29, 4, 128, vocab, "fp32")
+    tok = np.arange(vocab)
+    w[:, 0] = np.where(tok % 1024 < 256, 4.0, -4.0) - tok * (2.0 / vocab)
+    w[:, 1] = np.where(tok % 16 < 3, 4.0, -4.0) - tok * (2.0 / vocab)
+    for r in (0, 1):
+        ft[r] = 0.0
+        ft[r, r] = 1.0
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, k, "fp32")
+    want, alt, want_ce = oracle_losses(ft, fd, w, k)
+    check(got_topk, got_ce, want, alt, want_ce)
+
+
+def test_infinite_and_nan_logits(env):
+    # tokens ruled out on both sides have no weight (their product 0 * inf makes the whole-vocabulary term NaN, as it did);
+    # NaN logits show in that position's losses and in no other's
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(30, 5, 128, 9000, "fp32")
+    keep = np.arange(9000) % 3 > 0
+    ft[:, 0] = fd[:, 0] = 1.0
+    w[:, 0] = 0.0
+    want, alt, _ = oracle_losses(ft, fd, w[keep], 20)
+    w[~keep, 0] = -np.inf
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 20, "fp32")
+    assert (np.isclose(got_topk, want, **TOL) | np.isclose(got_topk, alt, **TOL)).all()
+    assert np.isnan(got_ce).all()
+    w[~keep, 0] = 0.0
+    clean = run_gpu(torch, P, ft, fd, w, 20, "fp32")
+    ft[3] = np.nan
+    fd[1] = np.nan
+    got = run_gpu(torch, P, ft, fd, w, 20, "fp32")
+    for g, c in zip(got[:2], clean[:2]):
+        assert np.isnan(g[[1, 3]]).all()
+        np.testing.assert_array_equal(g[[0, 2, 4]], c[[0, 2, 4]])
+
+
+@pytest.mark.parametrize("rows,vocab,k", [(1100, 32000, 128), (1537, 4096, 3), (600, 128256, 40)])
+def test_one_merge_for_several_chunks(env, rows, vocab, k):
+    # two chunks' slices merged at a time, then a ragged rest; all four in one merge; one chunk a merge.  A scratch with room
+    # for one chunk's only is merged chunk by chunk, with the same bits.
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(31, rows, 64, vocab, "bf16")
+    dev = lambda x: torch.from_numpy(x).cuda().bfloat16()
+    dft, dfd, head = dev(ft), dev(fd), P.spec_pack_weight(dev(w))
+    n = P.spec_topk_loss_scratch_bytes(rows, vocab, k)
+    up = lambda x: (x + 63) // 64 * 64
+    cand = lambda r: up(r * ((vocab + 4095) // 4096) * (8 + 3 * k))
+    least = 4 * (2 * up(512 * up(vocab)) + 2 * up(rows) + cand(512))
+    assert least <= n <= max(least, 4 * (2 * up(512 * up(vocab)) + 2 * up(rows)) + (16 << 20))
+    out = [P.spec_topk_loss(dft, dfd, head, k, scratch=torch.empty(b, dtype=torch.uint8, device="cuda")) for b in (n, least)]
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    with pytest.raises(P.SpecError):
+        P.spec_topk_loss(dft, dfd, head, k, scratch=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
+    sel = np.array([0, 511, 512, 513, rows - 77, rows - 76, rows - 1] + ([1023, 1024] if rows > 1024 else []))
+    want, alt, want_ce = oracle_losses(ft, fd, w, k, rows=sel)
+    got = [o.cpu().numpy().astype(np.float64) for o in out[0]]
+    check(got[0][sel], got[1][sel], want, alt, want_ce)
+
+
 def test_topk_loss_full_size_sampled_rows(env):
     # the benchmark's launch: 4096 positions (batch 2 x 2048), LLaMA2-7B widths; the oracle takes 24 sampled rows
     torch, P = env
