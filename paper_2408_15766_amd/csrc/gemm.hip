@@ -703,19 +703,22 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
 // ---- fp32 storage, launches that fill the chip ----------------------------------------------------------
 // gemm_f32_kernel fetches (tokens + weight rows) * 4 bytes for 2 * tokens * weight rows operations, in half used lines: about ten operations per
 // byte, and once the launch fills the chip the L2 limits it at about 60 TFLOP/s.  Here four wavefronts share a tile of 32 tokens x 64 weight
-// rows (two by two, 16 x 32 each) whose operands are copied straight into the LDS, 64 k at a time, one tile ahead; both keep the
-// packed layout there, in which a fragment read touches every bank evenly.  Three workgroups fit a compute unit, so one's waits are
-// covered by the others (tiles of 64 x 64, 64 x 128 and 128 x 128 were slower: fewer wavefronts).  Bound: the fp32 matrix rate (150 TFLOP/s
-// in a loop of nothing but these instructions).
+// rows (two by two, 16 x 32 each) whose operands are copied straight into the LDS, 32 k at a time into a ring of four, three ahead (in the LDS
+// that two tiles of 64 k, one ahead, took: what a launch of few k tiles waited for); both keep the packed layout there, in which a fragment
+// read touches every bank evenly.  Three workgroups fit a compute unit, so one's waits are covered by the others (tiles of 64 x 64, 64 x 128
+// and 128 x 128 were slower: fewer wavefronts).  Bound: the fp32 matrix rate (150 TFLOP/s in a loop of nothing but these instructions).
 // The bits are gemm_f32_kernel's: an fp32 MFMA is a chain of fused multiply-adds in the order of its k (both shapes, checked against
 // fmaf), the 64-k tiles w, w + 4, ... of the K range have one accumulator, w = 0, 1, 2, 3 one after the other here, and the four sums are
 // added up in that order.
 // Measured (MI355X, us; gemm_f32_kernel before): 512 x 32000 x 4096 1966 -> 1110 (121 TFLOP/s), 1400 x 32000 x 1024 1083 -> 799, 512 x 12288 x
-// 4096 588 -> 411, 300 x 5504 x 1024 53 -> 44.
+// 4096 588 -> 411, 300 x 5504 x 1024 53 -> 44.  The ring of halves against two whole tiles, then ragged tiles without padding: two sets of 129
+// rows x 9000, K = 512 38.1 -> 36.0 -> 34.9, K = 2048 116.8 -> 112.4 -> 105.8; two of 512 x 9000 x 512 97.9 -> 92.6, of 256 x 4096 x 4096 160 -> 151.
 constexpr int kF32Blocks = 2;                                 // 32-row weight blocks per workgroup
 __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f32_tiled_kernel(GemmArgs a) {
-  constexpr int KI = 64, XI = kTileBytes / 4096, WI = kF32Blocks * XI;   // 1 KB copies per wave and tile
-  __shared__ __attribute__((aligned(1024))) unsigned char xs0[kTileBytes], xs1[kTileBytes], ws0[kF32Blocks * kTileBytes], ws1[kF32Blocks * kTileBytes];   // (arrays of their own: see gemm_mm_kernel)
+  constexpr int KI = 64, HB = kTileBytes / 2, WI = 2, LOADS = WI + 1;   // half a tile (32 k) of a block; 1 KB copies per wave and half: weights, all
+  // (arrays of their own: see gemm_mm_kernel)
+  __shared__ __attribute__((aligned(1024))) unsigned char b0[3 * HB], b1[3 * HB], b2[3 * HB], b3[3 * HB];   // the tokens' half tile, then the weight blocks'
+  static_assert(kF32Blocks == 2 && HB == 4096, "eight weight pieces and four token pieces per half tile, for four wavefronts");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kg = lane >> 4, th = wave & 1, wh = wave >> 1;   // the wavefront's 16 tokens and its weight block
   // ids 8 apart run on one XCD: the token tiles of a weight tile follow each other there
@@ -727,6 +730,8 @@ __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f32_tiled_kernel(GemmArg
   const int set_tiles = (a.m + 31) / 32;
   const bool second = mt >= set_tiles;
   const int m0 = (second ? mt - set_tiles : mt) * 32, m_loc = min(a.m - m0, 32);
+  // up to 16 tokens: the wavefronts that would have the other 16 take the second half of the weight block instead of padding
+  const bool narrow = m_loc <= 16 && a.act == nullptr;
   const int n_it_total = (a.in + KI - 1) / KI;
   const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
   const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
@@ -735,87 +740,126 @@ __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f32_tiled_kernel(GemmArg
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
   auto seg_of = [&](int blk, int &b0) { const int s = blk < e0 ? 0 : (blk < e1 ? 1 : 2); b0 = s == 0 ? 0 : (s == 1 ? e0 : e1); return s; };
   // the 1 KB pieces this wave copies: of a weight tile as it is, of the X rows (piece j of row c, half g at j * 1024 + (g * 32 + c) * 16)
-  __amdgpu_buffer_rsrc_t wsrc[WI];
-#pragma unroll
-  for (int i = 0; i < WI; i++) {
-    const int p = wave * WI + i, blk = min(bx * kF32Blocks + p / 8, a.total_blocks - 1);
-    int b0;
-    const int seg = seg_of(blk, b0);
+  __amdgpu_buffer_rsrc_t wsrc;
+  {
+    const int blk = min(bx * kF32Blocks + (wave >> 1), a.total_blocks - 1);
+    int first;
+    const int seg = seg_of(blk, first);
     const void *w = seg == 0 ? a.seg_w[0] : (seg == 1 ? a.seg_w[1] : a.seg_w[2]);
-    wsrc[i] = buffer_of((const char *)w + (size_t)(blk - b0) * n_it_total * kTileBytes + p % 8 * 1024);
+    wsrc = buffer_of((const char *)w + (size_t)(blk - first) * n_it_total * kTileBytes + (wave & 1) * 2048);
   }
   const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const float *)(second ? a.x2 : a.x) + (size_t)m0 * a.ldx);
   const uint32_t xrow = (uint32_t)((lane & 31) < m_loc ? lane & 31 : 0) * (uint32_t)a.ldx * 4u;
-  auto copy = [&](unsigned char *xb, unsigned char *wb, int it) __attribute__((always_inline)) {
+  auto copy = [&](unsigned char *buf, int it, int half) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < WI; i++) load_to_lds(wsrc[i], lane * 16, it * kTileBytes, wb + (wave * WI + i) * 1024);
-#pragma unroll
-    for (int i = 0; i < XI; i++) {
-      const int k = it * KI + (lane >> 5) * 32 + (wave * XI + i) * 4;   // past K: meets a zero weight
-      load_to_lds(xsrc, (int)(xrow + (uint32_t)(k < a.in ? k : 0) * 4u), 0, xb + (wave * XI + i) * 1024);
-    }
+    for (int i = 0; i < WI; i++) load_to_lds(wsrc, lane * 16, it * kTileBytes + half * HB + i * 1024, buf + HB + (wave * WI + i) * 1024);
+    const int k = it * KI + (lane >> 5) * 32 + (half * 4 + wave) * 4;   // past K: meets a zero weight
+    load_to_lds(xsrc, (int)(xrow + (uint32_t)(k < a.in ? k : 0) * 4u), 0, buf + wave * 1024);
   };
 
   f32x4_t acc[2], sum[2];                                     // by half of the weight block
   acc[0] = acc[1] = sum[0] = sum[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   struct Frag { f32x4_t x, w[2]; };                           // of step jj, as in gemm_f32_kernel
-  const int xfrag = ((kg & 1) * 32 + th * 16 + r) * 16 + (kg >> 1) * 1024, wfrag = wh * kTileBytes + ((kg & 1) * 32 + r) * 16 + (kg >> 1) * 1024;
-  auto read = [&](Frag &f, const unsigned char *xb, const unsigned char *wb, int jj) __attribute__((always_inline)) {
-    f.w[0] = *(const f32x4_t *)(wb + wfrag + jj * 2048);
-    f.w[1] = *(const f32x4_t *)(wb + wfrag + 256 + jj * 2048);
-    f.x = *(const f32x4_t *)(xb + xfrag + jj * 2048);
+  const int xfrag = ((kg & 1) * 32 + (narrow ? 0 : th * 16) + r) * 16 + (kg >> 1) * 1024;
+  const int wfrag = (1 + wh) * HB + ((kg & 1) * 32 + (narrow ? th * 16 : 0) + r) * 16 + (kg >> 1) * 1024, wfrag1 = narrow ? wfrag : wfrag + 256;
+  auto read = [&](Frag &f, const unsigned char *buf, int jj) __attribute__((always_inline)) {
+    f.w[0] = *(const f32x4_t *)(buf + wfrag + jj * 2048);
+    f.w[1] = *(const f32x4_t *)(buf + wfrag1 + jj * 2048);
+    f.x = *(const f32x4_t *)(buf + xfrag + jj * 2048);
   };
   auto mul = [&](const Frag &f) __attribute__((always_inline)) {
+    if (narrow) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.x[e], f.w[0][e], acc[0], 0, 0, 0);
+      return;
+    }
 #pragma unroll
     for (int e = 0; e < 4; e++)
 #pragma unroll
       for (int b = 0; b < 2; b++) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.x[e], f.w[b][e], acc[b], 0, 0, 0);
   };
   Frag f[2];
-  int w = 0, it = it_begin, left = it_end - it_begin;         // tile `it` of those of group w: it_begin + w, + 4, ...
-  copy(xs0, ws0, it);
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-  wg_barrier();
-  read(f[0], xs0, ws0, 0);
-  auto stage = [&](unsigned char *xc, unsigned char *wc, unsigned char *xn, unsigned char *wn) __attribute__((always_inline)) {
-    // on entry f[0] = the fragments of step 0; nobody reads the other buffers any more
-    const bool more = left > 1, turn = it + 4 >= it_end;      // turn: the group's last tile
-    const int next_w = turn ? w + 1 : w, next_it = turn ? it_begin + w + 1 : it + 4;
-#pragma unroll
-    for (int jj = 0; jj < 3; jj++) {
-      read(f[(jj + 1) & 1], xc, wc, jj + 1);
-      if (jj == 0 && more) copy(xn, wn, next_it);
-      __builtin_amdgcn_sched_barrier(0);                      // the reads ahead of the products that hide them
-      mul(f[jj & 1]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (more) {
-      __builtin_amdgcn_s_waitcnt(0x0070);                     // vmcnt(0) lgkmcnt(0): every fragment of this tile is in registers, the next tile has arrived
+  // tile `it` of those of group w: it_begin + w, + 4, ...; the copies' tile is up to three halves ahead
+  int w = 0, it = it_begin, left = 2 * (it_end - it_begin), cw = 0, cit = it_begin;
+  auto copy_next = [&](unsigned char *buf, int half) __attribute__((always_inline)) {
+    copy(buf, cit, half);
+    if (half == 0) return;
+    const bool turn = cit + 4 >= it_end;
+    cw = turn ? cw + 1 : cw;
+    cit = turn ? it_begin + cw : cit + 4;
+  };
+  // half `h` of a tile, in `cur`; the next half is in `next`, the third one from here goes to `free`.  FULL: there is one
+  // (asked at run time in the loop, the compiler no longer knows how many copies are in flight and waits for too many)
+  auto stage = [&](auto full, int h, unsigned char *cur, unsigned char *next, unsigned char *free) __attribute__((always_inline)) {
+    // on entry f[0] = the fragments of step 0; nobody reads `free` any more
+    constexpr bool FULL = decltype(full)::value;
+    read(f[1], cur, 1);
+    if (FULL || left > 3) copy_next(free, 1 - h);
+    __builtin_amdgcn_sched_barrier(0);                        // the reads ahead of the products that hide them
+    mul(f[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (FULL || left > 1) {                                   // every fragment of this half is in registers, the next half has arrived
+      if (FULL || left > 3) __builtin_amdgcn_s_waitcnt(0x0076);       // vmcnt(6) lgkmcnt(0)
+      else if (left == 3) __builtin_amdgcn_s_waitcnt(0x0073);
+      else __builtin_amdgcn_s_waitcnt(0x0070);
       wg_barrier();
-      read(f[0], xn, wn, 0);
+      read(f[0], next, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
     mul(f[1]);
     __builtin_amdgcn_sched_barrier(0);
+    left--;
+    if (h == 0) return;
+    const bool turn = it + 4 >= it_end;                       // the group's last tile
     if (turn) {
 #pragma unroll
       for (int b = 0; b < 2; b++) {
         // (a group without tiles adds its zero in gemm_f32_kernel)
 #pragma unroll
-        for (int v = 0; v < 4; v++) sum[b][v] = (w == 0 ? acc[b][v] : sum[b][v] + acc[b][v]) + (more ? -0.f : 0.f);
+        for (int v = 0; v < 4; v++) sum[b][v] = (w == 0 ? acc[b][v] : sum[b][v] + acc[b][v]) + (left ? -0.f : 0.f);
         acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       }
     }
-    w = next_w; it = next_it; left--;
+    w = turn ? w + 1 : w;
+    it = turn ? it_begin + w : it + 4;
   };
-  while (left >= 2) {
-    stage(xs0, ws0, xs1, ws1);
-    stage(xs1, ws1, xs0, ws0);
+  constexpr std::true_type full{};
+  constexpr std::false_type rest{};
+  static_assert(LOADS == 3, "the counts of the waits");
+  copy_next(b0, 0);
+  copy_next(b1, 1);
+  if (left >= 8) {
+    copy_next(b2, 0);
+    __builtin_amdgcn_s_waitcnt(0x0F76);                       // vmcnt(6): all but the last two halves have arrived
+    wg_barrier();
+    read(f[0], b0, 0);
+    do {
+      stage(full, 0, b0, b1, b3);
+      stage(full, 1, b1, b2, b0);
+      stage(full, 0, b2, b3, b1);
+      stage(full, 1, b3, b0, b2);
+    } while (left >= 8);
+  } else {
+    if (left > 2) copy_next(b2, 0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    wg_barrier();
+    read(f[0], b0, 0);
   }
-  if (left) stage(xs0, ws0, xs1, ws1);
+  if (left) {
+    stage(rest, 0, b0, b1, b3);
+    stage(rest, 1, b1, b2, b0);
+  }
+  if (left) {
+    stage(rest, 0, b2, b3, b1);
+    stage(rest, 1, b3, b0, b2);
+  }
+  if (left) {
+    stage(rest, 0, b0, b1, b3);
+    stage(rest, 1, b1, b2, b0);
+  }
 
   // lane (r, kg) holds, for weight row r of a half, tokens th * 16 + 4 * kg + v
-  const int blk = bx * kF32Blocks + wh, i0 = th * 16 + 4 * kg;
+  const int blk = bx * kF32Blocks + wh, i0 = (narrow ? 0 : th * 16) + 4 * kg;
   if (blk >= a.total_blocks) return;
   if (a.act != nullptr) {                                     // SwiGLU: half 0 = gate rows, half 1 = the up rows of the same columns
     const int f_ = a.seg_rows[0], col = blk * 16 + r;
@@ -824,14 +868,15 @@ __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f32_tiled_kernel(GemmArg
       if (i0 + v < m_loc && col < f_) ((float *)a.act)[(size_t)(m0 + i0 + v) * f_ + col] = silu_mul(sum[0][v], sum[1][v]);
     return;
   }
-  int b0;
-  const int seg = seg_of(blk, b0);
+  int first;
+  const int seg = seg_of(blk, first);
   const int rows = seg == 0 ? a.seg_rows[0] : (seg == 1 ? a.seg_rows[1] : a.seg_rows[2]);
   const int col0 = seg == 0 ? a.seg_col0[0] : (seg == 1 ? a.seg_col0[1] : a.seg_col0[2]);
   float *out = (second ? a.part2 : a.part) + ((size_t)by * a.m_pad + m0) * a.ldp + col0;
 #pragma unroll
   for (int b = 0; b < 2; b++) {
-    const int row = (blk - b0) * 32 + b * 16 + r;
+    if (narrow && b) break;
+    const int row = (blk - first) * 32 + (narrow ? th : b) * 16 + r;
 #pragma unroll
     for (int v = 0; v < 4; v++)
       if (i0 + v < m_loc && row < rows) out[(size_t)(i0 + v) * a.ldp + row] = sum[b][v];

@@ -113,6 +113,21 @@ def test_gemm_fp32_tiled_matches_fp64_and_small_launches_bits(env, m, k, rows, n
     assert torch.equal(P.spec_k_gemm_swiglu(x[m - 1:].contiguous(), gate, up)[0], act[m - 1])
 
 
+@pytest.mark.parametrize("m,k", [(17, 128), (48, 192), (49, 192), (33, 256), (40, 320), (80, 448), (81, 640)])
+def test_gemm_fp32_tiled_ring_and_ragged_tiles(env, m, k):
+    """The ring of half k tiles: every count from two tiles to one past its second turn; last token tiles of up to 16 rows, whose
+    wavefronts share a weight block instead of the tokens, and of one row more."""
+    torch, P = env
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed("f32r", m, k) & 0xFFFF)
+    x = torch.randn(m, k, device="cuda", generator=g)
+    ws = [torch.randn(r, k, device="cuda", generator=g) * 0.05 for r in (32900, 47)]
+    got = P.spec_k_gemm(x, ws, 1)
+    want = x.double() @ torch.cat(ws).double().t()
+    assert (got.double().sum(0) - want).abs().max() <= 1e-6 * np.sqrt(k) * max(1.0, float(want.abs().max()))
+    for i in sorted({0, max(m // 32 * 32 - 1, 0), m // 32 * 32, m - 1}):
+        assert torch.equal(P.spec_k_gemm(x[i:i + 1].contiguous(), ws, 1)[:, 0], got[:, i])
+
+
 @pytest.mark.parametrize("dtype,m,k,rows", [("fp32", 16, 256, 688), ("bf16", 60, 4096, 1100), ("bf16", 1, 1280, 64), ("bf16", 200, 768, 300),
                                             ("bf16", 40, 256, 77), ("fp32", 33, 128, 77), ("bf16", 60, 512, 15), ("bf16", 130, 256, 45)])
 def test_gemm_swiglu_epilogue_matches_oracle(env, dtype, m, k, rows):
