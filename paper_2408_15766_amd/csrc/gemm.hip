@@ -118,6 +118,15 @@ __device__ __forceinline__ void swiglu_epilogue(const f32x16_t (&acc)[TB], T *ac
     }
 }
 
+// First slab of split y, floor(y * slabs / n_split).  With slabs = slab_base * n_split + slab_rem that is y * slab_base + floor(y * slab_rem /
+// n_split), and the quotient is the high word of a product with ceil(2^64 / n_split): exact, since the product of dividend and divisor
+// stays below 2^64 (n_split = 1: slab_rem = 0; n_split is a grid dimension, up to 65535).  A 64-bit division is some 150 instructions, and two of them stood ahead of a launch's
+// first load.
+__device__ __forceinline__ int slab_begin(const GemmArgs &a, int y) {
+  const uint32_t x = (uint32_t)y * (uint32_t)a.slab_rem;
+  return y * a.slab_base + (int)(((uint64_t)x * a.split_hi + __umulhi(x, a.split_lo)) >> 32);
+}
+
 // PAIR: a second set of m rows (x2 -> part2) follows the first as rows m .. 2m-1 of the token tile.
 template <typename T, int TB, bool PAIR>
 __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) void gemm_stream_kernel(GemmArgs a) {
@@ -152,9 +161,8 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
 
   // K splits are balanced to within one slab: split y covers slabs [y*S/n, (y+1)*S/n)
   const int n_it_total = (a.in + KI - 1) / KI;                         // tiles along k (K zero-padded to KI)
-  const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
-  const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
-  const int it_end = min(n_it_total, (int)((long long)(by + 1) * n_slabs_total / a.n_split) * kSlabIters);
+  const int it_begin = slab_begin(a, by) * kSlabIters;
+  const int it_end = min(n_it_total, slab_begin(a, by + 1) * kSlabIters);
   const int k_begin = it_begin * KI;
   const int n_iter = it_end - it_begin;
   const int n_slab = (n_iter + kSlabIters - 1) / kSlabIters;
@@ -351,8 +359,7 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
   const bool swiglu = a.act != nullptr;
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
   const int n_it_total = (a.in + 127) / 128;
-  const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
-  auto range_begin = [&](int r) { return min(n_it_total, (int)((long long)r * n_slabs_total / a.n_split) * kSlabIters); };
+  auto range_begin = [&](int r) { return min(n_it_total, slab_begin(a, r) * kSlabIters); };
   const int it_begin = range_begin(by), it_end = FOLD ? n_it_total : range_begin(by + 1);
   const int n_stage = 2 * (it_end - it_begin);
 
@@ -626,9 +633,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
   const void *seg_w = seg == 0 ? a.seg_w[0] : (seg == 1 ? a.seg_w[1] : a.seg_w[2]);
   constexpr int KI = 64;
   const int n_it_total = (a.in + KI - 1) / KI;
-  const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
-  const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
-  const int it_end = min(n_it_total, (int)((long long)(by + 1) * n_slabs_total / a.n_split) * kSlabIters);
+  const int it_begin = slab_begin(a, by) * kSlabIters;
+  const int it_end = min(n_it_total, slab_begin(a, by + 1) * kSlabIters);
 
   const char *w0 = (const char *)seg_w + (size_t)(blk - b0) * n_it_total * kTileBytes + (((kg & 1) * 32 + r) * 16 + (kg >> 1) * 1024);
   const float *xbase = (const float *)(second ? a.x2 : a.x) + (size_t)m0 * a.ldx;
@@ -733,9 +739,8 @@ __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f32_tiled_kernel(GemmArg
   // up to 16 tokens: the wavefronts that would have the other 16 take the second half of the weight block instead of padding
   const bool narrow = m_loc <= 16 && a.act == nullptr;
   const int n_it_total = (a.in + KI - 1) / KI;
-  const int n_slabs_total = (n_it_total + kSlabIters - 1) / kSlabIters;
-  const int it_begin = (int)((long long)by * n_slabs_total / a.n_split) * kSlabIters;
-  const int it_end = min(n_it_total, (int)((long long)(by + 1) * n_slabs_total / a.n_split) * kSlabIters);
+  const int it_begin = slab_begin(a, by) * kSlabIters;
+  const int it_end = min(n_it_total, slab_begin(a, by + 1) * kSlabIters);
 
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
   auto seg_of = [&](int blk, int &b0) { const int s = blk < e0 ? 0 : (blk < e1 ? 1 : 2); b0 = s == 0 ? 0 : (s == 1 ? e0 : e1); return s; };
@@ -1180,13 +1185,18 @@ static hipError_t launch_bf16(const GemmArgs &a, hipStream_t st) {
 int gemm_k_per_iter(int dtype) { return dtype == 1 ? 128 : 64; }
 int gemm_k_per_slab(int dtype) { return kSlabIters * gemm_k_per_iter(dtype); }
 
-hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st) {
+hipError_t launch_gemm(int dtype, const GemmArgs &args, hipStream_t st) {
+  GemmArgs a = args;
   { hipError_t e = gemm_init(); if (e != hipSuccess) return e; }
   if (a.m < 1 || a.m_pad < a.m || a.nseg < 1 || a.nseg > 3 || a.n_split < 1 || a.in < 1) return hipErrorInvalidValue;
   if (a.n_split > (a.in + gemm_k_per_slab(dtype) - 1) / gemm_k_per_slab(dtype)) return hipErrorInvalidValue;   // no empty split
   // SwiGLU mode: the one gate/up matrix, 16 columns per block, whole K (the activation is not linear)
   if (a.act != nullptr && (a.nseg != 1 || a.n_split != 1 || a.x2 != nullptr || a.seg_blocks[0] != (a.seg_rows[0] + 15) / 16))
     return hipErrorInvalidValue;
+  const int slabs = (a.in + gemm_k_per_slab(dtype) - 1) / gemm_k_per_slab(dtype);
+  const uint64_t inv = ~0ull / (uint64_t)a.n_split + 1;       // ceil(2^64 / n_split); 0 for n_split = 1
+  a.slab_base = slabs / a.n_split; a.slab_rem = slabs % a.n_split;
+  a.split_hi = (uint32_t)(inv >> 32); a.split_lo = (uint32_t)inv;
   return dtype == 1 ? launch_bf16(a, st) : launch_f32(a, st);
 }
 

@@ -52,6 +52,8 @@ struct GemmArgs {
   void *act;
   int m_tiles, grid_x;                  // set by launch_gemm: token tiles, workgroups per tile and split
   int n_big;                            // set by launch_gemm: whole 256 x 256 tiles per XCD (gemm_mm_mixed_kernel)
+  int slab_base, slab_rem;              // set by launch_gemm: slabs per split, and how many are left over (slab_begin in gemm.hip)
+  uint32_t split_hi, split_lo;          // set by launch_gemm: ceil(2^64 / n_split)
   int blk_per_wg, blk_per_wave;         // set by launch_gemm: wave w of workgroup x streams block x * blk_per_wg + w * blk_per_wave
 };
 hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st);
