@@ -31,6 +31,13 @@ int spec_k_gemm(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in
                 const void *w0, int32_t rows0, const void *w1, int32_t rows1, const void *w2, int32_t rows2,
                 float *part, int32_t ldp, int32_t m_pad, int32_t n_split, void *stream);
 
+/* The same in bf16 with the ranges' sums added up inside the launch, in ascending order: part is
+ * [1][m_pad][ldp] and has the bits of that sum.  x and the matrices 16-byte aligned, ldx a multiple of 8.
+ * tile_rows: the weight rows (192 or 256) of the tile that the launch takes. */
+int spec_k_gemm_folded(const void *x, int32_t ldx, int32_t m, int32_t in, const void *w0, int32_t rows0, const void *w1, int32_t rows1,
+                       const void *w2, int32_t rows2, float *part, int32_t ldp, int32_t m_pad, int32_t n_split, int32_t *tile_rows,
+                       void *stream);
+
 /* The tile (tokens x weight rows) that spec_k_gemm takes for m > 128 bf16 rows
  * and `blocks` 32-row weight blocks in all (host only; for tests). */
 int spec_k_gemm_tile(int32_t m, int32_t blocks, int32_t in, int32_t n_split, int32_t *tokens, int32_t *rows);

@@ -87,6 +87,8 @@ lib.spec_packed_gate_up_bytes.argtypes = [C.c_int32, C.c_int32, C.c_int32]
 lib.spec_pack_gate_up.argtypes = [C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
 lib.spec_k_gemm.argtypes = [C.c_int32, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p,
                             C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
+lib.spec_k_gemm_folded.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p,
+                                   C.c_int32, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.c_void_p]
 lib.spec_k_gemm_swiglu.argtypes = [C.c_int32, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]
 lib.spec_k_attention.argtypes = [C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                  C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]
@@ -282,6 +284,21 @@ def spec_k_gemm(x, ws: Sequence, n_split: int, m: Optional[int] = None):
     if rc:
         raise SpecError(rc, "spec_k_gemm")
     return part
+
+
+def spec_k_gemm_folded(x, ws: Sequence, n_split: int):
+    """x: torch bf16 [m, in]; ws as for spec_k_gemm.  Returns (fp32 torch [m, cols], weight rows of the launch's tile)."""
+    import torch
+    rows = [w.shape[0] for w in ws] + [0] * (3 - len(ws))
+    packed = [spec_pack_weight(w.contiguous()) for w in ws]
+    ptrs = [C.c_void_p(w.data_ptr()) for w in packed] + [None] * (3 - len(ws))
+    cols, m, tile = sum(rows), x.shape[0], C.c_int32()
+    part = torch.full((m, cols), float("nan"), dtype=torch.float32, device=x.device)
+    rc = lib.spec_k_gemm_folded(x.data_ptr(), x.stride(0), m, x.shape[1], ptrs[0], rows[0], ptrs[1], rows[1], ptrs[2], rows[2],
+                                part.data_ptr(), cols, m, n_split, C.byref(tile), _stream_ptr())
+    if rc:
+        raise SpecError(rc, "spec_k_gemm_folded")
+    return part, tile.value
 
 
 def spec_k_gemm_tile(m: int, blocks: int, k: int, n_split: int = 1):

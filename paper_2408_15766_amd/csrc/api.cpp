@@ -1116,9 +1116,9 @@ int spec_get_profile(spec_ctx *c, double *ms, int64_t *counts) {
 #include "../../include/spec_kernels.h"
 extern "C" {
 
-int spec_k_gemm(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in, const void *w0, int32_t rows0,
-                const void *w1, int32_t rows1, const void *w2, int32_t rows2, float *part, int32_t ldp, int32_t m_pad,
-                int32_t n_split, void *stream) {
+static int k_gemm(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in, const void *w0, int32_t rows0,
+                  const void *w1, int32_t rows1, const void *w2, int32_t rows2, float *part, int32_t ldp, int32_t m_pad,
+                  int32_t n_split, int32_t *fold_tile_rows, void *stream) {
   if (!x || !w0 || !part || rows0 < 1 || (dtype != 0 && dtype != 1)) return SPEC_EINVAL;
   const int epl = dtype == 1 ? 8 : 4;
   if (in < 1 || in % epl || ldx % epl || m < 1 || m > 4096 || m_pad < m) return SPEC_EINVAL;
@@ -1137,7 +1137,25 @@ int spec_k_gemm(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in
   }
   if (ldp < col) return SPEC_EINVAL;
   a.nseg = nseg; a.total_blocks = blocks; a.part = part; a.ldp = ldp; a.m_pad = m_pad; a.n_split = n_split;
+  if (fold_tile_rows) {
+    if (dtype != 1 || !gemm_can_fold(a)) return SPEC_EINVAL;
+    a.fold = 1;
+    *fold_tile_rows = gemm_fold_tile(m, blocks, in) == 1 ? 192 : 256;
+  }
   return launch_gemm(dtype, a, (hipStream_t)stream) == hipSuccess ? SPEC_OK : SPEC_EHIP;
+}
+
+int spec_k_gemm(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in, const void *w0, int32_t rows0,
+                const void *w1, int32_t rows1, const void *w2, int32_t rows2, float *part, int32_t ldp, int32_t m_pad,
+                int32_t n_split, void *stream) {
+  return k_gemm(dtype, x, ldx, m, in, w0, rows0, w1, rows1, w2, rows2, part, ldp, m_pad, n_split, nullptr, stream);
+}
+
+int spec_k_gemm_folded(const void *x, int32_t ldx, int32_t m, int32_t in, const void *w0, int32_t rows0, const void *w1, int32_t rows1,
+                       const void *w2, int32_t rows2, float *part, int32_t ldp, int32_t m_pad, int32_t n_split, int32_t *tile_rows,
+                       void *stream) {
+  if (!tile_rows) return SPEC_EINVAL;
+  return k_gemm(1, x, ldx, m, in, w0, rows0, w1, rows1, w2, rows2, part, ldp, m_pad, n_split, tile_rows, stream);
 }
 
 int spec_k_gemm_tile(int32_t m, int32_t blocks, int32_t in, int32_t n_split, int32_t *tokens, int32_t *rows) {

@@ -337,7 +337,7 @@ template <typename V> __device__ __forceinline__ V pinned(V v) { asm("" : "+s"(v
 
 // FOLD: the workgroup walks all K ranges of its tile one after the other (the copies run on across the borders) and adds up
 // the ranges' sums in registers, ((range 0 + range 1) + range 2) + .., the order in which the row kernels add partial sums: the
-// bits of n_split sets of partial sums with one set in memory.  Only the smallest tile leaves registers for a second set of sums.
+// bits of n_split sets of partial sums with one set in memory.  The 256 x 256 tile leaves no registers for a second set of sums; 256 x 192 just does.
 //
 // One tile: token rows from m0 on of the first or second set of rows, weight blocks from bx * kBlocks on, K range by.  xs, ws: the stage buffers.
 template <int TW, int TB, int WB, bool FOLD>
@@ -1089,8 +1089,18 @@ static hipError_t launch_mm_mixed(GemmArgs a, hipStream_t st) {
   hipLaunchKernelGGL(gemm_mm_mixed_kernel, dim3(8 * list), dim3(kMmThreads), 0, st, a);
   return hipGetLastError();
 }
+static float mm_xcd_us(int tile, int m, int blocks, int in, int ranges) {   // mm_us, with the rounds of the busiest XCD
+  const int tok = tile == 2 ? 128 : 256, wb = tile == 1 ? 6 : 8;
+  const float at4096 = tile == 0 ? 112.f : (tile == 1 ? 88.f : 64.f);
+  const int per_xcd = ((blocks + wb - 1) / wb * ranges + 7) / 8 * ((m + tok - 1) / tok);
+  return (float)((per_xcd + 31) / 32) * (at4096 * (float)in / (4096.f * (float)ranges) + 6.f);
+}
+// Tile of a folded launch: 256 x 192 or 128 x 256, whichever keeps the busiest XCD for less.  8B QKV of 2048 rows (6144 weight rows, K 4096): one
+// round of 256 workgroups instead of one and a half of 384: 136 us a launch in a request -> 96 alone (107 as two sets of sums); 1333 rows 75 (81), 70B QKV of
+// 1024 rows 170 (180).  A 4096-token prompt on 16 layers of the 8B widths 60.5 -> 59.6 ms a request, 1333 tokens on 8 layers 19.54 -> 19.30.
+int gemm_fold_tile(int m, int blocks, int in) { return mm_xcd_us(1, m, blocks, in, 1) < 0.97f * mm_xcd_us(2, m, blocks, in, 1) ? 1 : 2; }
 static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
-  if (a.fold) return launch_mm_tile<2, 2, 2, true>(a, st);
+  if (a.fold) return gemm_fold_tile(a.m, a.total_blocks, a.in) == 1 ? launch_mm_tile<4, 2, 3, true>(a, st) : launch_mm_tile<2, 2, 2, true>(a, st);
   switch (mm_tile(a.m, a.x2 ? 2 : 1, a.total_blocks, a.in, a.n_split)) {
     case 0: return launch_mm_mixed(a, st);
     case 1: return launch_mm_tile<4, 2, 3>(a, st);
@@ -1101,12 +1111,6 @@ static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
 // A set is written and read at about 8 TB/s (it stays in the memory-side cache).  us per layer of prefill, blocks -> fold: 7B shape, 1800 rows
 // 1152 -> 1087, 4096 2594 -> 2493; 8B 2048 1290 -> 1213; 70B 1024 2072 -> 1997.  The 13B shape keeps the blocks: folded tiles of its 5120
 // rows (20 per token tile) fall unevenly on the XCDs (1536 rows 1308 -> 1476 when folded), hence rounds by XCD.
-static float mm_xcd_us(int tile, int m, int blocks, int in, int ranges) {   // mm_us, with the rounds of the busiest XCD
-  const int tok = tile == 2 ? 128 : 256, wb = tile == 1 ? 6 : 8;
-  const float at4096 = tile == 0 ? 112.f : (tile == 1 ? 88.f : 64.f);
-  const int per_xcd = ((blocks + wb - 1) / wb * ranges + 7) / 8 * ((m + tok - 1) / tok);
-  return (float)((per_xcd + 31) / 32) * (at4096 * (float)in / (4096.f * (float)ranges) + 6.f);
-}
 bool gemm_fold_pays(int m, int rows, int in, int n_split, int block) {
   if (in >= (1 << 22) || rows >= (1 << 24)) return false;     // as mm_takes
   const int blocks = (rows + 31) / 32;
@@ -1116,7 +1120,7 @@ bool gemm_fold_pays(int m, int rows, int in, int n_split, int block) {
     const int n = std::min(block, m - r0);
     split_us += mm_xcd_us(mm_tile(n, 1, blocks, in, n_split), n, blocks, in, n_split);
   }
-  return mm_xcd_us(2, m, blocks, in, 1) + set_us < split_us;
+  return mm_xcd_us(gemm_fold_tile(m, blocks, in), m, blocks, in, 1) + set_us < split_us;
 }
 // Copies into the LDS need 16-byte aligned sources, and the kernel's offsets inside a tile are 32-bit.
 static bool mm_takes(const GemmArgs &a) {

@@ -58,6 +58,7 @@ struct GemmArgs {
 };
 hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st);
 bool gemm_can_fold(const GemmArgs &a);
+int gemm_fold_tile(int m, int blocks, int in);                // tile of a folded launch (1: 256 x 192, 2: 128 x 256)
 bool gemm_fold_pays(int m, int rows, int in, int n_split, int block);
 void gemm_mm_tile(int m, int sets, int blocks, int in, int n_split, int *tokens, int *rows);   // tile of a launch over more than 128 bf16 rows
 hipError_t gemm_init();                 // one-time kernel attributes; call outside any stream capture

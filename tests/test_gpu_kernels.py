@@ -271,6 +271,27 @@ def test_gemm_whole_and_half_tiles_match_fp64_and_single_rows(env, m, k, rows):
         assert torch.equal(P.spec_k_gemm_swiglu(x[i:i + 1].contiguous(), gate, up)[0], act[i])
 
 
+# m, k, weight rows of the segments, splits, weight rows of the tile: one round of 256 x 192 where 128 x 256 takes two (the 8B QKV projection, whole
+# and ragged, K ranges of unequal length among them), and shapes on the other side of the rule
+FOLDED = [(2048, 4096, (4096, 1024, 1024), 2, 192), (1999, 1288, (4096, 900, 1022), 2, 192), (1333, 2064, (4100, 1024, 1022), 3, 192),
+          (1025, 1032, (7600, 1024), 2, 192), (2048, 2056, (4096,), 4, 256), (300, 776, (700,), 3, 256), (129, 520, (40,), 2, 256)]
+
+
+@pytest.mark.parametrize("m,k,rows,n_split,tile", FOLDED)
+def test_gemm_folded_ranges_have_the_bits_of_the_split_sums(env, m, k, rows, n_split, tile):
+    torch, P = env
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed("fold", m, k) & 0xFFFF)
+    x = torch.randn(m, k, device="cuda", generator=g).to(torch.bfloat16)
+    ws = [(torch.randn(r, k, device="cuda", generator=g) * 0.05).to(torch.bfloat16) for r in rows]
+    got, tile_rows = P.spec_k_gemm_folded(x, ws, n_split)
+    assert tile_rows == tile
+    part = P.spec_k_gemm(x, ws, n_split)
+    want = part[0]
+    for s in range(1, n_split):
+        want = want + part[s]
+    assert torch.equal(got, want)
+
+
 def make_tree(rng, rows, max_depth):
     par = np.full(rows, -1, np.int32)
     dep = np.zeros(rows, np.int32)
