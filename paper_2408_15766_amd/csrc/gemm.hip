@@ -130,11 +130,12 @@ __device__ __forceinline__ int slab_begin(const GemmArgs &a, int y) {
 }
 
 // PAIR: a second set of m rows (x2 -> part2) follows the first as rows m .. 2m-1 of the token tile.
-template <typename T, int TB, bool PAIR>
-__global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) void gemm_stream_kernel(GemmArgs a) {
+template <typename T, int TB, bool PAIR, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && kStages <= 3) ? 2 : 1) void gemm_stream_kernel(GemmArgs a) {
+  constexpr int kThreads = WAVES * kWave;
   constexpr int EPL = GemmTraits<T>::kEpl;
   constexpr int KI = 2 * kLaneBytes / (int)sizeof(T);         // k elements per iteration
-  constexpr int XCH = TB * 32 * (kSlabRowBytes / 16) / kGemmThreads;   // 16-byte X chunks per thread per slab
+  constexpr int XCH = TB * 32 * (kSlabRowBytes / 16) / kThreads;   // 16-byte X chunks per thread per slab
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int kSlabBytes = TB * 32 * kSlabStride;
 
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
     const int k0 = k_begin + slab * kSlabIters * KI;
 #pragma unroll
     for (int i = 0; i < XCH; i++) {
-      const int q = tid + i * kGemmThreads;
+      const int q = tid + i * kThreads;
       const int r = q / (kSlabRowBytes / 16), cc = q % (kSlabRowBytes / 16);
       const int kk = k0 + cc * EPL;
       const bool second = PAIR && r >= a.m && r < m_loc;
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(kGemmThreads, (TB <= 2 && kStages <= 3) ? 2 : 1) vo
   auto store_x = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < XCH; i++) {
-      const int q = tid + i * kGemmThreads;
+      const int q = tid + i * kThreads;
       const int r = q / (kSlabRowBytes / 16), cc = q % (kSlabRowBytes / 16);
       *(u32x4_t *)(lds + buf * kSlabBytes + r * kSlabStride + cc * 16) = xr[i];
     }
@@ -1013,8 +1014,10 @@ hipError_t launch_pack_weight(int dtype, const void *src, int rows, int in, void
 template <int TB>
 static hipError_t init_tb() {
   const int lds = 2 * TB * 32 * kSlabStride;
-  hipError_t e = hipFuncSetAttribute((const void *)gemm_stream_kernel<bf16_t, TB, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_stream_kernel<bf16_t, TB, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipError_t e = hipSuccess;
+  for (const void *f : {(const void *)gemm_stream_kernel<bf16_t, TB, false, kGemmWaves>, (const void *)gemm_stream_kernel<bf16_t, TB, true, kGemmWaves>,
+                        (const void *)gemm_stream_kernel<bf16_t, TB, false, 8>, (const void *)gemm_stream_kernel<bf16_t, TB, true, 8>})
+    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   return e;
 }
 hipError_t gemm_init() {
@@ -1134,6 +1137,15 @@ static bool mm_takes(const GemmArgs &a) {
 
 bool gemm_can_fold(const GemmArgs &a) { return a.act == nullptr && a.x2 == nullptr && mm_takes(a); }
 
+template <int TB, bool PAIR>
+static hipError_t launch_stream_tb(const GemmArgs &a, int waves, hipStream_t st) {
+  constexpr size_t lds = (size_t)2 * TB * 32 * kSlabStride;
+  static_assert(lds <= 160 * 1024, "the token blocks fit the LDS");
+  const dim3 grid(a.grid_x, a.n_split), threads(waves * kWave);
+  if (waves == 8) hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, TB, PAIR, 8>), grid, threads, lds, st, a);
+  else hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, TB, PAIR, kGemmWaves>), grid, threads, lds, st, a);
+  return hipGetLastError();
+}
 template <bool PAIR>
 static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
   const int tb = ((PAIR ? 2 * a.m : a.m) + 31) / 32;
@@ -1142,30 +1154,39 @@ static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
   // units idle (7B gate/up: 688 blocks = 172 workgroups); if the blocks fit in three, two or one per workgroup on at
   // most 256 workgroups (all splits together), the launch takes that form: wave w streams block x + w * grid_x and
   // the waves left without a block only help to stage the X slab (7B gate/up 36.1 -> 33.6 us, O 10.8 -> 10.0, down with
-  // 4 splits 24.3 -> 20.3).  Otherwise four adjacent blocks per workgroup: spreading without lowering the largest count
+  // 4 splits 24.3 -> 20.3).  Otherwise four (or eight, below) adjacent blocks per workgroup: spreading without lowering the largest count
   // measured 1 - 4 % slower at the 13B shapes.
-  {
-    const int cap = std::max(1, 256 / a.n_split);
-    const int per_wg = (a.total_blocks + cap - 1) / cap;
-    if (per_wg < kGemmWaves) {
-      a.grid_x = (a.total_blocks + per_wg - 1) / per_wg;
-      a.blk_per_wg = 1; a.blk_per_wave = a.grid_x;
-    } else {
-      a.grid_x = (a.total_blocks + kGemmWaves - 1) / kGemmWaves;
-      a.blk_per_wg = kGemmWaves; a.blk_per_wave = 1;
-    }
+  const int cap = std::max(1, 256 / a.n_split);
+  const int per_wg = (a.total_blocks + cap - 1) / cap;
+  // Eight wavefronts share one X slab where that is worth it (the same sums in the same order):
+  //  * five to eight blocks per compute unit, any number of rows: one round of one workgroup each instead of a second, partly filled one of
+  //    workgroups of four.  Gate/up of 60 rows, K 4096, 1100 blocks 67.8 -> 50.2 us, 1500 73.8 -> 63.2, 2000 84.8 -> 82.3; K 8192, 1792 (70B) 152.7 -> 144.1,
+  //    ten rows 138.2 -> 136.5; 100 rows, 1500 blocks 96.7 -> 78.3;
+  //  * four on most compute units, up to 32 rows and K ranges up to 4096: four of the waves only stage, and the slab is there sooner.  1000 blocks,
+  //    K 4096, ten rows (7B LM head of the draft) 44.3 -> 41.7, 896 39.0 -> 37.5, 26 rows 40.0 -> 39.9; shorter ranges gain 6 to 9 %.  780 blocks 34.0 ->
+  //    35.7 (26 rows), K 5120 47.9 -> 49.3, 60 rows 41.3 -> 44.0;
+  //  * more than eight, more than 64 rows (a workgroup of four then has a compute unit to itself) and no more rounds x blocks: 100 rows, 4008 blocks 222 ->
+  //    193 (K 8192 434 -> 383; loss of 60 positions at that vocabulary 249 -> 219); 2300 144 -> 150, where two rounds of eight take the place of three of four.  Up to 64 rows two workgroups of four
+  //    share a compute unit: K 8192, 4008 blocks 335 -> 339 and 313 -> 324.
+  const int units = a.total_blocks * a.n_split;
+  const bool round8 = per_wg > kGemmWaves && per_wg <= 8;
+  const bool stage8 = per_wg == kGemmWaves && tb == 1 && units >= 896 && (long long)a.in <= 4096ll * a.n_split;
+  const bool slab8 = per_wg > 8 && tb >= 3 && 2 * ((per_wg + 7) / 8) <= (per_wg + 3) / 4;
+  const int waves = round8 || stage8 || slab8 ? 8 : kGemmWaves;
+  if (per_wg < waves) {
+    a.grid_x = (a.total_blocks + per_wg - 1) / per_wg;
+    a.blk_per_wg = 1; a.blk_per_wave = a.grid_x;
+  } else {
+    a.grid_x = (a.total_blocks + waves - 1) / waves;
+    a.blk_per_wg = waves; a.blk_per_wave = 1;
   }
-  const dim3 grid(a.grid_x, a.n_split);
-  const size_t lds = (size_t)2 * tb * 32 * kSlabStride;
-  static_assert((size_t)2 * 4 * 32 * kSlabStride <= 160 * 1024, "four token blocks fit the LDS");
   switch (tb) {
-    case 1: hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, 1, PAIR>), grid, dim3(kGemmThreads), lds, st, a); break;
-    case 2: hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, 2, PAIR>), grid, dim3(kGemmThreads), lds, st, a); break;
-    case 3: hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, 3, PAIR>), grid, dim3(kGemmThreads), lds, st, a); break;
-    case 4: hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, 4, PAIR>), grid, dim3(kGemmThreads), lds, st, a); break;
+    case 1: return launch_stream_tb<1, PAIR>(a, waves, st);
+    case 2: return launch_stream_tb<2, PAIR>(a, waves, st);
+    case 3: return launch_stream_tb<3, PAIR>(a, waves, st);
+    case 4: return launch_stream_tb<4, PAIR>(a, waves, st);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 // Up to 128 rows in all the launch is bound by the weights, read once; a pair of row sets shares that one pass.

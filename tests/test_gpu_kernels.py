@@ -271,6 +271,34 @@ def test_gemm_whole_and_half_tiles_match_fp64_and_single_rows(env, m, k, rows):
         assert torch.equal(P.spec_k_gemm_swiglu(x[i:i + 1].contiguous(), gate, up)[0], act[i])
 
 
+# m, k, weight rows, splits: workgroups of eight wavefronts with five to eight blocks spread over the compute units (the last wave of some without a block),
+# with four blocks and few rows, and with eight adjacent ones; each beside the nearest size that keeps workgroups of four
+WIDE_WGS = [(1, 264, 32790, 1), (33, 520, 41270, 1), (60, 264, 65500, 1), (100, 264, 57330, 1), (128, 136, 65540, 1), (65, 264, 128256, 1), (64, 264, 128256, 1),
+            (32, 1032, 28672, 1), (33, 1032, 28672, 1), (10, 1032, 28640, 1), (7, 2056, 14500, 2), (40, 2056, 20500, 2)]
+
+
+@pytest.mark.parametrize("m,k,rows,n_split", WIDE_WGS)
+def test_gemm_streams_of_eight_wavefronts_match_fp64_and_single_rows(env, m, k, rows, n_split):
+    """Against fp64 (fp32 sums of k terms of size 0.05), and every row has the bits it has beside others; SwiGLU over as many blocks likewise."""
+    torch, P = env
+    g = torch.Generator(device="cuda"); g.manual_seed(case_seed("wide", m, rows) & 0xFFFF)
+    x = torch.randn(m, k, device="cuda", generator=g).to(torch.bfloat16)
+    w = (torch.randn(rows, k, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    got = P.spec_k_gemm(x, [w], n_split)
+    want = x.double() @ w.double().t()
+    assert (got.double().sum(0) - want).abs().max() <= 1e-6 * np.sqrt(k) * max(1.0, float(want.abs().max()))
+    gate, up = w[:rows // 2], w[rows // 2:rows // 2 * 2]
+    act = P.spec_k_gemm_swiglu(x, gate, up)
+    gd, ud = want[:, :rows // 2], want[:, rows // 2:rows // 2 * 2]
+    ref = gd * torch.sigmoid(gd) * ud
+    assert ((act.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * np.sqrt(k)).all()
+    small = w[:4096].contiguous()                             # few blocks: workgroups of four wavefronts
+    assert torch.equal(P.spec_k_gemm(x, [small], n_split), got[:, :, :4096])
+    for i in sorted({0, m // 2, m - 1}):
+        assert torch.equal(P.spec_k_gemm(x[i:i + 1].contiguous(), [w], n_split)[:, 0], got[:, i])
+        assert torch.equal(P.spec_k_gemm_swiglu(x[i:i + 1].contiguous(), gate, up)[0], act[i])
+
+
 # m, k, weight rows of the segments, splits, weight rows of the tile: one round of 256 x 192 where 128 x 256 takes two (the 8B QKV projection, whole
 # and ragged, K ranges of unequal length among them), and shapes on the other side of the rule
 FOLDED = [(2048, 4096, (4096, 1024, 1024), 2, 192), (1999, 1288, (4096, 900, 1022), 2, 192), (1333, 2064, (4100, 1024, 1022), 3, 192),
