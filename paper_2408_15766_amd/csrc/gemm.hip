@@ -187,12 +187,12 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
   // nothing forces a wait between a load and its use two iterations later.  X never needs
   // zeroing either: out-of-range X addresses are clamped to valid finite data that meets a zero
   // weight or a token row that is never stored.
-  auto load_w = [&](u32x4_t (&dst)[8], int it) {
+  auto load_w = [&](u32x4_t (&dst)[8], int it) __attribute__((always_inline)) {
     const char *p = wstream + (size_t)it * kTileBytes;
 #pragma unroll
     for (int j = 0; j < 8; j++) dst[j] = __builtin_nontemporal_load((const u32x4_t *)(p + j * 1024));   // read once: do not keep in cache
   };
-  auto load_x = [&](int slab) {
+  auto load_x = [&](int slab) __attribute__((always_inline)) {
     const int k0 = k_begin + slab * kSlabIters * KI;
 #pragma unroll
     for (int i = 0; i < XCH; i++) {
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
       xr[i] = *(const u32x4_t *)(xbase + ((size_t)(r < m_loc ? (second ? r - a.m : r) : 0) * a.ldx + (kk < a.in ? kk : 0)) * sizeof(T));
     }
   };
-  auto store_x = [&](int buf) {
+  auto store_x = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < XCH; i++) {
       const int q = tid + i * kThreads;
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
       *(u32x4_t *)(lds + buf * kSlabBytes + r * kSlabStride + cc * 16) = xr[i];
     }
   };
-  auto compute = [&](const u32x4_t (&w)[8], int buf, int ii) {
+  auto compute = [&](const u32x4_t (&w)[8], int buf, int ii) __attribute__((always_inline)) {
     const unsigned char *base = lds + buf * kSlabBytes + c * kSlabStride + ii * (2 * kLaneBytes) + g * kLaneBytes;
 #pragma unroll
     for (int j = 0; j < 8; j++) {
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
   // (P = slab index mod kPeriod).  Steady state (FAST): every load of the slab is a full, in-range
   // iteration and a next slab exists, so the body has no branch and the compiler keeps exact
   // outstanding-load counts; the remaining slabs take the guarded form.
-  auto slab = [&](auto p_tag, auto fast_tag, int S) {
+  auto slab = [&](auto p_tag, auto fast_tag, int S) __attribute__((always_inline)) {
     constexpr int P = decltype(p_tag)::value;
     constexpr bool FAST = decltype(fast_tag)::value;
     if (!FAST && S >= n_slab) return;
@@ -254,18 +254,43 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
       if (FAST || it < n_iter_w) compute(ring[st_use], buf, ii);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (more) store_x(buf ^ 1);
-    __syncthreads();
+    if (more) {
+      store_x(buf ^ 1);
+      __syncthreads();
+    }
   };
-  constexpr int kPeriod = kStages / gcd_ce(kStages, kSlabIters);
-  auto period = [&](auto fast_tag, int S0) {
-    static_for<kPeriod>([&](auto p_tag) { slab(p_tag, fast_tag, S0 + decltype(p_tag)::value); });
+  constexpr int kPeriod = kStages / gcd_ce(kStages, kSlabIters), kTail = (kStages + kSlabIters - 2) / kSlabIters + 1;
+  auto period = [&](auto fast_tag, int S0) __attribute__((always_inline)) {
+    static_for<kPeriod>([&](auto p_tag) __attribute__((always_inline)) { slab(p_tag, fast_tag, S0 + decltype(p_tag)::value); });
   };
-  // slabs S whose last prefetch, iteration S*kSlabIters + kSlabIters - 1 + kStages - 1, is in range
+  // slabs S whose last prefetch, iteration S*kSlabIters + kSlabIters - 1 + kStages - 1, is in range: all but the last one or two
   const int n_steady = n_iter_w >= kSlabIters + kStages - 1 ? (n_iter_w - kStages + 1) / kSlabIters : 0;
   int s = 0;
   for (; s + kPeriod <= n_steady; s += kPeriod) period(std::true_type{}, s);
-  for (; s < n_slab; s += kPeriod) period(std::false_type{}, s);
+  if constexpr (TB <= (PAIR ? 1 : 2)) {
+    // The steady slabs left over run FAST too: in the guarded form the waits count on the loads that a branch may have left out, so
+    // a slab there waits for what it has just requested, up to three times a stream.  7B down of 60 rows 20.2 -> 19.3 us, of ten 17.2 -> 16.1, 8B down 25.6 ->
+    // 24.1, 13B O 14.3 -> 13.9, 7B QKV of ten rows 18.6 -> 18.0.  (More rows leave too few registers: 100 rows -8 to +4 %, pairs of sets spill, 60 positions of a loss 219 -> 251.)
+    if (n_iter_w == 0)                                        // no block: only help to stage
+      for (int S = 0; S + 1 < n_slab; S++) {
+        load_x(S + 1);
+        store_x((S & 1) ^ 1);
+        __syncthreads();
+      }
+    else
+      static_for<kPeriod>([&](auto r_tag) __attribute__((always_inline)) {   // R steady slabs are left
+        constexpr int R = decltype(r_tag)::value;
+        if (n_steady - s != R) return;
+        static_for<R>([&](auto p_tag) __attribute__((always_inline)) { slab(p_tag, std::true_type{}, s + decltype(p_tag)::value); });
+        static_for<kTail>([&](auto t_tag) __attribute__((always_inline)) {
+          constexpr int Q = R + decltype(t_tag)::value;
+          slab(std::integral_constant<int, Q % kPeriod>{}, std::false_type{}, s + Q);
+        });
+        s = n_slab + kPeriod;                                 // done: matches no other R
+      });
+  } else {
+    for (; s < n_slab; s += kPeriod) period(std::false_type{}, s);
+  }
 
   if (swiglu) {
     const int col = blk * 16 + (c & 15);

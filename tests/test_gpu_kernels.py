@@ -277,8 +277,12 @@ WIDE_WGS = [(1, 264, 32790, 1), (33, 520, 41270, 1), (60, 264, 65500, 1), (100, 
             (32, 1032, 28672, 1), (33, 1032, 28672, 1), (10, 1032, 28640, 1), (7, 2056, 14500, 2), (40, 2056, 20500, 2)]
 
 
-@pytest.mark.parametrize("m,k,rows,n_split", WIDE_WGS)
-def test_gemm_streams_of_eight_wavefronts_match_fp64_and_single_rows(env, m, k, rows, n_split):
+# every count of 256-k slabs around the period of three: whole, and with one 128-k tile in the last slab; waves without a block; 1, 2 and 4 token blocks
+STREAM_K = [(m, 256 * slabs - cut, 70 if slabs % 2 else 33000, 1) for m in (9, 60, 100) for slabs in range(1, 9) for cut in (0, 136)]
+
+
+@pytest.mark.parametrize("m,k,rows,n_split", WIDE_WGS + STREAM_K)
+def test_gemm_streams_match_fp64_and_single_rows(env, m, k, rows, n_split):
     """Against fp64 (fp32 sums of k terms of size 0.05), and every row has the bits it has beside others; SwiGLU over as many blocks likewise."""
     torch, P = env
     g = torch.Generator(device="cuda"); g.manual_seed(case_seed("wide", m, rows) & 0xFFFF)
@@ -292,8 +296,8 @@ def test_gemm_streams_of_eight_wavefronts_match_fp64_and_single_rows(env, m, k, 
     gd, ud = want[:, :rows // 2], want[:, rows // 2:rows // 2 * 2]
     ref = gd * torch.sigmoid(gd) * ud
     assert ((act.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * np.sqrt(k)).all()
-    small = w[:4096].contiguous()                             # few blocks: workgroups of four wavefronts
-    assert torch.equal(P.spec_k_gemm(x, [small], n_split), got[:, :, :4096])
+    few = min(rows, 4096)                                     # few blocks: workgroups of four wavefronts
+    assert torch.equal(P.spec_k_gemm(x, [w[:few].contiguous()], n_split), got[:, :, :few])
     for i in sorted({0, m // 2, m - 1}):
         assert torch.equal(P.spec_k_gemm(x[i:i + 1].contiguous(), [w], n_split)[:, 0], got[:, i])
         assert torch.equal(P.spec_k_gemm_swiglu(x[i:i + 1].contiguous(), gate, up)[0], act[i])
