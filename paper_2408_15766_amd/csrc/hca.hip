@@ -15,8 +15,8 @@
 // own sums and meet once, at the end).
 // Bound: the serial chain of a block inside a wavefront (LDS reads, matrix instructions, maximum, exponentials), with two
 // wavefronts per SIMD to cover each other; a wavefront's share of the staging is part of it and halves with 8 wavefronts.
-// Measured (MI355X, us, launches back to back): batch 2 x 2048, 32 heads of 128, three streams 115.7 -> 102 with 8
-// wavefronts -> 98 with the band behind the loop; with 4: batch 2 x 1024 45.3 -> 43.3 (value rows read whole 1.5 of it, the maximum without a shuffle
+// Measured (MI355X, us, launches back to back over one set of inputs): batch 2 x 2048, 32 heads of 128, three streams 115.7 -> 102 with 8
+// wavefronts -> 98 with the band behind the loop (inputs from HBM: 114 both ways); with 4: batch 2 x 1024 45.3 -> 43.3 (value rows read whole 1.5 of it, the maximum without a shuffle
 // 0.3) -> 38.0.  Short launches (333 positions, 16 heads of 64: 9.8) are bound by launch and latency and did not change.
 // Tried: scores of the next block under the exponentials of this one, with keys and values copied straight into the LDS and transposed by the
 // read (ds_read_b64_tr_b16): 84 -> 90 with one stream; without the exponentials that form would take 67, so the matrix cores' power limit is near.
