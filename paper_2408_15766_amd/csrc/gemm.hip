@@ -26,8 +26,8 @@
 // contiguous, which is harmless because A and B are indexed by the same (g, element) pair.
 //
 // Each wave owns one 32-row block of W for the workgroup's K range and all
-// token blocks; the four waves of a workgroup share the X slab.  Which blocks a
-// workgroup takes is the launch's choice (four adjacent ones, or fewer, spread so
+// token blocks; the four or eight waves of a workgroup share the X slab.  Which blocks a
+// workgroup takes is the launch's choice (adjacent ones, or fewer than it has waves, spread so
 // that every compute unit has a workgroup: launch_stream).  Weight loads
 // run kStages - 1 iterations ahead through a register ring; the X slab is
 // double-buffered in LDS and prefetched one slab ahead through registers.
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
   // form one period of the stage pattern and are unrolled with compile-time stage indices
   // (P = slab index mod kPeriod).  Steady state (FAST): every load of the slab is a full, in-range
   // iteration and a next slab exists, so the body has no branch and the compiler keeps exact
-  // outstanding-load counts; the remaining slabs take the guarded form.
+  // outstanding-load counts; the last slabs of a stream take the guarded form.
   auto slab = [&](auto p_tag, auto fast_tag, int S) __attribute__((always_inline)) {
     constexpr int P = decltype(p_tag)::value;
     constexpr bool FAST = decltype(fast_tag)::value;
