@@ -76,14 +76,6 @@ __device__ __forceinline__ void put_candidate(float *out, int pos, uint64_t key,
   out[8 + 3 * pos + 2] = key ? zp : 0.f;
 }
 
-// exp(x) for x <= 0 (and -inf -> 0, NaN -> NaN): 2^p for the rounded product p = x * log2(e), times 1 + the remainder x - p * ln 2.
-// Relative error: that of the exponential unit and |p| * 2e-9; results below 2^-126 are 0.  expf() scales for those and
-// checks both ends of its range: 14 instructions against 6, two thirds of the slices' vector instructions.
-__device__ __forceinline__ float exp_nonpos(float x) {
-  const float p = x * 1.44269504f, r = __builtin_amdgcn_exp2f(p);
-  return fmaf(r, fmaxf(fmaf(p, -0.693147182f, x), -1.f), r);  // the maximum takes the remainder of -inf, a NaN, to -1: r = 0
-}
-
 constexpr int kWaveCand = 128;                               // places for a wavefront's tokens at or above the bound
 struct SliceShared {
   float red_max[kLossWaves][2], red_sum[kLossWaves][4];
@@ -99,9 +91,12 @@ struct SliceShared {
 // Bound: vector instructions, then the logits' way from the last-level cache (eight 16-byte loads per thread in flight).
 // The candidates are found by comparing logits with a bound (one instruction a token; keys are built for those that pass), and
 // their places by the masks of these comparisons, most of which are empty; each wavefront lists its own, so one barrier
-// stands between finding and choosing.  512 positions, vocabulary 32000, K = 10, between two LM-head products: with
-// expf(), a key for every token and the places counted over the workgroup first 37.9 us, now 30.5 (the reads and maxima
-// alone 20.6); 188 positions, vocabulary 128256, K = 100: 69 -> 50.
+// stands between finding and choosing.  512 positions, vocabulary 32000, K = 10, between two LM-head products: with a key for every
+// token and the places counted over the workgroup first 37.9 us, now 35.8 (the reads and maxima alone 20.6); 188 positions,
+// vocabulary 128256, K = 100: 69 -> 54.5.
+// The exponentials are expf()'s, two thirds of the vector instructions.  2^(x * log2 e) with one correction takes 30.5 us, but errs by up to
+// 3.9 units of the last place where expf() errs by 0.86 (all arguments from -104 to 0), and has no value below 2^-126 nor for
+// differences that overflow when scaled; a form as exact as expf(), with one reduction of the argument and no range checks, takes 34.6.
 template <bool EDGE>
 __device__ __forceinline__ void loss_slice(const float *rq, const float *rp, int ldz, int vocab, int k, int c0, float *out, SliceShared &sh) {
   constexpr int PER = kTopkSlice / kLossThreads;   // 16
@@ -154,9 +149,9 @@ __device__ __forceinline__ void loss_slice(const float *rq, const float *rp, int
   float sq = 0.f, sp = 0.f, cross = 0.f;
 #pragma unroll
   for (int e = 0; e < PER; e++) {
-    const float wq = exp_nonpos(vq[e] - mq);                 // 0 for padding
+    const float wq = expf(vq[e] - mq);                 // 0 for padding
     sq += wq;
-    sp += exp_nonpos(vp[e] - mp);
+    sp += expf(vp[e] - mp);
     cross = inside(e) ? fmaf(wq, vp[e], cross) : cross;
   }
   sq = wave_sum(sq);

@@ -190,6 +190,37 @@ def test_infinite_and_nan_logits(env):
         np.testing.assert_array_equal(g[[0, 2, 4]], c[[0, 2, 4]])
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("side", ["target", "both"])
+def test_tokens_ruled_out_by_the_lowest_value(env, dtype, side):
+    # a column of the LM head takes every third token to the type's lowest value, on the target's side or on both: finite
+    # differences that overflow when scaled, tokens without weight, finite losses
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(32, 6, 128, 9000, dtype)
+    lowest = float(torch.finfo(torch.float32 if dtype == "fp32" else torch.bfloat16).min)
+    ft[:, 0], fd[:, 0] = 1.0, 1.0 if side == "both" else 0.0
+    w[:, 0] = np.where(np.arange(9000) % 3 == 0, lowest, 0.0)
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 20, dtype)
+    want, alt, want_ce = oracle_losses(ft, fd, w, 20)
+    check(got_topk, got_ce, want, alt, want_ce)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_draft_rules_tokens_out_by_the_lowest_value(env, dtype):
+    # three tokens that the target gives about 1e-13 of its best token's weight: the whole-vocabulary loss is that weight times
+    # 3.4e38 there, the top-K loss does not see them
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(33, 6, 128, 9000, dtype)
+    tok = [17, 4095, 8191]
+    ft[:, 0], fd[:, 0], ft[:, 1], fd[:, 1] = 0.0, 1.0, 1.0, 0.0
+    w[:, 0] = w[:, 1] = 0.0
+    w[tok, 0] = float(torch.finfo(torch.float32 if dtype == "fp32" else torch.bfloat16).min)
+    w[tok, 1] = -30.0
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 20, dtype)
+    want, alt, want_ce = oracle_losses(ft, fd, w, 20)
+    check(got_topk, got_ce, want, alt, want_ce)
+
+
 @pytest.mark.parametrize("rows,vocab,k", [(1100, 32000, 128), (1537, 4096, 3), (600, 128256, 40)])
 def test_one_merge_for_several_chunks(env, rows, vocab, k):
     # two chunks' slices merged at a time, then a ragged rest; all four in one merge; one chunk a merge.  A scratch with room
