@@ -147,11 +147,12 @@ __device__ __forceinline__ void loss_slice(const float *rq, const float *rp, int
     if (lane == 0) tau_s = tau ? key_value(tau) : -INFINITY;  // fewer than k threads with tokens: every token passes
   }
   float sq = 0.f, sp = 0.f, cross = 0.f;
+  const float q0 = mq == -INFINITY ? 0.f : mq, p0 = mp == -INFINITY ? 0.f : mp;   // a slice without any probability adds zeros
 #pragma unroll
   for (int e = 0; e < PER; e++) {
-    const float wq = expf(vq[e] - mq);                 // 0 for padding
+    const float wq = expf(vq[e] - q0);                       // 0 for padding
     sq += wq;
-    sp += expf(vp[e] - mp);
+    sp += expf(vp[e] - p0);
     cross = inside(e) ? fmaf(wq, vp[e], cross) : cross;
   }
   sq = wave_sum(sq);

@@ -190,6 +190,28 @@ def test_infinite_and_nan_logits(env):
         np.testing.assert_array_equal(g[[0, 2, 4]], c[[0, 2, 4]])
 
 
+@pytest.mark.parametrize("lo,hi", [(0, 4096), (4096, 8192), (8192, 9000)])
+def test_slices_without_any_probability(env, lo, hi):
+    # all logits of a 4096-token slice -inf: on the target's side (the product overflows) they have no weight; on both sides the top-K loss
+    # is the remaining tokens', and the whole-vocabulary term is 0 * inf
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(34, 5, 128, 9000, "fp32")
+    keep = np.ones(9000, bool)
+    keep[lo:hi] = False
+    ft[:, 0] = fd[:, 0] = 0.0
+    zq, zp = ft.astype(np.float64) @ w.astype(np.float64).T, fd.astype(np.float64) @ w.astype(np.float64).T
+    zq[:, ~keep] = -np.inf
+    ft[:, 0] = 2.0
+    w[:, 0] = np.where(keep, 0.0, -3e38)
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 20, "fp32")
+    want = distill.topk_distill_loss(zq, zp, 20)
+    check(got_topk, got_ce, want, want, distill.soft_cross_entropy(zq, zp))
+    fd[:, 0] = 2.0
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 20, "fp32")
+    np.testing.assert_allclose(got_topk, distill.topk_distill_loss(zq[:, keep], zp[:, keep], 20), **TOL)
+    assert np.isnan(got_ce).all()
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("side", ["target", "both"])
 def test_tokens_ruled_out_by_the_lowest_value(env, dtype, side):
