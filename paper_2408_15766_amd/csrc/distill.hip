@@ -30,6 +30,10 @@ namespace {
 constexpr int kLossThreads = 256;
 constexpr int kLossWaves = kLossThreads / 64;
 
+// The cross terms are summed at this scale: 4096 draft logits at the type's lowest value (a mask) would overflow, and with them slices whose
+// weight among the others is 0.
+constexpr float kCrossScale = 0x1p-32f;
+
 // scratch per (position, slice): 5 floats of statistics, then K (target logit, token, draft logit) triples
 __host__ __device__ inline size_t slice_floats(int k) { return 8 + 3 * (size_t)k; }
 
@@ -154,6 +158,12 @@ __device__ __forceinline__ void loss_slice(const float *rq, const float *rp, int
     sq += wq;
     sp += expf(vp[e] - p0);
     cross = inside(e) ? fmaf(wq, vp[e], cross) : cross;
+  }
+  cross = cross * kCrossScale;
+  if (__any(!(fabsf(cross) < INFINITY))) {                   // (also a NaN, which stays one)
+    cross = 0.f;
+#pragma unroll
+    for (int e = 0; e < PER; e++) cross = inside(e) ? fmaf(expf(vq[e] - q0) * kCrossScale, vp[e], cross) : cross;
   }
   sq = wave_sum(sq);
   sp = wave_sum(sp);
@@ -294,7 +304,7 @@ __global__ __launch_bounds__(WAVES * 64) void loss_merge_kernel(int k, int n_sli
       sp += wave_sum(in ? s[3] * expf(s[2] - mp) : 0.f);
       cr += wave_sum(in ? s[4] * fq : 0.f);
     }
-    if (t == 0) { sh[0] = mq + logf(sq); sh[1] = mp + logf(sp); sh[2] = cr / sq; }
+    if (t == 0) { sh[0] = mq + logf(sq); sh[1] = mp + logf(sp); sh[2] = cr / sq * (1.f / kCrossScale); }
   }
   int turn = 0;
   const uint64_t thr = kth_key(k, [&](uint64_t x) { return block_total<WAVES>(wave_count(key, x), cnt, turn); });

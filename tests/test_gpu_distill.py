@@ -227,6 +227,21 @@ def test_tokens_ruled_out_by_the_lowest_value(env, dtype, side):
     check(got_topk, got_ce, want, alt, want_ce)
 
 
+@pytest.mark.parametrize("lo,hi", [(0, 4096), (4096, 8192), (8192, 9000)])
+@pytest.mark.parametrize("dtype,side", [("fp32", "target"), ("bf16", "target"), ("fp32", "draft"), ("bf16", "draft"), ("fp32", "both"), ("bf16", "both")])
+def test_slices_ruled_out_by_the_lowest_value(env, dtype, side, lo, hi):
+    # a whole 4096-token slice, or the ragged one: its 4096 draft logits add up to more than the type holds.  On the draft's side alone the
+    # losses are the slice's target weight times 3.4e38
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(35, 6, 128, 9000, dtype)
+    ft[:, 0], fd[:, 0] = float(side != "draft"), float(side != "target")
+    w[:, 0] = 0.0
+    w[lo:hi, 0] = float(torch.finfo(torch.float32 if dtype == "fp32" else torch.bfloat16).min)
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 20, dtype)
+    want, alt, want_ce = oracle_losses(ft, fd, w, 20)
+    check(got_topk, got_ce, want, alt, want_ce)
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_draft_rules_tokens_out_by_the_lowest_value(env, dtype):
     # three tokens that the target gives about 1e-13 of its best token's weight: the whole-vocabulary loss is that weight times
