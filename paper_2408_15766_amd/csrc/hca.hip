@@ -16,7 +16,7 @@
 // Bound: the serial chain of a block inside a wavefront (LDS reads, matrix instructions, maximum, exponentials), with two
 // wavefronts per SIMD to cover each other; a wavefront's share of the staging is part of it and halves with 8 wavefronts.
 // Measured (MI355X, us, launches back to back over one set of inputs): batch 2 x 2048, 32 heads of 128, three streams 115.7 -> 102 with 8
-// wavefronts -> 98 with the band behind the loop (inputs from HBM: 114 both ways); with 4: batch 2 x 1024 45.3 -> 43.3 (value rows read whole 1.5 of it, the maximum without a shuffle
+// wavefronts -> 98 with the band behind the loop (inputs from HBM: 113 both ways, 110 with its first rows asked for ahead of the last barrier); with 4: batch 2 x 1024 45.3 -> 43.3 (value rows read whole 1.5 of it, the maximum without a shuffle
 // 0.3) -> 38.0.  Short launches (333 positions, 16 heads of 64: 9.8) are bound by launch and latency and did not change.
 // Tried: scores of the next block under the exponentials of this one, with keys and values copied straight into the LDS and transposed by the
 // read (ds_read_b64_tr_b16): 84 -> 90 with one stream; without the exponentials that form would take 67, so the matrix cores' power limit is near.
@@ -75,6 +75,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
   constexpr int KK = HD / 16;                 // MFMA steps of q.k
   constexpr int PPR = HD * 2 / 16;            // 16-byte pieces per key row
   constexpr int KP = kBlockKeys * PPR / NT;          // K pieces per thread per block
+  // The band's first rows are asked for ahead of the barrier behind the last key block, which a wavefront that sees nothing of that block reaches
+  // early (see the band below)
+  constexpr bool kAskEarly = WAVES == 8;
   constexpr int VP = kBlockKeys / 2 * PPR / NT;      // V (key pair, piece) items per thread per block
   static_assert(kBlockKeys * PPR % NT == 0 && (kBlockKeys / 2 * PPR) % NT == 0, "staging split");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -292,13 +295,19 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
       }
       l_run += ls;
     }
+    if (kAskEarly && blk + 1 == nb) break;
     __syncthreads();                                          // block blk+1 staged; everyone is done with block blk
   }
 
   // The band last: key t-off of stream J-1-off, off = J-2 .. 0.  These rows are read once, from HBM (67 MB a stream at batch 2 x 2048, 32
   // heads); ahead of the loop all workgroups of the launch asked for them at the same time and the matrix cores waited, behind it they ask as
   // they finish, under the others' blocks (three of 1000 positions, 8 heads, eight streams 41.7 -> 38.4 us, one of 852, 32 heads, five 34.0 ->
-  // 31.6; a single short workgroup per compute unit gains nothing, 608 positions of 4 heads 21.9 -> 22.1).  The 32 queries of the wavefront need 32 consecutive rows of a stream: they are read with coalesced
+  // 31.6; a single short workgroup per compute unit gains nothing, 608 positions of 4 heads 21.9 -> 22.1).  Many workgroups of heads that share their
+  // rows through the L2 lose by it: head dim 64, 64 heads on 8, two of 1024 positions 36.1 -> 37.4.  A workgroup of 8 wavefronts has the compute unit
+  // to itself and waits alone for its first rows; they are asked for ahead of the last barrier: 64 heads on 16, one of 2048 positions 98.6 -> 94.3 (96.5
+  // with the band ahead of the loop), 32 heads on 8, two of 2000, five streams 110.1 -> 108.2 (104.7).  With 4 wavefronts that pays
+  // for some (one of 2048 positions, 32 heads 64.1 -> 62.3) and costs others more (two of 1024 41.1 -> 43.4).
+  // The 32 queries of the wavefront need 32 consecutive rows of a stream: they are read with coalesced
   // 16-byte accesses (a row = PPR lanes) into the wavefront's own LDS area, and then every lane pair (c, c+32) picks up the row of ITS query,
   // splitting the dot product by the dims of its query fragments and the value row by the dims of its output registers.  No other wavefront is
   // involved (every one has left the key blocks' LDS at the last barrier); the next stream's rows travel while one's are used.
@@ -317,7 +326,10 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
         vw_[e] = *(const u32x4_t *)(vb + (size_t)row * kv_stride + (idx % PPR) * 8);
       }
     };
-    if (J > 1) fetch(J - 2);
+    if (J > 1) {
+      fetch(J - 2);
+      if (kAskEarly) __syncthreads();                         // everyone is done with the key blocks
+    }
     for (int off = J - 2; off >= 0; off--) {
 #pragma unroll
       for (int e = 0; e < BP; e++) {
@@ -377,15 +389,19 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 
 // Workgroups of 8 wavefronts save staging, but a tile of 256 has more rows past the end of the sequence, and a compute unit holds one
 // where it holds two of 4 wavefronts, so that the order longest first evens out less.  They pay
-//  * without a half-empty tile (an even number of 128-query tiles): 512 workgroups of 2000 positions 109 -> 98 us, of 1920 100 -> 99; 448 of
-//    2000 96 -> 94, of 1920 88 -> 93; 432 of 2304 102 -> 97, of 2100 92 -> 94;
-//  * from 1700 positions on (14 tiles): 448 of 1700 88 -> 82, of 1792 91 -> 85; 480 of 1536 103 -> 106, of 1280 83 -> 86, 400 of 1280 82 -> 85;
-//  * with 400 to 512 workgroups, a long and a short one for most of the 256 compute units: 400 of 2560 102 -> 97, 480 of 3072 138 -> 129, 512 of
-//    2048 110 -> 99, of 4096 179 -> 160; 320 of 2048 71 -> 75, 360 of 2304 85 -> 83, 384 of 4096 136 -> 135, 392 of 1792 80 -> 81; 560 of
-//    2560 140 -> 144, 576 of 2304 135 -> 139, 640 of 2048 169 -> 172;
-//  * and again from three each on, a little: 768 of 2000 179 -> 175, of 4096 266 -> 264, 864 of 2304 211 -> 205, 896 of 1792 181 -> 182, 1024 of
-//    4096 360 -> 336; 672 of 3072 194 -> 192, of 1792 143 -> 143, 720 of 2304 198 -> 198.
-// (4 -> 8 wavefronts, head dim 128, three streams, launches back to back.)  Head dim 64 has too few pieces per block for 512 threads to stage.
+//  * without a half-empty tile (an even number of 128-query tiles): 512 workgroups of 2000 positions 110 -> 104 us, of 1920 102 -> 101; 448 of
+//    2000 102 -> 97, of 1920 94 -> 96; 1024 of 2000 220 -> 204, of 1920 199 -> 202;
+//  * from 1700 positions on (14 tiles): 448 of 1700 92 -> 85, of 1792 94 -> 87; 480 of 1536 109 -> 108 and 92 -> 100, 400 of 1280 87 -> 88 and
+//    70 -> 78, but also 384 of 1536 77 -> 70 and 68 -> 61;
+//  * with 400 to 512 workgroups, a long and a short one for most of the 256 compute units: 400 of 2560 107 -> 101, 480 of 3072 141 -> 133, 512 of
+//    2048 112 -> 104 and 102 -> 95, of 4096 185 -> 168 and 174 -> 157; 320 of 2048 72 -> 72 and 80 -> 84, 384 of 2048 90 -> 84 and 85 -> 86; 560 of 1792
+//    129 -> 129 and 112 -> 121, 640 of 2048 166 -> 165 and 146 -> 154, 704 of 2048 172 -> 166 and 152 -> 156;
+//  * and again from three each on: 768 of 2000 177 -> 167 and 148 -> 145, of 4096 271 -> 262, 896 of 1792 181 -> 172 and 159 -> 157, 1024 of 4096 357 -> 341
+//    and 332 -> 313.
+// (4 -> 8 wavefronts, head dim 128, three streams, inputs from HBM; second figures: four query heads to a key head.  One stream gains as much or more, eight
+// 1 to 4 %.)  Where batch times key heads is no multiple of 8, and workgroups therefore not placed by XCD, they are slower
+// up to 512 workgroups (50 heads of 2048 109 -> 130, 25 of 4096 189 -> 207) and do not matter beyond.  Head dim 64 has too few pieces per block
+// for 512 threads to stage.
 bool wide_pays(long long tiles128, long long workgroups) {
   return tiles128 % 2 == 0 && tiles128 >= 14 && ((workgroups >= 400 && workgroups <= 512) || workgroups >= 768);
 }
