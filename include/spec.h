@@ -248,7 +248,7 @@ int spec_set_static_tree(spec_ctx *ctx, int32_t n_nodes, const int32_t *parent, 
  *   [4] GEMM ms inside verify      [5] GEMM ms inside draft
  *   [6] level 2 calibration: one event pair per verify with nothing between its two records, taken
  *       while the stream is busy (what the event mechanism itself adds to every interval of [4], [5])
- *   [7] reserved
+ *   [7] 0; its count: graphs captured (at every level)
  * counts[i] = number of intervals summed into ms[i]. */
 int spec_set_profile(spec_ctx *ctx, int32_t level);
 int spec_get_profile(spec_ctx *ctx, double *ms, int64_t *counts);

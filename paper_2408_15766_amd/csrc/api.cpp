@@ -523,6 +523,7 @@ int capture(spec_ctx *c, hipGraphExec_t *exec, const char *what, Launch launch) 
   e = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);
   if (e != hipSuccess) { *exec = nullptr; return fail(c, SPEC_EHIP, "graph instantiate (%s): %s", what, hipGetErrorString(e)); }
+  c->prof_cnt[7]++;
   return SPEC_OK;
 }
 
@@ -843,7 +844,7 @@ int spec_verify(spec_ctx *c, const spec_tree *tree) {
     return r ? r : lm_head(c, c->feats, N, c->logits);
   };
   const bool use_graph = c->graphs && c->stream != nullptr && c->prof_level < 2 && N == g.tree_total;
-  const int need = c->n + kMaxDepth;                            // largest key position a row of this cycle can have
+  const int need = std::min(c->n + kMaxDepth, g.max_seq - 1);   // largest key position a row of this cycle can have: the cache ends there
   if (use_graph && c->verify_exec != nullptr && c->verify_exec_rows == N && need <= c->verify_exec_bound) {
     HIPCHK(c, hipGraphLaunch(c->verify_exec, c->stream));
   } else {

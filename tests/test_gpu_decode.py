@@ -65,6 +65,25 @@ def test_tiny_fp32_spec_matches_oracle_per_cycle(env, tiny_gpu):
         assert np.abs(a["feats"] - b["feats"]).max() < 1e-4
 
 
+@pytest.mark.parametrize("tree", [(1, 1, 1), (2, 1, 3)], ids=["plain", "chain"])
+def test_filling_the_cache_captures_each_graph_once(env, tiny_gpu, tree):
+    """Decoding to the last slot of a cache without slack: the last cycles replay the graphs of the first (the cache's end bounds the rows'
+    positions), and the tokens are those of a roomy cache."""
+    torch, P = env
+    sh, hw, w64, prompt, dw = tiny_gpu
+    room = 24
+    eng = P.Engine(sh, dw, tree=tree, max_seq=len(prompt) + room)
+    got, cycles = [eng.prefill(prompt)], 0
+    while eng.committed + tree[2] <= len(prompt) + room:
+        t = eng.draft_tree()
+        eng.verify(t)
+        got += eng.accept(t)
+        cycles += 1
+    ms, cnt = P.spec_get_profile(eng.ctx)
+    assert cycles >= 20 // tree[2] and ms[7] == 0 and cnt[7] == (1 if tree[2] == 1 else 2)
+    assert got == P.Engine(sh, dw, tree=tree).generate(prompt, len(got))[0]
+
+
 @pytest.mark.parametrize("shape", [(1, 1, 2), (2, 3, 5), (15, 1, 16), (3, 16, 40), (6, 10, 60), (15, 16, 128)],
                          ids=lambda s: "D%d-K%d-N%d" % s)
 def test_tiny_fp32_tree_shapes_match_oracle(env, tiny_gpu, shape):
