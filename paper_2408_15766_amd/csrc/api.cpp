@@ -67,7 +67,8 @@ struct spec_ctx {
   uint32_t cycle = 0;
   int last_nodes = 0;
   int esz = 4;
-  int m_max = 0;        // largest row count of any forward
+  int m_small = 0;      // largest row count of any forward but a prompt's
+  int m_max = 0;        // ... of any forward
   int max_parts = 0;
   int seq_draft = 0;    // draft cache capacity in rows
   std::string err;
@@ -233,7 +234,7 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   TAKE(act, void *, (size_t)m_max * f * esz)
   TAKE(xcat, void *, (size_t)m_max * 2 * d * esz)
   TAKE(feats, void *, (size_t)m_max * d * esz)
-  TAKE(gfeat, void *, (size_t)m_max * d * esz)
+  TAKE(gfeat, void *, (size_t)m_small * d * esz)               // (a prompt's rows predict nothing)
   TAKE(pend_feat, void *, (size_t)(kMaxDepth + 1) * d * esz)
   TAKE(part, float *, part_floats * 4)
   // rows that write a partial per part (fp32: all; bf16: up to a long chain's), or one per row
@@ -289,7 +290,7 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   TAKE(acc, AcceptResult *, sizeof(AcceptResult))
 #undef TAKE
   if (x) {
-    x->esz = (int)esz; x->m_max = m_max; x->max_parts = max_parts; x->seq_draft = seq_draft;
+    x->esz = (int)esz; x->m_small = m_small; x->m_max = m_max; x->max_parts = max_parts; x->seq_draft = seq_draft;
     x->t_kv_stride = (size_t)c.max_seq * dkv; x->t_layer_stride = 2 * x->t_kv_stride;
     x->d_kv_stride = (size_t)seq_draft * dkv;
     x->part_floats = part_floats;
@@ -489,6 +490,7 @@ int draft_forward(spec_ctx *c, int m, int base, const void *feat, const int *src
                   const int *base_ptr = nullptr, bool keys_only = false) {
   const spec_config &g = c->cfg;
   const int d = g.d_model;
+  if (!keys_only && m > c->m_small) return fail(c, SPEC_EINVAL, "draft: %d rows", m);   // gfeat holds no more
   HIPCHK(c, launch_concat_feat_embed(g.dtype, feat, src_row, c->w.embed, rt.token, m, d, c->xcat, c->stream, rt.pos, g.head_dim,
                                      g.rope_theta, c->rope));
   const Seg segs[1] = {{c->w.draft_fc, d}};

@@ -60,6 +60,17 @@ def test_workspace_bytes_all_configs(P):
     assert sizes["llama3-70b"] < 2e9                    # caches + scratch stay far below the 288 GB of HBM
 
 
+def test_workspace_grows_by_what_a_prompt_row_needs(P):
+    # bf16, from 1024 to 1536 positions (whole prompts in one chunk): caches, one row of every buffer that a prompt's rows pass through, rotary
+    # table, four position arrays, and a partial output of 256 rows for each further attention part; nothing for predicted features
+    sh = wl.LLAMA3_8B
+    a, b = (P.spec_workspace_bytes(make_cfg(P, sh, max_seq=n, tree_depth=1, tree_topk=1, tree_total=1)) for n in (1024, 1536))
+    d, dq, dkv = sh.d_model, sh.d_q, sh.d_kv
+    row = 2 * 2 * dkv * (sh.n_layers + 1) + d * (4 + 2 + 4 + 2) + dq * (4 + 2) + 2 * sh.d_ffn + 4 * sh.head_dim + 16
+    part = 256 * sh.n_q_heads * (sh.head_dim + 2) * 4
+    assert abs(b - a - 512 * row - 4 * part) <= 16 * 256    # (every buffer starts at a multiple of 256)
+
+
 @pytest.mark.parametrize("kw", [dict(dtype=7), dict(head_dim=80), dict(n_q_heads=6, n_kv_heads=4), dict(tree_total=0),
                                 dict(tree_total=129), dict(tree_depth=16), dict(tree_topk=17), dict(max_seq=4),
                                 dict(temperature=-1.0), dict(d_model=255), dict(vocab=0)])
