@@ -42,6 +42,11 @@ int spec_k_gemm_folded(const void *x, int32_t ldx, int32_t m, int32_t in, const 
  * and `blocks` 32-row weight blocks in all (host only; for tests). */
 int spec_k_gemm_tile(int32_t m, int32_t blocks, int32_t in, int32_t n_split, int32_t *tokens, int32_t *rows);
 
+/* How a bf16 launch of `sets` (1 or 2) times m rows over `blocks` 32-row weight blocks runs (host only; for tests).  waves: wavefronts of a
+ * workgroup of the weight-streaming kernel, 0 beyond 128 rows in all.  tiles: 256 x 256 tiles of the fullest XCD where that tile is taken,
+ * else 0, and `whole` of them that run undivided (the others as halves of 128 x 256). */
+int spec_k_gemm_plan(int32_t m, int32_t sets, int32_t blocks, int32_t in, int32_t n_split, int32_t *waves, int32_t *whole, int32_t *tiles);
+
 /* The gate and up projections of the SwiGLU feed-forward block (the target LLMs of
  * Sec. 4.1 are LLaMA models) in one launch, with the activation applied in the
  * launch's epilogue: act[i][c] = silu(x[i] . w_gate[c]) * (x[i] . w_up[c]), silu(g)

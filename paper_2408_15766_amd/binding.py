@@ -301,6 +301,15 @@ def spec_k_gemm_folded(x, ws: Sequence, n_split: int):
     return part, tile.value
 
 
+def spec_k_gemm_plan(m: int, blocks: int, k: int, n_split: int = 1, sets: int = 1):
+    """(wavefronts of a streaming workgroup, whole 256 x 256 tiles of an XCD, all of them) of a launch over `sets` times m bf16 rows."""
+    out = [C.c_int32() for _ in range(3)]
+    rc = lib.spec_k_gemm_plan(m, sets, blocks, k, n_split, *(C.byref(o) for o in out))
+    if rc:
+        raise SpecError(rc, "spec_k_gemm_plan")
+    return tuple(o.value for o in out)
+
+
 def spec_k_gemm_tile(m: int, blocks: int, k: int, n_split: int = 1):
     """(tokens, weight rows) of the tile that a launch over m > 128 bf16 rows takes."""
     t, r = C.c_int32(), C.c_int32()

@@ -1167,6 +1167,12 @@ int spec_k_gemm_tile(int32_t m, int32_t blocks, int32_t in, int32_t n_split, int
   return SPEC_OK;
 }
 
+int spec_k_gemm_plan(int32_t m, int32_t sets, int32_t blocks, int32_t in, int32_t n_split, int32_t *waves, int32_t *whole, int32_t *tiles) {
+  if (!waves || !whole || !tiles || m < 1 || m > 4096 || sets < 1 || sets > 2 || blocks < 1 || in < 1 || n_split < 1) return SPEC_EINVAL;
+  gemm_plan(m, sets, blocks, in, n_split, waves, whole, tiles);
+  return SPEC_OK;
+}
+
 int spec_k_gemm_swiglu(int32_t dtype, const void *x, int32_t ldx, int32_t m, int32_t in, const void *w_gate_up, int32_t rows, void *act,
                        void *stream) {
   if (!x || !w_gate_up || !act || ((uintptr_t)act & 3) || rows < 1 || (dtype != 0 && dtype != 1)) return SPEC_EINVAL;

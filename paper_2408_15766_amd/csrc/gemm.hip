@@ -152,7 +152,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
   const int m_loc = PAIR ? 2 * a.m : a.m;                      // (more than 128 rows: gemm_mm_kernel)
   const bool swiglu = a.act != nullptr;
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
-  const int blk_raw = bx * a.blk_per_wg + wave * a.blk_per_wave;   // four adjacent blocks, or strided over more workgroups: see launch_stream
+  const int blk_raw = bx * a.blk_per_wg + wave * a.blk_per_wave;   // adjacent blocks, or strided over more workgroups: see launch_stream
   const bool active = blk_raw < a.total_blocks;
   const int blk = active ? blk_raw : a.total_blocks - 1;
   const int seg = blk < e0 ? 0 : (blk < e1 ? 1 : 2);
@@ -1070,10 +1070,13 @@ static hipError_t launch_mm_tile(GemmArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 // A compute unit holds one workgroup, so a launch lasts as many rounds as its workgroups fill the 256 compute units.  A round
-// of 256 x 256, 256 x 192 and 128 x 256 tiles (tokens x weight rows) takes 118, 94 and 70 us at K = 4096, of which about 6 are
-// filling and draining; the tile with the smallest product is taken, the larger one when they are close (it moves fewer bytes
-// per product).  512 rows at the 7B shape: QKV (2 splits) 55 us with 256 x 192 against 59 and 77, gate/up 98 against 108 and 138,
-// O (4 splits) 29 us with 128 x 256 against 38 and 34, LM head 129 us with 256 x 256 against 170 and 150.
+// of 256 x 256, 256 x 192 and 128 x 256 tiles (tokens x weight rows) takes 124, 90 and 62 us at K = 4096 and 37, 31 and 22 at 1024, of which about 6
+// are filling and draining; the tile with the smallest product is taken, the larger one when they are close (it moves fewer bytes
+// per product).  512 rows at the 7B shape: QKV (2 splits) 55 us with 256 x 192 against 58 and 74, gate/up 96 against 101 and 127,
+// O (4 splits) 22 us with 128 x 256 against 23 and 26, LM head 124 us with 256 x 256 against 181 and 149.
+// The 256 x 256 tile counts in whole rounds, though its last one may run in halves (mm_big_tiles).  Counted as it runs it would also be taken where it is
+// slower than 128 x 256 (loss of 300 positions at vocabulary 32000 219 -> 226 us, of 257 226 -> 232, 300 rows of the 70B gate/up 364 -> 394) beside
+// where it is faster (1333 rows of the 7B gate/up 249 -> 234, loss of 384 positions at vocabulary 128256 925 -> 900).
 static float mm_us(int tile, int m, int sets, int blocks, int in, int n_split) {
   const int tok = tile == 2 ? 128 : 256, wb = tile == 1 ? 6 : 8;
   const float at4096 = tile == 0 ? 112.f : (tile == 1 ? 88.f : 64.f);
@@ -1171,6 +1174,36 @@ static hipError_t launch_stream_tb(const GemmArgs &a, int waves, hipStream_t st)
   else hipLaunchKernelGGL((gemm_stream_kernel<bf16_t, TB, PAIR, kGemmWaves>), grid, threads, lds, st, a);
   return hipGetLastError();
 }
+static int stream_blocks(int blocks, int n_split) {          // of the fullest workgroup when all compute units get one
+  const int cap = std::max(1, 256 / n_split);
+  return (blocks + cap - 1) / cap;
+}
+// Eight wavefronts share one X slab where that is worth it (the same sums in the same order):
+//  * five to eight blocks per compute unit, any number of rows: one round of one workgroup each instead of a second, partly filled one of
+//    workgroups of four.  Gate/up of 60 rows, K 4096, 1100 blocks 67.8 -> 50.2 us, 1500 73.8 -> 63.2, 2000 84.8 -> 82.3; K 8192, 1792 (70B) 152.7 -> 144.1,
+//    ten rows 138.2 -> 136.5; 100 rows, 1500 blocks 96.7 -> 78.3;
+//  * four on most compute units, up to 32 rows and K ranges up to 4096: four of the waves only stage, and the slab is there sooner.  1000 blocks,
+//    K 4096, ten rows (7B LM head of the draft) 44.3 -> 41.7, 896 39.0 -> 37.5, 26 rows 40.0 -> 39.9; shorter ranges gain 6 to 9 %.  780 blocks 34.0 ->
+//    35.7 (26 rows), K 5120 47.9 -> 49.3, 60 rows 41.3 -> 44.0;
+//  * more than eight, more than 64 rows (a workgroup of four then has a compute unit to itself) and no more rounds x blocks: 100 rows, 4008 blocks 222 ->
+//    193 (K 8192 434 -> 383; loss of 60 positions at that vocabulary 249 -> 219); 2300 144 -> 150, where two rounds of eight take the place of three of four.  Up to 64 rows two workgroups of four
+//    share a compute unit: K 8192, 4008 blocks 335 -> 339 and 313 -> 324.
+static int stream_waves(int tb, int blocks, int in, int n_split) {   // tb: 32-row token blocks
+  const int units = blocks * n_split, per_wg = stream_blocks(blocks, n_split);
+  const bool round8 = per_wg > kGemmWaves && per_wg <= 8;
+  const bool stage8 = per_wg == kGemmWaves && tb == 1 && units >= 896 && (long long)in <= 4096ll * n_split;
+  const bool slab8 = per_wg > 8 && tb >= 3 && 2 * ((per_wg + 7) / 8) <= (per_wg + 3) / 4;
+  return round8 || stage8 || slab8 ? 8 : kGemmWaves;
+}
+void gemm_plan(int m, int sets, int blocks, int in, int n_split, int *waves, int *whole, int *tiles) {
+  *waves = *whole = *tiles = 0;
+  if ((long long)m * sets <= 128) { *waves = stream_waves((m * sets + 31) / 32, blocks, in, n_split); return; }
+  if (mm_tile(m, sets, blocks, in, n_split) != 0) return;
+  const int weight_tiles = (blocks + 7) / 8 * n_split;
+  *tiles = (weight_tiles + 7) / 8 * mm_lists(m, sets, weight_tiles).full;
+  *whole = mm_big_tiles(m, sets, weight_tiles, in, n_split);
+}
+
 template <bool PAIR>
 static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
   const int tb = ((PAIR ? 2 * a.m : a.m) + 31) / 32;
@@ -1179,25 +1212,10 @@ static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
   // units idle (7B gate/up: 688 blocks = 172 workgroups); if the blocks fit in three, two or one per workgroup on at
   // most 256 workgroups (all splits together), the launch takes that form: wave w streams block x + w * grid_x and
   // the waves left without a block only help to stage the X slab (7B gate/up 36.1 -> 33.6 us, O 10.8 -> 10.0, down with
-  // 4 splits 24.3 -> 20.3).  Otherwise four (or eight, below) adjacent blocks per workgroup: spreading without lowering the largest count
+  // 4 splits 24.3 -> 20.3).  Otherwise four (or eight, stream_waves) adjacent blocks per workgroup: spreading without lowering the largest count
   // measured 1 - 4 % slower at the 13B shapes.
-  const int cap = std::max(1, 256 / a.n_split);
-  const int per_wg = (a.total_blocks + cap - 1) / cap;
-  // Eight wavefronts share one X slab where that is worth it (the same sums in the same order):
-  //  * five to eight blocks per compute unit, any number of rows: one round of one workgroup each instead of a second, partly filled one of
-  //    workgroups of four.  Gate/up of 60 rows, K 4096, 1100 blocks 67.8 -> 50.2 us, 1500 73.8 -> 63.2, 2000 84.8 -> 82.3; K 8192, 1792 (70B) 152.7 -> 144.1,
-  //    ten rows 138.2 -> 136.5; 100 rows, 1500 blocks 96.7 -> 78.3;
-  //  * four on most compute units, up to 32 rows and K ranges up to 4096: four of the waves only stage, and the slab is there sooner.  1000 blocks,
-  //    K 4096, ten rows (7B LM head of the draft) 44.3 -> 41.7, 896 39.0 -> 37.5, 26 rows 40.0 -> 39.9; shorter ranges gain 6 to 9 %.  780 blocks 34.0 ->
-  //    35.7 (26 rows), K 5120 47.9 -> 49.3, 60 rows 41.3 -> 44.0;
-  //  * more than eight, more than 64 rows (a workgroup of four then has a compute unit to itself) and no more rounds x blocks: 100 rows, 4008 blocks 222 ->
-  //    193 (K 8192 434 -> 383; loss of 60 positions at that vocabulary 249 -> 219); 2300 144 -> 150, where two rounds of eight take the place of three of four.  Up to 64 rows two workgroups of four
-  //    share a compute unit: K 8192, 4008 blocks 335 -> 339 and 313 -> 324.
-  const int units = a.total_blocks * a.n_split;
-  const bool round8 = per_wg > kGemmWaves && per_wg <= 8;
-  const bool stage8 = per_wg == kGemmWaves && tb == 1 && units >= 896 && (long long)a.in <= 4096ll * a.n_split;
-  const bool slab8 = per_wg > 8 && tb >= 3 && 2 * ((per_wg + 7) / 8) <= (per_wg + 3) / 4;
-  const int waves = round8 || stage8 || slab8 ? 8 : kGemmWaves;
+  const int per_wg = stream_blocks(a.total_blocks, a.n_split);
+  const int waves = stream_waves(tb, a.total_blocks, a.in, a.n_split);
   if (per_wg < waves) {
     a.grid_x = (a.total_blocks + per_wg - 1) / per_wg;
     a.blk_per_wg = 1; a.blk_per_wave = a.grid_x;

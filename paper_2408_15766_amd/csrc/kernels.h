@@ -61,6 +61,7 @@ bool gemm_can_fold(const GemmArgs &a);
 int gemm_fold_tile(int m, int blocks, int in);                // tile of a folded launch (1: 256 x 192, 2: 128 x 256)
 bool gemm_fold_pays(int m, int rows, int in, int n_split, int block);
 void gemm_mm_tile(int m, int sets, int blocks, int in, int n_split, int *tokens, int *rows);   // tile of a launch over more than 128 bf16 rows
+void gemm_plan(int m, int sets, int blocks, int in, int n_split, int *waves, int *whole, int *tiles);   // see spec_k_gemm_plan
 hipError_t gemm_init();                 // one-time kernel attributes; call outside any stream capture
 int gemm_k_per_slab(int dtype);
 int gemm_k_per_iter(int dtype);

@@ -100,6 +100,7 @@ def test_null_context_calls_do_not_crash(P):
     assert P.lib.spec_accept(None, None, None, None) == P.binding.SPEC_EINVAL
     assert P.lib.spec_committed(None) == P.binding.SPEC_EINVAL
     P.lib.spec_destroy(None)
+    assert P.lib.spec_k_gemm_plan(60, 1, 4, 256, 1, None, None, None) == P.binding.SPEC_EINVAL
     assert P.lib.spec_k_gemm(0, None, 0, 0, 0, None, 0, None, 0, None, 0, None, 0, 0, 0, None) == P.binding.SPEC_EINVAL
 
 

@@ -94,6 +94,7 @@ def test_topk_loss_matches_oracle(env, dtype, rows, d, vocab, k):
 def test_lm_head_in_whole_and_half_tiles(env, rows):
     # both sides' rows through one launch whose token tiles end raggedly (74 and 4 rows) and whose last round runs in half tiles
     torch, P = env
+    assert P.spec_k_gemm_plan(rows, (37000 + 31) // 32, 264, sets=2) == (0, 32, 38)
     ft, fd, w = wl.make_distill_inputs(28, rows, 264, 37000, "bf16")
     got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 5, "bf16")
     want, alt, want_ce = oracle_losses(ft, fd, w, 5)

@@ -244,17 +244,19 @@ def test_gemm_many_rows_matches_fp64(env, m, k, rows, n_split, tile, tile_swiglu
         assert ((act - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * np.sqrt(k)).all()
 
 
-# m, k, weight rows, whole 256 x 256 tiles per XCD as the launch plans them: none, one round, two; with and without a ragged end of up to 128 rows,
-# lists of XCDs that differ by one weight tile, a last full tile of 129 .. 255 rows
-SPLIT_TILES = [(600, 264, 20500), (700, 520, 20510), (1333, 264, 20600), (2049, 264, 16500), (2300, 136, 7000), (2047, 264, 18499)]
+# m, k, weight rows, whole 256 x 256 tiles of the fullest XCD as the launch plans them, of all: none, one round, two; with and without a ragged end of up
+# to 128 rows, lists of XCDs that differ by one weight tile, a last full tile of 129 .. 255 rows
+SPLIT_TILES = [(600, 264, 20500, 0, 22), (700, 520, 20510, 32, 33), (1333, 264, 20600, 32, 55), (2049, 264, 16500, 64, 72), (2300, 136, 7000, 32, 36),
+               (2047, 264, 18499, 64, 80)]
 
 
-@pytest.mark.parametrize("m,k,rows", SPLIT_TILES)
-def test_gemm_whole_and_half_tiles_match_fp64_and_single_rows(env, m, k, rows):
+@pytest.mark.parametrize("m,k,rows,whole,tiles", SPLIT_TILES)
+def test_gemm_whole_and_half_tiles_match_fp64_and_single_rows(env, m, k, rows, whole, tiles):
     """Launches whose last round runs in tiles of half the tokens: against fp64 (fp32 sums of k terms of size 0.05), and rows at the edges of
     tiles and halves have the bits they have alone; SwiGLU over a matrix of the same block count likewise."""
     torch, P = env
     assert P.spec_k_gemm_tile(m, (rows + 31) // 32, k) == (256, 256)
+    assert P.spec_k_gemm_plan(m, (rows + 31) // 32, k) == P.spec_k_gemm_plan(m, (rows // 2 + 15) // 16, k) == (0, whole, tiles)
     g = torch.Generator(device="cuda"); g.manual_seed(case_seed("split", m, rows) & 0xFFFF)
     x = torch.randn(m, k, device="cuda", generator=g).to(torch.bfloat16)
     w = (torch.randn(rows, k, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
@@ -271,20 +273,24 @@ def test_gemm_whole_and_half_tiles_match_fp64_and_single_rows(env, m, k, rows):
         assert torch.equal(P.spec_k_gemm_swiglu(x[i:i + 1].contiguous(), gate, up)[0], act[i])
 
 
-# m, k, weight rows, splits: workgroups of eight wavefronts with five to eight blocks spread over the compute units (the last wave of some without a block),
-# with four blocks and few rows, and with eight adjacent ones; each beside the nearest size that keeps workgroups of four
-WIDE_WGS = [(1, 264, 32790, 1), (33, 520, 41270, 1), (60, 264, 65500, 1), (100, 264, 57330, 1), (128, 136, 65540, 1), (65, 264, 128256, 1), (64, 264, 128256, 1),
-            (32, 1032, 28672, 1), (33, 1032, 28672, 1), (10, 1032, 28640, 1), (7, 2056, 14500, 2), (40, 2056, 20500, 2)]
+# m, k, weight rows, splits, wavefronts of a workgroup in the two calls (partial sums; SwiGLU, never split): eight with five to eight blocks spread over the
+# compute units (the last wave of some without a block), with four blocks and few rows, and with eight adjacent ones; each beside the nearest size that
+# keeps workgroups of four
+WIDE_WGS = [(1, 264, 32790, 1, 8, 8), (33, 520, 41270, 1, 8, 8), (60, 264, 65500, 1, 8, 8), (100, 264, 57330, 1, 8, 8), (128, 136, 65540, 1, 4, 4),
+            (65, 264, 128256, 1, 8, 8), (64, 264, 128256, 1, 4, 4), (32, 1032, 28672, 1, 8, 8), (33, 1032, 28672, 1, 4, 4), (10, 1032, 28640, 1, 4, 4),
+            (7, 2056, 14500, 2, 8, 4), (40, 2056, 20500, 2, 8, 4)]
 
 
 # every count of 256-k slabs around the period of three: whole, and with one 128-k tile in the last slab; waves without a block; 1, 2 and 4 token blocks
-STREAM_K = [(m, 256 * slabs - cut, 70 if slabs % 2 else 33000, 1) for m in (9, 60, 100) for slabs in range(1, 9) for cut in (0, 136)]
+STREAM_K = [(m, 256 * slabs - cut, *((70, 1, 4, 4) if slabs % 2 else (33000, 1, 8, 8))) for m in (9, 60, 100) for slabs in range(1, 9) for cut in (0, 136)]
 
 
-@pytest.mark.parametrize("m,k,rows,n_split", WIDE_WGS + STREAM_K)
-def test_gemm_streams_match_fp64_and_single_rows(env, m, k, rows, n_split):
+@pytest.mark.parametrize("m,k,rows,n_split,waves,waves_swiglu", WIDE_WGS + STREAM_K)
+def test_gemm_streams_match_fp64_and_single_rows(env, m, k, rows, n_split, waves, waves_swiglu):
     """Against fp64 (fp32 sums of k terms of size 0.05), and every row has the bits it has beside others; SwiGLU over as many blocks likewise."""
     torch, P = env
+    assert P.spec_k_gemm_plan(m, (rows + 31) // 32, k, n_split) == (waves, 0, 0)
+    assert P.spec_k_gemm_plan(m, (rows // 2 + 15) // 16, k) == (waves_swiglu, 0, 0)
     g = torch.Generator(device="cuda"); g.manual_seed(case_seed("wide", m, rows) & 0xFFFF)
     x = torch.randn(m, k, device="cuda", generator=g).to(torch.bfloat16)
     w = (torch.randn(rows, k, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
