@@ -247,7 +247,7 @@ def topk_loss_bench(sh, with_cpu, launches=5):
            "dtype": "bf16", "ms_per_call": ms, "calls": launches, "mean_topk_loss": float(tot[0]) / rows, "mean_cross_entropy": float(tot[1]) / rows,
            "roofline": {"bound": "mfma", "achieved": flop / (ms * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                         "frac": flop / (ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
-                        "kernel": "gemm_mm_kernel (LM head, 512-row chunks) + loss_slice_kernel + loss_merge_kernel",
+                        "kernel": "gemm_mm_mixed_kernel (LM head, 512-row chunks) + loss_slice_kernel + loss_merge_kernel",
                         "algorithmic_flop_per_call": flop}}
     if with_cpu and host:
         from oracle import distill

@@ -320,7 +320,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
 // adds no waits to the two written below.  The sums of a row run in the order of gemm_stream_kernel's (k ascending in
 // one accumulator).
 // Measured (MI355X, us; before = 128 x 256 tiles with the weights streamed through registers): 512 x 12288 x 4096 with 2 splits
-// 86 -> 50, 512 x 32000 x 4096 161 -> 129, 4096 x 28672 x 4096 1113 -> 790, 4096 x 4096 x 14336 492 -> 373.
+// 86 -> 49, 512 x 32000 x 4096 161 -> 119, 4096 x 28672 x 4096 1113 -> 789, 4096 x 4096 x 14336 492 -> 363.
 // What limits it (LM head of 2 x 512 rows, 240 us when this was taken; with parts of the loop left out): without the copies into the LDS 194,
 // without the fragment reads as well 158, without the barrier no change.  So it is the traffic through the LDS, and the power: the clock falls
 // to 1.8 GHz in the large launches, the matrix cores are busy 59 % of the cycles, and products from registers alone run at 1.59 PFLOP/s on
@@ -744,8 +744,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
 // The bits are gemm_f32_kernel's: an fp32 MFMA is a chain of fused multiply-adds in the order of its k (both shapes, checked against
 // fmaf), the 64-k tiles w, w + 4, ... of the K range have one accumulator, w = 0, 1, 2, 3 one after the other here, and the four sums are
 // added up in that order.
-// Measured (MI355X, us; gemm_f32_kernel before): 512 x 32000 x 4096 1966 -> 1110 (121 TFLOP/s), 1400 x 32000 x 1024 1083 -> 799, 512 x 12288 x
-// 4096 588 -> 411, 300 x 5504 x 1024 53 -> 44.  The ring of halves against two whole tiles, then ragged tiles without padding: two sets of 129
+// Measured (MI355X, us; gemm_f32_kernel before): 512 x 32000 x 4096 1966 -> 1097 (122 TFLOP/s), 1400 x 32000 x 1024 1083 -> 786, 512 x 12288 x
+// 4096 588 -> 406, 300 x 5504 x 1024 53 -> 44.  The ring of halves against two whole tiles, then ragged tiles without padding: two sets of 129
 // rows x 9000, K = 512 38.1 -> 36.0 -> 34.9, K = 2048 116.8 -> 112.4 -> 105.8; two of 512 x 9000 x 512 97.9 -> 92.6, of 256 x 4096 x 4096 160 -> 151.
 constexpr int kF32Blocks = 2;                                 // 32-row weight blocks per workgroup
 __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f32_tiled_kernel(GemmArgs a) {
