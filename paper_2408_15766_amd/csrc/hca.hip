@@ -17,7 +17,7 @@
 // wavefronts per SIMD to cover each other; a wavefront's share of the staging is part of it and halves with 8 wavefronts.
 // Measured (MI355X, us, launches back to back over one set of inputs): batch 2 x 2048, 32 heads of 128, three streams 115.7 -> 102 with 8
 // wavefronts -> 98 with the band behind the loop (inputs from HBM: 113 both ways, 110 with its first rows asked for ahead of the last barrier); with 4: batch 2 x 1024 45.3 -> 43.3 (value rows read whole 1.5 of it, the maximum without a shuffle
-// 0.3) -> 38.0.  Short launches (333 positions, 16 heads of 64: 9.8) are bound by launch and latency and did not change.
+// 0.3) -> 38.0.  Launches that leave the chip idle have a kernel of their own (hca_split_kernel).
 // Tried: scores of the next block under the exponentials of this one, with keys and values copied straight into the LDS and transposed by the
 // read (ds_read_b64_tr_b16): 84 -> 90 with one stream; without the exponentials that form would take 67, so the matrix cores' power limit is near.
 #include "common.h"
@@ -67,6 +67,34 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Workgroup id -> (batch, kv head, head of the group, query tile).  Ids 8 apart run on one XCD: all tiles and heads that
+// read the same keys/values are placed there.  An XCD's (batch, kv head) groups are taken in chunks of up to kHcaChunk;
+// inside a chunk the workgroups go LONGEST TILE FIRST across its groups (the causal mask makes the last tile the
+// longest, and a launch of a few workgroups per slot ends when its last long tile does), the heads of one group next to
+// each other so that they share the keys and values through L2.  The chunk bounds the keys and values in use at a time:
+// tile-major order over 64 groups per XCD (batch 16) runs at 490 TFLOP/s where group-major order reaches 659; over the
+// 8 groups of the batch-2 launch it is 23 % faster than group-major.  (With a number of groups that is not a multiple
+// of 8 the XCD placement would leave XCDs idle or uneven; the ids then run chunk by chunk over all groups.)
+constexpr int kHcaChunk = 8;
+struct Place { int qt, gh, bi, hk; };
+__device__ __forceinline__ Place place(const HcaArgs &a, int rows) {   // rows: queries per workgroup
+  const int G = a.hq / a.hkv;
+  const int n_qt = (a.seq + rows - 1) / rows;
+  const int n_grp = a.batch * a.hkv;
+  const bool affine = (n_grp & 7) == 0;
+  const int grp_per_list = affine ? n_grp >> 3 : n_grp;      // groups whose workgroups form one ordered list
+  const int r_id = affine ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
+  const int chunk_wgs = kHcaChunk * G * n_qt;                // workgroups of a full chunk
+  const int chunk = r_id / chunk_wgs, in_chunk = r_id % chunk_wgs;
+  const int chunk_grps = min(kHcaChunk, grp_per_list - chunk * kHcaChunk);   // the last chunk may be short
+  const int qt = n_qt - 1 - in_chunk / (chunk_grps * G);
+  const int in_tile = in_chunk % (chunk_grps * G);
+  const int gh = in_tile % G;
+  const int grp_local = chunk * kHcaChunk + in_tile / G;
+  const int grp = affine ? grp_local * 8 + ((int)blockIdx.x & 7) : grp_local;
+  return Place{qt, gh, grp / a.hkv, grp % a.hkv};
+}
+
 template <int HD, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void hca_attention_kernel(HcaArgs a) {
   using L = HcaLds<HD, WAVES>;
@@ -82,30 +110,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
   static_assert(kBlockKeys * PPR % NT == 0 && (kBlockKeys / 2 * PPR) % NT == 0, "staging split");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
-  // Workgroup id -> (batch, kv head, head of the group, query tile).  Ids 8 apart run on one XCD: all tiles and heads that
-  // read the same keys/values are placed there.  An XCD's (batch, kv head) groups are taken in chunks of up to kHcaChunk;
-  // inside a chunk the workgroups go LONGEST TILE FIRST across its groups (the causal mask makes the last tile the
-  // longest, and a launch of a few workgroups per slot ends when its last long tile does), the heads of one group next to
-  // each other so that they share the keys and values through L2.  The chunk bounds the keys and values in use at a time:
-  // tile-major order over 64 groups per XCD (batch 16) runs at 490 TFLOP/s where group-major order reaches 659; over the
-  // 8 groups of the batch-2 launch it is 23 % faster than group-major.  (With a number of groups that is not a multiple
-  // of 8 the XCD placement would leave XCDs idle or uneven; the ids then run chunk by chunk over all groups.)
-  constexpr int kHcaChunk = 8;
-  const int G = a.hq / a.hkv;
-  const int n_qt = (a.seq + ROWS - 1) / ROWS;
-  const int n_grp = a.batch * a.hkv;
-  const bool affine = (n_grp & 7) == 0;
-  const int grp_per_list = affine ? n_grp >> 3 : n_grp;      // groups whose workgroups form one ordered list
-  const int r_id = affine ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
-  const int chunk_wgs = kHcaChunk * G * n_qt;                // workgroups of a full chunk
-  const int chunk = r_id / chunk_wgs, in_chunk = r_id % chunk_wgs;
-  const int chunk_grps = min(kHcaChunk, grp_per_list - chunk * kHcaChunk);   // the last chunk may be short
-  const int qt = n_qt - 1 - in_chunk / (chunk_grps * G);
-  const int in_tile = in_chunk % (chunk_grps * G);
-  const int gh = in_tile % G;
-  const int grp_local = chunk * kHcaChunk + in_tile / G;
-  const int grp = affine ? grp_local * 8 + ((int)blockIdx.x & 7) : grp_local;
-  const int bi = grp / a.hkv, hk = grp % a.hkv;
+  const Place at = place(a, ROWS);
+  const int qt = at.qt, gh = at.gh, bi = at.bi, hk = at.hk, G = a.hq / a.hkv;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 31, g = lane >> 5;
   const int T = a.seq, J = a.n_streams;
@@ -387,6 +393,202 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
+// ---- launches that leave the chip idle ------------------------------------------------------------
+// A workgroup = 8 wavefronts and 32 queries; the wavefronts share out the KEYS, 32 at a time (wavefront w takes blocks w, w + 8, ..), and the band (one
+// stream each, the last ones first: they have the fewest blocks), each with a softmax of its own, and merge in the LDS at the end.  Nothing is shared
+// before that, so there is no barrier in the loop: keys go from memory into the fragments, value rows into the wavefront's own LDS
+// area and out of it by the transposing read.  A 128-query tile's chain of T / 64 blocks becomes one of T / 256 half as long ones on four times as many
+// workgroups; the price is that every 32 queries load their keys and values themselves, so it is only for launches that do not fill the chip (split_pays).
+// Bound: latency (launch, first rows, two blocks, merge) up to 300 positions, then the chain of a block, about 1.5 us at head dim 128.  Four heads of 128, 2048 positions, three
+// streams 53.6 -> 27.1 us; 333 positions, 16 heads of 64 10.4 -> 6.5.
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+// Value rows in the LDS, HD * 2 bytes each; the 64-byte chunks are permuted by the row so that the four rows of a column read lie in different banks.
+template <int HD> __device__ __forceinline__ int value_chunk(int row, int chunk) { return chunk ^ (HD == 128 ? row & 3 : (row >> 1) & 1); }
+__device__ __forceinline__ u32x2_t read_columns(const unsigned char *p) {
+  return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)p));
+}
+
+constexpr int kSplitWaves = 8;
+template <int HD> struct SplitLds {
+  static constexpr int vals = 32 * HD * 2;              // a wavefront's value rows
+  static constexpr int orow = (HD + 4) * 4;             // a query's partial output (+4 floats: rows in different banks)
+  static constexpr int part = 32 * orow;                // ... and a wavefront's
+  static constexpr int stat = kSplitWaves * (vals > part ? vals : part);   // references, then sums, [wavefront][query]
+  static constexpr int total = stat + 2 * kSplitWaves * 32 * 4;
+};
+
+template <int HD>
+__global__ __launch_bounds__(kSplitWaves * 64, HD == 64 ? 4 : 2) void hca_split_kernel(HcaArgs a) {
+  using L = SplitLds<HD>;
+  constexpr int DB = HD / 32, KK = HD / 16, PPR = HD * 2 / 16, VP = 32 * PPR / 64;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const Place at = place(a, 32);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 31, g = lane >> 5;
+  const int T = a.seq, J = a.n_streams, G = a.hq / a.hkv;
+  const float c2 = a.scale_log2e;
+  const size_t kv_stride = (size_t)a.hkv * HD, kv_off = (size_t)at.bi * T * kv_stride + (size_t)at.hk * HD;
+  const bf16_t *kg = (const bf16_t *)a.k[0] + kv_off, *vg = (const bf16_t *)a.v[0] + kv_off;
+  const int r0 = at.qt * 32, tq = min(r0 + c, T - 1);         // queries past the end compute on the last one and are not stored
+  const int lim = tq - (J - 1);
+  const int last = min(r0 + 31, T - 1) - (J - 1);             // last old-region key of any query
+  const int nb = last >= 0 ? last / 32 + 1 : 0;
+  const bf16_t *qrow = (const bf16_t *)a.q + (((size_t)at.bi * T + tq) * a.hq + (size_t)at.hk * G + at.gh) * HD;
+  u32x4_t qf[KK], kf[KK], vr[VP];
+#pragma unroll
+  for (int kk = 0; kk < KK; kk++) qf[kk] = *(const u32x4_t *)(qrow + kk * 16 + g * 8);
+  f32x16_t o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; db++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) o[db][v] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+
+  auto load_k = [&](int blk) __attribute__((always_inline)) {   // (keys past the end: the last one, masked)
+    const bf16_t *row = kg + (size_t)min(blk * 32 + c, T - 1) * kv_stride + g * 8;
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++) kf[kk] = *(const u32x4_t *)(row + kk * 16);
+  };
+  auto load_v = [&](int blk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < VP; e++) {
+      const int idx = lane + 64 * e;
+      vr[e] = *(const u32x4_t *)(vg + (size_t)min(blk * 32 + idx / PPR, T - 1) * kv_stride + (idx % PPR) * 8);
+    }
+  };
+
+  const int off = kSplitWaves - 1 - wave;                     // this wavefront's band stream is J - 1 - off
+  static_assert(kMaxStreams - 1 <= kSplitWaves, "a wavefront per band stream");
+  if (off <= J - 2) {
+    // key tq - off of its stream for every query; a lane pair shares the dot product by the dims of its query fragments and the value row
+    // by the dims of its output registers
+    const size_t row = kv_off + (size_t)max(tq - off, 0) * kv_stride;
+    const bf16_t *kr = (const bf16_t *)a.k[J - 1 - off] + row + g * 8, *vb = (const bf16_t *)a.v[J - 1 - off] + row + 4 * g;
+    u32x2_t bv[DB * 4];
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++) kf[kk] = *(const u32x4_t *)(kr + kk * 16);
+#pragma unroll
+    for (int e = 0; e < DB * 4; e++) bv[e] = *(const u32x2_t *)(vb + e * 8);
+    float dot = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++) {
+      const uint32_t kx[4] = {kf[kk].x, kf[kk].y, kf[kk].z, kf[kk].w}, qx[4] = {qf[kk].x, qf[kk].y, qf[kk].z, qf[kk].w};
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        dot = fmaf(lo_f32(qx[e]), lo_f32(kx[e]), dot);
+        dot = fmaf(hi_f32(qx[e]), hi_f32(kx[e]), dot);
+      }
+    }
+    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(dot), __float_as_uint(dot), false, false);
+    dot = __uint_as_float(both[0]) + __uint_as_float(both[1]);
+    if (tq - off >= 0) {
+      m_run = dot * c2;                                       // the only key so far: probability 1
+      l_run = g == 0 ? 1.f : 0.f;                             // the two lanes of a query add up their sums at the end
+#pragma unroll
+      for (int e = 0; e < DB * 4; e++) {
+        const int db = e >> 2, v = 4 * (e & 3);
+        o[db][v] = lo_f32(bv[e].x); o[db][v + 1] = hi_f32(bv[e].x); o[db][v + 2] = lo_f32(bv[e].y); o[db][v + 3] = hi_f32(bv[e].y);
+      }
+    }
+  }
+
+  unsigned char *const vals = lds + wave * L::vals;
+  const int vrow = 4 * g + ((lane & 15) >> 2);                // a lane's place in a column read: row and 8 bytes of it
+  const int vcol = wave * L::vals + vrow * HD * 2 + value_chunk<HD>(vrow, 0) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+  if (wave < nb) { load_v(wave); load_k(wave); }
+  for (int blk = wave; blk < nb; blk += kSplitWaves) {
+#pragma unroll
+    for (int e = 0; e < VP; e++) {
+      const int idx = lane + 64 * e, row = idx / PPR, piece = idx % PPR;
+      *(u32x4_t *)(vals + row * HD * 2 + value_chunk<HD>(row, piece >> 2) * 64 + (piece & 3) * 16) = vr[e];
+    }
+    if (blk + kSplitWaves < nb) load_v(blk + kSplitWaves);
+    f32x16_t s;
+#pragma unroll
+    for (int v = 0; v < 16; v++) s[v] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++) s = mfma16(kf[kk], qf[kk], s);
+    if (blk + kSplitWaves < nb) load_k(blk + kSplitWaves);
+    // s[v] = q . k for key blk*32 + 8*(v/4) + 4*g + v%4 and query c
+    if (blk * 32 + 31 > r0 - (J - 1)) {                       // the block reaches past some query's region
+#pragma unroll
+      for (int v = 0; v < 16; v++)
+        if (blk * 32 + 4 * g + 8 * (v >> 2) + (v & 3) > lim) s[v] = -INFINITY;
+    }
+    float mb = s[0];
+#pragma unroll
+    for (int v = 1; v < 16; v++) mb = fmaxf(mb, s[v]);
+    mb = max_halves(mb) * c2;
+    const bool move = mb > m_run + 8.f;                       // (as in hca_attention_kernel: the reference moves by more than 2^8 only)
+    if (__any(move)) {
+      const float m_new = move ? mb : m_run;
+      const float corr = move ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
+      l_run *= corr;
+      m_run = m_new;
+#pragma unroll
+      for (int db = 0; db < DB; db++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) o[db][v] *= corr;
+    }
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;
+    float p[16];
+    uint32_t pk[8];
+#pragma unroll
+    for (int v = 0; v < 16; v++) { p[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c2, -m_use)); l_run += p[v]; }
+#pragma unroll
+    for (int e = 0; e < 8; e++) pk[e] = pack_bf16x2(p[2 * e], p[2 * e + 1]);
+    wave_lds_order();
+#pragma unroll
+    for (int h = 0; h < 2; h++) {                             // 16 keys: V^T fragment (A operand) of dims db*32 + c at keys 16h + 4g + {0..3, 8..11}
+      const u32x4_t pf = {pk[4 * h], pk[4 * h + 1], pk[4 * h + 2], pk[4 * h + 3]};
+#pragma unroll
+      for (int db = 0; db < DB; db++) {
+        const unsigned char *q = lds + (vcol ^ 64 * db) + 16 * h * HD * 2;
+        const u32x2_t v0 = read_columns(q), v1 = read_columns(q + 8 * HD * 2);
+        o[db] = mfma16(u32x4_t{v0.x, v0.y, v1.x, v1.y}, pf, o[db]);
+      }
+    }
+    wave_lds_order();                                         // the next block's values overwrite these
+  }
+
+  // merge: partial outputs and their references and sums through the LDS; a thread adds up HD / 16 dims of one query, wavefront by wavefront
+  const auto ls = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+  const float l_sum = __uint_as_float(ls[0]) + __uint_as_float(ls[1]);
+  __syncthreads();                                            // every wavefront is done with its values
+  float *const stat = (float *)(lds + L::stat);
+  if (g == 0) { stat[wave * 32 + c] = m_run; stat[kSplitWaves * 32 + wave * 32 + c] = l_sum; }
+#pragma unroll
+  for (int db = 0; db < DB; db++)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; q4++)
+      *(f32x4_t *)(lds + wave * L::part + c * L::orow + (db * 32 + 8 * q4 + 4 * g) * 4) = f32x4_t{o[db][4 * q4], o[db][4 * q4 + 1], o[db][4 * q4 + 2], o[db][4 * q4 + 3]};
+  __syncthreads();
+  constexpr int PER = HD / 64;                                // groups of four dims per thread
+  const int qi = tid >> 4, d0 = (tid & 15) * 4;
+  float m_max = -INFINITY, l_all = 0.f;
+#pragma unroll
+  for (int w = 0; w < kSplitWaves; w++) m_max = fmaxf(m_max, stat[w * 32 + qi]);
+  f32x4_t acc[PER] = {};
+#pragma unroll
+  for (int w = 0; w < kSplitWaves; w++) {
+    const float f = __builtin_amdgcn_exp2f(stat[w * 32 + qi] - m_max);   // (every query sees itself: the largest reference is no -inf)
+    l_all = fmaf(stat[kSplitWaves * 32 + w * 32 + qi], f, l_all);
+#pragma unroll
+    for (int e = 0; e < PER; e++) acc[e] += *(const f32x4_t *)(lds + w * L::part + qi * L::orow + (d0 + 64 * e) * 4) * f;
+  }
+  const int t = r0 + qi;
+  if (t >= T) return;
+  const float inv = 1.f / l_all;
+  bf16_t *orow = (bf16_t *)a.out + (((size_t)at.bi * T + t) * a.hq + (size_t)at.hk * G + at.gh) * HD;
+#pragma unroll
+  for (int e = 0; e < PER; e++) {
+    u32x2_t w;
+    w.x = pack_bf16x2(acc[e].x * inv, acc[e].y * inv);
+    w.y = pack_bf16x2(acc[e].z * inv, acc[e].w * inv);
+    *(u32x2_t *)(orow + d0 + 64 * e) = w;
+  }
+}
+
 // Workgroups of 8 wavefronts save staging, but a tile of 256 has more rows past the end of the sequence, and a compute unit holds one
 // where it holds two of 4 wavefronts, so that the order longest first evens out less.  They pay
 //  * without a half-empty tile (an even number of 128-query tiles): 512 workgroups of 2000 positions 110 -> 104 us, of 1920 102 -> 101; 448 of
@@ -404,6 +606,21 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 // for 512 threads to stage.
 bool wide_pays(long long tiles128, long long workgroups) {
   return tiles128 % 2 == 0 && tiles128 >= 14 && ((workgroups >= 400 && workgroups <= 512) || workgroups >= 768);
+}
+
+// Workgroups of 32 queries whose wavefronts share out the keys (hca_split_kernel) pay
+//  * where each gets a compute unit to itself, up to 256 of them: 16 heads of 64 on 4, 333 positions, two streams 10.4 -> 6.5 us, 4 heads of 128, 1500
+//    positions, three streams 41.9 -> 21.9, 32 heads, 256 positions 16.2 -> 10.8; one key block (up to 64 positions) and no band is merged for nothing: 6.2 ->
+//    7.2, with a band 8.3 -> 7.5;
+//  * in a second round of them only where the other kernel's chain is long: head dim 128 from 1000 positions on (512 workgroups of 1024 32.6 -> 24.8, of
+//    2048 53.8 -> 34.5; of 700 25.3 -> 25.0 and 21.2 -> 23.0, of 333 14.8 -> 17.7), 64, where a compute unit holds two, from 200 (512 of 200 11.1 -> 9.3,
+//    of 2048 34.7 -> 22.3; of 100 6.8 -> 7.1);
+//  * not beyond, where every 32 queries' own reads of keys and values fill the paths from the L2: 640 of 1024 positions 33.4 -> 40.7, 1024 of 2048 55.2 -> 64.7
+//    (head dim 64 22.0 -> 21.5 and 36.8 -> 33.0, but 640 of 700 17.0 -> 17.8).
+// (three streams or one, inputs in the caches)
+bool split_pays(int hd, int seq, int streams, long long workgroups) {
+  if (workgroups <= 256) return seq > 64 || streams > 1;
+  return workgroups <= 512 && seq >= (hd == 64 ? 200 : 1000);
 }
 
 template <int HD, int WAVES>
@@ -427,7 +644,26 @@ hipError_t launch_waves(const HcaArgs &a, hipStream_t st) {
 }
 
 template <int HD>
+hipError_t launch_split(const HcaArgs &a, hipStream_t st) {
+  constexpr int kLds = SplitLds<HD>::total;
+  static bool attr_done[64] = {};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64 || !attr_done[dev]) {
+    e = hipFuncSetAttribute((const void *)hca_split_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < 64) attr_done[dev] = true;
+  }
+  const long long grid = (long long)a.batch * a.hq * ((a.seq + 31) / 32);
+  if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(hca_split_kernel<HD>, dim3((unsigned)grid), dim3(kSplitWaves * 64), kLds, st, a);
+  return hipGetLastError();
+}
+
+template <int HD>
 hipError_t launch_hd(const HcaArgs &a, hipStream_t st) {
+  if (split_pays(HD, a.seq, a.n_streams, (long long)a.batch * a.hq * ((a.seq + 31) / 32))) return launch_split<HD>(a, st);
   if constexpr (HD == 128) {
     const long long tiles = (a.seq + 127) / 128;
     if (wide_pays(tiles, (long long)a.batch * a.hq * ((tiles + 1) / 2))) return launch_waves<HD, 8>(a, st);

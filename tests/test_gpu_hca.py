@@ -69,6 +69,24 @@ def test_hca_attention_matches_oracle(env, n_streams, batch, seq, hq, hkv, hd):
         check(got[b], want, vs)
 
 
+@pytest.mark.parametrize("n_streams,batch,seq,hq,hkv,hd", [
+    # launches of few workgroups, whose wavefronts share out the keys: edges of its 32-key blocks and of its eight wavefronts
+    (2, 1, 32, 1, 1, 128), (8, 1, 33, 2, 1, 64), (1, 1, 65, 2, 2, 128), (8, 2, 7, 4, 1, 128), (3, 1, 255, 2, 1, 64), (1, 1, 257, 3, 3, 128),
+    (8, 1, 264, 1, 1, 128), (3, 1, 1031, 2, 2, 64), (3, 1, 1025, 15, 5, 128), (5, 1, 203, 64, 8, 64),
+    # and one more head group, position or stream less than it takes: workgroups of 128 queries
+    (1, 1, 64, 2, 2, 128), (3, 1, 1024, 17, 17, 128), (3, 1, 999, 16, 2, 128), (2, 1, 199, 64, 16, 64), (8, 1, 150, 104, 13, 64), (4, 2, 257, 64, 8, 128),
+])
+def test_hca_attention_few_workgroups(env, n_streams, batch, seq, hq, hkv, hd):
+    torch, P = env
+    q, ks, vs = wl.make_hca_streams(17, n_streams, batch, seq, hq, hkv, hd)
+    got = run_gpu(torch, P, q, ks, vs)
+    heads = sorted({0, hq // 2, hq - 1})
+    for b in range(batch):
+        want = hca.hca_attention(q[b].astype(np.float64), [k[b].astype(np.float64) for k in ks],
+                                 [v[b].astype(np.float64) for v in vs], heads=heads)
+        check(got[b], want, vs, heads=heads)
+
+
 @pytest.mark.parametrize("n_streams,batch,seq,hq,hkv", [
     (3, 2, 2048, 32, 2),     # whole tiles; kv groups not a multiple of 8
     (8, 1, 1665, 64, 8),     # one query in the last 128: wavefronts of the last tile without a query, the band across the tiles' edge
