@@ -76,6 +76,12 @@ CASES = [
     ("bf16", 64, 256, 1000, 3),         # ... the largest such pair
     ("bf16", 65, 256, 1000, 3),         # ... and one row more per side: tiled, each side its own tiles
     ("fp32", 45, 200, 7000, 5),         # fp32 rows enough for the tiled LM head: each side its own 32-row tiles, ragged ones
+    ("fp32", 129, 512, 9000, 16),       # both sides' rows in 96-row tiles of products of bf16 parts
+    ("fp32", 100, 260, 9000, 16),       # ... five tiles of k, the last one of four; the sets' boundary inside a block
+    ("fp32", 33, 8, 32000, 10),         # ... one ragged tile of k, the second half of the wavefronts without one
+    ("fp32", 33, 192, 9000, 3),         # ... in 64-row tiles, two rows in the last; three tiles of k
+    ("fp32", 200, 64, 9090, 5),         # ... a ragged weight block in the last workgroup
+    ("fp32", 520, 132, 9000, 4),        # ... two chunks of positions, the second in the other kernel
     ("bf16", 1, 256, 100, 100),         # K = V: Eq. (1) becomes the cross-entropy (vocabulary smaller than one slice)
 ]
 
@@ -189,6 +195,27 @@ def test_infinite_and_nan_logits(env):
     for g, c in zip(got[:2], clean[:2]):
         assert np.isnan(g[[1, 3]]).all()
         np.testing.assert_array_equal(g[[0, 2, 4]], c[[0, 2, 4]])
+
+
+@pytest.mark.parametrize("value,factor", [("lowest", 1.0), ("lowest", 3.0), ("-inf", 2.0)])
+@pytest.mark.parametrize("rows", [40, 129])
+def test_ruled_out_tokens_in_products_of_parts(env, rows, value, factor):
+    # launches whose fp32 operands are cut into bf16 parts: a column takes every third token to the lowest value (whose parts are finite), past it
+    # (an overflow) or to -inf (which has no parts); beside the ruled out tokens the logits are those of a head without them
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(36, rows, 130 * 2, 9000, "fp32")
+    out = np.arange(9000) % 3 == 0
+    ft[:, 5] = fd[:, 5] = factor
+    w[:, 5] = 0.0
+    kept = w[~out]
+    w[out, 5] = float(torch.finfo(torch.float32).min) if value == "lowest" else -np.inf
+    got_topk, got_ce, _ = run_gpu(torch, P, ft, fd, w, 20, "fp32")
+    want, alt, want_ce = oracle_losses(ft, fd, kept, 20)
+    if value == "lowest" and factor == 1.0:
+        check(got_topk, got_ce, want, alt, want_ce)            # weight 0 times a finite logit
+    else:
+        assert (np.isclose(got_topk, want, **TOL) | np.isclose(got_topk, alt, **TOL)).all()
+        assert np.isnan(got_ce).all()                          # 0 * -inf, as the definition has it
 
 
 @pytest.mark.parametrize("lo,hi", [(0, 4096), (4096, 8192), (8192, 9000)])
