@@ -84,6 +84,7 @@ struct spec_ctx {
   int *sc_idx = nullptr, *top_tok = nullptr;
   int *d_prompt = nullptr, *d_pos = nullptr, *d_slot = nullptr, *d_depth = nullptr;
   int *pend_tok = nullptr, *root_tok = nullptr, *amax_idx = nullptr;
+  int *root_in = nullptr, *root_src = nullptr, *root_base = nullptr;   // the dynamic tree's root step: tokens and pending pairs of its rows, their first key position
   float *amax_val = nullptr;
   // verify tree on the device: packed exactly like the head of HostStage (tree_n .. anc)
   int *t_n = nullptr, *t_base = nullptr, *t_tok = nullptr, *t_par = nullptr, *t_dep = nullptr, *t_pos = nullptr, *t_slot = nullptr, *t_anc = nullptr;
@@ -91,6 +92,7 @@ struct spec_ctx {
   DraftState ds{};
   AcceptResult *acc = nullptr;
   HostStage *stage = nullptr;
+  HostStage *stage_dev = nullptr;         // ... as kernels see it: the drafted tree, the acceptance and the first token are written there
   size_t part_floats = 0;
 
   // static tree shape (spec_set_static_tree); n_nodes == 0: the dynamic tree of the configuration
@@ -109,8 +111,8 @@ struct spec_ctx {
   hipGraphExec_t verify_exec = nullptr;
   int verify_exec_rows = 0;
   int verify_exec_bound = 0;              // largest key position the captured launches are sized for
-  hipGraphExec_t expand_exec = nullptr;   // draft expansion steps 2..D + rerank
-  int expand_exec_bound = 0;
+  hipGraphExec_t draft_exec = nullptr;    // dynamic tree: root step, expansion steps 2..D, rerank
+  int draft_exec_bound = 0;
 
   // profiling
   int prof_level = 0;
@@ -256,6 +258,9 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   TAKE(d_depth, int *, (size_t)m_max * 4)
   TAKE(pend_tok, int *, (size_t)(kMaxDepth + 1) * 4)
   TAKE(root_tok, int *, 256)
+  TAKE(root_in, int *, (size_t)(kMaxDepth + 1) * 4)
+  TAKE(root_src, int *, (size_t)(kMaxDepth + 1) * 4)
+  TAKE(root_base, int *, 4)
   TAKE(amax_val, float *, (size_t)kMaxNodes * argmax_slices(c.vocab) * 4)
   TAKE(amax_idx, int *, (size_t)kMaxNodes * argmax_slices(c.vocab) * 4)
   // verify tree: one contiguous block mirroring the head of HostStage, so one copy moves it
@@ -529,10 +534,9 @@ int capture(spec_ctx *c, hipGraphExec_t *exec, const char *what, Launch launch) 
   return SPEC_OK;
 }
 
-// End of a drafting call: the device tree goes to the host arrays of the caller.
+// End of a drafting call: the tree in the staging memory goes to the host arrays of the caller.
 int finish_draft(spec_ctx *c, spec_tree *out) {
   c->gemm_bucket = 0;
-  HIPCHK(c, hipMemcpyAsync(&c->stage->tree_n, c->t_n, offsetof(HostStage, pos), hipMemcpyDeviceToHost, c->stream));
   phase_end(c, 0);
   int rc = sync(c);
   if (rc) return rc;
@@ -652,6 +656,10 @@ int spec_create(const spec_config *cfg, const spec_weights *w, spec_ctx **out) {
   hipError_t e = hipSetDevice(cfg->device);
   if (e == hipSuccess) e = gemm_init();
   if (e == hipSuccess) e = hipHostMalloc((void **)&c->stage, sizeof(HostStage), hipHostMallocDefault);
+  if (e == hipSuccess) {
+    e = hipHostGetDevicePointer((void **)&c->stage_dev, c->stage, 0);
+    if (e != hipSuccess) (void)hipHostFree(c->stage);
+  }
   if (e != hipSuccess) {
     int rc = fail(nullptr, SPEC_EHIP, "device %d / pinned staging: %s", cfg->device, hipGetErrorString(e));
     delete c;
@@ -670,7 +678,7 @@ void spec_destroy(spec_ctx *c) {
     for (int k = 0; k < 2; k++) if (c->ev_phase[p][k]) (void)hipEventDestroy(c->ev_phase[p][k]);
   for (hipEvent_t e : c->ev_gemm) (void)hipEventDestroy(e);
   if (c->verify_exec) (void)hipGraphExecDestroy(c->verify_exec);
-  if (c->expand_exec) (void)hipGraphExecDestroy(c->expand_exec);
+  if (c->draft_exec) (void)hipGraphExecDestroy(c->draft_exec);
   if (c->stage) (void)hipHostFree(c->stage);
   delete c;
 }
@@ -708,10 +716,8 @@ int spec_prefill(spec_ctx *c, const int32_t *prompt, int32_t n_prompt, int32_t *
         HIPCHK(c, launch_sample_row(c->logits, g.vocab, g.temperature, g.seed, 0, 0, c->root_tok, c->stream));
       else
         HIPCHK(c, launch_rows_argmax(c->logits, 1, g.vocab, c->amax_val, c->amax_idx, c->root_tok, c->stream));
-      // pending pair for the first draft root step: (feature of the last prompt position, first token)
-      HIPCHK(c, hipMemcpyAsync(c->pend_feat, (const char *)c->feats + (size_t)(m - 1) * g.d_model * c->esz,
-                               (size_t)g.d_model * c->esz, hipMemcpyDeviceToDevice, c->stream));
-      HIPCHK(c, hipMemcpyAsync(c->pend_tok, c->root_tok, 4, hipMemcpyDeviceToDevice, c->stream));
+      HIPCHK(c, launch_prefill_handoff((const char *)c->feats + (size_t)(m - 1) * g.d_model * c->esz, g.d_model * c->esz, c->root_tok, n_prompt, c->pend_feat,
+                                       c->pend_tok, c->t_base, c->acc, &c->stage_dev->first_token, c->stream));
     }
     // draft over the pairs (feature of position i-1, token at position i), i = c0+1 .. c0+m (the last
     // chunk stops one short: its final pair needs the first generated token and stays pending)
@@ -723,9 +729,6 @@ int spec_prefill(spec_ctx *c, const int32_t *prompt, int32_t n_prompt, int32_t *
       if (rc) return rc;
     }
   }
-  c->stage->base = n_prompt;
-  HIPCHK(c, hipMemcpyAsync(c->t_base, &c->stage->base, 4, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(&c->stage->first_token, c->root_tok, 4, hipMemcpyDeviceToHost, c->stream));
   phase_end(c, 3);
   int rc = sync(c);
   if (rc) return rc;
@@ -754,56 +757,65 @@ int spec_draft_tree(spec_ctx *c, spec_tree *out) {
   HIPCHK(c, hipSetDevice(g.device));
   phase_begin(c, 0);
   c->gemm_bucket = 5;
-  const int K = g.tree_topk, D = g.tree_depth, d = g.d_model;
-  // root step: the pending pairs occupy draft slots n - n_pend .. n - 1 (rotary positions one higher)
-  const int m1 = c->n_pend, base = c->n - m1;
-  HIPCHK(c, launch_chain_rows(base, m1, 1, c->d_pos, c->d_slot, c->d_depth, c->stream));
-  RowTables rt{c->pend_tok, c->d_pos, c->d_slot, c->d_depth, nullptr};
-  int rc = draft_forward(c, m1, base, c->pend_feat, nullptr, rt, base + m1 - 1);
-  if (rc) return rc;
-  rc = lm_head(c, (const char *)c->gfeat + (size_t)(m1 - 1) * d * c->esz, 1, c->dlogits);
-  if (rc) return rc;
+  const int K = g.tree_topk, D = g.tree_depth;
+  int rc;
   if (c->st.n_nodes > 0) {
+    // root step: the pending pairs occupy draft slots n - n_pend .. n - 1 (rotary positions one higher)
+    const int m1 = c->n_pend, base = c->n - m1;
+    HIPCHK(c, launch_chain_rows(base, m1, 1, c->d_pos, c->d_slot, c->d_depth, c->stream));
+    RowTables rt{c->pend_tok, c->d_pos, c->d_slot, c->d_depth, nullptr};
+    rc = draft_forward(c, m1, base, c->pend_feat, nullptr, rt, base + m1 - 1);
+    if (rc) return rc;
+    rc = lm_head(c, (const char *)c->gfeat + (size_t)(m1 - 1) * g.d_model * c->esz, 1, c->dlogits);
+    if (rc) return rc;
     rc = draft_static(c, m1);
     if (rc) return rc;
+    HIPCHK(c, hipMemcpyAsync(&c->stage->tree_n, c->t_n, offsetof(HostStage, pos), hipMemcpyDeviceToHost, c->stream));
     return finish_draft(c, out);
   }
-  HIPCHK(c, launch_rows_topk_logprob(c->dlogits, 1, g.vocab, K, c->sc_val, c->sc_idx, c->sc_stat, c->top_tok, c->top_lp, c->stream));
-  HIPCHK(c, launch_pool_init(c->ds, c->top_tok, c->top_lp, K, m1 - 1, c->t_base, c->stream));
-  // expansion steps 2..D (the frontier's k nodes, each fed (parent's predicted feature, own token)) and
-  // the rerank.  Every argument is fixed or device-resident (frontier tables, committed count), so the
-  // whole sequence is captured once and replayed.
-  auto expand_all = [&](const int *base_ptr, int base, int pos_bound) -> int {
+  // The root step over the pending pairs, expansion steps 2..D (the frontier's k nodes, each fed (parent's predicted feature, own token)) and
+  // the rerank.  Every argument is fixed or device-resident: the root step always has D + 1 rows, the pending pairs newest first (row 0's prediction is
+  // the one that is expanded) and the rest in scratch slots that the expansion overwrites.  So the whole sequence is captured once and replayed; the
+  // root step's launches one by one were 4 us each where its kernels take 2 to 3 (small models).  last: largest key position of the root
+  // step's rows, of an expansion's that plus its step (0: that of this cycle).
+  const int root_rows = std::max(D + 1, c->n_pend);             // (more: a tree deeper than the configured one was accepted)
+  auto draft_all = [&](int bound) -> int {
+    HIPCHK(c, launch_pending_rows(c->acc, c->t_base, c->pend_tok, root_rows, c->root_in, c->root_src, c->d_pos, c->d_slot, c->d_depth, c->root_base, c->stream));
+    RowTables rt{c->root_in, c->d_pos, c->d_slot, c->d_depth, nullptr};
+    int r = draft_forward(c, root_rows, 0, c->pend_feat, c->root_src, rt, bound ? bound : c->n - 1, c->root_base);
+    if (r) return r;
+    r = lm_head(c, c->gfeat, 1, c->dlogits);
+    if (r) return r;
+    HIPCHK(c, launch_pool_init(c->ds, c->dlogits, g.vocab, c->sc_val, c->sc_idx, c->sc_stat, c->top_tok, c->top_lp, K, 0, c->t_base, c->stream));
     for (int t = 2; t <= D; t++) {
       RowTables fr{c->ds.front_tok, c->ds.front_pos, c->ds.front_slot, c->ds.front_depth, c->ds.front_anc};
       // xcat is built from gfeat before the layer overwrites gfeat, so one buffer serves all steps
-      int r = draft_forward(c, K, base, c->gfeat, c->ds.front_src, fr, base_ptr ? pos_bound : base + t - 2, base_ptr);
+      r = draft_forward(c, K, 0, c->gfeat, c->ds.front_src, fr, bound ? bound : c->n + t - 2, c->t_base);
       if (r) return r;
       r = lm_head(c, c->gfeat, K, c->dlogits);
       if (r) return r;
-      HIPCHK(c, launch_rows_topk_logprob(c->dlogits, K, g.vocab, K, c->sc_val, c->sc_idx, c->sc_stat, c->top_tok, c->top_lp, c->stream));
-      HIPCHK(c, launch_pool_expand(c->ds, c->top_tok, c->top_lp, K, t, c->t_base, t < D ? 1 : 0, c->stream));
+      HIPCHK(c, launch_pool_expand(c->ds, c->dlogits, g.vocab, c->sc_val, c->sc_idx, c->sc_stat, c->top_tok, c->top_lp, K, t, c->t_base, t < D ? 1 : 0,
+                                   c->stream));
     }
-    HIPCHK(c, launch_rerank(c->ds, g.tree_total, c->root_tok, c->t_n, c->t_tok, c->t_par, c->t_dep, c->t_sc, c->stream));
+    HostStage *s = c->stage_dev;                                // (straight to the host)
+    HIPCHK(c, launch_rerank(c->ds, g.tree_total, c->root_tok, &s->tree_n, s->tok, s->par, s->dep, s->sc, c->stream));
     return SPEC_OK;
   };
-  if (c->graphs && c->stream != nullptr && c->prof_level < 2) {
-    const int need = c->n + D;                                  // largest key position of a draft row of this cycle
-    if (c->expand_exec == nullptr || need > c->expand_exec_bound) {
-      // no graph for this context yet: this cycle's launches go out one by one and the graph is captured while they run
-      rc = expand_all(nullptr, c->n, 0);
-      if (rc) return rc;
-      const int bound = std::min(c->seq_draft - 1, (need / kGraphBucket + 1) * kGraphBucket - 1);
-      c->expand_exec_bound = 0;
-      rc = capture(c, &c->expand_exec, "draft", [&] { return expand_all(c->t_base, 0, bound); });
-      if (rc) return rc;
-      c->expand_exec_bound = bound;
-    } else {
-      HIPCHK(c, hipGraphLaunch(c->expand_exec, c->stream));
-    }
+  const bool use_graph = c->graphs && c->stream != nullptr && c->prof_level < 2 && root_rows == D + 1;
+  const int need = c->n + D;                                    // largest key position of a draft row of this cycle
+  if (use_graph && c->draft_exec != nullptr && need <= c->draft_exec_bound) {
+    HIPCHK(c, hipGraphLaunch(c->draft_exec, c->stream));
   } else {
-    rc = expand_all(nullptr, c->n, 0);
+    rc = draft_all(0);
     if (rc) return rc;
+    if (use_graph) {
+      // no graph for this context yet: this cycle's launches go out one by one and the graph is captured while they run
+      const int bound = std::min(c->seq_draft - 1, (need / kGraphBucket + 1) * kGraphBucket - 1);
+      c->draft_exec_bound = 0;
+      rc = capture(c, &c->draft_exec, "draft", [&] { return draft_all(bound); });
+      if (rc) return rc;
+      c->draft_exec_bound = bound;
+    }
   }
   return finish_draft(c, out);
 }
@@ -912,8 +924,7 @@ int spec_accept(spec_ctx *c, const spec_tree *tree, int32_t *out_tokens, int32_t
     HIPCHK(c, launch_accept_greedy(c->amax_val, c->amax_idx, argmax_slices(g.vocab), c->t_tok, c->t_par, N, c->acc, c->stream));
   }
   HIPCHK(c, launch_commit(g.dtype, c->acc, c->kv_t, c->t_layer_stride, c->t_kv_stride, g.n_layers, g.n_kv_heads * g.head_dim,
-                          c->n, c->feats, g.d_model, c->pend_feat, c->pend_tok, c->root_tok, c->t_base, c->stream));
-  HIPCHK(c, hipMemcpyAsync(&c->stage->acc, c->acc, sizeof(AcceptResult), hipMemcpyDeviceToHost, c->stream));
+                          c->n, c->feats, g.d_model, c->pend_feat, c->pend_tok, c->root_tok, c->t_base, &c->stage_dev->acc, c->stream));
   phase_end(c, 2);
   int rc = sync(c);
   if (rc) return rc;

@@ -177,13 +177,14 @@ struct DraftState {
   int *front_pos;                                        // [K] rotary position
 };
 // n_draft (device int): committed draft-cache entries = committed tokens; scratch slots start there.
-// After the root step: pool <- top-k of the root row; frontier <- those k nodes.
-hipError_t launch_pool_init(const DraftState &s, const int *top_tok, const float *top_lp, int k, int root_row,
-                            const int *n_draft, hipStream_t st);
-// After expansion step t (frontier rows = k nodes of depth t-1): append k*k children; if `select_next`,
+// Both take the rows' draft logits and form their top-k lists on the way (scratch as launch_rows_topk_logprob's).
+// After the root step: pool <- top-k of the root row (row 0 of logits); frontier <- those k nodes.
+hipError_t launch_pool_init(const DraftState &s, const float *logits, int vocab, float *sc_val, int *sc_idx, float2 *sc_stat, int *top_tok, float *top_lp,
+                            int k, int root_row, const int *n_draft, hipStream_t st);
+// After expansion step t (frontier rows = k nodes of depth t-1, k rows of logits): append k*k children; if `select_next`,
 // choose the k best children as the next frontier and derive its attention tables.
-hipError_t launch_pool_expand(const DraftState &s, const int *top_tok, const float *top_lp, int k, int step,
-                              const int *n_draft, int select_next, hipStream_t st);
+hipError_t launch_pool_expand(const DraftState &s, const float *logits, int vocab, float *sc_val, int *sc_idx, float2 *sc_stat, int *top_tok, float *top_lp,
+                              int k, int step, const int *n_draft, int select_next, hipStream_t st);
 // Rerank: best (total-1) pool entries by score (ties: lower pool index), kept in pool order.
 // tree_* arrays have room for `total` nodes; node 0 = root.
 hipError_t launch_rerank(const DraftState &s, int total, const int *root_tok, int *tree_n, int *tree_tok, int *tree_par,
@@ -235,6 +236,15 @@ hipError_t launch_sample_row(const float *logits, int vocab, float temp, uint64_
 // *n_committed (device) += 1 + accepted.
 hipError_t launch_commit(int dtype, const AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride,
                          int n_layers, int row_elems, int n, const void *feat, int d, void *pend_feat, int *pend_tok,
-                         int *root_tok, int *n_committed, hipStream_t st);
+                         int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st);
+// (host_res: pinned host memory as the device sees it; *res is written there too)
+// After a prompt: the pending pair (feature row of row_bytes bytes, first token) for the first draft root step, the committed count, and the first token
+// for the host (pinned memory as the device sees it).  res: one pending pair, as after a cycle that accepted nothing.
+hipError_t launch_prefill_handoff(const void *feat, int row_bytes, const int *root_tok, int n_prompt, void *pend_feat, int *pend_tok,
+                                  int *n_committed, AcceptResult *res, int *host_first, hipStream_t st);
+// Tables of a draft root step of `rows` rows (at least the 1 + res->n_acc pending pairs, at most kMaxDepth + 1): row i holds pending pair n_acc - i (its token, its index in
+// src, causal chain from key position *base = *n_committed - 1 - n_acc); the rows left over repeat pair 0 in the slots behind the committed ones.
+hipError_t launch_pending_rows(const AcceptResult *res, const int *n_committed, const int *pend_tok, int rows, int *token, int *src, int *pos, int *slot,
+                               int *depth, int *base, hipStream_t st);
 
 }  // namespace spec

@@ -199,6 +199,40 @@ __global__ __launch_bounds__(kSelThreads) void topk_slice_kernel(const float *lo
 // FEW: up to 64 slices, one per lane and whole in its registers; else lane l walks the slices l, l + 64, .. in the LDS.
 constexpr int kMaxMergeCand = 4096;
 constexpr int kMergeThreads = 128;
+// The k best of up to 64 sorted lists (lane sl: slice sl's, whole in its registers), by one wavefront: best(r, value, index) for r = 0 .. k - 1, in lane 0.
+template <typename Best>
+__device__ __forceinline__ void merge_lists(int k, int n_slices, const float *val, const int *idx, int lane, Best best) {
+  float v[kMaxTopK];
+  int i[kMaxTopK];
+  const int sl = min(lane, n_slices - 1);
+#pragma unroll
+  for (int r = 0; r < kMaxTopK; r++) { v[r] = val[sl * kMaxTopK + min(r, k - 1)]; i[r] = idx[sl * kMaxTopK + min(r, k - 1)]; }
+#pragma unroll
+  for (int r = 0; r < kMaxTopK; r++)
+    if (lane >= n_slices || r >= k) { v[r] = -INFINITY; i[r] = INT_MAX; }
+  for (int r = 0; r < k; r++) {
+    const float bv = wave_max_dpp(v[0]);
+    const int bi = wave_min_dpp(v[0] == bv ? i[0] : INT_MAX);
+    if (lane == 0) best(r, bv, bi);
+    if (i[0] != bi || bi == INT_MAX) continue;                // (a token is in one list only)
+#pragma unroll
+    for (int e = 0; e + 1 < kMaxTopK; e++) { v[e] = v[e + 1]; i[e] = i[e + 1]; }
+    v[kMaxTopK - 1] = -INFINITY; i[kMaxTopK - 1] = INT_MAX;
+  }
+}
+// log-sum-exp of a row from its slices' statistics, by one wavefront
+__device__ __forceinline__ float lists_lse(int n_slices, const float2 *stat, int lane) {
+  float m = -INFINITY;
+  for (int sl = lane; sl < n_slices; sl += 64) m = fmaxf(m, stat[sl].x);
+  m = wave_max(m);
+  float tot = 0.f;
+  for (int s0 = 0; s0 < n_slices; s0 += 64) {                // slices in ascending groups of 64, fixed butterfly inside
+    const int sl = s0 + lane;
+    // (a slice without any probability has the maximum -inf and no sum of its own)
+    tot += wave_sum(sl < n_slices && stat[sl].x != -INFINITY ? stat[sl].y * expf(stat[sl].x - m) : 0.f);
+  }
+  return m + logf(tot);
+}
 template <bool FEW>
 __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(int k, int n_slices, const float *sc_val, const int *sc_idx,
                                                                    const float2 *sc_stat, int *top_tok, float *top_lp) {
@@ -210,6 +244,7 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(int k, int n_
   const int rowi = blockIdx.x, t = threadIdx.x, lane = t & 63;
   const float *val = sc_val + (size_t)rowi * n_slices * kMaxTopK;
   const int *idx = sc_idx + (size_t)rowi * n_slices * kMaxTopK;
+  auto best = [&](int r, float v, int i) __attribute__((always_inline)) { best_val[r] = v; best_idx[r] = i; };
   if constexpr (!FEW) {
     for (int id = t; id < n_slices * k; id += kMergeThreads) {   // candidate id = slice * k + r
       const int at = id / k * kMaxTopK + id % k;
@@ -219,53 +254,34 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(int k, int n_
     __syncthreads();
   }
   if (t < 64) {
-    float v[FEW ? kMaxTopK : 1];                              // FEW: the list, best entry first; else the lane's best entry
-    int i[FEW ? kMaxTopK : 1], from = -1;
     if constexpr (FEW) {
-      const int sl = min(lane, n_slices - 1);
-#pragma unroll
-      for (int r = 0; r < kMaxTopK; r++) { v[r] = val[sl * kMaxTopK + min(r, k - 1)]; i[r] = idx[sl * kMaxTopK + min(r, k - 1)]; }
-#pragma unroll
-      for (int r = 0; r < kMaxTopK; r++)
-        if (lane >= n_slices || r >= k) { v[r] = -INFINITY; i[r] = INT_MAX; }
-    }
-    auto head = [&]() __attribute__((always_inline)) {        // (not FEW) the best entry left in this lane's lists
-      v[0] = -INFINITY; i[0] = INT_MAX; from = -1;
-      for (int sl = lane; sl < n_slices; sl += 64) {
-        const int r = taken[sl];
-        if (r >= k) continue;
-        const float x = cand_val[sl * k + r];
-        const int c = cand_idx[sl * k + r];
-        if (c != INT_MAX && (from < 0 || better(x, c, v[0], i[0]))) { v[0] = x; i[0] = c; from = sl; }
-      }
-    };
-    if constexpr (!FEW) head();
-    for (int r = 0; r < k; r++) {
-      const float bv = wave_max_dpp(v[0]);
-      const int bi = wave_min_dpp(v[0] == bv ? i[0] : INT_MAX);
-      if (lane == 0) { best_val[r] = bv; best_idx[r] = bi; }
-      if (i[0] != bi || bi == INT_MAX) continue;              // (a token is in one list only)
-      if constexpr (FEW) {
-#pragma unroll
-        for (int e = 0; e + 1 < kMaxTopK; e++) { v[e] = v[e + 1]; i[e] = i[e + 1]; }
-        v[kMaxTopK - 1] = -INFINITY; i[kMaxTopK - 1] = INT_MAX;
-      } else {
+      merge_lists(k, n_slices, val, idx, lane, best);
+    } else {
+      float v;                                                // the best entry left in this lane's lists
+      int i, from;
+      auto head = [&]() __attribute__((always_inline)) {
+        v = -INFINITY; i = INT_MAX; from = -1;
+        for (int sl = lane; sl < n_slices; sl += 64) {
+          const int r = taken[sl];
+          if (r >= k) continue;
+          const float x = cand_val[sl * k + r];
+          const int c = cand_idx[sl * k + r];
+          if (c != INT_MAX && (from < 0 || better(x, c, v, i))) { v = x; i = c; from = sl; }
+        }
+      };
+      head();
+      for (int r = 0; r < k; r++) {
+        const float bv = wave_max_dpp(v);
+        const int bi = wave_min_dpp(v == bv ? i : INT_MAX);
+        if (lane == 0) best(r, bv, bi);
+        if (i != bi || bi == INT_MAX) continue;               // (a token is in one list only)
         taken[from]++;
         head();
       }
     }
   } else {
-    const float2 *stat = sc_stat + (size_t)rowi * n_slices;
-    float m = -INFINITY;
-    for (int sl = lane; sl < n_slices; sl += 64) m = fmaxf(m, stat[sl].x);
-    m = wave_max(m);
-    float tot = 0.f;
-    for (int s0 = 0; s0 < n_slices; s0 += 64) {            // slices in ascending groups of 64, fixed butterfly inside
-      const int sl = s0 + lane;
-      // (a slice without any probability has the maximum -inf and no sum of its own)
-      tot += wave_sum(sl < n_slices && stat[sl].x != -INFINITY ? stat[sl].y * expf(stat[sl].x - m) : 0.f);
-    }
-    if (lane == 0) lse_sh = m + logf(tot);
+    const float lse = lists_lse(n_slices, sc_stat + (size_t)rowi * n_slices, lane);
+    if (lane == 0) lse_sh = lse;
   }
   __syncthreads();
   if (t < k) {
@@ -273,13 +289,17 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(int k, int n_
     top_lp[rowi * kMaxTopK + t] = best_val[t] - lse_sh;
   }
 }
-hipError_t launch_rows_topk_logprob(const float *logits, int rows, int vocab, int k, float *sc_val, int *sc_idx,
-                                    float2 *sc_stat, int *top_tok, float *top_lp, hipStream_t st) {
+static hipError_t launch_topk_slices(const float *logits, int rows, int vocab, int k, float *sc_val, int *sc_idx, float2 *sc_stat, hipStream_t st) {
   const int n_slices = (vocab + kTopkSlice - 1) / kTopkSlice;
   if (rows < 1 || k < 1 || k > kMaxTopK || k > vocab || n_slices * k > kMaxMergeCand) return hipErrorInvalidValue;
   hipLaunchKernelGGL(topk_slice_kernel, dim3(n_slices, rows), dim3(kSelThreads), 0, st, logits, vocab, k, n_slices, sc_val,
                      sc_idx, sc_stat);
-  hipError_t e = hipGetLastError();
+  return hipGetLastError();
+}
+hipError_t launch_rows_topk_logprob(const float *logits, int rows, int vocab, int k, float *sc_val, int *sc_idx,
+                                    float2 *sc_stat, int *top_tok, float *top_lp, hipStream_t st) {
+  const int n_slices = (vocab + kTopkSlice - 1) / kTopkSlice;
+  const hipError_t e = launch_topk_slices(logits, rows, vocab, k, sc_val, sc_idx, sc_stat, st);
   if (e != hipSuccess) return e;
   if (n_slices <= 64)
     hipLaunchKernelGGL(topk_merge_kernel<true>, dim3(rows), dim3(kMergeThreads), 0, st, k, n_slices, sc_val, sc_idx, sc_stat, top_tok, top_lp);
@@ -289,44 +309,56 @@ hipError_t launch_rows_topk_logprob(const float *logits, int rows, int vocab, in
 }
 
 // ---- candidate pool ------------------------------------------------------------------------
-// top_tok / top_lp rows have stride kMaxTopK.
-__global__ void pool_init_kernel(DraftState s, const int *top_tok, const float *top_lp, int k, int root_row,
-                                 const int *n_draft_ptr) {
+// One workgroup: wavefront r merges the slices' lists of row r and forms its log-sum-exp (the same as topk_merge_kernel, bit for bit), then the pool takes
+// the rows' children.  Merge and pool were two launches of one workgroup's work each, a chain per draft depth: root step and five expansions at the
+// 7B shape 12 launches -> 6.
+constexpr int kPoolThreads = kMaxTopK * 64;
+struct TopRows { const float *sc_val; const int *sc_idx; const float2 *sc_stat; int n_slices; const int *tok; const float *lp; };   // tok: merged already (more than 64 slices)
+struct TopShared { int tok[kMaxTopK * kMaxTopK]; float lp[kMaxTopK * kMaxTopK]; };
+__device__ __forceinline__ void merge_rows(const TopRows &top, int rows, int k, TopShared &sh) {
+  const int lane = threadIdx.x & 63, r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (top.tok != nullptr) {
+    if (r < rows && lane < k) { sh.tok[r * kMaxTopK + lane] = top.tok[r * kMaxTopK + lane]; sh.lp[r * kMaxTopK + lane] = top.lp[r * kMaxTopK + lane]; }
+  } else if (r < rows) {
+    const size_t at = (size_t)r * top.n_slices;
+    const float lse = lists_lse(top.n_slices, top.sc_stat + at, lane);
+    merge_lists(k, top.n_slices, top.sc_val + at * kMaxTopK, top.sc_idx + at * kMaxTopK, lane,
+                [&](int j, float v, int i) __attribute__((always_inline)) { sh.tok[r * kMaxTopK + j] = i; sh.lp[r * kMaxTopK + j] = v - lse; });
+  }
+  __syncthreads();
+}
+__global__ __launch_bounds__(64) void pool_init_kernel(DraftState s, TopRows top, int k, int root_row, const int *n_draft_ptr) {
+  __shared__ TopShared sh;
   const int r = threadIdx.x;
   const int n_draft = *n_draft_ptr;
+  merge_rows(top, 1, k, sh);
   if (r < k) {
-    s.pool_tok[r] = top_tok[r]; s.pool_par[r] = -1; s.pool_dep[r] = 1; s.pool_sc[r] = top_lp[r];
-    s.front_pool[r] = r; s.front_tok[r] = top_tok[r]; s.front_src[r] = root_row; s.front_depth[r] = 0;
+    s.pool_tok[r] = sh.tok[r]; s.pool_par[r] = -1; s.pool_dep[r] = 1; s.pool_sc[r] = sh.lp[r];
+    s.front_pool[r] = r; s.front_tok[r] = sh.tok[r]; s.front_src[r] = root_row; s.front_depth[r] = 0;
     s.front_anc[r * kAncStride] = r;
     s.front_slot[r] = n_draft + r;
     s.front_pos[r] = n_draft + 1;
   }
   if (r == 0) *s.n_pool = k;
 }
-hipError_t launch_pool_init(const DraftState &s, const int *top_tok, const float *top_lp, int k, int root_row,
-                            const int *n_draft, hipStream_t st) {
-  if (k < 1 || k > kMaxTopK) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pool_init_kernel, dim3(1), dim3(64), 0, st, s, top_tok, top_lp, k, root_row, n_draft);
-  return hipGetLastError();
-}
-
 // `step` t in 2..D: the k frontier rows are nodes of depth t-1; their children have depth t.
-__global__ __launch_bounds__(kSelThreads) void pool_expand_kernel(DraftState s, const int *top_tok, const float *top_lp,
-                                                                  int k, int step, const int *n_draft_ptr, int select_next) {
+__global__ __launch_bounds__(kPoolThreads) void pool_expand_kernel(DraftState s, TopRows top, int k, int step, const int *n_draft_ptr, int select_next) {
+  __shared__ TopShared sh;
   __shared__ float sc[kMaxTopK * kMaxTopK];
   __shared__ int old_anc[kMaxTopK * kAncStride];
   __shared__ int old_pool[kMaxTopK];
+  __shared__ float old_sc[kMaxTopK];
   const int t = threadIdx.x, kk = k * k;
   const int n_draft = *n_draft_ptr;
   const int base = *s.n_pool;
-  if (t < k) old_pool[t] = s.front_pool[t];
-  for (int e = t; e < k * kAncStride; e += kSelThreads) old_anc[e] = s.front_anc[e];
-  __syncthreads();
+  if (t < k) { const int p = s.front_pool[t]; old_pool[t] = p; old_sc[t] = s.pool_sc[p]; }
+  if (t < k * kAncStride) old_anc[t] = s.front_anc[t];
+  merge_rows(top, k, k, sh);
   int r = 0, j = 0, tok = 0;
   if (t < kk) {
     r = t / k; j = t % k;                                   // children in (frontier order, best first) order
-    tok = top_tok[r * kMaxTopK + j];
-    const float v = s.pool_sc[old_pool[r]] + top_lp[r * kMaxTopK + j];
+    tok = sh.tok[r * kMaxTopK + j];
+    const float v = old_sc[r] + sh.lp[r * kMaxTopK + j];
     sc[t] = v;
     s.pool_tok[base + t] = tok; s.pool_par[base + t] = old_pool[r]; s.pool_dep[base + t] = step; s.pool_sc[base + t] = v;
   }
@@ -343,10 +375,31 @@ __global__ __launch_bounds__(kSelThreads) void pool_expand_kernel(DraftState s, 
   s.front_slot[rank] = n_draft + (step - 1) * k + rank;
   s.front_pos[rank] = n_draft + 1 + (step - 1);
 }
-hipError_t launch_pool_expand(const DraftState &s, const int *top_tok, const float *top_lp, int k, int step,
-                              const int *n_draft, int select_next, hipStream_t st) {
-  if (k < 1 || k > kMaxTopK || step < 2 || step > kMaxDepth) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pool_expand_kernel, dim3(1), dim3(kSelThreads), 0, st, s, top_tok, top_lp, k, step, n_draft, select_next);
+static_assert(kMaxTopK * kAncStride <= kMaxTopK * 64, "a thread per ancestor entry");
+// The rows' slices, merged by the kernel that follows; of a vocabulary of more than 64 slices by a launch of their own.
+static hipError_t top_rows(const float *logits, int rows, int vocab, int k, float *sc_val, int *sc_idx, float2 *sc_stat, int *top_tok, float *top_lp,
+                           TopRows *top, hipStream_t st) {
+  const int n_slices = (vocab + kTopkSlice - 1) / kTopkSlice;
+  const bool few = n_slices <= 64;
+  *top = TopRows{sc_val, sc_idx, sc_stat, n_slices, few ? nullptr : top_tok, top_lp};
+  return few ? launch_topk_slices(logits, rows, vocab, k, sc_val, sc_idx, sc_stat, st)
+             : launch_rows_topk_logprob(logits, rows, vocab, k, sc_val, sc_idx, sc_stat, top_tok, top_lp, st);
+}
+hipError_t launch_pool_init(const DraftState &s, const float *logits, int vocab, float *sc_val, int *sc_idx, float2 *sc_stat, int *top_tok, float *top_lp,
+                            int k, int root_row, const int *n_draft, hipStream_t st) {
+  TopRows top;
+  const hipError_t e = top_rows(logits, 1, vocab, k, sc_val, sc_idx, sc_stat, top_tok, top_lp, &top, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(pool_init_kernel, dim3(1), dim3(64), 0, st, s, top, k, root_row, n_draft);
+  return hipGetLastError();
+}
+hipError_t launch_pool_expand(const DraftState &s, const float *logits, int vocab, float *sc_val, int *sc_idx, float2 *sc_stat, int *top_tok, float *top_lp,
+                              int k, int step, const int *n_draft, int select_next, hipStream_t st) {
+  if (step < 2 || step > kMaxDepth) return hipErrorInvalidValue;
+  TopRows top;
+  const hipError_t e = top_rows(logits, k, vocab, k, sc_val, sc_idx, sc_stat, top_tok, top_lp, &top, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(pool_expand_kernel, dim3(1), dim3(k * 64), 0, st, s, top, k, step, n_draft, select_next);
   return hipGetLastError();
 }
 
@@ -812,9 +865,11 @@ __global__ __launch_bounds__(kSelThreads) void compact_kv_kernel(const AcceptRes
 // Features of root + accepted rows and the matching tokens for the next draft root step.
 template <typename T>
 __global__ __launch_bounds__(kSelThreads) void handoff_kernel(const AcceptResult *res, const T *feat, int d, T *pend_feat,
-                                                              int *pend_tok, int *root_tok, int *n_committed) {
+                                                              int *pend_tok, int *root_tok, int *n_committed, AcceptResult *host_res) {
   const int r = blockIdx.x, m = res->n_acc;
   if (r == 0 && threadIdx.x == 0) *n_committed += 1 + m;      // root + accepted tokens are now in the cache
+  // the result for the host, straight into its memory: a copy launched behind this kernel was 6 us more to wait for
+  if (r == kMaxDepth && threadIdx.x < sizeof(AcceptResult) / sizeof(int)) ((int *)host_res)[threadIdx.x] = ((const int *)res)[threadIdx.x];
   if (r > m) return;
   const T *src = feat + (size_t)res->node[r] * d;
   T *dst = pend_feat + (size_t)r * d;
@@ -826,7 +881,7 @@ __global__ __launch_bounds__(kSelThreads) void handoff_kernel(const AcceptResult
 }
 hipError_t launch_commit(int dtype, const AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride,
                          int n_layers, int row_elems, int n, const void *feat, int d, void *pend_feat, int *pend_tok,
-                         int *root_tok, int *n_committed, hipStream_t st) {
+                         int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st) {
   const size_t esz = dtype == 1 ? 2 : 4;
   const int row_bytes = (int)(row_elems * esz);
   if (row_bytes % 16 != 0 || n_layers < 1) return hipErrorInvalidValue;
@@ -838,10 +893,45 @@ hipError_t launch_commit(int dtype, const AcceptResult *res, void *kv_base, size
   if (e != hipSuccess) return e;
   if (dtype == 1)
     hipLaunchKernelGGL(handoff_kernel<bf16_t>, dim3(kMaxDepth + 1), dim3(kSelThreads), 0, st, res, (const bf16_t *)feat, d,
-                       (bf16_t *)pend_feat, pend_tok, root_tok, n_committed);
+                       (bf16_t *)pend_feat, pend_tok, root_tok, n_committed, host_res);
   else
     hipLaunchKernelGGL(handoff_kernel<float>, dim3(kMaxDepth + 1), dim3(kSelThreads), 0, st, res, (const float *)feat, d,
-                       (float *)pend_feat, pend_tok, root_tok, n_committed);
+                       (float *)pend_feat, pend_tok, root_tok, n_committed, host_res);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(kSelThreads) void prefill_handoff_kernel(const u32x4_t *feat, int pieces, const int *root_tok, int n_prompt, u32x4_t *pend_feat,
+                                                                      int *pend_tok, int *n_committed, AcceptResult *res, int *host_first) {
+  if (threadIdx.x == 0) {
+    res->n_acc = 0;
+    const int tok = *root_tok;
+    *pend_tok = tok; *host_first = tok; *n_committed = n_prompt;
+  }
+  for (int c = threadIdx.x; c < pieces; c += kSelThreads) pend_feat[c] = feat[c];
+}
+hipError_t launch_prefill_handoff(const void *feat, int row_bytes, const int *root_tok, int n_prompt, void *pend_feat, int *pend_tok,
+                                  int *n_committed, AcceptResult *res, int *host_first, hipStream_t st) {
+  if (row_bytes < 16 || row_bytes % 16 || n_prompt < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(prefill_handoff_kernel, dim3(1), dim3(kSelThreads), 0, st, (const u32x4_t *)feat, row_bytes / 16, root_tok, n_prompt,
+                     (u32x4_t *)pend_feat, pend_tok, n_committed, res, host_first);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(64) void pending_rows_kernel(const AcceptResult *res, const int *n_committed, const int *pend_tok, int rows, int *token, int *src,
+                                                          int *pos, int *slot, int *depth, int *base) {
+  const int i = threadIdx.x;
+  if (i >= rows) return;
+  const int m = res->n_acc, n = *n_committed, first = n - 1 - m, p = max(m - i, 0);
+  token[i] = pend_tok[p]; src[i] = p;
+  pos[i] = first + p + 1;
+  slot[i] = i <= m ? first + p : n + (i - m - 1);
+  depth[i] = p;
+  if (i == 0) *base = first;
+}
+hipError_t launch_pending_rows(const AcceptResult *res, const int *n_committed, const int *pend_tok, int rows, int *token, int *src, int *pos, int *slot,
+                               int *depth, int *base, hipStream_t st) {
+  if (rows < 1 || rows > kMaxDepth + 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(pending_rows_kernel, dim3(1), dim3(64), 0, st, res, n_committed, pend_tok, rows, token, src, pos, slot, depth, base);
   return hipGetLastError();
 }
 
