@@ -107,9 +107,11 @@ struct RowMerge {
 template <typename T> struct PartLds {
   static constexpr int vrow(int hd) { return hd * (int)sizeof(T) + 16; }   // +16: conflict-free row writes
 };
-template <typename T, int HD, int G>
+// AHEAD: the next 64 keys' rows are requested before this 64's are used (a second set of registers: where few wavefronts run).
+// emit(head of the group, reference, sum, outputs) takes the result.
+template <typename T, int HD, int G, bool AHEAD, typename Emit>
 __device__ __forceinline__ void attn_part_body(const AttnArgs &a, int i, int hk, int part, int lane, float (*qs)[HD],
-                                               unsigned char *vs, bool store) {
+                                               unsigned char *vs, Emit emit) {
   constexpr int EPL = Chunk<T>::kEpl;
   constexpr int DPL = HD / 64;                       // output dims per lane (contiguous)
   constexpr int VROW = PartLds<T>::vrow(HD);         // LDS bytes per staged value row
@@ -134,20 +136,25 @@ __device__ __forceinline__ void attn_part_body(const AttnArgs &a, int i, int hk,
   const T *kbase = (const T *)a.kcache + (size_t)hk * HD;
   const T *vbase = (const T *)a.vcache + (size_t)hk * HD;
 
-  for (int kb = k_lo; kb < k_hi; kb += 64) {
-    // lane = key: this lane's key row and value row (all loads issued before anything is used)
-    const int kq = kb + lane;
-    const bool valid = kq < k_hi;
+  struct Rows { u32x4_t k[HD / EPL], v[HD / EPL]; };
+  auto load = [&](Rows &r, int kb) __attribute__((always_inline)) {
+    // lane = key: this lane's key row and value row (all loads issued before anything is used);
     // lanes past the range re-read the last key of the range (initialised data; their weight is 0)
-    const int kr = valid ? kq : k_hi - 1;
+    const int kr = min(kb + lane, k_hi - 1);
     const int slot = kr < base ? kr : base + (anc ? anc[kr - base] : kr - base);
     const T *kptr = kbase + (size_t)slot * row_stride;
     const T *vptr = vbase + (size_t)slot * row_stride;
-    u32x4_t kc[HD / EPL], vc[HD / EPL];
 #pragma unroll
-    for (int dc = 0; dc < HD / EPL; dc++) kc[dc] = *(const u32x4_t *)(kptr + dc * EPL);
+    for (int dc = 0; dc < HD / EPL; dc++) r.k[dc] = *(const u32x4_t *)(kptr + dc * EPL);
 #pragma unroll
-    for (int dc = 0; dc < HD / EPL; dc++) vc[dc] = *(const u32x4_t *)(vptr + dc * EPL);
+    for (int dc = 0; dc < HD / EPL; dc++) r.v[dc] = *(const u32x4_t *)(vptr + dc * EPL);
+  };
+  Rows now, next;
+  load(now, k_lo);
+  for (int kb = k_lo; kb < k_hi; kb += 64) {
+    const bool valid = kb + lane < k_hi;
+    if (AHEAD && kb + 64 < k_hi) load(next, kb + 64);
+    const u32x4_t (&kc)[HD / EPL] = now.k, (&vc)[HD / EPL] = now.v;
     wave_lds_sync();                                   // qs written (first pass) / previous block's vs reads done
     float s[G];
 #pragma unroll
@@ -197,15 +204,13 @@ __device__ __forceinline__ void attn_part_body(const AttnArgs &a, int i, int hk,
           for (int dd = 0; dd < DPL; dd++) o[gh][dd] = fmaf(w, vv[kk][dd], o[gh][dd]);
         }
     }
+    if (kb + 64 < k_hi) {
+      if constexpr (AHEAD) now = next;
+      else load(now, kb + 64);
+    }
   }
-  if (!store) return;
 #pragma unroll
-  for (int gh = 0; gh < G; gh++) {
-    float *dst = a.part + (((size_t)i * a.hq + hk * G + gh) * a.max_parts + part) * (HD + 2);
-    if (lane == 0) { dst[0] = m_run[gh]; dst[1] = l_run[gh]; }
-#pragma unroll
-    for (int dd = 0; dd < DPL; dd++) dst[2 + lane * DPL + dd] = o[gh][dd];
-  }
+  for (int gh = 0; gh < G; gh++) emit(gh, m_run[gh], l_run[gh], o[gh]);
 }
 
 // The tail of a row in the hybrid path: positions [max(p - kMaxDepth, 0), p], at most kTailKeys = 16 keys,
@@ -308,7 +313,44 @@ template <typename T, int HD, int G>
 __global__ __launch_bounds__(64) void attn_part_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) float qs[G][HD];
   __shared__ __attribute__((aligned(16))) unsigned char vs[64 * PartLds<T>::vrow(HD)];
-  attn_part_body<T, HD, G>(a, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x, qs, vs, true);
+  const int lane = threadIdx.x;
+  float *const dst0 = a.part + (((size_t)blockIdx.x * a.hq + blockIdx.y * G) * a.max_parts + blockIdx.z) * (HD + 2);
+  attn_part_body<T, HD, G, false>(a, blockIdx.x, blockIdx.y, blockIdx.z, lane, qs, vs, [&](int gh, float m, float l, const float (&o)[HD / 64]) __attribute__((always_inline)) {
+    float *dst = dst0 + (size_t)gh * a.max_parts * (HD + 2);
+    if (lane == 0) { dst[0] = m; dst[1] = l; }
+#pragma unroll
+    for (int dd = 0; dd < HD / 64; dd++) dst[2 + lane * (HD / 64) + dd] = o[dd];
+  });
+}
+
+// fp32 storage, short contexts: grid (rows, kv heads), a wavefront per part (up to kRowParts), the parts merged in the LDS as attn_combine_kernel merges them,
+// bit for bit.  One launch instead of two and no partial outputs in memory: request of the small fp32 model 4.76 -> 4.63 ms (bound: latency; the launch saved is 1.2 us
+// of each layer and draft pass, the partial outputs' way as much again).
+constexpr int kRowParts = 4;
+template <int HD, int G> constexpr int row_wave_bytes() { return G * HD * 4 + 64 * PartLds<float>::vrow(HD); }
+template <int HD, int G>
+__global__ __launch_bounds__(kRowParts * 64, 1) void attn_row_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char row_lds[];
+  __shared__ float pm[kRowParts][G], pl[kRowParts][G];
+  const int i = blockIdx.x, hk = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_parts = attn_parts_covering((a.base_ptr ? *a.base_ptr : a.base) + a.depth[i] + 1);
+  unsigned char *const mine = row_lds + wave * row_wave_bytes<HD, G>();
+  attn_part_body<float, HD, G, HD == 64>(a, i, hk, wave, lane, (float (*)[HD])mine, mine + G * HD * 4, [&](int gh, float m, float l, const float (&o)[HD / 64]) __attribute__((always_inline)) {
+    if (lane == 0) { pm[wave][gh] = m; pl[wave][gh] = l; }
+#pragma unroll
+    for (int dd = 0; dd < HD / 64; dd++) ((float *)mine)[gh * HD + lane * (HD / 64) + dd] = o[dd];   // (the query's place)
+  });
+  __syncthreads();
+  for (int e = threadIdx.x; e < G * HD; e += blockDim.x) {
+    RowMerge row;
+    float o = 0.f;
+    for (int t = 0; t < n_parts; t++) {
+      float w;
+      const float turn = row.step(pm[t][e / HD], pl[t][e / HD], w);
+      o = fmaf(*(const float *)(row_lds + t * row_wave_bytes<HD, G>() + e * 4), w, o * turn);
+    }
+    ((float *)a.out)[((size_t)i * a.hq + (size_t)hk * G) * HD + e] = o / row.l;
+  }
 }
 
 // grid (rows, hq); block HD threads.  Merges the row's parts in ascending order (RowMerge); in hybrid mode these are
@@ -648,6 +690,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int v = 0; v < 16; v += 4) store4_any(dst + 2 + db * 32 + 2 * v + 4 * g, o[db][v], o[db][v + 1], o[db][v + 2], o[db][v + 3]);
 }
 
+// Dynamic LDS beyond 64 KB, once per device: the attribute belongs to the device's copy of the code.
+static hipError_t allow_lds(const void *kernel, int bytes, bool (&done)[64]) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess || (dev >= 0 && dev < 64 && done[dev])) return e;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess && dev >= 0 && dev < 64) done[dev] = true;
+  return e;
+}
+
 template <int HD, int G, int NW>
 static hipError_t launch_hybrid(AttnArgs a, int q_groups, hipStream_t st) {
   a.q_groups = q_groups;
@@ -880,15 +932,9 @@ __global__ __launch_bounds__(256) void attn_tail_kernel(AttnArgs a) {
 template <int HD, int G, int WAVES>
 static hipError_t launch_chain(AttnArgs a, hipStream_t st) {
   constexpr int kLds = ChainLds<HD, WAVES>::total;
-  static bool attr_done[64] = {};                             // per device: the attribute belongs to the device's copy of the code
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  static bool lds_allowed[64] = {};
+  hipError_t e = allow_lds((const void *)attn_chain_kernel<HD, WAVES>, kLds, lds_allowed);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64 || !attr_done[dev]) {
-    e = hipFuncSetAttribute((const void *)attn_chain_kernel<HD, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-    if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < 64) attr_done[dev] = true;
-  }
   const long long grid = (long long)a.hq * ((a.rows + WAVES * 32 - 1) / (WAVES * 32)), items = (long long)a.rows * a.hkv;
   if (grid > 0x7FFFFFFFll || items > 0x7FFFFFFFll) return hipErrorInvalidValue;
   a.max_parts = 1;                                            // the tail's partial is the only one
@@ -944,6 +990,18 @@ static hipError_t launch_thg(AttnArgs a, int max_pos, hipStream_t st) {
     a.bulk_blocks = 0;
     const int n_parts = attn_parts_covering(max_pos + 1);
     if (n_parts > a.max_parts) return hipErrorInvalidValue;
+    // (beyond one wavefront per SIMD the wavefronts of the two launches, with fewer registers and less LDS each, fill the chip better)
+    if constexpr (HD * G <= 128) {                            // (more heads to a key head do not fit the registers)
+      if (n_parts <= kRowParts && (long long)a.rows * a.hkv * n_parts <= 1024) {
+        constexpr int kWaveLds = row_wave_bytes<HD, G>();
+        static_assert(kRowParts * kWaveLds <= 158 * 1024, "a wavefront per part");
+        static bool lds_allowed[64] = {};
+        e = allow_lds((const void *)attn_row_kernel<HD, G>, kRowParts * kWaveLds, lds_allowed);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((attn_row_kernel<HD, G>), dim3(a.rows, a.hkv), dim3(n_parts * 64), n_parts * kWaveLds, st, a);
+        return hipGetLastError();
+      }
+    }
     hipLaunchKernelGGL((attn_part_kernel<T, HD, G>), dim3(a.rows, a.hkv, n_parts), dim3(64), 0, st, a);
     e = hipGetLastError();
   }

@@ -84,6 +84,55 @@ def test_filling_the_cache_captures_each_graph_once(env, tiny_gpu, tree):
     assert got == P.Engine(sh, dw, tree=tree).generate(prompt, len(got))[0]
 
 
+def test_pending_pairs_beyond_the_drafted_depth(env, tiny_gpu):
+    """Accepted chains of up to nine tokens in trees drafted two deep: the draft's root step over more pending pairs than the captured one has rows, and the
+    captured one again after them.  Tokens are the plain stream's, trees and features the oracle's, in graphs and without."""
+    torch, P = env
+    sh, hw, w64, prompt, dw = tiny_gpu
+    gen, plan = 40, [9, 0, 1, 2, 3, 8, 1, 0, 2]
+    greedy = oracle.greedy_decode(w64, sh, prompt, gen + 16)
+
+    def hook_for(calls):
+        def hook(n_committed, t):
+            want = plan[len(calls) % len(plan)]
+            calls.append(want)
+            if want > 2:                                       # a chain of its own instead of the drafted tree
+                at = n_committed - len(prompt) + 1
+                for j in range(1, t.n_nodes):
+                    t.parent[j], t.depth[j] = (j - 1, j) if j <= want else (0, 1)
+                    t.token[j] = greedy[at + j - 1] if j <= want else (greedy[at] + 1) % sh.vocab
+            return t
+        return hook
+    runs = []
+    for graphs in (True, False):
+        calls, rec = [], []
+        eng = P.Engine(sh, dw, tree=(2, 4, 12), graphs=graphs)
+        h = hook_for(calls)
+        got, taus = eng.generate(prompt, gen, tree_hook=lambda e, t: h(e.committed, t), record=rec)
+        assert got == greedy[:gen] and max(taus) == 10
+        runs.append((taus, rec))
+    assert runs[0][0] == runs[1][0]
+    for a, b in zip(runs[0][1], runs[1][1]):
+        assert list(a["tree"].token) == list(b["tree"].token) and list(a["tree"].parent) == list(b["tree"].parent)
+        assert np.array_equal(a["tree"].score, b["tree"].score) and np.array_equal(a["logits"], b["logits"])
+
+
+def test_vocabulary_of_more_than_64_slices(env):
+    """The candidate pool's kernels merge up to 64 slices of the vocabulary themselves; of a larger one the rows' lists come merged."""
+    torch, P = env
+    sh = wl.TINY.with_(d_model=64, d_ffn=128, vocab=262144 + 4097)
+    hw = wl.make_weights(sh)
+    prompt = wl.make_prompt(sh)
+    dw = P.upload_weights(hw, sh.dtype)
+    w64 = as_dtype(hw, np.float64)
+    rec, orec = [], []
+    got, taus = P.Engine(sh, dw).generate(prompt, 6, record=rec)
+    want, _ = oracle.spec_decode(w64, sh, prompt, 6, record=orec)
+    assert got == want == P.Engine(sh, dw, tree=(1, 1, 1)).generate(prompt, 6)[0]
+    for a, b in zip(rec, orec):
+        assert list(a["tree"].token) == list(b["tree"].token) and list(a["tree"].parent) == list(b["tree"].parent)
+
+
 @pytest.mark.parametrize("shape", [(1, 1, 2), (2, 3, 5), (15, 1, 16), (3, 16, 40), (6, 10, 60), (15, 16, 128)],
                          ids=lambda s: "D%d-K%d-N%d" % s)
 def test_tiny_fp32_tree_shapes_match_oracle(env, tiny_gpu, shape):

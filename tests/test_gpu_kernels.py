@@ -430,6 +430,22 @@ def test_attention_tree_row_equals_compacted_chain_row(env):
         assert torch.equal(one[0], tree_out[i])
 
 
+@pytest.mark.parametrize("hq,hkv,hd,base,rows", [(16, 16, 64, 95, 90), (8, 4, 64, 200, 160), (8, 8, 128, 100, 90), (4, 4, 64, 380, 140)])
+def test_fp32_attention_rows_alone_have_the_bits_of_many(env, hq, hkv, hd, base, rows):
+    # few rows over up to 512 keys: one launch whose wavefronts take a part each; many rows, or more keys: partial outputs in memory and a merge.  Rows
+    # across the edges of the 128-key parts and of their 64-key halves
+    torch, P = env
+    rng = np.random.default_rng(hq + base)
+    q = to_dev(torch, rand_storage(rng, (rows, hq * hd), "fp32"), "fp32")
+    kc = to_dev(torch, rand_storage(rng, (base + rows, hkv * hd), "fp32"), "fp32")
+    vc = to_dev(torch, rand_storage(rng, (base + rows, hkv * hd), "fp32"), "fp32")
+    dep = torch.arange(rows, dtype=torch.int32, device="cuda")
+    run = lambda a, b: P.spec_k_attention(q[a:b].contiguous(), kc, vc, base, dep[a:b].contiguous(), None, hq, hkv, hd)
+    whole = run(0, rows)
+    for a in range(0, rows, 5):
+        assert torch.equal(run(a, min(a + 5, rows)), whole[a:a + 5])
+
+
 @pytest.mark.parametrize("rows,vocab,k", [(1, 1024, 4), (4, 1024, 4), (10, 32000, 10), (10, 128256, 10), (3, 5000, 16), (16, 4097, 7)])
 def test_topk_logprob_matches_oracle(env, rows, vocab, k):
     torch, P = env
