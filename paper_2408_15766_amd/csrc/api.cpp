@@ -91,6 +91,14 @@ struct spec_ctx {
   float *t_sc = nullptr;
   DraftState ds{};
   AcceptResult *acc = nullptr;
+  // Row kernels that run inside the launch of the projection behind them (GemmHead, fp32): what they read and what the launch writes lie in
+  // different buffers, so sums and residual rows of forwards of up to kMaxNodes rows alternate between two.
+  float *h2 = nullptr, *part2 = nullptr;
+  size_t part2_floats = 0;
+  float *h_now = nullptr, *part_now = nullptr;   // the residual rows as they are; where the last partial sums went
+  GemmHead head{};                        // a row kernel that waits for the projection that reads its rows, head_x (nullptr: none)
+  void *head_x = nullptr;
+  int head_rows = 0;
   HostStage *stage = nullptr;
   HostStage *stage_dev = nullptr;         // ... as kernels see it: the drafted tree, the acceptance and the first token are written there
   size_t part_floats = 0;
@@ -217,12 +225,13 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   const int k = std::max(1, c.tree_topk), D = std::max(1, c.tree_depth);
   const int seq_draft = c.max_seq + D * k;
   const int max_parts = (c.max_seq + D * k) / kAttnPart + 2;   // parts of the longest row + the tail slot
-  size_t part_floats = 0;
+  size_t part_floats = 0, part2_floats = 0;
   {
     struct { int rows, in; } g[5] = {{dq + 2 * dkv, d}, {d, dq}, {gate_up_rows(f), d}, {d, f}, {d, 2 * d}};
     for (auto &e : g) {
       GemmPlan p = plan_gemm(e.rows, e.in, c.dtype);
       part_floats = std::max(part_floats, (size_t)p.n_split * std::min(m_max, kPartRows) * e.rows);
+      part2_floats = std::max(part2_floats, (size_t)p.n_split * std::min(m_max, kMaxNodes) * e.rows);
       part_floats = std::max(part_floats, std::min((size_t)v, (size_t)p.n_split * 512 * e.rows));   // the ratio rule's scratch, small models
     }
   }
@@ -293,12 +302,16 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   TAKE(ds.front_slot, int *, kMaxTopK * 4)
   TAKE(ds.front_pos, int *, kMaxTopK * 4)
   TAKE(acc, AcceptResult *, sizeof(AcceptResult))
+  if (c.dtype != SPEC_DTYPE_BF16) {
+    TAKE(h2, float *, (size_t)std::min(m_max, kMaxNodes) * d * 4)
+    TAKE(part2, float *, part2_floats * 4)
+  }
 #undef TAKE
   if (x) {
     x->esz = (int)esz; x->m_small = m_small; x->m_max = m_max; x->max_parts = max_parts; x->seq_draft = seq_draft;
     x->t_kv_stride = (size_t)c.max_seq * dkv; x->t_layer_stride = 2 * x->t_kv_stride;
     x->d_kv_stride = (size_t)seq_draft * dkv;
-    x->part_floats = part_floats;
+    x->part_floats = part_floats; x->part2_floats = part2_floats;
   }
   return L.total;
 }
@@ -331,6 +344,33 @@ void harvest_profile(spec_ctx *c) {
 // ---- launch sequences ------------------------------------------------------------------------
 struct Seg { const void *w; int rows; };
 
+// A row kernel that waits for a projection, as a launch of its own.
+int flush_head(spec_ctx *c) {
+  if (c->head_x == nullptr) return SPEC_OK;
+  const spec_config &g = c->cfg;
+  const GemmHead &h = c->head;
+  void *x = c->head_x;
+  const int rows = c->head_rows;
+  c->head_x = nullptr;
+  switch (h.kind) {
+    case kHeadSums:
+      HIPCHK(c, launch_reduce_add_norm(g.dtype, h.part, h.n_split, h.m_pad, h.ldp, rows, h.d, h.residual, h.norm_w, h.eps, c->h_now, x, c->stream));
+      break;
+    case kHeadEmbed:
+      HIPCHK(c, launch_embed_norm(g.dtype, h.embed, h.token, rows, h.d, h.norm_w, h.eps, c->h_now, x, c->stream, h.rope));
+      break;
+    default:
+      HIPCHK(c, launch_concat_feat_embed(g.dtype, h.feat, h.src_row, h.embed, h.token, rows, h.d, x, c->stream, h.rope));
+  }
+  return SPEC_OK;
+}
+// The rows of x are made by the projection that reads them (at the latest by the next one), where the forward is small enough for that.
+int defer_head(spec_ctx *c, const GemmHead &h, int rows, void *x) {
+  c->head = h; c->head_rows = rows; c->head_x = x;
+  return c->cfg.dtype == SPEC_DTYPE_BF16 || rows > kMaxNodes ? flush_head(c) : SPEC_OK;
+}
+
+// out == nullptr: partial sums, into one of their buffers (c->part_now behind the call)
 int run_gemm(spec_ctx *c, const void *x, int ldx, int m, int in, const Seg *segs, int nseg, float *out, int ldp, int m_pad,
              const GemmPlan &p, void *swiglu_act = nullptr) {
   GemmArgs a{};
@@ -346,13 +386,25 @@ int run_gemm(spec_ctx *c, const void *x, int ldx, int m, int in, const Seg *segs
     blocks += a.seg_blocks[s];
   }
   a.total_blocks = blocks;
-  a.part = out; a.ldp = ldp; a.m_pad = m_pad;
+  a.ldp = ldp; a.m_pad = m_pad;
   a.n_split = p.n_split; a.fold = p.fold;
-  if (out == c->part && !swiglu_act && (size_t)(p.fold ? 1 : p.n_split) * m_pad * ldp > c->part_floats)
+  const bool sums = out == nullptr && swiglu_act == nullptr;
+  bool headed = false;
+  if (c->head_x != nullptr) {                                   // a row kernel waits
+    GemmHead &h = c->head;
+    h.h_in = c->h_now; h.h_out = c->h_now == c->h ? c->h2 : c->h;
+    headed = c->head_x == x && c->head_rows == m && gemm_takes_head(c->cfg.dtype, a, h);
+    if (!headed) { const int rc = flush_head(c); if (rc) return rc; }
+    c->head_x = nullptr;
+    if (headed && h.kind != kHeadConcat) c->h_now = h.h_out;
+    if (headed && sums && h.kind == kHeadSums) c->part_now = h.part == c->part ? c->part2 : c->part;
+  }
+  a.part = out ? out : c->part_now;
+  if (sums && (size_t)(p.fold ? 1 : p.n_split) * m_pad * ldp > (c->part_now == c->part ? c->part_floats : c->part2_floats))
     return fail(c, SPEC_ECAP, "%d splits of %d x %d partial sums exceed the workspace", p.n_split, m_pad, ldp);
   const bool ev = c->prof_level >= 2 && c->gemm_bucket && c->n_gemm_ev < kMaxGemmEvents;
   if (ev) (void)hipEventRecord(c->ev_gemm[2 * c->n_gemm_ev], c->stream);
-  HIPCHK(c, launch_gemm(c->cfg.dtype, a, c->stream));
+  HIPCHK(c, launch_gemm(c->cfg.dtype, a, c->stream, headed ? &c->head : nullptr));
   if (ev) {
     (void)hipEventRecord(c->ev_gemm[2 * c->n_gemm_ev + 1], c->stream);
     c->gemm_ev_bucket[c->n_gemm_ev] = c->gemm_bucket;
@@ -382,10 +434,26 @@ int project(spec_ctx *c, const void *x, int m, int in, const Seg *segs, int nseg
   const int sets = p.fold ? 1 : p.n_split;
   for (int r0 = 0; r0 < m; r0 += step) {
     const int n = std::min(step, m - r0);
-    int rc = run_gemm(c, (const char *)x + (size_t)r0 * in * c->esz, in, n, in, segs, nseg, c->part, rows, n, p);
+    int rc = run_gemm(c, (const char *)x + (size_t)r0 * in * c->esz, in, n, in, segs, nseg, nullptr, rows, n, p);
     if (rc) return rc;
-    HIPCHK(c, reduce(r0, n, sets));
+    rc = reduce(r0, n, sets);
+    if (rc) return rc;
   }
+  return SPEC_OK;
+}
+
+// h = (residual ? h : 0) + the sums of rows r0 .. r0 + n of the forward's m; x = the normed rows.
+int add_norm_rows(spec_ctx *c, int r0, int n, int split, int m, int residual, const void *norm, void *x) {
+  const int d = c->cfg.d_model;
+  if (n == m) {
+    GemmHead h{};
+    h.kind = kHeadSums; h.d = d;
+    h.part = c->part_now; h.n_split = split; h.m_pad = n; h.ldp = d; h.residual = residual;
+    h.norm_w = (const float *)norm; h.eps = c->cfg.rms_eps;
+    return defer_head(c, h, m, x);
+  }
+  HIPCHK(c, launch_reduce_add_norm(c->cfg.dtype, c->part_now, split, n, d, n, d, residual, norm, c->cfg.rms_eps, c->h_now + (size_t)r0 * d,
+                                   (char *)x + (size_t)r0 * d * c->esz, c->stream));
   return SPEC_OK;
 }
 
@@ -396,8 +464,9 @@ int layer_keys_values(spec_ctx *c, const spec_layer_weights &lw, char *kcache, c
   const int dq = g.n_q_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim;
   const Seg segs[2] = {{lw.wk, dkv}, {lw.wv, dkv}};
   return project(c, c->x, m, g.d_model, segs, 2, 2 * dkv, [&](int r0, int n, int split) {
-    return launch_reduce_rope_kv(g.dtype, c->part, split, n, 2 * dkv, n, 0, g.n_kv_heads, g.head_dim, c->rope + (size_t)r0 * (g.head_dim / 2),
-                                 rt.slot + r0, nullptr, kcache, vcache, c->stream);
+    HIPCHK(c, launch_reduce_rope_kv(g.dtype, c->part_now, split, n, 2 * dkv, n, 0, g.n_kv_heads, g.head_dim, c->rope + (size_t)r0 * (g.head_dim / 2),
+                                    rt.slot + r0, nullptr, kcache, vcache, c->stream));
+    return SPEC_OK;
   }, dq + 2 * dkv);
 }
 
@@ -410,15 +479,14 @@ int layer_forward(spec_ctx *c, const spec_layer_weights &lw, char *kcache, char 
   const int dt = g.dtype;
   auto at = [](const void *p, size_t r, size_t row_bytes) { return (void *)((char *)p + r * row_bytes); };
   auto add_norm = [&](const void *norm, void *out) {          // h += the sums; out = the normed rows
-    return [&, norm, out](int r0, int n, int split) {
-      return launch_reduce_add_norm(dt, c->part, split, n, d, n, d, 1, norm, g.rms_eps, c->h + (size_t)r0 * d, at(out, r0, d * c->esz), c->stream);
-    };
+    return [&, norm, out](int r0, int n, int split) { return add_norm_rows(c, r0, n, split, m, 1, norm, out); };
   };
   {
     const Seg segs[3] = {{lw.wq, dq}, {lw.wk, dkv}, {lw.wv, dkv}};
     int rc = project(c, c->x, m, d, segs, 3, dq + 2 * dkv, [&](int r0, int n, int split) {
-      return launch_reduce_rope_kv(dt, c->part, split, n, dq + 2 * dkv, n, g.n_q_heads, g.n_kv_heads, g.head_dim, c->rope + (size_t)r0 * (g.head_dim / 2),
-                                   rt.slot + r0, at(c->qbuf, r0, (size_t)dq * 4), kcache, vcache, c->stream);
+      HIPCHK(c, launch_reduce_rope_kv(dt, c->part_now, split, n, dq + 2 * dkv, n, g.n_q_heads, g.n_kv_heads, g.head_dim, c->rope + (size_t)r0 * (g.head_dim / 2),
+                                      rt.slot + r0, at(c->qbuf, r0, (size_t)dq * 4), kcache, vcache, c->stream));
+      return SPEC_OK;
     });
     if (rc) return rc;
   }
@@ -445,11 +513,12 @@ int layer_forward(spec_ctx *c, const spec_layer_weights &lw, char *kcache, char 
     int rc;
     if (p.n_split == 1) {
       const Seg segs[1] = {{lw.w_gate_up, f}};
-      rc = run_gemm(c, c->x, d, m, d, segs, 1, c->part, gu, m, p, c->act);
+      rc = run_gemm(c, c->x, d, m, d, segs, 1, nullptr, gu, m, p, c->act);
     } else {
       const Seg segs[1] = {{lw.w_gate_up, gu}};
       rc = project(c, c->x, m, d, segs, 1, gu, [&](int r0, int n, int split) {
-        return launch_reduce_swiglu(dt, c->part, split, n, gu, n, f, at(c->act, r0, (size_t)f * c->esz), c->stream);
+        HIPCHK(c, launch_reduce_swiglu(dt, c->part_now, split, n, gu, n, f, at(c->act, r0, (size_t)f * c->esz), c->stream));
+        return SPEC_OK;
       });
     }
     if (rc) return rc;
@@ -474,9 +543,15 @@ int lm_head(spec_ctx *c, const void *x, int rows, float *logits) {
 // sizes: the launch sequence is then independent of the cycle and can be captured into a graph.
 int target_forward(spec_ctx *c, int m, int base, const RowTables &rt, int max_pos, const int *base_ptr = nullptr) {
   const spec_config &g = c->cfg;
-  // (the launch that opens the forward also fills the rotary table of its rows)
-  HIPCHK(c, launch_embed_norm(g.dtype, c->w.embed, rt.token, m, g.d_model, c->layers[0].attn_norm, g.rms_eps, c->h, c->x, c->stream,
-                              rt.pos, g.head_dim, g.rope_theta, c->rope));
+  c->h_now = c->h; c->part_now = c->part;
+  c->head_x = nullptr;
+  GemmHead open{};                                              // (what opens the forward also fills the rotary table of its rows)
+  open.kind = kHeadEmbed; open.d = g.d_model;
+  open.norm_w = (const float *)c->layers[0].attn_norm; open.eps = g.rms_eps;
+  open.embed = (const float *)c->w.embed; open.token = rt.token;
+  open.rope = make_rope_fill(rt.pos, g.head_dim, g.rope_theta, c->rope);
+  const int opened = defer_head(c, open, m, c->x);
+  if (opened) return opened;
   for (int l = 0; l < g.n_layers; l++) {
     char *kc = c->kv_t + (size_t)l * c->t_layer_stride * c->esz;
     char *vc = kc + c->t_kv_stride * c->esz;
@@ -496,12 +571,18 @@ int draft_forward(spec_ctx *c, int m, int base, const void *feat, const int *src
   const spec_config &g = c->cfg;
   const int d = g.d_model;
   if (!keys_only && m > c->m_small) return fail(c, SPEC_EINVAL, "draft: %d rows", m);   // gfeat holds no more
-  HIPCHK(c, launch_concat_feat_embed(g.dtype, feat, src_row, c->w.embed, rt.token, m, d, c->xcat, c->stream, rt.pos, g.head_dim,
-                                     g.rope_theta, c->rope));
+  int rc = flush_head(c);                                       // (feat may be rows that are still to be made)
+  if (rc) return rc;
+  c->h_now = c->h; c->part_now = c->part;
+  GemmHead open{};
+  open.kind = kHeadConcat; open.d = d;
+  open.embed = (const float *)c->w.embed; open.token = rt.token; open.feat = (const float *)feat; open.src_row = src_row;
+  open.rope = make_rope_fill(rt.pos, g.head_dim, g.rope_theta, c->rope);
+  rc = defer_head(c, open, m, c->xcat);
+  if (rc) return rc;
   const Seg segs[1] = {{c->w.draft_fc, d}};
-  int rc = project(c, c->xcat, m, 2 * d, segs, 1, d, [&](int r0, int n, int split) {
-    return launch_reduce_add_norm(g.dtype, c->part, split, n, d, n, d, 0, c->w.draft_layer.attn_norm, g.rms_eps, c->h + (size_t)r0 * d,
-                                  (char *)c->x + (size_t)r0 * d * c->esz, c->stream);
+  rc = project(c, c->xcat, m, 2 * d, segs, 1, d, [&](int r0, int n, int split) {
+    return add_norm_rows(c, r0, n, split, m, 0, c->w.draft_layer.attn_norm, c->x);
   });
   if (rc) return rc;
   char *kc = c->kv_d;
@@ -784,6 +865,7 @@ int spec_draft_tree(spec_ctx *c, spec_tree *out) {
     RowTables rt{c->root_in, c->d_pos, c->d_slot, c->d_depth, nullptr};
     int r = draft_forward(c, root_rows, 0, c->pend_feat, c->root_src, rt, bound ? bound : c->n - 1, c->root_base);
     if (r) return r;
+    if (c->head_x == c->gfeat) c->head_rows = 1;                // row 0's prediction is the only one that is read
     r = lm_head(c, c->gfeat, 1, c->dlogits);
     if (r) return r;
     HIPCHK(c, launch_pool_init(c->ds, c->dlogits, g.vocab, c->sc_val, c->sc_idx, c->sc_stat, c->top_tok, c->top_lp, K, 0, c->t_base, c->stream));

@@ -152,6 +152,26 @@ __device__ __forceinline__ int key_rank(const uint64_t *keys, int n2, uint64_t k
   return rank;
 }
 
+// ---- RMSNorm rows and the rotary table: shared by every kernel that forms them (the same operations in the same order, so the bits do not depend on
+// which does).  Virtual thread t of kNormThreads owns the 4-column groups t, t + kNormThreads, ..; its squares are added up in this order, then
+// over the wavefronts of 64 virtual threads (wave_sum), then over these in ascending order.
+constexpr int kNormThreads = 1024;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+__device__ __forceinline__ float add_squares(float ss, f32x4_t v) {
+  float q = __builtin_fmaf(v.x, v.x, v.y * v.y);
+  q = __builtin_fmaf(v.z, v.z, q);
+  return ss + __builtin_fmaf(v.w, v.w, q);
+}
+__device__ __forceinline__ float norm_scale(float sum, int d, float eps) { return 1.0f / sqrtf(sum / (float)d + eps); }
+// (cos, sin) of pos * theta^(-j/half), the angle formed in double so that large positions keep their phase
+__device__ __forceinline__ float2 rope_entry(int pos, int j, int half, double log2_theta) {
+  const double inv = exp2(-(double)j / (double)half * log2_theta);
+  const double ang = (double)pos * inv;
+  double s, c;
+  sincos(ang, &s, &c);
+  return make_float2((float)c, (float)s);
+}
+
 // Block-wide sum for blocks of up to 16 waves; `sh` needs 16 floats.  Fixed order.
 __device__ __forceinline__ float block_sum(float x, float *sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;

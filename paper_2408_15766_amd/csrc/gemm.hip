@@ -642,9 +642,17 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_mixed_kernel(GemmArgs a
 // Measured (MI355X), against 32 x 32 tiles with all of K in one wavefront: the projections of a 256-wide layer, up to 16 rows,
 // 9.4 -> 3.4 us per launch.  Launches that fill the chip take gemm_f32_tiled_kernel below (same bits).
 // Lane (r = lane % 16, kg = lane / 16) supplies row r and, in step jj of a tile, the four k of piece (g = kg % 2, j = 2 jj + kg / 2).
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-template <int RB>
-__global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
+//
+// KIND: the row kernel that makes x runs inside the launch (HeadKind).  At a 256-wide layer these kernels were a third of a forward's launches, 2 to 3 us each
+// and as much again between them, for 16 KB of work.  Every workgroup makes the rows of its token block for itself, into the LDS (four wavefronts, four
+// rows each; the weights of the first tile are requested before); the workgroups of the first weight block also store them and the residual rows.  The
+// rotary table is filled by a workgroup per token block that has no weights.  Same operations in the same order as the row kernels: same bits.
+// Request of the small fp32 model (66 launches a cycle -> 50) 4.54 -> 4.25 ms.
+constexpr int kHeadCols = 512;                                // widest row
+struct NoHead {};
+template <int KIND> using HeadArg = std::conditional_t<KIND == kHeadNone, NoHead, GemmHead>;
+template <int RB, int KIND>
+__global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a, HeadArg<KIND> head) {
   constexpr int E = RB * 4;                                   // sums per lane
   __shared__ float sums[kGemmWaves][E][kWave];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -652,6 +660,16 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
   const int tiles = (a.m + 15) / 16;                          // per set of rows
   const bool second = (int)blockIdx.z >= tiles;
   const int m0 = ((int)blockIdx.z - (second ? tiles : 0)) * 16, m_loc = min(a.m - m0, 16);
+  if constexpr (KIND == kHeadEmbed || KIND == kHeadConcat) {
+    if (blockIdx.x == gridDim.x - 1) {                        // the rotary table's workgroup
+      if (blockIdx.y == 0)
+        for (int n = tid; n < m_loc * head.rope.half; n += kGemmThreads) {
+          const int i = m0 + n / head.rope.half, j = n % head.rope.half;
+          head.rope.table[i * head.rope.half + j] = rope_entry(head.rope.pos[i], j, head.rope.half, head.rope.log2_theta);
+        }
+      return;
+    }
+  }
   const int by = blockIdx.y, blk = RB == 2 ? (int)blockIdx.x : (int)blockIdx.x >> 1, h0 = RB == 2 ? 0 : (int)blockIdx.x & 1;
   const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
   const int seg = blk < e0 ? 0 : (blk < e1 ? 1 : 2);
@@ -666,24 +684,39 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
 
   const char *w0 = (const char *)seg_w + (size_t)(blk - b0) * n_it_total * kTileBytes + (((kg & 1) * 32 + r) * 16 + (kg >> 1) * 1024);
   const float *xbase = (const float *)(second ? a.x2 : a.x) + (size_t)m0 * a.ldx;
-  const float *xrow = xbase + (size_t)(r < m_loc ? r : 0) * a.ldx;
+  const float *xrow = xbase + (size_t)(r < m_loc ? r : 0) * a.ldx, *erow = nullptr;
+  if constexpr (KIND == kHeadConcat) {
+    const int i = m0 + (r < m_loc ? r : 0);
+    xrow = head.feat + (size_t)(head.src_row ? head.src_row[i] : i) * head.d;
+    erow = head.embed + (size_t)head.token[i] * head.d - head.d;
+  }
+  constexpr bool kRows = KIND == kHeadSums || KIND == kHeadEmbed;
+  constexpr int kXStride = kHeadCols + 4;                     // floats of a row in the LDS
+  __shared__ __attribute__((aligned(16))) float xs[kRows ? 16 * kXStride : 4];
   f32x4_t acc[RB];
 #pragma unroll
   for (int b = 0; b < RB; b++) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   struct Tile { f32x4_t x[4], w[4][RB]; };
   const int n_tiles = max(0, (it_end - it_begin - wave + 3) / 4);   // of this wavefront
-  auto load = [&](Tile &d, int s) {
-    const int it = it_begin + wave + 4 * s;
-    const char *wp = w0 + (size_t)it * kTileBytes;
+  auto load_w = [&](Tile &d, int s) {
+    const char *wp = w0 + (size_t)(it_begin + wave + 4 * s) * kTileBytes;
 #pragma unroll
-    for (int jj = 0; jj < 4; jj++) {
+    for (int jj = 0; jj < 4; jj++)
 #pragma unroll
       for (int b = 0; b < RB; b++) d.w[jj][b] = *(const f32x4_t *)(wp + (h0 + b) * 256 + jj * 2048);
-      const int kk = it * KI + (kg & 1) * 32 + (2 * jj + (kg >> 1)) * 4;
-      d.x[jj] = *(const f32x4_t *)(xrow + (kk < a.in ? kk : 0));   // past K: meets a zero weight
+  };
+  auto load_x = [&](Tile &d, int s) {
+#pragma unroll
+    for (int jj = 0; jj < 4; jj++) {
+      int kk = (it_begin + wave + 4 * s) * KI + (kg & 1) * 32 + (2 * jj + (kg >> 1)) * 4;
+      kk = kk < a.in ? kk : 0;                                // past K: meets a zero weight
+      if constexpr (kRows) d.x[jj] = *(const f32x4_t *)(xs + (r < m_loc ? r : 0) * kXStride + kk);
+      else if constexpr (KIND == kHeadConcat) d.x[jj] = *(const f32x4_t *)((kk < head.d ? xrow : erow) + kk);
+      else d.x[jj] = *(const f32x4_t *)(xrow + kk);
     }
   };
+  auto load = [&](Tile &d, int s) { load_w(d, s); load_x(d, s); };
   auto mul = [&](const Tile &d) {
 #pragma unroll
     for (int jj = 0; jj < 4; jj++)
@@ -693,7 +726,76 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a) {
         for (int b = 0; b < RB; b++) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x[jj][e], d.w[jj][b][e], acc[b], 0, 0, 0);
   };
   Tile cur, nxt;
-  if (n_tiles > 0) load(cur, 0);
+  if constexpr (kRows) {
+    constexpr int NB = kHeadCols / 256;                       // a lane has columns 256 b + 4 lane .. + 3
+    f32x4_t v[4][NB], nw[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+      const int c = b * 256 + lane * 4, cc = c < head.d ? c : 0;
+      if (b * 256 >= head.d) continue;
+      nw[b] = head.norm_w != nullptr ? *(const f32x4_t *)(head.norm_w + cc) : f32x4_t{1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int i = m0 + min(wave + 4 * j, m_loc - 1);
+        if constexpr (KIND == kHeadEmbed) v[j][b] = *(const f32x4_t *)(head.embed + (size_t)head.token[i] * head.d + cc);
+        else v[j][b] = *(const f32x4_t *)(head.part + (size_t)i * head.ldp + cc);
+      }
+    }
+    if constexpr (KIND == kHeadSums) {
+      f32x4_t res[4][NB];
+#pragma unroll
+      for (int b = 0; b < NB; b++) {
+        const int c = b * 256 + lane * 4, cc = c < head.d ? c : 0;
+        if (b * 256 >= head.d || !head.residual) continue;
+#pragma unroll
+        for (int j = 0; j < 4; j++) res[j][b] = *(const f32x4_t *)(head.h_in + (size_t)(m0 + min(wave + 4 * j, m_loc - 1)) * head.d + cc);
+      }
+      if (n_tiles > 0) load_w(cur, 0);
+#pragma unroll
+      for (int b = 0; b < NB; b++) {
+        const int c = b * 256 + lane * 4, cc = c < head.d ? c : 0;
+        if (b * 256 >= head.d) continue;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          for (int sp = 1; sp < head.n_split; sp++)
+            v[j][b] += *(const f32x4_t *)(head.part + ((size_t)sp * head.m_pad + m0 + min(wave + 4 * j, m_loc - 1)) * head.ldp + cc);
+          if (head.residual) v[j][b] = res[j][b] + v[j][b];
+        }
+      }
+    } else {
+      if (n_tiles > 0) load_w(cur, 0);
+    }
+    const bool store = blockIdx.x == 0 && by == 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const int i = wave + 4 * j;
+      if (i >= m_loc) continue;
+      float scale = 1.f;
+      if (head.norm_w != nullptr) {
+        float t = 0.f;
+#pragma unroll
+        for (int b = 0; b < NB; b++)
+          if (b * 256 < head.d) t += wave_sum(b * 256 + lane * 4 < head.d ? add_squares(0.f, v[j][b]) : 0.f);
+        scale = norm_scale(t, head.d, head.eps);
+      }
+#pragma unroll
+      for (int b = 0; b < NB; b++) {
+        const int c = b * 256 + lane * 4;
+        if (c >= head.d) continue;
+        f32x4_t o = v[j][b];
+        if (head.norm_w != nullptr) o = o * scale * nw[b];
+        *(f32x4_t *)(xs + i * kXStride + c) = o;
+        if (store) {
+          *(f32x4_t *)(head.h_out + (size_t)(m0 + i) * head.d + c) = v[j][b];
+          *(f32x4_t *)((float *)a.x + (size_t)(m0 + i) * a.ldx + c) = o;
+        }
+      }
+    }
+    __syncthreads();
+    if (n_tiles > 0) load_x(cur, 0);
+  } else {
+    if (n_tiles > 0) load(cur, 0);
+  }
   int s = 0;
   for (; s + 2 < n_tiles; s += 2) {
     load(nxt, s + 1);
@@ -1151,19 +1253,41 @@ static bool f32_tiled_pays(const GemmArgs &a) {
 // 1024, 2 splits) 4.1 / 4.1; 192 (32 rows, 1024 x 3072) 5.7 / 6.8, 256 (32 rows, 2752 x 1024) 4.9 / 5.8; up to 16 rows 172 (one row, 1024 x 5504) 5.4 / 5.0, 282
 // (one row, 1024 x 9000) 8.8 / 7.1, 384 (16 rows, 4096 x 12288) 34.3 / 35.3, 512 (16 rows, 4096 x 4096, 4 splits) 13.3 / 14.7.  More 16-token blocks per
 // workgroup (2, 3, 4, 6) only lengthen it: 48 rows of 688 x 256 4.0 / 5.1 with two, 6.3 with three.
-static hipError_t launch_f32(const GemmArgs &a, hipStream_t st) {
+static bool f32_halves(const GemmArgs &a, int tiles) { return a.act == nullptr && (long long)a.total_blocks * a.n_split * tiles <= (a.m <= 16 ? 300 : 128); }
+template <int KIND>
+static hipError_t launch_f32_small(const GemmArgs &a, int tiles, const HeadArg<KIND> &head, hipStream_t st) {
+  const int more = KIND == kHeadEmbed || KIND == kHeadConcat ? 1 : 0;   // the rotary table's workgroups
+  if (f32_halves(a, tiles))
+    hipLaunchKernelGGL((gemm_f32_kernel<1, KIND>), dim3(a.total_blocks * 2 + more, a.n_split, tiles), dim3(kGemmThreads), 0, st, a, head);
+  else
+    hipLaunchKernelGGL((gemm_f32_kernel<2, KIND>), dim3(a.total_blocks + more, a.n_split, tiles), dim3(kGemmThreads), 0, st, a, head);
+  return hipGetLastError();
+}
+static hipError_t launch_f32(const GemmArgs &a, hipStream_t st, const GemmHead *head) {
+  const int tiles = (a.m + 15) / 16 * (a.x2 ? 2 : 1);
+  if (head != nullptr)
+    return head->kind == kHeadSums ? launch_f32_small<kHeadSums>(a, tiles, *head, st)
+           : head->kind == kHeadEmbed ? launch_f32_small<kHeadEmbed>(a, tiles, *head, st) : launch_f32_small<kHeadConcat>(a, tiles, *head, st);
   switch (f32_split_blocks(a)) {
     case 2: return launch_f32_split<2>(a, st);
     case 3: return launch_f32_split<3>(a, st);
   }
   if (f32_tiled_pays(a)) return launch_f32_tiled(a, st);
-  const int tiles = (a.m + 15) / 16 * (a.x2 ? 2 : 1);
   if (tiles > 65535) return hipErrorInvalidValue;
-  const long long wgs = (long long)a.total_blocks * a.n_split * tiles;
-  const bool halves = a.act == nullptr && wgs <= (a.m <= 16 ? 300 : 128);
-  if (halves) hipLaunchKernelGGL(gemm_f32_kernel<1>, dim3(a.total_blocks * 2, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
-  else hipLaunchKernelGGL(gemm_f32_kernel<2>, dim3(a.total_blocks, a.n_split, tiles), dim3(kGemmThreads), 0, st, a);
-  return hipGetLastError();
+  return launch_f32_small<kHeadNone>(a, tiles, NoHead{}, st);
+}
+// Whether a launch makes its own x: launches of gemm_f32_kernel over one set of up to 128 rows.  Rows of up to 256 columns always (us, two layers and their
+// draft, 256 wide, launches of their own / this: draft of 4-row passes 157 / 139, of 10 367 / 342, of 16 507 / 480; verify and accept of 16 rows 97 / 91,
+// 60 97 / 95, 128 107.5 / 105.5); of up to 512 with at most three rows a wavefront (512 wide: drafts of 4 rows 169.5 / 163, of 10 394 / 390, of 16 525 / 528; verify of one
+// row 93.7 / 92, of 16 101.5 / 108, 60 109.5 / 115.5, 128 125.5 / 130).
+bool gemm_takes_head(int dtype, const GemmArgs &a, const GemmHead &h) {
+  if (dtype != 0 || h.kind == kHeadNone || a.m < 1 || a.m > kMaxNodes || a.x2 != nullptr || h.d % 4 || h.d > (a.m <= 12 ? kHeadCols : 256) || f32_tiled_pays(a))
+    return false;
+  if (h.kind != kHeadSums && (h.rope.table == nullptr || h.rope.half < 1)) return false;
+  uintptr_t low = (uintptr_t)h.embed | (uintptr_t)h.feat | (uintptr_t)h.norm_w | (uintptr_t)h.part | (uintptr_t)h.h_in | (uintptr_t)h.h_out;
+  if (h.kind == kHeadConcat) return (low & 15) == 0 && a.in == 2 * h.d;
+  low |= (uintptr_t)a.x;
+  return (low & 15) == 0 && a.in == h.d && a.ldx == h.d && (h.kind != kHeadSums || (h.ldp % 4 == 0 && h.n_split >= 1));
 }
 
 // ---- packing ---------------------------------------------------------------------------------
@@ -1468,8 +1592,9 @@ static hipError_t launch_bf16(const GemmArgs &a, hipStream_t st) {
 int gemm_k_per_iter(int dtype) { return dtype == 1 ? 128 : 64; }
 int gemm_k_per_slab(int dtype) { return kSlabIters * gemm_k_per_iter(dtype); }
 
-hipError_t launch_gemm(int dtype, const GemmArgs &args, hipStream_t st) {
+hipError_t launch_gemm(int dtype, const GemmArgs &args, hipStream_t st, const GemmHead *head) {
   GemmArgs a = args;
+  if (head != nullptr && !gemm_takes_head(dtype, a, *head)) return hipErrorInvalidValue;
   { hipError_t e = gemm_init(); if (e != hipSuccess) return e; }
   if (a.m < 1 || a.m_pad < a.m || a.nseg < 1 || a.nseg > 3 || a.n_split < 1 || a.in < 1) return hipErrorInvalidValue;
   if (a.n_split > (a.in + gemm_k_per_slab(dtype) - 1) / gemm_k_per_slab(dtype)) return hipErrorInvalidValue;   // no empty split
@@ -1480,7 +1605,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs &args, hipStream_t st) {
   const uint64_t inv = ~0ull / (uint64_t)a.n_split + 1;       // ceil(2^64 / n_split); 0 for n_split = 1
   a.slab_base = slabs / a.n_split; a.slab_rem = slabs % a.n_split;
   a.split_hi = (uint32_t)(inv >> 32); a.split_lo = (uint32_t)inv;
-  return dtype == 1 ? launch_bf16(a, st) : launch_f32(a, st);
+  return dtype == 1 ? launch_bf16(a, st) : launch_f32(a, st, head);
 }
 
 }  // namespace spec

@@ -56,7 +56,28 @@ struct GemmArgs {
   uint32_t split_hi, split_lo;          // set by launch_gemm: ceil(2^64 / n_split)
   int blk_per_wg, blk_per_wave;         // set by launch_gemm: wave w of workgroup x streams block x * blk_per_wg + w * blk_per_wave
 };
-hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st);
+// (cos, sin) of pos[i] * theta^(-j/half) for j < half -> table[i * half + j], the angles formed in double precision; table == nullptr: nothing to fill
+struct RopeFill { const int *pos; int half; double log2_theta; float2 *table; };
+RopeFill make_rope_fill(const int *pos, int head_dim, float theta, float2 *table);
+// The row kernel that makes a GEMM's x, run by the GEMM's own launch (fp32, small models: gemm_takes_head).  Nothing that it reads is written by the launch.
+enum HeadKind {
+  kHeadNone = 0,
+  kHeadSums,                            // launch_reduce_add_norm: h_out[i] = (residual ? h_in[i] : 0) + sum_s part[s][i], x[i] = norm of h_out[i]
+  kHeadEmbed,                           // launch_embed_norm: h_out[i] = embed[token[i]], x[i] = norm of h_out[i]; fills the rotary table
+  kHeadConcat                           // launch_concat_feat_embed: x[i] = [feat[src_row ? src_row[i] : i] ; embed[token[i]]], not stored; fills the table
+};
+struct GemmHead {
+  int kind;
+  int d;                                // row length of h, embed and feat
+  const float *part; int n_split, m_pad, ldp, residual;
+  const float *h_in; float *h_out;
+  const float *norm_w; float eps;       // norm_w == nullptr: x = h_out
+  const float *embed; const int *token;
+  const float *feat; const int *src_row;
+  RopeFill rope;
+};
+bool gemm_takes_head(int dtype, const GemmArgs &a, const GemmHead &h);
+hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st, const GemmHead *head = nullptr);
 bool gemm_can_fold(const GemmArgs &a);
 int gemm_fold_tile(int m, int blocks, int in);                // tile of a folded launch (1: 256 x 192, 2: 128 x 256)
 bool gemm_fold_pays(int m, int rows, int in, int n_split, int block);
@@ -74,15 +95,12 @@ hipError_t launch_pack_gate_up(int dtype, const void *gate, const void *up, int 
 
 // ---- rowops.hip ------------------------------------------------------------------------------
 // h[i] = embed[token[i]] (fp32);  x[i] = rmsnorm(h[i]) * w  in the storage type.
-// With `table` set, the launch also fills the rotary table of its rows: (cos, sin) of pos[i] * theta^(-2j/hd) for j < hd/2,
-// the angles formed in double precision.
+// The launch also fills the rotary table of its rows (RopeFill).
 hipError_t launch_embed_norm(int dtype, const void *embed, const int *token, int rows, int d, const void *norm_w,
-                             float eps, float *h, void *x, hipStream_t st, const int *pos = nullptr, int head_dim = 0,
-                             float theta = 0.f, float2 *table = nullptr);
+                             float eps, float *h, void *x, hipStream_t st, const RopeFill &rope = RopeFill{});
 // xcat[i] = [feat[src_row[i]] ; embed[token[i]]]  ([rows, 2d], storage type).  src_row == nullptr: identity.
 hipError_t launch_concat_feat_embed(int dtype, const void *feat, const int *src_row, const void *embed,
-                                    const int *token, int rows, int d, void *xcat, hipStream_t st, const int *pos = nullptr,
-                                    int head_dim = 0, float theta = 0.f, float2 *table = nullptr);
+                                    const int *token, int rows, int d, void *xcat, hipStream_t st, const RopeFill &rope = RopeFill{});
 // h[i] = (residual ? h[i] : 0) + sum_s part[s][i][:d];  x[i] = norm_w ? rmsnorm(h[i]) * norm_w : h[i].
 hipError_t launch_reduce_add_norm(int dtype, const float *part, int n_split, int m_pad, int ldp, int rows, int d,
                                   int residual, const void *norm_w, float eps, float *h, void *x, hipStream_t st);

@@ -12,23 +12,13 @@
 namespace spec {
 
 constexpr int kRowThreads = 256;      // threads of the elementwise kernels
-constexpr int kNormThreads = 1024;    // threads of the kernels that hold one row per workgroup
 
-// ---- rotary table: cos/sin of pos[i] * theta^(-2j/hd) for j < hd/2 ------------------------
-// (cos, sin) of pos * theta^(-j/half), the angle formed in double so that large positions keep their phase
-__device__ __forceinline__ float2 rope_entry(int pos, int j, int half, double log2_theta) {
-  const double inv = exp2(-(double)j / (double)half * log2_theta);
-  const double ang = (double)pos * inv;
-  double s, c;
-  sincos(ang, &s, &c);
-  return make_float2((float)c, (float)s);
-}
+// ---- rotary table ----
 // The kernels that open a forward (one workgroup per row) also fill the row's part of the rotary table, which saves a launch.
-struct RopeFill { const int *pos; int half; double log2_theta; float2 *table; };   // table == nullptr: nothing to fill
 __device__ __forceinline__ void rope_fill_row(const RopeFill &r, int i) {
   if (r.table != nullptr && (int)threadIdx.x < r.half) r.table[i * r.half + threadIdx.x] = rope_entry(r.pos[i], threadIdx.x, r.half, r.log2_theta);
 }
-static RopeFill make_rope_fill(const int *pos, int head_dim, float theta, float2 *table) {
+RopeFill make_rope_fill(const int *pos, int head_dim, float theta, float2 *table) {
   return RopeFill{pos, head_dim / 2, log2((double)theta), table};
 }
 
@@ -36,8 +26,6 @@ static RopeFill make_rope_fill(const int *pos, int head_dim, float theta, float2
 // Thread t owns the 4-column groups t, t + 1024, ... (PER of them, guarded), so all global loads of a
 // row are independent 16-byte loads issued up front, and the row is written exactly once.  With 1024
 // threads a 4096-wide row is one group per thread: the kernel is three dependent memory round trips.
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
 template <typename T> __device__ __forceinline__ f32x4_t load4(const T *p);
 template <> __device__ __forceinline__ f32x4_t load4<float>(const float *p) { return *(const f32x4_t *)p; }
 template <> __device__ __forceinline__ f32x4_t load4<bf16_t>(const bf16_t *p) {
@@ -70,11 +58,11 @@ __device__ __forceinline__ void finish_row(f32x4_t (&v)[PER], int d, const T *no
     const int c = (e * kNormThreads + threadIdx.x) * 4;
     if (c < d) {
       *(f32x4_t *)(h_row + c) = v[e];
-      ss += v[e].x * v[e].x + v[e].y * v[e].y + v[e].z * v[e].z + v[e].w * v[e].w;
+      ss = add_squares(ss, v[e]);
     }
   }
   float r = 1.f;
-  if (norm_w != nullptr) r = 1.0f / sqrtf(block_sum(ss, sh) / (float)d + eps);
+  if (norm_w != nullptr) r = norm_scale(block_sum(ss, sh), d, eps);
 #pragma unroll
   for (int e = 0; e < PER; e++) {
     const int c = (e * kNormThreads + threadIdx.x) * 4;
@@ -110,10 +98,9 @@ static void embed_norm_launch(const void *embed, const int *token, int rows, int
 }
 
 hipError_t launch_embed_norm(int dtype, const void *embed, const int *token, int rows, int d, const void *norm_w,
-                             float eps, float *h, void *x, hipStream_t st, const int *pos, int head_dim, float theta, float2 *table) {
-  if (rows < 1 || d < 4 || d % 4 || d > kNormThreads * 4 * 4 || (table != nullptr && (head_dim < 2 || head_dim / 2 > kNormThreads)))
+                             float eps, float *h, void *x, hipStream_t st, const RopeFill &rf) {
+  if (rows < 1 || d < 4 || d % 4 || d > kNormThreads * 4 * 4 || (rf.table != nullptr && (rf.half < 1 || rf.half > kNormThreads)))
     return hipErrorInvalidValue;
-  const RopeFill rf = make_rope_fill(pos, head_dim, theta, table);
   const int per = (d + kNormThreads * 4 - 1) / (kNormThreads * 4);
   if (dtype == 1) {
     if (per <= 1) embed_norm_launch<bf16_t, 1>(embed, token, rows, d, norm_w, eps, h, x, rf, st);
@@ -155,10 +142,8 @@ __global__ __launch_bounds__(kRowThreads) void concat_feat_embed_kernel(const T 
 }
 
 hipError_t launch_concat_feat_embed(int dtype, const void *feat, const int *src_row, const void *embed,
-                                    const int *token, int rows, int d, void *xcat, hipStream_t st, const int *pos, int head_dim, float theta,
-                                    float2 *table) {
-  if (rows < 1 || (table != nullptr && (head_dim < 2 || head_dim / 2 > kRowThreads))) return hipErrorInvalidValue;
-  const RopeFill rf = make_rope_fill(pos, head_dim, theta, table);
+                                    const int *token, int rows, int d, void *xcat, hipStream_t st, const RopeFill &rf) {
+  if (rows < 1 || (rf.table != nullptr && (rf.half < 1 || rf.half > kRowThreads))) return hipErrorInvalidValue;
   if (dtype == 1)
     hipLaunchKernelGGL(concat_feat_embed_kernel<bf16_t>, dim3(rows), dim3(kRowThreads), 0, st, (const bf16_t *)feat, src_row,
                        (const bf16_t *)embed, token, d, (bf16_t *)xcat, rf);

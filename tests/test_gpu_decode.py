@@ -687,3 +687,23 @@ def test_full_depth_7b_bench_configuration(env):
     for v, w_row in head_rows.items():
         want = r["feats"].astype(np.float64) @ w_row.astype(np.float64)
         assert np.abs(r["logits"][:, v] - want).max() < 2e-3
+
+
+@pytest.mark.parametrize("m", [1, 5, 12, 13, 16, 17, 100, 128])
+@pytest.mark.parametrize("d", [64, 256, 260, 512, 516])
+def test_fp32_rows_made_by_the_projections_have_the_row_kernels_bits(env, d, m):
+    """Up to 128 rows of up to 256 columns, up to 12 of up to 512, are embedded, normed and concatenated by the projections' own launches, a longer prompt's by kernels of their
+    own: keys and values of every layer, which depend on all rows before, have the same bits (516 columns: kernels of their own in both)."""
+    torch, P = env
+    sh = wl.TINY.with_(d_model=d)
+    w = P.upload_weights(wl.make_weights(sh), sh.dtype)
+    prompt = wl.make_prompt(sh, 150)
+    kv = []
+    for n in (m, 150):
+        eng = P.Engine(sh, w, max_seq=192)
+        eng.prefill(prompt[:n])
+        kv.append([eng.kv(0, l, m) for l in range(sh.n_layers)] + ([eng.kv(1, 0, m - 1)] if m > 1 else []))
+        eng.close()
+    for few, many in zip(*kv):
+        for a, b in zip(few, many):
+            assert np.isfinite(a).all() and np.array_equal(a, b)
