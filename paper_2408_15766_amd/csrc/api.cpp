@@ -1003,10 +1003,14 @@ int spec_accept(spec_ctx *c, const spec_tree *tree, int32_t *out_tokens, int32_t
     HIPCHK(c, launch_accept_sample(c->logits, g.vocab, c->stats, g.temperature, c->t_tok, c->t_par, N, g.seed, c->cycle, c->acc, c->stream));
   } else {
     HIPCHK(c, launch_rows_argmax(c->logits, N, g.vocab, c->amax_val, c->amax_idx, nullptr, c->stream));
-    HIPCHK(c, launch_accept_greedy(c->amax_val, c->amax_idx, argmax_slices(g.vocab), c->t_tok, c->t_par, N, c->acc, c->stream));
   }
-  HIPCHK(c, launch_commit(g.dtype, c->acc, c->kv_t, c->t_layer_stride, c->t_kv_stride, g.n_layers, g.n_kv_heads * g.head_dim,
-                          c->n, c->feats, g.d_model, c->pend_feat, c->pend_tok, c->root_tok, c->t_base, &c->stage_dev->acc, c->stream));
+  const int row_elems = g.n_kv_heads * g.head_dim;
+  if (g.temperature > 0.f)
+    HIPCHK(c, launch_commit(g.dtype, c->acc, c->kv_t, c->t_layer_stride, c->t_kv_stride, g.n_layers, row_elems, c->n, c->feats, g.d_model, c->pend_feat, c->pend_tok,
+                            c->root_tok, c->t_base, &c->stage_dev->acc, c->stream));
+  else
+    HIPCHK(c, launch_commit_greedy(c->amax_val, c->amax_idx, argmax_slices(g.vocab), c->t_tok, c->t_par, N, g.dtype, c->acc, c->kv_t, c->t_layer_stride, c->t_kv_stride,
+                                   g.n_layers, row_elems, c->n, c->feats, g.d_model, c->pend_feat, c->pend_tok, c->root_tok, c->t_base, &c->stage_dev->acc, c->stream));
   phase_end(c, 2);
   int rc = sync(c);
   if (rc) return rc;

@@ -213,8 +213,6 @@ struct AcceptResult {                   // lives on the device; copied to the ho
   int node[kMaxDepth + 1];              // node[0] = 0 (root), node[d] = accepted node of depth d
   int token[kMaxDepth + 1];             // m accepted tokens then the bonus token
 };
-hipError_t launch_accept_greedy(const float *amax_val, const int *amax_idx, int n_slices, const int *tree_tok,
-                                const int *tree_par, int n_nodes, AcceptResult *res, hipStream_t st);
 hipError_t launch_accept_sample(const float *logits, int vocab, const float2 *stat_part, float temp, const int *tree_tok,
                                 const int *tree_par, int n_nodes, uint64_t seed, uint32_t cycle, AcceptResult *res,
                                 hipStream_t st);
@@ -252,9 +250,12 @@ hipError_t launch_sample_row(const float *logits, int vocab, float temp, uint64_
 // Commit: in every layer move key/value of accepted node d from slot n + node[d] to slot n + d; gather
 // the features of root + accepted rows and the tokens for the next draft root step; *root_tok <- bonus;
 // *n_committed (device) += 1 + accepted.
-hipError_t launch_commit(int dtype, const AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride,
-                         int n_layers, int row_elems, int n, const void *feat, int d, void *pend_feat, int *pend_tok,
-                         int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st);
+hipError_t launch_commit(int dtype, AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride, int n_layers, int row_elems, int n, const void *feat, int d,
+                         void *pend_feat, int *pend_tok, int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st);
+// The greedy acceptance (launch_rows_argmax's slices of the tree's rows) -> *res, and the commit, in one launch.
+hipError_t launch_commit_greedy(const float *amax_val, const int *amax_idx, int n_slices, const int *tree_tok, const int *tree_par, int n_nodes, int dtype,
+                                AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride, int n_layers, int row_elems, int n, const void *feat, int d,
+                                void *pend_feat, int *pend_tok, int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st);
 // (host_res: pinned host memory as the device sees it; *res is written there too)
 // After a prompt: the pending pair (feature row of row_bytes bytes, first token) for the first draft root step, the committed count, and the first token
 // for the host (pinned memory as the device sees it).  res: one pending pair, as after a cycle that accepted nothing.

@@ -7,6 +7,8 @@
 // unique and independent of how the work is split over lanes.
 #include <limits.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -462,38 +464,6 @@ hipError_t launch_rerank(const DraftState &s, int total, const int *root_tok, in
 }
 
 // ---- acceptance ----------------------------------------------------------------------------
-// First child of `cur` (lowest node index) carrying `tok`, or INT_MAX.  One wavefront.
-__device__ __forceinline__ int find_child(const int *tree_tok, const int *tree_par, int n_nodes, int cur, int tok, int lane) {
-  int best = INT_MAX;
-  for (int c = lane; c < n_nodes; c += 64)
-    if (c > cur && tree_par[c] == cur && tree_tok[c] == tok) best = min(best, c);
-  return wave_min_i(best);
-}
-
-__global__ __launch_bounds__(64) void accept_greedy_kernel(const float *amax_val, const int *amax_idx, int n_slices,
-                                                           const int *tree_tok, const int *tree_par, int n_nodes,
-                                                           AcceptResult *res) {
-  const int lane = threadIdx.x;
-  int cur = 0, m = 0;
-  if (lane == 0) res->node[0] = 0;
-  for (int step = 0; step <= kMaxDepth; step++) {
-    const int best = merge_argmax(amax_val, amax_idx, n_slices, cur, lane);   // argmax of the target's row
-    const int c = m < kMaxDepth ? find_child(tree_tok, tree_par, n_nodes, cur, best, lane) : INT_MAX;
-    if (lane == 0) res->token[m] = best;                    // accepted token, or the bonus when the walk stops
-    if (c == INT_MAX) break;
-    cur = c; m++;
-    if (lane == 0) res->node[m] = cur;
-  }
-  if (lane == 0) res->n_acc = m;
-}
-hipError_t launch_accept_greedy(const float *amax_val, const int *amax_idx, int n_slices, const int *tree_tok,
-                                const int *tree_par, int n_nodes, AcceptResult *res, hipStream_t st) {
-  if (n_nodes < 1 || n_nodes > kMaxNodes || n_slices < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(accept_greedy_kernel, dim3(1), dim3(64), 0, st, amax_val, amax_idx, n_slices, tree_tok, tree_par, n_nodes,
-                     res);
-  return hipGetLastError();
-}
-
 // f(v, load(v)) for the thread's share v = threadIdx.x, + blockDim.x, ... of [0, n) in ascending order, with the loads of U
 // entries in flight (one workgroup walks a whole vocabulary row: taken one by one, every entry waits for its own load).
 template <int U = 8, typename Load, typename F>
@@ -839,65 +809,124 @@ hipError_t launch_sample_row(const float *logits, int vocab, float temp, uint64_
   return hipGetLastError();
 }
 
-// ---- commit: KV compaction + hand-off ------------------------------------------------------
-// Thread = one 16-byte chunk of one (layer, key|value) row; it moves that chunk for depths 1..m in
+// ---- commit: greedy acceptance, KV compaction, hand-off -----------------------------------------
+// The walk of the greedy acceptance, by one workgroup: every node's argmax (the slices' best, ascending, two threads a row) and the tree into the LDS in one
+// trip, then the accepted child of a node is the first one that carries its argmax.  (One wavefront that fetched each node's slices as it came to it
+// took 4 us and more, a trip a step.)
+struct GreedyWalk { const float *amax_val; const int *amax_idx; int n_slices; const int *tree_tok, *tree_par; int n_nodes; };   // amax_val == nullptr: accepted already
+__device__ __forceinline__ void greedy_walk(const GreedyWalk &w, AcceptResult &res) {
+  __shared__ int best[kMaxNodes], tok[kMaxNodes], par[kMaxNodes];
+  static_assert(kSelThreads == 2 * kMaxNodes, "two threads a row");
+  const int t = threadIdx.x, row = t >> 1;
+  ValIdx b{-INFINITY, INT_MAX};
+  if (row < w.n_nodes)
+#pragma unroll 4
+    for (int sl = t & 1; sl < w.n_slices; sl += 2) {
+      const float x = w.amax_val[(size_t)row * w.n_slices + sl];
+      const int c = w.amax_idx[(size_t)row * w.n_slices + sl];
+      if (better(x, c, b.v, b.i)) { b.v = x; b.i = c; }
+    }
+  best_step<1>(b);
+  if (row < w.n_nodes) {
+    if (t & 1) { tok[row] = w.tree_tok[row]; par[row] = w.tree_par[row]; } else best[row] = b.i;
+  }
+  __syncthreads();
+  if (t < 64) {
+    int cur = 0, m = 0;
+    if (t == 0) res.node[0] = 0;
+    for (int step = 0; step <= kMaxDepth; step++) {
+      const int want = best[cur];
+      if (t == 0) res.token[m] = want;                       // accepted token, or the bonus when the walk stops
+      int child = -1;
+      if (m < kMaxDepth)
+        for (int c0 = 0; c0 < w.n_nodes && child < 0; c0 += 64) {
+          const int c = c0 + t;
+          const uint64_t found = __ballot(c > cur && c < w.n_nodes && par[c] == cur && tok[c] == want);
+          if (found) child = c0 + __ffsll((unsigned long long)found) - 1;
+        }
+      if (child < 0) break;
+      cur = child; m++;
+      if (t == 0) res.node[m] = cur;
+    }
+    if (t == 0) res.n_acc = m;
+  }
+}
+// One launch: every workgroup walks the tree for itself (or fetches what was accepted), the first n_compact then move the keys and values, the others hand over.
+// Three launches of 4 us in a chain before (a cycle of plain decoding has little else that waits for the host).
+// Compaction: thread = one 16-byte chunk of one (layer, key|value) row; it moves that chunk for depths 1..m in
 // ascending order.  Depth d's destination slot n+d is never a later depth's source (sources
 // n+node[d'] have node[d'] > d for d' > d), and a chunk column is owned by one thread, so the
 // in-place move is race-free.
+// Hand-off: features of root + accepted rows and the matching tokens for the next draft root step.
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
-__global__ __launch_bounds__(kSelThreads) void compact_kv_kernel(const AcceptResult *res, char *kv_base, size_t layer_bytes,
-                                                                 size_t kv_bytes, int n_layers, int row_bytes, int n) {
-  const int m = res->n_acc;
-  if (m == 0) return;
-  const int chunks = row_bytes / 16;
-  const size_t total = (size_t)n_layers * 2 * chunks;
-  for (size_t w = (size_t)blockIdx.x * kSelThreads + threadIdx.x; w < total; w += (size_t)gridDim.x * kSelThreads) {
-    const int ch = (int)(w % chunks);
-    const int kv = (int)((w / chunks) & 1);
-    const int l = (int)(w / chunks / 2);
-    char *base = kv_base + (size_t)l * layer_bytes + (size_t)kv * kv_bytes + (size_t)ch * 16;
-    for (int d = 1; d <= m; d++) {
-      const int src = n + res->node[d], dst = n + d;
-      if (src != dst) *(u32x4_t *)(base + (size_t)dst * row_bytes) = *(const u32x4_t *)(base + (size_t)src * row_bytes);
-    }
-  }
-}
-// Features of root + accepted rows and the matching tokens for the next draft root step.
 template <typename T>
-__global__ __launch_bounds__(kSelThreads) void handoff_kernel(const AcceptResult *res, const T *feat, int d, T *pend_feat,
-                                                              int *pend_tok, int *root_tok, int *n_committed, AcceptResult *host_res) {
-  const int r = blockIdx.x, m = res->n_acc;
-  if (r == 0 && threadIdx.x == 0) *n_committed += 1 + m;      // root + accepted tokens are now in the cache
-  // the result for the host, straight into its memory: a copy launched behind this kernel was 6 us more to wait for
-  if (r == kMaxDepth && threadIdx.x < sizeof(AcceptResult) / sizeof(int)) ((int *)host_res)[threadIdx.x] = ((const int *)res)[threadIdx.x];
+__global__ __launch_bounds__(kSelThreads) void commit_kernel(GreedyWalk walk, AcceptResult *res, int n_compact, char *kv_base, size_t layer_bytes, size_t kv_bytes, int n_layers,
+                                                             int row_bytes, int n, const T *feat, int d, T *pend_feat, int *pend_tok, int *root_tok,
+                                                             int *n_committed, AcceptResult *host_res) {
+  __shared__ AcceptResult acc;
+  constexpr int kWords = sizeof(AcceptResult) / sizeof(int);
+  const int t = threadIdx.x;
+  if (walk.amax_val != nullptr) greedy_walk(walk, acc);
+  else if (t < kWords) ((int *)&acc)[t] = ((const int *)res)[t];
+  __syncthreads();
+  const int m = acc.n_acc;
+  if ((int)blockIdx.x < n_compact) {
+    if (m == 0) return;
+    const int chunks = row_bytes / 16;
+    const size_t total = (size_t)n_layers * 2 * chunks;
+    for (size_t w = (size_t)blockIdx.x * kSelThreads + t; w < total; w += (size_t)n_compact * kSelThreads) {
+      const int ch = (int)(w % chunks);
+      const int kv = (int)((w / chunks) & 1);
+      const int l = (int)(w / chunks / 2);
+      char *base = kv_base + (size_t)l * layer_bytes + (size_t)kv * kv_bytes + (size_t)ch * 16;
+      for (int e = 1; e <= m; e++) {
+        const int src = n + acc.node[e], dst = n + e;
+        if (src != dst) *(u32x4_t *)(base + (size_t)dst * row_bytes) = *(const u32x4_t *)(base + (size_t)src * row_bytes);
+      }
+    }
+    return;
+  }
+  const int r = (int)blockIdx.x - n_compact;
+  if (r == 0 && t == 0) *n_committed += 1 + m;                // root + accepted tokens are now in the cache
+  // the result for the next draft and for the host, straight into its memory: a copy launched behind this kernel was 6 us more to wait for
+  if (r == kMaxDepth && t < kWords && (t == 0 || (t - 1) % (kMaxDepth + 1) <= m)) {
+    const int x = ((const int *)&acc)[t];
+    ((int *)host_res)[t] = x;
+    if (walk.amax_val != nullptr) ((int *)res)[t] = x;
+  }
   if (r > m) return;
-  const T *src = feat + (size_t)res->node[r] * d;
+  const T *src = feat + (size_t)acc.node[r] * d;
   T *dst = pend_feat + (size_t)r * d;
-  for (int c = threadIdx.x; c < d; c += kSelThreads) dst[c] = src[c];
-  if (threadIdx.x == 0) {
-    pend_tok[r] = res->token[r];
-    if (r == m) *root_tok = res->token[m];
+  for (int c = t; c < d; c += kSelThreads) dst[c] = src[c];
+  if (t == 0) {
+    pend_tok[r] = acc.token[r];
+    if (r == m) *root_tok = acc.token[m];
   }
 }
-hipError_t launch_commit(int dtype, const AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride,
-                         int n_layers, int row_elems, int n, const void *feat, int d, void *pend_feat, int *pend_tok,
-                         int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st) {
+static hipError_t commit(const GreedyWalk &walk, int dtype, AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride, int n_layers, int row_elems, int n,
+                         const void *feat, int d, void *pend_feat, int *pend_tok, int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st) {
   const size_t esz = dtype == 1 ? 2 : 4;
   const int row_bytes = (int)(row_elems * esz);
   if (row_bytes % 16 != 0 || n_layers < 1) return hipErrorInvalidValue;
   const size_t total = (size_t)n_layers * 2 * (row_bytes / 16);
-  const int blocks = (int)((total + kSelThreads - 1) / kSelThreads);
-  hipLaunchKernelGGL(compact_kv_kernel, dim3(blocks > 2048 ? 2048 : blocks), dim3(kSelThreads), 0, st, res, (char *)kv_base,
-                     layer_stride * esz, kv_stride * esz, n_layers, row_bytes, n);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (dtype == 1)
-    hipLaunchKernelGGL(handoff_kernel<bf16_t>, dim3(kMaxDepth + 1), dim3(kSelThreads), 0, st, res, (const bf16_t *)feat, d,
-                       (bf16_t *)pend_feat, pend_tok, root_tok, n_committed, host_res);
-  else
-    hipLaunchKernelGGL(handoff_kernel<float>, dim3(kMaxDepth + 1), dim3(kSelThreads), 0, st, res, (const float *)feat, d,
-                       (float *)pend_feat, pend_tok, root_tok, n_committed, host_res);
+  const int blocks = (int)std::min<size_t>(2048, (total + kSelThreads - 1) / kSelThreads);
+  const dim3 grid(blocks + kMaxDepth + 1), threads(kSelThreads);
+#define SPEC_COMMIT(T) hipLaunchKernelGGL(commit_kernel<T>, grid, threads, 0, st, walk, res, blocks, (char *)kv_base, layer_stride * esz, kv_stride * esz, n_layers, \
+                                          row_bytes, n, (const T *)feat, d, (T *)pend_feat, pend_tok, root_tok, n_committed, host_res)
+  if (dtype == 1) SPEC_COMMIT(bf16_t); else SPEC_COMMIT(float);
+#undef SPEC_COMMIT
   return hipGetLastError();
+}
+hipError_t launch_commit(int dtype, AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride, int n_layers, int row_elems, int n, const void *feat, int d,
+                         void *pend_feat, int *pend_tok, int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st) {
+  return commit(GreedyWalk{}, dtype, res, kv_base, layer_stride, kv_stride, n_layers, row_elems, n, feat, d, pend_feat, pend_tok, root_tok, n_committed, host_res, st);
+}
+hipError_t launch_commit_greedy(const float *amax_val, const int *amax_idx, int n_slices, const int *tree_tok, const int *tree_par, int n_nodes, int dtype,
+                                AcceptResult *res, void *kv_base, size_t layer_stride, size_t kv_stride, int n_layers, int row_elems, int n, const void *feat, int d,
+                                void *pend_feat, int *pend_tok, int *root_tok, int *n_committed, AcceptResult *host_res, hipStream_t st) {
+  if (n_nodes < 1 || n_nodes > kMaxNodes || n_slices < 1) return hipErrorInvalidValue;
+  return commit(GreedyWalk{amax_val, amax_idx, n_slices, tree_tok, tree_par, n_nodes}, dtype, res, kv_base, layer_stride, kv_stride, n_layers, row_elems, n, feat, d, pend_feat,
+                pend_tok, root_tok, n_committed, host_res, st);
 }
 
 __global__ __launch_bounds__(kSelThreads) void prefill_handoff_kernel(const u32x4_t *feat, int pieces, const int *root_tok, int n_prompt, u32x4_t *pend_feat,

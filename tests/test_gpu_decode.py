@@ -707,3 +707,42 @@ def test_fp32_rows_made_by_the_projections_have_the_row_kernels_bits(env, d, m):
     for few, many in zip(*kv):
         for a, b in zip(few, many):
             assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("vocab", [1000, 4096, 9000])
+@pytest.mark.parametrize("accepted", [0, 1, 7, 15])
+def test_greedy_walk_over_a_full_tree_takes_nodes_beyond_the_first_wavefront(env, vocab, accepted):
+    """128 nodes, the accepted path spread over all of them among siblings with other tokens, one to three argmax slices: the tokens are plain decoding's,
+    also the ones behind the commit (keys and values moved to their places)."""
+    torch, P = env
+    sh = wl.TINY.with_(vocab=vocab, tree_depth=15, tree_topk=8, tree_total=128)
+    w = P.upload_weights(wl.make_weights(sh), sh.dtype)
+    prompt = wl.make_prompt(sh, 20)
+    plain = P.Engine(sh, w, max_seq=256, tree=(1, 1, 1))
+    want = plain.generate(prompt, 40)[0]
+    plain.close()
+    eng = P.Engine(sh, w, max_seq=256)
+    out = [eng.prefill(prompt)]
+    t = eng.draft_tree()
+    rng = np.random.default_rng(accepted)
+    path = sorted(rng.choice(np.arange(2, 128), accepted, replace=False).tolist()) if accepted else []
+    path = [0] + path
+    t.n_nodes = 128
+    for j in range(1, 128):
+        if j in path:
+            d = path.index(j)
+            t.parent[j], t.depth[j], t.token[j] = path[d - 1], d, want[d]
+        else:                                                 # a sibling of the next node of the path, with another token
+            d = sum(p < j for p in path)
+            par = path[min(d - 1, 14)]
+            t.parent[j], t.depth[j], t.token[j] = par, t.depth[par] + 1, (want[t.depth[par] + 1] + 1 + j % (vocab - 1)) % vocab
+    eng.verify(t)
+    got = eng.accept(t)
+    assert got == want[1:accepted + 2]
+    out += got
+    while len(out) < 40:
+        t = eng.draft_tree()
+        eng.verify(t)
+        out += eng.accept(t)
+    assert out[:40] == want[:40]
+    eng.close()
