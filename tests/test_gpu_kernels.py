@@ -465,6 +465,19 @@ def test_topk_logprob_matches_oracle(env, rows, vocab, k):
     assert tok[0, 0] == 7 and tok[0, 1] == 900 and (rows == 1 or tok[-1, 0] == vocab - 1)
 
 
+@pytest.mark.parametrize("rows,vocab,k", [(2, 16, 16), (3, 1023, 16), (4, 1024, 16), (4, 1025, 16), (1, 300, 1)])
+def test_topk_logprob_around_the_short_slice(env, rows, vocab, k):
+    """Up to 1024 tokens a thread holds four of them, beyond that sixteen."""
+    torch, P = env
+    logits = np.random.default_rng(vocab).standard_normal((rows, vocab)).astype(np.float32)
+    logits[0, vocab // 2] = logits[0, vocab - 1] = 9.0                # equal: lower index first
+    tok, lp = (t.cpu().numpy() for t in P.spec_k_topk_logprob(torch.from_numpy(logits).cuda(), k))
+    want_lp = log_softmax(logits.astype(np.float64))
+    for r in range(rows):
+        want = top_k(logits[r], k)
+        assert list(tok[r][:k]) == list(want) and np.abs(lp[r][:k] - want_lp[r, want]).max() < 5e-6
+
+
 @pytest.mark.parametrize("name,rows,k,n_split", [("70b-down", 8192, 28672, 4), ("70b-gateup-slice", 4096, 8192, 1), ("13b-qkv-slice", 5120, 5120, 2)])
 def test_gemm_large_shapes_sampled_against_oracle(env, name, rows, k, n_split):
     """Matrix shapes of the largest configurations, M = 60: sampled output columns against fp64 dot products."""
