@@ -91,8 +91,8 @@ struct spec_ctx {
   float *t_sc = nullptr;
   DraftState ds{};
   AcceptResult *acc = nullptr;
-  // Row kernels that run inside the launch of the projection behind them (GemmHead, fp32): what they read and what the launch writes lie in
-  // different buffers, so sums and residual rows of forwards of up to kMaxNodes rows alternate between two.
+  // Row kernels that run inside the launch of the projection behind them (GemmHead): what they read and what the launch writes lie in different
+  // buffers, so sums and residual rows of forwards that are small enough for it alternate between two.
   float *h2 = nullptr, *part2 = nullptr;
   size_t part2_floats = 0;
   float *h_now = nullptr, *part_now = nullptr;   // the residual rows as they are; where the last partial sums went
@@ -225,13 +225,14 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   const int k = std::max(1, c.tree_topk), D = std::max(1, c.tree_depth);
   const int seq_draft = c.max_seq + D * k;
   const int max_parts = (c.max_seq + D * k) / kAttnPart + 2;   // parts of the longest row + the tail slot
+  const int head_rows = c.dtype == SPEC_DTYPE_BF16 ? kHeadRowsBf16 : kHeadRowsFp32;   // rows that projections make for themselves
   size_t part_floats = 0, part2_floats = 0;
   {
     struct { int rows, in; } g[5] = {{dq + 2 * dkv, d}, {d, dq}, {gate_up_rows(f), d}, {d, f}, {d, 2 * d}};
     for (auto &e : g) {
       GemmPlan p = plan_gemm(e.rows, e.in, c.dtype);
       part_floats = std::max(part_floats, (size_t)p.n_split * std::min(m_max, kPartRows) * e.rows);
-      part2_floats = std::max(part2_floats, (size_t)p.n_split * std::min(m_max, kMaxNodes) * e.rows);
+      part2_floats = std::max(part2_floats, (size_t)p.n_split * std::min(m_max, head_rows) * e.rows);
       part_floats = std::max(part_floats, std::min((size_t)v, (size_t)p.n_split * 512 * e.rows));   // the ratio rule's scratch, small models
     }
   }
@@ -302,10 +303,8 @@ size_t layout(const spec_config &c, spec_ctx *x, char *base) {
   TAKE(ds.front_slot, int *, kMaxTopK * 4)
   TAKE(ds.front_pos, int *, kMaxTopK * 4)
   TAKE(acc, AcceptResult *, sizeof(AcceptResult))
-  if (c.dtype != SPEC_DTYPE_BF16) {
-    TAKE(h2, float *, (size_t)std::min(m_max, kMaxNodes) * d * 4)
-    TAKE(part2, float *, part2_floats * 4)
-  }
+  TAKE(h2, float *, (size_t)std::min(m_max, head_rows) * d * 4)
+  TAKE(part2, float *, part2_floats * 4)
 #undef TAKE
   if (x) {
     x->esz = (int)esz; x->m_small = m_small; x->m_max = m_max; x->max_parts = max_parts; x->seq_draft = seq_draft;
@@ -356,6 +355,9 @@ int flush_head(spec_ctx *c) {
     case kHeadSums:
       HIPCHK(c, launch_reduce_add_norm(g.dtype, h.part, h.n_split, h.m_pad, h.ldp, rows, h.d, h.residual, h.norm_w, h.eps, c->h_now, x, c->stream));
       break;
+    case kHeadParts:
+      HIPCHK(c, launch_attn_merge(h.merge, rows, x, c->stream));
+      break;
     case kHeadEmbed:
       HIPCHK(c, launch_embed_norm(g.dtype, h.embed, h.token, rows, h.d, h.norm_w, h.eps, c->h_now, x, c->stream, h.rope));
       break;
@@ -367,7 +369,8 @@ int flush_head(spec_ctx *c) {
 // The rows of x are made by the projection that reads them (at the latest by the next one), where the forward is small enough for that.
 int defer_head(spec_ctx *c, const GemmHead &h, int rows, void *x) {
   c->head = h; c->head_rows = rows; c->head_x = x;
-  return c->cfg.dtype == SPEC_DTYPE_BF16 || rows > kMaxNodes ? flush_head(c) : SPEC_OK;
+  const bool waits = c->cfg.dtype == SPEC_DTYPE_BF16 ? rows <= kHeadRowsBf16 && (h.kind == kHeadSums || h.kind == kHeadParts) : rows <= kHeadRowsFp32;
+  return waits ? SPEC_OK : flush_head(c);
 }
 
 // out == nullptr: partial sums, into one of their buffers (c->part_now behind the call)
@@ -396,7 +399,7 @@ int run_gemm(spec_ctx *c, const void *x, int ldx, int m, int in, const Seg *segs
     headed = c->head_x == x && c->head_rows == m && gemm_takes_head(c->cfg.dtype, a, h);
     if (!headed) { const int rc = flush_head(c); if (rc) return rc; }
     c->head_x = nullptr;
-    if (headed && h.kind != kHeadConcat) c->h_now = h.h_out;
+    if (headed && (h.kind == kHeadSums || h.kind == kHeadEmbed)) c->h_now = h.h_out;
     if (headed && sums && h.kind == kHeadSums) c->part_now = h.part == c->part ? c->part2 : c->part;
   }
   a.part = out ? out : c->part_now;
@@ -449,7 +452,7 @@ int add_norm_rows(spec_ctx *c, int r0, int n, int split, int m, int residual, co
     GemmHead h{};
     h.kind = kHeadSums; h.d = d;
     h.part = c->part_now; h.n_split = split; h.m_pad = n; h.ldp = d; h.residual = residual;
-    h.norm_w = (const float *)norm; h.eps = c->cfg.rms_eps;
+    h.norm_w = norm; h.eps = c->cfg.rms_eps;
     return defer_head(c, h, m, x);
   }
   HIPCHK(c, launch_reduce_add_norm(c->cfg.dtype, c->part_now, split, n, d, n, d, residual, norm, c->cfg.rms_eps, c->h_now + (size_t)r0 * d,
@@ -498,7 +501,13 @@ int layer_forward(spec_ctx *c, const spec_layer_weights &lw, char *kcache, char 
     a.depth = rt.depth; a.anc = rt.anc;
     a.scale = 1.0f / sqrtf((float)g.head_dim);
     a.part = c->attn_part; a.max_parts = c->max_parts; a.out = c->attn_out;
-    HIPCHK(c, launch_attention(dt, a, max_pos, c->stream));
+    GemmHead merge{};
+    merge.kind = kHeadParts;
+    HIPCHK(c, launch_attention(dt, a, max_pos, c->stream, &merge.merge));
+    if (merge.merge.part != nullptr) {
+      const int rc = defer_head(c, merge, m, c->attn_out);
+      if (rc) return rc;
+    }
   }
   {
     const Seg segs[1] = {{lw.wo, d}};
@@ -547,8 +556,8 @@ int target_forward(spec_ctx *c, int m, int base, const RowTables &rt, int max_po
   c->head_x = nullptr;
   GemmHead open{};                                              // (what opens the forward also fills the rotary table of its rows)
   open.kind = kHeadEmbed; open.d = g.d_model;
-  open.norm_w = (const float *)c->layers[0].attn_norm; open.eps = g.rms_eps;
-  open.embed = (const float *)c->w.embed; open.token = rt.token;
+  open.norm_w = c->layers[0].attn_norm; open.eps = g.rms_eps;
+  open.embed = c->w.embed; open.token = rt.token;
   open.rope = make_rope_fill(rt.pos, g.head_dim, g.rope_theta, c->rope);
   const int opened = defer_head(c, open, m, c->x);
   if (opened) return opened;
@@ -576,7 +585,7 @@ int draft_forward(spec_ctx *c, int m, int base, const void *feat, const int *src
   c->h_now = c->h; c->part_now = c->part;
   GemmHead open{};
   open.kind = kHeadConcat; open.d = d;
-  open.embed = (const float *)c->w.embed; open.token = rt.token; open.feat = (const float *)feat; open.src_row = src_row;
+  open.embed = c->w.embed; open.token = rt.token; open.feat = feat; open.src_row = src_row;
   open.rope = make_rope_fill(rt.pos, g.head_dim, g.rope_theta, c->rope);
   rc = defer_head(c, open, m, c->xcat);
   if (rc) return rc;

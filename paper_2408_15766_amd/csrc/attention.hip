@@ -69,9 +69,6 @@ template <> struct Chunk<bf16_t> {
   }
 };
 
-// End of the bulk region of a row at position p: the tail is the last kMaxDepth + 1 positions.  See the header.
-__device__ __host__ __forceinline__ int bulk_end(int p) { return p > kMaxDepth ? p - kMaxDepth : 0; }
-
 // Orders this wavefront's LDS writes before its later LDS reads of other lanes' data.  The LDS executes
 // one wavefront's operations in issue order, so only the compiler has to be kept from reordering them.
 __device__ __forceinline__ void wave_lds_sync() {
@@ -79,27 +76,6 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-
-// Scores are kept in units of log2: the launch's scale holds 1/sqrt(hd) * log2(e), and every weight is a power of two taken by the hardware.
-__device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// The merge of a row's parts, in ascending order and the tail last: (reference m, sum l, outputs o) of part after part go into the row's.  The row's
-// reference moves only when a part's exceeds it by more than kRefSlack: until then weights are up to 2^kRefSlack, harmless in fp32, and the
-// sums are left alone.  The final division cancels the choice.  step() returns what the row's sums are to be multiplied by before the part
-// is added with weight w.
-constexpr float kRefSlack = 8.f;
-struct RowMerge {
-  float m = -INFINITY, l = 0.f;
-  __device__ __forceinline__ float step(float m_part, float l_part, float &w) {
-    const bool move = m_part > m + kRefSlack;                  // also the first part
-    const float m_new = move ? m_part : m;
-    const float turn = move ? exp2_(m - m_new) : 1.f;
-    m = m_new;
-    w = exp2_(m_part - (m_new == -INFINITY ? 0.f : m_new));     // (a part whose scores are all -inf weighs nothing)
-    l = fmaf(l_part, w, l * turn);
-    return turn;
-  }
-};
 
 // One wavefront: row i, kv head hk, part `part` (full mode) or the tail range (tail mode).  `qs` and `vs`
 // are this wavefront's own LDS areas ([G][HD] floats and 64 staged value rows); no workgroup barrier is
@@ -957,7 +933,7 @@ static bool chain_pays(int rows, int hq, int keys) {
 }
 
 template <typename T, int HD, int G>
-static hipError_t launch_thg(AttnArgs a, int max_pos, hipStream_t st) {
+static hipError_t launch_thg(AttnArgs a, int max_pos, hipStream_t st, AttnMerge *merge) {
   hipError_t e;
   if constexpr (sizeof(T) == 2) {
     if (attn_parts_covering(bulk_end(max_pos)) + 1 > a.max_parts) return hipErrorInvalidValue;
@@ -976,6 +952,10 @@ static hipError_t launch_thg(AttnArgs a, int max_pos, hipStream_t st) {
       if (qblocks <= 4) e = launch_hybrid<HD, G, 4>(a, 1, st);
       else e = launch_hybrid<HD, G, 8>(a, (qblocks + 7) / 8, st);
       if (e != hipSuccess) return e;
+      if (merge != nullptr && rows <= kHeadRowsBf16 && a.bulk_parts + 1 <= kHeadMaxParts) {
+        *merge = AttnMerge{a.part, a.max_parts, a.hq, HD, a.base, a.base_ptr, a.depth};
+        return hipSuccess;
+      }
       hipLaunchKernelGGL((attn_combine_kernel<T, HD>), dim3(a.rows, a.hq), dim3(HD), 0, st, a);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
@@ -1010,24 +990,35 @@ static hipError_t launch_thg(AttnArgs a, int max_pos, hipStream_t st) {
   return hipGetLastError();
 }
 template <typename T, int HD>
-static hipError_t launch_th(const AttnArgs &a, int max_pos, hipStream_t st) {
+static hipError_t launch_th(const AttnArgs &a, int max_pos, hipStream_t st, AttnMerge *merge) {
   switch (a.hq / a.hkv) {
-    case 1: return launch_thg<T, HD, 1>(a, max_pos, st);
-    case 2: return launch_thg<T, HD, 2>(a, max_pos, st);
-    case 4: return launch_thg<T, HD, 4>(a, max_pos, st);
-    case 8: return launch_thg<T, HD, 8>(a, max_pos, st);
+    case 1: return launch_thg<T, HD, 1>(a, max_pos, st, merge);
+    case 2: return launch_thg<T, HD, 2>(a, max_pos, st, merge);
+    case 4: return launch_thg<T, HD, 4>(a, max_pos, st, merge);
+    case 8: return launch_thg<T, HD, 8>(a, max_pos, st, merge);
     default: return hipErrorInvalidValue;
   }
 }
 
 // max_pos: largest key position any row attends to (host-known bound: base + max depth).
-hipError_t launch_attention(int dtype, const AttnArgs &args, int max_pos, hipStream_t st) {
+hipError_t launch_attention(int dtype, const AttnArgs &args, int max_pos, hipStream_t st, AttnMerge *merge) {
+  if (merge != nullptr) merge->part = nullptr;
   AttnArgs a = args;
   a.scale = (float)((double)a.scale * 1.4426950408889634);    // scores in units of log2
   if (a.rows < 1 || a.hkv < 1 || a.hq % a.hkv != 0) return hipErrorInvalidValue;
-  if (a.hd == 128) return dtype == 1 ? launch_th<bf16_t, 128>(a, max_pos, st) : launch_th<float, 128>(a, max_pos, st);
-  if (a.hd == 64) return dtype == 1 ? launch_th<bf16_t, 64>(a, max_pos, st) : launch_th<float, 64>(a, max_pos, st);
+  if (a.hd == 128) return dtype == 1 ? launch_th<bf16_t, 128>(a, max_pos, st, merge) : launch_th<float, 128>(a, max_pos, st, merge);
+  if (a.hd == 64) return dtype == 1 ? launch_th<bf16_t, 64>(a, max_pos, st, merge) : launch_th<float, 64>(a, max_pos, st, merge);
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_attn_merge(const AttnMerge &m, int rows, void *out, hipStream_t st) {
+  if (rows < 1 || (m.hd != 64 && m.hd != 128)) return hipErrorInvalidValue;
+  AttnArgs a{};
+  a.rows = rows; a.hq = m.hq; a.base = m.base; a.base_ptr = m.base_ptr; a.depth = m.depth;
+  a.part = (float *)m.part; a.max_parts = m.max_parts; a.out = out; a.tail_only = 1;
+  if (m.hd == 128) hipLaunchKernelGGL((attn_combine_kernel<bf16_t, 128>), dim3(rows, m.hq), dim3(128), 0, st, a);
+  else hipLaunchKernelGGL((attn_combine_kernel<bf16_t, 64>), dim3(rows, m.hq), dim3(64), 0, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace spec

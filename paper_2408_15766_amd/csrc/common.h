@@ -152,6 +152,28 @@ __device__ __forceinline__ int key_rank(const uint64_t *keys, int n2, uint64_t k
   return rank;
 }
 
+// ---- merge of an attention's parts ----
+// Scores are kept in units of log2: the launch's scale holds 1/sqrt(hd) * log2(e), and every weight is a power of two taken by the hardware.
+__device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// The merge of a row's parts, in ascending order and the tail last: (reference m, sum l, outputs o) of part after part go into the row's.  The row's
+// reference moves only when a part's exceeds it by more than kRefSlack: until then weights are up to 2^kRefSlack, harmless in fp32, and the
+// sums are left alone.  The final division cancels the choice.  step() returns what the row's sums are to be multiplied by before the part
+// is added with weight w.
+constexpr float kRefSlack = 8.f;
+struct RowMerge {
+  float m = -INFINITY, l = 0.f;
+  __device__ __forceinline__ float step(float m_part, float l_part, float &w) {
+    const bool move = m_part > m + kRefSlack;                  // also the first part
+    const float m_new = move ? m_part : m;
+    const float turn = move ? exp2_(m - m_new) : 1.f;
+    m = m_new;
+    w = exp2_(m_part - (m_new == -INFINITY ? 0.f : m_new));     // (a part whose scores are all -inf weighs nothing)
+    l = fmaf(l_part, w, l * turn);
+    return turn;
+  }
+};
+
 // ---- RMSNorm rows and the rotary table: shared by every kernel that forms them (the same operations in the same order, so the bits do not depend on
 // which does).  Virtual thread t of kNormThreads owns the 4-column groups t, t + kNormThreads, ..; its squares are added up in this order, then
 // over the wavefronts of 64 virtual threads (wave_sum), then over these in ascending order.
@@ -163,6 +185,13 @@ __device__ __forceinline__ float add_squares(float ss, f32x4_t v) {
   return ss + __builtin_fmaf(v.w, v.w, q);
 }
 __device__ __forceinline__ float norm_scale(float sum, int d, float eps) { return 1.0f / sqrtf(sum / (float)d + eps); }
+template <typename T> __device__ __forceinline__ f32x4_t load4(const T *p);
+template <> __device__ __forceinline__ f32x4_t load4<float>(const float *p) { return *(const f32x4_t *)p; }
+template <> __device__ __forceinline__ f32x4_t load4<bf16_t>(const bf16_t *p) {
+  const uint2 u = *(const uint2 *)p;
+  return f32x4_t{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
+                 __uint_as_float(u.y & 0xFFFF0000u)};
+}
 // (cos, sin) of pos * theta^(-j/half), the angle formed in double so that large positions keep their phase
 __device__ __forceinline__ float2 rope_entry(int pos, int j, int half, double log2_theta) {
   const double inv = exp2(-(double)j / (double)half * log2_theta);

@@ -309,6 +309,199 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : (TB <= 2 && 
     }
 }
 
+// ---- one row, bf16 (plain decoding) ---------------------------------------------------------------------
+// A row fits the LDS whole (the launch's K range of it), so the wavefronts stream their weights without a barrier, and a launch can make its x by itself:
+// every workgroup for itself, while its first weights are on their way.  What a row is made of (the partial sums of the projection before and the residual,
+// or the attention's parts) is 20 to 80 KB, read from the caches by all workgroups; as launches of their own the row kernels were 4.7 us each of 92 a layer,
+// most of it the way from launch to launch.  (Rows made by one workgroup and handed to the others inside a launch cost more than the launch: 9 us.)
+// Sums, norm and merge are the row kernels' operations in their order, and the products run in gemm_stream_kernel's order: same bits.
+// Measured (7B shape, us, row kernel and streaming launch / this): O 4.7 + 7.9 / 8.5, gate/up 4.75 + 28.9 / 30.4, QKV 4.75 + 18.0 / 19.8, LM head 4.75 + 41.6 / 42.3;
+// plain decoding of 16 tokens behind a prompt of 77 49.4 -> 47.0 ms.  Eight wavefronts share the sums (with four, 256 registers spill: 36 us the gate/up launch; with sixteen
+// 37).  More rows do not pay: verify of two 820 -> 814 us (8 layers; 13B, 6 layers 851 -> 883), of four 828 -> 906.
+struct NoHead {};
+template <int KIND> using HeadArg = std::conditional_t<KIND == kHeadNone, NoHead, GemmHead>;
+constexpr int kRowMaxCols = 2 * 4 * kNormThreads;             // widest row of kHeadSums
+constexpr int kRowLds = 64 * 1024 - 256;                      // bytes of the row's K range (what a launch may ask for without more ado)
+__host__ __device__ inline int row_bytes(int slab_base, int slab_rem) { return (slab_base + (slab_rem ? 1 : 0)) * kSlabRowBytes; }
+
+// The row of launch_reduce_add_norm by THREADS threads: pass q is virtual thread q * THREADS + tid
+template <int THREADS>
+struct SumsRow {
+  static constexpr int kPass = kNormThreads / THREADS, E = kRowMaxCols / (4 * kNormThreads), NS = 4;   // NS: split sums requested at once
+  f32x4_t p[E][kPass][NS], res[E][kPass];
+  static __device__ __forceinline__ int col(int e, int q) { return (e * kNormThreads + q * THREADS + (int)threadIdx.x) * 4; }
+  __device__ __forceinline__ void load(const GemmHead &h) {
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      if (e * 4 * kNormThreads >= h.d) continue;              // (the same for all)
+#pragma unroll
+      for (int q = 0; q < kPass; q++) {
+        const int c = col(e, q) < h.d ? col(e, q) : 0;
+        res[e][q] = *(const f32x4_t *)(h.h_in + c);
+#pragma unroll
+        for (int s = 0; s < NS; s++) p[e][q][s] = *(const f32x4_t *)(h.part + (size_t)(s < h.n_split ? s : 0) * h.m_pad * h.ldp + c);
+      }
+    }
+  }
+  // The normed row's columns [k0, k1) to xl (LDS) and, with `store`, the whole row to x and h_out.  sh: kNormThreads / 64 floats
+  __device__ __forceinline__ void finish(const GemmHead &h, unsigned char *xl, int k0, int k1, bf16_t *x, bool store, float *sh) {
+    const bf16_t *norm_w = (const bf16_t *)h.norm_w;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    f32x4_t v[E][kPass], nw[E][kPass];
+    float ss[kPass] = {};
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      if (e * 4 * kNormThreads >= h.d) continue;
+#pragma unroll
+      for (int q = 0; q < kPass; q++) nw[e][q] = (norm_w != nullptr && col(e, q) < h.d) ? load4<bf16_t>(norm_w + col(e, q)) : f32x4_t{1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+      for (int q = 0; q < kPass; q++) {
+        const int c = col(e, q) < h.d ? col(e, q) : 0;
+        f32x4_t acc = p[e][q][0];
+#pragma unroll
+        for (int s = 1; s < NS; s++)
+          if (s < h.n_split) acc += p[e][q][s];
+        for (int s = NS; s < h.n_split; s++) acc += *(const f32x4_t *)(h.part + (size_t)s * h.m_pad * h.ldp + c);
+        v[e][q] = h.residual ? res[e][q] + acc : acc;
+        if (col(e, q) < h.d) ss[q] = add_squares(ss[q], v[e][q]);
+      }
+    }
+    float r = 1.f;
+    if (norm_w != nullptr) {
+#pragma unroll
+      for (int q = 0; q < kPass; q++) {
+        const float w = wave_sum(ss[q]);
+        if (lane == 0) sh[q * (THREADS / kWave) + wave] = w;
+      }
+      __syncthreads();
+      float t = 0.f;
+      for (int w = 0; w < kNormThreads / kWave; w++) t += sh[w];
+      r = norm_scale(t, h.d, h.eps);
+    }
+#pragma unroll
+    for (int e = 0; e < E; e++)
+#pragma unroll
+      for (int q = 0; q < kPass; q++) {
+        const int c = col(e, q);
+        if (c >= h.d) continue;
+        f32x4_t o = v[e][q];
+        if (norm_w != nullptr) o = o * r * nw[e][q];
+        const uint2 u = {pack_bf16x2(o.x, o.y), pack_bf16x2(o.z, o.w)};
+        if (c >= k0 && c < k1) *(uint2 *)(xl + (c - k0) * 2) = u;
+        if (store) {
+          *(f32x4_t *)(h.h_out + c) = v[e][q];
+          *(uint2 *)(x + c) = u;
+        }
+      }
+  }
+};
+
+// Dynamic LDS: row_bytes(), the row's K range
+template <int KIND, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, WAVES > 4 ? WAVES / 4 : 2) void gemm_row_kernel(GemmArgs a, GemmHead head) {
+  constexpr int kThreads = WAVES * kWave, KI = 2 * kLaneBytes / (int)sizeof(bf16_t);
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  __shared__ float sh[kNormThreads / kWave];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 31, g = lane >> 5;
+  // blocks, segments and K ranges as in gemm_stream_kernel
+  const int bx = blockIdx.x, by = blockIdx.y;
+  const int e0 = a.seg_blocks[0], e1 = e0 + (a.nseg > 1 ? a.seg_blocks[1] : 0);
+  const int blk_raw = bx * a.blk_per_wg + wave * a.blk_per_wave;
+  const bool active = blk_raw < a.total_blocks;
+  const int blk = active ? blk_raw : a.total_blocks - 1;
+  const int seg = blk < e0 ? 0 : (blk < e1 ? 1 : 2);
+  const int b0 = seg == 0 ? 0 : (seg == 1 ? e0 : e1);
+  const int seg_rows = seg == 0 ? a.seg_rows[0] : (seg == 1 ? a.seg_rows[1] : a.seg_rows[2]);
+  const int seg_col0 = seg == 0 ? a.seg_col0[0] : (seg == 1 ? a.seg_col0[1] : a.seg_col0[2]);
+  const void *seg_w = seg == 0 ? a.seg_w[0] : (seg == 1 ? a.seg_w[1] : a.seg_w[2]);
+  const int row = (blk - b0) * 32 + c;
+  const int n_it_total = (a.in + KI - 1) / KI;
+  const int it_begin = slab_begin(a, by) * kSlabIters, it_end = min(n_it_total, slab_begin(a, by + 1) * kSlabIters);
+  const int n_iter = __builtin_amdgcn_readfirstlane(active ? it_end - it_begin : 0);   // of this wavefront
+  const int k0 = it_begin * KI, k1 = min(it_end * KI, a.in);
+  const char *wstream = (const char *)seg_w + ((size_t)(blk - b0) * n_it_total + it_begin) * (size_t)kTileBytes + lane * 16;
+  u32x4_t ring[kStages][8];
+  auto load_w = [&](u32x4_t (&dst)[8], int it) __attribute__((always_inline)) {
+    const char *p = wstream + (size_t)it * kTileBytes;
+#pragma unroll
+    for (int j = 0; j < 8; j++) dst[j] = __builtin_nontemporal_load((const u32x4_t *)(p + j * 1024));
+  };
+  auto first_weights = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int it = 0; it < kStages - 1; it++)
+      if (it < n_iter) load_w(ring[it], it);
+  };
+
+  for (int q = k1 + tid; q < it_end * KI; q += kThreads) *(uint16_t *)(lds + (q - k0) * 2) = 0;   // past K: meets zero weights, has to be finite
+  if constexpr (KIND == kHeadSums) {
+    SumsRow<kThreads> r;
+    r.load(head);
+    first_weights();
+    r.finish(head, lds, k0, k1, (bf16_t *)a.x, bx == 0 && by == 0, sh);
+  } else {
+    // four columns a thread (of one head: hd is a multiple of 4), all their parts in flight
+    const AttnMerge &mg = head.merge;
+    const int n_front = attn_parts_covering(bulk_end((mg.base_ptr ? *mg.base_ptr : mg.base) + mg.depth[0])), n_parts = n_front + 1;
+    auto columns = [&](int col, auto between) __attribute__((always_inline)) {
+      const int at = min(col, a.in - 4), dim = at % mg.hd;
+      const float *src = mg.part + (size_t)(at / mg.hd) * mg.max_parts * (mg.hd + 2);
+      float2 ml[kHeadMaxParts], lo[kHeadMaxParts], hi[kHeadMaxParts];
+#pragma unroll
+      for (int t = 0; t < kHeadMaxParts; t++) {
+        const float *sp = src + (size_t)(t < n_front ? t : mg.max_parts - 1) * (mg.hd + 2);
+        if (t < n_parts) { ml[t] = *(const float2 *)sp; lo[t] = *(const float2 *)(sp + 2 + dim); hi[t] = *(const float2 *)(sp + 4 + dim); }
+      }
+      between();
+      if (col >= k1) return;
+      RowMerge rm;
+      f32x4_t o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < kHeadMaxParts; t++)
+        if (t < n_parts) {
+          float w;
+          const float turn = rm.step(ml[t].x, ml[t].y, w);
+          o.x = fmaf(lo[t].x, w, o.x * turn); o.y = fmaf(lo[t].y, w, o.y * turn);
+          o.z = fmaf(hi[t].x, w, o.z * turn); o.w = fmaf(hi[t].y, w, o.w * turn);
+        }
+      *(uint2 *)(lds + (col - k0) * 2) = uint2{pack_bf16x2(o.x / rm.l, o.y / rm.l), pack_bf16x2(o.z / rm.l, o.w / rm.l)};
+    };
+    columns(k0 + tid * 4, first_weights);
+    for (int col = k0 + (tid + kThreads) * 4; col < k1; col += kThreads * 4) columns(col, []() {});
+  }
+  __syncthreads();
+
+  f32x16_t acc[1];
+#pragma unroll
+  for (int v = 0; v < 16; v++) acc[0][v] = 0.f;
+  const unsigned char *xl = lds + g * kLaneBytes;             // (all 32 token rows of the products are the one row)
+  auto compute = [&](const u32x4_t (&w)[8], int it) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 8; j++) mfma_step(acc[0], *(const u32x4_t *)(xl + it * (2 * kLaneBytes) + j * 16), w[j], bf16_t{});
+  };
+  int it = 0;
+  for (; it + 2 * kStages - 1 <= n_iter; it += kStages)       // every load is in range: no branch, exact waits
+#pragma unroll
+    for (int u = 0; u < kStages; u++) {
+      load_w(ring[(u + kStages - 1) % kStages], it + u + kStages - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(ring[u], it + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+  for (int u = 0; u < 2 * kStages - 2; u++)
+    if (it + u < n_iter) {
+      if (it + u + kStages - 1 < n_iter) load_w(ring[(u + kStages - 1) % kStages], it + u + kStages - 1);
+      compute(ring[u % kStages], it + u);
+    }
+
+  if (a.act != nullptr) {
+    const int col = blk * 16 + (c & 15);
+    swiglu_epilogue<1>(acc, (bf16_t *)a.act + col, seg_rows, col, active && col < seg_rows, 1, c, g);
+    return;
+  }
+  if (active && row < seg_rows && g == 0) store_through(&a.part[(size_t)by * a.m_pad * a.ldp + seg_col0 + row], acc[0][0]);
+}
+
 // ---- more than 128 token rows, bf16 (prefill, LM head of the loss) ------------------------------
 // Here the matrix cores are the limit, and what holds them up is the arrival of operands.  A workgroup of eight wavefronts
 // (two per SIMD, so that one's products cover the other's waits) owns TW*TB 32-token blocks x (8/TW)*WB 32-row weight blocks
@@ -649,8 +842,6 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_mixed_kernel(GemmArgs a
 // rotary table is filled by a workgroup per token block that has no weights.  Same operations in the same order as the row kernels: same bits.
 // Request of the small fp32 model (66 launches a cycle -> 50) 4.54 -> 4.25 ms.
 constexpr int kHeadCols = 512;                                // widest row
-struct NoHead {};
-template <int KIND> using HeadArg = std::conditional_t<KIND == kHeadNone, NoHead, GemmHead>;
 template <int RB, int KIND>
 __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a, HeadArg<KIND> head) {
   constexpr int E = RB * 4;                                   // sums per lane
@@ -687,8 +878,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a, Head
   const float *xrow = xbase + (size_t)(r < m_loc ? r : 0) * a.ldx, *erow = nullptr;
   if constexpr (KIND == kHeadConcat) {
     const int i = m0 + (r < m_loc ? r : 0);
-    xrow = head.feat + (size_t)(head.src_row ? head.src_row[i] : i) * head.d;
-    erow = head.embed + (size_t)head.token[i] * head.d - head.d;
+    xrow = (const float *)head.feat + (size_t)(head.src_row ? head.src_row[i] : i) * head.d;
+    erow = (const float *)head.embed + (size_t)head.token[i] * head.d - head.d;
   }
   constexpr bool kRows = KIND == kHeadSums || KIND == kHeadEmbed;
   constexpr int kXStride = kHeadCols + 4;                     // floats of a row in the LDS
@@ -733,11 +924,11 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs a, Head
     for (int b = 0; b < NB; b++) {
       const int c = b * 256 + lane * 4, cc = c < head.d ? c : 0;
       if (b * 256 >= head.d) continue;
-      nw[b] = head.norm_w != nullptr ? *(const f32x4_t *)(head.norm_w + cc) : f32x4_t{1.f, 1.f, 1.f, 1.f};
+      nw[b] = head.norm_w != nullptr ? *(const f32x4_t *)((const float *)head.norm_w + cc) : f32x4_t{1.f, 1.f, 1.f, 1.f};
 #pragma unroll
       for (int j = 0; j < 4; j++) {
         const int i = m0 + min(wave + 4 * j, m_loc - 1);
-        if constexpr (KIND == kHeadEmbed) v[j][b] = *(const f32x4_t *)(head.embed + (size_t)head.token[i] * head.d + cc);
+        if constexpr (KIND == kHeadEmbed) v[j][b] = *(const f32x4_t *)((const float *)head.embed + (size_t)head.token[i] * head.d + cc);
         else v[j][b] = *(const f32x4_t *)(head.part + (size_t)i * head.ldp + cc);
       }
     }
@@ -1280,7 +1471,18 @@ static hipError_t launch_f32(const GemmArgs &a, hipStream_t st, const GemmHead *
 // draft, 256 wide, launches of their own / this: draft of 4-row passes 157 / 139, of 10 367 / 342, of 16 507 / 480; verify and accept of 16 rows 97 / 91,
 // 60 97 / 95, 128 107.5 / 105.5); of up to 512 with at most three rows a wavefront (512 wide: drafts of 4 rows 169.5 / 163, of 10 394 / 390, of 16 525 / 528; verify of one
 // row 93.7 / 92, of 16 101.5 / 108, 60 109.5 / 115.5, 128 125.5 / 130).
+static bool row_takes_head(const GemmArgs &a, const GemmHead &h) {
+  if (a.m != 1 || a.x2 != nullptr || a.fold || a.n_split < 1) return false;
+  const int slabs = (a.in + gemm_k_per_slab(1) - 1) / gemm_k_per_slab(1);
+  if (row_bytes(slabs / a.n_split, slabs % a.n_split) > kRowLds) return false;
+  if (h.kind == kHeadParts) return a.in == h.merge.hq * h.merge.hd && h.merge.hd % 4 == 0 && ((uintptr_t)h.merge.part & 7) == 0;
+  const uintptr_t low = (uintptr_t)a.x | (uintptr_t)h.part | (uintptr_t)h.h_in | (uintptr_t)h.h_out;
+  return h.kind == kHeadSums && a.in == h.d && h.d % 4 == 0 && h.d <= kRowMaxCols && h.ldp % 4 == 0 && h.n_split >= 1 && (low & 15) == 0 &&
+         ((uintptr_t)h.norm_w & 7) == 0;
+}
 bool gemm_takes_head(int dtype, const GemmArgs &a, const GemmHead &h) {
+  if (dtype == 1) return row_takes_head(a, h);
+  if (h.kind == kHeadParts) return false;
   if (dtype != 0 || h.kind == kHeadNone || a.m < 1 || a.m > kMaxNodes || a.x2 != nullptr || h.d % 4 || h.d > (a.m <= 12 ? kHeadCols : 256) || f32_tiled_pays(a))
     return false;
   if (h.kind != kHeadSums && (h.rope.table == nullptr || h.rope.half < 1)) return false;
@@ -1541,6 +1743,15 @@ void gemm_plan(int m, int sets, int blocks, int in, int n_split, int *waves, int
   *whole = mm_big_tiles(m, sets, weight_tiles, in, n_split);
 }
 
+template <int KIND, int WAVES>
+static hipError_t launch_row(GemmArgs a, const GemmHead &head, hipStream_t st) {
+  const int per_wg = std::min(WAVES, stream_blocks(a.total_blocks, a.n_split));   // blocks of a workgroup, on as many compute units as there are
+  a.grid_x = (a.total_blocks + per_wg - 1) / per_wg;
+  a.blk_per_wg = 1; a.blk_per_wave = a.grid_x;
+  hipLaunchKernelGGL((gemm_row_kernel<KIND, WAVES>), dim3(a.grid_x, a.n_split), dim3(WAVES * kWave), row_bytes(a.slab_base, a.slab_rem), st, a, head);
+  return hipGetLastError();
+}
+
 template <bool PAIR>
 static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
   const int tb = ((PAIR ? 2 * a.m : a.m) + 31) / 32;
@@ -1570,8 +1781,9 @@ static hipError_t launch_stream(GemmArgs a, hipStream_t st) {
 }
 
 // Up to 128 rows in all the launch is bound by the weights, read once; a pair of row sets shares that one pass.
-static hipError_t launch_bf16(const GemmArgs &a, hipStream_t st) {
+static hipError_t launch_bf16(const GemmArgs &a, hipStream_t st, const GemmHead *head) {
   const long long rows = (long long)a.m * (a.x2 ? 2 : 1);
+  if (head != nullptr) return head->kind == kHeadSums ? launch_row<kHeadSums, 8>(a, *head, st) : launch_row<kHeadParts, kGemmWaves>(a, *head, st);
   if (a.fold && !gemm_can_fold(a)) return hipErrorInvalidValue;
   if (rows <= 128 && !a.fold) return a.x2 ? launch_stream<true>(a, st) : launch_stream<false>(a, st);
   if (mm_takes(a)) return launch_mm(a, st);
@@ -1605,7 +1817,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs &args, hipStream_t st, const Ge
   const uint64_t inv = ~0ull / (uint64_t)a.n_split + 1;       // ceil(2^64 / n_split); 0 for n_split = 1
   a.slab_base = slabs / a.n_split; a.slab_rem = slabs % a.n_split;
   a.split_hi = (uint32_t)(inv >> 32); a.split_lo = (uint32_t)inv;
-  return dtype == 1 ? launch_bf16(a, st) : launch_f32(a, st, head);
+  return dtype == 1 ? launch_bf16(a, st, head) : launch_f32(a, st, head);
 }
 
 }  // namespace spec

@@ -31,6 +31,8 @@ __host__ __device__ inline int attn_part_begin(int t) {
 __host__ __device__ inline int attn_parts_covering(int keys) {
   return keys <= kAttnNear ? (keys + kAttnPart - 1) / kAttnPart : kAttnNear / kAttnPart + (keys - kAttnNear + kAttnFarPart - 1) / kAttnFarPart;
 }
+// End of the bulk region of a row at position p: the tail is the last kMaxDepth + 1 positions.  See attention.hip.
+__host__ __device__ inline int bulk_end(int p) { return p > kMaxDepth ? p - kMaxDepth : 0; }
 constexpr int kTopkSlice = 4096;       // vocabulary entries per first-stage top-k workgroup
 
 // ---- gemm.hip --------------------------------------------------------------------------------
@@ -59,22 +61,29 @@ struct GemmArgs {
 // (cos, sin) of pos[i] * theta^(-j/half) for j < half -> table[i * half + j], the angles formed in double precision; table == nullptr: nothing to fill
 struct RopeFill { const int *pos; int half; double log2_theta; float2 *table; };
 RopeFill make_rope_fill(const int *pos, int head_dim, float theta, float2 *table);
-// The row kernel that makes a GEMM's x, run by the GEMM's own launch (fp32, small models: gemm_takes_head).  Nothing that it reads is written by the launch.
+// The row kernel that makes a GEMM's x, run by the GEMM's own launch (narrow fp32 rows, one bf16 row: gemm_takes_head).  Nothing that it reads is written by
+// the launch.
 enum HeadKind {
   kHeadNone = 0,
   kHeadSums,                            // launch_reduce_add_norm: h_out[i] = (residual ? h_in[i] : 0) + sum_s part[s][i], x[i] = norm of h_out[i]
   kHeadEmbed,                           // launch_embed_norm: h_out[i] = embed[token[i]], x[i] = norm of h_out[i]; fills the rotary table
-  kHeadConcat                           // launch_concat_feat_embed: x[i] = [feat[src_row ? src_row[i] : i] ; embed[token[i]]], not stored; fills the table
+  kHeadConcat,                          // launch_concat_feat_embed: x[i] = [feat[src_row ? src_row[i] : i] ; embed[token[i]]], not stored; fills the table
+  kHeadParts                            // launch_attn_merge: x[i] = the attention's parts of row i, merged; not stored
 };
+// Partial outputs of an attention that are still to be merged (bf16: the bulk's parts, then the tail in the last slot)
+struct AttnMerge { const float *part; int max_parts, hq, hd, base; const int *base_ptr, *depth; };
+constexpr int kHeadMaxParts = 8;        // parts of a row, the tail among them, that a head merges
+constexpr int kHeadRowsBf16 = 1, kHeadRowsFp32 = kMaxNodes;   // most rows of a launch that makes its own x
 struct GemmHead {
   int kind;
   int d;                                // row length of h, embed and feat
   const float *part; int n_split, m_pad, ldp, residual;
   const float *h_in; float *h_out;
-  const float *norm_w; float eps;       // norm_w == nullptr: x = h_out
-  const float *embed; const int *token;
-  const float *feat; const int *src_row;
+  const void *norm_w; float eps;        // norm_w == nullptr: x = h_out
+  const void *embed; const int *token;
+  const void *feat; const int *src_row;
   RopeFill rope;
+  AttnMerge merge;
 };
 bool gemm_takes_head(int dtype, const GemmArgs &a, const GemmHead &h);
 hipError_t launch_gemm(int dtype, const GemmArgs &a, hipStream_t st, const GemmHead *head = nullptr);
@@ -137,7 +146,9 @@ struct AttnArgs {
 // bf16: rows whose partials of all parts `part` has to hold ([min(rows, kPartialRows)][hq][max_parts][hd + 2], and at least
 // [rows][hq][hd + 2]); a chain (anc == nullptr) of more rows goes in blocks, or keeps one partial per row and head (the tail's).
 constexpr int kPartialRows = 256;
-hipError_t launch_attention(int dtype, const AttnArgs &a, int max_pos, hipStream_t st);
+// merge: where the rows' parts may be left unmerged (few parts of one row, bf16), they are, and *merge says what is to be merged (else merge->part == nullptr).
+hipError_t launch_attention(int dtype, const AttnArgs &a, int max_pos, hipStream_t st, AttnMerge *merge = nullptr);
+hipError_t launch_attn_merge(const AttnMerge &m, int rows, void *out, hipStream_t st);
 
 // ---- hca.hip ---------------------------------------------------------------------------------
 // Training attention over J = n_streams key/value streams: query t (from the newest stream) uses, for the key

@@ -26,13 +26,6 @@ RopeFill make_rope_fill(const int *pos, int head_dim, float theta, float2 *table
 // Thread t owns the 4-column groups t, t + 1024, ... (PER of them, guarded), so all global loads of a
 // row are independent 16-byte loads issued up front, and the row is written exactly once.  With 1024
 // threads a 4096-wide row is one group per thread: the kernel is three dependent memory round trips.
-template <typename T> __device__ __forceinline__ f32x4_t load4(const T *p);
-template <> __device__ __forceinline__ f32x4_t load4<float>(const float *p) { return *(const f32x4_t *)p; }
-template <> __device__ __forceinline__ f32x4_t load4<bf16_t>(const bf16_t *p) {
-  const uint2 u = *(const uint2 *)p;
-  return f32x4_t{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
-                 __uint_as_float(u.y & 0xFFFF0000u)};
-}
 template <typename T> __device__ __forceinline__ void store4(T *p, f32x4_t v);
 template <> __device__ __forceinline__ void store4<float>(float *p, f32x4_t v) { *(f32x4_t *)p = v; }
 template <> __device__ __forceinline__ void store4<bf16_t>(bf16_t *p, f32x4_t v) {

@@ -746,3 +746,38 @@ def test_greedy_walk_over_a_full_tree_takes_nodes_beyond_the_first_wavefront(env
         out += eng.accept(t)
     assert out[:40] == want[:40]
     eng.close()
+
+
+@pytest.mark.parametrize("d,heads,prompt", [(256, (4, 4, 64), 1), (264, (4, 2, 64), 20), (512, (8, 2, 128), 47), (1000, (8, 8, 128), 700), (4096, (16, 16, 64), 300),
+                                            (4104, (32, 32, 128), 130), (8192, (8, 1, 128), 900), (8200, (4, 4, 128), 60)])
+def test_bf16_row_alone_has_the_bits_of_a_row_among_others(env, d, heads, prompt):
+    """A row alone is summed, normed and merged by the projections' own launches, two rows by kernels of their own (also rows of more than 8192 columns and
+    more than eight attention parts): logits, keys and values of every layer have the same bits."""
+    torch, P = env
+    hq, hkv, hd = heads
+    sh = wl.TINY.with_(dtype="bf16", d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ffn=1416)
+    w = P.upload_weights(wl.make_weights(sh), sh.dtype)
+    tokens, logits, kv = [], [], []
+    for tree in ((1, 1, 1), (1, 1, 2)):
+        eng = P.Engine(sh, w, max_seq=1024, tree=tree)
+        out = [eng.prefill(wl.make_prompt(sh, prompt))]
+        for cycle in range(3):                                # launches one by one, then the replayed graph
+            t = eng.draft_tree()
+            if tree[2] == 2:
+                t.token[1] = (t.token[0] + 1) % sh.vocab      # (a sibling that is not taken, as a rule)
+            eng.verify(t)
+            logits.append(eng.logits(t.n_nodes)[0])
+            got = eng.accept(t)
+            if len(got) > 1:
+                pytest.skip("the draft's token was taken")
+            out += got
+        n = prompt + 3
+        kv.append([eng.kv(0, l, n) for l in range(sh.n_layers)])
+        tokens.append(out)
+        eng.close()
+    assert tokens[0] == tokens[1]
+    for a, b in zip(logits[:3], logits[3:]):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+    for one, two in zip(*kv):
+        for a, b in zip(one, two):
+            assert np.array_equal(a, b)
