@@ -484,19 +484,24 @@ int layer_forward(spec_ctx *c, const spec_layer_weights &lw, char *kcache, char 
   auto add_norm = [&](const void *norm, void *out) {          // h += the sums; out = the normed rows
     return [&, norm, out](int r0, int n, int split) { return add_norm_rows(c, r0, n, split, m, 1, norm, out); };
   };
+  AttnRaw raw{};                                              // one bf16 row: the attention takes it as it leaves the projection
   {
     const Seg segs[3] = {{lw.wq, dq}, {lw.wk, dkv}, {lw.wv, dkv}};
     int rc = project(c, c->x, m, d, segs, 3, dq + 2 * dkv, [&](int r0, int n, int split) {
+      if (m == 1 && dt == SPEC_DTYPE_BF16) {
+        raw = AttnRaw{c->part_now, split, (size_t)n * (dq + 2 * dkv), c->rope, rt.slot};
+        return (int)SPEC_OK;
+      }
       HIPCHK(c, launch_reduce_rope_kv(dt, c->part_now, split, n, dq + 2 * dkv, n, g.n_q_heads, g.n_kv_heads, g.head_dim, c->rope + (size_t)r0 * (g.head_dim / 2),
                                       rt.slot + r0, at(c->qbuf, r0, (size_t)dq * 4), kcache, vcache, c->stream));
-      return SPEC_OK;
+      return (int)SPEC_OK;
     });
     if (rc) return rc;
   }
   {
     if (rt.anc != nullptr && m > kMaxNodes) return fail(c, SPEC_EINVAL, "attention: %d rows of a tree", m);   // partial outputs are planned for fewer
     AttnArgs a{};
-    a.q = c->qbuf; a.kcache = kcache; a.vcache = vcache;
+    a.q = c->qbuf; a.kcache = kcache; a.vcache = vcache; a.raw = raw;
     a.rows = m; a.hq = g.n_q_heads; a.hkv = g.n_kv_heads; a.hd = g.head_dim; a.base = base; a.base_ptr = base_ptr;
     a.depth = rt.depth; a.anc = rt.anc;
     a.scale = 1.0f / sqrtf((float)g.head_dim);

@@ -196,9 +196,20 @@ __device__ __forceinline__ void attn_part_body(const AttnArgs &a, int i, int hk,
 // The result goes to the last part slot.
 constexpr int kTailKeys = kMaxDepth + 1;
 static_assert(kTailKeys * 4 == 64, "one wavefront = 16 keys x 4 lanes");
-template <typename T, int HD, int G>
+// The rotary plane j of a head (column col of the partial sums, plane partner HD / 2 further on) from the QKV projection's partial sums, as
+// reduce_rope_kv_kernel forms it.
+__device__ __forceinline__ float2 raw_plane(const AttnRaw &r, int col, int half, int j, bool turned) {
+  float a = r.qkv[col], b = r.qkv[col + half];
+  for (int s = 1; s < r.n_split; s++) { a += r.qkv[(size_t)s * r.split_stride + col]; b += r.qkv[(size_t)s * r.split_stride + col + half]; }
+  if (!turned) return make_float2(a, b);
+  const float2 cs = r.rope[j];
+  return make_float2(rope_first(a, b, cs), rope_second(a, b, cs));
+}
+// RAW: queries, key and value of the row come from the partial sums.  The row's own key and value go to own (LDS, the stored type, key first) and to the caches;
+// all other keys are in the caches.
+template <typename T, int HD, int G, bool RAW = false>
 __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk, int lane, float (*qs)[HD],
-                                               unsigned char *vs, bool store) {
+                                               unsigned char *vs, bool store, T *own = nullptr) {
   constexpr int EPL = Chunk<T>::kEpl;
   constexpr int DPL = HD / 64;                       // output dims per lane (contiguous)
   constexpr int VROW = PartLds<T>::vrow(HD);
@@ -212,7 +223,8 @@ __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk,
   const bool valid = kq <= p;
   const int *anc = a.anc ? a.anc + (size_t)i * kAncStride : nullptr;
   // lanes past position p re-read the row's own key (initialised data; their weight is 0)
-  const int kr = valid ? kq : p;
+  const bool mine = RAW && kq >= p;                  // the row's own key, out of the LDS (the address below is then only a valid one)
+  const int kr = mine ? max(p - 1, 0) : valid ? kq : p;
   const int slot = kr < base ? kr : base + (anc ? anc[kr - base] : kr - base);
   const size_t row_stride = (size_t)a.hkv * HD;
   const T *kptr = (const T *)a.kcache + (size_t)slot * row_stride + (size_t)hk * HD + qt * QD;
@@ -222,9 +234,34 @@ __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk,
   for (int dc = 0; dc < QC; dc++) kc[dc] = *(const u32x4_t *)(kptr + dc * EPL);
 #pragma unroll
   for (int dc = 0; dc < QC; dc++) vc[dc] = *(const u32x4_t *)(vptr + dc * EPL);
-  const float *qrow = (const float *)a.q + ((size_t)i * a.hq + (size_t)hk * G) * HD;   // queries are fp32
-  for (int e = lane; e < G * HD; e += 64) qs[e / HD][e % HD] = qrow[e];
+  if constexpr (RAW) {
+    constexpr int half = HD / 2;
+    T *const cache[2] = {(T *)a.kcache, (T *)a.vcache};
+    const size_t at = ((size_t)a.raw.slot[i] * a.hkv + hk) * HD;
+#pragma unroll
+    for (int e0 = 0; e0 < (G + 2) * half; e0 += 64) {         // heads of the group, then the key, then the value
+      const int e = e0 + lane, head = e / half, j = e % half;
+      if (e >= (G + 2) * half) continue;                      // (head dim 64, an odd number of heads)
+      const int col = (head < G ? hk * G + head : head == G ? a.hq + hk : a.hq + a.hkv + hk) * HD + j;
+      const float2 x = raw_plane(a.raw, col, half, j, head <= G);
+      if (head < G) { qs[head][j] = x.x; qs[head][j + half] = x.y; continue; }
+      const T x0 = from_f32<T>(x.x), x1 = from_f32<T>(x.y);
+      T *const o = own + (head - G) * HD, *const c = cache[head - G] + at;
+      o[j] = x0; o[j + half] = x1;
+      if (store) { c[j] = x0; c[j + half] = x1; }
+    }
+  } else {
+    const float *qrow = (const float *)a.q + ((size_t)i * a.hq + (size_t)hk * G) * HD;   // queries are fp32
+    for (int e = lane; e < G * HD; e += 64) qs[e / HD][e % HD] = qrow[e];
+  }
   wave_lds_sync();
+  if (mine) {
+#pragma unroll
+    for (int dc = 0; dc < QC; dc++) {
+      kc[dc] = *(const u32x4_t *)(own + qt * QD + dc * EPL);
+      vc[dc] = *(const u32x4_t *)(own + HD + qt * QD + dc * EPL);
+    }
+  }
   float s[G];
 #pragma unroll
   for (int gh = 0; gh < G; gh++) s[gh] = 0.f;
@@ -479,7 +516,9 @@ struct PartSoftmax {
 #endif
 constexpr int kBulkRing = SPEC_ATTN_RING;   // register sets for K/V blocks in flight per bulk workgroup
 template <int NW> struct TailWaves { static constexpr int value = NW < 4 ? NW : 4; };
-template <int HD, int G, int NW>
+// RAW: one row, whose queries, key and value every workgroup takes from the QKV projection's partial sums (a launch of 4.7 us ahead of this one before;
+// its way from launch to launch is what it cost).
+template <int HD, int G, int NW, bool RAW = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_hybrid_kernel(AttnArgs a) {
   constexpr int DB = HD / 32;                 // 32-dim blocks of the output
   constexpr int KK = HD / 16;                 // MFMA steps of q.k
@@ -488,11 +527,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int PIECES = (32 * HD * 2 / 16 + NT - 1) / NT;   // 16-byte pieces of one K (or V) block per thread
   constexpr int kTailWaves = TailWaves<NW>::value;
   constexpr int kTailQ = G * HD * 4;                                         // a tail wavefront's query area
-  constexpr int kTailWave = kTailQ + kTailKeys * PartLds<bf16_t>::vrow(HD);  // ... plus its staged value rows
+  constexpr int kTailVs = kTailQ + kTailKeys * PartLds<bf16_t>::vrow(HD);    // ... plus its staged value rows
+  constexpr int kTailWave = kTailVs + (RAW ? 2 * HD * 2 : 0);                // ... plus the row's own key and value
   constexpr int kBulkBuf = 32 * KSTR + 32 * HD * 2;                          // one staged K block + V block
   constexpr int kBulkLds = 2 * kBulkBuf;                                     // double-buffered
   constexpr int kLds = kBulkLds > kTailWaves * kTailWave ? kBulkLds : kTailWaves * kTailWave;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  __shared__ __attribute__((aligned(16))) float raw_q[RAW ? G * HD : 4];
 
   const int n_bulk = a.bulk_parts * a.hkv * a.q_groups;
   if ((int)blockIdx.x >= n_bulk) {
@@ -502,7 +543,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const bool active = item < a.rows * a.hkv;
     if (!active) item = a.rows * a.hkv - 1;               // valid addresses; result discarded
     unsigned char *mine = lds + w * kTailWave;
-    attn_tail_body<bf16_t, HD, G>(a, item / a.hkv, item % a.hkv, threadIdx.x & 63, (float (*)[HD])mine, mine + kTailQ, active);
+    attn_tail_body<bf16_t, HD, G, RAW>(a, item / a.hkv, item % a.hkv, threadIdx.x & 63, (float (*)[HD])mine, mine + kTailQ, active, (bf16_t *)(mine + kTailVs));
     return;
   }
   const int part = (int)blockIdx.x % a.bulk_parts, hk = ((int)blockIdx.x / a.bulk_parts) % a.hkv;
@@ -583,9 +624,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   auto run = [&](auto nb_tag) {
     constexpr int NB = decltype(nb_tag)::value;
     static_assert(NB >= 1 && NB <= 16, "a part is unrolled block by block");
+    if constexpr (RAW) {
+      for (int e = tid; e < G * (HD / 2); e += NT) {
+        const int head = e / (HD / 2), j = e % (HD / 2);
+        const float2 x = raw_plane(a.raw, (hk * G + head) * HD + j, HD / 2, j, true);
+        raw_q[head * HD + j] = x.x; raw_q[head * HD + j + HD / 2] = x.y;
+      }
+    }
     unrolled<(R < NB ? R : NB)>([&](auto t_tag) { prefetch(t_tag, b_lo + decltype(t_tag)::value); });
+    if constexpr (RAW) __syncthreads();
     {
-      const float *qrow = (const float *)a.q + ((size_t)i * a.hq + (size_t)hk * G + gh) * HD;
+      const float *qrow = RAW ? raw_q + gh * HD : (const float *)a.q + ((size_t)i * a.hq + (size_t)hk * G + gh) * HD;
 #pragma unroll
       for (int kk = 0; kk < KK; kk++) {
         float x[8];
@@ -680,7 +729,14 @@ template <int HD, int G, int NW>
 static hipError_t launch_hybrid(AttnArgs a, int q_groups, hipStream_t st) {
   a.q_groups = q_groups;
   const int n_tail = (a.rows * a.hkv + TailWaves<NW>::value - 1) / TailWaves<NW>::value;
-  hipLaunchKernelGGL((attn_hybrid_kernel<HD, G, NW>), dim3(a.bulk_parts * a.hkv * q_groups + n_tail), dim3(NW * 64), 0, st, a);
+  const dim3 grid(a.bulk_parts * a.hkv * q_groups + n_tail), threads(NW * 64);
+  if constexpr (NW == 4) {
+    if (a.raw.qkv != nullptr) {
+      hipLaunchKernelGGL((attn_hybrid_kernel<HD, G, NW, true>), grid, threads, 0, st, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((attn_hybrid_kernel<HD, G, NW>), grid, threads, 0, st, a);
   return hipGetLastError();
 }
 
@@ -1006,6 +1062,7 @@ hipError_t launch_attention(int dtype, const AttnArgs &args, int max_pos, hipStr
   AttnArgs a = args;
   a.scale = (float)((double)a.scale * 1.4426950408889634);    // scores in units of log2
   if (a.rows < 1 || a.hkv < 1 || a.hq % a.hkv != 0) return hipErrorInvalidValue;
+  if (a.raw.qkv != nullptr && (dtype != 1 || a.rows != 1)) return hipErrorInvalidValue;
   if (a.hd == 128) return dtype == 1 ? launch_th<bf16_t, 128>(a, max_pos, st, merge) : launch_th<float, 128>(a, max_pos, st, merge);
   if (a.hd == 64) return dtype == 1 ? launch_th<bf16_t, 64>(a, max_pos, st, merge) : launch_th<float, 64>(a, max_pos, st, merge);
   return hipErrorInvalidValue;

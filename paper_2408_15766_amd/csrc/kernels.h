@@ -130,6 +130,8 @@ hipError_t launch_chain_rows(int base, int rows, int pos_offset, int *pos, int *
 // Row i sits at key position base + depth[i] and attends to positions 0 .. base + depth[i]:
 // position q < base lives in cache slot q; position q >= base lives in slot base + anc[i][q - base]
 // (anc == nullptr: slot q, i.e. a causal chain).  Output [rows, hq*hd] in the storage type.
+// One bf16 row may come as the QKV projection's partial sums instead (qkv != nullptr): the attention then does what launch_reduce_rope_kv does first.
+struct AttnRaw { const float *qkv; int n_split; size_t split_stride; const float2 *rope; const int *slot; };
 struct AttnArgs {
   const void *q;                        // fp32 [rows, hq*hd]
   const void *kcache; const void *vcache;
@@ -137,6 +139,7 @@ struct AttnArgs {
   const int *base_ptr;                  // if not null: the base is read from here (device) and `base` is ignored
   const int *depth;                     // [rows]
   const int *anc;                       // [rows][kAncStride] or nullptr
+  AttnRaw raw;                          // raw.qkv != nullptr (bf16, one row): q is not read, and the row's key and value are written to the caches here
   float scale;
   float *part;                          // scratch: [rows][hq][max_parts][hd + 2]; max_parts >= attn_parts_covering(max_pos + 1) + 1
   int max_parts;
