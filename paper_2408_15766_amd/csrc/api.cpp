@@ -475,21 +475,23 @@ int layer_keys_values(spec_ctx *c, const spec_layer_weights &lw, char *kcache, c
 
 // One decoder layer over m rows.  In: c->h (fp32 residual stream) and c->x (rows normed by the
 // layer's attn_norm).  Out: c->h updated; x_out = rmsnorm(h) * next_norm (or h itself, cast).
+// apart: no row attends to another row of this forward.
 int layer_forward(spec_ctx *c, const spec_layer_weights &lw, char *kcache, char *vcache, int m, int base,
-                  const RowTables &rt, int max_pos, const void *next_norm, void *x_out, const int *base_ptr = nullptr) {
+                  const RowTables &rt, int max_pos, const void *next_norm, void *x_out, const int *base_ptr = nullptr, bool apart = false) {
   const spec_config &g = c->cfg;
+  apart |= m == 1;
   const int d = g.d_model, dq = g.n_q_heads * g.head_dim, dkv = g.n_kv_heads * g.head_dim, f = g.d_ffn;
   const int dt = g.dtype;
   auto at = [](const void *p, size_t r, size_t row_bytes) { return (void *)((char *)p + r * row_bytes); };
   auto add_norm = [&](const void *norm, void *out) {          // h += the sums; out = the normed rows
     return [&, norm, out](int r0, int n, int split) { return add_norm_rows(c, r0, n, split, m, 1, norm, out); };
   };
-  AttnRaw raw{};                                              // one bf16 row: the attention takes it as it leaves the projection
+  AttnRaw raw{};                                              // the attention takes the rows as they leave the projection
   {
     const Seg segs[3] = {{lw.wq, dq}, {lw.wk, dkv}, {lw.wv, dkv}};
     int rc = project(c, c->x, m, d, segs, 3, dq + 2 * dkv, [&](int r0, int n, int split) {
-      if (m == 1 && dt == SPEC_DTYPE_BF16) {
-        raw = AttnRaw{c->part_now, split, (size_t)n * (dq + 2 * dkv), c->rope, rt.slot};
+      if (apart && n == m && attention_takes_raw(dt, m, g.n_q_heads, g.n_kv_heads)) {
+        raw = AttnRaw{c->part_now, split, dq + 2 * dkv, (size_t)n * (dq + 2 * dkv), c->rope, rt.slot};
         return (int)SPEC_OK;
       }
       HIPCHK(c, launch_reduce_rope_kv(dt, c->part_now, split, n, dq + 2 * dkv, n, g.n_q_heads, g.n_kv_heads, g.head_dim, c->rope + (size_t)r0 * (g.head_dim / 2),
@@ -581,7 +583,7 @@ int target_forward(spec_ctx *c, int m, int base, const RowTables &rt, int max_po
 // keys_only: the rows' keys and values alone.  That is all that the prompt's pairs are for: nobody reads what the draft predicts at them, so the
 // attention and the three projections behind it are not run (request of 4096 prompt tokens at 16 layers of the 8B widths 68.5 -> 66.5 ms).
 int draft_forward(spec_ctx *c, int m, int base, const void *feat, const int *src_row, const RowTables &rt, int max_pos,
-                  const int *base_ptr = nullptr, bool keys_only = false) {
+                  const int *base_ptr = nullptr, bool keys_only = false, bool apart = false) {
   const spec_config &g = c->cfg;
   const int d = g.d_model;
   if (!keys_only && m > c->m_small) return fail(c, SPEC_EINVAL, "draft: %d rows", m);   // gfeat holds no more
@@ -602,7 +604,7 @@ int draft_forward(spec_ctx *c, int m, int base, const void *feat, const int *src
   char *kc = c->kv_d;
   char *vc = kc + c->d_kv_stride * c->esz;
   if (keys_only) return layer_keys_values(c, c->w.draft_layer, kc, vc, m, rt);
-  return layer_forward(c, c->w.draft_layer, kc, vc, m, base, rt, max_pos, nullptr, c->gfeat, base_ptr);
+  return layer_forward(c, c->w.draft_layer, kc, vc, m, base, rt, max_pos, nullptr, c->gfeat, base_ptr, apart);
 }
 
 int sync(spec_ctx *c) {
@@ -679,7 +681,7 @@ int draft_static(spec_ctx *c, int m1) {
     const int rows = st.rows[d];
     if (rows == 0) break;                                     // no node of this depth has children: nothing deeper exists
     RowTables fr{c->ds.front_tok, c->ds.front_pos, c->ds.front_slot, c->ds.front_depth, c->ds.front_anc};
-    int rc = draft_forward(c, rows, c->n, c->gfeat, c->ds.front_src, fr, c->n + d - 1);
+    int rc = draft_forward(c, rows, c->n, c->gfeat, c->ds.front_src, fr, c->n + d - 1, nullptr, false, true);
     if (rc) return rc;
     rc = lm_head(c, c->gfeat, rows, c->dlogits);
     if (rc) return rc;
@@ -886,7 +888,8 @@ int spec_draft_tree(spec_ctx *c, spec_tree *out) {
     for (int t = 2; t <= D; t++) {
       RowTables fr{c->ds.front_tok, c->ds.front_pos, c->ds.front_slot, c->ds.front_depth, c->ds.front_anc};
       // xcat is built from gfeat before the layer overwrites gfeat, so one buffer serves all steps
-      r = draft_forward(c, K, 0, c->gfeat, c->ds.front_src, fr, bound ? bound : c->n + t - 2, c->t_base);
+      // (the frontier's rows are of one depth: their ancestors' keys are in the cache)
+      r = draft_forward(c, K, 0, c->gfeat, c->ds.front_src, fr, bound ? bound : c->n + t - 2, c->t_base, false, true);
       if (r) return r;
       r = lm_head(c, c->gfeat, K, c->dlogits);
       if (r) return r;

@@ -196,15 +196,36 @@ __device__ __forceinline__ void attn_part_body(const AttnArgs &a, int i, int hk,
 // The result goes to the last part slot.
 constexpr int kTailKeys = kMaxDepth + 1;
 static_assert(kTailKeys * 4 == 64, "one wavefront = 16 keys x 4 lanes");
-// The rotary plane j of a head (column col of the partial sums, plane partner HD / 2 further on) from the QKV projection's partial sums, as
-// reduce_rope_kv_kernel forms it.
-__device__ __forceinline__ float2 raw_plane(const AttnRaw &r, int col, int half, int j, bool turned) {
-  float a = r.qkv[col], b = r.qkv[col + half];
-  for (int s = 1; s < r.n_split; s++) { a += r.qkv[(size_t)s * r.split_stride + col]; b += r.qkv[(size_t)s * r.split_stride + col + half]; }
-  if (!turned) return make_float2(a, b);
-  const float2 cs = r.rope[j];
-  return make_float2(rope_first(a, b, cs), rope_second(a, b, cs));
+// The rotary planes j .. j + 3 of a head (columns col .. of the partial sums, the planes' partners HD / 2 further on) of row i from the QKV projection's partial sums,
+// as reduce_rope_kv_kernel forms them; all loads first, up to four splits (absent ones read split 0 again and are left out).
+struct RawPlanes { f32x4_t a, b; };
+__device__ __forceinline__ RawPlanes raw_planes(const AttnRaw &r, int i, int col, int half, int j, bool turned) {
+  constexpr int NS = 4;
+  const float *p = r.qkv + (size_t)i * r.ldp + col;
+  const f32x4_t *cs = (const f32x4_t *)(r.rope + (size_t)i * half + j);
+  const f32x4_t cs0 = cs[0], cs1 = cs[1];                     // (cos, sin) of planes j, j + 1 and j + 2, j + 3
+  f32x4_t pa[NS], pb[NS];
+#pragma unroll
+  for (int s = 0; s < NS; s++) {
+    const float *q = p + (size_t)(s < r.n_split ? s : 0) * r.split_stride;
+    pa[s] = *(const f32x4_t *)q; pb[s] = *(const f32x4_t *)(q + half);
+  }
+  RawPlanes x{pa[0], pb[0]};
+#pragma unroll
+  for (int s = 1; s < NS; s++)
+    if (s < r.n_split) { x.a += pa[s]; x.b += pb[s]; }
+  for (int s = NS; s < r.n_split; s++) { x.a += *(const f32x4_t *)(p + (size_t)s * r.split_stride); x.b += *(const f32x4_t *)(p + (size_t)s * r.split_stride + half); }
+  if (turned) {
+    const float2 c[4] = {{cs0.x, cs0.y}, {cs0.z, cs0.w}, {cs1.x, cs1.y}, {cs1.z, cs1.w}};
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float u = rope_first(x.a[e], x.b[e], c[e]), v = rope_second(x.a[e], x.b[e], c[e]);
+      x.a[e] = u; x.b[e] = v;
+    }
+  }
+  return x;
 }
+__device__ __forceinline__ uint2 pack4(f32x4_t v) { return uint2{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)}; }
 // RAW: queries, key and value of the row come from the partial sums.  The row's own key and value go to own (LDS, the stored type, key first) and to the caches;
 // all other keys are in the caches.
 template <typename T, int HD, int G, bool RAW = false>
@@ -235,20 +256,21 @@ __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk,
 #pragma unroll
   for (int dc = 0; dc < QC; dc++) vc[dc] = *(const u32x4_t *)(vptr + dc * EPL);
   if constexpr (RAW) {
-    constexpr int half = HD / 2;
+    static_assert(sizeof(T) == 2, "bf16 rows");
+    constexpr int half = HD / 2, per_head = half / 4;
     T *const cache[2] = {(T *)a.kcache, (T *)a.vcache};
     const size_t at = ((size_t)a.raw.slot[i] * a.hkv + hk) * HD;
 #pragma unroll
-    for (int e0 = 0; e0 < (G + 2) * half; e0 += 64) {         // heads of the group, then the key, then the value
-      const int e = e0 + lane, head = e / half, j = e % half;
-      if (e >= (G + 2) * half) continue;                      // (head dim 64, an odd number of heads)
+    for (int e0 = 0; e0 < (G + 2) * per_head; e0 += 64) {     // heads of the group, then the key, then the value
+      const int e = e0 + lane, head = e / per_head, j = e % per_head * 4;
+      if (e >= (G + 2) * per_head) continue;
       const int col = (head < G ? hk * G + head : head == G ? a.hq + hk : a.hq + a.hkv + hk) * HD + j;
-      const float2 x = raw_plane(a.raw, col, half, j, head <= G);
-      if (head < G) { qs[head][j] = x.x; qs[head][j + half] = x.y; continue; }
-      const T x0 = from_f32<T>(x.x), x1 = from_f32<T>(x.y);
-      T *const o = own + (head - G) * HD, *const c = cache[head - G] + at;
-      o[j] = x0; o[j + half] = x1;
-      if (store) { c[j] = x0; c[j + half] = x1; }
+      const RawPlanes x = raw_planes(a.raw, i, col, half, j, head <= G);
+      if (head < G) { *(f32x4_t *)&qs[head][j] = x.a; *(f32x4_t *)&qs[head][j + half] = x.b; continue; }
+      const uint2 x0 = pack4(x.a), x1 = pack4(x.b);
+      T *const o = own + (head - G) * HD + j, *const c = cache[head - G] + at + j;
+      *(uint2 *)o = x0; *(uint2 *)(o + half) = x1;
+      if (store) { *(uint2 *)c = x0; *(uint2 *)(c + half) = x1; }
     }
   } else {
     const float *qrow = (const float *)a.q + ((size_t)i * a.hq + (size_t)hk * G) * HD;   // queries are fp32
@@ -516,8 +538,9 @@ struct PartSoftmax {
 #endif
 constexpr int kBulkRing = SPEC_ATTN_RING;   // register sets for K/V blocks in flight per bulk workgroup
 template <int NW> struct TailWaves { static constexpr int value = NW < 4 ? NW : 4; };
-// RAW: one row, whose queries, key and value every workgroup takes from the QKV projection's partial sums (a launch of 4.7 us ahead of this one before;
-// its way from launch to launch is what it cost).
+// RAW: queries, keys and values come from the QKV projection's partial sums: every bulk workgroup forms its queries, a tail wavefront its row's query, key and
+// value.  The launch for that, 4.7 us ahead of this one, was mostly the way from launch to launch: 7B, one row at 90 keys 4.7 + 6.7 -> 7.0 us, a draft
+// pass of ten rows at 530 4.8 + 8.4 -> 9.1, 8B, ten rows (40 queries to a key) at 4100 4.8 + 13.6 -> 16.0, four at 1340 4.9 + 12.2 -> 13.4.
 template <int HD, int G, int NW, bool RAW = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_hybrid_kernel(AttnArgs a) {
   constexpr int DB = HD / 32;                 // 32-dim blocks of the output
@@ -533,7 +556,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int kBulkLds = 2 * kBulkBuf;                                     // double-buffered
   constexpr int kLds = kBulkLds > kTailWaves * kTailWave ? kBulkLds : kTailWaves * kTailWave;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
-  __shared__ __attribute__((aligned(16))) float raw_q[RAW ? G * HD : 4];
+  static_assert(!RAW || kRawQueries * HD * 4 <= kLds, "the queries lie where the keys and values will");
 
   const int n_bulk = a.bulk_parts * a.hkv * a.q_groups;
   if ((int)blockIdx.x >= n_bulk) {
@@ -625,16 +648,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     constexpr int NB = decltype(nb_tag)::value;
     static_assert(NB >= 1 && NB <= 16, "a part is unrolled block by block");
     if constexpr (RAW) {
-      for (int e = tid; e < G * (HD / 2); e += NT) {
-        const int head = e / (HD / 2), j = e % (HD / 2);
-        const float2 x = raw_plane(a.raw, (hk * G + head) * HD + j, HD / 2, j, true);
-        raw_q[head * HD + j] = x.x; raw_q[head * HD + j + HD / 2] = x.y;
+      constexpr int per_head = HD / 8;
+      for (int e = tid; e < a.rows * G * per_head; e += NT) { // (rows * G <= kRawQueries)
+        const int query = e / per_head, j = e % per_head * 4;
+        const RawPlanes x = raw_planes(a.raw, query / G, (hk * G + query % G) * HD + j, HD / 2, j, true);
+        *(f32x4_t *)((float *)lds + query * HD + j) = x.a;
+        *(f32x4_t *)((float *)lds + query * HD + j + HD / 2) = x.b;
       }
     }
     unrolled<(R < NB ? R : NB)>([&](auto t_tag) { prefetch(t_tag, b_lo + decltype(t_tag)::value); });
     if constexpr (RAW) __syncthreads();
     {
-      const float *qrow = RAW ? raw_q + gh * HD : (const float *)a.q + ((size_t)i * a.hq + (size_t)hk * G + gh) * HD;
+      const float *qrow = RAW ? (const float *)lds + (i * G + gh) * HD : (const float *)a.q + ((size_t)i * a.hq + (size_t)hk * G + gh) * HD;
 #pragma unroll
       for (int kk = 0; kk < KK; kk++) {
         float x[8];
@@ -643,6 +668,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         split8(x, qhi[kk], qlo[kk]);
       }
     }
+    if constexpr (RAW) __syncthreads();
     stage(std::integral_constant<int, 0>{}, 0);
     __syncthreads();
     if constexpr (R < NB) prefetch(std::integral_constant<int, 0>{}, b_lo + R);
@@ -1062,7 +1088,7 @@ hipError_t launch_attention(int dtype, const AttnArgs &args, int max_pos, hipStr
   AttnArgs a = args;
   a.scale = (float)((double)a.scale * 1.4426950408889634);    // scores in units of log2
   if (a.rows < 1 || a.hkv < 1 || a.hq % a.hkv != 0) return hipErrorInvalidValue;
-  if (a.raw.qkv != nullptr && (dtype != 1 || a.rows != 1)) return hipErrorInvalidValue;
+  if (a.raw.qkv != nullptr && (!attention_takes_raw(dtype, a.rows, a.hq, a.hkv) || a.raw.ldp % 4 || a.raw.split_stride % 4)) return hipErrorInvalidValue;
   if (a.hd == 128) return dtype == 1 ? launch_th<bf16_t, 128>(a, max_pos, st, merge) : launch_th<float, 128>(a, max_pos, st, merge);
   if (a.hd == 64) return dtype == 1 ? launch_th<bf16_t, 64>(a, max_pos, st, merge) : launch_th<float, 64>(a, max_pos, st, merge);
   return hipErrorInvalidValue;

@@ -130,8 +130,11 @@ hipError_t launch_chain_rows(int base, int rows, int pos_offset, int *pos, int *
 // Row i sits at key position base + depth[i] and attends to positions 0 .. base + depth[i]:
 // position q < base lives in cache slot q; position q >= base lives in slot base + anc[i][q - base]
 // (anc == nullptr: slot q, i.e. a causal chain).  Output [rows, hq*hd] in the storage type.
-// One bf16 row may come as the QKV projection's partial sums instead (qkv != nullptr): the attention then does what launch_reduce_rope_kv does first.
-struct AttnRaw { const float *qkv; int n_split; size_t split_stride; const float2 *rope; const int *slot; };
+// bf16 rows may come as the QKV projection's partial sums instead (qkv != nullptr; attention_takes_raw): the attention then does what
+// launch_reduce_rope_kv does first.  No row may attend to another row's new key: ancestors are in the caches already.
+struct AttnRaw { const float *qkv; int n_split, ldp; size_t split_stride; const float2 *rope; const int *slot; };
+constexpr int kRawQueries = 64;         // rows x heads of a kv head's group
+inline bool attention_takes_raw(int dtype, int rows, int hq, int hkv) { return dtype == 1 && rows * (hq / hkv) <= kRawQueries; }
 struct AttnArgs {
   const void *q;                        // fp32 [rows, hq*hd]
   const void *kcache; const void *vcache;
@@ -139,7 +142,7 @@ struct AttnArgs {
   const int *base_ptr;                  // if not null: the base is read from here (device) and `base` is ignored
   const int *depth;                     // [rows]
   const int *anc;                       // [rows][kAncStride] or nullptr
-  AttnRaw raw;                          // raw.qkv != nullptr (bf16, one row): q is not read, and the row's key and value are written to the caches here
+  AttnRaw raw;                          // raw.qkv != nullptr: q is not read, and the rows' keys and values are written to the caches here
   float scale;
   float *part;                          // scratch: [rows][hq][max_parts][hd + 2]; max_parts >= attn_parts_covering(max_pos + 1) + 1
   int max_parts;

@@ -781,3 +781,31 @@ def test_bf16_row_alone_has_the_bits_of_a_row_among_others(env, d, heads, prompt
     for one, two in zip(*kv):
         for a, b in zip(one, two):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("heads,prompt", [((8, 1, 128), 5), ((8, 1, 128), 300), ((16, 2, 64), 77), ((8, 2, 128), 1300)])
+def test_bf16_draft_rows_turned_by_the_attention_have_the_rope_kernels_bits(env, heads, prompt):
+    """Up to 64 queries to a kv head are taken from the projection's partial sums by the attention, more go through a kernel of their own (10 or 16 rows of 8 or 4
+    heads against 8): what the draft thinks of a node has the same bits whichever way its parent's row went."""
+    torch, P = env
+    hq, hkv, hd = heads
+    sh = wl.TINY.with_(dtype="bf16", d_model=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ffn=1416)
+    w = P.upload_weights(wl.make_weights(sh), sh.dtype)
+    many = 10 if hq // hkv == 8 else 16
+    found = []
+    for k, total in ((8, 73), (many, 111 if many == 10 else 128)):
+        eng = P.Engine(sh, w, max_seq=1536, tree=(2, k, total))
+        eng.prefill(wl.make_prompt(sh, prompt))
+        for _ in range(2):                                    # launches one by one, then the replayed graph
+            t = eng.draft_tree()
+            nodes = {}
+            for j in range(1, t.n_nodes):
+                par = t.parent[j]
+                nodes[(t.token[par] if par else -1, t.token[j])] = t.score[j].tobytes()
+            found.append(nodes)
+            eng.verify(t)
+            eng.accept(t)
+        eng.close()
+    for a, b in zip(found[:2], found[2:]):
+        common = set(a) & set(b)
+        assert len(common) >= 60 and all(a[n] == b[n] for n in common)
