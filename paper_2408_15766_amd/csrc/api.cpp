@@ -1390,15 +1390,14 @@ constexpr int kLossChunk = 512;                               // positions whose
 // The slices' results of as many chunks as this holds are merged by one launch: a merge of 512 positions is one wavefront for
 // each and takes 7 us, most of it the launch and two dependent reads; one of 4096 takes 10 instead of eight times 7.
 constexpr size_t kLossMergeFloats = (16u << 20) / sizeof(float);
-struct LossLayout { int chunk, merged, ldz; size_t zq, zp, rows_topk, rows_ce, cand, least, total; };   // offsets in floats
+struct LossLayout { int chunk, merged, ldz; size_t zq, rows_topk, rows_ce, cand, least, total; };   // offsets in floats
 LossLayout loss_layout(int rows, int vocab, int k) {
   LossLayout l{};
   l.chunk = rows < kLossChunk ? rows : kLossChunk;
   l.ldz = (vocab + 63) / 64 * 64;
   auto up = [](size_t x) { return (x + 63) / 64 * 64; };
   size_t o = 0;
-  l.zq = o; o += up((size_t)l.chunk * l.ldz);
-  l.zp = o; o += up((size_t)l.chunk * l.ldz);
+  l.zq = o; o += 2 * (size_t)l.chunk * l.ldz;                 // target rows of a chunk, then the draft's
   l.rows_topk = o; o += up((size_t)rows);                     // used when the caller does not want the per-row losses
   l.rows_ce = o; o += up((size_t)rows);
   l.cand = o;
@@ -1436,7 +1435,7 @@ int spec_topk_loss(int32_t dtype, const void *feat_target, const void *feat_draf
   for (int r0 = 0; r0 < rows; r0 += l.chunk) {
     const int m = rows - r0 < l.chunk ? rows - r0 : l.chunk;
     const void *xs[2] = {(const char *)feat_target + (size_t)r0 * d * esz, (const char *)feat_draft + (size_t)r0 * d * esz};
-    float *zs[2] = {sf + l.zq, sf + l.zp};
+    float *zs[2] = {sf + l.zq, sf + l.zq + (size_t)m * l.ldz};   // one behind the other, so that the launch may take them as one set of rows
     GemmArgs a{};                                             // the LM head over both sides' rows: fp32 logits
     a.x = xs[0]; a.x2 = xs[1]; a.ldx = d; a.m = m; a.in = d;
     for (int s = 0; s < 3; s++) { a.seg_w[s] = lm_head; a.seg_rows[s] = 0; a.seg_blocks[s] = 0; a.seg_col0[s] = 0; }

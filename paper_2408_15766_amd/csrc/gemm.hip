@@ -597,7 +597,9 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
   }
   // the X rows this wave copies: row segment rs = (t * 2 + g) * 32 + c holds the 64 bytes (32 k) of half g, its four 16-byte
   // pieces rotated by the row so that the fragment reads of eight consecutive rows touch all banks
-  const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const char *)(second ? x_1 : x_0) + (size_t)m0 * a.ldx * 2);
+  const int join = FOLD ? 0 : pinned(a.join);
+  const uint32_t x_off0 = pinned(a.x_off[0]), x_off1 = pinned(a.x_off[1]);
+  const __amdgpu_buffer_rsrc_t xsrc = buffer_of((const char *)(second ? x_1 : x_0) + (join ? 0 : (size_t)m0 * a.ldx * 2));
   uint32_t xoff[XI];
   int xk[XI];
 #pragma unroll
@@ -606,7 +608,8 @@ __device__ __forceinline__ void mm_tile_body(const GemmArgs &a, int bx, int by, 
     const int rc = rs & 31, rg = (rs >> 5) & 1, row = (rs >> 6) * 32 + rc;
     const int piece = (lane & 3) ^ ((rc >> 2) & 3);
     xk[i] = it_begin * 128 + rg * 64 + piece * 8;
-    xoff[i] = (uint32_t)(row < m_loc ? row : 0) * (uint32_t)a.ldx * 2u;
+    const int r = row < m_loc ? row : 0, r_all = m0 + r;
+    xoff[i] = (uint32_t)(!join ? r : r_all < join ? r_all : r_all - join) * (uint32_t)a.ldx * 2u + (!join ? 0u : r_all < join ? x_off0 : x_off1);
   }
   auto load_w = [&](unsigned char *buf, int s, int i0, int i1) {
     s = min(s, n_stage - 1);                                  // past the end: the last stage again (never read)
@@ -805,8 +808,14 @@ __global__ __launch_bounds__(kMmThreads, 2) void gemm_mm_mixed_kernel(GemmArgs a
   const int x = (int)blockIdx.x % 8, j = (int)blockIdx.x / 8;
   const int n_q = (l.weight_tiles - x + 7) / 8, n_full = n_q * l.full;
   int ql, set, m0;
-  const bool big = j < a.n_big;
-  if (big || j - a.n_big < 2 * (n_full - a.n_big)) {
+  const bool big = a.beside ? j % (l.full + l.ragged) < l.full : j < a.n_big;
+  if (a.beside) {
+    const int t = j % (l.full + l.ragged);
+    ql = j / (l.full + l.ragged);
+    if (ql >= n_q) return;
+    set = big ? t / l.set_full : t - l.full;
+    m0 = (big ? t % l.set_full : l.set_full) * L::kTok;
+  } else if (big || j - a.n_big < 2 * (n_full - a.n_big)) {
     const int h = big ? 0 : j - a.n_big, t = big ? j : a.n_big + h / 2;
     if (t >= n_full) return;
     ql = t / l.full;
@@ -1658,6 +1667,7 @@ static hipError_t launch_mm_mixed(GemmArgs a, hipStream_t st) {
   a.n_big = mm_big_tiles(a.m, sets, l.weight_tiles, a.in, a.n_split);
   const int n_q = (l.weight_tiles + 7) / 8;                   // (of XCD 0, the longest list)
   const int list = a.n_big + 2 * (n_q * l.full - a.n_big) + n_q * l.ragged;
+  a.beside = a.join && l.ragged > 0 && l.full > 0 && a.n_big == n_q * l.full;
   hipLaunchKernelGGL(gemm_mm_mixed_kernel, dim3(8 * list), dim3(kMmThreads), 0, st, a);
   return hipGetLastError();
 }
@@ -1671,7 +1681,33 @@ static float mm_xcd_us(int tile, int m, int blocks, int in, int ranges) {   // m
 // round of 256 workgroups instead of one and a half of 384: 136 us a launch in a request -> 96 alone (107 as two sets of sums); 1333 rows 75 (81), 70B QKV of
 // 1024 rows 170 (180).  A 4096-token prompt on 16 layers of the 8B widths 60.5 -> 59.6 ms a request, 1333 tokens on 8 layers 19.54 -> 19.30.
 int gemm_fold_tile(int m, int blocks, int in) { return mm_xcd_us(1, m, blocks, in, 1) < 0.97f * mm_xcd_us(2, m, blocks, in, 1) ? 1 : 2; }
-static hipError_t launch_mm(const GemmArgs &a, hipStream_t st) {
+// Two sets of rows as one of twice the rows, its tiles running across the border: where that takes fewer tiles of 128 rows (a set's last, partly filled one
+// is then the only one), the launch fills the chip all the same and the results of the second set follow those of the first.  A weight tile's ragged end
+// then runs beside its whole tiles, so that the weights come from HBM once.  Row offsets are 32-bit.  Measured (us a loss, K = 4096 unless said, apart /
+// joined): vocabulary 32000, 188 positions 145 / 134, 257 216 / 204, 300 223 / 210; 128256, 300, K = 2048 496 / 423, 700 (188 in the last chunk)
+// 1666 / 1647; with the ragged ends behind all whole tiles 300 x 128256 took 470.  Vocabulary 1000, 188 positions, 12 tiles: 52.8 / 54.3, left apart,
+// as are sets that would get a ragged end of a few rows where they have none (129 positions 137 / 137 to 150: its padding reads one row over and over).
+static bool join_pays(int m, int blocks) {
+  const long long tiles = (2ll * m + 127) / 128;
+  if (m % 256 > 128 && m % 256 < 144) return false;
+  return tiles < (m + 127) / 128 * 2ll && tiles * ((blocks + 7) / 8) >= 256;
+}
+static bool mm_joins(const GemmArgs &a) {
+  if (a.x2 == nullptr || a.act != nullptr || a.n_split != 1 || !join_pays(a.m, a.total_blocks)) return false;
+  if (a.part2 != a.part + (ptrdiff_t)a.m * a.ldp) return false;
+  const uintptr_t x = (uintptr_t)a.x, x2 = (uintptr_t)a.x2, apart = x < x2 ? x2 - x : x - x2;
+  return apart < (1u << 30) && 2ll * a.m * a.ldx + a.in < (1ll << 29);
+}
+static hipError_t launch_mm(const GemmArgs &args, hipStream_t st) {
+  GemmArgs a = args;
+  a.join = 0;
+  if (mm_joins(a)) {
+    const uintptr_t x = (uintptr_t)a.x, x2 = (uintptr_t)a.x2, base = std::min(x, x2);
+    a.x_off[0] = (uint32_t)(x - base); a.x_off[1] = (uint32_t)(x2 - base);
+    a.x = (const void *)base; a.x2 = nullptr; a.part2 = nullptr;
+    a.join = a.m;
+    a.m *= 2; a.m_pad = std::max(a.m_pad, a.m);
+  }
   if (a.fold) return gemm_fold_tile(a.m, a.total_blocks, a.in) == 1 ? launch_mm_tile<4, 2, 3, true>(a, st) : launch_mm_tile<2, 2, 2, true>(a, st);
   switch (mm_tile(a.m, a.x2 ? 2 : 1, a.total_blocks, a.in, a.n_split)) {
     case 0: return launch_mm_mixed(a, st);
@@ -1737,6 +1773,7 @@ static int stream_waves(int tb, int blocks, int in, int n_split) {   // tb: 32-r
 void gemm_plan(int m, int sets, int blocks, int in, int n_split, int *waves, int *whole, int *tiles) {
   *waves = *whole = *tiles = 0;
   if ((long long)m * sets <= 128) { *waves = stream_waves((m * sets + 31) / 32, blocks, in, n_split); return; }
+  if (sets == 2 && n_split == 1 && join_pays(m, blocks)) { m *= 2; sets = 1; }   // (where the sets' addresses allow it)
   if (mm_tile(m, sets, blocks, in, n_split) != 0) return;
   const int weight_tiles = (blocks + 7) / 8 * n_split;
   *tiles = (weight_tiles + 7) / 8 * mm_lists(m, sets, weight_tiles).full;

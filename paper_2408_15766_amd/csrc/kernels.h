@@ -53,6 +53,9 @@ struct GemmArgs {
   // act[i][c] = silu(gate) * up in the storage type instead of partial sums.
   void *act;
   int m_tiles, grid_x;                  // set by launch_gemm: token tiles, workgroups per tile and split
+  int join;                             // set by launch_gemm: not 0: rows join .. of x follow the first `join` as the second set's, at x_off[1] bytes from x ..
+  uint32_t x_off[2];                    // .. the first set's at x_off[0] (gemm_mm kernels)
+  int beside;                           // set by launch_gemm: a weight tile's ragged ends follow its whole tiles (gemm_mm_mixed_kernel)
   int n_big;                            // set by launch_gemm: whole 256 x 256 tiles per XCD (gemm_mm_mixed_kernel)
   int slab_base, slab_rem;              // set by launch_gemm: slabs per split, and how many are left over (slab_begin in gemm.hip)
   uint32_t split_hi, split_lo;          // set by launch_gemm: ceil(2^64 / n_split)

@@ -345,3 +345,23 @@ def test_topk_loss_error_paths_and_optional_outputs(env):
     torch.cuda.synchronize()
     want, _, want_ce = oracle_losses(ft, fd, w, 10)
     np.testing.assert_allclose(tot.cpu().numpy(), [want.sum(), want_ce.sum()], rtol=2e-4)
+
+
+@pytest.mark.parametrize("rows,d,vocab", [(144, 64, 22000), (188, 136, 33000), (192, 64, 22016), (300, 72, 16500), (513, 64, 22000)])
+def test_both_sides_rows_as_one_set_of_tiles(env, rows, d, vocab):
+    """Where the sides' rows take fewer tiles together, one launch runs over them as one set: the border inside a 32-row block, inside a tile and (192 rows) at
+    the end of a half tile, either side first in memory, a second chunk of one position."""
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(5, rows, d, vocab, "bf16")
+    ft, fd = (torch.from_numpy(x).cuda().to(torch.bfloat16) for x in (ft, fd))
+    packed = P.spec_pack_weight(torch.from_numpy(w).cuda().to(torch.bfloat16))
+    got = []
+    for first, second in ((ft, fd), (fd, ft)):
+        both = torch.stack([first, second])
+        a, b = (both[0], both[1]) if first is ft else (both[1], both[0])
+        got.append([t.cpu() for t in P.spec_topk_loss(a, b, packed, 7)[:2]])
+    assert all(torch.equal(x, y) for x, y in zip(*got))
+    head = torch.from_numpy(w).to(torch.bfloat16).double()
+    zq, zp = ft.cpu().double() @ head.T, fd.cpu().double() @ head.T
+    want = -(torch.softmax(zq, -1) * torch.log_softmax(zp, -1)).sum(-1)
+    np.testing.assert_allclose(got[0][1].numpy(), want.numpy(), rtol=2e-4, atol=2e-4)      # as the oracle's cases
