@@ -77,20 +77,20 @@ __device__ __forceinline__ void wave_lds_order() {
 // of 8 the XCD placement would leave XCDs idle or uneven; the ids then run chunk by chunk over all groups.)
 constexpr int kHcaChunk = 8;
 struct Place { int qt, gh, bi, hk; };
-__device__ __forceinline__ Place place(const HcaArgs &a, int rows) {   // rows: queries per workgroup
+__device__ __forceinline__ Place place(const HcaArgs &a, int rows, int chunk_most = kHcaChunk) {   // rows: queries per workgroup
   const int G = a.hq / a.hkv;
   const int n_qt = (a.seq + rows - 1) / rows;
   const int n_grp = a.batch * a.hkv;
   const bool affine = (n_grp & 7) == 0;
   const int grp_per_list = affine ? n_grp >> 3 : n_grp;      // groups whose workgroups form one ordered list
   const int r_id = affine ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
-  const int chunk_wgs = kHcaChunk * G * n_qt;                // workgroups of a full chunk
+  const int chunk_wgs = chunk_most * G * n_qt;               // workgroups of a full chunk
   const int chunk = r_id / chunk_wgs, in_chunk = r_id % chunk_wgs;
-  const int chunk_grps = min(kHcaChunk, grp_per_list - chunk * kHcaChunk);   // the last chunk may be short
+  const int chunk_grps = min(chunk_most, grp_per_list - chunk * chunk_most);   // the last chunk may be short
   const int qt = n_qt - 1 - in_chunk / (chunk_grps * G);
   const int in_tile = in_chunk % (chunk_grps * G);
   const int gh = in_tile % G;
-  const int grp_local = chunk * kHcaChunk + in_tile / G;
+  const int grp_local = chunk * chunk_most + in_tile / G;
   const int grp = affine ? grp_local * 8 + ((int)blockIdx.x & 7) : grp_local;
   return Place{qt, gh, grp / a.hkv, grp % a.hkv};
 }
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
       const float m_use = m_new == -INFINITY ? 0.f : m_new;
       const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
       const float p = have ? __builtin_amdgcn_exp2f(sc - m_use) : 0.f;
-      l_run = l_run * corr + (g == 0 ? p : 0.f);               // the two lanes of a query add up their sums at the end
+      l_run = fmaf(l_run, corr, g == 0 ? p : 0.f);             // the two lanes of a query add up their sums at the end
       m_run = m_new;
 #pragma unroll
       for (int db = 0; db < DB; db++)
@@ -394,198 +394,234 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 }
 
 // ---- launches that leave the chip idle ------------------------------------------------------------
-// A workgroup = 8 wavefronts and 32 queries; the wavefronts share out the KEYS, 32 at a time (wavefront w takes blocks w, w + 8, ..), and the band (one
-// stream each, the last ones first: they have the fewest blocks), each with a softmax of its own, and merge in the LDS at the end.  Nothing is shared
-// before that, so there is no barrier in the loop: keys go from memory into the fragments, value rows into the wavefront's own LDS
-// area and out of it by the transposing read.  A 128-query tile's chain of T / 64 blocks becomes one of T / 256 half as long ones on four times as many
-// workgroups; the price is that every 32 queries load their keys and values themselves, so it is only for launches that do not fill the chip (split_pays).
-// Bound: latency (launch, first rows, two blocks, merge) up to 300 positions, then the chain of a block, about 1.5 us at head dim 128.  Four heads of 128, 2048 positions, three
-// streams 53.6 -> 27.1 us; 333 positions, 16 heads of 64 10.4 -> 6.5.
+// A workgroup = 4 wavefronts and 32 queries; the wavefronts share out the KEYS, a block of kBlockKeys each a round, and do what hca_attention_kernel
+// does, operation by operation: a sequence's outputs have the same bits in a launch of any size.  What does not depend on the blocks before is
+// done side by side: a block's scores and their maximum.  The chain of references runs through the maxima of a round's blocks, every wavefront
+// for itself, and with its own block's reference a wavefront forms the probabilities and their sum.  What is left in the blocks' order is
+// O^T += V^T P^T, and there the output's 32-dim parts do not depend on each other: wavefront db takes a round's blocks one after the other for dims
+// 32 db .. from the LDS (probabilities as fragments, value rows as they are, transposed by the read).  The band's products with the queries are
+// formed ahead, a stream a wavefront, and its value rows wait in the LDS.  A 128-query tile's chain of T / 64 blocks becomes one of T / 256 rounds on
+// four times as many workgroups; the price is that every 32 queries load their keys and values themselves, so it is only for launches that do not
+// fill the chip (split_pays).
+// Bound: latency up to 300 positions (launch, first rows, two barriers a round), then the way of a round's 256 keys from the L2 with nothing of the next
+// round under it: requested ahead they spill at head dim 128 (2048 positions 33 -> 42 us) and gain nothing at 64.  Four heads of 128, 2048 positions, three
+// streams 51.7 -> 33.2 us (hca_attention_kernel / this); 333 positions, 16 heads of 64, two streams 9.8 -> 7.1.  Wavefronts with a softmax of their own that merge at the end need no
+// rounds, 25.5 and 6.0, but add up in another order: a sequence then differed by rounding (1.6e-3) with the number of sequences and heads beside it.
+// Eight wavefronts in halves: 31.9 and 6.9, 256 positions of 32 heads 7.3 -> 8.2.
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 // Value rows in the LDS, HD * 2 bytes each; the 64-byte chunks are permuted by the row so that the four rows of a column read lie in different banks.
 template <int HD> __device__ __forceinline__ int value_chunk(int row, int chunk) { return chunk ^ (HD == 128 ? row & 3 : (row >> 1) & 1); }
 __device__ __forceinline__ u32x2_t read_columns(const unsigned char *p) {
   return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)p));
 }
+// (each rounded by itself: hca_attention_kernel multiplies in a branch of its own)
+__device__ __forceinline__ float turn_add(float l, float turn, float ls) {
+#pragma clang fp contract(off)
+  const float x = l * turn;
+  return x + ls;
+}
 
-constexpr int kSplitWaves = 8;
+constexpr int kSplitWaves = 4;
 template <int HD> struct SplitLds {
-  static constexpr int vals = 32 * HD * 2;              // a wavefront's value rows
-  static constexpr int orow = (HD + 4) * 4;             // a query's partial output (+4 floats: rows in different banks)
-  static constexpr int part = 32 * orow;                // ... and a wavefront's
-  static constexpr int stat = kSplitWaves * (vals > part ? vals : part);   // references, then sums, [wavefront][query]
-  static constexpr int total = stat + 2 * kSplitWaves * 32 * 4;
+  static constexpr int vals = kBlockKeys * HD * 2;      // a block's value rows
+  static constexpr int probs = 32 * kBlockKeys * 2;     // ... and probabilities
+  static constexpr int probs0 = kSplitWaves * vals;     // (of a round's blocks)
+  static constexpr int max0 = probs0 + kSplitWaves * probs;   // two sets (rounds alternate) of the blocks' maxima, [block][query] ..
+  static constexpr int sum0 = max0 + 2 * kSplitWaves * 32 * 4;    // .. and sums, [block][lane]
+  static constexpr int score0 = sum0 + 2 * kSplitWaves * 64 * 4;  // the band's scores, [stream][query]
+  static constexpr int band0 = score0 + (kMaxStreams - 1) * 32 * 4;   // ... and value rows, [stream][query]
+  static constexpr int brow = HD * 2 + 16;
+  static constexpr int total(int streams) { return band0 + (streams - 1) * 32 * brow; }
 };
 
 template <int HD>
-__global__ __launch_bounds__(kSplitWaves * 64, HD == 64 ? 4 : 2) void hca_split_kernel(HcaArgs a) {
+__global__ __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void hca_split_kernel(HcaArgs a) {
   using L = SplitLds<HD>;
-  constexpr int DB = HD / 32, KK = HD / 16, PPR = HD * 2 / 16, VP = 32 * PPR / 64;
+  constexpr int W = kSplitWaves, DB = HD / 32, KK = HD / 16, PPR = HD * 2 / 16, VP = kBlockKeys * PPR / 64, BP = 32 * PPR / 64;
+  static_assert(DB <= W, "a wavefront per 32 dims");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const Place at = place(a, 32);
+  const Place at = place(a, 32, a.batch * a.hkv);             // (few workgroups: one list, longest tile first)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 31, g = lane >> 5;
   const int T = a.seq, J = a.n_streams, G = a.hq / a.hkv;
   const float c2 = a.scale_log2e;
   const size_t kv_stride = (size_t)a.hkv * HD, kv_off = (size_t)at.bi * T * kv_stride + (size_t)at.hk * HD;
   const bf16_t *kg = (const bf16_t *)a.k[0] + kv_off, *vg = (const bf16_t *)a.v[0] + kv_off;
-  const int r0 = at.qt * 32, tq = min(r0 + c, T - 1);         // queries past the end compute on the last one and are not stored
+  const int r0 = at.qt * 32, t = r0 + c, tq = min(t, T - 1);  // queries past the end compute on the last one and are not stored
   const int lim = tq - (J - 1);
   const int last = min(r0 + 31, T - 1) - (J - 1);             // last old-region key of any query
-  const int nb = last >= 0 ? last / 32 + 1 : 0;
-  const bf16_t *qrow = (const bf16_t *)a.q + (((size_t)at.bi * T + tq) * a.hq + (size_t)at.hk * G + at.gh) * HD;
-  u32x4_t qf[KK], kf[KK], vr[VP];
+  const int nb = last >= 0 ? last / kBlockKeys + 1 : 0;
+  const size_t q_off = (((size_t)at.bi * T + tq) * a.hq + (size_t)at.hk * G + at.gh) * HD;
+  float *const max_sh = (float *)(lds + L::max0), *const sum_sh = (float *)(lds + L::sum0), *const score_sh = (float *)(lds + L::score0);
+  u32x4_t qf[KK], kf[kKeyTiles][KK], vr[VP];
 #pragma unroll
-  for (int kk = 0; kk < KK; kk++) qf[kk] = *(const u32x4_t *)(qrow + kk * 16 + g * 8);
-  f32x16_t o[DB];
-#pragma unroll
-  for (int db = 0; db < DB; db++)
-#pragma unroll
-    for (int v = 0; v < 16; v++) o[db][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  for (int kk = 0; kk < KK; kk++) qf[kk] = *(const u32x4_t *)((const bf16_t *)a.q + q_off + kk * 16 + g * 8);
 
-  auto load_k = [&](int blk) __attribute__((always_inline)) {   // (keys past the end: the last one, masked)
-    const bf16_t *row = kg + (size_t)min(blk * 32 + c, T - 1) * kv_stride + g * 8;
+  // A block's loads are a uniform base and 32-bit offsets (a launch of few workgroups has few heads).  Keys past the end are the last one, masked.
+  const uint32_t row_bytes = (uint32_t)kv_stride * 2;
+  auto load_k = [&](int blk) __attribute__((always_inline)) {
+    const unsigned char *const base = (const unsigned char *)(kg + (size_t)blk * kBlockKeys * kv_stride);
+    const int most = T - 1 - blk * kBlockKeys;
 #pragma unroll
-    for (int kk = 0; kk < KK; kk++) kf[kk] = *(const u32x4_t *)(row + kk * 16);
-  };
-  auto load_v = [&](int blk) __attribute__((always_inline)) {
+    for (int kt = 0; kt < kKeyTiles; kt++) {
+      const uint32_t row = (uint32_t)min(kt * 32 + c, most) * row_bytes + g * 16;
 #pragma unroll
-    for (int e = 0; e < VP; e++) {
-      const int idx = lane + 64 * e;
-      vr[e] = *(const u32x4_t *)(vg + (size_t)min(blk * 32 + idx / PPR, T - 1) * kv_stride + (idx % PPR) * 8);
+      for (int kk = 0; kk < KK; kk++) kf[kt][kk] = *(const u32x4_t *)(base + row + kk * 32);
     }
   };
+  auto load_v = [&](int blk) __attribute__((always_inline)) {
+    const unsigned char *const base = (const unsigned char *)(vg + (size_t)blk * kBlockKeys * kv_stride);
+    const int most = T - 1 - blk * kBlockKeys;
+#pragma unroll
+    for (int e = 0; e < VP; e++) vr[e] = *(const u32x4_t *)(base + ((uint32_t)min(lane / PPR + e * (64 / PPR), most) * row_bytes + lane % PPR * 16));
+  };
 
-  const int off = kSplitWaves - 1 - wave;                     // this wavefront's band stream is J - 1 - off
-  static_assert(kMaxStreams - 1 <= kSplitWaves, "a wavefront per band stream");
-  if (off <= J - 2) {
-    // key tq - off of its stream for every query; a lane pair shares the dot product by the dims of its query fragments and the value row
-    // by the dims of its output registers
-    const size_t row = kv_off + (size_t)max(tq - off, 0) * kv_stride;
-    const bf16_t *kr = (const bf16_t *)a.k[J - 1 - off] + row + g * 8, *vb = (const bf16_t *)a.v[J - 1 - off] + row + 4 * g;
-    u32x2_t bv[DB * 4];
+  // the band: key tq - off of stream J-1-off for every query, off = J-2 .. 0.  A lane pair shares the product by the dims of its query fragments.
+  for (int off = W - 1 - wave; off <= J - 2; off += W) {      // (the last wavefronts first: they have the fewest blocks)
+    const bf16_t *kb = (const bf16_t *)a.k[J - 1 - off] + kv_off, *vb = (const bf16_t *)a.v[J - 1 - off] + kv_off;
+    u32x4_t bk[KK], bv[BP];
 #pragma unroll
-    for (int kk = 0; kk < KK; kk++) kf[kk] = *(const u32x4_t *)(kr + kk * 16);
+    for (int kk = 0; kk < KK; kk++) bk[kk] = *(const u32x4_t *)(kb + (size_t)max(tq - off, 0) * kv_stride + kk * 16 + g * 8);
 #pragma unroll
-    for (int e = 0; e < DB * 4; e++) bv[e] = *(const u32x2_t *)(vb + e * 8);
+    for (int e = 0; e < BP; e++) {
+      const int idx = lane + 64 * e;
+      bv[e] = *(const u32x4_t *)(vb + (size_t)min(max(r0 + idx / PPR - off, 0), T - 1) * kv_stride + (idx % PPR) * 8);
+    }
     float dot = 0.f;
 #pragma unroll
     for (int kk = 0; kk < KK; kk++) {
-      const uint32_t kx[4] = {kf[kk].x, kf[kk].y, kf[kk].z, kf[kk].w}, qx[4] = {qf[kk].x, qf[kk].y, qf[kk].z, qf[kk].w};
+      const uint32_t kx[4] = {bk[kk].x, bk[kk].y, bk[kk].z, bk[kk].w}, qx[4] = {qf[kk].x, qf[kk].y, qf[kk].z, qf[kk].w};
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         dot = fmaf(lo_f32(qx[e]), lo_f32(kx[e]), dot);
         dot = fmaf(hi_f32(qx[e]), hi_f32(kx[e]), dot);
       }
     }
-    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(dot), __float_as_uint(dot), false, false);
-    dot = __uint_as_float(both[0]) + __uint_as_float(both[1]);
-    if (tq - off >= 0) {
-      m_run = dot * c2;                                       // the only key so far: probability 1
-      l_run = g == 0 ? 1.f : 0.f;                             // the two lanes of a query add up their sums at the end
+    dot += __shfl_xor(dot, 32, 64);
+    if (g == 0) score_sh[off * 32 + c] = tq - off >= 0 ? dot * c2 : -INFINITY;
 #pragma unroll
-      for (int e = 0; e < DB * 4; e++) {
-        const int db = e >> 2, v = 4 * (e & 3);
-        o[db][v] = lo_f32(bv[e].x); o[db][v + 1] = hi_f32(bv[e].x); o[db][v + 2] = lo_f32(bv[e].y); o[db][v + 3] = hi_f32(bv[e].y);
-      }
+    for (int e = 0; e < BP; e++) {
+      const int idx = lane + 64 * e;
+      *(u32x4_t *)(lds + L::band0 + (off * 32 + idx / PPR) * L::brow + (idx % PPR) * 16) = bv[e];
     }
   }
 
-  unsigned char *const vals = lds + wave * L::vals;
+  f32x16_t o;                                                 // dims 32 wave .. of this wavefront's part of the output
+#pragma unroll
+  for (int v = 0; v < 16; v++) o[v] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
   const int vrow = 4 * g + ((lane & 15) >> 2);                // a lane's place in a column read: row and 8 bytes of it
-  const int vcol = wave * L::vals + vrow * HD * 2 + value_chunk<HD>(vrow, 0) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
-  if (wave < nb) { load_v(wave); load_k(wave); }
-  for (int blk = wave; blk < nb; blk += kSplitWaves) {
+  const int vcol = (vrow * HD * 2 + value_chunk<HD>(vrow, 0) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8) ^ 64 * wave;
+  for (int b0 = 0, set = 0; b0 < nb; b0 += W, set ^= 1) {
+    const int blk = b0 + wave;
+    const bool live = blk < nb;
+    f32x16_t s[kKeyTiles];
+    float mb2 = -INFINITY;
+    if (live) {
+      load_k(blk);
+      load_v(blk);
 #pragma unroll
-    for (int e = 0; e < VP; e++) {
-      const int idx = lane + 64 * e, row = idx / PPR, piece = idx % PPR;
-      *(u32x4_t *)(vals + row * HD * 2 + value_chunk<HD>(row, piece >> 2) * 64 + (piece & 3) * 16) = vr[e];
+      for (int kt = 0; kt < kKeyTiles; kt++) {
+#pragma unroll
+        for (int v = 0; v < 16; v++) s[kt][v] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; kk++) s[kt] = mfma16(kf[kt][kk], qf[kk], s[kt]);
+      }
+      // s[kt][v] = q . k for key blk*kBlockKeys + kt*32 + 8*(v/4) + 4*g + v%4 and query c
+      if (blk * kBlockKeys + kBlockKeys - 1 > r0 - (J - 1)) {  // the block reaches past some query's region
+        const int key0 = blk * kBlockKeys + 4 * g;
+#pragma unroll
+        for (int kt = 0; kt < kKeyTiles; kt++)
+#pragma unroll
+          for (int v = 0; v < 16; v++)
+            if (key0 + kt * 32 + 8 * (v >> 2) + (v & 3) > lim) s[kt][v] = -INFINITY;
+      }
+      float mb = -INFINITY;
+#pragma unroll
+      for (int kt = 0; kt < kKeyTiles; kt++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) mb = fmaxf(mb, s[kt][v]);
+      mb2 = max_halves(mb) * c2;
     }
-    if (blk + kSplitWaves < nb) load_v(blk + kSplitWaves);
-    f32x16_t s;
+    if (g == 0) max_sh[(set * W + wave) * 32 + c] = mb2;
+    __syncthreads();                                          // the round's maxima are there, and the round before is used up
+
+    // the chain of references: a block's moves it by more than 2^8 only (as in hca_attention_kernel)
+    float corr[W], m_own = -INFINITY;
 #pragma unroll
-    for (int v = 0; v < 16; v++) s[v] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < KK; kk++) s = mfma16(kf[kk], qf[kk], s);
-    if (blk + kSplitWaves < nb) load_k(blk + kSplitWaves);
-    // s[v] = q . k for key blk*32 + 8*(v/4) + 4*g + v%4 and query c
-    if (blk * 32 + 31 > r0 - (J - 1)) {                       // the block reaches past some query's region
-#pragma unroll
-      for (int v = 0; v < 16; v++)
-        if (blk * 32 + 4 * g + 8 * (v >> 2) + (v & 3) > lim) s[v] = -INFINITY;
-    }
-    float mb = s[0];
-#pragma unroll
-    for (int v = 1; v < 16; v++) mb = fmaxf(mb, s[v]);
-    mb = max_halves(mb) * c2;
-    const bool move = mb > m_run + 8.f;                       // (as in hca_attention_kernel: the reference moves by more than 2^8 only)
-    if (__any(move)) {
-      const float m_new = move ? mb : m_run;
-      const float corr = move ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
-      l_run *= corr;
+    for (int j = 0; j < W; j++) {
+      const float mbj = max_sh[(set * W + j) * 32 + c];
+      const bool move = mbj > m_run + 8.f;
+      const float m_new = move ? mbj : m_run;
+      corr[j] = move ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
       m_run = m_new;
-#pragma unroll
-      for (int db = 0; db < DB; db++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) o[db][v] *= corr;
+      if (j == wave) m_own = m_run;
     }
-    const float m_use = m_run == -INFINITY ? 0.f : m_run;
-    float p[16];
-    uint32_t pk[8];
+    uint32_t pk[kKeyTiles * 8];                               // probabilities, two bf16 per word
+    if (live) {
+      const float m_use = m_own == -INFINITY ? 0.f : m_own;   // nothing seen yet: every term below becomes 0
+      float ls = 0.f;
 #pragma unroll
-    for (int v = 0; v < 16; v++) { p[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c2, -m_use)); l_run += p[v]; }
+      for (int kt = 0; kt < kKeyTiles; kt++) {
+        float p[16];
 #pragma unroll
-    for (int e = 0; e < 8; e++) pk[e] = pack_bf16x2(p[2 * e], p[2 * e + 1]);
-    wave_lds_order();
+        for (int v = 0; v < 16; v++) { p[v] = __builtin_amdgcn_exp2f(fmaf(s[kt][v], c2, -m_use)); ls += p[v]; }
 #pragma unroll
-    for (int h = 0; h < 2; h++) {                             // 16 keys: V^T fragment (A operand) of dims db*32 + c at keys 16h + 4g + {0..3, 8..11}
-      const u32x4_t pf = {pk[4 * h], pk[4 * h + 1], pk[4 * h + 2], pk[4 * h + 3]};
+        for (int e = 0; e < 8; e++) pk[kt * 8 + e] = pack_bf16x2(p[2 * e], p[2 * e + 1]);
+      }
+      sum_sh[(set * W + wave) * 64 + lane] = ls;
+      unsigned char *const vals = lds + wave * L::vals, *const probs = lds + L::probs0 + wave * L::probs + lane * 16;
 #pragma unroll
-      for (int db = 0; db < DB; db++) {
-        const unsigned char *q = lds + (vcol ^ 64 * db) + 16 * h * HD * 2;
-        const u32x2_t v0 = read_columns(q), v1 = read_columns(q + 8 * HD * 2);
-        o[db] = mfma16(u32x4_t{v0.x, v0.y, v1.x, v1.y}, pf, o[db]);
+      for (int e = 0; e < VP; e++) {
+        const int idx = lane + 64 * e, row = idx / PPR, piece = idx % PPR;
+        *(u32x4_t *)(vals + row * HD * 2 + value_chunk<HD>(row, piece >> 2) * 64 + (piece & 3) * 16) = vr[e];
+      }
+#pragma unroll
+      for (int st = 0; st < 4; st++) *(u32x4_t *)(probs + st * 1024) = u32x4_t{pk[4 * st], pk[4 * st + 1], pk[4 * st + 2], pk[4 * st + 3]};
+    }
+    __syncthreads();
+    if (wave >= DB) continue;
+#pragma unroll
+    for (int j = 0; j < W; j++) {
+      if (b0 + j >= nb) break;
+      l_run = turn_add(l_run, corr[j], sum_sh[(set * W + j) * 64 + lane]);
+      const unsigned char *const vals = lds + j * L::vals + vcol, *const probs = lds + L::probs0 + j * L::probs + lane * 16;
+#pragma unroll
+      for (int v = 0; v < 16; v++) o[v] *= corr[j];
+#pragma unroll
+      for (int st = 0; st < 4; st++) {                        // 16 keys: V^T fragment (A operand) of dims 32 wave + c at keys 16 st + 4 g + {0..3, 8..11}
+        const u32x2_t v0 = read_columns(vals + 16 * st * HD * 2), v1 = read_columns(vals + (16 * st + 8) * HD * 2);
+        o = mfma16(u32x4_t{v0.x, v0.y, v1.x, v1.y}, *(const u32x4_t *)(probs + st * 1024), o);
       }
     }
-    wave_lds_order();                                         // the next block's values overwrite these
   }
-
-  // merge: partial outputs and their references and sums through the LDS; a thread adds up HD / 16 dims of one query, wavefront by wavefront
-  const auto ls = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-  const float l_sum = __uint_as_float(ls[0]) + __uint_as_float(ls[1]);
-  __syncthreads();                                            // every wavefront is done with its values
-  float *const stat = (float *)(lds + L::stat);
-  if (g == 0) { stat[wave * 32 + c] = m_run; stat[kSplitWaves * 32 + wave * 32 + c] = l_sum; }
+  if (nb == 0) __syncthreads();                               // the band is there
+  if (wave >= DB) return;
+  for (int off = J - 2; off >= 0; off--) {
+    const float sc = score_sh[off * 32 + c];
+    const float m_new = fmaxf(m_run, sc);
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
+    const float p = tq - off >= 0 ? __builtin_amdgcn_exp2f(sc - m_use) : 0.f;
+    l_run = fmaf(l_run, corr, g == 0 ? p : 0.f);              // the two lanes of a query add up their sums at the end
+    m_run = m_new;
 #pragma unroll
-  for (int db = 0; db < DB; db++)
-#pragma unroll
-    for (int q4 = 0; q4 < 4; q4++)
-      *(f32x4_t *)(lds + wave * L::part + c * L::orow + (db * 32 + 8 * q4 + 4 * g) * 4) = f32x4_t{o[db][4 * q4], o[db][4 * q4 + 1], o[db][4 * q4 + 2], o[db][4 * q4 + 3]};
-  __syncthreads();
-  constexpr int PER = HD / 64;                                // groups of four dims per thread
-  const int qi = tid >> 4, d0 = (tid & 15) * 4;
-  float m_max = -INFINITY, l_all = 0.f;
-#pragma unroll
-  for (int w = 0; w < kSplitWaves; w++) m_max = fmaxf(m_max, stat[w * 32 + qi]);
-  f32x4_t acc[PER] = {};
-#pragma unroll
-  for (int w = 0; w < kSplitWaves; w++) {
-    const float f = __builtin_amdgcn_exp2f(stat[w * 32 + qi] - m_max);   // (every query sees itself: the largest reference is no -inf)
-    l_all = fmaf(stat[kSplitWaves * 32 + w * 32 + qi], f, l_all);
-#pragma unroll
-    for (int e = 0; e < PER; e++) acc[e] += *(const f32x4_t *)(lds + w * L::part + qi * L::orow + (d0 + 64 * e) * 4) * f;
+    for (int q4 = 0; q4 < 4; q4++) {
+      const u32x2_t vw = *(const u32x2_t *)(lds + L::band0 + (off * 32 + c) * L::brow + (wave * 32 + 8 * q4 + 4 * g) * 2);
+      o[4 * q4 + 0] = fmaf(p, lo_f32(vw.x), o[4 * q4 + 0] * corr);
+      o[4 * q4 + 1] = fmaf(p, hi_f32(vw.x), o[4 * q4 + 1] * corr);
+      o[4 * q4 + 2] = fmaf(p, lo_f32(vw.y), o[4 * q4 + 2] * corr);
+      o[4 * q4 + 3] = fmaf(p, hi_f32(vw.y), o[4 * q4 + 3] * corr);
+    }
   }
-  const int t = r0 + qi;
+  const float inv = 1.f / (l_run + __shfl_xor(l_run, 32, 64));
   if (t >= T) return;
-  const float inv = 1.f / l_all;
-  bf16_t *orow = (bf16_t *)a.out + (((size_t)at.bi * T + t) * a.hq + (size_t)at.hk * G + at.gh) * HD;
+  bf16_t *const orow = (bf16_t *)a.out + q_off + wave * 32;
 #pragma unroll
-  for (int e = 0; e < PER; e++) {
+  for (int q4 = 0; q4 < 4; q4++) {
     u32x2_t w;
-    w.x = pack_bf16x2(acc[e].x * inv, acc[e].y * inv);
-    w.y = pack_bf16x2(acc[e].z * inv, acc[e].w * inv);
-    *(u32x2_t *)(orow + d0 + 64 * e) = w;
+    w.x = pack_bf16x2(o[4 * q4 + 0] * inv, o[4 * q4 + 1] * inv);
+    w.y = pack_bf16x2(o[4 * q4 + 2] * inv, o[4 * q4 + 3] * inv);
+    *(u32x2_t *)(orow + 8 * q4 + 4 * g) = w;
   }
 }
 
@@ -608,15 +644,15 @@ bool wide_pays(long long tiles128, long long workgroups) {
   return tiles128 % 2 == 0 && tiles128 >= 14 && ((workgroups >= 400 && workgroups <= 512) || workgroups >= 768);
 }
 
-// Workgroups of 32 queries whose wavefronts share out the keys (hca_split_kernel) pay
-//  * where each gets a compute unit to itself, up to 256 of them: 16 heads of 64 on 4, 333 positions, two streams 10.4 -> 6.5 us, 4 heads of 128, 1500
-//    positions, three streams 41.9 -> 21.9, 32 heads, 256 positions 16.2 -> 10.8; one key block (up to 64 positions) and no band is merged for nothing: 6.2 ->
-//    7.2, with a band 8.3 -> 7.5;
-//  * in a second round of them only where the other kernel's chain is long: head dim 128 from 1000 positions on (512 workgroups of 1024 32.6 -> 24.8, of
-//    2048 53.8 -> 34.5; of 700 25.3 -> 25.0 and 21.2 -> 23.0, of 333 14.8 -> 17.7), 64, where a compute unit holds two, from 200 (512 of 200 11.1 -> 9.3,
-//    of 2048 34.7 -> 22.3; of 100 6.8 -> 7.1);
-//  * not beyond, where every 32 queries' own reads of keys and values fill the paths from the L2: 640 of 1024 positions 33.4 -> 40.7, 1024 of 2048 55.2 -> 64.7
-//    (head dim 64 22.0 -> 21.5 and 36.8 -> 33.0, but 640 of 700 17.0 -> 17.8).
+// Workgroups of 32 queries whose wavefronts share out the keys (hca_split_kernel; the same bits) pay
+//  * where each gets a compute unit to itself, up to 256 of them: 16 heads of 64 on 4, 333 positions, two streams 9.8 -> 7.1 us, 4 heads of 128, 1500
+//    positions, three streams 40.7 -> 25.8, 32 heads, 256 positions 10.8 -> 7.2; one key block (up to 64 positions) and no band has nothing to share out: 4.0 ->
+//    4.1 and 4.9 -> 4.7, with a band 6.8 -> 5.2;
+//  * in a second round of them only where the other kernel's chain is long: head dim 128 from 1000 positions on (512 workgroups of 1024 30.9 -> 24.9, of
+//    2048 52.3 -> 39.6; 506 of 700 23.6 -> 22.7, of 333 13.1 -> 13.4 and 17.5 -> 16.2), 64, where a compute unit holds two, from 200 (448 of 200 7.2 ->
+//    6.3 and 9.3 -> 6.9, 512 of 2048 32.9 -> 22.7; of 100 5.8 -> 5.8 and 7.9 -> 6.6);
+//  * not beyond, where every 32 queries' own reads of keys and values fill the paths from the L2: 640 of 1024 positions 31.7 -> 35.3, 1024 of 2048 53.4 -> 77.9
+//    (head dim 64 19.8 -> 20.0 and 33.5 -> 32.3, but 640 of 300 7.9 -> 9.6, of 700 15.3 -> 17.4).
 // (three streams or one, inputs in the caches)
 bool split_pays(int hd, int seq, int streams, long long workgroups) {
   if (workgroups <= 256) return seq > 64 || streams > 1;
@@ -645,19 +681,20 @@ hipError_t launch_waves(const HcaArgs &a, hipStream_t st) {
 
 template <int HD>
 hipError_t launch_split(const HcaArgs &a, hipStream_t st) {
-  constexpr int kLds = SplitLds<HD>::total;
+  using L = SplitLds<HD>;
+  static_assert(L::total(kMaxStreams) <= 160 * 1024, "the LDS of a compute unit");
   static bool attr_done[64] = {};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64 || !attr_done[dev]) {
-    e = hipFuncSetAttribute((const void *)hca_split_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    e = hipFuncSetAttribute((const void *)hca_split_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, L::total(kMaxStreams));
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64) attr_done[dev] = true;
   }
   const long long grid = (long long)a.batch * a.hq * ((a.seq + 31) / 32);
   if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(hca_split_kernel<HD>, dim3((unsigned)grid), dim3(kSplitWaves * 64), kLds, st, a);
+  hipLaunchKernelGGL(hca_split_kernel<HD>, dim3((unsigned)grid), dim3(kSplitWaves * 64), L::total(a.n_streams), st, a);
   return hipGetLastError();
 }
 

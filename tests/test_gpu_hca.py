@@ -70,7 +70,7 @@ def test_hca_attention_matches_oracle(env, n_streams, batch, seq, hq, hkv, hd):
 
 
 @pytest.mark.parametrize("n_streams,batch,seq,hq,hkv,hd", [
-    # launches of few workgroups, whose wavefronts share out the keys: edges of its 32-key blocks and of its eight wavefronts
+    # launches of few workgroups, whose wavefronts share out the keys: edges of its 64-key blocks and of its four wavefronts
     (2, 1, 32, 1, 1, 128), (8, 1, 33, 2, 1, 64), (1, 1, 65, 2, 2, 128), (8, 2, 7, 4, 1, 128), (3, 1, 255, 2, 1, 64), (1, 1, 257, 3, 3, 128),
     (8, 1, 264, 1, 1, 128), (3, 1, 1031, 2, 2, 64), (3, 1, 1025, 15, 5, 128), (5, 1, 203, 64, 8, 64),
     # and one more head group, position or stream less than it takes: workgroups of 128 queries
@@ -85,6 +85,27 @@ def test_hca_attention_few_workgroups(env, n_streams, batch, seq, hq, hkv, hd):
         want = hca.hca_attention(q[b].astype(np.float64), [k[b].astype(np.float64) for k in ks],
                                  [v[b].astype(np.float64) for v in vs], heads=heads)
         check(got[b], want, vs, heads=heads)
+
+
+@pytest.mark.parametrize("n_streams,seq,hq,hkv,hd", [
+    (2, 333, 16, 4, 64), (1, 65, 8, 8, 128), (3, 256, 8, 2, 128), (8, 700, 8, 8, 128), (5, 257, 3, 1, 64), (8, 3, 4, 4, 128), (4, 2048, 4, 4, 64),
+    (3, 1000, 15, 5, 128),                                     # more than 256 workgroups alone
+])
+@pytest.mark.parametrize("steep", [1.0, 25.0])
+def test_hca_attention_of_a_sequence_has_the_same_bits_in_any_launch(env, n_streams, seq, hq, hkv, hd, steep):
+    """A launch of few workgroups of 32 queries shares the keys out among its wavefronts, a larger one runs 128 queries a workgroup: a sequence alone and among
+    others has the same bits (steep: scores far apart, so that the softmax's reference moves from block to block)."""
+    torch, P = env
+    tiles = hq * ((seq + 31) // 32)
+    batch = 512 // tiles + 1
+    assert tiles <= 512 < batch * tiles and (tiles <= 256 or seq >= 1000)
+    q, ks, vs = wl.make_hca_streams(23, n_streams, batch, seq, hq, hkv, hd)
+    dev = lambda x: torch.from_numpy(x).cuda().to(torch.bfloat16)
+    q, ks, vs = dev(q) * steep, [dev(k) for k in ks], [dev(v) for v in vs]
+    many = P.spec_hca_attention(q, ks, vs)
+    for b in {0, batch - 1}:
+        one = P.spec_hca_attention(q[b:b + 1].contiguous(), [k[b:b + 1].contiguous() for k in ks], [v[b:b + 1].contiguous() for v in vs])
+        assert torch.isfinite(one.float()).all() and torch.equal(one[0], many[b])
 
 
 @pytest.mark.parametrize("n_streams,batch,seq,hq,hkv", [
