@@ -1218,213 +1218,6 @@ __global__ __launch_bounds__(kGemmThreads, 3) void gemm_f32_tiled_kernel(GemmArg
   }
 }
 
-// ---- fp32 storage, both sides of a loss through the LM head ------------------------------------------------
-// The fp32 matrix rate is a sixteenth of the bf16 one, so here every operand is cut into three bf16 values that add up to it exactly (24 bits: the
-// upper 8 by truncation, the next 8 rounded, the rest), and the six largest of their nine products go through v_mfma_f32_32x32x16_bf16, smallest first
-// into one fp32 sum.  Products are exact, the three left out are below 2^-24 of the product, and a sum is rounded 6 times in 16 k instead of 16 times.
-// A workgroup of eight wavefronts owns TM 32-row blocks of X (both sets of rows as one) x 4 weight blocks; the wavefronts 0 .. 3 walk the even, 4 .. 7 the
-// odd 64-k tiles, each with a weight block of its own, which it reads into registers in the packed layout and cuts up there.  X is cut up once per
-// workgroup and tile, into the LDS, a tile ahead.  The two sums of a value meet in the LDS, even tiles first.
-// Where a value comes out infinite or NaN (an infinite operand, whose parts have no meaning, or an overflow) it is formed again with fp32
-// products, so such operands give what they give in the other fp32 kernels.
-// (Not for a model's projections: a prompt's row has to have the bits that gemm_f32_kernel gives it when decoded.)
-// Measured (MI355X, us a loss, gemm_f32_tiled_kernel before): 129 positions x 9000, K = 512 48 -> 39, K = 1024 71 -> 53; vocabulary 32000, K = 1024: 33
-// positions 93 -> 60, 300 381 -> 300, 512 619 -> 472 (its GEMM at 190 TFLOP/s of fp32 operations, 1.1 PFLOP/s of bf16 products).  Logits against 64 bits, 2-norm:
-// 2.1e-7 -> 1.2e-7 at K = 512, 1.5e-7 -> 1.2e-7 at 256, 4.1e-7 -> 1.4e-7 at 2048 (a tile's sums start from zero and are added up in fp32).
-__device__ __forceinline__ void split3(const f32x4_t &lo, const f32x4_t &hi, u32x4_t (&p)[3]) {
-#pragma unroll
-  for (int e = 0; e < 4; e++) {
-    const float x0 = e < 2 ? lo[2 * e] : hi[2 * e - 4], x1 = e < 2 ? lo[2 * e + 1] : hi[2 * e - 3];
-    const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
-    const float r0 = x0 - __uint_as_float(u0 & 0xFFFF0000u), r1 = x1 - __uint_as_float(u1 & 0xFFFF0000u);
-    const uint32_t m = pack_bf16x2(r0, r1);
-    p[0][e] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);     // the upper halves of both
-    p[1][e] = m;
-    p[2][e] = pack_bf16x2(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xFFFF0000u));
-  }
-}
-template <int TM>
-__global__ __launch_bounds__(512, 2) void gemm_f32_split_kernel(GemmArgs a) {
-  constexpr int kPlane = TM * 4096, kBuf = 3 * kPlane;        // one part of a tile of X: [block][step][lane] 16 bytes
-  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];   // [half of the wavefronts][two buffers][three parts]
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = lane & 31, g = lane >> 5, odd = wave >> 2, wn = wave & 3;
-  const int per = 8 * a.m_tiles;                              // (ids 8 apart run on one XCD: the token tiles of a weight tile follow each other there)
-  const int q = ((int)blockIdx.x / per) * 8 + ((int)blockIdx.x % 8), mt = ((int)blockIdx.x % per) / 8;
-  if (q >= a.grid_x) return;
-  const int rows = a.m * (a.x2 ? 2 : 1), row0 = mt * TM * 32;
-  const int n_tiles = (a.in + 63) / 64, n_iter = (n_tiles + 1) / 2;
-  const int blk = min(q * 4 + wn, a.total_blocks - 1);
-  const char *wp = (const char *)a.seg_w[0] + (size_t)blk * n_tiles * kTileBytes + lane * 16;
-  const float *xrow[TM];
-#pragma unroll
-  for (int t = 0; t < TM; t++) {
-    const int r = min(row0 + t * 32 + c, rows - 1);
-    xrow[t] = r < a.m ? (const float *)a.x + (size_t)r * a.ldx : (const float *)a.x2 + (size_t)(r - a.m) * a.ldx;
-  }
-  f32x4_t xr[TM][2], wr[8];
-  u32x4_t xf[2][TM][3], wf[2][3];                             // the parts of this step and of the next
-  // (tiles past the end: the last one again, its products are not added)
-  auto load_x = [&](int t, int it) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < 2; u++) {
-      const int k = min(it, n_tiles - 1) * 64 + g * 32 + wn * 8 + u * 4;
-      xr[t][u] = *(const f32x4_t *)(xrow[t] + (k < a.in ? k : 0));   // past K: meets a zero weight
-    }
-  };
-  auto load_w = [&](int s, int it) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < 2; u++) wr[2 * s + u] = *(const f32x4_t *)(wp + (size_t)min(it, n_tiles - 1) * kTileBytes + (2 * s + u) * 1024);
-  };
-  unsigned char *const mine = lds + odd * 2 * kBuf + lane * 16;
-  auto stage_x = [&](int t, int buf) __attribute__((always_inline)) {
-    u32x4_t p[3];
-    split3(xr[t][0], xr[t][1], p);
-#pragma unroll
-    for (int i = 0; i < 3; i++) *(u32x4_t *)(mine + buf * kBuf + i * kPlane + (t * 4 + wn) * 1024) = p[i];
-  };
-  auto read_x = [&](int s, int buf, u32x4_t (&x)[TM][3]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < TM; t++)
-#pragma unroll
-      for (int i = 0; i < 3; i++) x[t][i] = *(const u32x4_t *)(mine + buf * kBuf + i * kPlane + (t * 4 + s) * 1024);
-  };
-  auto barrier = [&]() __attribute__((always_inline)) {       // this wavefront's LDS accesses are done; its loads run on
-    __builtin_amdgcn_s_waitcnt(0xC07F);                       // lgkmcnt(0)
-    wg_barrier();
-  };
-  f32x16_t sum[TM], acc[TM];
-#pragma unroll
-  for (int t = 0; t < TM; t++)
-#pragma unroll
-    for (int v = 0; v < 16; v++) sum[t][v] = 0.f;
-
-#pragma unroll
-  for (int t = 0; t < TM; t++) load_x(t, odd);
-#pragma unroll
-  for (int s = 0; s < 4; s++) load_w(s, odd);
-#pragma unroll
-  for (int t = 0; t < TM; t++) { stage_x(t, 0); load_x(t, odd + 2); }
-  barrier();
-  read_x(0, 0, xf[0]);
-  split3(wr[0], wr[1], wf[0]);
-  load_w(0, odd + 2);
-  for (int i = 0; i < n_iter; i++) {
-    const int it = 2 * i + odd, buf = i & 1;
-    static_for<4>([&](auto s_tag) __attribute__((always_inline)) {
-      constexpr int s = decltype(s_tag)::value, cur = s & 1;
-      const u32x4_t (&x)[TM][3] = xf[cur];
-      const u32x4_t (&w)[3] = wf[cur];
-      // what the next step needs, between this step's products; the next tile of X is complete ahead of the last step
-      if constexpr (s == 3) barrier();
-      read_x((s + 1) & 3, s == 3 ? buf ^ 1 : buf, xf[cur ^ 1]);
-      if constexpr (s < TM) { stage_x(s, buf ^ 1); load_x(s, it + 4); }
-      split3(wr[2 * ((s + 1) & 3)], wr[2 * ((s + 1) & 3) + 1], wf[cur ^ 1]);
-      load_w((s + 1) & 3, it + (s == 3 ? 4 : 2));
-      constexpr int xi[6] = {2, 0, 1, 1, 0, 0}, wi[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-      for (int k = 0; k < 6; k++)
-#pragma unroll
-        for (int t = 0; t < TM; t++) {
-          if (s == 0 && k == 0) {
-            f32x16_t zero;
-#pragma unroll
-            for (int v = 0; v < 16; v++) zero[v] = 0.f;
-            acc[t] = zero;
-          }
-          mfma_step(acc[t], x[t][xi[k]], w[wi[k]], bf16_t{});
-        }
-#pragma unroll
-      for (int k = 0; k < 6 * TM; k++) {                      // (in the order that the scheduler is to keep: 3 % of a launch)
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // a product,
-        if (k < 3 * TM) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read,
-        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);    // and vector arithmetic
-      }
-    });
-    if (it < n_tiles) {
-#pragma unroll
-      for (int t = 0; t < TM; t++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) sum[t][v] += acc[t][v];
-    }
-  }
-  barrier();
-
-  // the wavefronts of the even tiles finish the first eight values of a block, those of the odd tiles the others
-  float *const red = (float *)lds + (wn * TM * 16) * 64 + lane;
-#pragma unroll
-  for (int t = 0; t < TM; t++)
-#pragma unroll
-    for (int v = 0; v < 8; v++) red[(t * 16 + (odd ? v : 8 + v)) * 64] = odd ? sum[t][v] : sum[t][8 + v];
-  __syncthreads();
-  const int row = blk * 32 + c;
-  const bool mine_to_store = q * 4 + wn < a.total_blocks && row < a.seg_rows[0];
-  float *const out = a.part + a.seg_col0[0] + row, *const out2 = a.x2 ? a.part2 + a.seg_col0[0] + row - (ptrdiff_t)a.m * a.ldp : out;
-  auto store = [&](int t, int v, float y) __attribute__((always_inline)) {
-    const int r = row0 + t * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-    if (mine_to_store && r < rows) (r < a.m ? out : out2)[(ptrdiff_t)r * a.ldp] = y;
-  };
-  uint32_t wrong = 0;
-#pragma unroll
-  for (int t = 0; t < TM; t++)
-#pragma unroll
-    for (int v8 = 0; v8 < 8; v8++) {
-      const int v = odd ? 8 + v8 : v8;
-      const float other = red[(t * 16 + v) * 64], y = odd ? other + sum[t][8 + v8] : sum[t][v8] + other;
-      if (!(fabsf(y) <= 3.402823466e38f)) wrong |= 1u << (t * 8 + v8);
-      store(t, v, y);
-    }
-  // (rare: once more with fp32 products, straight from memory)
-  if (!__any(wrong != 0)) return;
-#pragma unroll 1
-  for (int t = 0; t < TM; t++) {
-    const int r = min(row0 + t * 32 + c, rows - 1);
-    const float *x = r < a.m ? (const float *)a.x + (size_t)r * a.ldx : (const float *)a.x2 + (size_t)(r - a.m) * a.ldx;
-    f32x16_t y;
-#pragma unroll
-    for (int v = 0; v < 16; v++) y[v] = 0.f;
-#pragma unroll 1
-    for (int it = 0; it < n_tiles; it++) {
-      f32x4_t xs[8], ws[8];
-#pragma unroll
-      for (int j = 0; j < 8; j++) {
-        const int k = it * 64 + g * 32 + j * 4;
-        xs[j] = *(const f32x4_t *)(x + (k < a.in ? k : 0));
-        ws[j] = *(const f32x4_t *)(wp + (size_t)it * kTileBytes + j * 1024);
-      }
-#pragma unroll
-      for (int j = 0; j < 8; j++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) y = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[j][e], ws[j][e], y, 0, 0, 0);
-    }
-#pragma unroll
-    for (int v8 = 0; v8 < 8; v8++)
-      if (wrong >> (t * 8 + v8) & 1) store(t, odd ? 8 + v8 : v8, odd ? y[8 + v8] : y[v8]);
-  }
-}
-template <int TM>
-static hipError_t launch_f32_split(GemmArgs a, hipStream_t st) {
-  a.m_tiles = (a.m * (a.x2 ? 2 : 1) + TM * 32 - 1) / (TM * 32);
-  a.grid_x = (a.total_blocks + 3) / 4;
-  const long long grid = ((long long)a.grid_x + 7) / 8 * 8 * a.m_tiles;
-  if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gemm_f32_split_kernel<TM>, dim3((unsigned)grid), dim3(512), 4 * 3 * TM * 4096, st, a);
-  return hipGetLastError();
-}
-
-// 32-row blocks of X per workgroup of gemm_f32_split_kernel, 0: not for it.  Two sets of rows through one matrix, more than 32 each, and 140 workgroups of two
-// blocks (a workgroup has a compute unit to itself and takes 10 us however few there are: vocabulary 1000, K = 512, 100 positions 19 -> 28, 512 of
-// K = 256, 128 workgroups, 25.1 -> 26.3; vocabulary 9000, 33 positions, 142 workgroups, K = 256 25.5 -> 25.5, 1024 45 -> 42; 24 positions 22.5 -> 24.2 and
-// 36.7 -> 40.2, though at vocabulary 32000 31 -> 29 and 59 -> 51).  Three blocks where that takes at most three quarters of the rounds of 256 (129 positions x 9000, K =
-// 512 48.0 -> 39.4, 33 x 32000 51 -> 41; 200 x 9000, two rounds both, 51.6 and 58.3, 512 x 9000, five and four, 105 and 107).
-static int f32_split_blocks(const GemmArgs &a) {
-  if (a.x2 == nullptr || a.nseg != 1 || a.n_split != 1 || a.act != nullptr || a.m <= 32) return 0;
-  if ((((uintptr_t)a.x | (uintptr_t)a.x2 | (uintptr_t)a.seg_w[0]) & 15) || a.ldx % 4) return 0;   // whole 16-byte pieces
-  const long long tiles = (a.total_blocks + 3) / 4, two = (2ll * a.m + 63) / 64 * tiles, three = (2ll * a.m + 95) / 96 * tiles;
-  if (two < 140) return 0;
-  return 4 * ((three + 255) / 256) <= 3 * ((two + 255) / 256) ? 3 : 2;
-}
-
 static hipError_t launch_f32_tiled(GemmArgs a, hipStream_t st) {
   a.m_tiles = (a.m + 31) / 32 * (a.x2 ? 2 : 1);
   a.grid_x = (a.total_blocks + kF32Blocks - 1) / kF32Blocks;
@@ -1468,10 +1261,6 @@ static hipError_t launch_f32(const GemmArgs &a, hipStream_t st, const GemmHead *
   if (head != nullptr)
     return head->kind == kHeadSums ? launch_f32_small<kHeadSums>(a, tiles, *head, st)
            : head->kind == kHeadEmbed ? launch_f32_small<kHeadEmbed>(a, tiles, *head, st) : launch_f32_small<kHeadConcat>(a, tiles, *head, st);
-  switch (f32_split_blocks(a)) {
-    case 2: return launch_f32_split<2>(a, st);
-    case 3: return launch_f32_split<3>(a, st);
-  }
   if (f32_tiled_pays(a)) return launch_f32_tiled(a, st);
   if (tiles > 65535) return hipErrorInvalidValue;
   return launch_f32_small<kHeadNone>(a, tiles, NoHead{}, st);
@@ -1598,9 +1387,7 @@ hipError_t gemm_init() {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev >= 0 && dev < 64 && done[dev]) return hipSuccess;
-  e = hipFuncSetAttribute((const void *)gemm_f32_split_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 3 * 2 * 4096);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_f32_split_kernel<3>, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 3 * 3 * 4096);
-  if (e == hipSuccess) e = init_tb<1>();
+  e = init_tb<1>();
   if (e == hipSuccess) e = init_tb<2>();
   if (e == hipSuccess) e = init_tb<3>();
   if (e == hipSuccess) e = init_tb<4>();

@@ -76,10 +76,10 @@ CASES = [
     ("bf16", 64, 256, 1000, 3),         # ... the largest such pair
     ("bf16", 65, 256, 1000, 3),         # ... and one row more per side: tiled, each side its own tiles
     ("fp32", 45, 200, 7000, 5),         # fp32 rows enough for the tiled LM head: each side its own 32-row tiles, ragged ones
-    ("fp32", 129, 512, 9000, 16),       # both sides' rows in 96-row tiles of products of bf16 parts
-    ("fp32", 100, 260, 9000, 16),       # ... five tiles of k, the last one of four; the sets' boundary inside a block
-    ("fp32", 33, 8, 32000, 10),         # ... one ragged tile of k, the second half of the wavefronts without one
-    ("fp32", 33, 192, 9000, 3),         # ... in 64-row tiles, two rows in the last; three tiles of k
+    ("fp32", 129, 512, 9000, 16),       # ... eight tiles of k
+    ("fp32", 100, 260, 9000, 16),       # ... five, the last one of four k
+    ("fp32", 33, 8, 32000, 10),         # ... one ragged tile of k
+    ("fp32", 33, 192, 9000, 3),         # ... one row in a side's last tile; three tiles of k
     ("fp32", 200, 64, 9090, 5),         # ... a ragged weight block in the last workgroup
     ("fp32", 520, 132, 9000, 4),        # ... two chunks of positions, the second in the other kernel
     ("bf16", 1, 256, 100, 100),         # K = V: Eq. (1) becomes the cross-entropy (vocabulary smaller than one slice)
@@ -199,9 +199,9 @@ def test_infinite_and_nan_logits(env):
 
 @pytest.mark.parametrize("value,factor", [("lowest", 1.0), ("lowest", 3.0), ("-inf", 2.0)])
 @pytest.mark.parametrize("rows", [40, 129])
-def test_ruled_out_tokens_in_products_of_parts(env, rows, value, factor):
-    # launches whose fp32 operands are cut into bf16 parts: a column takes every third token to the lowest value (whose parts are finite), past it
-    # (an overflow) or to -inf (which has no parts); beside the ruled out tokens the logits are those of a head without them
+def test_ruled_out_tokens_in_the_tiled_head(env, rows, value, factor):
+    # a column takes every third token to the lowest value, past it (an overflow) or to -inf; beside the ruled out tokens the logits are those of a
+    # head without them
     torch, P = env
     ft, fd, w = wl.make_distill_inputs(36, rows, 130 * 2, 9000, "fp32")
     out = np.arange(9000) % 3 == 0
@@ -216,6 +216,36 @@ def test_ruled_out_tokens_in_products_of_parts(env, rows, value, factor):
     else:
         assert (np.isclose(got_topk, want, **TOL) | np.isclose(got_topk, alt, **TOL)).all()
         assert np.isnan(got_ce).all()                          # 0 * -inf, as the definition has it
+
+
+@pytest.mark.parametrize("d,vocab", [(512, 9000), (132, 32000), (64, 1000)])
+def test_fp32_losses_of_a_position_have_the_same_bits_in_any_call(env, d, vocab):
+    # few positions and many, whole chunks of 512 and short ones: three ways of the LM head, whose sums run in the same order
+    torch, P = env
+    ft, fd, w = wl.make_distill_inputs(41, 520, d, vocab, "fp32")
+    topk, ce, _ = run_gpu(torch, P, ft, fd, w, 10, "fp32")
+    for lo, hi in ((0, 1), (100, 116), (0, 33), (391, 520), (512, 520)):
+        a, b, _ = run_gpu(torch, P, np.ascontiguousarray(ft[lo:hi]), np.ascontiguousarray(fd[lo:hi]), w, 10, "fp32")
+        assert np.array_equal(a, topk[lo:hi]) and np.array_equal(b, ce[lo:hi])
+
+
+@pytest.mark.parametrize("rows", [4, 40, 129, 512])
+def test_fp32_logits_of_one_product_are_rounded_once(env, rows):
+    # Target logits of one product each, 4096 * s^2 for even tokens and 4096 * s * (1 + 2^-7) for odd ones, where s has its bits in three groups of
+    # eight: an LM head that leaves out part of a product moves the even logits against the odd ones, and the draft's 3 for even tokens shows it in
+    # the losses.  Rounded once a logit has 2^-24 of itself, which is in the expected value; what the losses add to that is 1e-6.
+    torch, P = env
+    vocab, d = 9000, 512
+    s = np.float32(1 + 2.0 ** -7 - 2.0 ** -15 + 2.0 ** -16 - 2.0 ** -22)
+    even = np.arange(vocab) % 2 == 0
+    ft, fd, w = np.zeros((rows, d), np.float32), np.zeros((rows, d), np.float32), np.zeros((vocab, d), np.float32)
+    ft[:, 5], fd[:, 5], fd[:, 6] = 64 * s, 1, 1
+    w[:, 5], w[:, 6] = np.where(even, 64 * s, np.float32(64 * (1 + 2.0 ** -7))), np.where(even, 3, 0)
+    zq = (ft[0, 5] * w[:, 5]).astype(np.float64)
+    zp = w[:, 5].astype(np.float64) + w[:, 6]
+    want = -(np.exp(zq - zq.max()) / np.exp(zq - zq.max()).sum() * (zp - zp.max() - np.log(np.exp(zp - zp.max()).sum()))).sum()
+    _, ce, _ = run_gpu(torch, P, ft, fd, w, 10, "fp32")
+    np.testing.assert_allclose(ce, want, rtol=1e-5)
 
 
 @pytest.mark.parametrize("lo,hi", [(0, 4096), (4096, 8192), (8192, 9000)])
