@@ -6,6 +6,7 @@ been built, importing this module raises.
 """
 from __future__ import annotations
 
+import collections
 import ctypes as C
 import dataclasses
 import os
@@ -188,36 +189,42 @@ def spec_accept(ctx, tree: Tree) -> List[int]:
 
 
 # Logits go to the host as tens of MB.  Into pageable memory that is 10 to 17 GB/s (60 rows of 128256 logits 1.7 to 3 ms, of 32000 0.4 to 1.2), into
-# pinned memory 56 (0.55, 0.15).  The pinned memory is torch's (its caching host allocator: a block is given out again once its array is
-# gone); arrays that the caller still holds count against a limit, and beyond it the memory is pageable as for small copies.
+# pinned memory 56 (0.55, 0.15).  The pinned memory is torch's (its caching host allocator).  That rounds a block up to a power of two and keeps
+# it, locked, for the next array of its size once an array is gone, until the process ends or the program empties torch's cache: what is locked is
+# for every size of block the most that were held at once, and all of these together stay below a limit.  Beyond it, and for small
+# copies, the memory is pageable.  The first array of a size takes 0.3 to 0.5 ms more, for the locking.
 _PINNED_LEAST, _PINNED_LIMIT = 1 << 20, 256 << 20
-_pinned_held = 0
+_pinned: Dict[int, List[int]] = {}                             # bytes of a block -> how many are held, and the most that were
+_pinned_gone: collections.deque = collections.deque()          # blocks whose arrays are gone (a finalizer runs anywhere: it takes no lock)
 _pinned_lock = threading.Lock()
 
 
-def _pinned_release(nbytes: int) -> None:
-    global _pinned_held
+def _pinned_take(block: int) -> bool:
     with _pinned_lock:
-        _pinned_held -= nbytes
+        while _pinned_gone:
+            _pinned[_pinned_gone.popleft()][0] -= 1
+        use = _pinned.setdefault(block, [0, 0])
+        if use[0] == use[1]:
+            if sum(size * most for size, (_, most) in _pinned.items()) + block > _PINNED_LIMIT:
+                return False
+            use[1] += 1
+        use[0] += 1
+        return True
 
 
 def _host_floats(rows: int, cols: int) -> np.ndarray:
-    global _pinned_held
     nbytes = rows * cols * 4
-    if nbytes >= _PINNED_LEAST:
-        with _pinned_lock:
-            fits = _pinned_held + nbytes <= _PINNED_LIMIT
-            if fits:
-                _pinned_held += nbytes
-        if fits:
-            import torch
-            try:
-                buf = torch.empty((rows, cols), dtype=torch.float32, pin_memory=True).numpy()   # (keeps the tensor)
-            except RuntimeError:                               # no memory to pin
-                _pinned_release(nbytes)
-            else:
-                weakref.finalize(buf, _pinned_release, nbytes).atexit = False
-                return buf
+    block = 1 << max(nbytes - 1, 0).bit_length()
+    if nbytes >= _PINNED_LEAST and _pinned_take(block):
+        import torch
+        try:
+            buf = torch.empty((rows, cols), dtype=torch.float32, pin_memory=True).numpy()   # (keeps the tensor)
+            weakref.finalize(buf, _pinned_gone.append, block).atexit = False
+            return buf
+        except BaseException as e:
+            _pinned_gone.append(block)
+            if not isinstance(e, RuntimeError):                # (RuntimeError: no memory to pin)
+                raise
     return np.empty((rows, cols), dtype=np.float32)
 
 
@@ -257,8 +264,12 @@ def spec_get_profile(ctx):
 
 def _stream_ptr(stream=None):
     import torch
-    # (the handle without a Stream object around it: 3.0 us of a call -> 0.4)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+    if stream is None:
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # the handle without a Stream object around it: 3.0 us of a call -> 0.4
+        if raw is not None:                                    # (not a public name: a torch may come without it)
+            return raw(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
 
 
 def spec_packed_bytes(dtype: int, rows: int, cols: int) -> int:
