@@ -377,20 +377,35 @@ def test_topk_loss_error_paths_and_optional_outputs(env):
     np.testing.assert_allclose(tot.cpu().numpy(), [want.sum(), want_ce.sum()], rtol=2e-4)
 
 
-@pytest.mark.parametrize("rows,d,vocab", [(144, 64, 22000), (188, 136, 33000), (192, 64, 22016), (300, 72, 16500), (513, 64, 22000)])
-def test_both_sides_rows_as_one_set_of_tiles(env, rows, d, vocab):
+@pytest.mark.parametrize("rows,d,vocab,tile", [
+    (144, 64, 22000, (256, 192)), (188, 136, 33000, (128, 256)), (192, 64, 22016, (256, 192)),
+    (300, 72, 16500, (256, 256)), (188, 1096, 32000, (256, 256)), (257, 1024, 40000, (256, 256)), (310, 1096, 20000, (256, 256)),   # ragged ends beside whole tiles
+    (700, 64, 22000, (256, 192)), (700, 1096, 33000, (128, 256)),                                    # 512 apart, then 188
+])
+def test_both_sides_rows_as_one_set_of_tiles(env, rows, d, vocab, tile):
     """Where the sides' rows take fewer tiles together, one launch runs over them as one set: the border inside a 32-row block, inside a tile and (192 rows) at
-    the end of a half tile, either side first in memory, a second chunk of one position."""
+    the end of a half tile, either side first in memory, a second chunk behind one that is not joined, every tile, one to sixteen tiles of k.  The losses have
+    the bits of two sets of tiles (sides too far apart in memory for one), and fp64's value."""
     torch, P = env
+    m, blocks = rows % 512 or 512, (vocab + 31) // 32
+    assert (2 * m + 127) // 128 < 2 * ((m + 127) // 128) and P.spec_k_gemm_tile(2 * m, blocks, d) == tile
+    _, whole, tiles = P.spec_k_gemm_plan(m, blocks, d, sets=2)
+    assert (0, whole, tiles) == P.spec_k_gemm_plan(2 * m, blocks, d)
+    if tile == (256, 256):
+        assert whole == tiles > 0 and 0 < 2 * m % 256 <= 128
     ft, fd, w = wl.make_distill_inputs(5, rows, d, vocab, "bf16")
-    ft, fd = (torch.from_numpy(x).cuda().to(torch.bfloat16) for x in (ft, fd))
     packed = P.spec_pack_weight(torch.from_numpy(w).cuda().to(torch.bfloat16))
+    ft, fd = (torch.from_numpy(x).cuda().to(torch.bfloat16) for x in (ft, fd))
+    memory = torch.empty((1 << 29) + 2 * rows * d, dtype=torch.bfloat16, device="cuda")
     got = []
-    for first, second in ((ft, fd), (fd, ft)):
-        both = torch.stack([first, second])
-        a, b = (both[0], both[1]) if first is ft else (both[1], both[0])
-        got.append([t.cpu() for t in P.spec_topk_loss(a, b, packed, 7)[:2]])
-    assert all(torch.equal(x, y) for x, y in zip(*got))
+    for far in (False, True):
+        low, high = memory[:rows * d].view(rows, d), memory[1 << 29 if far else rows * d:][:rows * d].view(rows, d)
+        for a, b in ((low, high), (high, low)):
+            a.copy_(ft), b.copy_(fd)
+            assert (abs(a.data_ptr() - b.data_ptr()) < 1 << 30) != far
+            got.append([t.cpu() for t in P.spec_topk_loss(a, b, packed, 7)[:2]])
+    for topk, ce in got[1:]:
+        assert torch.equal(topk, got[0][0]) and torch.equal(ce, got[0][1])
     head = torch.from_numpy(w).to(torch.bfloat16).double()
     zq, zp = ft.cpu().double() @ head.T, fd.cpu().double() @ head.T
     want = -(torch.softmax(zq, -1) * torch.log_softmax(zp, -1)).sum(-1)
