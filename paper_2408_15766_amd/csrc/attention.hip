@@ -42,7 +42,6 @@
 
 namespace spec {
 
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 template <int N, int I = 0, typename F>
 __device__ __forceinline__ void unrolled(F &&f) {
@@ -77,9 +76,9 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One wavefront: row i, kv head hk, part `part` (full mode) or the tail range (tail mode).  `qs` and `vs`
-// are this wavefront's own LDS areas ([G][HD] floats and 64 staged value rows); no workgroup barrier is
-// used, so wavefronts of one workgroup may work on different items.  `store` = false discards the result.
+// One wavefront: row i, kv head hk, part `part`.  `qs` and `vs` are this wavefront's own LDS areas ([G][HD]
+// floats and 64 staged value rows); no workgroup barrier is used, so wavefronts of one workgroup may work on
+// different items.
 template <typename T> struct PartLds {
   static constexpr int vrow(int hd) { return hd * (int)sizeof(T) + 16; }   // +16: conflict-free row writes
 };
@@ -196,38 +195,13 @@ __device__ __forceinline__ void attn_part_body(const AttnArgs &a, int i, int hk,
 // The result goes to the last part slot.
 constexpr int kTailKeys = kMaxDepth + 1;
 static_assert(kTailKeys * 4 == 64, "one wavefront = 16 keys x 4 lanes");
-// The rotary planes j .. j + 3 of a head (columns col .. of the partial sums, the planes' partners HD / 2 further on) of row i from the QKV projection's partial sums,
-// as reduce_rope_kv_kernel forms them; all loads first, up to four splits (absent ones read split 0 again and are left out).
-struct RawPlanes { f32x4_t a, b; };
-__device__ __forceinline__ RawPlanes raw_planes(const AttnRaw &r, int i, int col, int half, int j, bool turned) {
-  constexpr int NS = 4;
-  const float *p = r.qkv + (size_t)i * r.ldp + col;
-  const f32x4_t *cs = (const f32x4_t *)(r.rope + (size_t)i * half + j);
-  const f32x4_t cs0 = cs[0], cs1 = cs[1];                     // (cos, sin) of planes j, j + 1 and j + 2, j + 3
-  f32x4_t pa[NS], pb[NS];
-#pragma unroll
-  for (int s = 0; s < NS; s++) {
-    const float *q = p + (size_t)(s < r.n_split ? s : 0) * r.split_stride;
-    pa[s] = *(const f32x4_t *)q; pb[s] = *(const f32x4_t *)(q + half);
-  }
-  RawPlanes x{pa[0], pb[0]};
-#pragma unroll
-  for (int s = 1; s < NS; s++)
-    if (s < r.n_split) { x.a += pa[s]; x.b += pb[s]; }
-  for (int s = NS; s < r.n_split; s++) { x.a += *(const f32x4_t *)(p + (size_t)s * r.split_stride); x.b += *(const f32x4_t *)(p + (size_t)s * r.split_stride + half); }
-  if (turned) {
-    const float2 c[4] = {{cs0.x, cs0.y}, {cs0.z, cs0.w}, {cs1.x, cs1.y}, {cs1.z, cs1.w}};
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const float u = rope_first(x.a[e], x.b[e], c[e]), v = rope_second(x.a[e], x.b[e], c[e]);
-      x.a[e] = u; x.b[e] = v;
-    }
-  }
-  return x;
+// The rotary planes j .. j + 3 of a head (columns col .. of the partial sums, the planes' partners HD / 2 further on) of row i from the QKV projection's partial sums
+__device__ __forceinline__ RotaryPlanes raw_planes(const AttnRaw &r, int i, int col, int half, int j, bool turned) {
+  return rotary_planes<4>(r.qkv + (size_t)i * r.ldp + col, r.n_split, r.split_stride, r.rope + (size_t)i * half + j, half, turned);
 }
 __device__ __forceinline__ uint2 pack4(f32x4_t v) { return uint2{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)}; }
 // RAW: queries, key and value of the row come from the partial sums.  The row's own key and value go to own (LDS, the stored type, key first) and to the caches;
-// all other keys are in the caches.
+// all other keys are in the caches.  `store` = false discards the result.
 template <typename T, int HD, int G, bool RAW = false>
 __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk, int lane, float (*qs)[HD],
                                                unsigned char *vs, bool store, T *own = nullptr) {
@@ -265,7 +239,7 @@ __device__ __forceinline__ void attn_tail_body(const AttnArgs &a, int i, int hk,
       const int e = e0 + lane, head = e / per_head, j = e % per_head * 4;
       if (e >= (G + 2) * per_head) continue;
       const int col = (head < G ? hk * G + head : head == G ? a.hq + hk : a.hq + a.hkv + hk) * HD + j;
-      const RawPlanes x = raw_planes(a.raw, i, col, half, j, head <= G);
+      const RotaryPlanes x = raw_planes(a.raw, i, col, half, j, head <= G);
       if (head < G) { *(f32x4_t *)&qs[head][j] = x.a; *(f32x4_t *)&qs[head][j + half] = x.b; continue; }
       const uint2 x0 = pack4(x.a), x1 = pack4(x.b);
       T *const o = own + (head - G) * HD + j, *const c = cache[head - G] + at + j;
@@ -450,7 +424,7 @@ __global__ __launch_bounds__(HD) void attn_combine_kernel(AttnArgs a) {
 // ---- matrix-core path for the bulk region (bf16 storage) -----------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
+
 
 // x = hi + lo with hi, lo bf16: the pair keeps ~16 mantissa bits of an fp32 value.
 __device__ __forceinline__ void split8(const float (&x)[8], u32x4_t &hi, u32x4_t &lo) {
@@ -467,36 +441,13 @@ __device__ __forceinline__ f32x16_t mfma_bf16(const u32x4_t &a, const u32x4_t &b
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// Value rows in the LDS: HD * 2 bytes a row, its 64-byte chunks permuted by the row so that the four rows a column read takes at a time
-// lie in different banks.
-template <int HD> __device__ __forceinline__ int value_chunk(int row, int chunk) { return chunk ^ (HD == 128 ? row & 3 : (row >> 1) & 1); }
-template <int HD> __device__ __forceinline__ int value_piece(int row, int piece) { return row * HD * 2 + value_chunk<HD>(row, piece >> 2) * 64 + (piece & 3) * 16; }
-// V^T fragments (A operand) out of them, by the LDS's transposing read (of the 4 x 16 matrix of 16-bit values whose row r the lanes 4 r .. 4 r + 3 of
-// sixteen point at, lane i gets column i): lane (c, g) has dim db * 32 + c at keys first + 4 g + {0 .. 3, 8 .. 11}.
-template <int HD> __device__ __forceinline__ int value_lane(int lane) {   // for db = 0, first = 0; db: ^ 64 db, first: a multiple of 16 rows further on
-  const int row = 4 * (lane >> 5) + ((lane & 15) >> 2);
-  return row * HD * 2 + value_chunk<HD>(row, 0) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
-}
-typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-__device__ __forceinline__ u32x2_t read_columns(const unsigned char *p) {
-  return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)p));
-}
-template <int HD> __device__ __forceinline__ u32x4_t value_fragment(const unsigned char *v_lds, int at, int db, int first) {
-  const unsigned char *p = v_lds + (at ^ 64 * db) + first * HD * 2;
-  const u32x2_t v0 = read_columns(p), v1 = read_columns(p + 8 * HD * 2);
-  return u32x4_t{v0.x, v0.y, v1.x, v1.y};
-}
 // four floats at a 4-byte aligned address in one store
 __device__ __forceinline__ void store4_any(float *p, float a, float b, float c, float d) {
   typedef __attribute__((ext_vector_type(4), aligned(4))) float f4_t;
   *(f4_t *)p = f4_t{a, b, c, d};
 }
 
-// Maximum and sum over the lanes l and l ^ 32, in both, without the LDS round trip of a shuffle
-__device__ __forceinline__ float max_halves(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
+// Sum over the lanes l and l ^ 32, in both (max_halves)
 __device__ __forceinline__ float sum_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -651,7 +602,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       constexpr int per_head = HD / 8;
       for (int e = tid; e < a.rows * G * per_head; e += NT) { // (rows * G <= kRawQueries)
         const int query = e / per_head, j = e % per_head * 4;
-        const RawPlanes x = raw_planes(a.raw, query / G, (hk * G + query % G) * HD + j, HD / 2, j, true);
+        const RotaryPlanes x = raw_planes(a.raw, query / G, (hk * G + query % G) * HD + j, HD / 2, j, true);
         *(f32x4_t *)((float *)lds + query * HD + j) = x.a;
         *(f32x4_t *)((float *)lds + query * HD + j + HD / 2) = x.b;
       }
@@ -739,16 +690,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   for (int db = 0; db < DB; db++)
 #pragma unroll
     for (int v = 0; v < 16; v += 4) store4_any(dst + 2 + db * 32 + 2 * v + 4 * g, o[db][v], o[db][v + 1], o[db][v + 2], o[db][v + 3]);
-}
-
-// Dynamic LDS beyond 64 KB, once per device: the attribute belongs to the device's copy of the code.
-static hipError_t allow_lds(const void *kernel, int bytes, bool (&done)[64]) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess || (dev >= 0 && dev < 64 && done[dev])) return e;
-  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess && dev >= 0 && dev < 64) done[dev] = true;
-  return e;
 }
 
 template <int HD, int G, int NW>

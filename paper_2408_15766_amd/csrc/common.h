@@ -152,6 +152,45 @@ __device__ __forceinline__ int key_rank(const uint64_t *keys, int n2, uint64_t k
   return rank;
 }
 
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
+
+// Dynamic LDS beyond 64 KB, once per device: the attribute belongs to the device's copy of the code.
+inline hipError_t allow_lds(const void *kernel, int bytes, bool (&done)[64]) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess || (dev >= 0 && dev < 64 && done[dev])) return e;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess && dev >= 0 && dev < 64) done[dev] = true;
+  return e;
+}
+
+// ---- shared by the attention kernels ----
+// Maximum over the lanes l and l ^ 32, in both, without the LDS round trip of a shuffle
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// Value rows in the LDS: HD * 2 bytes a row, its 64-byte chunks permuted by the row so that the four rows a column read takes at a time
+// lie in different banks.
+template <int HD> __device__ __forceinline__ int value_chunk(int row, int chunk) { return chunk ^ (HD == 128 ? row & 3 : (row >> 1) & 1); }
+template <int HD> __device__ __forceinline__ int value_piece(int row, int piece) { return row * HD * 2 + value_chunk<HD>(row, piece >> 2) * 64 + (piece & 3) * 16; }
+// V^T fragments (A operand) out of them, by the LDS's transposing read (of the 4 x 16 matrix of 16-bit values whose row r the lanes 4 r .. 4 r + 3 of
+// sixteen point at, lane i gets column i): lane (c, g) has dim db * 32 + c at keys first + 4 g + {0 .. 3, 8 .. 11}.
+template <int HD> __device__ __forceinline__ int value_lane(int lane) {   // for db = 0, first = 0; db: ^ 64 db, first: a multiple of 16 rows further on
+  const int row = 4 * (lane >> 5) + ((lane & 15) >> 2);
+  return row * HD * 2 + value_chunk<HD>(row, 0) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+}
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+__device__ __forceinline__ u32x2_t read_columns(const unsigned char *p) {
+  return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)p));
+}
+template <int HD> __device__ __forceinline__ u32x4_t value_fragment(const unsigned char *v_lds, int at, int db, int first) {
+  const unsigned char *p = v_lds + (at ^ 64 * db) + first * HD * 2;
+  const u32x2_t v0 = read_columns(p), v1 = read_columns(p + 8 * HD * 2);
+  return u32x4_t{v0.x, v0.y, v1.x, v1.y};
+}
+
 // ---- merge of an attention's parts ----
 // Scores are kept in units of log2: the launch's scale holds 1/sqrt(hd) * log2(e), and every weight is a power of two taken by the hardware.
 __device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -199,6 +238,35 @@ __device__ __forceinline__ float2 rope_entry(int pos, int j, int half, double lo
   double s, c;
   sincos(ang, &s, &c);
   return make_float2((float)c, (float)s);
+}
+
+// Four rotary planes (a: their first dims, b: their partners `half` further on) of a row from the projection's partial sums p; rope: the planes' (cos, sin).  Not
+// turned: the sums alone.  All loads first, up to NS splits (absent ones read split 0 again and are left out).
+struct RotaryPlanes { f32x4_t a, b; };
+template <int NS>
+__device__ __forceinline__ RotaryPlanes rotary_planes(const float *p, int n_split, size_t split_stride, const float2 *rope, int half, bool turned) {
+  const f32x4_t *cs = (const f32x4_t *)rope;
+  const f32x4_t cs0 = cs[0], cs1 = cs[1];                     // of planes j, j + 1 and j + 2, j + 3
+  f32x4_t pa[NS], pb[NS];
+#pragma unroll
+  for (int s = 0; s < NS; s++) {
+    const float *q = p + (size_t)(s < n_split ? s : 0) * split_stride;
+    pa[s] = *(const f32x4_t *)q; pb[s] = *(const f32x4_t *)(q + half);
+  }
+  RotaryPlanes x{pa[0], pb[0]};
+#pragma unroll
+  for (int s = 1; s < NS; s++)
+    if (s < n_split) { x.a += pa[s]; x.b += pb[s]; }
+  for (int s = NS; s < n_split; s++) { x.a += *(const f32x4_t *)(p + (size_t)s * split_stride); x.b += *(const f32x4_t *)(p + (size_t)s * split_stride + half); }
+  if (turned) {
+    const float2 c[4] = {{cs0.x, cs0.y}, {cs0.z, cs0.w}, {cs1.x, cs1.y}, {cs1.z, cs1.w}};
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float u = rope_first(x.a[e], x.b[e], c[e]), v = rope_second(x.a[e], x.b[e], c[e]);
+      x.a[e] = u; x.b[e] = v;
+    }
+  }
+  return x;
 }
 
 // Block-wide sum for blocks of up to 16 waves; `sh` needs 16 floats.  Fixed order.

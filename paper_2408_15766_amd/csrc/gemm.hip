@@ -1265,10 +1265,7 @@ static hipError_t launch_f32(const GemmArgs &a, hipStream_t st, const GemmHead *
   if (tiles > 65535) return hipErrorInvalidValue;
   return launch_f32_small<kHeadNone>(a, tiles, NoHead{}, st);
 }
-// Whether a launch makes its own x: launches of gemm_f32_kernel over one set of up to 128 rows.  Rows of up to 256 columns always (us, two layers and their
-// draft, 256 wide, launches of their own / this: draft of 4-row passes 157 / 139, of 10 367 / 342, of 16 507 / 480; verify and accept of 16 rows 97 / 91,
-// 60 97 / 95, 128 107.5 / 105.5); of up to 512 with at most three rows a wavefront (512 wide: drafts of 4 rows 169.5 / 163, of 10 394 / 390, of 16 525 / 528; verify of one
-// row 93.7 / 92, of 16 101.5 / 108, 60 109.5 / 115.5, 128 125.5 / 130).
+// One bf16 row: its K range in the LDS, sums of a row that eight wavefronts hold in registers, or an attention's parts (gemm_row_kernel's comment has both sides).
 static bool row_takes_head(const GemmArgs &a, const GemmHead &h) {
   if (a.m != 1 || a.x2 != nullptr || a.fold || a.n_split < 1) return false;
   const int slabs = (a.in + gemm_k_per_slab(1) - 1) / gemm_k_per_slab(1);
@@ -1278,6 +1275,10 @@ static bool row_takes_head(const GemmArgs &a, const GemmHead &h) {
   return h.kind == kHeadSums && a.in == h.d && h.d % 4 == 0 && h.d <= kRowMaxCols && h.ldp % 4 == 0 && h.n_split >= 1 && (low & 15) == 0 &&
          ((uintptr_t)h.norm_w & 7) == 0;
 }
+// Whether a launch makes its own x: one bf16 row, and launches of gemm_f32_kernel over one set of up to 128 rows.  Rows of up to 256 columns always (us, two layers and their
+// draft, 256 wide, launches of their own / this: draft of 4-row passes 157 / 139, of 10 367 / 342, of 16 507 / 480; verify and accept of 16 rows 97 / 91,
+// 60 97 / 95, 128 107.5 / 105.5); of up to 512 with at most three rows a wavefront (512 wide: drafts of 4 rows 169.5 / 163, of 10 394 / 390, of 16 525 / 528; verify of one
+// row 93.7 / 92, of 16 101.5 / 108, 60 109.5 / 115.5, 128 125.5 / 130).
 bool gemm_takes_head(int dtype, const GemmArgs &a, const GemmHead &h) {
   if (dtype == 1) return row_takes_head(a, h);
   if (h.kind == kHeadParts) return false;

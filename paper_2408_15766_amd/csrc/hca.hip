@@ -27,8 +27,6 @@ namespace spec {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
@@ -40,12 +38,6 @@ __device__ __forceinline__ f32x16_t mfma16(const u32x4_t &a, const u32x4_t &b, f
 }
 __device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// Maximum over the lanes l and l ^ 32, in both, without the LDS round trip of a shuffle.
-__device__ __forceinline__ float max_halves(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
 
 template <int HD, int WAVES> struct HcaLds {
   static constexpr int kstr = HD * 2 + 16;              // bytes per staged key row (+16: conflict-free b128 reads)
@@ -408,12 +400,6 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 // streams 51.7 -> 33.2 us (hca_attention_kernel / this); 333 positions, 16 heads of 64, two streams 9.8 -> 7.1.  Wavefronts with a softmax of their own that merge at the end need no
 // rounds, 25.5 and 6.0, but add up in another order: a sequence then differed by rounding (1.6e-3) with the number of sequences and heads beside it.
 // Eight wavefronts in halves: 31.9 and 6.9, 256 positions of 32 heads 7.3 -> 8.2.
-typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-// Value rows in the LDS, HD * 2 bytes each; the 64-byte chunks are permuted by the row so that the four rows of a column read lie in different banks.
-template <int HD> __device__ __forceinline__ int value_chunk(int row, int chunk) { return chunk ^ (HD == 128 ? row & 3 : (row >> 1) & 1); }
-__device__ __forceinline__ u32x2_t read_columns(const unsigned char *p) {
-  return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)p));
-}
 // (each rounded by itself: hca_attention_kernel multiplies in a branch of its own)
 __device__ __forceinline__ float turn_add(float l, float turn, float ls) {
 #pragma clang fp contract(off)
@@ -509,8 +495,7 @@ __global__ __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_e
 #pragma unroll
   for (int v = 0; v < 16; v++) o[v] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
-  const int vrow = 4 * g + ((lane & 15) >> 2);                // a lane's place in a column read: row and 8 bytes of it
-  const int vcol = (vrow * HD * 2 + value_chunk<HD>(vrow, 0) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8) ^ 64 * wave;
+  const int vlane = value_lane<HD>(lane);
   for (int b0 = 0, set = 0; b0 < nb; b0 += W, set ^= 1) {
     const int blk = b0 + wave;
     const bool live = blk < nb;
@@ -573,7 +558,7 @@ __global__ __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_e
 #pragma unroll
       for (int e = 0; e < VP; e++) {
         const int idx = lane + 64 * e, row = idx / PPR, piece = idx % PPR;
-        *(u32x4_t *)(vals + row * HD * 2 + value_chunk<HD>(row, piece >> 2) * 64 + (piece & 3) * 16) = vr[e];
+        *(u32x4_t *)(vals + value_piece<HD>(row, piece)) = vr[e];
       }
 #pragma unroll
       for (int st = 0; st < 4; st++) *(u32x4_t *)(probs + st * 1024) = u32x4_t{pk[4 * st], pk[4 * st + 1], pk[4 * st + 2], pk[4 * st + 3]};
@@ -584,14 +569,12 @@ __global__ __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_e
     for (int j = 0; j < W; j++) {
       if (b0 + j >= nb) break;
       l_run = turn_add(l_run, corr[j], sum_sh[(set * W + j) * 64 + lane]);
-      const unsigned char *const vals = lds + j * L::vals + vcol, *const probs = lds + L::probs0 + j * L::probs + lane * 16;
+      const unsigned char *const vals = lds + j * L::vals, *const probs = lds + L::probs0 + j * L::probs + lane * 16;
 #pragma unroll
       for (int v = 0; v < 16; v++) o[v] *= corr[j];
 #pragma unroll
-      for (int st = 0; st < 4; st++) {                        // 16 keys: V^T fragment (A operand) of dims 32 wave + c at keys 16 st + 4 g + {0..3, 8..11}
-        const u32x2_t v0 = read_columns(vals + 16 * st * HD * 2), v1 = read_columns(vals + (16 * st + 8) * HD * 2);
-        o = mfma16(u32x4_t{v0.x, v0.y, v1.x, v1.y}, *(const u32x4_t *)(probs + st * 1024), o);
-      }
+      for (int st = 0; st < 4; st++)                          // 16 keys
+        o = mfma16(value_fragment<HD>(vals, vlane, wave, 16 * st), *(const u32x4_t *)(probs + st * 1024), o);
     }
   }
   if (nb == 0) __syncthreads();                               // the band is there
@@ -662,15 +645,9 @@ bool split_pays(int hd, int seq, int streams, long long workgroups) {
 template <int HD, int WAVES>
 hipError_t launch_waves(const HcaArgs &a, hipStream_t st) {
   constexpr int kLds = HcaLds<HD, WAVES>::total;
-  static bool attr_done[64] = {};                             // per device: the attribute belongs to the device's copy of the code
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  static bool lds_allowed[64] = {};
+  const hipError_t e = allow_lds((const void *)hca_attention_kernel<HD, WAVES>, kLds, lds_allowed);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64 || !attr_done[dev]) {
-    e = hipFuncSetAttribute((const void *)hca_attention_kernel<HD, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-    if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < 64) attr_done[dev] = true;
-  }
   const int G = a.hq / a.hkv;
   const int n_qt = (a.seq + WAVES * 32 - 1) / (WAVES * 32);
   const long long grid = (long long)a.batch * a.hkv * G * n_qt;
@@ -683,15 +660,9 @@ template <int HD>
 hipError_t launch_split(const HcaArgs &a, hipStream_t st) {
   using L = SplitLds<HD>;
   static_assert(L::total(kMaxStreams) <= 160 * 1024, "the LDS of a compute unit");
-  static bool attr_done[64] = {};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  static bool lds_allowed[64] = {};
+  const hipError_t e = allow_lds((const void *)hca_split_kernel<HD>, L::total(kMaxStreams), lds_allowed);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64 || !attr_done[dev]) {
-    e = hipFuncSetAttribute((const void *)hca_split_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, L::total(kMaxStreams));
-    if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < 64) attr_done[dev] = true;
-  }
   const long long grid = (long long)a.batch * a.hq * ((a.seq + 31) / 32);
   if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
   hipLaunchKernelGGL(hca_split_kernel<HD>, dim3((unsigned)grid), dim3(kSplitWaves * 64), L::total(a.n_streams), st, a);

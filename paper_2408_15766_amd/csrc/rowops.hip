@@ -217,38 +217,15 @@ __global__ __launch_bounds__(kRowThreads) void reduce_rope_kv_kernel(const float
   const int col = head * hd + j;
   const int sl = slot[i];
   const bool turned = head < hq + hkv;
-  const f32x4_t *cs = (const f32x4_t *)(rope + (size_t)i * half + j);
-  const f32x4_t cs0 = cs[0], cs1 = cs[1];                     // (cos, sin) of planes j, j + 1 and j + 2, j + 3
-  f32x4_t pa[NS], pb[NS];
-#pragma unroll
-  for (int s = 0; s < NS; s++) {
-    const float *p = part + ((size_t)(s < n_split ? s : 0) * m_pad + i) * ldp + col;
-    pa[s] = *(const f32x4_t *)p; pb[s] = *(const f32x4_t *)(p + half);
-  }
-  f32x4_t a = pa[0], b = pb[0];
-#pragma unroll
-  for (int s = 1; s < NS; s++)
-    if (s < n_split) { a += pa[s]; b += pb[s]; }
-  for (int s = NS; s < n_split; s++) {
-    const float *p = part + ((size_t)s * m_pad + i) * ldp + col;
-    a += *(const f32x4_t *)p; b += *(const f32x4_t *)(p + half);
-  }
-  if (turned) {
-    const float2 c[4] = {{cs0.x, cs0.y}, {cs0.z, cs0.w}, {cs1.x, cs1.y}, {cs1.z, cs1.w}};
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const float x = rope_first(a[e], b[e], c[e]), y = rope_second(a[e], b[e], c[e]);
-      a[e] = x; b[e] = y;
-    }
-  }
+  const RotaryPlanes x = rotary_planes<NS>(part + (size_t)i * ldp + col, n_split, (size_t)m_pad * ldp, rope + (size_t)i * half + j, half, turned);
   if (head < hq) {                                     // query head: kept in fp32, it is read once and never cached
     float *dst = q + ((size_t)i * hq + head) * hd + j;
-    store4<float>(dst, a);
-    store4<float>(dst + half, b);
+    store4<float>(dst, x.a);
+    store4<float>(dst + half, x.b);
   } else {                                             // (a value head is stored as it is)
     T *dst = (turned ? kcache + ((size_t)sl * hkv + (head - hq)) * hd : vcache + ((size_t)sl * hkv + (head - hq - hkv)) * hd) + j;
-    store4<T>(dst, a);
-    store4<T>(dst + half, b);
+    store4<T>(dst, x.a);
+    store4<T>(dst + half, x.b);
   }
 }
 
