@@ -218,14 +218,15 @@ def test_ruled_out_tokens_in_the_tiled_head(env, rows, value, factor):
         assert np.isnan(got_ce).all()                          # 0 * -inf, as the definition has it
 
 
-@pytest.mark.parametrize("d,vocab", [(512, 9000), (132, 32000), (64, 1000)])
-def test_fp32_losses_of_a_position_have_the_same_bits_in_any_call(env, d, vocab):
-    # few positions and many, whole chunks of 512 and short ones: three ways of the LM head, whose sums run in the same order
+@pytest.mark.parametrize("dtype,d,vocab", [("fp32", 512, 9000), ("fp32", 132, 32000), ("fp32", 64, 1000), ("bf16", 1096, 33000), ("bf16", 136, 9000)])
+def test_losses_of_a_position_have_the_same_bits_in_any_call(env, dtype, d, vocab):
+    # few positions and many, whole chunks of 512 and short ones (bf16: 188 rows a side join at 33000 tokens): the ways of the LM head add up a logit in the same order
     torch, P = env
-    ft, fd, w = wl.make_distill_inputs(41, 520, d, vocab, "fp32")
-    topk, ce, _ = run_gpu(torch, P, ft, fd, w, 10, "fp32")
-    for lo, hi in ((0, 1), (100, 116), (0, 33), (391, 520), (512, 520)):
-        a, b, _ = run_gpu(torch, P, np.ascontiguousarray(ft[lo:hi]), np.ascontiguousarray(fd[lo:hi]), w, 10, "fp32")
+    rows = 520 if dtype == "fp32" else 700
+    ft, fd, w = wl.make_distill_inputs(41, rows, d, vocab, dtype)
+    topk, ce, _ = run_gpu(torch, P, ft, fd, w, 10, dtype)
+    for lo, hi in ((0, 1), (100, 116), (0, 33), (30, 94), (391, 520), (512, 520), (512, rows)):
+        a, b, _ = run_gpu(torch, P, np.ascontiguousarray(ft[lo:hi]), np.ascontiguousarray(fd[lo:hi]), w, 10, dtype)
         assert np.array_equal(a, topk[lo:hi]) and np.array_equal(b, ce[lo:hi])
 
 
